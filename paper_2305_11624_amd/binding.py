@@ -1,6 +1,7 @@
-"""ctypes binding of libconvbn.so: same entry-point names as include/convbn.h.
+"""Binding of libconvbn.so: same entry-point names as include/convbn.h.
 
-Argument marshalling only -- every step of the block runs in the library's HIP kernels.
+The block calls go through the extension `_call` (csrc/py_call.cpp), which turns tensors into pointers natively; the
+rest through ctypes.  Argument marshalling only -- every step of the block runs in the library's HIP kernels.
 PyTorch supplies device memory and the stream.  There is no fallback: if the compiled
 library is missing this module raises on first use.
 """
@@ -12,6 +13,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libconvbn.so")
+CALL_PATH = os.path.join(_HERE, "_call.so")
 
 OK, ERR_NULL, ERR_SHAPE, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_LAUNCH = range(6)
 F32, BF16 = 0, 1
@@ -66,15 +68,31 @@ class ConvBNError(RuntimeError):
 
 
 _lib = None
+_call = _at = _NO_WS = None   # the extension's `call`, the entry points' addresses by name, its "no workspace" marker
+_pointer = _stream_handle = None
+
+
+class _Addresses:
+    """Addresses of the library's entry points as attributes."""
+
+    def __init__(self, L):
+        for name in EXPORTS:
+            setattr(self, name, C.cast(getattr(L, name), C.c_void_p).value)
+
+
+def _load():
+    lib()
+    return _call
 
 
 def lib():
     """The loaded library.  Raises if it has not been built (no silent fallback)."""
-    global _lib
+    global _lib, _call, _at, _NO_WS, _pointer, _stream_handle
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
+        missing = [p for p in (LIB_PATH, CALL_PATH) if not os.path.exists(p)]
+        if missing:
             raise ImportError(
-                f"{LIB_PATH} is missing: build it with `python -m paper_2305_11624_amd.build` "
+                f"{', '.join(missing)} missing: build it with `python -m paper_2305_11624_amd.build` "
                 "(hipcc, gfx950).  This package has no CPU or PyTorch fallback.")
         L = C.CDLL(LIB_PATH)
         vp, fp = C.c_void_p, C.c_void_p
@@ -175,6 +193,9 @@ def lib():
         L.convbn_tune_fwd_static.argtypes = [dp, vp, vp, fp, fp, fp, fp, fp, vp, vp, vp]
         L.convbn_static_workspace_limit.restype = C.c_size_t
         L.convbn_static_workspace_limit.argtypes = []
+        from . import _call as ext
+        _call, _NO_WS, _pointer, _stream_handle = ext.call, ext.NO_WS, ext.pointer, ext.stream
+        _at = _Addresses(L)
         _lib = L
     return _lib
 
@@ -206,20 +227,18 @@ def torch_dtype(desc: Desc):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
+    return _pointer(t)   # (AssertionError for anything but a dense device tensor, an address or None)
+
+
+def _handle(stream):
+    """A stream argument as the extension takes it: None (the current stream) or a raw handle."""
+    if stream is None:
         return None
-    if isinstance(t, int):
-        return C.c_void_p(t)
-    assert t.is_cuda and t.is_contiguous(), "device, dense tensors only"
-    return C.c_void_p(t.data_ptr())
+    return stream.cuda_stream if isinstance(stream, torch.cuda.Stream) else int(stream)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    if isinstance(stream, torch.cuda.Stream):
-        return C.c_void_p(stream.cuda_stream)
-    return C.c_void_p(int(stream))
+    return _stream_handle(_handle(stream))
 
 
 def _check(status: int):
@@ -247,27 +266,19 @@ def convbn_saved_bytes(desc: Desc, mode: int, refold: bool = False) -> int:
     return lib().convbn_saved_bytes(C.byref(desc), mode, int(refold))
 
 
-def _ws(ws):
-    if ws is None:
-        return None, 0
-    return _ptr(ws), ws.numel() * ws.element_size()
-
-
 def convbn_tune_fwd(desc, x, W, b, gamma, beta, mean, var, z, w_folded, ws, stream=None,
                     check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_tune_fwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta),
-                               _ptr(mean), _ptr(var), _ptr(z), _ptr(w_folded), p, n,
-                               _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tune_fwd, desc, None, x, W, b, gamma, beta, mean, var, z, w_folded, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_tune_fwd_static(desc, x, W, b, gamma, beta, mean, var, z, w_folded, stream=None, check=True):
-    st = lib().convbn_tune_fwd_static(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta),
-                                      _ptr(mean), _ptr(var), _ptr(z), _ptr(w_folded), _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tune_fwd_static, desc, None, x, W, b, gamma, beta, mean, var, z, w_folded,
+                            _NO_WS, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
@@ -278,43 +289,36 @@ def convbn_static_workspace_limit() -> int:
 
 def convbn_tune_bwd(desc, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db, dgamma, dbeta, ws,
                     stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_tune_bwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(mean),
-                               _ptr(var), _ptr(w_folded), _ptr(dz), _ptr(dx), _ptr(dW), _ptr(db),
-                               _ptr(dgamma), _ptr(dbeta), p, n, _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tune_bwd, desc, None, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db,
+                            dgamma, dbeta, ws, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_eval_fwd(desc, x, W, b, gamma, beta, mean, var, z, y_saved, ws, stream=None,
                     check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_eval_fwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta),
-                               _ptr(mean), _ptr(var), _ptr(z), _ptr(y_saved), p, n,
-                               _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_eval_fwd, desc, None, x, W, b, gamma, beta, mean, var, z, y_saved, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_eval_bwd(desc, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma, dbeta, ws,
                     stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_eval_bwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(mean),
-                               _ptr(var), _ptr(y_saved), _ptr(dz), _ptr(dx), _ptr(dW), _ptr(db),
-                               _ptr(dgamma), _ptr(dbeta), p, n, _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_eval_bwd, desc, None, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma,
+                            dbeta, ws, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_fold(desc, W, b, gamma, beta, mean, var, w_fprop, w_folded, b_folded, stream=None,
                 check=True):
-    st = lib().convbn_fold(C.byref(desc), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta), _ptr(mean),
-                           _ptr(var), _ptr(w_fprop), _ptr(w_folded), _ptr(b_folded),
-                           _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_fold, desc, None, W, b, gamma, beta, mean, var, w_fprop, w_folded, b_folded,
+                            _NO_WS, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
@@ -387,23 +391,20 @@ def convbn_conv_workspace_bytes(desc, pass_: int) -> int:
 
 
 def convbn_conv_fprop(desc, x, w, bias, z, ws=None, stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_conv_fprop(C.byref(desc), _ptr(x), _ptr(w), _ptr(bias), _ptr(z), p, n,
-                                 _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_conv_fprop, desc, None, x, w, bias, z, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_conv_dgrad(desc, dz, w_t, dx, ws=None, stream=None, check=True, x_mask=None):
-    p, n = _ws(ws)
+    h = None if stream is None else _handle(stream)
     if x_mask is not None:
-        st = lib().convbn_conv_dgrad_masked(C.byref(desc), _ptr(dz), _ptr(w_t), _ptr(x_mask), _ptr(dx), p, n,
-                                            _stream(stream))
+        st = (_call or _load())(_at.convbn_conv_dgrad_masked, desc, None, dz, w_t, x_mask, dx, ws, h)
     else:
-        st = lib().convbn_conv_dgrad(C.byref(desc), _ptr(dz), _ptr(w_t), _ptr(dx), p, n,
-                                     _stream(stream))
-    if check:
+        st = (_call or _load())(_at.convbn_conv_dgrad, desc, None, dz, w_t, dx, ws, h)
+    if st and check:
         _check(st)
     return st
 
@@ -417,20 +418,18 @@ def convbn_rsum_parts(desc) -> int:
 
 
 def convbn_conv_wgrad(desc, x, dz, dw_part, r_part, ws=None, stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_conv_wgrad(C.byref(desc), _ptr(x), _ptr(dz), _ptr(dw_part), _ptr(r_part), p, n,
-                                 _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_conv_wgrad, desc, None, x, dz, dw_part, r_part, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_fold_back(desc, dw_part, r_part, W, b, gamma, mean, var, dW, db, dgamma, dbeta,
                      stream=None, check=True):
-    st = lib().convbn_fold_back(C.byref(desc), _ptr(dw_part), _ptr(r_part), _ptr(W), _ptr(b),
-                                _ptr(gamma), _ptr(mean), _ptr(var), _ptr(dW), _ptr(db),
-                                _ptr(dgamma), _ptr(dbeta), _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_fold_back, desc, None, dw_part, r_part, W, b, gamma, mean, var, dW, db, dgamma,
+                            dbeta, _NO_WS, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
@@ -480,51 +479,44 @@ def convbn_tconv_saved_bytes(desc: Desc, mode: int, refold: bool = False) -> int
 
 
 def convbn_tconv_eval_fwd(desc, x, W, b, gamma, beta, mean, var, z, y_saved, ws, stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_tconv_eval_fwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta),
-                                     _ptr(mean), _ptr(var), _ptr(z), _ptr(y_saved), p, n, _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tconv_eval_fwd, desc, None, x, W, b, gamma, beta, mean, var, z, y_saved, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_tconv_eval_bwd(desc, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma, dbeta, ws,
                           stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_tconv_eval_bwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(mean),
-                                     _ptr(var), _ptr(y_saved), _ptr(dz), _ptr(dx), _ptr(dW), _ptr(db),
-                                     _ptr(dgamma), _ptr(dbeta), p, n, _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tconv_eval_bwd, desc, None, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db,
+                            dgamma, dbeta, ws, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_tconv_tune_fwd(desc, x, W, b, gamma, beta, mean, var, z, w_folded, ws, stream=None,
                           check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_tconv_tune_fwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta),
-                                     _ptr(mean), _ptr(var), _ptr(z), _ptr(w_folded), p, n,
-                                     _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tconv_tune_fwd, desc, None, x, W, b, gamma, beta, mean, var, z, w_folded, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_tconv_tune_bwd(desc, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db, dgamma, dbeta, ws,
                           stream=None, check=True):
-    p, n = _ws(ws)
-    st = lib().convbn_tconv_tune_bwd(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(mean),
-                                     _ptr(var), _ptr(w_folded), _ptr(dz), _ptr(dx), _ptr(dW), _ptr(db),
-                                     _ptr(dgamma), _ptr(dbeta), p, n, _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tconv_tune_bwd, desc, None, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db,
+                            dgamma, dbeta, ws, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_tune_fwd_scale_epilogue(desc, x, W, b, gamma, beta, mean, var, z, stream=None, check=True):
-    st = lib().convbn_tune_fwd_scale_epilogue(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta),
-                                              _ptr(mean), _ptr(var), _ptr(z), _stream(stream))
-    if check:
+    st = (_call or _load())(_at.convbn_tune_fwd_scale_epilogue, desc, None, x, W, b, gamma, beta, mean, var, z, _NO_WS,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
@@ -537,41 +529,39 @@ def convbn_dw_saved_bytes(desc: Desc, mode: int, refold: bool = False) -> int:
     return int(lib().convbn_dw_saved_bytes(C.byref(desc), mode, int(refold)))
 
 
-def _block_fwd(fn, desc, x, W, b, gamma, beta, mean, var, z, keep, ws, stream, check):
-    p, n = _ws(ws)
-    st = fn(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta), _ptr(mean), _ptr(var), _ptr(z),
-            _ptr(keep), p, n, _stream(stream))
-    if check:
+def _block_fwd(name, desc, x, W, b, gamma, beta, mean, var, z, keep, ws, stream, check):
+    st = (_call or _load())(getattr(_at, name), desc, None, x, W, b, gamma, beta, mean, var, z, keep, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
-def _block_bwd(fn, desc, x, W, b, gamma, mean, var, kept, dz, dx, dW, db, dgamma, dbeta, ws, stream, check):
-    p, n = _ws(ws)
-    st = fn(C.byref(desc), _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(mean), _ptr(var), _ptr(kept), _ptr(dz),
-            _ptr(dx), _ptr(dW), _ptr(db), _ptr(dgamma), _ptr(dbeta), p, n, _stream(stream))
-    if check:
+def _block_bwd(name, desc, x, W, b, gamma, mean, var, kept, dz, dx, dW, db, dgamma, dbeta, ws, stream, check):
+    st = (_call or _load())(getattr(_at, name), desc, None, x, W, b, gamma, mean, var, kept, dz, dx, dW, db, dgamma,
+                            dbeta, ws, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_dw_tune_fwd(desc, x, W, b, gamma, beta, mean, var, z, w_folded, ws, stream=None, check=True):
-    return _block_fwd(lib().convbn_dw_tune_fwd, desc, x, W, b, gamma, beta, mean, var, z, w_folded, ws, stream, check)
+    return _block_fwd("convbn_dw_tune_fwd", desc, x, W, b, gamma, beta, mean, var, z, w_folded, ws, stream, check)
 
 
 def convbn_dw_tune_bwd(desc, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db, dgamma, dbeta, ws, stream=None,
                        check=True):
-    return _block_bwd(lib().convbn_dw_tune_bwd, desc, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db, dgamma,
+    return _block_bwd("convbn_dw_tune_bwd", desc, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db, dgamma,
                       dbeta, ws, stream, check)
 
 
 def convbn_dw_eval_fwd(desc, x, W, b, gamma, beta, mean, var, z, y_saved, ws, stream=None, check=True):
-    return _block_fwd(lib().convbn_dw_eval_fwd, desc, x, W, b, gamma, beta, mean, var, z, y_saved, ws, stream, check)
+    return _block_fwd("convbn_dw_eval_fwd", desc, x, W, b, gamma, beta, mean, var, z, y_saved, ws, stream, check)
 
 
 def convbn_dw_eval_bwd(desc, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma, dbeta, ws, stream=None,
                        check=True):
-    return _block_bwd(lib().convbn_dw_eval_bwd, desc, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma,
+    return _block_bwd("convbn_dw_eval_bwd", desc, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma,
                       dbeta, ws, stream, check)
 
 
@@ -585,43 +575,41 @@ def convbn_grouped_saved_bytes(desc: Desc, groups: int, mode: int, refold: bool 
     return int(lib().convbn_grouped_saved_bytes(C.byref(desc), groups, mode, int(refold)))
 
 
-def _gblock_fwd(fn, desc, groups, x, W, b, gamma, beta, mean, var, z, keep, ws, stream, check):
-    p, n = _ws(ws)
-    st = fn(C.byref(desc), groups, _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(beta), _ptr(mean), _ptr(var), _ptr(z),
-            _ptr(keep), p, n, _stream(stream))
-    if check:
+def _gblock_fwd(name, desc, groups, x, W, b, gamma, beta, mean, var, z, keep, ws, stream, check):
+    st = (_call or _load())(getattr(_at, name), desc, groups, x, W, b, gamma, beta, mean, var, z, keep, ws,
+                            None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
-def _gblock_bwd(fn, desc, groups, x, W, b, gamma, mean, var, kept, dz, dx, dW, db, dgamma, dbeta, ws, stream, check):
-    p, n = _ws(ws)
-    st = fn(C.byref(desc), groups, _ptr(x), _ptr(W), _ptr(b), _ptr(gamma), _ptr(mean), _ptr(var), _ptr(kept), _ptr(dz),
-            _ptr(dx), _ptr(dW), _ptr(db), _ptr(dgamma), _ptr(dbeta), p, n, _stream(stream))
-    if check:
+def _gblock_bwd(name, desc, groups, x, W, b, gamma, mean, var, kept, dz, dx, dW, db, dgamma, dbeta, ws, stream, check):
+    st = (_call or _load())(getattr(_at, name), desc, groups, x, W, b, gamma, mean, var, kept, dz, dx, dW, db, dgamma,
+                            dbeta, ws, None if stream is None else _handle(stream))
+    if st and check:
         _check(st)
     return st
 
 
 def convbn_grouped_tune_fwd(desc, groups, x, W, b, gamma, beta, mean, var, z, w_folded, ws, stream=None, check=True):
-    return _gblock_fwd(lib().convbn_grouped_tune_fwd, desc, groups, x, W, b, gamma, beta, mean, var, z, w_folded, ws,
+    return _gblock_fwd("convbn_grouped_tune_fwd", desc, groups, x, W, b, gamma, beta, mean, var, z, w_folded, ws,
                        stream, check)
 
 
 def convbn_grouped_tune_bwd(desc, groups, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db, dgamma, dbeta, ws,
                             stream=None, check=True):
-    return _gblock_bwd(lib().convbn_grouped_tune_bwd, desc, groups, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db,
+    return _gblock_bwd("convbn_grouped_tune_bwd", desc, groups, x, W, b, gamma, mean, var, w_folded, dz, dx, dW, db,
                        dgamma, dbeta, ws, stream, check)
 
 
 def convbn_grouped_eval_fwd(desc, groups, x, W, b, gamma, beta, mean, var, z, y_saved, ws, stream=None, check=True):
-    return _gblock_fwd(lib().convbn_grouped_eval_fwd, desc, groups, x, W, b, gamma, beta, mean, var, z, y_saved, ws,
+    return _gblock_fwd("convbn_grouped_eval_fwd", desc, groups, x, W, b, gamma, beta, mean, var, z, y_saved, ws,
                        stream, check)
 
 
 def convbn_grouped_eval_bwd(desc, groups, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db, dgamma, dbeta, ws,
                             stream=None, check=True):
-    return _gblock_bwd(lib().convbn_grouped_eval_bwd, desc, groups, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db,
+    return _gblock_bwd("convbn_grouped_eval_bwd", desc, groups, x, W, b, gamma, mean, var, y_saved, dz, dx, dW, db,
                        dgamma, dbeta, ws, stream, check)
 
 

@@ -67,7 +67,7 @@ convbn_status make_geom(const convbn_desc* d, Geom* g) {
   g->Min = d->N * d->Hin * d->Win;
   g->K = d->kH * d->kW * d->Cin;
   // the kernels index the fp32 partial copies of split sums with 32 bits as well
-  if (widest_partial_elems(*g, d->dtype) > lim)
+  if (planned<long long>(*g, d->dtype, [&] { return widest_partial_elems(*g, d->dtype); }) > lim)
     return fail(CONVBN_ERR_UNSUPPORTED, "a buffer of partial sums would have more than 2^31-1 elements");
   return CONVBN_OK;
 }

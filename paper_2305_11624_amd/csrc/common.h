@@ -3,7 +3,9 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <stddef.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "../../include/convbn.h"
 
@@ -144,6 +146,48 @@ inline hipError_t set_lds_limit_once(LdsLimitOnce& s, const void* kernel, int by
   std::call_once(s.once, [&] { s.err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
   return s.err;
 }
+// The launch plan of a problem depends on its sizes alone, and a block call asks for it several times (is the shape
+// taken, how much scratch, the launch itself): plans are worked out once per thread and problem and kept in a small
+// direct-mapped table, compared by the whole key.  A step of the transposed block spent about 20 us of host time on
+// planning, one of a deep 3x3 block about 15 us; a hit costs about 30 ns.
+template <class Key, class Val>
+class PlanTable {
+ public:
+  template <class F>
+  const Val& get(const Key& k, F&& compute) {
+    uint32_t h = 2166136261u;
+    uint32_t w[(sizeof(Key) + 3) / 4] = {};
+    memcpy(w, &k, sizeof(Key));
+    for (uint32_t v : w) h = (h ^ v) * 16777619u;
+    Slot& s = slots_[(h ^ (h >> 15)) % kSlots];
+    if (!s.used || memcmp(&s.key, &k, sizeof(Key)) != 0) {
+      s.val = compute();   // (first: a plan may look up plans of its own)
+      memcpy(&s.key, &k, sizeof(Key));
+      s.used = true;
+    }
+    return s.val;
+  }
+
+ private:
+  static constexpr int kSlots = 64;
+  struct Slot { bool used; Key key; Val val; };
+  Slot slots_[kSlots] = {};
+};
+// ... of a block's problem: everything up to K in Geom, and the element type
+struct GeomKey { int v[16]; int dtype; };
+inline GeomKey geom_key(const Geom& g, int dtype) {
+  static_assert(offsetof(Geom, K) == 15 * sizeof(int), "the sizes come first in Geom");
+  GeomKey k;
+  memcpy(k.v, &g, sizeof(k.v));
+  k.dtype = dtype;
+  return k;
+}
+template <class Val, class F>
+const Val& planned(const Geom& g, int dtype, F&& compute) {   // one table per place of use (F is its own type there)
+  static thread_local PlanTable<GeomKey, Val> table;
+  return table.get(geom_key(g, dtype), compute);
+}
+
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- launchers (each enqueues on `st`, returns the hipError of the launch) ----

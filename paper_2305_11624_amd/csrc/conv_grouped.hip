@@ -576,12 +576,22 @@ GcPlan gc_plan(int N, int C, int cg, int in_h, int in_w, int out_h, int out_w, i
   return pl;
 }
 
-GcPlan gc_fprop_plan(const Geom& g, int groups, int dtype, GcParams* p) {
+GcPlan gc_fprop_work_out(const Geom& g, int groups, int dtype, GcParams* p) {
   if (dtype != CONVBN_BF16 || g.Cin != g.Cout || g.sh > 2 || g.sw > 2) return GcPlan{false, 0, 0};
   return gc_plan(g.N, g.Cin, g.Cin / groups, g.Hin, g.Win, g.Hout, g.Wout, g.kH, g.kW, g.sh, g.sw, g.ph, g.pw, p);
 }
+GcPlan gc_fprop_plan(const Geom& g, int groups, int dtype, GcParams* p) {
+  struct Known { GcPlan pl; GcParams p; };
+  const Known& k = planned<Known>(g, dtype + 4 * groups, [&] {
+    Known r;
+    r.pl = gc_fprop_work_out(g, groups, dtype, &r.p);
+    return r;
+  });
+  *p = k.p;
+  return k.pl;
+}
 // stride 1 only: dX is the forward kernel on dZ with the window reversed and padding k - 1 - p
-GcPlan gc_dgrad_plan(const Geom& g, int groups, int dtype, GcParams* p) {
+GcPlan gc_dgrad_work_out(const Geom& g, int groups, int dtype, GcParams* p) {
   if (dtype != CONVBN_BF16 || g.Cin != g.Cout || g.sh != 1 || g.sw != 1 || g.ph > g.kH - 1 || g.pw > g.kW - 1)
     return GcPlan{false, 0, 0};
   GcPlan pl = gc_plan(g.N, g.Cin, g.Cin / groups, g.Hout, g.Wout, g.Hin, g.Win, g.kH, g.kW, 1, 1, g.kH - 1 - g.ph,
@@ -590,6 +600,16 @@ GcPlan gc_dgrad_plan(const Geom& g, int groups, int dtype, GcParams* p) {
   p->mode = 1;
   for (int t = 0; t < g.kH * g.kW; ++t) p->tapw[t] = g.kH * g.kW - 1 - t;
   return pl;
+}
+GcPlan gc_dgrad_plan(const Geom& g, int groups, int dtype, GcParams* p) {
+  struct Known { GcPlan pl; GcParams p; };
+  const Known& k = planned<Known>(g, dtype + 4 * groups, [&] {
+    Known r;
+    r.pl = gc_dgrad_work_out(g, groups, dtype, &r.p);
+    return r;
+  });
+  *p = k.p;
+  return k.pl;
 }
 // One dimension of a strided input gradient: the input positions h = s a + q (residue class q) read dZ positions
 // a + d - t through window rows i0 + s t (those below k).  With T the largest number of taps of any class, every
@@ -612,7 +632,7 @@ int gc_class_taps(int s, int pad, int k) {   // most taps a class has
   return T;
 }
 // dX of a strided block: the forward kernel on dZ, one residue class of input positions per blockIdx.y
-GcPlan gc_dgrad_strided_plan(const Geom& g, int groups, int dtype, GcParams* p) {
+GcPlan gc_dgrad_strided_work_out(const Geom& g, int groups, int dtype, GcParams* p) {
   if (dtype != CONVBN_BF16 || g.Cin != g.Cout || (g.sh == 1 && g.sw == 1) || g.sh > 2 || g.sw > 2) return GcPlan{false, 0, 0};
   const int Th = gc_class_taps(g.sh, g.ph, g.kH), Tw = gc_class_taps(g.sw, g.pw, g.kW);
   GcPlan pl = gc_plan(g.N, g.Cin, g.Cin / groups, g.Hout, g.Wout, ceil_div(g.Hin, g.sh), ceil_div(g.Win, g.sw), Th, Tw, 1, 1,
@@ -636,6 +656,16 @@ GcPlan gc_dgrad_strided_plan(const Geom& g, int groups, int dtype, GcParams* p) 
         }
     }
   return pl;
+}
+GcPlan gc_dgrad_strided_plan(const Geom& g, int groups, int dtype, GcParams* p) {
+  struct Known { GcPlan pl; GcParams p; };
+  const Known& k = planned<Known>(g, dtype + 4 * groups, [&] {
+    Known r;
+    r.pl = gc_dgrad_strided_work_out(g, groups, dtype, &r.p);
+    return r;
+  });
+  *p = k.p;
+  return k.pl;
 }
 
 hipError_t gc_launch(const GcPlan& pl, const GcParams& p, hipStream_t st) {
@@ -846,7 +876,7 @@ __global__ __launch_bounds__(256) void g_wgrad_mfma_kernel(GwParams p) {
 }
 
 struct GwPlan { bool ok; size_t lds; int grid; };
-GwPlan gw_plan(const Geom& g, int groups, int dtype, GwParams* pp) {
+GwPlan gw_work_out(const Geom& g, int groups, int dtype, GwParams* pp) {
   GwPlan pl{false, 0, 0};
   GwParams& p = *pp;
   p = GwParams{};
@@ -906,6 +936,16 @@ GwPlan gw_plan(const Geom& g, int groups, int dtype, GwParams* pp) {
   pl.grid = workers * p.ncg;
   pl.ok = true;
   return pl;
+}
+GwPlan gw_plan(const Geom& g, int groups, int dtype, GwParams* pp) {
+  struct Known { GwPlan pl; GwParams p; };
+  const Known& k = planned<Known>(g, dtype + 4 * groups, [&] {
+    Known r;
+    r.pl = gw_work_out(g, groups, dtype, &r.p);
+    return r;
+  });
+  *pp = k.p;
+  return k.pl;
 }
 
 int direct_splits(const Geom& g, int cg) {

@@ -347,7 +347,7 @@ template <int NW, int CB> size_t plan_cfg(PwParams& p, int nch) {
   return 1024 + (size_t)NW * 4096 + p.wtile_bytes + (size_t)Cfg::NBUF * Cfg::SLOT;
 }
 
-PwPlan make_plan(PwParams& p) {
+PwPlan work_out_plan(PwParams& p) {
   PwPlan pl{false, 0, 0, 0};
   if (p.C % 16 || p.R % 8) return pl;
   if ((size_t)p.M * p.C * 2 >= OOB || (size_t)p.M * p.R * 2 >= OOB || (size_t)p.R * p.C * 2 >= OOB) return pl;
@@ -364,6 +364,18 @@ PwPlan make_plan(PwParams& p) {
       return pl;
     }
   return pl;
+}
+PwPlan make_plan(PwParams& p) {
+  struct Known { PwPlan pl; PwParams p; };
+  static thread_local PlanTable<PwParams, Known> table;
+  const Known& k = table.get(p, [&] {
+    Known r;
+    r.p = p;
+    r.pl = work_out_plan(r.p);
+    return r;
+  });
+  p = k.p;
+  return k.pl;
 }
 
 template <int NW, int NCH, int CB, bool SC = false>

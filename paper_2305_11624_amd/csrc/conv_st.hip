@@ -469,7 +469,7 @@ bool finish_plan(StParams& p, int kH, int kW) {
   return true;
 }
 
-bool fprop_params(const Geom& g, StParams* p) {
+bool fprop_work_out(const Geom& g, StParams* p) {
   StParams& q = *p;
   q = StParams{};
   if (g.sh != 1 || g.sw != 1) return false;
@@ -484,7 +484,7 @@ bool fprop_params(const Geom& g, StParams* p) {
   return finish_plan(q, g.kH, g.kW);
 }
 
-bool dgrad_params(const Geom& g, StParams* p) {
+bool dgrad_work_out(const Geom& g, StParams* p) {
   StParams& q = *p;
   q = StParams{};
   if (g.sh != 1 || g.sw != 1) return false;
@@ -498,6 +498,26 @@ bool dgrad_params(const Geom& g, StParams* p) {
   q.act_bytes = (unsigned)((size_t)g.M * g.Cout * 2);
   q.wgt_bytes = (unsigned)((size_t)g.Cout * g.K * 2);
   return finish_plan(q, g.kH, g.kW);
+}
+
+struct Known { bool ok; StParams p; };
+bool fprop_params(const Geom& g, StParams* p) {
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r;
+    r.ok = fprop_work_out(g, &r.p);
+    return r;
+  });
+  *p = k.p;
+  return k.ok;
+}
+bool dgrad_params(const Geom& g, StParams* p) {
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r;
+    r.ok = dgrad_work_out(g, &r.p);
+    return r;
+  });
+  *p = k.p;
+  return k.ok;
 }
 
 template <class S>

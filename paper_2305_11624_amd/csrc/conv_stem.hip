@@ -376,7 +376,7 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
 }
 
 struct StemWgPlan { bool ok; bool x3; int nco; size_t lds; int grid; };
-StemWgPlan stem_wg_plan(const Geom& g, StemWgParams* pp) {
+StemWgPlan stem_wg_work_out(const Geom& g, StemWgParams* pp) {
   StemWgPlan pl{false, false, 0, 0, 0};
   StemWgParams& p = *pp;
   p = StemWgParams{};
@@ -402,6 +402,16 @@ StemWgPlan stem_wg_plan(const Geom& g, StemWgParams* pp) {
   pl.x3 = x3;
   pl.ok = true;
   return pl;
+}
+StemWgPlan stem_wg_plan(const Geom& g, StemWgParams* pp) {
+  struct Known { StemWgPlan pl; StemWgParams p; };
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r;
+    r.pl = stem_wg_work_out(g, &r.p);
+    return r;
+  });
+  *pp = k.p;
+  return k.pl;
 }
 
 // ---- input gradient of a first layer -------------------------------------------------------------------
@@ -592,7 +602,7 @@ __global__ __launch_bounds__(256) void stem_dgrad_pack_kernel(const bf16_t* __re
 }
 
 struct StemDgPlan { bool ok; size_t lds; int grid; };
-StemDgPlan stem_dg_plan(const Geom& g, StemDgParams* pp) {
+StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
   StemDgPlan pl{false, 0, 0};
   StemDgParams& p = *pp;
   p = StemDgParams{};
@@ -640,13 +650,23 @@ StemDgPlan stem_dg_plan(const Geom& g, StemDgParams* pp) {
   pl.ok = true;
   return pl;
 }
+StemDgPlan stem_dg_plan(const Geom& g, StemDgParams* pp) {
+  struct Known { StemDgPlan pl; StemDgParams p; };
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r;
+    r.pl = stem_dg_work_out(g, &r.p);
+    return r;
+  });
+  *pp = k.p;
+  return k.pl;
+}
 
 bool stem_shape(const Geom& g, int dtype) {
   return dtype == CONVBN_BF16 && g.Cin <= 4 && g.kW <= 8 && g.kH <= 16 && g.Cout % 8 == 0 && g.Cout <= 128 && g.sw <= 4;
 }
 
 struct StemPlan { bool ok; bool x3; int nco; size_t lds; int grid; };
-StemPlan stem_plan(const Geom& g, StemParams* pp) {
+StemPlan stem_work_out(const Geom& g, StemParams* pp) {
   StemPlan pl{false, false, 0, 0, 0};
   StemParams& p = *pp;
   p = StemParams{};
@@ -671,6 +691,16 @@ StemPlan stem_plan(const Geom& g, StemParams* pp) {
   pl.x3 = x3;
   pl.ok = true;
   return pl;
+}
+StemPlan stem_plan(const Geom& g, StemParams* pp) {
+  struct Known { StemPlan pl; StemParams p; };
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r;
+    r.pl = stem_work_out(g, &r.p);
+    return r;
+  });
+  *pp = k.p;
+  return k.pl;
 }
 
 }  // namespace

@@ -673,7 +673,7 @@ size_t plan_lds(TileParams& p, int nw, int nwc, int nch, int cb, bool rows) {
   return cb == 64 ? plan_lds_cfg<4, 64>(p, nw, nwc, rows) : plan_lds_cfg<4, 32>(p, nw, nwc, rows);
 }
 
-TilePlan make_plan(TileParams& p) {
+TilePlan work_out_plan(TileParams& p) {
   TilePlan pl{false, 0, 0, 0, 0, 0, 0};
   if (p.C % 8 || p.R % 8) return pl;
   if (p.act_bytes >= OOB || p.wgt_bytes >= OOB) return pl;   // byte offsets must stay below the zero-fill offset
@@ -747,6 +747,19 @@ TilePlan make_plan(TileParams& p) {
     }
   }
   return pl;
+}
+
+TilePlan make_plan(TileParams& p) {
+  struct Known { TilePlan pl; TileParams p; };
+  static thread_local PlanTable<TileParams, Known> table;
+  const Known& k = table.get(p, [&] {
+    Known r;
+    r.p = p;
+    r.pl = work_out_plan(r.p);
+    return r;
+  });
+  p = k.p;
+  return k.pl;
 }
 
 template <int NW, int NWC, int NCH, int CB, int HPS, bool SC = false>
@@ -951,47 +964,57 @@ __global__ __launch_bounds__(256) void fill_rows_kernel(uint4* __restrict__ out,
 
 bool tile_fprop_supported(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16) return false;
-  TileParams p;
-  if (!fprop_params(g, &p)) return false;
-  if ((g.sh > 1 || g.sw > 1) && g.kH * g.kW > 1 && p.C % 8 == 0 && p.act_bytes < OOB && p.wgt_bytes < OOB &&
-      (size_t)p.M * p.R * 2 < OOB && gm_conv_supported(p.M, p.C, p.R, gm_conv_of(p)))
-    return true;   // the tiled product's window mode takes it
-  return make_plan(p).ok;
+  return planned<bool>(g, dtype, [&]() -> bool {
+    TileParams p;
+    if (!fprop_params(g, &p)) return false;
+    if ((g.sh > 1 || g.sw > 1) && g.kH * g.kW > 1 && p.C % 8 == 0 && p.act_bytes < OOB && p.wgt_bytes < OOB &&
+        (size_t)p.M * p.R * 2 < OOB && gm_conv_supported(p.M, p.C, p.R, gm_conv_of(p)))
+      return true;   // the tiled product's window mode takes it
+    return make_plan(p).ok;
+  });
 }
 
 bool tile_dgrad_supported(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16) return false;
-  TileParams p;
-  if (g.sh == 1 && g.sw == 1) return dgrad_params(g, &p) && make_plan(p).ok;
-  if ((size_t)g.Min * g.Cin * 2 >= OOB || g.Cin % 8) return false;
-  for (int a = 0; a < g.sh; ++a)
-    for (int b = 0; b < g.sw; ++b) {
-      const ClassKind k = dgrad_class_params(g, a, b, &p);
-      if (k == CLASS_RUN && p.act_bytes < OOB && p.wgt_bytes < OOB && gm_conv_supported(p.M, p.C, p.R, gm_conv_of(p))) continue;
-      if (k == CLASS_UNSUPPORTED || (k == CLASS_RUN && !make_plan(p).ok)) return false;
-    }
-  return true;
+  return planned<bool>(g, dtype, [&]() -> bool {
+    TileParams p;
+    if (g.sh == 1 && g.sw == 1) return dgrad_params(g, &p) && make_plan(p).ok;
+    if ((size_t)g.Min * g.Cin * 2 >= OOB || g.Cin % 8) return false;
+    for (int a = 0; a < g.sh; ++a)
+      for (int b = 0; b < g.sw; ++b) {
+        const ClassKind k = dgrad_class_params(g, a, b, &p);
+        if (k == CLASS_RUN && p.act_bytes < OOB && p.wgt_bytes < OOB && gm_conv_supported(p.M, p.C, p.R, gm_conv_of(p))) continue;
+        if (k == CLASS_UNSUPPORTED || (k == CLASS_RUN && !make_plan(p).ok)) return false;
+      }
+    return true;
+  });
 }
 
 bool tile_fprop_scaled_supported(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16) return false;
-  TileParams p;
-  if (!fprop_params(g, &p)) return false;
-  const TilePlan pl = make_plan(p);
-  return pl.ok && p.ksplit == 1 && scaled_plan(pl);
+  return planned<bool>(g, dtype, [&]() -> bool {
+    TileParams p;
+    if (!fprop_params(g, &p)) return false;
+    const TilePlan pl = make_plan(p);
+    return pl.ok && p.ksplit == 1 && scaled_plan(pl);
+  });
 }
 
 size_t tile_fprop_partial_bytes(const Geom& g) {
-  TileParams p;
-  if (!fprop_params(g, &p) || !make_plan(p).ok) return 0;
-  return partial_bytes(p);
+  return planned<size_t>(g, CONVBN_BF16, [&]() -> size_t {
+    TileParams p;
+    if (!fprop_params(g, &p) || !make_plan(p).ok) return 0;
+    return partial_bytes(p);
+  });
 }
 
 size_t tile_dgrad_partial_bytes(const Geom& g) {
-  TileParams p;
-  if (g.sh != 1 || g.sw != 1) return 0;   // the residue-class launches do not split their sums
-  if (!dgrad_params(g, &p) || !make_plan(p).ok) return 0;
-  return partial_bytes(p);
+  return planned<size_t>(g, CONVBN_BF16, [&]() -> size_t {
+    TileParams p;
+    if (g.sh != 1 || g.sw != 1) return 0;   // the residue-class launches do not split their sums
+    if (!dgrad_params(g, &p) || !make_plan(p).ok) return 0;
+    return partial_bytes(p);
+  });
 }
 
 hipError_t launch_fprop_tile(const Geom& g, const void* x, const void* w_krsc, const float* bias,

@@ -671,7 +671,7 @@ int max_window_pixels(const SqParams& p, int tile) {
 
 struct SqPlan { bool ok; int ks, ncpy, nsplit; size_t lds; };
 
-SqPlan make_plan(const Geom& g, SqParams* pp) {
+SqPlan work_out_plan(const Geom& g, SqParams* pp) {
   SqPlan pl{false, 0, 0, 0, 0};
   SqParams& p = *pp;
   p = SqParams{};
@@ -730,6 +730,17 @@ SqPlan make_plan(const Geom& g, SqParams* pp) {
   p.nblocks = p.blocks_per_split * pl.nsplit;
   pl.ok = true;
   return pl;
+}
+
+SqPlan make_plan(const Geom& g, SqParams* pp) {
+  struct Known { SqPlan pl; SqParams p; };
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r;
+    r.pl = work_out_plan(g, &r.p);
+    return r;
+  });
+  *pp = k.p;
+  return k.pl;
 }
 
 template <int KS, int NCPY>

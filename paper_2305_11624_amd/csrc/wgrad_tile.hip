@@ -521,7 +521,7 @@ bool base_params(const Geom& g_in, WgParams* p) {
   return true;
 }
 
-WgPlan make_plan(const Geom& g, WgParams* pp) {
+WgPlan work_out_plan(const Geom& g, WgParams* pp) {
   WgPlan pl{false, 0, 0, 0, 1, 0, 0};
   if (g.Cin % 8 || g.Cout % 8) return pl;
   WgParams& p = *pp;
@@ -565,6 +565,17 @@ WgPlan make_plan(const Geom& g, WgParams* pp) {
   pl.nsplit = ceil_div(p.ntiles, p.tiles_per_split);
   pl.ok = true;
   return pl;
+}
+
+WgPlan make_plan(const Geom& g, WgParams* pp) {
+  struct Known { WgPlan pl; WgParams p; };
+  const Known& k = planned<Known>(g, CONVBN_BF16, [&] {
+    Known r{};
+    r.pl = work_out_plan(g, &r.p);
+    return r;
+  });
+  *pp = k.p;
+  return k.pl;
 }
 
 template <int TPB, int NA, int NB, int NT>
