@@ -88,7 +88,7 @@ Geom padded_geom(const Geom& g) {
   return q;
 }
 
-struct WgradWay { int nsplit; int nrpart; bool fused_r; bool sq = false; };
+struct WgradWay { int nsplit; int nrpart; bool fused_r; bool sq = false; bool wave = false; };
 WgradWay wgrad_way(const Geom& g0, int dtype) {
   if (needs_cin_pad(g0, dtype) && stem_wgrad_supported(g0, dtype)) {   // a first layer: its own kernel
     const int s = stem_wgrad_slices(g0);
@@ -102,6 +102,10 @@ WgradWay wgrad_way(const Geom& g0, int dtype) {
   if (wgrad_tile_supported(g, dtype)) {
     const int s = wgrad_tile_splits(g);
     return {s, s, true};
+  }
+  if (wave_f32_supported(g, dtype)) {
+    const int s = wave_wgrad_splits(g);
+    return {s, s, true, false, true};
   }
   return {igemm_supported(g, dtype) ? wgrad_splits(g) : wgrad_direct_splits(g), colsum_parts(g), false};
 }
@@ -282,6 +286,7 @@ hipError_t fprop_any(const Geom& g, int dtype, const void* x, const void* w_krsc
   else if (rw_fprop_supported(g, dtype)) { e = launch_fprop_rw(g, x, w_krsc, bias, z, st); fused = FUSED_RW; }
   else if (st_fprop_supported(g, dtype)) { e = launch_fprop_st(g, x, w_krsc, bias, z, st); fused = FUSED_ST; }
   else if (tile_fprop_supported(g, dtype)) { e = launch_fprop_tile(g, x, w_krsc, bias, z, scratch, st); fused = FUSED_TILE; }
+  else if (wave_f32_supported(g, dtype)) { e = launch_fprop_wave(g, x, w_krsc, bias, z, st); fused = true; }
   else e = igemm_supported(g, dtype) ? launch_fprop_igemm(g, x, w_krsc, bias, z, st)
                                      : launch_fprop_direct(g, dtype, x, w_krsc, bias, z, st);
   if (e != hipSuccess || fused || !has_post_op(g)) return e;
@@ -295,6 +300,7 @@ hipError_t dgrad_any(const Geom& g, int dtype, const void* dz, const void* w_crs
   else if (rw_dgrad_supported(g, dtype)) { e = launch_dgrad_rw(g, dz, w_crsk, bias, dx, st); fused = FUSED_RW; }
   else if (st_dgrad_supported(g, dtype)) { e = launch_dgrad_st(g, dz, w_crsk, bias, dx, st); fused = FUSED_ST; }
   else if (tile_dgrad_supported(g, dtype)) { e = launch_dgrad_tile(g, dz, w_crsk, bias, dx, scratch, st); fused = FUSED_TILE; }
+  else if (wave_f32_supported(g, dtype)) { e = launch_dgrad_wave(g, dz, w_crsk, bias, dx, st); fused = true; }
   else e = igemm_supported(g, dtype) ? launch_dgrad_igemm(g, dz, w_crsk, bias, dx, st)
                                      : launch_dgrad_direct(g, dtype, dz, w_crsk, bias, dx, st);
   if (e != hipSuccess || fused || !has_post_op(g)) return e;
@@ -353,6 +359,7 @@ hipError_t run_dgrad(const Geom& g, int dtype, const void* dz, const void* w_crs
 hipError_t wgrad_any(const Geom& g, int dtype, const void* x, const void* dz, float* part, float* r_part,
                      const WgradWay& way, hipStream_t st) {
   if (way.sq) return launch_wgrad_sq(g, x, dz, part, r_part, st);
+  if (way.wave) return launch_wgrad_wave(g, x, dz, part, r_part, st);
   if (way.fused_r) return launch_wgrad_tile(g, x, dz, part, r_part, st);
   hipError_t e = igemm_supported(g, dtype) ? launch_wgrad_igemm(g, x, dz, part, way.nsplit, st)
                                            : launch_wgrad_direct(g, dtype, x, dz, part, st);
@@ -638,6 +645,11 @@ convbn_status convbn_tune_fwd(const convbn_desc* desc, const void* x, const void
   hipStream_t st = static_cast<hipStream_t>(stream);
   g.post_relu = g.act & CONVBN_ACT_RELU_OUT; g.post_add = g.add_out;
   const size_t nz = (size_t)g.M * g.Cout;
+  if (wave_f32_supported(g, dt)) {   // one launch, as below
+    const BnEpilogue bn{gamma, beta, mean, var, b, g.eps, w_folded, g.kH * g.kW, g.Cin, g.Cout};
+    LAUNCH(launch_fprop_wave(g, x, W, nullptr, z, st, &bn));
+    return CONVBN_OK;
+  }
   if (!needs_cin_pad(g, dt) && !pw_fprop_supported(g, dt) && (g.kH > 1 || g.kW > 1)) {
     // The scale is per output channel, so Z = s (w (*) X) + b' (Sec. 3.3): the convolution reads the unfolded
     // weight and applies s and b' in its epilogue, and -- where w' is kept for backward -- its workgroups each
@@ -709,6 +721,12 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
       // shallow layers: the two gradient passes are independent and share one launch (see wgrad_sq.hip)
       LAUNCH(launch_wgrad_dgrad_pair(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       if (!FUSED_RW) LAUNCH(post_op_pass(g, dt, dx, (size_t)g.Min * g.Cin, st));
+      LAUNCH(launch_fold_back(g, dt, w.dwf_part, w.nsplit, w.r_part, w.nrpart, W, b, gamma, mean, var, 0,
+                              dW, db, dgamma, dbeta, st));
+      return CONVBN_OK;
+    }
+    if (params && wave_f32_supported(g, dt)) {   // both gradient passes in one launch
+      LAUNCH(launch_pair_wave(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       LAUNCH(launch_fold_back(g, dt, w.dwf_part, w.nsplit, w.r_part, w.nrpart, W, b, gamma, mean, var, 0,
                               dW, db, dgamma, dbeta, st));
       return CONVBN_OK;

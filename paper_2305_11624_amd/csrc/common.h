@@ -287,6 +287,19 @@ bool g_wgrad_makes_rsum(const Geom& g, int groups, int dtype);
 hipError_t launch_g_wgrad(const Geom& g, int groups, int dtype, const void* x, const void* dz, float* part,
                           float* r_part, hipStream_t st);
 
+// conv_wave.hip : operands straight from memory into the matrix cores, the reduction split over a workgroup's waves.
+// The fp32 path of a dense block (tensors under 2 GB): forward and input gradient (post-operation applied), weight
+// gradient (fp32 copies [splits][Cout][K], r_part [splits][Cout] or null), and both gradients as one launch.
+bool wave_f32_supported(const Geom& g, int dtype);
+hipError_t launch_fprop_wave(const Geom& g, const void* x, const void* w_krsc, const float* bias, void* z, hipStream_t st,
+                             const BnEpilogue* bn = nullptr);
+hipError_t launch_dgrad_wave(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx,
+                             hipStream_t st);
+int wave_wgrad_splits(const Geom& g);
+hipError_t launch_wgrad_wave(const Geom& g, const void* x, const void* dz, float* part, float* r_part, hipStream_t st);
+hipError_t launch_pair_wave(const Geom& g, const void* x, const void* dz, const void* w_crsk, void* dx, float* part,
+                            float* r_part, hipStream_t st);
+
 // conv_direct.hip : one thread per output element, fp32 accumulation (any shape, both dtypes)
 hipError_t launch_fprop_direct(const Geom& g, int dtype, const void* x, const void* w_krsc,
                                const float* bias, void* z, hipStream_t st);
