@@ -226,14 +226,33 @@ convbn_status check_ws(size_t need, void* ws, size_t ws_bytes) {
   return CONVBN_OK;
 }
 
+// Which problems the window product takes: strided windows, what the LDS-tile kernel has no plan for, and what that
+// kernel would run with split sums (fp32 partial outputs, a reduction launch, element-wise launches behind it) as long as
+// one workgroup's chain of 64-channel chunks is not what the launch then waits for.  Measured, whole steps: 1x1, 512 -> 128
+// at 28 x 28, 4 images (8 chunks) 30.3 -> 23.6 us; 1024 -> 256 at 14 x 14, 1 image (16) 37.0 -> 30.7; 2048 -> 512 at 9 x 9,
+// 6 images of 7 x 7 (32) 39.2 -> 41.4; 3x3 with 256 channels (36) 43.5 -> 46.4, with 512 (72) 46 -> 71.
+constexpr int WIN_CHUNKS = 24;
+bool win_fprop_taken(const Geom& g, int dtype) {
+  if (!win_supported(g, dtype)) return false;
+  if (g.sh > 1 || g.sw > 1) return true;
+  return !tile_fprop_supported(g, dtype) || (g.K <= 64 * WIN_CHUNKS && tile_fprop_partial_bytes(g) > 0);
+}
+bool win_dgrad_taken(const Geom& g, int dtype) {
+  if (!win_supported(g, dtype)) return false;
+  if (g.sh > 1 || g.sw > 1) return true;
+  return !tile_dgrad_supported(g, dtype) || (g.kH * g.kW * g.Cout <= 64 * WIN_CHUNKS && tile_dgrad_partial_bytes(g) > 0);
+}
+
 // Scratch the three convolutions of a problem need (0 for most): fp32 partial outputs when the
 // reduced channels are split over workgroups, and the zero-padded copies of needs_cin_pad().
 size_t inner_fprop_scratch(const Geom& g, int dtype) {
-  if (pw_fprop_supported(g, dtype) || rw_fprop_supported(g, dtype) || st_fprop_supported(g, dtype)) return 0;
+  if (pw_fprop_supported(g, dtype) || rw_fprop_supported(g, dtype) || st_fprop_supported(g, dtype) ||
+      win_fprop_taken(g, dtype)) return 0;
   return tile_fprop_supported(g, dtype) ? align_up(tile_fprop_partial_bytes(g), 256) : 0;
 }
 size_t inner_dgrad_scratch(const Geom& g, int dtype) {
-  if (pw_dgrad_supported(g, dtype) || rw_dgrad_supported(g, dtype) || st_dgrad_supported(g, dtype)) return 0;
+  if (pw_dgrad_supported(g, dtype) || rw_dgrad_supported(g, dtype) || st_dgrad_supported(g, dtype) ||
+      win_dgrad_taken(g, dtype)) return 0;
   return tile_dgrad_supported(g, dtype) ? align_up(tile_dgrad_partial_bytes(g), 256) : 0;
 }
 size_t fprop_scratch_bytes(const Geom& g, int dtype) {
@@ -285,6 +304,7 @@ hipError_t fprop_any(const Geom& g, int dtype, const void* x, const void* w_krsc
   if (pw_fprop_supported(g, dtype)) { e = launch_fprop_pw(g, x, w_krsc, bias, z, st); fused = FUSED_PW; }
   else if (rw_fprop_supported(g, dtype)) { e = launch_fprop_rw(g, x, w_krsc, bias, z, st); fused = FUSED_RW; }
   else if (st_fprop_supported(g, dtype)) { e = launch_fprop_st(g, x, w_krsc, bias, z, st); fused = FUSED_ST; }
+  else if (win_fprop_taken(g, dtype)) { e = launch_fprop_win(g, x, w_krsc, bias, z, st); fused = true; }
   else if (tile_fprop_supported(g, dtype)) { e = launch_fprop_tile(g, x, w_krsc, bias, z, scratch, st); fused = FUSED_TILE; }
   else if (wave_f32_supported(g, dtype)) { e = launch_fprop_wave(g, x, w_krsc, bias, z, st); fused = true; }
   else e = igemm_supported(g, dtype) ? launch_fprop_igemm(g, x, w_krsc, bias, z, st)
@@ -299,6 +319,7 @@ hipError_t dgrad_any(const Geom& g, int dtype, const void* dz, const void* w_crs
   if (pw_dgrad_supported(g, dtype)) { e = launch_dgrad_pw(g, dz, w_crsk, bias, dx, st); fused = FUSED_PW; }
   else if (rw_dgrad_supported(g, dtype)) { e = launch_dgrad_rw(g, dz, w_crsk, bias, dx, st); fused = FUSED_RW; }
   else if (st_dgrad_supported(g, dtype)) { e = launch_dgrad_st(g, dz, w_crsk, bias, dx, st); fused = FUSED_ST; }
+  else if (win_dgrad_taken(g, dtype)) { e = launch_dgrad_win(g, dz, w_crsk, bias, dx, st); fused = true; }
   else if (tile_dgrad_supported(g, dtype)) { e = launch_dgrad_tile(g, dz, w_crsk, bias, dx, scratch, st); fused = FUSED_TILE; }
   else if (wave_f32_supported(g, dtype)) { e = launch_dgrad_wave(g, dz, w_crsk, bias, dx, st); fused = true; }
   else e = igemm_supported(g, dtype) ? launch_dgrad_igemm(g, dz, w_crsk, bias, dx, st)
@@ -650,11 +671,17 @@ convbn_status convbn_tune_fwd(const convbn_desc* desc, const void* x, const void
     LAUNCH(launch_fprop_wave(g, x, W, nullptr, z, st, &bn));
     return CONVBN_OK;
   }
-  if (!needs_cin_pad(g, dt) && !pw_fprop_supported(g, dt) && (g.kH > 1 || g.kW > 1)) {
+  if (!needs_cin_pad(g, dt) &&
+      (!pw_fprop_supported(g, dt) || pw_fprop_folds_aside(g, dt) || (!w_folded && pw_fprop_scaled_supported(g, dt)))) {
     // The scale is per output channel, so Z = s (w (*) X) + b' (Sec. 3.3): the convolution reads the unfolded
     // weight and applies s and b' in its epilogue, and -- where w' is kept for backward -- its workgroups each
     // write a slice of w' on the side.  The forward pass is one launch; no w' is materialised for it.
     const BnEpilogue bn{gamma, beta, mean, var, b, g.eps, w_folded, g.kH * g.kW, g.Cin, g.Cout};
+    if (pw_fprop_supported(g, dt)) {
+      LAUNCH(launch_fprop_pw(g, x, W, nullptr, z, st, &bn));
+      if (!FUSED_PW) LAUNCH(post_op_pass(g, dt, z, nz, st));
+      return CONVBN_OK;
+    }
     if (rw_fprop_supported(g, dt)) {
       LAUNCH(launch_fprop_rw(g, x, W, nullptr, z, st, &bn));
       if (!FUSED_RW) LAUNCH(post_op_pass(g, dt, z, nz, st));
@@ -665,7 +692,11 @@ convbn_status convbn_tune_fwd(const convbn_desc* desc, const void* x, const void
       if (!FUSED_ST) LAUNCH(post_op_pass(g, dt, z, nz, st));
       return CONVBN_OK;
     }
-    if (tile_fprop_scaled_supported(g, dt)) {
+    if (win_fprop_taken(g, dt)) {
+      LAUNCH(launch_fprop_win(g, x, W, nullptr, z, st, &bn));
+      return CONVBN_OK;
+    }
+    if (g.kH * g.kW > 1 && tile_fprop_scaled_supported(g, dt)) {
       LAUNCH(launch_fprop_tile(g, x, W, nullptr, z, nullptr, st, &bn));
       if (!FUSED_TILE) LAUNCH(post_op_pass(g, dt, z, nz, st));
       return CONVBN_OK;

@@ -1,30 +1,28 @@
-// bf16 convolution as a tiled matrix product without a window tile in LDS
-//     out[m][r] = sum_{tap, c} act[row(m, tap)][c] wgt[r][tap][c] (+ bias[r]),     m over the output pixels:
-//   forward conv   Z  = w' (*) X + b'   (Sec. 3.1 / 3.3)   act = x,   wgt = w' as [Cout][taps][Cin]
-//   input gradient dX = w'_rot (*) dZ   (Sec. 3.2.1)       act = dz,  wgt = w' as [Cin][taps][Cout]
-// for pointwise (1x1) layers with or without a stride, and -- window mode -- for strided 3x3 layers, forward and the
-// residue classes of the input gradient.
+// bf16 pointwise (1x1) convolution, with or without a stride, as a tiled matrix product
+//     out[m][r] = sum_c act[m][c] wgt[r][c] (+ bias[r]):
+//   forward conv   Z  = w' (*) X + b'   (Sec. 3.1 / 3.3)   act = x,   wgt = w' as [Cout][Cin]
+//   input gradient dX = w'_rot (*) dZ   (Sec. 3.2.1)       act = dz,  wgt = w' as [Cin][Cout]   (stride 1)
 //
 // One output tile per workgroup, as large as still fills the chip: 256 (or 128) pixels x 128 channels, shared by
 // EIGHT waves as 4 (2) pixel groups x 2 channel groups, so that a wave owns 64 x 64 (32 x 64) outputs and reads four
 // (three) operand fragments for four (two) multiplies, and the matrix pipe of every SIMD is fed by two waves.  Channel
 // counts that are no multiple of 128 get 128 x 64 tiles, and so do layers with too few 128 x 128 tiles for the chip.
 //
-// Pipeline.  The reduction runs over 64-channel chunks (window mode: over the taps, chunks innermost).  A chunk of
+// Pipeline.  The reduction runs over 64-channel chunks.  A chunk of
 // the activation tile and of the weight tile is copied global -> LDS directly (1 KB per instruction: 8 rows x 128
 // bytes) into one of three stages, two chunks ahead; every wave issues the same number of copies per chunk, so "at
 // most that many copies outstanding" means the current chunk has landed; one barrier per chunk.  LDS rows are 128
 // bytes, unpadded: the copy permutes the eight 16-byte granules of row r by (r / 2) % 8 (it chooses which granule
 // each lane fetches), so that the 128-bit operand reads of 16 consecutive rows fall on distinct banks.  The copies of
 // a chunk are issued between its multiplies; operands are double-buffered in registers one 16-channel step ahead.
-// A copy's per-lane byte offset is free, which is all a stride needs: a strided pointwise layer gathers every
-// stride-th pixel's row (forward) or scatters its output rows (input gradient); in window mode the offset of a row
-// is recomputed per tap from the output pixel's window origin, rows outside the image being zero-fill copies.
+// A copy's per-lane byte offset is free, which is all a stride needs: a strided layer gathers every stride-th pixel's row.
+// A forward launch given the unfolded weight applies s and b' in the epilogue and folds on the side (fold_tile.h).
 //
 // Layers that are bound by their stores rather than by the product (64 or 128 reduced channels over tens of
 // thousands of pixels) run a variant with all their one or two chunks resident: no ring, about 70 registers, 33 or
 // 65 KB of LDS -- several workgroups share a compute unit, and one's stores overlap another's loads.
 #include "common.h"
+#include "fold_tile.h"
 
 namespace convbn {
 
@@ -36,6 +34,7 @@ constexpr int KK = CB / 16;
 constexpr int NSTAGE = 3;
 constexpr unsigned OOB = 0x80000000u;  // beyond any buffer: the load returns zeros
 
+enum { ORDER_TOGETHER, ORDER_PIXEL_RUNS, ORDER_CHANNEL_RUNS };
 struct GmParams {
   const bf16_t* act;     // [M][C]
   const bf16_t* wgt;     // [R][C]
@@ -49,17 +48,12 @@ struct GmParams {
   int M, C, R;
   int ntr;               // channel tiles
   int nchunks;
-  // A pointwise layer with a stride (a downsampling shortcut) is the same product over the output pixels, whose rows
-  // of the strided tensor are not consecutive: row m = (n, ho, wo) of the dense side is pixel (n, ho sh, wo sw) of an
-  // [N][Hs][Ws] tensor.  gather: the activation rows are taken from there (forward); scatter: the output rows go there
-  // (input gradient; the other pixels of dx are zero and are filled by the caller).
-  int gather, scatter;
+  int order;             // of the tiles, see the kernel
+  int nconv;             // the product's workgroups, those behind it fold
+  // A pointwise layer with a stride (a downsampling shortcut) is the same product over the output pixels; gather: the
+  // activation row of output pixel m = (n, ho, wo) is pixel (n, ho sh, wo sw) of an [N][Hs][Ws] tensor.
+  int gather;
   int Ho, Wo, Hs, Ws, sh, sw;
-  // Window mode (template flag CONV): a kH x kW window slides with stride (csh, csw) and padding (cph, cpw) over an
-  // [N][aH][aW] activation grid; output pixel m = (n, ho, wo) of an [N][oHo][oWo] grid.  Every tap is a step of its own
-  // in the reduction, its activation rows gathered per output pixel (zeros outside the grid): no window tile in LDS,
-  // the taps re-read their rows through the L2 -- for strided layers, whose windows hardly overlap.
-  GmConv cv;
 };
 
 // pixel index in the strided tensor of row m of the dense side
@@ -112,9 +106,8 @@ struct GmCfg {
   static_assert(NWAVES * 32 * CW * 2 <= STAGE, "the epilogue stages every wave's outputs (32 pixels at a time) in the first stage");
 };
 
-template <int TM, int RES = 0, int TN = 128, bool CONV = false>
+template <int TM, int RES = 0, int TN = 128>
 __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
-  static_assert(!CONV || RES == 0, "window mode runs on the ring");
   using Cfg = GmCfg<TM, RES, TN>;
   constexpr bool ONE = Cfg::ONE;
   constexpr int CW = Cfg::CW;
@@ -124,16 +117,33 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
   constexpr int NPS = Cfg::NPS, NCS = Cfg::NCS, AUW = Cfg::AUW, WUW = Cfg::WUW, CPW = Cfg::CPW, STAGE = Cfg::STAGE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* biasl = reinterpret_cast<float*>(smem + Cfg::OFF_BIAS);
+  if ((int)blockIdx.x >= p.nconv) {
+    fold_side(p.bn, p.wgt, (int)blockIdx.x - p.nconv, smem);
+    return;
+  }
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;      // pixel group, channel group
-  // Workgroups are handed to the eight XCDs in turn (id % 8), and each XCD has its own L2: the channel tiles of one
-  // pixel tile read the same activation rows and should share one.  Pixel tiles go in groups of eight, one per XCD;
-  // the k-th workgroup of an XCD (k = id / 8) is channel tile k % ntr of the XCD's (k / ntr)-th pixel tile.
-  const int kx = (int)blockIdx.x >> 3;
-  const int ctile = kx % p.ntr, ptile = (kx / p.ntr) * 8 + ((int)blockIdx.x & 7);
-  if (ptile * TM >= p.M) return;   // (the last group of eight may be short)
+  // Workgroups are handed to the eight XCDs in turn (id % 8), and each XCD has its own L2, which what its workgroups share
+  // should fit: the tiles are split into eight contiguous runs, along the channels where the weight is the larger operand
+  // (an XCD then reads its channel tiles' rows and all activations), else along the pixels (2048 <- 512 channels at 7 x 7,
+  // 64 images, whole step: 60.3 -> 57.0 us).  Long streams are read and written front to back by all XCDs together, a pixel
+  // tile's channel tiles on one of them: eight far-apart streams cost 3 % (64 -> 256 channels, 253k pixels: 121.9 against
+  // 125.7 us a step).
+  const int npt = (p.M + TM - 1) / TM, ntiles = npt * p.ntr;
+  const int xcd = (int)blockIdx.x & 7, kx = (int)blockIdx.x >> 3;
+  int ptile, ctile;
+  if (p.order == ORDER_TOGETHER) {
+    ctile = kx % p.ntr;
+    ptile = (kx / p.ntr) * 8 + xcd;
+    if (ptile >= npt) return;
+  } else {
+    const int tile = xcd * ((ntiles + 7) >> 3) + kx;
+    if (tile >= ntiles) return;
+    if (p.order == ORDER_CHANNEL_RUNS) { ctile = tile / npt; ptile = tile - ctile * npt; }
+    else { ptile = tile / p.ntr; ctile = tile - ptile * p.ntr; }
+  }
   const int r0 = ctile * TN, m0 = ptile * TM;
   const __amdgpu_buffer_rsrc_t act_rsrc = make_rsrc(p.act, p.act_bytes);
   const __amdgpu_buffer_rsrc_t wgt_rsrc = make_rsrc(p.wgt, p.wgt_bytes);
@@ -153,48 +163,24 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
   // 8 u + l / 8 and fetches the granule that belongs there, (l % 8) ^ key(row), key = (row / 2) % 8
   const int crow = lane >> 3, cpos = lane & 7;
   unsigned voff_a[AUW], voff_w[WUW];
-  int cv_h[AUW], cv_w[AUW];   // window mode: the row's window origin (h, w of tap (0, 0)); voff_a holds its image and granule
 #pragma unroll
   for (int j = 0; j < AUW; ++j) {
     const int row = (wave + NWAVES * j) * 8 + crow;
     const int g = cpos ^ ((row >> 1) & 7);
-    if constexpr (CONV) {
-      const int m = min(m0 + row, p.M - 1);
-      const int hw = p.cv.oHo * p.cv.oWo;
-      const int n = m / hw, rem = m - n * hw;
-      const int ho = rem / p.cv.oWo, wo = rem - ho * p.cv.oWo;
-      cv_h[j] = m0 + row < p.M ? ho * p.cv.csh - p.cv.cph : -(1 << 20);   // rows past the last pixel: never inside the grid
-      cv_w[j] = wo * p.cv.csw - p.cv.cpw;
-      voff_a[j] = (unsigned)((n * p.cv.a_n + g * 8) * 2);
-    } else {
-      const size_t arow = (p.gather && m0 + row < p.M) ? strided_row(p, m0 + row) : (size_t)(m0 + row);
-      voff_a[j] = m0 + row < p.M ? (unsigned)((arow * p.C + g * 8) * 2) : OOB;   // rows past the last pixel: zeros
-      cv_h[j] = cv_w[j] = 0;
-    }
+    const size_t arow = (p.gather && m0 + row < p.M) ? strided_row(p, m0 + row) : (size_t)(m0 + row);
+    voff_a[j] = m0 + row < p.M ? (unsigned)((arow * p.C + g * 8) * 2) : OOB;   // rows past the last pixel: zeros
   }
 #pragma unroll
   for (int j = 0; j < WUW; ++j) {
     const int row = (wave + NWAVES * j) * 8 + crow;
     const int g = cpos ^ ((row >> 1) & 7);
-    voff_w[j] = (unsigned)(((size_t)(r0 + row) * (CONV ? p.cv.wrow : p.C) + g * 8) * 2);
+    voff_w[j] = (unsigned)(((size_t)(r0 + row) * p.C + g * 8) * 2);
   }
-  // copy i (0 .. CPW-1) of a reduction step: chunk `chunk` of (window mode) tap (ti, tj)
-  auto issue_copy = [&](int i, int chunk, int ti, int tj, unsigned char* stage) {
+  // copy i (0 .. CPW-1) of a chunk
+  auto issue_copy = [&](int i, int chunk, unsigned char* stage) {
     const unsigned soff = (unsigned)(chunk * (CB * 2));
-    if (i < AUW) {
-      const int ii = i < AUW ? i : 0;
-      unsigned voff = voff_a[ii];
-      if constexpr (CONV) {
-        const int h = cv_h[ii] + ti, w = cv_w[ii] + tj;
-        const bool ok = (unsigned)h < (unsigned)p.cv.aH && (unsigned)w < (unsigned)p.cv.aW;
-        voff = ok ? voff + (unsigned)((h * p.cv.a_h + w * p.cv.a_w) * 2) : OOB;
-      }
-      dma16(act_rsrc, voff, soff, stage + (wave + NWAVES * i) * 1024);
-    } else {
-      const int jj = i - AUW < WUW ? i - AUW : 0;
-      const unsigned wsoff = CONV ? (unsigned)((p.cv.wt0 + ti * p.cv.wt_row + tj * p.cv.wt_col) * p.C * 2) + soff : soff;
-      dma16(wgt_rsrc, voff_w[jj], wsoff, stage + TM * 128 + (wave + NWAVES * (i - AUW)) * 1024);
-    }
+    if (i < AUW) dma16(act_rsrc, voff_a[i < AUW ? i : 0], soff, stage + (wave + NWAVES * i) * 1024);
+    else dma16(wgt_rsrc, voff_w[i - AUW < WUW ? i - AUW : 0], soff, stage + TM * 128 + (wave + NWAVES * (i - AUW)) * 1024);
   };
 
   // ---- operand addresses: row l % 32 of a subtile, granule 2 kk + l / 32 of the chunk, which sits at position
@@ -231,17 +217,7 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
     const int g = (lane % GR) ^ ((row >> 1) & (GR - 1));
     const int m = m0 + wm * (32 * NPS) + ps * 32 + row;
     if (m >= p.M) return -1;
-    if constexpr (CONV) {
-      if (p.cv.out_strided) {
-        const int hw = p.cv.oHo * p.cv.oWo;
-        const int n = m / hw, rem = m - n * hw;
-        const int ho = rem / p.cv.oWo, wo = rem - ho * p.cv.oWo;
-        return (long long)p.cv.out_base + (long long)n * p.cv.out_n + (long long)ho * p.cv.out_h + (long long)wo * p.cv.out_w +
-               r0 + wn * CW + g * 8;
-      }
-    }
-    const size_t orow = p.scatter ? strided_row(p, m) : (size_t)m;
-    return (long long)(orow * p.R + r0 + wn * CW + g * 8);
+    return (long long)((size_t)m * p.R + r0 + wn * CW + g * 8);
   };
   uint4 addv[NPS][ITS], maskv[NPS][ITS];
   if (!ONE && (p.add || p.mask)) {
@@ -257,27 +233,16 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
   }
 
   // ---- prologue: chunks 0 and 1 (a chunk past the end is the last one again, into a stage nobody reads)
-  // (window mode: a step is (tap, chunk), chunks innermost; p.nchunks counts the steps and cpt the chunks per tap)
   const int nchunks = p.nchunks;
-  const int cpt = CONV ? p.C / CB : nchunks;
-  int f_c = 0, f_i = 0, f_j = 0;   // the step whose copies are issued next: chunk and tap
-  auto advance_fill = [&]() {       // ... the one after it (the last step stays)
-    if constexpr (CONV) {
-      if (f_c + 1 < cpt) ++f_c;
-      else if (f_j + 1 < p.cv.kW) { f_c = 0; ++f_j; }
-      else if (f_i + 1 < p.cv.kH) { f_c = 0; f_j = 0; ++f_i; }
-    } else {
-      if (f_c + 1 < nchunks) ++f_c;
-    }
-  };
+  int f_c = 0;   // the chunk whose copies are issued next; the last one stays
 #pragma unroll
-  for (int i = 0; i < CPW; ++i) issue_copy(i, f_c, f_i, f_j, smem);
-  advance_fill();
+  for (int i = 0; i < CPW; ++i) issue_copy(i, f_c, smem);
+  if (f_c + 1 < nchunks) ++f_c;
   if constexpr (RES != 1) {
 #pragma unroll
-    for (int i = 0; i < CPW; ++i) issue_copy(i, f_c, f_i, f_j, smem + STAGE);
+    for (int i = 0; i < CPW; ++i) issue_copy(i, f_c, smem + STAGE);
   }
-  advance_fill();
+  if (f_c + 1 < nchunks) ++f_c;
 
   int st_cur = 0;   // stage of the current chunk
   for (int c = 0; c < nchunks; ++c) {
@@ -303,18 +268,18 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
           acc[i][ps] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][ps], acc[i][ps], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
           if (!ONE && issued < PER && kk * PER + issued < CPW) {
-            issue_copy(kk * PER + issued, f_c, f_i, f_j, fill);
+            issue_copy(kk * PER + issued, f_c, fill);
             ++issued;
             __builtin_amdgcn_sched_barrier(0);
           }
         }
 #pragma unroll
       for (; issued < PER; ++issued)
-        if (!ONE && kk * PER + issued < CPW) issue_copy(kk * PER + issued, f_c, f_i, f_j, fill);
+        if (!ONE && kk * PER + issued < CPW) issue_copy(kk * PER + issued, f_c, fill);
       __builtin_amdgcn_sched_barrier(0);
     }
     st_cur = st_cur + 1 == NSTAGE ? 0 : st_cur + 1;
-    advance_fill();
+    if (f_c + 1 < nchunks) ++f_c;
   }
   wait_vm<0>();      // trailing copies must not outlive the loop: the ring becomes the staging space
   __syncthreads();   // (and the bias is visible)
@@ -360,6 +325,8 @@ constexpr int MIN_TILES_SMALL = 96;  // down to this many (measured against the 
                                      // 1024 -> 256 at 14 x 14, 98 tiles, 10.8 against 12.0 us)
 constexpr int MAX_PIXELS = 32768;    // longer pixel ranges with short reductions stream through the weight-stationary kernel
 
+constexpr size_t LONG_OUTPUT = 32u << 20, LONG_STREAM = 48u << 20;   // bytes written, read and written
+
 struct GmPlan { int tm, res, tn; };   // tm == 0: not taken
 
 GmPlan choose_plan(int M, int C, int R) {
@@ -384,80 +351,24 @@ GmPlan choose_plan(int M, int C, int R) {
 }
 
 template <int TM, int RES, int TN>
-hipError_t launch_inst(const GmParams& p, hipStream_t st) {
+hipError_t launch_inst(GmParams p, hipStream_t st) {
   static LdsLimitOnce lds_once;
   constexpr int lds = GmCfg<TM, RES, TN>::LDS_BYTES;
   if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_gm_kernel<TM, RES, TN>), lds);
       e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_gm_kernel<TM, RES, TN>), dim3(ceil_div(ceil_div(p.M, TM), 8) * 8 * p.ntr), dim3(64 * NWAVES), lds, st, p);
+  static_assert(2 * FOLD_TILE_BYTES <= lds, "two tiles of the fold on the side");
+  const int npt = ceil_div(p.M, TM);
+  const size_t out_bytes = (size_t)p.M * p.R * 2;
+  p.order = out_bytes > LONG_OUTPUT || out_bytes + p.act_bytes > LONG_STREAM ? ORDER_TOGETHER
+            : p.wgt_bytes > p.act_bytes ? ORDER_CHANNEL_RUNS : ORDER_PIXEL_RUNS;
+  p.nconv = p.order == ORDER_TOGETHER ? ceil_div(npt, 8) * 8 * p.ntr : ceil_div(npt * p.ntr, 8) * 8;
+  hipLaunchKernelGGL((conv_gm_kernel<TM, RES, TN>), dim3(p.nconv + fold_side_blocks(p.bn)), dim3(64 * NWAVES), lds, st, p);
   return hipGetLastError();
-}
-
-template <int TM, int TN>
-hipError_t launch_conv_inst(const GmParams& p, hipStream_t st) {
-  static LdsLimitOnce lds_once;
-  constexpr int lds = GmCfg<TM, 0, TN>::LDS_BYTES;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_gm_kernel<TM, 0, TN, true>), lds);
-      e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_gm_kernel<TM, 0, TN, true>), dim3(ceil_div(ceil_div(p.M, TM), 8) * 8 * p.ntr), dim3(64 * NWAVES), lds, st, p);
-  return hipGetLastError();
-}
-
-// tile of the window mode: tm = 0: not taken
-GmPlan conv_tile_plan(int M, int C, int R, const GmConv& cv) {
-  GmPlan none{0, 0, 0};
-  if (M < 1 || C % CB || R % 128 || cv.kH < 1 || cv.kW < 1 || cv.kH * cv.kW > 16) return none;
-  const long long t256 = (long long)ceil_div(M, 256) * (R / 128), t128 = (long long)ceil_div(M, 128) * (R / 128);
-  if (t256 >= MIN_TILES) return GmPlan{256, 0, 128};
-  // (as in the plain mode; 3x3 / 2 layers: 512 channels to 7 x 7, 52 tiles, forward 30.8 -> 27.9 us; 256 channels to 14 x 14,
-  // 98 tiles, forward 19.5 -> 17.9, input gradient 33.4 -> 28.8)
-  if (t128 < MIN_TILES && 2 * t128 >= MIN_TILES_SMALL) return GmPlan{128, 0, 64};
-  if (t128 >= MIN_TILES_SMALL) return GmPlan{128, 0, 128};
-  return none;
 }
 
 }  // namespace
 
-bool gm_conv_supported(int M, int C, int R, const GmConv& cv) { return conv_tile_plan(M, C, R, cv).tm != 0; }
-
-hipError_t launch_gm_conv(int M, int C, int R, const GmConv& cv, const void* act, unsigned act_bytes, const void* wgt,
-                          unsigned wgt_bytes, const float* bias, void* out, int relu, const void* mask, const void* add,
-                          hipStream_t st) {
-  const GmPlan pl = conv_tile_plan(M, C, R, cv);
-  const int tm = pl.tm;
-  if (tm == 0 || act_bytes >= OOB || wgt_bytes >= OOB) return hipErrorInvalidValue;
-  GmParams p{};
-  p.M = M; p.C = C; p.R = R;
-  p.act_bytes = act_bytes; p.wgt_bytes = wgt_bytes;
-  p.ntr = R / pl.tn;
-  p.nchunks = cv.kH * cv.kW * (C / CB);   // steps: (tap, chunk)
-  p.cv = cv;
-  p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
-  p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
-  if (pl.tn == 64) return launch_conv_inst<128, 64>(p, st);
-  return tm == 256 ? launch_conv_inst<256, 128>(p, st) : launch_conv_inst<128, 128>(p, st);
-}
-
 bool gm_supported(int M, int C, int R) { return choose_plan(M, C, R).tm != 0; }
-
-// every row of a [rows][R] bf16 tensor <- bias (zeros if null); R is a multiple of 8
-__global__ __launch_bounds__(256) void gm_fill_kernel(uint4* __restrict__ p, size_t n16, int R8, const float* __restrict__ bias) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (bias) {
-      const float* b = bias + (i % (size_t)R8) * 8;
-      v = make_uint4(pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3]), pack_bf16x2(b[4], b[5]), pack_bf16x2(b[6], b[7]));
-    }
-    p[i] = v;
-  }
-}
-
-hipError_t launch_gm_fill(void* p, size_t rows, int R, const float* bias, hipStream_t st) {
-  const size_t n16 = rows * (size_t)R / 8;
-  const int blocks = (int)((n16 + 255) / 256 < 4096 ? (n16 + 255) / 256 : 4096);
-  hipLaunchKernelGGL(gm_fill_kernel, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, st, (uint4*)p, n16, R / 8, bias);
-  return hipGetLastError();
-}
 
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
                      void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd) {
@@ -468,11 +379,10 @@ hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, cons
   p.act_bytes = (unsigned)((size_t)M * C * 2);
   if (sd) {
     const size_t strided_pixels = (size_t)sd->N * sd->Hs * sd->Ws;
-    if (strided_pixels * (size_t)(sd->scatter ? R : C) * 2 >= OOB) return hipErrorInvalidValue;
-    p.gather = !sd->scatter; p.scatter = sd->scatter;
+    if (strided_pixels * (size_t)C * 2 >= OOB) return hipErrorInvalidValue;
+    p.gather = 1;
     p.Ho = sd->Ho; p.Wo = sd->Wo; p.Hs = sd->Hs; p.Ws = sd->Ws; p.sh = sd->sh; p.sw = sd->sw;
-    if (p.gather) p.act_bytes = (unsigned)(strided_pixels * C * 2);
-    if (p.scatter && (mask || add || relu)) return hipErrorInvalidValue;   // the caller applies them to all of dx
+    p.act_bytes = (unsigned)(strided_pixels * C * 2);
   }
   p.wgt_bytes = (unsigned)((size_t)R * C * 2);
   p.ntr = R / pl.tn;

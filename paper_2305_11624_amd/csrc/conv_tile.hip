@@ -21,9 +21,7 @@
 //
 //   forward conv   Z  = w' (*) X + b'        (Sec. 3.1 / 3.3)    act = x,  weights [Cout][taps][Cin]
 //   input gradient dX = w'_rot (*) dZ        (Sec. 3.2.1), stride 1: the same sweep over dz with
-//                  the taps reversed and padding k-1-p,          weights [Cin][taps][Cout];
-//                  strided: one such sweep per residue class of input positions (see
-//                  dgrad_class_params), written to that class's positions of dX
+//                  the taps reversed and padding k-1-p,          weights [Cin][taps][Cout]
 #include "common.h"
 
 #include <type_traits>
@@ -67,16 +65,12 @@ struct TileParams {
   int kH, kW, sh, sw, ph, pw;
   int wrow;              // elements per output-channel row of the weight tensor (its taps x C)
   // window position (ti, tj) reads tap wt0 + ti wt_row + tj wt_col of the weight tensor (forward: the same
-  // position; input gradient: the rotated one; strided input gradient: every stride-th tap, rotated)
+  // position; input gradient: the rotated one)
   int wt0, wt_row, wt_col;
-  int no_split;          // the output is strided: no split sums (their reduction assumes a dense output)
-  int out_strided;       // output pixel (n, ho, wo) lives at out_base + n out_n + ho out_h + wo out_w (elements)
-  int out_base, out_n, out_h, out_w;
   int M;                 // N*Ho*Wo
   int Hv, Wv;            // rows / columns of one image's (virtually padded) window footprint
   int ntr;               // channel tiles
   int nhb, hps, spread;  // activation tile ring depth, copy units per wave and step, steps a prefetch spans
-  int min_hps;           // host side: the planner picks at least this many copy units per wave and step
   int ksplit, chunks_per_split;   // channel chunks are divided over gridDim.y workgroups
   float* part;           // [ksplit][M][R] fp32 partial outputs when ksplit > 1
   int halo_stride;       // bytes per activation tile buffer
@@ -443,15 +437,7 @@ __device__ __forceinline__ void tile_body(const TileParams& p, int bx, int by, i
     const int pi = wp * 32 + row;
     const int ch = r0 + (cw0 / 2 + rp) * 64 + g * 8;
     if (pi >= len || ch >= p.R) return -1;
-    size_t o = (size_t)(m0 + pi) * p.R;
-    if (p.out_strided) {
-      const int m = m0 + pi;
-      const int n = fdiv(m, p.dHoWo);
-      const int rem = m - n * HoWo;
-      const int ho = fdiv(rem, p.dWo);
-      o = (size_t)p.out_base + (size_t)n * p.out_n + (size_t)ho * p.out_h + (size_t)(rem - ho * p.Wo) * p.out_w;
-    }
-    return (long long)(o + ch);
+    return (long long)((size_t)(m0 + pi) * p.R + ch);
   };
   for (int left = nsteps;;) {
     step(std::integral_constant<int, 0>{}); if (--left == 0) break;
@@ -533,24 +519,6 @@ __global__ __launch_bounds__(64 * NW) void conv_tile_kernel(TileParams p) {
   tile_body<NW, NWC, NCH, CB, HPS, SC>(p, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, smem);
 }
 
-// Several problems of one kernel shape in ONE launch (the residue classes of a strided input gradient: each alone
-// leaves most of the chip idle, and launches of one stream do not overlap): the workgroups of problem c are
-// [first[c], first[c + 1]).  No split sums.
-struct TileMulti {
-  TileParams p[4];
-  int first[5];
-  int n;
-};
-template <int NW, int NWC, int NCH, int CB, int HPS>
-__global__ __launch_bounds__(64 * NW) void conv_tile_multi_kernel(TileMulti m) {
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int b = (int)blockIdx.x;
-  int c = 0;
-  while (c + 1 < m.n && b >= m.first[c + 1]) ++c;
-  c = __builtin_amdgcn_readfirstlane(c);
-  tile_body<NW, NWC, NCH, CB, HPS, false>(m.p[c], b - m.first[c], 0, m.first[c + 1] - m.first[c], smem);
-}
-
 // out[m][r] = bf16( sum_s part[s][m][r] + bias[r] ), eight channels per thread (R % 8 == 0).
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ part, int ksplit,
                                                               size_t MR, int R, const float* __restrict__ bias,
@@ -626,7 +594,7 @@ size_t plan_lds_cfg(TileParams& p, int nw, int nwc, bool rows) {
   const long long ptiles = rows ? (long long)p.N * p.tiles_per_image : ceil_div(p.M, TPx);
   const long long blocks = ptiles * ceil_div(p.R, Cfg::TRC);
   int ks = 1;
-  if (blocks < 160 && all_chunks >= 4 && !p.no_split) {
+  if (blocks < 160 && all_chunks >= 4) {
     ks = (int)((200 + blocks - 1) / blocks);
     if (ks > all_chunks / 2) ks = all_chunks / 2;
     if (ks > 8) ks = 8;
@@ -652,7 +620,7 @@ size_t plan_lds_cfg(TileParams& p, int nw, int nwc, bool rows) {
     static const int hps_values[] = {1, 2, 3, 4, 6, 8};
     hps = 0;
     for (int v : hps_values)
-      if (v >= p.min_hps && ceil_div(per_wave, v) <= max_spread) { hps = v; break; }
+      if (ceil_div(per_wave, v) <= max_spread) { hps = v; break; }
     if (hps == 0) return 0;
     spread = ceil_div(per_wave, hps);
   }
@@ -810,27 +778,6 @@ hipError_t launch_plan(const TileParams& p, const TilePlan& pl, hipStream_t st) 
   return hipErrorInvalidValue;
 }
 
-template <int NW, int NWC, int NCH, int CB, int HPS>
-hipError_t launch_multi_inst(const TileMulti& m, size_t lds, hipStream_t st) {
-  static LdsLimitOnce lds_once;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_tile_multi_kernel<NW, NWC, NCH, CB, HPS>),
-                                        (int)LDS_USABLE); e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_tile_multi_kernel<NW, NWC, NCH, CB, HPS>), dim3(m.first[m.n]), dim3(64 * NW), lds, st, m);
-  return hipGetLastError();
-}
-// the kernel shapes the strided 3x3 layers of a ResNet ask for; anything else runs class by class
-bool multi_shape(const TilePlan& pl) {
-  return (pl.nw == 4 && pl.nwc == 2 && pl.nch == 4 && pl.cb == 64 && (pl.hps == 2 || pl.hps == 3)) ||
-         (pl.nw == 4 && pl.nwc == 1 && pl.nch == 4 && pl.cb == 32 && (pl.hps == 4 || pl.hps == 6));
-}
-hipError_t launch_multi(const TileMulti& m, const TilePlan& pl, size_t lds, hipStream_t st) {
-  if (pl.cb == 64 && pl.hps == 2) return launch_multi_inst<4, 2, 4, 64, 2>(m, lds, st);
-  if (pl.cb == 64 && pl.hps == 3) return launch_multi_inst<4, 2, 4, 64, 3>(m, lds, st);
-  if (pl.cb == 32 && pl.hps == 4) return launch_multi_inst<4, 1, 4, 32, 4>(m, lds, st);
-  if (pl.cb == 32 && pl.hps == 6) return launch_multi_inst<4, 1, 4, 32, 6>(m, lds, st);
-  return hipErrorInvalidValue;
-}
-
 // A 1x1 window with stride 1 and no padding is a plain matrix product over all N*H*W pixels: present
 // the activations as one image of M rows and one column, so a pixel tile is exactly its own rows.
 void flatten_pointwise(TileParams& q, int M, int C) {
@@ -890,76 +837,6 @@ bool dgrad_params(const Geom& g, TileParams* p) {
   return true;
 }
 
-// Input gradient of a strided convolution, one residue class of input positions at a time
-// (Sec. 3.2.1: dX = w'_rot (*) dZ): the positions h = sh hq + a, w = sw wq + b only receive the taps
-// i = i0 + sh ti, j = j0 + sw tj with i0 = (a + ph) mod sh, j0 = (b + pw) mod sw, and
-//   dX[n, h, w] = sum_{ti,tj} w'[i, j] . dZ[n, hq + dh0 - ti, wq + dw0 - tj],   dh0 = (a + ph - i0) / sh,
-// which is a stride-1 sweep over dZ with a (kh x kw) window, padding (kh-1-dh0, kw-1-dw0) and the taps
-// taken in reverse -- no multiplications with the zeros a dilated dZ would contain.  The result is
-// written to the class's positions of dX.
-enum ClassKind { CLASS_RUN, CLASS_NO_PIXELS, CLASS_ZERO, CLASS_UNSUPPORTED };
-ClassKind dgrad_class_params(const Geom& g, int a, int b, TileParams* p) {
-  const int Hq = a < g.Hin ? (g.Hin - a + g.sh - 1) / g.sh : 0;
-  const int Wq = b < g.Win ? (g.Win - b + g.sw - 1) / g.sw : 0;
-  if (Hq == 0 || Wq == 0) return CLASS_NO_PIXELS;
-  const int i0 = (a + g.ph) % g.sh, j0 = (b + g.pw) % g.sw;
-  const int kh = i0 < g.kH ? (g.kH - i0 + g.sh - 1) / g.sh : 0;
-  const int kw = j0 < g.kW ? (g.kW - j0 + g.sw - 1) / g.sw : 0;
-  if (kh == 0 || kw == 0) return CLASS_ZERO;   // no tap reaches these positions
-  const int dh0 = (a + g.ph - i0) / g.sh, dw0 = (b + g.pw - j0) / g.sw;
-  if (kh - 1 - dh0 < 0 || kw - 1 - dw0 < 0 || kh * kw > 64) return CLASS_UNSUPPORTED;
-  TileParams& q = *p;
-  q = TileParams{};
-  q.N = g.N; q.C = g.Cout; q.H = g.Hout; q.W = g.Wout;
-  q.Ho = Hq; q.Wo = Wq; q.R = g.Cin; q.M = g.N * Hq * Wq;
-  q.kH = kh; q.kW = kw; q.sh = 1; q.sw = 1;
-  q.ph = kh - 1 - dh0; q.pw = kw - 1 - dw0;
-  q.wt0 = (i0 + g.sh * (kh - 1)) * g.kW + j0 + g.sw * (kw - 1);
-  q.wt_row = -g.sh * g.kW; q.wt_col = -g.sw;
-  q.act_n_stride = g.Hout * g.Wout * g.Cout;
-  q.act_h_stride = g.Wout * g.Cout;
-  q.act_w_stride = g.Cout;
-  q.act_bytes = (unsigned)((size_t)g.M * g.Cout * 2);
-  q.wgt_bytes = (unsigned)((size_t)g.Cout * g.K * 2);
-  q.Hv = (q.Ho - 1) + q.kH;
-  q.Wv = (q.Wo - 1) + q.kW;
-  q.wrow = g.kH * g.kW * g.Cout;
-  q.no_split = 1;
-  q.out_strided = 1;
-  q.out_base = (a * g.Win + b) * g.Cin;
-  q.out_n = g.Hin * g.Win * g.Cin;
-  q.out_h = g.sh * g.Win * g.Cin;
-  q.out_w = g.sw * g.Cin;
-  return CLASS_RUN;
-}
-
-// The same problem for the tiled product's window mode (conv_gm.hip), which takes strided windows: they hardly overlap,
-// so a window tile in LDS buys little and costs the chunk width (32-channel chunks here against 64 there).
-GmConv gm_conv_of(const TileParams& q) {
-  GmConv c{};
-  c.kH = q.kH; c.kW = q.kW; c.cph = q.ph; c.cpw = q.pw; c.csh = q.sh; c.csw = q.sw; c.aH = q.H; c.aW = q.W;
-  c.a_n = q.act_n_stride; c.a_h = q.act_h_stride; c.a_w = q.act_w_stride;
-  c.oHo = q.Ho; c.oWo = q.Wo;
-  c.wt0 = q.wt0; c.wt_row = q.wt_row; c.wt_col = q.wt_col; c.wrow = q.wrow;
-  c.out_strided = q.out_strided; c.out_base = q.out_base; c.out_n = q.out_n; c.out_h = q.out_h; c.out_w = q.out_w;
-  return c;
-}
-
-// Every pixel row of out ([pixels][R] bf16, R % 8 == 0) := bf16(bias) (zeros without a bias).
-__global__ __launch_bounds__(256) void fill_rows_kernel(uint4* __restrict__ out, size_t n16, int R,
-                                                        const float* __restrict__ bias) {
-  const int r8 = R >> 3;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256) {
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (bias) {
-      const float* bb = bias + (size_t)(i % r8) * 8;
-      v = make_uint4(pack_bf16x2(bb[0], bb[1]), pack_bf16x2(bb[2], bb[3]), pack_bf16x2(bb[4], bb[5]),
-                     pack_bf16x2(bb[6], bb[7]));
-    }
-    out[i] = v;
-  }
-}
-
 }  // namespace
 
 bool tile_fprop_supported(const Geom& g, int dtype) {
@@ -967,9 +844,6 @@ bool tile_fprop_supported(const Geom& g, int dtype) {
   return planned<bool>(g, dtype, [&]() -> bool {
     TileParams p;
     if (!fprop_params(g, &p)) return false;
-    if ((g.sh > 1 || g.sw > 1) && g.kH * g.kW > 1 && p.C % 8 == 0 && p.act_bytes < OOB && p.wgt_bytes < OOB &&
-        (size_t)p.M * p.R * 2 < OOB && gm_conv_supported(p.M, p.C, p.R, gm_conv_of(p)))
-      return true;   // the tiled product's window mode takes it
     return make_plan(p).ok;
   });
 }
@@ -978,15 +852,7 @@ bool tile_dgrad_supported(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16) return false;
   return planned<bool>(g, dtype, [&]() -> bool {
     TileParams p;
-    if (g.sh == 1 && g.sw == 1) return dgrad_params(g, &p) && make_plan(p).ok;
-    if ((size_t)g.Min * g.Cin * 2 >= OOB || g.Cin % 8) return false;
-    for (int a = 0; a < g.sh; ++a)
-      for (int b = 0; b < g.sw; ++b) {
-        const ClassKind k = dgrad_class_params(g, a, b, &p);
-        if (k == CLASS_RUN && p.act_bytes < OOB && p.wgt_bytes < OOB && gm_conv_supported(p.M, p.C, p.R, gm_conv_of(p))) continue;
-        if (k == CLASS_UNSUPPORTED || (k == CLASS_RUN && !make_plan(p).ok)) return false;
-      }
-    return true;
+    return dgrad_params(g, &p) && make_plan(p).ok;   // (stride 1; strided: conv_win.hip)
   });
 }
 
@@ -1011,7 +877,6 @@ size_t tile_fprop_partial_bytes(const Geom& g) {
 size_t tile_dgrad_partial_bytes(const Geom& g) {
   return planned<size_t>(g, CONVBN_BF16, [&]() -> size_t {
     TileParams p;
-    if (g.sh != 1 || g.sw != 1) return 0;   // the residue-class launches do not split their sums
     if (!dgrad_params(g, &p) || !make_plan(p).ok) return 0;
     return partial_bytes(p);
   });
@@ -1021,12 +886,6 @@ hipError_t launch_fprop_tile(const Geom& g, const void* x, const void* w_krsc, c
                              void* z, float* partials, hipStream_t st, const BnEpilogue* bn) {
   TileParams p;
   fprop_params(g, &p);
-  if (!bn && (g.sh > 1 || g.sw > 1) && g.kH * g.kW > 1) {
-    const GmConv cv = gm_conv_of(p);
-    if (gm_conv_supported(p.M, p.C, p.R, cv))
-      return launch_gm_conv(p.M, p.C, p.R, cv, x, p.act_bytes, w_krsc, p.wgt_bytes, bias, z, g.post_relu, g.post_mask,
-                            g.post_add, st);
-  }
   const TilePlan pl = make_plan(p);
   if (p.ksplit > 1 && (!partials || bn)) return hipErrorInvalidValue;   // split sums add the bias in their reduction
   if (bn && !scaled_plan(pl)) return hipErrorInvalidValue;
@@ -1040,102 +899,6 @@ hipError_t launch_fprop_tile(const Geom& g, const void* x, const void* w_krsc, c
 hipError_t launch_dgrad_tile(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx,
                              float* partials, hipStream_t st) {
   TileParams p;
-  if (g.sh != 1 || g.sw != 1) {
-    bool zero_first = false;
-    for (int a = 0; a < g.sh; ++a)
-      for (int b = 0; b < g.sw; ++b) zero_first |= dgrad_class_params(g, a, b, &p) == CLASS_ZERO;
-    // an addend also reaches the positions no tap does: then the whole post-operation follows as passes of its own
-    const bool defer = zero_first && g.post_add != nullptr;
-    if (zero_first) {   // positions no tap reaches hold the bias alone: fill dX once, the other classes overwrite theirs
-      const size_t n16 = (size_t)g.Min * g.Cin * 2 / 16;
-      const int blocks = (int)((n16 + 255) / 256 < 4096 ? (n16 + 255) / 256 : 4096);
-      hipLaunchKernelGGL(fill_rows_kernel, dim3(blocks), dim3(256), 0, st, (uint4*)dx, n16, g.Cin, bias);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    // all classes as one launch where they share a kernel shape (the one that needs the most copy units per step
-    // sets it for all), at most four of them, none with split sums
-    {
-      TileMulti m{};
-      TilePlan pls[4];
-      int n = 0, hps = 0;
-      bool same = true;
-      for (int a = 0; a < g.sh && same; ++a)
-        for (int b = 0; b < g.sw && same; ++b) {
-          TileParams q;
-          if (dgrad_class_params(g, a, b, &q) != CLASS_RUN) continue;
-          if (n == 4) { same = false; break; }
-          pls[n] = make_plan(q);
-          same = pls[n].ok && q.ksplit == 1 && multi_shape(pls[n]) &&
-                 (n == 0 || (pls[n].nw == pls[0].nw && pls[n].nwc == pls[0].nwc && pls[n].nch == pls[0].nch && pls[n].cb == pls[0].cb));
-          if (pls[n].hps > hps) hps = pls[n].hps;
-          ++n;
-        }
-      if (same && n >= 2) {
-        size_t lds = 0;
-        n = 0;
-        for (int a = 0; a < g.sh && same; ++a)
-          for (int b = 0; b < g.sw && same; ++b) {
-            TileParams& q = m.p[n];
-            if (dgrad_class_params(g, a, b, &q) != CLASS_RUN) continue;
-            q.min_hps = hps;
-            const TilePlan pl = make_plan(q);
-            same = pl.ok && q.ksplit == 1 && pl.hps == hps && pl.nw == pls[0].nw && pl.nwc == pls[0].nwc &&
-                   pl.nch == pls[0].nch && pl.cb == pls[0].cb;
-            if (!same) break;
-            q.act = (const bf16_t*)dz; q.wgt = (const bf16_t*)w_crsk; q.bias = bias; q.out = (bf16_t*)dx;
-            q.relu = g.post_relu; q.mask = (const bf16_t*)g.post_mask; q.add = (const bf16_t*)g.post_add;
-            if (defer) { q.relu = 0; q.mask = nullptr; q.add = nullptr; }
-            q.part = nullptr;
-            const int ptiles = q.tile_rows > 0 ? q.N * q.tiles_per_image : ceil_div(q.M, 32 * (pl.nw / pl.nwc));
-            m.first[n + 1] = m.first[n] + q.ntr * ptiles;
-            if (pl.lds > lds) lds = pl.lds;
-            pls[n] = pl;
-            ++n;
-          }
-        // (measured: it pays for the deep layer, whose classes are long reductions over few pixels -- 512 channels,
-        // 14 x 14, 100 workgroups per class: 48.5 -> 33.5 us; with 256 channels at 28 x 28, 98 workgroups per class,
-        // the classes are bound by their traffic and one launch takes 42.9 against 40.4 us)
-        if (same && m.first[n] <= 448 && g.Cout >= 512) {
-          m.n = n;
-          hipError_t e = launch_multi(m, pls[0], lds, st);
-          if (e != hipSuccess) return e;
-          goto classes_done;
-        }
-      }
-    }
-    for (int a = 0; a < g.sh; ++a)
-      for (int b = 0; b < g.sw; ++b) {
-        if (dgrad_class_params(g, a, b, &p) != CLASS_RUN) continue;
-        {
-          const GmConv cv = gm_conv_of(p);
-          if (gm_conv_supported(p.M, p.C, p.R, cv)) {
-            hipError_t e = launch_gm_conv(p.M, p.C, p.R, cv, dz, p.act_bytes, w_crsk, p.wgt_bytes, bias, dx,
-                                          defer ? 0 : g.post_relu, defer ? nullptr : g.post_mask,
-                                          defer ? nullptr : g.post_add, st);
-            if (e != hipSuccess) return e;
-            continue;
-          }
-        }
-        const TilePlan pl = make_plan(p);
-        if (!pl.ok) return hipErrorInvalidValue;
-        p.act = (const bf16_t*)dz; p.wgt = (const bf16_t*)w_crsk; p.bias = bias; p.out = (bf16_t*)dx;
-        p.relu = g.post_relu; p.mask = (const bf16_t*)g.post_mask; p.add = (const bf16_t*)g.post_add;
-        if (defer) { p.relu = 0; p.mask = nullptr; p.add = nullptr; }
-        p.part = nullptr;
-        hipError_t e = launch_plan(p, pl, st);
-        if (e != hipSuccess) return e;
-      }
-  classes_done:
-    if (defer) {
-      const size_t n = (size_t)g.Min * g.Cin;
-      hipError_t e = launch_eltwise(3 /* a + b */, CONVBN_BF16, dx, g.post_add, nullptr, n, st);
-      if (e == hipSuccess && g.post_relu) e = launch_eltwise(0, CONVBN_BF16, dx, nullptr, nullptr, n, st);
-      if (e == hipSuccess && g.post_mask) e = launch_eltwise(1, CONVBN_BF16, dx, g.post_mask, nullptr, n, st);
-      return e;
-    }
-    return hipSuccess;
-  }
   dgrad_params(g, &p);
   const TilePlan pl = make_plan(p);
   if (p.ksplit > 1 && !partials) return hipErrorInvalidValue;

@@ -5,6 +5,7 @@
 //   bn_affine   Z = gamma (Y - mu)/sqrt(var+eps) + beta     (Sec. 3.1; Eval comparison path)
 //   bn_bwd      dY = s dZ and the per-channel sums of Table 2, row "Eval"
 #include "common.h"
+#include "fold_tile.h"
 
 #include <cstring>
 
@@ -85,79 +86,9 @@ __global__ __launch_bounds__(256) void fold_kernel(const T* __restrict__ W, cons
   }
 }
 
-// bf16 fast path (K and Cout multiples of 8): 64 x 64 tiles, every global access is a 16-byte vector --
-// rows of W are read and written back eight columns per thread, the transposed copy leaves through an
-// LDS tile as rows of 64 consecutive output channels.
-struct FoldArgs {
-  const bf16_t* W; const float* b; const float* gamma; const float* beta; const float* mean; const float* var;
-  bf16_t* w_krsc; bf16_t* w_crsk; float* bfold;
-  float eps; int identity, Cout, K, Cin, taps;
-};
-// One 64 x 64 tile (bx along K, by along Cout) of one block's fold.
-__device__ __forceinline__ void fold_tile_bf16x8(const FoldArgs& a, int bx, int by, unsigned short (*tile)[72]) {
-  const bf16_t* __restrict__ W = a.W;
-  const float* __restrict__ b = a.b; const float* __restrict__ gamma = a.gamma; const float* __restrict__ beta = a.beta;
-  const float* __restrict__ mean = a.mean; const float* __restrict__ var = a.var;
-  bf16_t* __restrict__ w_krsc = a.w_krsc; bf16_t* __restrict__ w_crsk = a.w_crsk; float* __restrict__ bfold = a.bfold;
-  const float eps = a.eps;
-  const int identity = a.identity, Cout = a.Cout, K = a.K, Cin = a.Cin, taps = a.taps;
-  const int tid = threadIdx.x;
-  const int co0 = by * 64;
-  const int k0 = bx * 64;
-  const bool do_bias = bx == 0 && tid < 64 && bfold && co0 + tid < Cout;
-  float bg = 1.f, bv = 1.f, bm = 0.f, bb = 0.f, bc = 0.f;
-  if (do_bias) {
-    const int co = co0 + tid;
-    if (!identity) { bg = gamma[co]; bv = var[co]; bm = mean[co]; bb = beta[co]; }
-    if (b) bc = b[co];
-  }
-  const int kv = (tid & 7) * 8, r = tid >> 3;
-  uint4 wv[2];
-  float gv[2], vv[2];
-  bool ok[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int co = co0 + r + 32 * e;
-    ok[e] = co < Cout && k0 + kv < K;
-    wv[e] = ok[e] ? *reinterpret_cast<const uint4*>(W + (size_t)co * K + k0 + kv) : make_uint4(0u, 0u, 0u, 0u);
-    gv[e] = (ok[e] && !identity) ? gamma[co] : 1.f;
-    vv[e] = (ok[e] && !identity) ? var[co] : 1.f - eps;
-  }
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const float sc = identity ? 1.f : gv[e] / sqrtf(vv[e] + eps);
-    const uint32_t in[4] = {wv[e].x, wv[e].y, wv[e].z, wv[e].w};
-    uint32_t out[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      out[i] = pack_bf16x2(bf16_lo(in[i]) * sc, bf16_hi(in[i]) * sc);
-      tile[kv + 2 * i][r + 32 * e] = (unsigned short)(out[i] & 0xffffu);
-      tile[kv + 2 * i + 1][r + 32 * e] = (unsigned short)(out[i] >> 16);
-    }
-    if (ok[e] && w_krsc)
-      *reinterpret_cast<uint4*>(w_krsc + (size_t)(co0 + r + 32 * e) * K + k0 + kv) = make_uint4(out[0], out[1], out[2], out[3]);
-  }
-  if (do_bias) {
-    const float sc = identity ? 1.f : bg / sqrtf(bv + eps);
-    bfold[co0 + tid] = identity ? bc : (bc - bm) * sc + bb;
-  }
-  __syncthreads();
-  if (!w_crsk) return;
-  const int kl = tid >> 2, c16 = (tid & 3) * 16;
-  const int k = k0 + kl;
-  if (k < K) {
-    const int tap = k / Cin, ci = k - tap * Cin;
-    bf16_t* dst = w_crsk + ((size_t)ci * taps + tap) * Cout + co0 + c16;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (co0 + c16 + 8 * h < Cout)
-        *reinterpret_cast<uint4*>(dst + 8 * h) = *reinterpret_cast<const uint4*>(&tile[kl][c16 + 8 * h]);
-  }
-}
-
 __global__ __launch_bounds__(256) void fold_bf16x8_kernel(FoldArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned short tile[64][72];   // [k][co], 144-byte rows
-  fold_tile_bf16x8(a, blockIdx.x, blockIdx.y, tile);
+  fold_tile_bf16x8(a, blockIdx.x, blockIdx.y, threadIdx.x, tile);
 }
 
 // The folds of several blocks in one launch (Sec. 3.3: a training step starts by folding every block's
@@ -173,7 +104,7 @@ __global__ __launch_bounds__(256) void fold_group_kernel(const FoldGroupItem* __
   }
   const FoldGroupItem it = items[lo];
   const int t = blockIdx.x - it.first_block;
-  fold_tile_bf16x8(it.a, t % it.tiles_k, t / it.tiles_k, tile);
+  fold_tile_bf16x8(it.a, t % it.tiles_k, t / it.tiles_k, threadIdx.x, tile);
 }
 
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }

@@ -1,0 +1,66 @@
+"""GPU parity of the window product (conv_win.hip): channel counts that end inside a 64-channel chunk or a channel tile,
+one and several taps per chunk, pixel tails, few chunks against the depth of its ring, residue classes of a strided input
+gradient with few or no taps (and more than four of them), the post-operations on positions no tap reaches, and the
+fold on the side of forward launches (also of the pointwise product)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_11624_amd import binding as B
+from paper_2305_11624_amd import synth
+from paper_2305_11624_amd.synth import BlockShape
+
+from helpers import compare, oracle_block
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    BlockShape("win_8_channels", 2, 8, 5, 7, 8, 3, 1, 1, "bf16", 921),                # eight taps in a chunk
+    BlockShape("win_one_chunk", 3, 24, 9, 5, 72, 1, 1, 0, "bf16", 922),               # one chunk, ring of six
+    BlockShape("win_72_136", 2, 72, 17, 19, 136, 3, 1, 1, "bf16", 923),
+    BlockShape("win_200_56_5x5", 1, 200, 11, 13, 56, 5, 1, 2, "bf16", 924),
+    BlockShape("win_many_tiles_ragged", 24, 40, 33, 31, 232, 3, 1, 1, "bf16", 925),   # ring of three, 128 x 128 tiles
+    BlockShape("win_stride2_64", 5, 64, 23, 18, 64, 3, 2, 1, "bf16", 926),
+    BlockShape("win_stride2_512", 9, 512, 14, 13, 512, 3, 2, 1, "bf16", 927),         # weight larger than the activations
+    BlockShape("win_stride2_1x1", 4, 192, 13, 15, 320, 1, 2, 0, "bf16", 928),         # three classes without a tap
+    BlockShape("win_stride3_2x2", 2, 32, 16, 17, 48, 2, 3, 0, "bf16", 929),           # nine classes, five without a tap
+    BlockShape("win_stride2_wide", 40, 128, 30, 30, 256, 3, 2, 1, "bf16", 930),       # 256-pixel tiles
+    BlockShape("win_small_1x1", 2, 256, 9, 11, 1024, 1, 1, 0, "bf16", 931),
+    BlockShape("gm_fold_aside", 7, 128, 28, 28, 512, 1, 1, 0, "bf16", 932),           # pointwise product, folds on the side
+    BlockShape("gm_long_runs", 40, 256, 30, 33, 192, 1, 1, 0, "bf16", 933),
+]
+BOTH = B.ACT_RELU_OUT | B.ACT_RELU_IN
+
+
+@pytest.mark.parametrize("keep", [True, False], ids=["keeps_w", "keeps_nothing"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+def test_block(shape, keep):
+    from paper_2305_11624_amd.runner import BlockRun
+    inp = synth.make_inputs(shape, bias=True)
+    inp["x"] = torch.clamp(inp["x"], min=0)
+    ref = oracle_block(inp)
+    run = BlockRun(inp, mode="tune", keep_folded=keep, poison=True, act=BOTH)
+    run.step()
+    got = run.results()
+    ref["Z"] = np.maximum(ref["Z"], 0)
+    ref["dX"] = ref["dX"] * (inp["x"].double().numpy() > 0)
+    compare(got, ref, "bf16", tag=shape.name)
+    if keep:   # w' = bf16(float(W) s), whichever launch folds
+        w = torch.empty_like(run.w_folded)
+        B.convbn_fold(run.desc, run.W, run.b, run.gamma, run.beta, run.mean, run.var, None, w, None)
+        torch.cuda.synchronize()
+        assert torch.equal(w, run.w_folded)
+
+
+def test_addend_reaches_positions_no_tap_does():
+    from paper_2305_11624_amd.runner import BlockRun
+    shape = SHAPES[7]
+    inp = synth.make_inputs(shape)
+    add = torch.randn((shape.N, shape.Hin, shape.Win, shape.Cin), generator=torch.Generator().manual_seed(5)).bfloat16().cuda()
+    run = BlockRun(inp, mode="tune", poison=True, act=B.ACT_ADD_IN, add_in=add)
+    run.step()
+    plain = BlockRun(inp, mode="tune", poison=True)
+    plain.step()
+    B.convbn_aux_eltwise(B.OP_ADD, plain.dx, add)
+    torch.cuda.synchronize()
+    assert torch.equal(run.dx, plain.dx)
