@@ -27,6 +27,7 @@ int out_size(int in, int k, int s, int p) { return (in + 2 * p - k) / s + 1; }
 struct WgradWay;
 WgradWay wgrad_way(const Geom& g, int dtype);
 bool needs_cin_pad(const Geom& g, int dtype);
+bool pair_taken(const Geom& g, int dtype);
 Geom padded_geom(const Geom& g);
 long long widest_partial_elems(const Geom& g, int dtype);
 
@@ -88,20 +89,28 @@ Geom padded_geom(const Geom& g) {
   return q;
 }
 
-struct WgradWay { int nsplit; int nrpart; bool fused_r; bool sq = false; bool wave = false; };
+struct WgradWay { int nsplit; int nrpart; bool fused_r; bool sq = false; bool wave = false; bool win = false; };
 WgradWay wgrad_way(const Geom& g0, int dtype) {
   if (needs_cin_pad(g0, dtype) && stem_wgrad_supported(g0, dtype)) {   // a first layer: its own kernel
     const int s = stem_wgrad_slices(g0);
     return {s, s, true};
   }
   const Geom g = needs_cin_pad(g0, dtype) ? padded_geom(g0) : g0;
-  if (wgrad_sq_supported(g, dtype)) {
+  // 3x3 windows share one window tile in wgrad_sq; strided windows hardly overlap, and with few channel pairs its pixel
+  // splits, sized for long pixel ranges, write more copies of dw' than that saves (whole steps: 64 channels, 56 x 56, 4
+  // images 34.5 -> 31.9 us, 32 images 48.3 -> 53.2; 128 channels, 38 x 38 / 2, 4 images 34.4 -> 32.6; 256 channels,
+  // 28 x 28 / 2, 64 images 90.9 -> 87.2)
+  const bool sq = wgrad_sq_supported(g, dtype) && !pair_taken(g, dtype) &&
+                  (wgrad_sq_splits(g) == 1 ||
+                   (g.sh == 1 && g.sw == 1 &&
+                    ((long long)g.Cin * g.Cout > 64 * 64 || (g.M > 32768 && wgrad_dgrad_pair_supported(g, dtype)))));
+  if (sq) {
     const int s = wgrad_sq_splits(g);
     return {s, s, true, true};
   }
-  if (wgrad_tile_supported(g, dtype)) {
-    const int s = wgrad_tile_splits(g);
-    return {s, s, true};
+  if (wgrad_win_supported(g, dtype)) {
+    const int s = wgrad_win_splits(g);
+    return {s, s, true, false, false, true};
   }
   if (wave_f32_supported(g, dtype)) {
     const int s = wave_wgrad_splits(g);
@@ -226,21 +235,32 @@ convbn_status check_ws(size_t need, void* ws, size_t ws_bytes) {
   return CONVBN_OK;
 }
 
-// Which problems the window product takes: strided windows, what the LDS-tile kernel has no plan for, and what that
-// kernel would run with split sums (fp32 partial outputs, a reduction launch, element-wise launches behind it) as long as
-// one workgroup's chain of 64-channel chunks is not what the launch then waits for.  Measured, whole steps: 1x1, 512 -> 128
-// at 28 x 28, 4 images (8 chunks) 30.3 -> 23.6 us; 1024 -> 256 at 14 x 14, 1 image (16) 37.0 -> 30.7; 2048 -> 512 at 9 x 9,
-// 6 images of 7 x 7 (32) 39.2 -> 41.4; 3x3 with 256 channels (36) 43.5 -> 46.4, with 512 (72) 46 -> 71.
-constexpr int WIN_CHUNKS = 24;
+// Which problems the window product takes: strided windows, what the LDS-tile kernel has no plan for, and few tiles, where
+// that kernel would split its sums (fp32 partial outputs, a reduction launch, forward a fold launch), as long as one
+// workgroup's chain of 64-channel chunks is not what the launch then waits for -- and few tiles let the two gradient passes
+// share a launch (win_pair.hip).  Measured, whole steps: 1x1, 512 -> 128 at 28 x 28, 4 images (8 chunks) 38.2 -> 24 us;
+// 1024 -> 256 at 14 x 14, 1 image (16 forward) 37.2 -> 22.3; 512 -> 2048 at 8 x 8, 22 images (32 backward) 47 -> 31; 3x3 with
+// 256 channels at 14 x 14, 8 images (36) 50.7 -> 40.8; with 512 channels (72) 46.4 -> 66.
+constexpr int WIN_CHUNKS = 40, WIN_SMALL_TILES = 128;
+bool win_small(int M, int R, int K) {   // M pixels, R produced channels, K reduced
+  return K <= 64 * WIN_CHUNKS && (long long)ceil_div(M, 128) * ceil_div(R, 64) <= WIN_SMALL_TILES;
+}
 bool win_fprop_taken(const Geom& g, int dtype) {
   if (!win_supported(g, dtype)) return false;
   if (g.sh > 1 || g.sw > 1) return true;
-  return !tile_fprop_supported(g, dtype) || (g.K <= 64 * WIN_CHUNKS && tile_fprop_partial_bytes(g) > 0);
+  return !tile_fprop_supported(g, dtype) || win_small(g.M, g.Cout, g.K);
 }
 bool win_dgrad_taken(const Geom& g, int dtype) {
   if (!win_supported(g, dtype)) return false;
   if (g.sh > 1 || g.sw > 1) return true;
-  return !tile_dgrad_supported(g, dtype) || (g.kH * g.kW * g.Cout <= 64 * WIN_CHUNKS && tile_dgrad_partial_bytes(g) > 0);
+  return !tile_dgrad_supported(g, dtype) || win_small(g.Min, g.Cin, g.kH * g.kW * g.Cout);
+}
+
+// Whether the two gradient passes of a block share a launch (win_pair.hip): the input gradient then is the window product
+// also where the pointwise product would take it alone.
+bool pair_taken(const Geom& g, int dtype) {
+  return win_pair_supported(g, dtype) && !rw_dgrad_supported(g, dtype) && !st_dgrad_supported(g, dtype) &&
+         (pw_dgrad_supported(g, dtype) || win_dgrad_taken(g, dtype));
 }
 
 // Scratch the three convolutions of a problem need (0 for most): fp32 partial outputs when the
@@ -380,8 +400,8 @@ hipError_t run_dgrad(const Geom& g, int dtype, const void* dz, const void* w_crs
 hipError_t wgrad_any(const Geom& g, int dtype, const void* x, const void* dz, float* part, float* r_part,
                      const WgradWay& way, hipStream_t st) {
   if (way.sq) return launch_wgrad_sq(g, x, dz, part, r_part, st);
+  if (way.win) return launch_wgrad_win(g, x, dz, part, r_part, st);
   if (way.wave) return launch_wgrad_wave(g, x, dz, part, r_part, st);
-  if (way.fused_r) return launch_wgrad_tile(g, x, dz, part, r_part, st);
   hipError_t e = igemm_supported(g, dtype) ? launch_wgrad_igemm(g, x, dz, part, way.nsplit, st)
                                            : launch_wgrad_direct(g, dtype, x, dz, part, st);
   if (e != hipSuccess || !r_part) return e;
@@ -760,6 +780,13 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
       LAUNCH(launch_pair_wave(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       LAUNCH(launch_fold_back(g, dt, w.dwf_part, w.nsplit, w.r_part, w.nrpart, W, b, gamma, mean, var, 0,
                               dW, db, dgamma, dbeta, st));
+      return CONVBN_OK;
+    }
+    // ... few pixels: likewise
+    if (params && !needs_cin_pad(g, dt) && pair_taken(g, dt)) {
+      const int ns = win_pair_splits(g);
+      LAUNCH(launch_win_pair(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
+      LAUNCH(launch_fold_back(g, dt, w.dwf_part, ns, w.r_part, ns, W, b, gamma, mean, var, 0, dW, db, dgamma, dbeta, st));
       return CONVBN_OK;
     }
     LAUNCH(run_dgrad(g, dt, dz, wt, dx, w.conv_scratch, st));   // dX = w'_rot (*) dZ
@@ -1349,7 +1376,7 @@ int32_t convbn_tune_bwd_is_fused(const convbn_desc* desc) {
   Geom g;
   if (make_geom(desc, &g) != CONVBN_OK) return 0;
   const int dt = desc->dtype;
-  return !needs_cin_pad(g, dt) && wgrad_sq_fused_supported(g, dt) &&
+  return !needs_cin_pad(g, dt) && wgrad_sq_fused_supported(g, dt) && !pair_taken(g, dt) &&
          wgrad_sq_fused_scratch_bytes(g) <= (size_t)wgrad_way(g, dt).nsplit * g.Cout * g.K * 4;
 }
 

@@ -397,15 +397,21 @@ hipError_t launch_fprop_tile(const Geom& g, const void* x, const void* w_krsc, c
 hipError_t launch_dgrad_tile(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx,
                              float* partials, hipStream_t st);
 
-// wgrad_tile.hip : bf16 MFMA weight gradient with LDS-resident pixel tiles; also produces the
-// per-channel sums r (one partial per split) when r_part != nullptr.
-bool wgrad_tile_supported(const Geom& g, int dtype);
-int wgrad_tile_splits(const Geom& g);
-hipError_t launch_wgrad_tile(const Geom& g, const void* x, const void* dz, float* dwf_part, float* r_part,
-                             hipStream_t st);
+// wgrad_win.hip : bf16 MFMA weight gradient of any window and stride (channels multiples of 8, tensors under 2 GB); also
+// produces the per-channel sums r (one partial per split) when r_part != nullptr.
+bool wgrad_win_supported(const Geom& g, int dtype);
+int wgrad_win_splits(const Geom& g);
+hipError_t launch_wgrad_win(const Geom& g, const void* x, const void* dz, float* dwf_part, float* r_part, hipStream_t st);
+
+// win_pair.hip : the two above as one launch, for problems whose workgroups fit the chip together; win_pair_splits() (at
+// most wgrad_win_splits()) fp32 copies of dw' and of r.
+bool win_pair_supported(const Geom& g, int dtype);
+int win_pair_splits(const Geom& g);
+hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const void* w_crsk, void* dx, float* dwf_part,
+                           float* r_part, hipStream_t st);
 
 // wgrad_sq.hip : bf16 MFMA weight gradient of 3x3 windows (any stride), one 32 x 32 channel pair x 9 taps per
-// workgroup; same outputs as launch_wgrad_tile (fp32 dw' copies [splits][Cout][taps][Cin], r_part [splits][Cout]).
+// workgroup; same outputs as launch_wgrad_win (fp32 dw' copies [splits][Cout][taps][Cin], r_part [splits][Cout]).
 bool wgrad_sq_supported(const Geom& g, int dtype);
 int wgrad_sq_splits(const Geom& g);
 hipError_t launch_wgrad_sq(const Geom& g, const void* x, const void* dz, float* dwf_part, float* r_part,

@@ -1,5 +1,5 @@
-"""GPU parity of the window product (conv_win.hip): channel counts that end inside a 64-channel chunk or a channel tile,
-one and several taps per chunk, pixel tails, few chunks against the depth of its ring, residue classes of a strided input
+"""GPU parity of the window product and the window weight gradient (conv_win.hip, wgrad_win.hip, and both as one launch): channel counts that end inside a 64-channel chunk or a channel tile,
+one and several taps per chunk, pixel tails, few chunks against the depth of its ring, pixel slices, residue classes of a strided input
 gradient with few or no taps (and more than four of them), the post-operations on positions no tap reaches, and the
 fold on the side of forward launches (also of the pointwise product)."""
 import numpy as np
@@ -28,6 +28,13 @@ SHAPES = [
     BlockShape("win_small_1x1", 2, 256, 9, 11, 1024, 1, 1, 0, "bf16", 931),
     BlockShape("gm_fold_aside", 7, 128, 28, 28, 512, 1, 1, 0, "bf16", 932),           # pointwise product, folds on the side
     BlockShape("gm_long_runs", 40, 256, 30, 33, 192, 1, 1, 0, "bf16", 933),
+    BlockShape("ww_one_pixel", 1, 8, 1, 1, 16, 1, 1, 0, "bf16", 934),
+    BlockShape("ww_64_64_tile", 3, 64, 13, 10, 64, 1, 1, 0, "bf16", 935),             # 390 pixels: four slices, the last ragged
+    BlockShape("ww_128_64_tile", 2, 56, 9, 15, 120, 1, 1, 0, "bf16", 936),
+    BlockShape("ww_64_128_tile", 2, 24, 16, 8, 48, 3, 1, 1, "bf16", 937),
+    BlockShape("ww_alone", 30, 136, 29, 31, 264, 1, 1, 0, "bf16", 938),               # too many workgroups for one launch of both
+    BlockShape("ww_alone_5x5", 12, 96, 27, 26, 72, 5, 2, 2, "bf16", 939),
+    BlockShape("pair_3x3_256", 3, 256, 13, 14, 256, 3, 1, 1, "bf16", 940),
 ]
 BOTH = B.ACT_RELU_OUT | B.ACT_RELU_IN
 
