@@ -10,8 +10,8 @@
 //
 // Pipeline.  The reduction runs over 64-channel chunks.  A chunk of
 // the activation tile and of the weight tile is copied global -> LDS directly (1 KB per instruction: 8 rows x 128
-// bytes) into one of three stages, two chunks ahead; every wave issues the same number of copies per chunk, so "at
-// most that many copies outstanding" means the current chunk has landed; one barrier per chunk.  LDS rows are 128
+// bytes) into one of three (two) stages, two (one) chunks ahead; every wave issues the same number of copies per chunk,
+// so "at most that many copies outstanding" means the current chunk has landed; one barrier per chunk.  LDS rows are 128
 // bytes, unpadded: the copy permutes the eight 16-byte granules of row r by (r / 2) % 8 (it chooses which granule
 // each lane fetches), so that the 128-bit operand reads of 16 consecutive rows fall on distinct banks.  The copies of
 // a chunk are issued between its multiplies; operands are double-buffered in registers one 16-channel step ahead.
@@ -31,7 +31,6 @@ namespace {
 constexpr int NWAVES = 8;
 constexpr int CB = 64;                 // reduced channels per chunk
 constexpr int KK = CB / 16;
-constexpr int NSTAGE = 3;
 constexpr unsigned OOB = 0x80000000u;  // beyond any buffer: the load returns zeros
 
 enum { ORDER_TOGETHER, ORDER_PIXEL_RUNS, ORDER_CHANNEL_RUNS };
@@ -91,7 +90,8 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 // stores and another's loads overlap.
 // TN: output channels per workgroup (128; 64 for layers whose channel count is no multiple of 128 -- the two channel
 // groups of waves then own 32 channels each).
-template <int TM, int RES = 0, int TN = 128>
+// NS: stages of the ring.
+template <int TM, int RES = 0, int TN = 128, int NS = 3>
 struct GmCfg {
   static constexpr bool ONE = RES > 0;
   static constexpr int CW = TN / 2;                     // channels per wave
@@ -101,14 +101,14 @@ struct GmCfg {
   static constexpr int WUW = TN / 8 / NWAVES;           // weight copies per wave and chunk
   static constexpr int CPW = AUW + WUW;
   static constexpr int STAGE = (TM + TN) * 128;
-  static constexpr int OFF_BIAS = (RES ? RES : NSTAGE) * STAGE;   // [TN] bias, [TN] scale
+  static constexpr int OFF_BIAS = (RES ? RES : NS) * STAGE;   // [TN] bias, [TN] scale
   static constexpr int LDS_BYTES = OFF_BIAS + 2 * TN * 4;
   static_assert(NWAVES * 32 * CW * 2 <= STAGE, "the epilogue stages every wave's outputs (32 pixels at a time) in the first stage");
 };
 
-template <int TM, int RES = 0, int TN = 128>
+template <int TM, int RES = 0, int TN = 128, int NS = 3>
 __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
-  using Cfg = GmCfg<TM, RES, TN>;
+  using Cfg = GmCfg<TM, RES, TN, NS>;
   constexpr bool ONE = Cfg::ONE;
   constexpr int CW = Cfg::CW;
   constexpr int GR = CW / 8;          // 16-byte granules of a wave's staged output row
@@ -232,25 +232,26 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
     asm volatile("" ::: "memory");
   }
 
-  // ---- prologue: chunks 0 and 1 (a chunk past the end is the last one again, into a stage nobody reads)
+  // ---- prologue: chunk 0 and, but for a ring of two stages, chunk 1 (a chunk past the end is the last one again, into a
+  // stage nobody reads)
   const int nchunks = p.nchunks;
   int f_c = 0;   // the chunk whose copies are issued next; the last one stays
 #pragma unroll
   for (int i = 0; i < CPW; ++i) issue_copy(i, f_c, smem);
   if (f_c + 1 < nchunks) ++f_c;
-  if constexpr (RES != 1) {
+  if constexpr (ONE ? RES > 1 : NS > 2) {
 #pragma unroll
     for (int i = 0; i < CPW; ++i) issue_copy(i, f_c, smem + STAGE);
+    if (f_c + 1 < nchunks) ++f_c;
   }
-  if (f_c + 1 < nchunks) ++f_c;
 
   int st_cur = 0;   // stage of the current chunk
   for (int c = 0; c < nchunks; ++c) {
-    if (ONE && c == RES - 1) wait_vm<0>();   // (all chunks resident: the last one has nothing behind it)
+    if (ONE ? c == RES - 1 : NS == 2) wait_vm<0>();   // (nothing behind it: the last resident chunk; two stages)
     else wait_vm<CPW>();    // this chunk has landed (the next one's copies may be in flight) ...
     block_barrier();   // ... for every wave, and everybody is done with the stage refilled below
     const unsigned char* const stage = smem + st_cur * STAGE;
-    const int st_fill = st_cur >= 1 ? st_cur - 1 : NSTAGE - 1;   // (c + 2) % 3
+    const int st_fill = st_cur >= 1 ? st_cur - 1 : NS - 1;   // (c + NS - 1) % NS
     unsigned char* const fill = smem + st_fill * STAGE;
     load_frags(0, stage, 0);
 #pragma unroll
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
       const int cur = kk & 1;
       if (kk + 1 < KK) load_frags(cur ^ 1, stage, kk + 1);
       __builtin_amdgcn_sched_barrier(0);
-      // the copies of the chunk two ahead, spread over the multiplies of this one
+      // the copies of the chunk NS - 1 ahead, spread over the multiplies of this one
       constexpr int PER = (CPW + KK - 1) / KK;
       int issued = 0;
 #pragma unroll
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
         if (!ONE && kk * PER + issued < CPW) issue_copy(kk * PER + issued, f_c, fill);
       __builtin_amdgcn_sched_barrier(0);
     }
-    st_cur = st_cur + 1 == NSTAGE ? 0 : st_cur + 1;
+    st_cur = st_cur + 1 == NS ? 0 : st_cur + 1;
     if (f_c + 1 < nchunks) ++f_c;
   }
   wait_vm<0>();      // trailing copies must not outlive the loop: the ring becomes the staging space
@@ -327,34 +328,40 @@ constexpr int MAX_PIXELS = 32768;    // longer pixel ranges with short reduction
 
 constexpr size_t LONG_OUTPUT = 32u << 20, LONG_STREAM = 48u << 20;   // bytes written, read and written
 
-struct GmPlan { int tm, res, tn; };   // tm == 0: not taken
+struct GmPlan { int tm, res, tn, ns; };   // tm == 0: not taken
 
 GmPlan choose_plan(int M, int C, int R) {
-  GmPlan none{0, 0, 0};
+  GmPlan none{0, 0, 0, 3};
   if (M < 1 || C < CB || C % CB || R % 64) return none;
   if ((size_t)M * C * 2 >= OOB || (size_t)M * R * 2 >= OOB || (size_t)R * C * 2 >= OOB) return none;
   const int tn = R % 128 == 0 ? 128 : 64;
   const int ntr = R / tn;
   const long long t128 = (long long)ceil_div(M, 128) * ntr, t256 = (long long)ceil_div(M, 256) * ntr;
   // short reductions over many tiles: every chunk resident, several workgroups per compute unit
-  if ((C == CB || C == 2 * CB) && t128 >= 3 * MIN_TILES) return GmPlan{128, C / CB, tn};
-  if (tn == 64) return t128 >= MIN_TILES_SMALL ? GmPlan{128, 0, 64} : none;
+  if ((C == CB || C == 2 * CB) && t128 >= 3 * MIN_TILES) return GmPlan{128, C / CB, tn, 3};
+  if (tn == 64) return t128 >= MIN_TILES_SMALL ? GmPlan{128, 0, 64, 3} : none;
   // (measured on the 56 x 56 stage: with 256 reduced channels the tile beats the streaming kernel, 21.9 against 26.1 us
   // for 256 -> 128; with 64 or 128 both are bound by their stores and take the same time)
   if (M > MAX_PIXELS && C < 256) return none;
-  if (t256 >= MIN_TILES) return GmPlan{256, 0, 128};
+  // many tiles: 256 x 128 ones in a ring of three stages need the whole LDS of a compute unit, so nothing covers a tile's
+  // first loads and its stores; with up to four chunks these are most of its time, and 128 x 128 tiles with two stages, two
+  // workgroups per compute unit, are faster although they read more operands per multiply (256 -> 1024 at 14 x 14 with an
+  // addend: 128 images 53.0 -> 43.5 us, 64 images 21.8 -> 19.8; 256 -> 128 at 56 x 56, 128 images 79.5 -> 68.4, 32 images
+  // 21.8 -> 19.4).  With eight chunks both take the same time (512 -> 256 at 28 x 28, 64 images: 22.5 and 22.8), with
+  // sixteen the larger tile wins (1024 -> 256 at 14 x 14, 128 images: 17.8 against 19.3).
+  if (t256 >= MIN_TILES) return C <= 4 * CB ? GmPlan{128, 0, 128, 2} : GmPlan{256, 0, 128, 3};
   // too few 128 x 128 tiles for the chip: twice as many of half the channels (measured: 1024 -> 256 at 14 x 14, 98 tiles,
   // 10.4 -> 9.0 us; 2048 -> 512 at 7 x 7, 52 tiles, 16.8 us on the split-sum tile kernel -> 12.6)
-  if (t128 < MIN_TILES && 2 * t128 >= MIN_TILES_SMALL) return GmPlan{128, 0, 64};
-  if (t128 >= MIN_TILES_SMALL) return GmPlan{128, 0, 128};
+  if (t128 < MIN_TILES && 2 * t128 >= MIN_TILES_SMALL) return GmPlan{128, 0, 64, 3};
+  if (t128 >= MIN_TILES_SMALL) return GmPlan{128, 0, 128, 3};
   return none;
 }
 
-template <int TM, int RES, int TN>
+template <int TM, int RES, int TN, int NS = 3>
 hipError_t launch_inst(GmParams p, hipStream_t st) {
   static LdsLimitOnce lds_once;
-  constexpr int lds = GmCfg<TM, RES, TN>::LDS_BYTES;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_gm_kernel<TM, RES, TN>), lds);
+  constexpr int lds = GmCfg<TM, RES, TN, NS>::LDS_BYTES;
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_gm_kernel<TM, RES, TN, NS>), lds);
       e != hipSuccess) return e;
   static_assert(2 * FOLD_TILE_BYTES <= lds, "two tiles of the fold on the side");
   const int npt = ceil_div(p.M, TM);
@@ -362,7 +369,7 @@ hipError_t launch_inst(GmParams p, hipStream_t st) {
   p.order = out_bytes > LONG_OUTPUT || out_bytes + p.act_bytes > LONG_STREAM ? ORDER_TOGETHER
             : p.wgt_bytes > p.act_bytes ? ORDER_CHANNEL_RUNS : ORDER_PIXEL_RUNS;
   p.nconv = p.order == ORDER_TOGETHER ? ceil_div(npt, 8) * 8 * p.ntr : ceil_div(npt * p.ntr, 8) * 8;
-  hipLaunchKernelGGL((conv_gm_kernel<TM, RES, TN>), dim3(p.nconv + fold_side_blocks(p.bn)), dim3(64 * NWAVES), lds, st, p);
+  hipLaunchKernelGGL((conv_gm_kernel<TM, RES, TN, NS>), dim3(p.nconv + fold_side_blocks(p.bn)), dim3(64 * NWAVES), lds, st, p);
   return hipGetLastError();
 }
 
@@ -390,6 +397,7 @@ hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, cons
   p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
   if (bn) p.bn = *bn;
   p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
+  if (pl.ns == 2) return launch_inst<128, 0, 128, 2>(p, st);
 #define GM_CASE(TM_, RES_, TN_) if (pl.tm == TM_ && pl.res == RES_ && pl.tn == TN_) return launch_inst<TM_, RES_, TN_>(p, st);
   GM_CASE(256, 0, 128) GM_CASE(128, 0, 128) GM_CASE(128, 1, 128) GM_CASE(128, 2, 128)
   GM_CASE(128, 0, 64) GM_CASE(128, 1, 64) GM_CASE(128, 2, 64)

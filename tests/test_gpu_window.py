@@ -28,6 +28,8 @@ SHAPES = [
     BlockShape("win_small_1x1", 2, 256, 9, 11, 1024, 1, 1, 0, "bf16", 931),
     BlockShape("gm_fold_aside", 7, 128, 28, 28, 512, 1, 1, 0, "bf16", 932),           # pointwise product, folds on the side
     BlockShape("gm_long_runs", 40, 256, 30, 33, 192, 1, 1, 0, "bf16", 933),
+    BlockShape("gm_two_stages_3_chunks", 21, 192, 31, 33, 256, 1, 1, 0, "bf16", 941),
+    BlockShape("gm_two_stages_4_chunks", 9, 256, 24, 25, 1024, 1, 1, 0, "bf16", 942),
     BlockShape("ww_one_pixel", 1, 8, 1, 1, 16, 1, 1, 0, "bf16", 934),
     BlockShape("ww_64_64_tile", 3, 64, 13, 10, 64, 1, 1, 0, "bf16", 935),             # 390 pixels: four slices, the last ragged
     BlockShape("ww_128_64_tile", 2, 56, 9, 15, 120, 1, 1, 0, "bf16", 936),
