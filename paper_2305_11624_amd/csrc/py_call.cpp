@@ -16,6 +16,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <exception>
+
+#include "../../include/convbn.h"
 
 namespace {
 
@@ -23,10 +26,24 @@ constexpr int kMaxPtr = 16;
 
 PyObject* g_no_ws = nullptr;   // the NO_WS marker
 
+// Torch throws where a tensor has no memory of its own or there is no device; the interpreter's C frames let no C++
+// exception through, so it becomes a Python error.
+template <typename F>
+bool guarded(F&& f) {
+  try {
+    return f();
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {
+    PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+  }
+  return false;
+}
+
 // Address of a tensor argument; false (with a Python error set) where it is neither None, an int nor a dense device tensor.
 bool pointer_of(PyObject* o, void** out) {
   if (o == Py_None) { *out = nullptr; return true; }
-  if (THPVariable_Check(o)) {
+  if (THPVariable_Check(o)) return guarded([&] {
     const at::Tensor& t = THPVariable_Unpack(o);
     if (!t.is_cuda() || !t.is_contiguous()) {
       PyErr_SetString(PyExc_AssertionError, "device, dense tensors only");
@@ -34,7 +51,7 @@ bool pointer_of(PyObject* o, void** out) {
     }
     *out = t.data_ptr();
     return true;
-  }
+  });
   if (PyLong_Check(o)) {
     *out = PyLong_AsVoidPtr(o);
     return !PyErr_Occurred();
@@ -44,10 +61,10 @@ bool pointer_of(PyObject* o, void** out) {
 }
 
 bool stream_of(PyObject* o, void** out) {
-  if (o == Py_None) {
+  if (o == Py_None) return guarded([&] {
     *out = c10::hip::getCurrentHIPStream().stream();
     return true;
-  }
+  });
   *out = PyLong_AsVoidPtr(o);
   return !PyErr_Occurred();
 }
@@ -101,12 +118,17 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   size_t ws_bytes = 0;
   if (has_ws) {
     if (!pointer_of(ws_o, &ws)) return nullptr;
-    if (THPVariable_Check(ws_o)) ws_bytes = THPVariable_Unpack(ws_o).nbytes();
+    if (THPVariable_Check(ws_o) && !guarded([&] { ws_bytes = THPVariable_Unpack(ws_o).nbytes(); return true; })) return nullptr;
   }
   void* stream = nullptr;
   if (!stream_of(args[4 + n], &stream)) return nullptr;
   Py_buffer d;
   if (PyObject_GetBuffer(args[1], &d, PyBUF_SIMPLE) != 0) return nullptr;
+  if (d.len != (Py_ssize_t)sizeof(convbn_desc)) {
+    PyBuffer_Release(&d);
+    PyErr_SetString(PyExc_TypeError, "expected a convbn_desc");
+    return nullptr;
+  }
   bool known = true;
   int st = 0;
   Py_BEGIN_ALLOW_THREADS

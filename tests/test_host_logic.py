@@ -237,3 +237,21 @@ def test_sizes_beyond_32_bit_indexing_are_rejected_on_the_host():
     need = B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_BWD)
     assert need > 0 and need % 256 == 0
     assert B.convbn_wgrad_parts(d) * 4096 * 9 * 4096 <= 0x7fffffff
+
+
+def test_native_call_raises_python_errors():
+    """The extension lets no C++ exception into the interpreter (that would end the process): a stream asked for without
+    a device, a tensor on the host, something that is no descriptor."""
+    import torch
+    none = [None] * 9
+    B.lib()
+    call, at = B._load(), B._at.convbn_fold
+    assert call(at, B.Desc(), None, *none, B._NO_WS, 0) != B.OK      # the library's own refusal
+    if not torch.cuda.is_available():
+        with pytest.raises(RuntimeError):
+            call(at, B.Desc(), None, *none, B._NO_WS, None)
+    with pytest.raises(AssertionError):
+        call(at, B.Desc(), None, torch.zeros(4), *none[1:], B._NO_WS, 0)
+    for bad in (None, b"\0" * 8):
+        with pytest.raises(TypeError):
+            call(at, bad, None, *none, B._NO_WS, 0)
