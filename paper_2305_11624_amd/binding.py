@@ -194,8 +194,9 @@ def lib():
         L.convbn_static_workspace_limit.restype = C.c_size_t
         L.convbn_static_workspace_limit.argtypes = []
         from . import _call as ext
-        _call, _NO_WS, _pointer, _stream_handle = ext.call, ext.NO_WS, ext.pointer, ext.stream
-        _at = _Addresses(L)
+        # another thread may be in its first call: what a call reads behind `_call` or `_lib` is there before they are
+        _at, _NO_WS, _pointer, _stream_handle = _Addresses(L), ext.NO_WS, ext.pointer, ext.stream
+        _call = ext.call
         _lib = L
     return _lib
 

@@ -4,6 +4,8 @@ accounting reproduces the paper's memory model."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -255,3 +257,32 @@ def test_native_call_raises_python_errors():
     for bad in (None, b"\0" * 8):
         with pytest.raises(TypeError):
             call(at, bad, None, *none, B._NO_WS, 0)
+
+
+def test_first_calls_from_two_threads():
+    """A call that arrives while another thread loads the library finds either nothing loaded (and loads it too) or
+    everything: the entry points' addresses are there before the fast path that uses them."""
+    code = """if 1:
+        import threading
+        from paper_2305_11624_amd import binding as B
+        seen, build = [], B._Addresses.__init__
+
+        def second():
+            try:
+                seen.append(B.convbn_fold(B.Desc(), *[None] * 9, stream=0, check=False))
+            except Exception as e:
+                seen.append(repr(e))
+
+        def first(self, L):
+            if not seen:
+                t = threading.Thread(target=second)
+                B._Addresses.__init__ = build
+                t.start(); t.join()
+            build(self, L)
+
+        B._Addresses.__init__ = first
+        B.lib()
+        assert seen == [B.ERR_SHAPE], seen
+        assert B.convbn_fold(B.Desc(), *[None] * 9, stream=0, check=False) == B.ERR_SHAPE
+    """
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=100)
