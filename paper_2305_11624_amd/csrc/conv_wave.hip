@@ -35,7 +35,8 @@ struct WvParams {
   int N, C, R;                   // C reduced, R produced channels
   int aH, aW, oH, oW;            // activation and output planes
   int kH, kW, sh, sw, ph, pw;
-  int ptiles, rtiles, ncls;      // pixel tiles of a class, channel tiles, residue classes (input gradient)
+  int ptiles, rtiles;            // pixel tiles of a class, channel tiles
+  int ncls, ncw;                 // residue classes that have positions (input gradient), columns of them
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
@@ -99,14 +100,14 @@ __device__ __forceinline__ void conv_body(const WvParams& p, const int block, co
   int csh = p.sh, csw = p.sw, ch0 = -p.ph, cw0 = -p.pw, dth = 1, i0 = 0, j0 = 0, wsh = 1, wsw = 1, kh = p.kH, kw = p.kW;
   int qH = p.oH, qW = p.oW, osh = 1, osw = 1, oh0 = 0, ow0 = 0;
   if (p.dgrad) {
-    const int a = cls / p.sw, b = cls - a * p.sw;
+    const int a = cls / p.ncw, b = cls - a * p.ncw;
     i0 = (a + p.ph) % p.sh; j0 = (b + p.pw) % p.sw;
     ch0 = (a + p.ph - i0) / p.sh; cw0 = (b + p.pw - j0) / p.sw;
     csh = csw = 1; dth = -1; wsh = p.sh; wsw = p.sw;
-    kh = i0 < p.kH ? (p.kH - i0 + p.sh - 1) / p.sh : 0;
-    kw = j0 < p.kW ? (p.kW - j0 + p.sw - 1) / p.sw : 0;
-    qH = a < p.oH ? (p.oH - a + p.sh - 1) / p.sh : 0;
-    qW = b < p.oW ? (p.oW - b + p.sw - 1) / p.sw : 0;
+    kh = i0 < p.kH ? 1 + (p.kH - 1 - i0) / p.sh : 0;
+    kw = j0 < p.kW ? 1 + (p.kW - 1 - j0) / p.sw : 0;
+    qH = 1 + (p.oH - 1 - a) / p.sh;
+    qW = 1 + (p.oW - 1 - b) / p.sw;
     osh = p.sh; osw = p.sw; oh0 = a; ow0 = b;
   }
   const int npix = p.N * qH * qW;
@@ -428,7 +429,7 @@ WvParams fprop_params(const Geom& g) {
   p.wgt_bytes = (unsigned)((size_t)g.Cout * g.K * 4);
   p.rtiles = ceil_div(g.Cout, 32);
   p.ptiles = ceil_div(g.M, 32);
-  p.ncls = 1;
+  p.ncls = p.ncw = 1;
   p.relu = g.post_relu; p.mask = g.post_mask; p.add = g.post_add;
   return p;
 }
@@ -440,8 +441,9 @@ WvParams dgrad_params(const Geom& g) {
   p.act_bytes = (unsigned)((size_t)g.M * g.Cout * 4);
   p.wgt_bytes = (unsigned)((size_t)g.Cout * g.K * 4);
   p.rtiles = ceil_div(g.Cin, 32);
-  p.ptiles = ceil_div(g.N * ceil_div(g.Hin, g.sh) * ceil_div(g.Win, g.sw), 32);
-  p.ncls = g.sh * g.sw;
+  p.ptiles = ceil_div(g.N * (1 + (g.Hin - 1) / g.sh) * (1 + (g.Win - 1) / g.sw), 32);
+  p.ncw = g.sw < g.Win ? g.sw : g.Win;
+  p.ncls = (g.sh < g.Hin ? g.sh : g.Hin) * p.ncw;
   p.relu = g.post_relu; p.mask = g.post_mask; p.add = g.post_add;
   return p;
 }

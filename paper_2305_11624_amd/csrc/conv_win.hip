@@ -84,41 +84,41 @@ bool sizes_fit(const Geom& g, int dtype) {
 
 // The residue class (a, b) of input positions h = sh hq + a, w = sw wq + b of an input gradient (Sec. 3.2.1:
 // dX = w'_rot (*) dZ) only receives the taps i = i0 + sh t with i0 = (a + ph) mod sh (columns alike), from
-// dZ[hq + dh0 - t], dh0 = (a + ph - i0) / sh: a stride-1 window over dZ, taps in reverse.  False: no such positions.
-bool dgrad_class(const Geom& g, int a, int b, Window* cv, int* M) {
-  const int Hq = a < g.Hin ? (g.Hin - a + g.sh - 1) / g.sh : 0;
-  const int Wq = b < g.Win ? (g.Win - b + g.sw - 1) / g.sw : 0;
-  if (Hq == 0 || Wq == 0) return false;
+// dZ[hq + dh0 - t], dh0 = (a + ph - i0) / sh: a stride-1 window over dZ, taps in reverse.
+void dgrad_class(const Geom& g, int a, int b, Window* cv, int* M) {
+  const int Hq = 1 + (g.Hin - 1 - a) / g.sh, Wq = 1 + (g.Win - 1 - b) / g.sw;
   const int i0 = (a + g.ph) % g.sh, j0 = (b + g.pw) % g.sw;
-  int kh = i0 < g.kH ? (g.kH - i0 + g.sh - 1) / g.sh : 0;
-  int kw = j0 < g.kW ? (g.kW - j0 + g.sw - 1) / g.sw : 0;
+  int kh = i0 < g.kH ? 1 + (g.kH - 1 - i0) / g.sh : 0;
+  int kw = j0 < g.kW ? 1 + (g.kW - 1 - j0) / g.sw : 0;
   if (kh == 0 || kw == 0) { kh = 0; kw = 1; }   // no tap reaches these positions
+  // (a stride may be larger than image and window: what it multiplies is formed where there is a second row or column)
   Window c{};
   c.kH = kh; c.kW = kw;
   c.cph = kh - 1 - (a + g.ph - i0) / g.sh; c.cpw = kw - 1 - (b + g.pw - j0) / g.sw;
   c.csh = c.csw = 1; c.aH = g.Hout; c.aW = g.Wout;
   c.a_n = g.Hout * g.Wout * g.Cout; c.a_h = g.Wout * g.Cout; c.a_w = g.Cout;
   c.oHo = Hq; c.oWo = Wq;
-  c.wt0 = (i0 + g.sh * (kh - 1)) * g.kW + j0 + g.sw * (kw - 1);
-  c.wt_row = -g.sh * g.kW; c.wt_col = -g.sw;
+  c.wt_row = kh > 1 ? -g.sh * g.kW : 0; c.wt_col = kw > 1 ? -g.sw : 0;
+  if (kh > 0) c.wt0 = i0 * g.kW + j0 - (kh - 1) * c.wt_row - (kw - 1) * c.wt_col;
   c.wrow = g.kH * g.kW * g.Cout;
   c.out_strided = g.sh > 1 || g.sw > 1;
-  c.out_base = (a * g.Win + b) * g.Cin; c.out_n = g.Hin * g.Win * g.Cin; c.out_h = g.sh * g.Win * g.Cin; c.out_w = g.sw * g.Cin;
+  c.out_base = (a * g.Win + b) * g.Cin; c.out_n = g.Hin * g.Win * g.Cin;
+  c.out_h = Hq > 1 ? g.sh * g.Win * g.Cin : 0; c.out_w = Wq > 1 ? g.sw * g.Cin : 0;
   *cv = c;
   *M = g.N * Hq * Wq;
-  return true;
 }
+// residue classes that have positions, in rows and columns
+int classes_h(const Geom& g) { return g.sh < g.Hin ? g.sh : g.Hin; }
+int classes_w(const Geom& g) { return g.sw < g.Win ? g.sw : g.Win; }
 
 }  // namespace
 
 bool win::dgrad_params(const Geom& g, WnParams* p) {
-  if (!sizes_fit(g, CONVBN_BF16) || g.sh * g.sw > MAXC) return false;
+  if (!sizes_fit(g, CONVBN_BF16) || classes_h(g) * classes_w(g) > MAXC) return false;
   Window c[MAXC];
   int M[MAXC], n = 0;
-  for (int a = 0; a < g.sh; ++a)
-    for (int b = 0; b < g.sw; ++b)
-      if (dgrad_class(g, a, b, &c[n], &M[n])) ++n;
-  if (n == 0) return false;
+  for (int a = 0; a < classes_h(g); ++a)
+    for (int b = 0; b < classes_w(g); ++b, ++n) dgrad_class(g, a, b, &c[n], &M[n]);
   *p = make_params(g.Cout, g.Cin, n, M, c, (size_t)g.M * g.Cout * 2, (size_t)g.Cout * g.K * 2);
   return true;
 }
@@ -141,17 +141,16 @@ hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, c
   auto flush = [&]() -> hipError_t {
     const int k = n;
     n = 0;
-    if (k == 0) return hipSuccess;
     return launch_win(g.Cout, g.Cin, k, M, c, dz, (size_t)g.M * g.Cout * 2, w_crsk, (size_t)g.Cout * g.K * 2, bias, nullptr, dx,
                       g.post_relu, g.post_mask, g.post_add, st);
   };
-  for (int a = 0; a < g.sh; ++a)
-    for (int b = 0; b < g.sw; ++b) {
-      if (!dgrad_class(g, a, b, &c[n], &M[n])) continue;
+  for (int a = 0; a < classes_h(g); ++a)
+    for (int b = 0; b < classes_w(g); ++b) {
+      dgrad_class(g, a, b, &c[n], &M[n]);
       if (++n == MAXC)
         if (hipError_t e = flush(); e != hipSuccess) return e;
     }
-  return flush();
+  return n > 0 ? flush() : hipSuccess;
 }
 
 }  // namespace convbn

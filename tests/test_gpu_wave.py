@@ -21,6 +21,7 @@ SHAPES = [
     BlockShape("wave_stride3_5x5", 2, 8, 17, 16, 12, 5, 3, 2, "f32", 908),       # single-tap groups
     BlockShape("wave_ragged_slices", 5, 96, 13, 17, 96, 3, 1, 1, "f32", 909),    # 1105 pixels
     BlockShape("wave_pad0_wide", 8, 64, 30, 29, 96, 3, 1, 0, "f32", 910),
+    BlockShape("wave_stride_beyond_image", 2, 64, 5, 4, 64, 3, 65536, 1, "f32", 911),   # twenty classes of one position, most without a tap
 ]
 
 

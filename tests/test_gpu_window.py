@@ -37,6 +37,7 @@ SHAPES = [
     BlockShape("ww_alone", 30, 136, 29, 31, 264, 1, 1, 0, "bf16", 938),               # too many workgroups for one launch of both
     BlockShape("ww_alone_5x5", 12, 96, 27, 26, 72, 5, 2, 2, "bf16", 939),
     BlockShape("pair_3x3_256", 3, 256, 13, 14, 256, 3, 1, 1, "bf16", 940),
+    BlockShape("win_stride_beyond_image", 2, 64, 5, 4, 64, 3, 65536, 1, "bf16", 943),   # twenty classes of one position, most without a tap
 ]
 BOTH = B.ACT_RELU_OUT | B.ACT_RELU_IN
 

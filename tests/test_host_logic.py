@@ -286,3 +286,15 @@ def test_first_calls_from_two_threads():
         assert B.convbn_fold(B.Desc(), *[None] * 9, stream=0, check=False) == B.ERR_SHAPE
     """
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=100)
+
+
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32], ids=["bf16", "f32"])
+def test_strides_beyond_the_image_are_planned(dtype):
+    """Residue classes of input positions are counted by the positions there are, not by the stride (whose square wraps
+    in 32 bits): one output pixel whatever the stride is, and the same plan."""
+    sizes = set()
+    for stride in (9, 46341, 65536, 0x7fffffff):
+        d = B.make_desc(2, 64, 5, 4, 64, 3, 3, stride, 1, dtype=dtype)
+        assert (B.convbn_hout(d), B.convbn_wout(d)) == (1, 1)
+        sizes.add((B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_FWD), B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_BWD)))
+    assert len(sizes) == 1 and min(sizes.pop()) > 0
