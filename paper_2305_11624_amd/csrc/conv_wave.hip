@@ -448,6 +448,7 @@ WvParams dgrad_params(const Geom& g) {
   return p;
 }
 long long conv_blocks(const WvParams& p) { return (long long)p.ptiles * p.rtiles * p.ncls; }
+constexpr long long MAX_BLOCKS = 0xffffffffLL / (64 * KS);   // a launch has fewer than 2^32 threads
 
 // a tap group is a window row of a 3-wide window, else single taps
 int tap_group(const Geom& g) { return g.kW == 3 ? 3 : 1; }
@@ -475,7 +476,7 @@ WgParams wgrad_params(const Geom& g) {
   p.per = wgrad_split(g).per;
   return p;
 }
-int wgrad_blocks(const Geom& g, const WgParams& p) { return p.nci * p.nco * p.ntg * wgrad_split(g).slices; }
+long long wgrad_blocks(const Geom& g, const WgParams& p) { return (long long)p.nci * p.nco * p.ntg * wgrad_split(g).slices; }
 
 #define WAVE_LAUNCH(KERNEL, GRID, ...)                                                                            \
   do {                                                                                                            \
@@ -494,8 +495,9 @@ hipError_t launch_conv(const WvParams& p, hipStream_t st) {
 }  // namespace
 
 bool wave_f32_supported(const Geom& g, int dtype) {
-  return dtype == CONVBN_F32 && sizes_fit(g) && conv_blocks(fprop_params(g)) < 0x7fffffff &&
-         conv_blocks(dgrad_params(g)) < 0x7fffffff;
+  if (dtype != CONVBN_F32 || !sizes_fit(g)) return false;
+  return conv_blocks(fprop_params(g)) <= MAX_BLOCKS &&   // (the weight gradient's workgroups share the input gradient's launch)
+         conv_blocks(dgrad_params(g)) + wgrad_blocks(g, wgrad_params(g)) <= MAX_BLOCKS;
 }
 
 hipError_t launch_fprop_wave(const Geom& g, const void* x, const void* w_krsc, const float* bias, void* z, hipStream_t st,
@@ -515,7 +517,7 @@ int wave_wgrad_splits(const Geom& g) { return wgrad_split(g).slices; }
 hipError_t launch_wgrad_wave(const Geom& g, const void* x, const void* dz, float* part, float* r_part, hipStream_t st) {
   WgParams p = wgrad_params(g);
   p.x = (const float*)x; p.dz = (const float*)dz; p.part = part; p.r_part = r_part;
-  const int blocks = wgrad_blocks(g, p);
+  const int blocks = (int)wgrad_blocks(g, p);
   if (tap_group(g) == 3) WAVE_LAUNCH((wave_wgrad_kernel<3>), blocks, p);
   WAVE_LAUNCH((wave_wgrad_kernel<1>), blocks, p);
 }
@@ -525,7 +527,7 @@ hipError_t launch_pair_wave(const Geom& g, const void* x, const void* dz, const 
   p.x = (const float*)x; p.dz = (const float*)dz; p.part = part; p.r_part = r_part;
   WvParams d = dgrad_params(g);
   d.act = dz; d.wgt = w_crsk; d.out = dx;
-  const int ng = wgrad_blocks(g, p);
+  const int ng = (int)wgrad_blocks(g, p);
   const unsigned grid = ng + (unsigned)conv_blocks(d);
   const bool whole = g.Cout % 4 == 0;
   if (tap_group(g) == 3) {

@@ -298,3 +298,12 @@ def test_strides_beyond_the_image_are_planned(dtype):
         assert (B.convbn_hout(d), B.convbn_wout(d)) == (1, 1)
         sizes.add((B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_FWD), B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_BWD)))
     assert len(sizes) == 1 and min(sizes.pop()) > 0
+
+
+def test_fp32_launches_stay_below_2_32_threads():
+    """One channel over 2^28 pixels (1 GiB, 32 pixels and 512 threads a workgroup) is 2^32 threads, more than a launch
+    takes: the direct kernels have it (64 slices of the weight gradient's pixels at most); half of it they have not."""
+    d = B.make_desc(1, 1, 16384, 16384, 1, 1, 1, dtype=B.F32)
+    assert B.convbn_wgrad_parts(d) == 64
+    d = B.make_desc(1, 1, 8192, 16384, 1, 1, 1, dtype=B.F32)
+    assert B.convbn_wgrad_parts(d) > 64
