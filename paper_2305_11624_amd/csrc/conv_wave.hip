@@ -260,6 +260,30 @@ __device__ __forceinline__ void conv_body(const WvParams& p, const int block, co
   }
   const int rl = 8 * wave + 4 * half, rr = r0 + rl;
   if (!px.ok || rr >= p.R) return;
+  // A tap in the padding takes no part in a pixel's sum (Sec. 3.1), but the product multiplies it with zeros, and zero
+  // times an infinite weight is NaN: such a sum is formed again over the taps inside, up to its first NaN.  (8 images, 28 x 28, 64 -> 64
+  // channels, forward and backward: 34.9 us without, 35.0 with.)
+  const float nan = (v[0] + v[1]) + (v[2] + v[3]);
+  if (__builtin_expect(nan != nan, 0)) {
+    const int h0 = px.P * csh + ch0, w0 = px.Q * csw + cw0, h1 = h0 + (kh - 1) * dth, w1 = w0 + (kw - 1) * dth;
+    const bool inside = (unsigned)h0 < (unsigned)p.aH && (unsigned)h1 < (unsigned)p.aH && (unsigned)w0 < (unsigned)p.aW &&
+                        (unsigned)w1 < (unsigned)p.aW;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (inside || v[e] == v[e] || rr + e >= p.R) continue;
+      float u = 0.f;
+      for (int i = 0; i < kh && u == u; ++i)
+        for (int j = 0; j < kw && u == u; ++j) {
+          const int h = h0 + i * dth, w = w0 + j * dth;
+          if ((unsigned)h >= (unsigned)p.aH || (unsigned)w >= (unsigned)p.aW) continue;
+          const float* xp = static_cast<const float*>(p.act) + ((size_t)(px.n * p.aH + h) * p.aW + w) * p.C;
+          const float* wp = static_cast<const float*>(p.wgt) +
+                            ((size_t)((rr + e) * p.kH + i0 + i * wsh) * p.kW + j0 + j * wsw) * p.C;
+          for (int c = 0; c < p.C; ++c) u = fmaf(xp[c], wp[c], u);
+        }
+      v[e] = u;
+    }
+  }
   const size_t o = ((size_t)(px.n * p.oH + px.P * osh + oh0) * p.oW + px.Q * osw + ow0) * p.R + rr;
   float* out = static_cast<float*>(p.out) + o;
   const float* add = p.add ? static_cast<const float*>(p.add) + o : nullptr;
@@ -379,6 +403,16 @@ __device__ __forceinline__ void wgrad_body(const WgParams& p, const int block, u
 #pragma unroll
       for (int s = 0; s < KS; ++s) v += red[s][i][lane];
       const int c = it_co * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+      if (__builtin_expect(v != v && c < p.Cout && ci < p.Cin, 0)) {   // (as in conv_body: an infinite dZ where the tap is in the padding)
+        const int h0 = ti - p.ph, w0 = tj + u - p.pw;
+        v = 0.f;
+        for (int m = m0; m < m1 && v == v; ++m) {
+          const int q = (int)((unsigned)m / (unsigned)p.Wo), img = (int)((unsigned)q / (unsigned)p.Ho);
+          const int h = h0 + (q - img * p.Ho) * p.sh, w = w0 + (m - q * p.Wo) * p.sw;
+          if ((unsigned)h >= (unsigned)p.H || (unsigned)w >= (unsigned)p.W) continue;
+          v = fmaf(p.dz[(size_t)m * p.Cout + c], p.x[((size_t)(img * p.H + h) * p.W + w) * p.Cin + ci], v);
+        }
+      }
       if (c < p.Cout && ci < p.Cin)
         p.part[((size_t)slice * p.Cout + c) * taps * p.Cin + (size_t)(tg * TG + u) * p.Cin + ci] = v;
     }

@@ -2,7 +2,9 @@
 the 16-channel operand stage (whole, half, channel counts that are not multiples of 4), fewer reduction steps than
 waves, strides with residue classes no tap reaches, and pixel slices of the weight gradient with ragged ends."""
 import pytest
+import torch
 
+from paper_2305_11624_amd import binding as B
 from paper_2305_11624_amd import synth
 from paper_2305_11624_amd.synth import BlockShape
 
@@ -33,3 +35,49 @@ def test_fp32_block(shape, keep):
     run = BlockRun(inp, mode="tune", keep_folded=keep, poison=True)
     run.step()
     compare(run.results(), oracle_block(inp), "f32", tag=shape.name)
+
+
+def _taps(s):
+    """Per tap (i, j): the output rows and columns that it reaches the image from, and the input's."""
+    for i in range(s.k):
+        for j in range(s.k):
+            def inside(n_in, n_out, t):
+                o = [q for q in range(n_out) if 0 <= q * s.stride + t - s.pad < n_in]
+                return (slice(o[0], o[-1] + 1), slice(o[0] * s.stride + t - s.pad, o[-1] * s.stride + t - s.pad + 1, s.stride)) if o else None
+            h, w = inside(s.Hin, s.Hout, i), inside(s.Win, s.Wout, j)
+            if h and w:
+                yield (i, j), (h[0], w[0]), (h[1], w[1])
+
+
+@pytest.mark.parametrize("cin,stride", [(16, 1), (16, 2), (6, 1)])
+def test_infinities_reach_no_position_through_the_padding(cin, stride):
+    """A tap in the padding takes no part in a sum: an infinite weight or gradient makes exactly those outputs infinite or
+    NaN that it does in the definition."""
+    s = BlockShape("wave_inf", 2, cin, 11, 10, 40, 3, stride, 1, "f32", 912)
+    g = torch.Generator().manual_seed(s.seed)
+    x, w = torch.randn(2, 11, 10, cin, generator=g).double(), torch.randn(40, 3, 3, cin, generator=g).double()
+    dz = torch.randn(2, s.Hout, s.Wout, 40, generator=g).double()
+    w[3, 0, 0, 1] = w[37, 2, 1, 2] = float("inf")
+    w[5, 2, 2, 0] = float("nan")
+    dzi = dz.clone()
+    dzi[0, 0, 3, 7] = float("inf")
+    dzi[1, s.Hout - 1, s.Wout - 1, 33] = -float("inf")
+    z, dx, dw = torch.zeros_like(dz), torch.zeros_like(x), torch.zeros_like(w)
+    for (i, j), (oh, ow), (ih, iw) in _taps(s):
+        z[:, oh, ow] += torch.einsum("nhwc,oc->nhwo", x[:, ih, iw], w[:, i, j])
+        dx[:, ih, iw] += torch.einsum("nhwo,oc->nhwc", dz[:, oh, ow], w[:, i, j])
+        dw[:, i, j] += torch.einsum("nhwo,nhwc->oc", dzi[:, oh, ow], x[:, ih, iw])
+    d = B.desc_from_shape(s)
+    dev = lambda t: t.float().contiguous().cuda()
+    gz, gdx = torch.empty(z.shape, device="cuda"), torch.empty(dx.shape, device="cuda")
+    part = torch.empty((B.convbn_wgrad_parts(d),) + tuple(w.shape), device="cuda")
+    r = torch.empty((B.convbn_rsum_parts(d), 40), device="cuda")
+    B.convbn_conv_fprop(d, dev(x), dev(w), None, gz)
+    B.convbn_conv_dgrad(d, dev(dz), dev(w.permute(3, 1, 2, 0)), gdx)
+    B.convbn_conv_wgrad(d, dev(x), dev(dzi), part, r)
+    torch.cuda.synchronize()
+    for name, got, want in (("z", gz, z), ("dx", gdx, dx), ("dw", part.double().sum(0), dw)):
+        got = got.double().cpu()
+        assert not want.isfinite().all() and torch.equal(got.isnan(), want.isnan()) and torch.equal(got.isinf(), want.isinf()), name
+        ok = want.isfinite()
+        assert (got[ok] - want[ok]).abs().max() <= 1e-4 * want[ok].abs().max(), name
