@@ -341,8 +341,10 @@ convbn_status convbn_fold_group_plan(int n, const convbn_fold_item *items, void 
 convbn_status convbn_fold_group(int n, const void *table_dev, int grid_blocks, void *stream);
 
 /* 1 if convbn_tune_bwd computes this block's weight gradient and fold-back in one launch (deep 3x3
- * layers whose pixels need no split: the fp32 dw' never reaches memory), else 0.  A caller that groups
- * fold-backs (below) leaves such blocks to convbn_tune_bwd. */
+ * layers whose pixels need no split: the fp32 dw' never reaches memory), else 0.  (Where dx is asked
+ * for too and the workgroups of both gradients fit the chip together, they share the launch instead
+ * and a fold-back follows.)  A caller that groups fold-backs (below) leaves such blocks to
+ * convbn_tune_bwd. */
 int32_t convbn_tune_bwd_is_fused(const convbn_desc *desc);
 
 /* The fold-backs of several blocks in ONE launch (Table 2 "Tune", last four lines: dW = s dw',

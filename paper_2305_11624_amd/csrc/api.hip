@@ -99,10 +99,11 @@ WgradWay wgrad_way(const Geom& g0, int dtype) {
   // 3x3 windows share one window tile in wgrad_sq; strided windows hardly overlap, and with few channel pairs its pixel
   // splits, sized for long pixel ranges, write more copies of dw' than that saves (whole steps: 64 channels, 56 x 56, 4
   // images 34.5 -> 31.9 us, 32 images 48.3 -> 53.2; 128 channels, 38 x 38 / 2, 4 images 34.4 -> 32.6; 256 channels,
-  // 28 x 28 / 2, 64 images 90.9 -> 87.2)
-  const bool sq = wgrad_sq_supported(g, dtype) && !pair_taken(g, dtype) &&
+  // 28 x 28 / 2, 64 images 90.9 -> 87.2).  Likewise with few pixels, also where the two gradients are asked for one by one
+  // (ResNet-50, grouped units, 4 images: step 1.81 ms with wgrad_sq, 1.76 without); no split: one launch with the fold-back.
+  const bool sq = wgrad_sq_supported(g, dtype) &&
                   (wgrad_sq_splits(g) == 1 ||
-                   (g.sh == 1 && g.sw == 1 &&
+                   (!pair_taken(g, dtype) && g.sh == 1 && g.sw == 1 &&
                     ((long long)g.Cin * g.Cout > 64 * 64 || (g.M > 32768 && wgrad_dgrad_pair_supported(g, dtype)))));
   if (sq) {
     const int s = wgrad_sq_splits(g);
@@ -181,9 +182,11 @@ TuneBwdWs carve_tune_bwd(const Geom& g, int dtype, void* ws) {
   const WgradWay way = wgrad_way(g, dtype);
   r.nsplit = way.nsplit;
   r.nrpart = way.nrpart;
+  // (room for either of the two ways that backward may take: both gradients in one launch, or this one on its own)
+  const int npair = !needs_cin_pad(g, dtype) && pair_taken(g, dtype) ? win_pair_splits(g) : 0;
   r.w_crsk = c.take((size_t)g.Cout * g.K * esize(dtype));
-  r.dwf_part = (float*)c.take((size_t)r.nsplit * g.Cout * g.K * 4);
-  r.r_part = (float*)c.take((size_t)r.nrpart * g.Cout * 4);
+  r.dwf_part = (float*)c.take((size_t)(npair > r.nsplit ? npair : r.nsplit) * g.Cout * g.K * 4);
+  r.r_part = (float*)c.take((size_t)(npair > r.nrpart ? npair : r.nrpart) * g.Cout * 4);
   r.conv_scratch = (float*)c.take(dgrad_scratch_bytes(g, dtype));
   r.wgrad_scratch = c.take(wgrad_scratch_bytes(g, dtype));
   r.bytes = c.off;
@@ -753,7 +756,8 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.act & CONVBN_ACT_RELU_IN) g.post_mask = x;   // dx comes out masked with x > 0
   g.post_add = g.add_in;                             // ... after the addend
-  if (params && convbn_tune_bwd_is_fused(desc)) {
+  const bool pair = params && dx && !needs_cin_pad(g, dt) && pair_taken(g, dt);
+  if (params && !pair && convbn_tune_bwd_is_fused(desc)) {
     // deep layers: dw', r and the fold-back in one launch (the fp32 dw' never reaches memory); the space of the
     // fp32 copy holds the few partial sums the workgroups exchange.  Where nothing was kept, the same launch leaves
     // w' for the input gradient, which then runs second: no fold launch.
@@ -782,8 +786,7 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
                               dW, db, dgamma, dbeta, st));
       return CONVBN_OK;
     }
-    // ... few pixels: likewise
-    if (params && !needs_cin_pad(g, dt) && pair_taken(g, dt)) {
+    if (pair) {   // ... few pixels: likewise
       const int ns = win_pair_splits(g);
       LAUNCH(launch_win_pair(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       LAUNCH(launch_fold_back(g, dt, w.dwf_part, ns, w.r_part, ns, W, b, gamma, mean, var, 0, dW, db, dgamma, dbeta, st));
@@ -1376,7 +1379,7 @@ int32_t convbn_tune_bwd_is_fused(const convbn_desc* desc) {
   Geom g;
   if (make_geom(desc, &g) != CONVBN_OK) return 0;
   const int dt = desc->dtype;
-  return !needs_cin_pad(g, dt) && wgrad_sq_fused_supported(g, dt) && !pair_taken(g, dt) &&
+  return !needs_cin_pad(g, dt) && wgrad_sq_fused_supported(g, dt) &&
          wgrad_sq_fused_scratch_bytes(g) <= (size_t)wgrad_way(g, dt).nsplit * g.Cout * g.K * 4;
 }
 

@@ -307,3 +307,14 @@ def test_fp32_launches_stay_below_2_32_threads():
     assert B.convbn_wgrad_parts(d) == 64
     d = B.make_desc(1, 1, 8192, 16384, 1, 1, 1, dtype=B.F32)
     assert B.convbn_wgrad_parts(d) > 64
+
+
+def test_weight_gradient_on_its_own_is_planned_as_such():
+    """That both gradients of a small block share a launch concerns convbn_tune_bwd with dx alone.  Deep 3x3 blocks whose
+    pixels need no split keep their one-launch weight gradient and fold-back, hence one fp32 copy of dw' and no part in a
+    unit's grouped fold-back (ResNet-50: the last two stages' 3x3 blocks at one image, the last stage's at more)."""
+    for n, fused in ((1, 8), (2, 3), (4, 3), (32, 3)):
+        blocks = [B.desc_from_shape(s) for s in synth.resnet50_blocks(n, 224, "bf16")]
+        one = [d for d in blocks if B.convbn_tune_bwd_is_fused(d)]
+        assert len(one) == fused, n
+        assert all(B.convbn_wgrad_parts(d) == 1 for d in one)
