@@ -50,11 +50,13 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rsrc, unsigned voff
 __device__ __forceinline__ unsigned lds_off(const void* p) {
   return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
 }
-// LDS reads as inline asm with waits of their own: the compiler would hold them until the copies of the next stage landed
-__device__ __forceinline__ u32x4 lds_read16(unsigned addr) {
-  u32x4 v;
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
-  return v;
+// The operands of a stage: 16 bytes each at g0 and g1 (activations) and 2048 behind them (weights).  Inline asm: the compiler
+// would hold the reads until the copies of the next stage have landed.  The wait is in the same block: registers that a
+// read still writes are nothing the compiler knows of.
+__device__ __forceinline__ void lds_read_stage(unsigned g0, unsigned g1, u32x4& x0, u32x4& w0, u32x4& x1, u32x4& w1) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:2048\n\tds_read_b128 %2, %5\n\t"
+               "ds_read_b128 %3, %5 offset:2048\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(x0), "=&v"(w0), "=&v"(x1), "=&v"(w1) : "v"(g0), "v"(g1) : "memory");
 }
 __device__ __forceinline__ float ldf(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
@@ -209,9 +211,8 @@ __device__ __forceinline__ void conv_body(const WvParams& p, const int block, co
       } else {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
-      u32x4 x0 = lds_read16(g0 + buf), w0 = lds_read16(g0 + buf + 2048);
-      u32x4 x1 = lds_read16(g1 + buf), w1 = lds_read16(g1 + buf + 2048);
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x0), "+v"(w0), "+v"(x1), "+v"(w1) :: "memory");
+      u32x4 x0, w0, x1, w1;
+      lds_read_stage(g0 + buf, g1 + buf, x0, w0, x1, w1);
       acc = mul(w0, x0, acc);
       if (mc + 1 < nch || last_full) acc = mul(w1, x1, acc);
       if (++mc == nch) mc = 0;

@@ -60,9 +60,18 @@ template <int N> __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit field");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// as inline asm, with waits of their own: the compiler would hold every LDS read until the copies in flight have landed
-template <int OFF> __device__ __forceinline__ void tr_read(i32x2& dst, unsigned addr) {
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+// The operands of a 16-pixel step: channels 0-31 of a block's row half (f[0]) and the other half (f[1]), each as pixels 0-3
+// and 4-7 of this lane's eight (512 bytes apart).  Inline asm: the compiler would hold every LDS read until the copies in
+// flight have landed.  The wait is in the same block: registers that a read still writes are nothing the compiler knows of.
+__device__ __forceinline__ void tr_read_step(unsigned a0, unsigned a1, unsigned b0, unsigned b1, i32x2 (&fa)[2][2], i32x2 (&fb)[2][2]) {
+  asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:512\n\t"
+               "ds_read_b64_tr_b16 %2, %10\n\tds_read_b64_tr_b16 %3, %10 offset:512\n\t"
+               "ds_read_b64_tr_b16 %4, %9\n\tds_read_b64_tr_b16 %5, %9 offset:512\n\t"
+               "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:512\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&v"(fa[0][0]), "=&v"(fa[0][1]), "=&v"(fb[0][0]), "=&v"(fb[0][1]), "=&v"(fa[1][0]), "=&v"(fa[1][1]),
+                 "=&v"(fb[1][0]), "=&v"(fb[1][1])
+               : "v"(a0), "v"(a1), "v"(b0), "v"(b1) : "memory");
 }
 
 template <int TA, int TB>
@@ -194,17 +203,11 @@ __device__ __forceinline__ void body(const WwParams& p, const int wg, unsigned c
     for (int u = 0; u < U; ++u) {
       i32x2 fa[2][2], fb[2][2];
       const unsigned a0 = st + a_blk + u * 2048, b0 = st + b_blk + u * 2048;
-      tr_read<0>(fa[0][0], a0 + h0); tr_read<512>(fa[0][1], a0 + h0);
-      tr_read<0>(fb[0][0], b0 + h0); tr_read<512>(fb[0][1], b0 + h0);
-      tr_read<0>(fa[1][0], a0 + h1); tr_read<512>(fa[1][1], a0 + h1);
-      tr_read<0>(fb[1][0], b0 + h1); tr_read<512>(fb[1][1], b0 + h1);
-      if (u == 0) {   // the copies of the chunk NST - 1 ahead, while the operands arrive
+      if (u == 0) {   // the copies of the chunk NST - 1 ahead
 #pragma unroll
         for (int i = 0; i < CPW; ++i) issue_copy(i, fill);
       }
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(fa[0][0]), "+v"(fa[0][1]), "+v"(fb[0][0]), "+v"(fb[0][1]), "+v"(fa[1][0]), "+v"(fa[1][1]), "+v"(fb[1][0]), "+v"(fb[1][1])
-                   :: "memory");
+      tr_read_step(a0 + h0, a0 + h1, b0 + h0, b0 + h1, fa, fb);
       bf16x8 A[2], Bq[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
