@@ -7,13 +7,20 @@ using namespace wgw;
 
 namespace {
 
-// slices of at least two chunks, about `workgroups` in all, and no more fp32 copies of dw' than the inputs weigh (the
-// fold-back reads them all)
+// Slices of the pixels, about `workgroups` in all.  Every slice is an fp32 copy of dw': written here, read by the fold-back, and
+// workspace that the caller holds.  So a slice has at least 128 pixels (two chunks) while the copies stay within 4 MB, else at
+// least 256 (weight gradient and fold-back with slices of 128 and of 256 pixels: 256 -> 128 channels at 56 x 56, 4 images, 98 or 49
+// copies of 0.13 MB 17.9 / 15.2 us; 512 -> 256 at 28 x 28, 4 images, 25 or 13 of 0.5 MB 16.9 / 14.9; 128 -> 512 at 28 x 28,
+// 1 image, 7 or 4 of 0.26 MB 11.1 / 12.1), and the copies weigh no more than the inputs and 8 MB (3x3, 256 channels at 14 x 14,
+// 8 images, 2.4 MB a copy: 4 copies 16.9 us, 1 copy 25.0).
+constexpr size_t SHORT_SLICE_BYTES = (size_t)4 << 20;
 void slice_up(WwParams& p, int workgroups) {
   int want = workgroups / (p.nta * p.ntb);
-  const int most = ceil_div(p.M, 128);
-  if (want > most) want = most;
   const size_t copy = (size_t)p.Co * p.K * 4;
+  const int few = (int)(SHORT_SLICE_BYTES / copy);
+  int most = ceil_div(p.M, 128);
+  if (most > few) most = ceil_div(p.M, 256) > few ? ceil_div(p.M, 256) : few;
+  if (want > most) want = most;
   const int cap = (int)(((size_t)p.x_bytes + p.dz_bytes + ((size_t)8 << 20)) / copy);
   if (want > cap) want = cap;
   if (want < 1) want = 1;

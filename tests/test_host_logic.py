@@ -318,3 +318,15 @@ def test_weight_gradient_on_its_own_is_planned_as_such():
         one = [d for d in blocks if B.convbn_tune_bwd_is_fused(d)]
         assert len(one) == fused, n
         assert all(B.convbn_wgrad_parts(d) == 1 for d in one)
+
+
+@pytest.mark.parametrize("n", [1, 2, 4, 8, 32])
+def test_copies_of_the_weight_gradient_are_long_slices_or_small(n):
+    """The window weight gradient's fp32 copies are workspace: beyond 4 MB in all, each stands for at least 256 pixels."""
+    odd = synth.BlockShape("odd", n, 72, 61, 45, 136, 5, 2, 2, "bf16", 1)
+    for s in [b for b in synth.resnet50_blocks(n, 224, "bf16") if b.k == 1] + [odd]:
+        if s.Cin % 8:
+            continue
+        d = B.desc_from_shape(s)
+        copy, m = 4 * s.Cout * s.K, s.N * s.Hout * s.Wout
+        assert B.convbn_wgrad_parts(d) * copy <= max(4 << 20, -(-m // 256) * copy), s.name
