@@ -323,7 +323,7 @@ size_t stem_input_copy_bytes(const Geom& g);      // scratch for a 4-channel cop
 hipError_t launch_fprop_stem(const Geom& g, const void* x, const void* w, void* wpad, const float* bias, void* z,
                              hipStream_t st);
 
-// conv_igemm.hip : bf16 MFMA implicit GEMM
+// conv_igemm.hip : bf16 MFMA implicit GEMM with 64-bit addresses, for tensors of 2 GB and more (channels multiples of 8)
 bool igemm_supported(const Geom& g, int dtype);
 int wgrad_splits(const Geom& g);
 hipError_t launch_fprop_igemm(const Geom& g, const void* x, const void* w_krsc, const float* bias,

@@ -1,7 +1,8 @@
 // Direct convolution kernels: one thread per output element, fp32 accumulation.
-// They serve the fp32 problems and every bf16 shape the MFMA path does not take
-// (channel counts that are not multiples of 8).  Cross-correlation, zero padding
-// (Sec. 3.1); input gradient = adjoint of the forward gather (Sec. 3.2.1).
+// They serve the fp32 problems with a tensor of 2 GB and more (the others: conv_wave.hip) and the
+// bf16 shapes that no MFMA kernel takes (channel counts that are not multiples of 8).
+// Cross-correlation, zero padding (Sec. 3.1); input gradient = adjoint of the forward gather
+// (Sec. 3.2.1).
 #include "common.h"
 
 namespace convbn {

@@ -11,6 +11,7 @@
 // per lane per MFMA operand.  fprop/dgrad read activations with the reduced index
 // already contiguous in memory (channels-last); wgrad reduces over pixels, which are
 // strided in memory, so its loaders transpose 8x8 blocks in registers on the way in.
+// It serves the problems with a tensor of 2 GB and more: the other kernels' byte offsets end there.
 #include "common.h"
 
 namespace convbn {

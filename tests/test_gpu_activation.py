@@ -20,12 +20,12 @@ SHAPES = [
     BlockShape("act_pw_1x1_wide", 5, 64, 28, 28, 256, 1, 1, 0, "bf16", 302),
     BlockShape("act_pw_strided", 4, 256, 28, 28, 512, 1, 2, 0, "bf16", 303),      # a downsampling shortcut
     BlockShape("act_shallow_3x3", 9, 64, 47, 53, 64, 3, 1, 1, "bf16", 304),       # weight and window resident in LDS
-    BlockShape("act_deep_3x3", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 305),         # deep-layer kernel, fused weight gradient
+    BlockShape("act_deep_3x3", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 305),         # split sums + their reduction, fused weight gradient
     BlockShape("act_mid_3x3", 6, 128, 28, 28, 128, 3, 1, 1, "bf16", 306),         # LDS-tile kernel
     BlockShape("act_mid_3x3_s2", 6, 128, 28, 28, 128, 3, 2, 1, "bf16", 307),      # strided: residue classes in the input gradient
-    BlockShape("act_split_sums", 2, 256, 14, 14, 256, 3, 1, 1, "bf16", 308),      # split sums + their reduction
+    BlockShape("act_split_sums", 2, 256, 14, 14, 256, 3, 1, 1, "bf16", 308),    # few pixels, a 36-chunk reduction: window product
     BlockShape("act_stem", 2, 3, 64, 64, 64, 7, 2, 3, "bf16", 309),               # first layer: padded channels
-    BlockShape("act_odd_bf16", 2, 24, 9, 11, 40, 3, 1, 1, "bf16", 310),           # generic kernels
+    BlockShape("act_odd_bf16", 2, 24, 9, 11, 40, 3, 1, 1, "bf16", 310),           # no channel count fits a tile: window product
     BlockShape("act_gm_fwd_256", 5, 128, 31, 33, 1024, 1, 1, 0, "bf16", 313),    # tiled matrix product, 256-pixel tiles, ragged tail
     BlockShape("act_gm_fwd_128", 5, 192, 31, 33, 512, 1, 1, 0, "bf16", 314),     # ... 128-pixel tiles, three chunks
     BlockShape("act_gm_bwd", 5, 1024, 31, 33, 128, 1, 1, 0, "bf16", 315),        # ... in the input gradient
@@ -38,6 +38,7 @@ SHAPES = [
     BlockShape("act_gm_strided", 30, 256, 27, 29, 512, 1, 2, 0, "bf16", 322),    # ... a downsampling shortcut: gathered / scattered rows
     BlockShape("act_f32", 2, 16, 12, 10, 24, 3, 1, 1, "f32", 311),
     BlockShape("act_f32_ragged", 1, 5, 7, 9, 7, 3, 2, 1, "f32", 312),             # element counts that are not multiples of 8
+    BlockShape("act_split_sums_ragged", 3, 384, 13, 11, 320, 3, 1, 1, "bf16", 323),   # split sums + their reduction, both passes
 ]
 BOTH = B.ACT_RELU_OUT | B.ACT_RELU_IN
 

@@ -1,0 +1,79 @@
+"""GPU parity of tensors beyond 2 GiB, which the kernels with 32-bit byte offsets decline: bf16 runs the implicit GEMM
+(conv_igemm.hip), fp32 one thread per output (conv_direct.hip).  One 3x3 block, Tune mode; three images are compared,
+one of them across the 2 GiB line, against the definition in fp64, and the others' input gradient is zero."""
+import pytest
+import torch
+import torch.nn.functional as F
+
+from paper_2305_11624_amd import binding as B
+
+from helpers import TOL
+
+pytestmark = pytest.mark.gpu
+
+N, H, W, K = 33, 2050, 2047, 3
+IMAGES = (0, 31, 32)   # (16 bytes a pixel: the 2 GiB line is in image 31)
+ROWS = (slice(0, 8), slice(H // 2, H // 2 + 8), slice(H - 8, H))   # rows that have a gradient: sums short enough for fp32
+
+
+@pytest.mark.parametrize("dtype,cin,cout", [("bf16", 8, 8), ("f32", 4, 4)])
+def test_block_beyond_2_gib(dtype, cin, cout):
+    g = torch.Generator(device="cuda").manual_seed(951)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    d = B.make_desc(N, cin, H, W, cout, K, K, 1, 1, dtype=B.BF16 if dtype == "bf16" else B.F32)
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    x, dz = torch.empty((N, H, W, cin), dtype=dt, device="cuda"), torch.zeros((N, H, W, cout), dtype=dt, device="cuda")
+    assert x.nbytes > 1 << 31 and x[31].data_ptr() - x.data_ptr() < 1 << 31 < x[32].data_ptr() - x.data_ptr()
+    for n in range(N):
+        x[n] = normal(H, W, cin)
+    for n in IMAGES:
+        for r in ROWS:
+            dz[n, r] = normal(8, W, cout)
+    w = (normal(cout, K, K, cin) * 0.2).to(dt)
+    gamma, var = torch.rand(cout, generator=g, device="cuda") + 0.5, torch.rand(cout, generator=g, device="cuda") + 0.5
+    b, beta, mean = normal(cout), normal(cout), normal(cout)
+    nan = lambda like: torch.full_like(like, float("nan"))
+    z, dx, dw, wf = nan(dz), nan(x), nan(w), torch.empty((cin, K, K, cout), dtype=dt, device="cuda")
+    db, dgamma, dbeta = nan(b), nan(gamma), nan(beta)
+    ws = [torch.empty(max(16, B.convbn_workspace_bytes(d, B.MODE_TUNE, p)), dtype=torch.uint8, device="cuda")
+          for p in (B.PASS_FWD, B.PASS_BWD)]
+    print(dtype, "forward", flush=True)
+    B.convbn_tune_fwd(d, x, w, b, gamma, beta, mean, var, z, wf, ws[0])
+    torch.cuda.synchronize()
+    print(dtype, "backward", flush=True)
+    B.convbn_tune_bwd(d, x, w, b, gamma, mean, var, wf, dz, dx, dw, db, dgamma, dbeta, ws[1])
+    torch.cuda.synchronize()
+
+    def close(got, ref, what):
+        err = (got.double() - ref).abs().max() / ref.abs().max()
+        assert err <= TOL[dtype], (what, err.item())
+
+    wd, isd = w.double(), 1.0 / (var.double() + d.eps).sqrt()
+    s = gamma.double() * isd
+    taps = [(i, j) for i in range(K) for j in range(K)]
+    pad = lambda t: F.pad(t.double(), (0, 0, 1, 1, 1, 1))
+    rdw, rdgamma, r = torch.zeros_like(wd), torch.zeros_like(s), torch.zeros_like(s)
+    for n in IMAGES:
+        xp, zp = pad(x[n]), pad(dz[n])
+        y = torch.zeros((H * W, cout), dtype=torch.float64, device="cuda")
+        rdx = torch.zeros((H * W, cin), dtype=torch.float64, device="cuda")
+        for i, j in taps:
+            xt = xp[i:i + H, j:j + W].reshape(-1, cin)
+            y += xt @ wd[:, i, j].t().contiguous()
+            rdx += zp[2 - i:2 - i + H, 2 - j:2 - j + W].reshape(-1, cout) @ (wd[:, i, j] * s[:, None])
+            for q in ROWS:
+                xq = xp[q.start + i:q.stop + i, j:j + W].reshape(-1, 1, cin)
+                rdw[:, i, j] += (dz[n, q].double().reshape(-1, cout, 1) * xq).sum(0) * s[:, None]
+        y += b.double() - mean.double()
+        close(z[n].reshape(-1, cout), y * s + beta.double(), ("Z", n))
+        close(dx[n].reshape(-1, cin), rdx, ("dX", n))
+        for q in ROWS:
+            dzq = dz[n, q].double().reshape(-1, cout)
+            rdgamma += (dzq * y[q.start * W:q.stop * W]).sum(0) * isd
+            r += dzq.sum(0)
+    close(dw, rdw, "dW")
+    close(dgamma, rdgamma, "dgamma")
+    close(dbeta, r, "dbeta")
+    close(db, r * s, "db")
+    for n in range(1, 31):
+        assert not dx[n].any(), n

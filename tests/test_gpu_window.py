@@ -24,7 +24,8 @@ SHAPES = [
     BlockShape("win_stride2_512", 9, 512, 14, 13, 512, 3, 2, 1, "bf16", 927),         # weight larger than the activations
     BlockShape("win_stride2_1x1", 4, 192, 13, 15, 320, 1, 2, 0, "bf16", 928),         # three classes without a tap
     BlockShape("win_stride3_2x2", 2, 32, 16, 17, 48, 2, 3, 0, "bf16", 929),           # nine classes, five without a tap
-    BlockShape("win_stride2_wide", 40, 128, 30, 30, 256, 3, 2, 1, "bf16", 930),       # 256-pixel tiles
+    BlockShape("win_stride2_wide", 40, 128, 30, 30, 256, 3, 2, 1, "bf16", 930),       # 128-pixel tiles of 64 (forward) and 128 channels
+    BlockShape("win_stride2_256", 90, 128, 30, 30, 256, 3, 2, 1, "bf16", 944),        # 256-pixel tiles (from 160 on: 80 x 2, and 4 x 80), the last ragged
     BlockShape("win_small_1x1", 2, 256, 9, 11, 1024, 1, 1, 0, "bf16", 931),
     BlockShape("gm_fold_aside", 7, 128, 28, 28, 512, 1, 1, 0, "bf16", 932),           # pointwise product, folds on the side
     BlockShape("gm_long_runs", 40, 256, 30, 33, 192, 1, 1, 0, "bf16", 933),
@@ -64,7 +65,7 @@ def test_block(shape, keep):
 
 def test_addend_reaches_positions_no_tap_does():
     from paper_2305_11624_amd.runner import BlockRun
-    shape = SHAPES[7]
+    shape = next(s for s in SHAPES if s.name == "win_stride2_1x1")
     inp = synth.make_inputs(shape)
     add = torch.randn((shape.N, shape.Hin, shape.Win, shape.Cin), generator=torch.Generator().manual_seed(5)).bfloat16().cuda()
     run = BlockRun(inp, mode="tune", poison=True, act=B.ACT_ADD_IN, add_in=add)

@@ -11,7 +11,8 @@ from helpers import TOL, oracle_block, rel_err
 
 pytestmark = pytest.mark.gpu
 
-FIRST = BlockShape("na_big", 8, 256, 14, 14, 256, 3, 1, 1, "bf16", 71)      # split sums: part of the workspace is fp32 partials
+FIRST = BlockShape("na_big", 8, 256, 14, 14, 256, 3, 1, 1, "bf16", 71)
+SPLIT = BlockShape("na_split", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 73)      # split sums: part of the workspace is fp32 partials
 SECOND = BlockShape("na_small", 2, 64, 9, 11, 72, 3, 1, 1, "bf16", 72)
 
 
@@ -49,6 +50,8 @@ def _run(shape, B):
 
 def test_static_workspace_forward_two_calls_in_a_row():
     from paper_2305_11624_amd import binding as B
+    assert B.convbn_conv_workspace_bytes(B.desc_from_shape(SPLIT), B.PASS_FWD) > 0
+    _run(SPLIT, B)
     _run(FIRST, B)
     _run(SECOND, B)     # a smaller block right after: the array still holds the first call's bytes
 
