@@ -326,7 +326,13 @@ constexpr int MIN_TILES_SMALL = 96;  // down to this many (measured against the 
                                      // 1024 -> 256 at 14 x 14, 98 tiles, 10.8 against 12.0 us)
 constexpr int MAX_PIXELS = 32768;    // longer pixel ranges with short reductions stream through the weight-stationary kernel
 
-constexpr size_t LONG_OUTPUT = 32u << 20, LONG_STREAM = 48u << 20;   // bytes written, read and written
+// Bytes written, read and written, from which on the channel tiles of a pixel tile follow one another on an XCD
+// (ORDER_TOGETHER) instead of each XCD taking a run of the tiles.  Forward, together / runs, ten channel counts from 64 to 2048:
+// above the line 1-13 % in favour of together (64 -> 256, 160 MB 36.8 / 41.6 us; 1024 -> 256, 70 MB 22.5 / 22.7), but for launches
+// whose pixel tiles, rounded up to eights, need one more round (512 -> 2048, 46 MB 38.5 / 34.0).  Below it the two are within 4 %
+// for most, and that round costs more (512 -> 2048, 26 MB 26.2 / 20.9; 512 -> 512, 34 MB 24.4 / 21.1); 64 -> 256 and
+// 128 -> 512 gain 4-9 % together from 14 MB on (20 MB 7.0 / 7.6).
+constexpr size_t LONG_OUTPUT = 32u << 20, LONG_STREAM = 48u << 20;
 
 struct GmPlan { int tm, res, tn, ns; };   // tm == 0: not taken
 
