@@ -75,3 +75,16 @@ def test_addend_reaches_positions_no_tap_does():
     B.convbn_aux_eltwise(B.OP_ADD, plain.dx, add)
     torch.cuda.synchronize()
     assert torch.equal(run.dx, plain.dx)
+
+
+@pytest.mark.parametrize("name", ["win_72_136", "win_stride2_wide", "gm_fold_aside", "gm_two_stages_4_chunks"])
+def test_forward_rounds_once(name):
+    """Z = s (w (*) X) + b' with s and b' in the epilogue: fp32 up to the one rounding to bf16 on the way out, which is at
+    most 2^-9 of a value, hence of the 2-norm (1e-5: the fp32 sums).  A product of the rounded w' is further off (2.3e-3)."""
+    from paper_2305_11624_amd.runner import BlockRun
+    inp = synth.make_inputs(next(s for s in SHAPES if s.name == name), bias=True)
+    run = BlockRun(inp, mode="tune", poison=True)
+    run.forward()
+    ref = oracle_block(inp, need_dx=False)["Z"]
+    err = np.linalg.norm(run.results()["Z"].numpy() - ref) / np.linalg.norm(ref)
+    assert err <= 2.0 ** -9 + 1e-5, err
