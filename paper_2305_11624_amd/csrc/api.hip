@@ -523,12 +523,18 @@ DwBwdWs carve_dw_bwd(const Geom& g, int dtype, int mode, void* ws) {
   Carve c(ws);
   DwBwdWs r;
   const int taps = g.kH * g.kW;
-  r.slices = dw_wgrad_slices(g, dtype);
   r.nparts = bn_bwd_parts(g);
-  r.wf = c.take((size_t)taps * g.Cin * esize(dtype));
-  r.part = (float*)c.take((size_t)r.slices * taps * g.Cin * 4);
-  r.r_part = (float*)c.take((size_t)r.slices * g.Cin * 4);
-  r.sums = (float*)c.take((size_t)(taps + 1) * g.Cin * 4);
+  if (dw3_supported(g, dtype)) {   // (folded and summed without scratch of their own)
+    r.slices = 0;
+    r.wf = nullptr; r.r_part = nullptr; r.sums = nullptr;
+    r.part = (float*)c.take(dw3_part_bytes(g));
+  } else {
+    r.slices = dw_wgrad_slices(g, dtype);
+    r.wf = c.take((size_t)taps * g.Cin * esize(dtype));
+    r.part = (float*)c.take((size_t)r.slices * taps * g.Cin * 4);
+    r.r_part = (float*)c.take((size_t)r.slices * g.Cin * 4);
+    r.sums = (float*)c.take((size_t)(taps + 1) * g.Cin * 4);
+  }
   r.dy = nullptr; r.bn_part = nullptr;
   if (mode == CONVBN_MODE_EVAL) {
     r.dy = c.take((size_t)g.M * g.Cout * esize(dtype));
@@ -1047,6 +1053,10 @@ convbn_status convbn_dw_tune_fwd(const convbn_desc* desc, const void* x, const v
   if (s != CONVBN_OK) return s;
   const DwFwdWs w = carve_dw_fwd(g, dt, ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (dw3_supported(g, dt)) {
+    LAUNCH(launch_dw3_fprop(g, x, W, b, gamma, beta, mean, var, z, w_folded, st));
+    return CONVBN_OK;
+  }
   void* wf = w_folded ? w_folded : w.wf;
   LAUNCH(launch_dw_fold(g, dt, W, b, gamma, beta, mean, var, wf, w.bfold, st));   // w' = s w (tap-major), b'
   LAUNCH(launch_dw_fprop(g, dt, x, wf, w.bfold, z, st));                          // Z = w' (*) X + b'
@@ -1077,6 +1087,11 @@ convbn_status convbn_dw_tune_bwd(const convbn_desc* desc, const void* x, const v
   if (s != CONVBN_OK) return s;
   const DwBwdWs w = carve_dw_bwd(g, dt, CONVBN_MODE_TUNE, ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (dw3_supported(g, dt)) {
+    LAUNCH(launch_dw3_bwd(g, x, dz, W, w_folded, gamma, var, dx, params ? w.part : nullptr, st));
+    if (params) LAUNCH(launch_dw3_fold_back(g, w.part, W, b, gamma, mean, var, dW, db, dgamma, dbeta, st));
+    return CONVBN_OK;
+  }
   if (dx) {
     const void* wf = w_folded;
     if (!wf) {
@@ -1107,8 +1122,12 @@ convbn_status convbn_dw_eval_fwd(const convbn_desc* desc, const void* x, const v
   if (s != CONVBN_OK) return s;
   const DwFwdWs w = carve_dw_fwd(g, dt, ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  LAUNCH(launch_dw_fold(g, dt, W, b, nullptr, nullptr, nullptr, nullptr, w.wf, w.bfold, st));   // reorder only
-  LAUNCH(launch_dw_fprop(g, dt, x, w.wf, w.bfold, y_saved, st));                                 // Y = w (*) X + b
+  if (dw3_supported(g, dt)) {
+    LAUNCH(launch_dw3_fprop(g, x, W, b, nullptr, nullptr, nullptr, nullptr, y_saved, nullptr, st));
+  } else {
+    LAUNCH(launch_dw_fold(g, dt, W, b, nullptr, nullptr, nullptr, nullptr, w.wf, w.bfold, st));   // reorder only
+    LAUNCH(launch_dw_fprop(g, dt, x, w.wf, w.bfold, y_saved, st));                                 // Y = w (*) X + b
+  }
   LAUNCH(launch_bn_affine_fwd(g, dt, y_saved, gamma, beta, mean, var, z, st));                   // Z from Y
   return CONVBN_OK;
 }
@@ -1139,6 +1158,12 @@ convbn_status convbn_dw_eval_bwd(const convbn_desc* desc, const void* x, const v
   hipStream_t st = static_cast<hipStream_t>(stream);
   LAUNCH(launch_bn_bwd(g, dt, dz, y_saved, gamma, mean, var, w.dy, w.bn_part, st));
   if (params) LAUNCH(launch_bn_bwd_finalize(g, w.bn_part, w.nparts, gamma, var, dgamma, dbeta, db, st));
+  if (dw3_supported(g, dt)) {
+    LAUNCH(launch_dw3_bwd(g, x, w.dy, W, nullptr, nullptr, nullptr, dx, params ? w.part : nullptr, st));
+    if (params)
+      LAUNCH(launch_dw3_fold_back(g, w.part, W, nullptr, nullptr, nullptr, nullptr, dW, nullptr, nullptr, nullptr, st));
+    return CONVBN_OK;
+  }
   if (dx) {
     LAUNCH(launch_dw_fold(g, dt, W, nullptr, nullptr, nullptr, nullptr, nullptr, w.wf, nullptr, st));
     LAUNCH(launch_dw_dgrad(g, dt, w.dy, w.wf, dx, st));

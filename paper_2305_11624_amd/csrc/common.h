@@ -32,7 +32,10 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
   return (uint32_t)__builtin_bit_cast(unsigned short, h);
 }
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {lo, hi};   // one conversion for the pair (two, a shift and an or if they are rounded one by one)
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -274,6 +277,21 @@ hipError_t launch_dw_wgrad(const Geom& g, int dtype, const void* x, const void* 
 hipError_t launch_dw_fold_back(const Geom& g, int dtype, const float* part, const float* r_part, int slices,
                                float* sums, const void* W, const float* b, const float* gamma, const float* mean,
                                const float* var, void* dW, float* db, float* dgamma, float* dbeta, hipStream_t st);
+
+// ... 3x3 windows with stride 1 or 2 and paddings up to 2, bf16, channels multiples of 8: the filter is folded by the threads
+// that use it (w is the unfolded [C][9] filter, gamma == null: s = 1), forward leaves w_folded [9][C] on the side (or
+// null), and backward's two gradients are one launch (w_folded: what forward kept, or null; dx or part may be null; part:
+// dw3_part_bytes()).
+bool dw3_supported(const Geom& g, int dtype);
+size_t dw3_part_bytes(const Geom& g);
+hipError_t launch_dw3_fprop(const Geom& g, const void* x, const void* W, const float* b, const float* gamma,
+                            const float* beta, const float* mean, const float* var, void* z, void* w_folded,
+                            hipStream_t st);
+hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const void* W, const void* w_folded,
+                          const float* gamma, const float* var, void* dx, float* part, hipStream_t st);
+hipError_t launch_dw3_fold_back(const Geom& g, const float* part, const void* W, const float* b, const float* gamma,
+                                const float* mean, const float* var, void* dW, float* db, float* dgamma, float* dbeta,
+                                hipStream_t st);
 
 // conv_grouped.hip : the three contractions of a grouped block (groups divides g.Cin and g.Cout; cg = Cin / groups).
 // w_krsc is [Cout][kH][kW][cg], w_crsk [cg][kH][kW][Cout]; part [slices][Cout][kH kW cg] fp32.  Where

@@ -117,267 +117,674 @@ __global__ __launch_bounds__(256) void dw_dgrad_kernel(const T* __restrict__ dz,
   Vec<T, VEC>::store(dx + idx * VEC, acc);
 }
 
-// 3x3 windows, stride S, bf16, C % 8 == 0: a thread owns 8 channels of SEG vertically consecutive outputs of one
-// output column.  It first issues every load of the ((SEG-1) S + 3) x 3 input patch those outputs need (kept packed, 16
-// bytes each, so all of them are in flight together and the memory latency is paid once per thread), keeps the
-// filter (9 x 8 values) in registers, and pays the index arithmetic once per segment: the generic kernel above
-// spends its time on integer divisions, on re-reading the filter and on nine dependent trips to memory.
-//   out[n][ho][wo][c] = bias[c] + sum_{i,j} wf[tap(i,j)][c] in[n][ho S + i - ph][wo S + j - pw][c]
-// FLIP (input gradient of a stride-1 convolution): tap(i,j) is the rotated one, in = dZ, ph = 2 - ph.
-constexpr int patch_seg(int S) { return S == 1 ? 4 : 3; }
+// ---- 3x3 windows, stride 1 or 2, paddings 0..2, bf16, C % 8 == 0 ------------------------------------------------
+// A pass has to move its tensors once and multiply 9 times per element (18 with the weight gradient), so two things
+// bound it: the bytes in flight, and the vector unit.  A thread owns 4 channels (8 bytes; consecutive threads =
+// consecutive channels, then columns) of two neighbouring columns and slides down R rows: an input row is requested
+// two steps (stride 2: one) before it is used, widened once, and multiplied into the three output rows that it
+// reaches, which live in registers; the column overlap is re-read from the L1 (4 columns for 2 outputs).  Input gradient
+// and weight gradient are one sweep -- dx and dw' both need dZ, and the pixel that owns a dx element owns its x too, so
+// the halo is one tensor's --, and the filter is folded by the threads that use it: a forward pass is one launch, a
+// backward pass two.  Before (a thread per four outputs of one column, all loads of its patch up front, each pass and
+// the fold a launch of its own): 144 channels at 56 x 56, 32 images, @BEFORE@; now @AFTER@.
+// Out-of-image loads and stores are offsets beyond the buffer, which read zeros and are dropped.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+constexpr int DW_BLK = 512;              // threads of a workgroup
+constexpr int DW_MAXQ = 64;              // channel quads of a workgroup (the others are its columns)
+constexpr unsigned DW_INV = 1u << 30;    // row or column offset of nothing; twice that is still no valid offset
 
-__device__ __forceinline__ void unpack8(const uint4& t, float (&v)[8]) {
+struct Dw3Params {
+  const bf16_t* a;       // the tensor with the halo: x (forward), dZ (backward)
+  const bf16_t* y;       // weight gradient: x
+  bf16_t* out;           // z or dx
+  const bf16_t* W;       // [C][9], or the folded filter [9][C] (tap_major)
+  const float *b, *gamma, *beta, *mean, *var;   // gamma == null: s = 1; b' is added where `bias`
+  bf16_t* wf_out;        // forward: where the folded filter [9][C] is left, or null
+  float* part;           // weight gradient: [C / 8][slices_all][10][8], row 9 the channel sums of dZ
+  float eps;
+  int tap_major, flip, bias;
+  int N, C, Ha, Wa, Ho, Wo;     // images; a's and out's (and y's) planes
+  int pa, pb;                   // a's row for output row o and window row i: o S + i - pa
+  int u0, v0;                   // stride 2 backward: the first dZ row and column a thread owns
+  int R, nstrip, npair, cq, items, per_slice, slice0, slices_all;
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dw_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x2 dw_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void dw_store(__amdgpu_buffer_rsrc_t r, unsigned off, const float (&v)[4]) {
+  u32x2 t;
+  t.x = pack_bf16x2(v[0], v[1]);
+  t.y = pack_bf16x2(v[2], v[3]);
+  __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)off, 0, 0);
+}
+__device__ __forceinline__ void unpack4(u32x2 t, float (&v)[4]) {
   v[0] = bf16_lo(t.x); v[1] = bf16_hi(t.x); v[2] = bf16_lo(t.y); v[3] = bf16_hi(t.y);
-  v[4] = bf16_lo(t.z); v[5] = bf16_hi(t.z); v[6] = bf16_lo(t.w); v[7] = bf16_hi(t.w);
 }
 
-template <int S, bool FLIP>
-__global__ __launch_bounds__(256) void dw_patch3_kernel(const bf16_t* __restrict__ in, const bf16_t* __restrict__ wf,
-                                                      const float* __restrict__ bias, bf16_t* __restrict__ out, int N,
-                                                      int Hi, int Wi, int Ho, int Wo, int C, int ph, int pw, int nseg) {
-  // the SEG outputs are consecutive along H: consecutive threads are then consecutive (channel group, column)
-  // pairs of one row and every load of the wave is one contiguous kilobyte
-  constexpr int K = 3, SEG = patch_seg(S), NR = (SEG - 1) * S + K;
-  const int cgs = C >> 3;
-  const unsigned id = blockIdx.x * 256u + threadIdx.x;
-  if (id >= (unsigned)N * nseg * Wo * cgs) return;
-  const int cg = id % cgs;
-  unsigned t = id / cgs;
-  const int wo = t % Wo;
-  t /= Wo;
-  const int sg = t % nseg, n = t / nseg;
-  const int c = cg * 8;
-  const int ho0 = sg * SEG;
-  // the input patch, then the filter: every load is issued before the first use
-  uint4 xr[NR][K];
+// Workgroups are handed to the eight XCDs in turn: neighbouring slices, which share rows, go to one XCD and its L2.
+__device__ __forceinline__ int dw_slice() {
+  const int n = gridDim.y, b = blockIdx.y;
+  return gridDim.x == 1 && n % 8 == 0 ? (b & 7) * (n >> 3) + (b >> 3) : b;
+}
+
+// The filter of a thread's 4 channels (s already in it) and their b'; a forward launch leaves w' on the side.
+__device__ __forceinline__ void dw_filter(const Dw3Params& p, int c, float (&t)[9][4], float (&bb)[4]) {
+  // (every load is issued before the first use; a vector that is not there is read from the filter, which is larger)
+  const float* const any = reinterpret_cast<const float*>(p.W);
+  const float4 ga = *reinterpret_cast<const float4*>((p.gamma ? p.gamma : any) + c);
+  const float4 va = *reinterpret_cast<const float4*>((p.gamma ? p.var : any) + c);
+  const float4 me = *reinterpret_cast<const float4*>((p.bias && p.gamma ? p.mean : any) + c);
+  const float4 be = *reinterpret_cast<const float4*>((p.bias && p.gamma ? p.beta : any) + c);
+  const float4 bi = *reinterpret_cast<const float4*>((p.bias && p.b ? p.b : any) + c);
+  const float gv[4] = {ga.x, ga.y, ga.z, ga.w}, vv[4] = {va.x, va.y, va.z, va.w}, mv[4] = {me.x, me.y, me.z, me.w};
+  const float ev[4] = {be.x, be.y, be.z, be.w}, iv[4] = {bi.x, bi.y, bi.z, bi.w};
+  float s[4];
 #pragma unroll
-  for (int q = 0; q < NR; ++q) {
-    const int h = ho0 * S + q - ph;
-    const bool rok = (unsigned)h < (unsigned)Hi;
-    const bf16_t* rowp = in + ((size_t)n * Hi + (rok ? h : 0)) * Wi * C + c;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const int w = wo * S + j - pw;
-      xr[q][j] = (rok && (unsigned)w < (unsigned)Wi) ? *reinterpret_cast<const uint4*>(rowp + (size_t)w * C)
-                                                     : make_uint4(0u, 0u, 0u, 0u);
-    }
+  for (int e = 0; e < 4; ++e) {
+    s[e] = p.gamma ? gv[e] / sqrtf(vv[e] + p.eps) : 1.f;
+    const float b0 = p.b ? iv[e] : 0.f;
+    bb[e] = !p.bias ? 0.f : p.gamma ? (b0 - mv[e]) * s[e] + ev[e] : b0;
   }
-  float wv[K * K][8], bv[8];
+  float w[9][4];
+  if (p.tap_major) {
 #pragma unroll
-  for (int q = 0; q < K * K; ++q) Vec<bf16_t, 8>::load(wf + (size_t)(FLIP ? K * K - 1 - q : q) * C + c, wv[q]);
+    for (int q = 0; q < 9; ++q) unpack4(*reinterpret_cast<const u32x2*>(p.W + (size_t)q * p.C + c), w[q]);
+  } else {
+    unsigned raw[18];   // 36 consecutive values: element e * 9 + q is channel e, tap q
 #pragma unroll
-  for (int e = 0; e < 8; ++e) bv[e] = bias ? bias[c + e] : 0.f;
-  // every patch element is widened once and multiplied into each output that covers it
-  float acc[SEG][8];
+    for (int k = 0; k < 9; ++k) {
+      const u32x2 v = *reinterpret_cast<const u32x2*>(p.W + (size_t)c * 9 + 4 * k);
+      raw[2 * k] = v.x;
+      raw[2 * k + 1] = v.y;
+    }
 #pragma unroll
-  for (int o = 0; o < SEG; ++o)
+    for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[o][e] = bv[e];
-#pragma unroll
-  for (int q = 0; q < NR; ++q)
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      float xv[8];
-      unpack8(xr[q][j], xv);
-#pragma unroll
-      for (int o = 0; o < SEG; ++o) {
-        const int i = q - o * S;
-        if (i < 0 || i >= K) continue;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[o][e] += xv[e] * wv[i * K + j][e];
+      for (int q = 0; q < 9; ++q) {
+        const int k = e * 9 + q;
+        w[q][e] = ((k & 1) ? bf16_hi(raw[k >> 1]) : bf16_lo(raw[k >> 1])) * s[e];
       }
-    }
-#pragma unroll
-  for (int o = 0; o < SEG; ++o)
-    if (ho0 + o < Ho) Vec<bf16_t, 8>::store(out + (((size_t)n * Ho + ho0 + o) * Wo + wo) * C + c, acc[o]);
-}
-
-// Input gradient of a 3x3 stride-2 depthwise convolution, same idea as the patch kernel: 8 channels of 4
-// consecutive dX pixels of one row (first pixel even).  dX[h][w] = sum over the taps (i, j) with h + ph - i and
-// w + pw - j even of wf[i][j] dZ[(h + ph - i)/2][(w + pw - j)/2]: at most two dZ rows (which ones depends on the
-// parity of h: rows that do not qualify are loaded as zeros) and exactly three dZ columns, the even ones among
-// w0 + pw - 2 .. w0 + pw + 3, whose parity pattern is the same for every thread.
-__global__ __launch_bounds__(256) void dw_dgrad_s2_patch3_kernel(const bf16_t* __restrict__ dz, const bf16_t* __restrict__ wf,
-                                                               bf16_t* __restrict__ dx, int N, int Hin, int Win, int Ho,
-                                                               int Wo, int C, int ph, int pw, int nseg) {
-  constexpr int K = 3, SEG = 4;
-  const int cgs = C >> 3;
-  const unsigned id = blockIdx.x * 256u + threadIdx.x;
-  if (id >= (unsigned)N * Hin * nseg * cgs) return;
-  const int cg = id % cgs;
-  unsigned t = id / cgs;
-  const int sg = t % nseg;
-  t /= nseg;
-  const int h = t % Hin, n = t / Hin;
-  const int c = cg * 8;
-  const int w0 = sg * SEG;
-  const int base = w0 + pw - 2;                 // smallest w + pw - j of the segment
-  const int par = base & 1;                     // its parity: the same for every thread (w0 is even)
-  const int wo_first = (base + par) >> 1;       // first of the three dZ columns (may be negative: zeros)
-  uint4 gr[K][3];
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    const int hz = h + ph - i;
-    const bool rok = hz >= 0 && (hz & 1) == 0 && (hz >> 1) < Ho;
-    const bf16_t* rowp = dz + ((size_t)n * Ho + (rok ? hz >> 1 : 0)) * Wo * C + c;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int wo = wo_first + q;
-      gr[i][q] = (rok && (unsigned)wo < (unsigned)Wo) ? *reinterpret_cast<const uint4*>(rowp + (size_t)wo * C)
-                                                      : make_uint4(0u, 0u, 0u, 0u);
-    }
   }
-  float wv[K * K][8];
 #pragma unroll
-  for (int q = 0; q < K * K; ++q) Vec<bf16_t, 8>::load(wf + (size_t)q * C + c, wv[q]);
-  bf16_t* orow = dx + ((size_t)n * Hin + h) * Win * C + c;
+  for (int q = 0; q < 9; ++q)
 #pragma unroll
-  for (int o = 0; o < SEG; ++o) {
-    if (w0 + o >= Win) break;
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const int d = o + 2 - j;                  // w + pw - j = base + d
-      if ((d & 1) != par) continue;             // odd: this tap does not reach the pixel
-      const int q = (d - par) >> 1;             // 0 .. 2 (d = 5 only with par = 1)
-#pragma unroll
-      for (int i = 0; i < K; ++i) {
-        float gv[8];
-        unpack8(q == 0 ? gr[i][0] : q == 1 ? gr[i][1] : gr[i][2], gv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] += gv[e] * wv[i * K + j][e];
-      }
-    }
-    Vec<bf16_t, 8>::store(orow + (size_t)(w0 + o) * C, acc);
+    for (int e = 0; e < 4; ++e) t[q][e] = p.flip ? w[8 - q][e] : w[q][e];
+}
+// w'[tap][c] = bf16(s w), a value per thread of the launch's first threads
+__device__ __forceinline__ void dw_emit_folded(const Dw3Params& p) {
+  if (!p.wf_out) return;
+  const int nthr = gridDim.x * gridDim.y * DW_BLK;
+  for (int j = (blockIdx.y * gridDim.x + blockIdx.x) * DW_BLK + threadIdx.x; j < 9 * p.C; j += nthr) {
+    const int q = j / p.C, c = j - q * p.C;
+    const float s = p.gamma ? p.gamma[c] / sqrtf(p.var[c] + p.eps) : 1.f;
+    p.wf_out[j] = (bf16_t)((float)p.W[(size_t)c * 9 + q] * s);
   }
 }
 
-bool patch3_shape(const Geom& g, int dtype) {
-  return dtype == CONVBN_BF16 && g.Cin % 8 == 0 && g.kH == 3 && g.kW == 3 && g.sh == g.sw && (g.sh == 1 || g.sh == 2) &&
-         (size_t)g.N * (g.Hin > g.Hout ? g.Hin : g.Hout) * ceil_div(g.Win > g.Wout ? g.Win : g.Wout, 3) * (g.Cin / 8) <
-             0xffffffffull;
-}
-template <int S, bool FLIP>
-hipError_t launch_patch3(const void* in, const void* wf, const float* bias, void* out, int N, int Hi, int Wi, int Ho,
-                       int Wo, int C, int ph, int pw, hipStream_t st) {
-  const int nseg = ceil_div(Ho, patch_seg(S));
-  const size_t total = (size_t)N * nseg * Wo * (C / 8);
-  hipLaunchKernelGGL((dw_patch3_kernel<S, FLIP>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16_t*)in,
-                     (const bf16_t*)wf, bias, (bf16_t*)out, N, Hi, Wi, Ho, Wo, C, ph, pw, nseg);
-  return hipGetLastError();
+// Sums the weight-gradient accumulators of a workgroup's threads (thread = column lane * cq + quad) over its column lanes
+// and writes them as one slice of `part`.  Five of the ten rows at a time: 40 KB of LDS.
+__device__ __forceinline__ void dw_slice_sums(const Dw3Params& p, const float (&acc)[10][4], int L, float* red) {
+  const int tid = threadIdx.x, ncol = p.cq * 4;
+  const int slice = p.slice0 + dw_slice();
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[(q * 4 + e) * DW_BLK + tid] = acc[half * 5 + q][e];
+    __syncthreads();
+    for (int j = tid; j < 5 * ncol; j += DW_BLK) {
+      const int q = j / ncol, col = j - q * ncol;
+      const int c = (int)blockIdx.x * ncol + col;
+      if (c >= p.C) continue;
+      const float* src = red + (q * 4 + (col & 3)) * DW_BLK + (col >> 2);
+      float v = 0.f;
+      for (int l = 0; l < L; ++l) v += src[l * p.cq];
+      p.part[(((size_t)(c >> 3) * p.slices_all + slice) * 10 + half * 5 + q) * 8 + (c & 7)] = v;
+    }
+  }
 }
 
-// Weight gradient for the shapes of the patch kernel.  An item is SEG vertically consecutive outputs of one column; a
-// thread owns 8 channels and every L-th item of its workgroup's slice of the items (L = threads / channel groups
-// of the workgroup), loads an item's dZ values and input patch up front and accumulates the 9 x 8 products and
-// the channel sums in registers; the L lanes are then summed through LDS.  Outputs as dw_wgrad_kernel.
-template <int S>
-__global__ __launch_bounds__(256) void dw_wgrad_patch3_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dz,
-                                                            float* __restrict__ part, float* __restrict__ r_part, int N,
-                                                            int Hi, int Wi, int Ho, int Wo, int C, int ph, int pw,
-                                                            int nseg, int cgb, int items_per_slice) {
-  constexpr int K = 3, SEG = patch_seg(S), NR = (SEG - 1) * S + K;
-  __shared__ float red[256 * 8];
-  const int cgs = C >> 3;
-  const int L = 256 / cgb;
-  const int tx = threadIdx.x % cgb, lane = threadIdx.x / cgb;
-  const int cg = blockIdx.x * cgb + tx;
-  const bool live = lane < L && cg < cgs;
-  const int c = cg * 8;
-  const int nitems = N * nseg * Wo;
-  const int it0 = blockIdx.y * items_per_slice, it1 = min(nitems, it0 + items_per_slice);
-  float acc[K * K][8], racc[8];
+// Stride 1.  CONV: out[n][h][w] = b' + sum_{i,j} T[i][j] a[n][h + i - pa][w + j - pb], T the filter (flip: rotated).
+// WG (a = dZ, flip): dw'[8 - (i, j)] += y[n][h][w] a[n][h + i - pa][w + j - pb] over the owned (h, w), and the sums of a.
+// Products with a position outside an image are skipped, not multiplied by zero: an infinite x or dZ at the border does
+// not reach the taps that do not touch it.
+// PAD1: pa = pb = 1, the sizes of a and out are the same.
+template <bool CONV, bool WG, bool PAD1>
+__global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p) {
+  __shared__ float red[WG ? 20 * DW_BLK : 1];
+  if (CONV && !WG) dw_emit_folded(p);
+  const int pad_h = PAD1 ? 1 : p.pa, pad_w = PAD1 ? 1 : p.pb;
+  const int L = DW_BLK / p.cq;
+  const int tx = threadIdx.x % p.cq, lane = threadIdx.x / p.cq;
+  const int c = ((int)blockIdx.x * p.cq + tx) * 4;
+  const bool live = lane < L && c < p.C;
+  const unsigned px = (unsigned)p.C * 2u, arow = px * p.Wa, orow = px * p.Wo;
+  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow), ry = dw_rsrc(WG ? p.y : p.a, (size_t)p.N * p.Ho * orow);
+  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
+  float t[9][4], bb[4], wacc[10][4];
+  if constexpr (WG) {
 #pragma unroll
-  for (int q = 0; q < K * K; ++q)
+    for (int q = 0; q < 10; ++q)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[q][e] = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) racc[e] = 0.f;
+      for (int e = 0; e < 4; ++e) wacc[q][e] = 0.f;
+  }
+  const int slice = dw_slice(), it1 = min(p.items, (slice + 1) * p.per_slice);
+  if (CONV && !WG && live) dw_filter(p, c, t, bb);
+  bool first = true;
   if (live)
-    for (int it = it0 + lane; it < it1; it += L) {
-      const int wo = it % Wo;
-      const int t = it / Wo;
-      const int sg = t % nseg, n = t / nseg;
-      const int ho0 = sg * SEG;
-      uint4 gr[SEG], xr[NR][K];
+    for (int it = slice * p.per_slice + lane; it < it1; it += L) {
+      const int pair = it % p.npair;
+      const int rest = it / p.npair;
+      const int strip = rest % p.nstrip, n = rest / p.nstrip;
+      const int w0 = pair * 2, h0 = strip * p.R;
+      unsigned acol[4], ocol[2];
 #pragma unroll
-      for (int o = 0; o < SEG; ++o)
-        gr[o] = ho0 + o < Ho ? *reinterpret_cast<const uint4*>(dz + (((size_t)n * Ho + ho0 + o) * Wo + wo) * C + c)
-                             : make_uint4(0u, 0u, 0u, 0u);
+      for (int k = 0; k < 4; ++k) {
+        const int w = w0 + k - pad_w;
+        acol[k] = (unsigned)w < (unsigned)p.Wa ? (unsigned)w * px : DW_INV;
+      }
 #pragma unroll
-      for (int q = 0; q < NR; ++q) {
-        const int h = ho0 * S + q - ph;
-        const bool rok = (unsigned)h < (unsigned)Hi;
-        const bf16_t* rowp = x + ((size_t)n * Hi + (rok ? h : 0)) * Wi * C + c;
+      for (int k = 0; k < 2; ++k) ocol[k] = w0 + k < p.Wo ? (unsigned)(w0 + k) * px : DW_INV;
+      const bool has_l = acol[0] != DW_INV, has_r = acol[3] != DW_INV, two = ocol[1] != DW_INV;
+      const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
+      // running offsets: the next row of a (with its index), of y and of out
+      const int nq = p.R + 2, rows = max(min(p.Ho - h0, p.R), 0), hend = min(p.Ha, h0 - pad_h + nq);
+      int ha = h0 - pad_h;
+      unsigned aoff = abase + (unsigned)ha * arow, yoff = obase + (unsigned)h0 * orow, ooff = yoff - 2 * orow;
+      u32x2 pa[2][4], py[2][2];
+      auto fetch = [&](int q, int slot) {   // (unconditional: steps past the last one read nothing)
+        const unsigned r = (unsigned)ha < (unsigned)hend ? aoff : DW_INV;
+        ++ha;
+        aoff += arow;
 #pragma unroll
-        for (int jj = 0; jj < K; ++jj) {
-          const int w = wo * S + jj - pw;
-          xr[q][jj] = (rok && (unsigned)w < (unsigned)Wi) ? *reinterpret_cast<const uint4*>(rowp + (size_t)w * C)
-                                                          : make_uint4(0u, 0u, 0u, 0u);
+        for (int k = 0; k < 4; ++k) pa[slot][k] = dw_load(ra, r + acol[k]);
+        if constexpr (WG) {
+          const unsigned s = q < rows ? yoff : DW_INV;
+          yoff += orow;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) py[slot][k] = dw_load(ry, s + ocol[k]);
         }
-      }
-      float gv[SEG][8];
+      };
+      fetch(0, 0);
+      fetch(1, 1);
+      if (CONV && WG && first) dw_filter(p, c, t, bb);   // (behind the first rows' requests)
+      first = false;
+      float acc[3][2][4], yv[3][2][4], ye[3][2][4];   // ye: zero where the neighbouring column of a is outside
 #pragma unroll
-      for (int o = 0; o < SEG; ++o) {
-        unpack8(gr[o], gv[o]);
+      for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) racc[e] += gv[o][e];
-      }
+        for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int q = 0; q < NR; ++q)
+          for (int e = 0; e < 4; ++e) { acc[k][x][e] = 0.f; yv[k][x][e] = 0.f; ye[k][x][e] = 0.f; }
+      for (int q0 = 0; q0 < nq; q0 += 6) {
 #pragma unroll
-        for (int jj = 0; jj < K; ++jj) {
-          float xv[8];
-          unpack8(xr[q][jj], xv);
+        for (int u = 0; u < 6; ++u) {
+          const int q = q0 + u;
+          if (q >= nq) break;
+          float av[4][4];
 #pragma unroll
-          for (int o = 0; o < SEG; ++o) {
-            const int i = q - o * S;
-            if (i < 0 || i >= K) continue;
+          for (int k = 0; k < 4; ++k) unpack4(pa[u & 1][k], av[k]);
+          if constexpr (WG) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[i * K + jj][e] += gv[o][e] * xv[e];
+            for (int k = 0; k < 2; ++k) unpack4(py[u & 1][k], yv[u % 3][k]);
+            if constexpr (PAD1) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                ye[u % 3][0][e] = has_l ? yv[u % 3][0][e] : 0.f;
+                ye[u % 3][1][e] = has_r ? yv[u % 3][1][e] : 0.f;
+              }
+            }
+          }
+          fetch(q + 2, u & 1);
+          if constexpr (CONV) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[u % 3][x][e] = bb[e];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+              for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) acc[(u + 3 - i) % 3][x][e] += t[i * 3 + j][e] * av[x + j][e];
+            const unsigned r = (unsigned)(q - 2) < (unsigned)rows ? ooff : DW_INV;   // the row that is complete now
+            ooff += orow;
+#pragma unroll
+            for (int x = 0; x < 2; ++x) dw_store(ro, r + ocol[x], acc[(u + 1) % 3][x]);
+          }
+          if constexpr (WG) {
+            if ((unsigned)(h0 + q - pad_h) < (unsigned)p.Ha) {
+              if (q >= pad_h && q < pad_h + p.R) {   // a's owned pixels
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  if constexpr (PAD1) wacc[9][e] += av[1][e] + av[2][e];
+                  else wacc[9][e] += pad_w == 0 ? av[0][e] + av[1][e] : pad_w == 1 ? av[1][e] + av[2][e] : av[2][e] + av[3][e];
+                }
+              }
+#pragma unroll
+              for (int i = 0; i < 3; ++i) {
+                constexpr int T = 8;   // (a is swept with the rotated window)
+                const float(&y)[2][4] = yv[(u + 3 - i) % 3];
+                const float(&z)[2][4] = ye[(u + 3 - i) % 3];
+                if (q >= i && q - i < p.R)   // (the others are the neighbouring strips' rows)
+                  if (q - i < rows) {
+                    if constexpr (PAD1) {
+#pragma unroll
+                      for (int e = 0; e < 4; ++e) {
+                        wacc[T - i * 3][e] += z[0][e] * av[0][e];
+                        wacc[T - i * 3 - 1][e] += y[0][e] * av[1][e];
+                      }
+                      if (two) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                          wacc[T - i * 3 - 2][e] += y[0][e] * av[2][e] + z[1][e] * av[3][e];
+                          wacc[T - i * 3][e] += y[1][e] * av[1][e];
+                          wacc[T - i * 3 - 1][e] += y[1][e] * av[2][e];
+                        }
+                      }
+                    } else {
+#pragma unroll
+                      for (int j = 0; j < 3; ++j)
+#pragma unroll
+                        for (int x = 0; x < 2; ++x)
+                          if (ocol[x] != DW_INV && acol[x + j] != DW_INV) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) wacc[T - i * 3 - j][e] += y[x][e] * av[x + j][e];
+                          }
+                    }
+                  }
+              }
+            }
           }
         }
+      }
     }
-  // sum the lanes: one window position at a time (q == 9: the channel sums)
-  const int ncol = cgb * 8;
+  if constexpr (WG) dw_slice_sums(p, wacc, L, red);
+}
+
+// Stride 2, forward: two neighbouring output columns (5 input columns); a step brings the two input rows that complete
+// an output row, the second of which begins the next one.
+__global__ __launch_bounds__(DW_BLK, 4) void dw3_s2_fprop_kernel(Dw3Params p) {
+  dw_emit_folded(p);
+  const int L = DW_BLK / p.cq;
+  const int tx = threadIdx.x % p.cq, lane = threadIdx.x / p.cq;
+  const int c = ((int)blockIdx.x * p.cq + tx) * 4;
+  if (lane >= L || c >= p.C) return;
+  const unsigned px = (unsigned)p.C * 2u, arow = px * p.Wa, orow = px * p.Wo;
+  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow);
+  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
+  float t[9][4], bb[4];
+  dw_filter(p, c, t, bb);
+  const int slice = dw_slice(), it1 = min(p.items, (slice + 1) * p.per_slice);
+  for (int it = slice * p.per_slice + lane; it < it1; it += L) {
+    const int pair = it % p.npair;
+    const int rest = it / p.npair;
+    const int strip = rest % p.nstrip, n = rest / p.nstrip;
+    const int w0 = pair * 2, h0 = strip * p.R;
+    unsigned acol[5], ocol[2];
 #pragma unroll
-  for (int q = 0; q <= K * K; ++q) {
-    if (q == K * K && !r_part) continue;
-    __syncthreads();
-    if (lane < L) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) red[lane * ncol + tx * 8 + e] = q < K * K ? acc[q < K * K ? q : 0][e] : racc[e];
+    for (int k = 0; k < 5; ++k) {
+      const int w = w0 * 2 + k - p.pb;
+      acol[k] = (unsigned)w < (unsigned)p.Wa ? (unsigned)w * px : DW_INV;
     }
-    __syncthreads();
-    for (int col = threadIdx.x; col < ncol; col += 256) {
-      const int cc = blockIdx.x * ncol + col;
-      if (cc >= C) continue;
-      float v = 0.f;
-      for (int l = 0; l < L; ++l) v += red[l * ncol + col];
-      if (q < K * K) part[((size_t)blockIdx.y * (K * K) + q) * C + cc] = v;
-      else r_part[(size_t)blockIdx.y * C + cc] = v;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) ocol[k] = w0 + k < p.Wo ? (unsigned)(w0 + k) * px : DW_INV;
+    const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
+    u32x2 pa[2][5];
+    auto fetch = [&](int q) {   // window rows 1 and 2 of output row h0 + q - 1
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int h = (h0 + q - 1) * 2 + 1 + i - p.pa;
+        const unsigned r = q <= p.R && (unsigned)h < (unsigned)p.Ha ? abase + (unsigned)h * arow : DW_INV;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) pa[i][k] = dw_load(ra, r + acol[k]);
+      }
+    };
+    fetch(0);
+    float acc[2][4];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[x][e] = 0.f;
+    for (int q = 0; q <= p.R; ++q) {
+      float av[2][5][4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 5; ++k) unpack4(pa[i][k], av[i][k]);
+      fetch(q + 1);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[x][e] += t[(i + 1) * 3 + j][e] * av[i][2 * x + j][e];
+      const int o = h0 + q - 1;
+      const unsigned r = q >= 1 && o < p.Ho ? obase + (unsigned)o * orow : DW_INV;
+#pragma unroll
+      for (int x = 0; x < 2; ++x) dw_store(ro, r + ocol[x], acc[x]);
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[x][e] = bb[e];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[x][e] += t[j][e] * av[1][2 * x + j][e];
     }
   }
 }
 
-// workgroup shape of the kernel above: x-blocks, channel groups per block, slices of the items
-struct PatchWgPlan { int nxb, cgb, nseg, slices, items_per_slice; };
-PatchWgPlan patch_wg_plan(const Geom& g) {
-  PatchWgPlan p;
-  const int cgs = g.Cin / 8;
-  p.nxb = ceil_div(cgs, 64);
-  p.cgb = ceil_div(cgs, p.nxb);
-  p.nseg = ceil_div(g.Hout, patch_seg(g.sh));
-  const int L = 256 / p.cgb;
-  const int nitems = g.N * p.nseg * g.Wout;
-  int want = ceil_div(256, p.nxb);                       // about one workgroup per CU
-  const int maxs = ceil_div(nitems, 2 * L);              // at least two items per thread
-  if (want > maxs) want = maxs;
+// Stride 2, backward.  In coordinates that count the padding (hh = h + ph), dZ row v reaches hh = 2v, 2v + 1, 2v + 2.  A
+// thread that owns dZ columns u and u + 1 owns the x and dx columns 2u + 1 .. 2u + 4, which meet dZ columns u .. u + 2, and
+// per step the rows 2v + 1 (window row 1 of dZ row v) and 2v + 2 (window row 2 of v, 0 of v + 1): with padding 1 nothing is
+// computed twice and nothing lies outside.  u and v start at u0 and v0 (-1 with padding 0).
+template <bool CONV, bool WG>
+__global__ __launch_bounds__(DW_BLK, 2) void dw3_s2_bwd_kernel(Dw3Params p) {
+  __shared__ float red[WG ? 20 * DW_BLK : 1];
+  const int L = DW_BLK / p.cq;
+  const int tx = threadIdx.x % p.cq, lane = threadIdx.x / p.cq;
+  const int c = ((int)blockIdx.x * p.cq + tx) * 4;
+  const bool live = lane < L && c < p.C;
+  const unsigned px = (unsigned)p.C * 2u, arow = px * p.Wa, orow = px * p.Wo;
+  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow), ry = dw_rsrc(WG ? p.y : p.a, (size_t)p.N * p.Ho * orow);
+  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
+  float t[9][4], bb[4], wacc[10][4];
+  if (CONV && live) dw_filter(p, c, t, bb);
+  if constexpr (WG) {
+#pragma unroll
+    for (int q = 0; q < 10; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wacc[q][e] = 0.f;
+  }
+  const int slice = dw_slice(), it1 = min(p.items, (slice + 1) * p.per_slice);
+  if (live)
+    for (int it = slice * p.per_slice + lane; it < it1; it += L) {
+      const int pair = it % p.npair;
+      const int rest = it / p.npair;
+      const int strip = rest % p.nstrip, n = rest / p.nstrip;
+      const int u0 = p.u0 + pair * 2, v0 = p.v0 + strip * p.R;
+      unsigned acol[3], ocol[4];
+      bool inside = true;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const bool ok = (unsigned)(u0 + k) < (unsigned)p.Wa;
+        acol[k] = ok ? (unsigned)(u0 + k) * px : DW_INV;
+        inside &= ok;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int w = 2 * u0 + 1 + k - p.pb;
+        const bool ok = (unsigned)w < (unsigned)p.Wo;
+        ocol[k] = ok ? (unsigned)w * px : DW_INV;
+        inside &= ok;
+      }
+      const bool wave_inside = WG && __all(inside);
+      const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
+      auto a_row = [&](int v) { return (unsigned)v < (unsigned)p.Ha ? abase + (unsigned)v * arow : DW_INV; };
+      auto o_row = [&](int h) { return (unsigned)h < (unsigned)p.Ho ? obase + (unsigned)h * orow : DW_INV; };
+      u32x2 pa[3], py[2][4];
+      auto fetch = [&](int v) {   // dZ row v + 1 and the x rows of step v
+        const bool step = v < v0 + p.R;
+        const unsigned r = step ? a_row(v + 1) : DW_INV;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pa[k] = dw_load(ra, r + acol[k]);
+        if constexpr (WG) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const unsigned s = step ? o_row(2 * v + 1 + i - p.pa) : DW_INV;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) py[i][k] = dw_load(ry, s + ocol[k]);
+          }
+        }
+      };
+      float a0[3][4], a1[3][4];   // dZ rows v and v + 1
+      {
+        const unsigned r = a_row(v0);
+        u32x2 f[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) f[k] = dw_load(ra, r + acol[k]);
+        fetch(v0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) unpack4(f[k], a0[k]);
+      }
+      for (int q = 0; q < p.R; ++q) {
+        const int v = v0 + q;
+        float yv[2][4][4];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) unpack4(pa[k], a1[k]);
+        if constexpr (WG) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) unpack4(py[i][k], yv[i][k]);
+        }
+        fetch(v + 1);
+        // column k of the four meets: k = 0: tap 1 of u;  1: tap 0 of u + 1, tap 2 of u;  2: tap 1 of u + 1;
+        // 3: tap 0 of u + 2, tap 2 of u + 1
+        if constexpr (CONV) {
+          float acc[2][4][4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int m = k >> 1;
+              if (k & 1) {
+                acc[0][k][e] = t[3][e] * a0[m + 1][e] + t[5][e] * a0[m][e];
+                acc[1][k][e] = t[0][e] * a1[m + 1][e] + t[2][e] * a1[m][e] + t[6][e] * a0[m + 1][e] + t[8][e] * a0[m][e];
+              } else {
+                acc[0][k][e] = t[4][e] * a0[m][e];
+                acc[1][k][e] = t[1][e] * a1[m][e] + t[7][e] * a0[m][e];
+              }
+            }
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const unsigned r = o_row(2 * v + 1 + i - p.pa);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dw_store(ro, r + ocol[k], acc[i][k]);
+          }
+        }
+        if constexpr (WG) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) wacc[9][e] += a0[0][e] + a0[1][e];
+          const bool z0 = (unsigned)v < (unsigned)p.Ha, z1 = (unsigned)(v + 1) < (unsigned)p.Ha;
+          const bool r1 = (unsigned)(2 * v + 1 - p.pa) < (unsigned)p.Ho, r2 = (unsigned)(2 * v + 2 - p.pa) < (unsigned)p.Ho;
+          if (wave_inside && __all(z0 && z1 && r1 && r2)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int m = k >> 1;
+                if (k & 1) {
+                  wacc[3][e] += yv[0][k][e] * a0[m + 1][e];
+                  wacc[5][e] += yv[0][k][e] * a0[m][e];
+                  wacc[0][e] += yv[1][k][e] * a1[m + 1][e];
+                  wacc[2][e] += yv[1][k][e] * a1[m][e];
+                  wacc[6][e] += yv[1][k][e] * a0[m + 1][e];
+                  wacc[8][e] += yv[1][k][e] * a0[m][e];
+                } else {
+                  wacc[4][e] += yv[0][k][e] * a0[m][e];
+                  wacc[1][e] += yv[1][k][e] * a1[m][e];
+                  wacc[7][e] += yv[1][k][e] * a0[m][e];
+                }
+              }
+          } else {
+            auto prod = [&](float (&w)[4], bool ok, const float (&x)[4], unsigned xcol, const float (&a)[4], unsigned zcol) {
+              if (ok && xcol != DW_INV && zcol != DW_INV) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] += x[e] * a[e];
+              }
+            };
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const int m = k >> 1;
+              if (k & 1) {
+                prod(wacc[3], r1 && z0, yv[0][k], ocol[k], a0[m + 1], acol[m + 1]);
+                prod(wacc[5], r1 && z0, yv[0][k], ocol[k], a0[m], acol[m]);
+                prod(wacc[0], r2 && z1, yv[1][k], ocol[k], a1[m + 1], acol[m + 1]);
+                prod(wacc[2], r2 && z1, yv[1][k], ocol[k], a1[m], acol[m]);
+                prod(wacc[6], r2 && z0, yv[1][k], ocol[k], a0[m + 1], acol[m + 1]);
+                prod(wacc[8], r2 && z0, yv[1][k], ocol[k], a0[m], acol[m]);
+              } else {
+                prod(wacc[4], r1 && z0, yv[0][k], ocol[k], a0[m], acol[m]);
+                prod(wacc[1], r2 && z1, yv[1][k], ocol[k], a1[m], acol[m]);
+                prod(wacc[7], r2 && z0, yv[1][k], ocol[k], a0[m], acol[m]);
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a0[k][e] = a1[k][e];
+      }
+    }
+  if constexpr (WG) dw_slice_sums(p, wacc, L, red);
+}
+
+// Sums the slices of 8 channels (a workgroup's 320 bytes of a slice are contiguous) and folds back; gamma == null (Eval):
+// dW = dw' only.
+__global__ __launch_bounds__(1024) void dw3_fold_back_kernel(const float* __restrict__ part, int slices,
+                                                             const bf16_t* __restrict__ W, const float* __restrict__ b,
+                                                             const float* __restrict__ gamma, const float* __restrict__ mean,
+                                                             const float* __restrict__ var, float eps,
+                                                             bf16_t* __restrict__ dW, float* __restrict__ db,
+                                                             float* __restrict__ dgamma, float* __restrict__ dbeta) {
+  constexpr int LN = 51;   // slice lanes: 51 x 20 float4 of the 1024 threads
+  __shared__ float4 red[LN * 20];
+  __shared__ float mid[8][80];
+  __shared__ float sums[80];
+  const int tid = threadIdx.x;
+  const int v4 = tid % 20, l = tid / 20;
+  const float4* src = reinterpret_cast<const float4*>(part + (size_t)blockIdx.x * slices * 80);
+  if (l < LN) {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 6
+    for (int s = l; s < slices; s += LN) {
+      const float4 t = src[(size_t)s * 20 + v4];
+      a.x += t.x; a.y += t.y; a.z += t.z; a.w += t.w;
+    }
+    red[l * 20 + v4] = a;
+  }
+  __syncthreads();
+  const float* rf = reinterpret_cast<const float*>(red);
+  if (tid < 640) {
+    const int o = tid % 80, k = tid / 80;
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+      if (k + 8 * j < LN) v += rf[(k + 8 * j) * 80 + o];
+    mid[k][o] = v;
+  }
+  __syncthreads();
+  if (tid < 80) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v += mid[k][tid];
+    sums[tid] = v;
+  }
+  __syncthreads();
+  if (tid >= 8) return;
+  const int c = blockIdx.x * 8 + tid;
+  const float sd = gamma ? sqrtf(var[c] + eps) : 1.f;
+  const float s = gamma ? gamma[c] / sd : 1.f;
+  float dot = 0.f;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const float dw = sums[q * 8 + tid];
+    dW[(size_t)c * 9 + q] = (bf16_t)(s * dw);
+    dot += dw * (float)W[(size_t)c * 9 + q];
+  }
+  if (!gamma) return;
+  const float r = sums[72 + tid];
+  dgamma[c] = (dot + r * ((b ? b[c] : 0.f) - mean[c])) / sd;
+  dbeta[c] = r;
+  if (db) db[c] = s * r;
+}
+
+// ---- host side of these kernels
+bool dw3_shape(const Geom& g, int dtype) {   // the 32-bit offsets of a launch reach 1 GiB: several launches split the images
+  return dtype == CONVBN_BF16 && g.Cin % 8 == 0 && g.kH == 3 && g.kW == 3 && g.sh == g.sw && (g.sh == 1 || g.sh == 2) &&
+         g.ph <= 2 && g.pw <= 2 && (size_t)g.Hin * g.Win * g.Cin * 2 < DW_INV && (size_t)g.Hout * g.Wout * g.Cin * 2 < DW_INV;
+}
+struct Dw3Plan {
+  int cq, nxb;               // channel quads of a workgroup, workgroups across the channels
+  int imgs, launches;        // images of a launch
+  int rows, cols;            // rows and columns of two that the threads share out
+  int R, nstrip, npair, items, slices, per_slice;
+};
+// `waves`: per SIMD.  Rows per strip: as many as give every thread the same number of strips, a strip costing its rows
+// and the ones it shares with its neighbours (`extra`).
+Dw3Plan dw3_plan(const Geom& g, int rows, int cols, int extra, int waves) {
+  Dw3Plan p;
+  const int quads = g.Cin / 4;
+  p.nxb = ceil_div(quads, DW_MAXQ);
+  p.cq = ceil_div(quads, p.nxb);
+  const size_t img = (size_t)(g.Hin > g.Hout ? g.Hin : g.Hout) * (g.Win > g.Wout ? g.Win : g.Wout) * g.Cin * 2;
+  const size_t fit = (DW_INV - 1) / img;
+  p.imgs = fit < (size_t)g.N ? (fit > 1 ? (int)fit : 1) : g.N;
+  p.launches = ceil_div(g.N, p.imgs);
+  p.rows = rows; p.cols = cols;
+  p.npair = ceil_div(cols, 2);
+  const int L = DW_BLK / p.cq;
+  int want = 256 * waves / 2 / p.nxb;      // workgroups of eight waves that the chip holds
   if (want < 1) want = 1;
-  p.items_per_slice = ceil_div(nitems, want);
-  p.slices = ceil_div(nitems, p.items_per_slice);
+  long long best = -1;
+  p.R = rows;
+  for (int ns = 1; ns <= rows; ++ns) {
+    const int R = ceil_div(rows, ns);
+    if (ceil_div(rows, R) != ns) continue;
+    const long long items = (long long)p.imgs * ns * p.npair;
+    const long long rounds = (items + (long long)want * L - 1) / ((long long)want * L);
+    const long long cost = rounds * (R + extra);
+    if (best < 0 || cost < best) { best = cost; p.R = R; }
+  }
+  p.nstrip = ceil_div(rows, p.R);
+  p.items = p.imgs * p.nstrip * p.npair;
+  const int rounds = ceil_div(p.items, want * L);
+  p.per_slice = rounds * L;
+  p.slices = ceil_div(p.items, p.per_slice);
+  return p;
+}
+Dw3Plan dw3_fprop_plan(const Geom& g) {
+  return planned<Dw3Plan>(g, 1, [&] { return dw3_plan(g, g.Hout, g.Wout, g.sh == 1 ? 4 : 2, 4); });
+}
+int dw3_first(int pad) { return pad == 0 ? -1 : 0; }   // stride 2: the first dZ row (column) that owns x rows
+Dw3Plan dw3_bwd_plan(const Geom& g) {
+  return planned<Dw3Plan>(g, 1, [&] {
+    if (g.sh == 1)
+      return dw3_plan(g, g.Hin > g.Hout ? g.Hin : g.Hout, g.Win > g.Wout ? g.Win : g.Wout, 4, 2);
+    // x row Hin - 1 belongs to the step v with 2 v + 2 >= Hin - 1 + ph; every dZ row is some step's own
+    auto span = [](int in, int out, int pad) {
+      int last = (in - 1 + pad - 1) / 2;
+      if (last < out - 1) last = out - 1;
+      return last - dw3_first(pad) + 1;
+    };
+    return dw3_plan(g, span(g.Hin, g.Hout, g.ph), span(g.Win, g.Wout, g.pw), 2, 2);
+  });
+}
+Dw3Params dw3_params(const Dw3Plan& pl, const Geom& g, int img0, int N) {
+  Dw3Params p{};
+  p.eps = g.eps;
+  p.N = N;
+  p.C = g.Cin;
+  p.R = pl.R; p.nstrip = pl.nstrip; p.npair = pl.npair; p.cq = pl.cq;
+  p.items = N * pl.nstrip * pl.npair;
+  p.per_slice = pl.per_slice;
+  p.slice0 = img0 / pl.imgs * pl.slices;
+  p.slices_all = pl.launches * pl.slices;
   return p;
 }
 
@@ -516,10 +923,6 @@ hipError_t launch_dw_fold(const Geom& g, int dtype, const void* W, const float* 
 
 hipError_t launch_dw_fprop(const Geom& g, int dtype, const void* x, const void* wf, const float* bias, void* z,
                            hipStream_t st) {
-  if (patch3_shape(g, dtype)) {
-    if (g.sh == 1) return launch_patch3<1, false>(x, wf, bias, z, g.N, g.Hin, g.Win, g.Hout, g.Wout, g.Cin, g.ph, g.pw, st);
-    return launch_patch3<2, false>(x, wf, bias, z, g.N, g.Hin, g.Win, g.Hout, g.Wout, g.Cin, g.ph, g.pw, st);
-  }
   const int vec = vec8(g, dtype) ? 8 : 1;
   const size_t total = (size_t)g.M * (g.Cin / vec);
   const dim3 grid((unsigned)((total + 255) / 256));
@@ -536,15 +939,6 @@ hipError_t launch_dw_fprop(const Geom& g, int dtype, const void* x, const void* 
 }
 
 hipError_t launch_dw_dgrad(const Geom& g, int dtype, const void* dz, const void* wf, void* dx, hipStream_t st) {
-  if (patch3_shape(g, dtype) && g.sh == 1 && g.ph <= 2 && g.pw <= 2)   // the same sweep over dZ with the rotated filter
-    return launch_patch3<1, true>(dz, wf, nullptr, dx, g.N, g.Hout, g.Wout, g.Hin, g.Win, g.Cin, 2 - g.ph, 2 - g.pw, st);
-  if (patch3_shape(g, dtype) && g.sh == 2) {
-    const int nseg = ceil_div(g.Win, 4);
-    const size_t total = (size_t)g.N * g.Hin * nseg * (g.Cin / 8);
-    hipLaunchKernelGGL(dw_dgrad_s2_patch3_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16_t*)dz,
-                       (const bf16_t*)wf, (bf16_t*)dx, g.N, g.Hin, g.Win, g.Hout, g.Wout, g.Cin, g.ph, g.pw, nseg);
-    return hipGetLastError();
-  }
   const int vec = vec8(g, dtype) ? 8 : 1;
   const size_t total = (size_t)g.Min * (g.Cin / vec);
   const dim3 grid((unsigned)((total + 255) / 256));
@@ -562,7 +956,6 @@ hipError_t launch_dw_dgrad(const Geom& g, int dtype, const void* dz, const void*
 
 // pixel slices of the weight-gradient reduction: enough workgroups to fill the chip a few times over
 int dw_wgrad_slices(const Geom& g, int dtype) {
-  if (patch3_shape(g, dtype)) return patch_wg_plan(g).slices;
   const int vec = vec8(g, dtype) ? 8 : 1;
   const int cblocks = ceil_div(g.Cin / vec, WG_CG) * ceil_div(g.kH * g.kW, WG_TAPS);
   int want = ceil_div(1024, cblocks);
@@ -575,16 +968,6 @@ int dw_wgrad_slices(const Geom& g, int dtype) {
 
 hipError_t launch_dw_wgrad(const Geom& g, int dtype, const void* x, const void* dz, float* part, float* r_part,
                            hipStream_t st) {
-  if (patch3_shape(g, dtype)) {
-    const PatchWgPlan p = patch_wg_plan(g);
-    const dim3 grid(p.nxb, p.slices);
-#define PATCHWG(SV) \
-    hipLaunchKernelGGL((dw_wgrad_patch3_kernel<SV>), grid, dim3(256), 0, st, (const bf16_t*)x, (const bf16_t*)dz, part, \
-                       r_part, g.N, g.Hin, g.Win, g.Hout, g.Wout, g.Cin, g.ph, g.pw, p.nseg, p.cgb, p.items_per_slice)
-    if (g.sh == 1) PATCHWG(1); else PATCHWG(2);
-#undef PATCHWG
-    return hipGetLastError();
-  }
   const int vec = vec8(g, dtype) ? 8 : 1;
   const int slices = dw_wgrad_slices(g, dtype);
   const int pps = ceil_div(g.M, slices);
@@ -615,6 +998,78 @@ hipError_t launch_dw_fold_back(const Geom& g, int dtype, const float* part, cons
   else
     hipLaunchKernelGGL(dw_fold_back_kernel<float>, dim3(ceil_div(C, 256)), dim3(256), 0, st, sums, (const float*)W, b,
                        gamma, mean, var, g.eps, C, taps, (float*)dW, db, dgamma, dbeta);
+  return hipGetLastError();
+}
+
+// ---- the 3x3 kernels
+bool dw3_supported(const Geom& g, int dtype) { return dw3_shape(g, dtype); }
+
+size_t dw3_part_bytes(const Geom& g) {
+  const Dw3Plan pl = dw3_bwd_plan(g);
+  return (size_t)g.Cin * 10 * pl.slices * pl.launches * 4;
+}
+
+hipError_t launch_dw3_fprop(const Geom& g, const void* x, const void* W, const float* b, const float* gamma,
+                            const float* beta, const float* mean, const float* var, void* z, void* w_folded,
+                            hipStream_t st) {
+  const Dw3Plan pl = dw3_fprop_plan(g);
+  for (int n = 0; n < g.N; n += pl.imgs) {
+    Dw3Params p = dw3_params(pl, g, n, g.N - n < pl.imgs ? g.N - n : pl.imgs);
+    p.a = (const bf16_t*)x + (size_t)n * g.Hin * g.Win * g.Cin;
+    p.out = (bf16_t*)z + (size_t)n * g.Hout * g.Wout * g.Cin;
+    p.W = (const bf16_t*)W; p.b = b; p.gamma = gamma; p.beta = beta; p.mean = mean; p.var = var;
+    p.bias = 1;
+    p.wf_out = n == 0 ? (bf16_t*)w_folded : nullptr;
+    p.Ha = g.Hin; p.Wa = g.Win; p.Ho = g.Hout; p.Wo = g.Wout; p.pa = g.ph; p.pb = g.pw;
+    const dim3 grid(pl.nxb, pl.slices);
+    if (g.sh == 1) hipLaunchKernelGGL((dw3_s1_kernel<true, false, false>), grid, dim3(DW_BLK), 0, st, p);
+    else hipLaunchKernelGGL(dw3_s2_fprop_kernel, grid, dim3(DW_BLK), 0, st, p);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const void* W, const void* w_folded,
+                          const float* gamma, const float* var, void* dx, float* part, hipStream_t st) {
+  const Dw3Plan pl = dw3_bwd_plan(g);
+  for (int n = 0; n < g.N; n += pl.imgs) {
+    Dw3Params p = dw3_params(pl, g, n, g.N - n < pl.imgs ? g.N - n : pl.imgs);
+    p.a = (const bf16_t*)dz + (size_t)n * g.Hout * g.Wout * g.Cin;
+    p.y = (const bf16_t*)x + (size_t)n * g.Hin * g.Win * g.Cin;
+    p.out = dx ? (bf16_t*)dx + (size_t)n * g.Hin * g.Win * g.Cin : nullptr;
+    p.part = part;
+    p.W = (const bf16_t*)(w_folded ? w_folded : W);
+    p.tap_major = w_folded != nullptr;
+    p.gamma = w_folded ? nullptr : gamma; p.var = var;
+    p.Ha = g.Hout; p.Wa = g.Wout; p.Ho = g.Hin; p.Wo = g.Win;
+    const dim3 grid(pl.nxb, pl.slices);
+    if (g.sh == 1) {
+      p.flip = 1; p.pa = 2 - g.ph; p.pb = 2 - g.pw;
+      const bool pad1 = g.ph == 1 && g.pw == 1;
+      if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<true, false, false>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<true, true, true>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false>), grid, dim3(DW_BLK), 0, st, p);
+      else if (pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true>), grid, dim3(DW_BLK), 0, st, p);
+      else hipLaunchKernelGGL((dw3_s1_kernel<false, true, false>), grid, dim3(DW_BLK), 0, st, p);
+    } else {
+      p.pa = g.ph; p.pb = g.pw; p.v0 = dw3_first(g.ph); p.u0 = dw3_first(g.pw);
+      if (dx && part) hipLaunchKernelGGL((dw3_s2_bwd_kernel<true, true>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx) hipLaunchKernelGGL((dw3_s2_bwd_kernel<true, false>), grid, dim3(DW_BLK), 0, st, p);
+      else hipLaunchKernelGGL((dw3_s2_bwd_kernel<false, true>), grid, dim3(DW_BLK), 0, st, p);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_dw3_fold_back(const Geom& g, const float* part, const void* W, const float* b, const float* gamma,
+                                const float* mean, const float* var, void* dW, float* db, float* dgamma, float* dbeta,
+                                hipStream_t st) {
+  const Dw3Plan pl = dw3_bwd_plan(g);
+  hipLaunchKernelGGL(dw3_fold_back_kernel, dim3(g.Cin / 8), dim3(1024), 0, st, part, pl.slices * pl.launches,
+                     (const bf16_t*)W, b, gamma, mean, var, g.eps, (bf16_t*)dW, db, dgamma, dbeta);
   return hipGetLastError();
 }
 

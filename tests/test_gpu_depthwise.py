@@ -56,6 +56,44 @@ def test_refold_input_gradient_only_and_wide_scale():
     assert res["dW"] is None and res["dgamma"] is None
 
 
+# the sweep of the 3x3 kernels: every padding it takes, odd and even sides, strips with a remainder, one channel group and
+# several workgroups of channels, fewer positions than threads, strides
+SWEEP = [(n, c, h, w, s, p) for n, c, h, w, s, p in [
+    (1, 8, 3, 3, 1, 0), (1, 8, 1, 1, 1, 1), (2, 16, 5, 4, 1, 2), (3, 264, 13, 11, 1, 1), (1, 520, 31, 7, 1, 0),
+    (2, 32, 57, 63, 1, 1), (40, 96, 29, 30, 1, 1), (2, 24, 9, 10, 1, 2), (1, 8, 3, 3, 2, 0), (1, 8, 1, 2, 2, 1),
+    (2, 16, 5, 4, 2, 2), (3, 264, 13, 10, 2, 1), (2, 40, 14, 15, 2, 0), (2, 32, 57, 64, 2, 1), (24, 96, 28, 29, 2, 1),
+    (2, 24, 8, 11, 2, 2)]]
+
+
+@pytest.mark.parametrize("n,c,h,w,s,p", SWEEP)
+def test_row_sweep(n, c, h, w, s, p):
+    shape = BlockShape("d_sweep", n, c, h, w, c, 3, s, p, "bf16", 7 * c + h + w + p)
+    inp = synth.make_dw_inputs(shape, bias=(h + w) % 2 == 0)
+    ref = oracle_dw_block(inp)
+    compare(_run(inp), ref, "bf16", keys=KEYS, tag=str((n, c, h, w, s, p)))
+    compare(_run(inp, keep_folded=False, need_dx=False), ref, "bf16", keys=("Z", "dW", "db", "dgamma", "dbeta"), tag="no dx")
+    compare(_run(inp, keep_folded=False, params=False), ref, "bf16", keys=("dX",), tag="dx only")
+    compare(_run(inp, mode="eval"), ref, "bf16", keys=EVAL_KEYS, tag="eval")
+
+
+@pytest.mark.parametrize("s", [1, 2])
+@pytest.mark.parametrize("where", ["x", "dy"])
+def test_infinity_stays_with_the_taps_that_touch_it(where, s):
+    """An infinite value in the last row and column meets fewer than nine taps: dW is finite at the others."""
+    h = 13
+    shape = BlockShape("d_inf", 2, 16, h, h, 16, 3, s, 1, "bf16", 3)
+    inp = synth.make_dw_inputs(shape)
+    t = inp[where].clone()
+    t[1, 5, -1, -1] = float("inf")
+    finite = torch.isfinite(_run(dict(inp, **{where: t}))["dW"])
+    assert finite[[c for c in range(16) if c != 5]].all()
+    # x[h-1] meets dZ[h + 1 - i]: taps 1, 2 (stride 2 with an odd side: tap 1);  dZ[last] meets x[last + i - 1]: taps 0, 1
+    hit = ([1] if s == 2 else [1, 2]) if where == "x" else [0, 1]
+    for i in range(3):
+        for j in range(3):
+            assert bool(finite[5, 0, i, j]) == (i not in hit or j not in hit), (i, j)
+
+
 def test_full_size_layer():
     """A depthwise layer at network size: 144 channels, 56x56, N = 32 (an inverted-residual stage), sampled against
     the oracle run on the first two images (the block is independent across images except for the parameter gradients,
