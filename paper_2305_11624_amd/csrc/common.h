@@ -137,6 +137,13 @@ __device__ __forceinline__ void emit_folded_slice(const BnEpilogue& bn, const bf
   }
 }
 
+// 16 bytes of a result past the caches (whole lines: 16-byte pieces of lines written at different times cost more)
+__device__ __forceinline__ void store_result(void* p, uint4 v) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 t = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(t, static_cast<u32x4*>(p));
+}
+
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Raises a kernel's dynamic-LDS limit once per process -- also when several host threads launch it for the first
@@ -367,7 +374,8 @@ hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, co
                             const BnEpilogue* bn = nullptr);
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st);
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
-                     void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd = nullptr);
+                     void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd = nullptr,
+                     bool grad = false);   // grad: an input gradient
 bool pw_fprop_supported(const Geom& g, int dtype);
 bool pw_fprop_scaled_supported(const Geom& g, int dtype);     // ... with a BnEpilogue
 bool pw_fprop_folds_aside(const Geom& g, int dtype);          // ... whose launch also leaves w_folded_out

@@ -502,7 +502,8 @@ hipError_t launch_fprop_pw(const Geom& g, const void* x, const void* w_krsc, con
 hipError_t launch_dgrad_pw(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx,
                            hipStream_t st) {
   if (gm_supported(g.M, g.Cout, g.Cin))
-    return launch_gm(g.M, g.Cout, g.Cin, dz, w_crsk, bias, nullptr, dx, g.post_relu, g.post_mask, g.post_add, st);
+    return launch_gm(g.M, g.Cout, g.Cin, dz, w_crsk, bias, nullptr, dx, g.post_relu, g.post_mask, g.post_add, st, nullptr,
+                     bias == nullptr);   // (with a bias: a transposed convolution, forward)
   PwParams p = dgrad_params(g);
   const PwPlan pl = make_plan(p);
   if (!pl.ok) return hipErrorInvalidValue;
