@@ -55,9 +55,9 @@ class _Block:
     def _forward(self, x, z, ws):
         s = self.shape
         if self.unit is not None:
-            # w' of this block was produced by its unit's grouped fold: only the convolution is left
-            B.convbn_conv_fprop(self.desc, x, self.unit["w_fprop"], self.unit["b_folded"], z, ws)
             self.saved = self.unit["w_folded"]
+            B.convbn_tune_fwd(self.desc, x, self.W, None, self.gamma, self.beta, self.mean, self.var, z,
+                              self.saved, ws)
         elif self.grouped is not None:
             # w' of this block was produced by the network's grouped fold: only the convolution is left
             B.convbn_conv_fprop(self.desc, x, self.grouped["w_fprop"], self.grouped["b_folded"], z, ws)
@@ -111,9 +111,10 @@ class ResNet50:
                  fuse_residual: bool = True):
         """group_fold (Tune mode): fold all blocks in one launch at the start of forward instead of one
         launch per block.  Faster, but every w' (in both orders) then lives for the whole step.
-        group_units (Tune mode): one fold launch and one fold-back launch per bottleneck unit (its three or four
-        blocks) instead of one per block; the forward-order w' and the fp32 partial sums live in arenas the size of
-        the largest unit."""
+        group_units (Tune mode): in backward one launch per bottleneck unit (its three or four blocks) folds again what
+        forward did not keep, and one folds back, instead of one per block; the fp32 partial sums live in an arena the
+        size of the largest unit.  (In forward every convolution folds on the side: a grouped fold was 16 launches and
+        87 us of a forward pass over 32 images.)"""
         assert mode in ("tune", "eval")
         self.N, self.image, self.mode, self.device = N, image, mode, device
         # the residual sum of a unit (and the ReLU behind it) applied by the unit's last convolution, the sum of the two
@@ -142,16 +143,15 @@ class ResNet50:
             self._build_units()
 
     def _build_units(self):
-        """Tables and arenas of the per-unit grouped fold and fold-back.  Everything the tables point to is allocated
-        once: the kept w' of every block (what Tune mode keeps anyway), and three arenas the size of the largest
-        unit -- the forward-order w' + b', the w' folded again in backward for blocks that keep nothing, and the
-        fp32 partial sums of the weight gradients."""
+        """Tables and arena of the per-unit grouped re-fold and fold-back.  Everything the tables point to is allocated
+        once: the kept w' of every block (what Tune mode keeps anyway), and an arena the size of the largest unit: the w'
+        folded again in backward for blocks that keep nothing, and the fp32 partial sums of the weight gradients."""
         bl, dev = self.blocks, self.device
         names = [[u + sfx for sfx in (".c", ".b", ".a", ".ds") if (u + sfx) in bl] for st in self.stages for u in st]
-        need = dict(fwd=0, refold=0, part=0)
+        need = dict(refold=0, part=0)
         plans = []
         for unit in names:
-            off = dict(fwd=0, refold=0, part=0)
+            off = dict(refold=0, part=0)
             rows = []
             for nme in unit:
                 b = bl[nme]
@@ -160,8 +160,7 @@ class ResNet50:
                 # blocks whose backward is one launch anyway, or whose fp32 partial sums are large (they would set the
                 # size of the arena), keep their own backward call
                 big = B.convbn_wgrad_parts(b.desc) * P * 4 > (16 << 20)
-                row = dict(block=b, fwd=off["fwd"], fused=B.convbn_tune_bwd_is_fused(b.desc) or big)
-                off["fwd"] += (P * 2 + 255) // 256 * 256 + (s.Cout * 4 + 255) // 256 * 256
+                row = dict(block=b, fused=B.convbn_tune_bwd_is_fused(b.desc) or big)
                 if not b.keep_folded and not row["fused"]:
                     row["refold"] = off["refold"]
                     off["refold"] += (P * 2 + 255) // 256 * 256
@@ -174,11 +173,9 @@ class ResNet50:
             plans.append(rows)
             for k in need:
                 need[k] = max(need[k], off[k])
-        # one arena: the forward-order w' of a unit lives in it during forward, the re-folded w' and the partial sums
-        # of a unit during backward
         need["refold"] = (need["refold"] + 255) // 256 * 256
-        one = torch.empty(max(need["fwd"], need["refold"] + need["part"], 256), dtype=torch.uint8, device=dev)
-        arena = dict(fwd=one, refold=one, part=one[need["refold"]:])
+        one = torch.empty(max(need["refold"] + need["part"], 256), dtype=torch.uint8, device=dev)
+        arena = dict(refold=one, part=one[need["refold"]:])
 
         def view(buf, off, nbytes, dtype):
             return buf[off:off + nbytes].view(dtype)
@@ -186,18 +183,14 @@ class ResNet50:
         self.units = {}
         kept_bytes = 0
         for unit, rows in zip(names, plans):
-            fold_items, refold_items, back_items = [], [], []
+            refold_items, back_items = [], []
             for row in rows:
                 b = row["block"]
                 s = b.shape
                 P = s.Cout * s.K
                 u = dict(fused=row["fused"])
-                u["w_fprop"] = view(arena["fwd"], row["fwd"], P * 2, self.dt)
-                u["b_folded"] = view(arena["fwd"], row["fwd"] + (P * 2 + 255) // 256 * 256, s.Cout * 4, torch.float32)
                 u["w_folded"] = torch.empty(P, dtype=self.dt, device=dev) if b.keep_folded else None
                 kept_bytes += P * 2 if b.keep_folded else 0
-                fold_items.append(dict(desc=b.desc, W=b.W, b=None, gamma=b.gamma, beta=b.beta, mean=b.mean, var=b.var,
-                                       w_fprop=u["w_fprop"], w_folded=u["w_folded"], b_folded=u["b_folded"]))
                 if not row["fused"]:
                     if b.keep_folded:
                         u["w_t"] = u["w_folded"]
@@ -214,7 +207,6 @@ class ResNet50:
                 b.unit = u
             key = unit[0].rsplit(".", 1)[0]
             self.units[key] = dict(
-                fold=B.convbn_fold_group_plan(fold_items, device=dev),
                 refold=B.convbn_fold_group_plan(refold_items, device=dev) if refold_items else None,
                 back=B.convbn_fold_back_group_plan(back_items, device=dev) if back_items else None)
         self._unit_keep = (arena, plans)
@@ -275,8 +267,6 @@ class ResNet50:
         cur = p
         for names in self.stages:
             for name in names:
-                if self.units is not None:
-                    B.convbn_fold_group(*self.units[name]["fold"])
                 a = bl[name + ".a"].forward(cur, ws)     # (ReLU applied by the block: its act bits)
                 b = bl[name + ".b"].forward(a, ws)
                 has_ds = (name + ".ds") in bl
