@@ -1212,6 +1212,11 @@ convbn_status convbn_grouped_tune_fwd(const convbn_desc* desc, int groups, const
   if (s != CONVBN_OK) return s;
   const GFwdWs w = carve_g_fwd(gf, dt, ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (g_fprop_scaled_supported(g, groups, dt)) {   // one launch: s and b' in the epilogue, w' left on the side
+    const BnEpilogue bn{gamma, beta, mean, var, b, g.eps, w_folded, g.kH * g.kW, gf.Cin, g.Cout};
+    LAUNCH(launch_g_fprop(g, groups, dt, x, W, nullptr, z, st, &bn));
+    return CONVBN_OK;
+  }
   // w' = s w in both orders ([Cout][taps][cg] for this pass, [cg][taps][Cout] kept for backward), b'
   LAUNCH(launch_fold(gf, dt, W, b, gamma, beta, mean, var, 0, w.w_krsc, w_folded, w.bfold, st));
   LAUNCH(launch_g_fprop(g, groups, dt, x, w.w_krsc, w.bfold, z, st));              // Z = w' (*) X + b'
@@ -1249,6 +1254,12 @@ convbn_status convbn_grouped_tune_bwd(const convbn_desc* desc, int groups, const
     if (!wf) {   // not kept: fold again (Sec. 3.3 recomputes w' from the parameters)
       LAUNCH(launch_fold(gf, dt, W, b, gamma, nullptr, mean, var, 0, nullptr, w.w_crsk, nullptr, st));
       wf = w.w_crsk;
+    }
+    if (params && g3_pair_supported(g, groups, dt)) {   // dX, dw' and r in one launch
+      LAUNCH(launch_g3_pair(g, groups, x, dz, wf, dx, w.part, w.r_part, st));
+      LAUNCH(launch_fold_back(gf, dt, w.part, w.slices, w.r_part, w.nrpart, W, b, gamma, mean, var, 0, dW, db, dgamma,
+                              dbeta, st));
+      return CONVBN_OK;
     }
     LAUNCH(launch_g_dgrad(g, groups, dt, dz, wf, dx, st));                          // dX = w'_rot (*) dZ
   }

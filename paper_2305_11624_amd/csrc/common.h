@@ -121,6 +121,19 @@ struct BnEpilogue {
   int taps, Cin, Cout;
 };
 
+// s and b' of channel `ch` (no BatchNorm given: 1 and the bias), every load issued before the first use
+__device__ __forceinline__ void bn_scale_bias(const BnEpilogue& bn, const float* bias, int ch, float* s, float* bb) {
+  *s = 1.f;
+  *bb = 0.f;
+  if (bn.gamma) {
+    const float ga = bn.gamma[ch], va = bn.var[ch], me = bn.mean[ch], be = bn.beta[ch], b = (bn.b ? bn.b : bn.mean)[ch];
+    *s = ga / sqrtf(va + bn.eps);
+    *bb = ((bn.b ? b : 0.f) - me) * *s + be;
+  } else if (bias) {
+    *bb = bias[ch];
+  }
+}
+
 // Slice `wg` of `nwg` of w' = bf16(float(w) s), written in [Cin][taps][Cout] order (w is [Cout][taps][Cin]); the same
 // values, bit for bit, as the fold kernel's.  Called by all threads of a workgroup.
 __device__ __forceinline__ void emit_folded_slice(const BnEpilogue& bn, const bf16_t* __restrict__ w, int wg, int nwg) {
@@ -303,13 +316,27 @@ hipError_t launch_dw3_fold_back(const Geom& g, const float* part, const void* W,
 // conv_grouped.hip : the three contractions of a grouped block (groups divides g.Cin and g.Cout; cg = Cin / groups).
 // w_krsc is [Cout][kH][kW][cg], w_crsk [cg][kH][kW][Cout]; part [slices][Cout][kH kW cg] fp32.  Where
 // g_wgrad_makes_rsum() the weight-gradient launch also writes r_part [slices][Cout] (else it ignores it).
+// bn != nullptr (g_fprop_scaled_supported): w_krsc is the UNFOLDED weight.
+bool g_fprop_scaled_supported(const Geom& g, int groups, int dtype);
 hipError_t launch_g_fprop(const Geom& g, int groups, int dtype, const void* x, const void* w_krsc, const float* bias,
-                          void* z, hipStream_t st);
+                          void* z, hipStream_t st, const BnEpilogue* bn = nullptr);
 hipError_t launch_g_dgrad(const Geom& g, int groups, int dtype, const void* dz, const void* w_crsk, void* dx,
                           hipStream_t st);
 int g_wgrad_slices(const Geom& g, int groups, int dtype);
 bool g_wgrad_makes_rsum(const Geom& g, int groups, int dtype);
 hipError_t launch_g_wgrad(const Geom& g, int groups, int dtype, const void* x, const void* dz, float* part,
+                          float* r_part, hipStream_t st);
+
+// conv_grouped3.hip : the same for 3x3 windows, stride 1 or 2, groups of 4 to 32 channels (tensors under 1 GB).  W is the unfolded
+// weight [Cout][kH][kW][cg] (bn: s, b' and where w' is left, or null); w_crsk as above; part [slices][Cout][kH kW cg], r_part
+// [slices][Cout] or null.
+bool g3_supported(const Geom& g, int groups, int dtype);
+hipError_t launch_g3_fprop(const Geom& g, int groups, const void* x, const void* W, const BnEpilogue& bn, void* z, hipStream_t st);
+hipError_t launch_g3_dgrad(const Geom& g, int groups, const void* dz, const void* w_crsk, void* dx, hipStream_t st);
+int g3_wgrad_slices(const Geom& g);
+hipError_t launch_g3_wgrad(const Geom& g, int groups, const void* x, const void* dz, float* part, float* r_part, hipStream_t st);
+bool g3_pair_supported(const Geom& g, int groups, int dtype);   // both gradients as one launch
+hipError_t launch_g3_pair(const Geom& g, int groups, const void* x, const void* dz, const void* w_crsk, void* dx, float* part,
                           float* r_part, hipStream_t st);
 
 // conv_wave.hip : operands straight from memory into the matrix cores, the reduction split over a workgroup's waves.

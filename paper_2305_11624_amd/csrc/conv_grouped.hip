@@ -348,6 +348,7 @@ struct GcParams {
   const bf16_t* in;     // [N][Hi][Wi][C]
   const bf16_t* w;      // mode 0: [C][taps][cg]; mode 1: [cg][taps][C]
   const float* bias;    // [C] or null
+  BnEpilogue bn;        // bn.gamma != null: the weight is unfolded (mode 0), the epilogue applies s and b' (bias unused)
   bf16_t* out;          // [N][Ho][Wo][C]
   int N, Hi, Wi, C, Ho, Wo, kH, kW, sh, sw, ph, pw, cg;
   int mode;             // 0 forward, 1 input gradient (taps reversed, ph / pw already those of the reversed window)
@@ -424,46 +425,76 @@ __global__ __launch_bounds__(256) void g_conv_mfma_kernel(GcParams p) {
 
   fetch(worker);   // in flight while the weights arrive
 
-  // ---- weight fragments: row = lane % 32 (output channel; mode 1: input channel), 8 consecutive reduced channels
+  // ---- weight fragments: row = lane % 32 (output channel; mode 1: input channel), 8 consecutive reduced channels.  Every
+  // address is inside the weight whatever the masks say: a layout's loads are all issued in one go and masked afterwards
+  // (a branch between two loads is a wait for the first: 18 round trips, 12 of the 18 us of 256 channels at 28 x 28).
   bf16x8 wf[TAPS][KS];
   {
     const int row = px, rgrp = row >> p.lcg;
+    auto tap_of = [&](int t) { return p.ncls > 1 ? p.ctapw[cls][t] : p.tapw[t]; };   // -1: no tap (load tap 0 and drop it)
+    uint4 raw[TAPS][KS];
+    if (p.mode == 0 && KS == 2 && p.cg == 4) {
+      const bf16_t* wr = p.w + (size_t)(chunk * 32 + row) * p.wtaps * 4;
+#pragma unroll
+      for (int t = 0; t < TAPS; ++t) {
+        const uint2 r = *reinterpret_cast<const uint2*>(wr + max(tap_of(t), 0) * 4);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) raw[t][ks] = make_uint4(r.x, r.y, r.x, r.y);
+      }
+    } else {
+      // element offsets of tap 0 and of a tap further; the 8 reduced channels start at k0 (KS == 4: the group's 64 x 64
+      // block as it is)
+      const size_t w0 = p.mode == 0 ? (size_t)(chunk * 32 + row) * p.wtaps * p.cg
+                        : KS == 4   ? (size_t)(cl * 32 + row) * p.wtaps * p.C + cgrp * 64
+                                    : (size_t)(row & (p.cg - 1)) * p.wtaps * p.C + chunk * 32;
+      const int wtap = p.mode == 0 ? p.cg : p.C;
+      const int kmask = p.mode == 0 && KS == 2 ? p.cg - 1 : 63;
+#pragma unroll
+      for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          raw[t][ks] = *reinterpret_cast<const uint4*>(p.w + w0 + max(tap_of(t), 0) * wtap + ((ks * 16 + kb * 8) & kmask));
+    }
 #pragma unroll
     for (int t = 0; t < TAPS; ++t)
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const int k0 = ks * 16 + kb * 8;             // first of the 8 reduced channels (local)
-        const int tw = p.ncls > 1 ? p.ctapw[cls][t] : p.tapw[t];
-        const int twc = tw < 0 ? 0 : tw;                 // (no tap: load tap 0 and drop it)
-        const bool lo = tw >= 0 && (KS == 4 || (k0 >> p.lcg) == rgrp), hi = tw >= 0 && (KS == 4 || ((k0 + 4) >> p.lcg) == rgrp);
-        // every address below is inside the weight whatever the masks say: load first, zero afterwards, so that
-        // all loads of the lane are in flight together
-        uint4 v;
-        if (KS == 4) {   // groups of 64: rows and columns of the group's 64 x 64 block as they are
-          v = p.mode == 0
-                  ? *reinterpret_cast<const uint4*>(p.w + ((size_t)(chunk * 32 + row) * p.wtaps + twc) * 64 + k0)
-                  : *reinterpret_cast<const uint4*>(p.w + ((size_t)(cl * 32 + row) * p.wtaps + twc) * p.C + cgrp * 64 + k0);
-        } else if (p.mode == 0) {
-          const bf16_t* wr = p.w + ((size_t)(chunk * 32 + row) * p.wtaps + twc) * p.cg;
-          if (p.cg == 4) {
-            const uint2 r = *reinterpret_cast<const uint2*>(wr);
-            v = make_uint4(r.x, r.y, r.x, r.y);
-          } else {
-            v = *reinterpret_cast<const uint4*>(wr + (k0 & (p.cg - 1)));
-          }
-        } else {
-          v = *reinterpret_cast<const uint4*>(p.w + ((size_t)(row & (p.cg - 1)) * p.wtaps + twc) * p.C + chunk * 32 + k0);
-        }
-        v.x = lo ? v.x : 0u; v.y = lo ? v.y : 0u;
-        v.z = hi ? v.z : 0u; v.w = hi ? v.w : 0u;
-        wf[t][ks] = __builtin_bit_cast(bf16x8, v);
+        const bool tap = tap_of(t) >= 0;
+        const bool lo = tap && (KS == 4 || (k0 >> p.lcg) == rgrp), hi = tap && (KS == 4 || ((k0 + 4) >> p.lcg) == rgrp);
+        const uint4 v = raw[t][ks];
+        wf[t][ks] = __builtin_bit_cast(bf16x8, make_uint4(lo ? v.x : 0u, lo ? v.y : 0u, hi ? v.z : 0u, hi ? v.w : 0u));
       }
   }
-  // bias of the lane's 16 accumulator channels 8 (e / 4) + 4 kb + e % 4
-  float bv[16];
+  // scale and bias of the workgroup's channels (visible behind the tile loop's first barrier)
+  float* const sb = reinterpret_cast<float*>(smem + (size_t)p.PR * p.PC * p.pitch + 4 * 32 * 80);   // [32 nch] scale, [32 nch] bias
+  if (tid < p.nch * 32) {
+    const int ch = cgrp * p.nch * 32 + tid;
+    float s, bb;
+    bn_scale_bias(p.bn, p.bias, ch, &s, &bb);
+    sb[tid] = s;
+    sb[p.nch * 32 + tid] = bb;
+  }
+  if (p.bn.w_folded_out) {
+    // w' = s w as [cg][taps][C], what backward reads, from the fragments: one worker per window position stores it
+    __syncthreads();
+    if (wfirst == 0) {
+      const float s = sb[cl * 32 + px];
+      bf16_t* out = static_cast<bf16_t*>(p.bn.w_folded_out) + chunk * 32 + px;
 #pragma unroll
-  for (int e = 0; e < 16; ++e)
-    bv[e] = p.bias ? p.bias[chunk * 32 + 8 * (e >> 2) + 4 * kb + (e & 3)] : 0.f;
+      for (int t = 0; t < TAPS; ++t) {
+        if (worker != t % p.nworkers) continue;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int k = ks * 16 + kb * 8 + e;
+            if (KS == 4 || (k >> p.lcg) == (px >> p.lcg))
+              out[((size_t)(KS == 4 ? k : k & (p.cg - 1)) * TAPS + t) * p.C] = (bf16_t)((float)wf[t][ks][e] * s);
+          }
+      }
+    }
+  }
 
   for (int tile = worker; tile < p.ntiles; tile += p.nworkers) {
     const int tc = tile % p.ntc;
@@ -483,7 +514,7 @@ __global__ __launch_bounds__(256) void g_conv_mfma_kernel(GcParams p) {
       const unsigned char* b0 = patch + ((r * p.sh) * p.PC + c * p.sw) * p.pitch + (KS == 4 ? 0 : cl * 64) + kb * 16;
       f32x16 acc;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] = bv[e];
+      for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
       for (int t = 0; t < TAPS; ++t) {
         const int i = t / p.kW, j = t - i * p.kW;
@@ -496,9 +527,13 @@ __global__ __launch_bounds__(256) void g_conv_mfma_kernel(GcParams p) {
       }
       // ---- the wave's 32 pixels x 32 channels through its own LDS block, so that a store is 16 bytes per lane
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q) {   // (accumulator element e is channel 8 (e / 4) + 4 kb + e % 4)
+        const float4 sc = *reinterpret_cast<const float4*>(sb + cl * 32 + q * 8 + kb * 4);
+        const float4 bb = *reinterpret_cast<const float4*>(sb + (p.nch + cl) * 32 + q * 8 + kb * 4);
         *reinterpret_cast<uint2*>(stage + px * 80 + q * 16 + kb * 8) =
-            make_uint2(pack_bf16x2(acc[q * 4 + 0], acc[q * 4 + 1]), pack_bf16x2(acc[q * 4 + 2], acc[q * 4 + 3]));
+            make_uint2(pack_bf16x2(fmaf(acc[q * 4 + 0], sc.x, bb.x), fmaf(acc[q * 4 + 1], sc.y, bb.y)),
+                       pack_bf16x2(fmaf(acc[q * 4 + 2], sc.z, bb.z), fmaf(acc[q * 4 + 3], sc.w, bb.w)));
+      }
 #pragma unroll
       for (int pass = 0; pass < 2; ++pass) {
         const int sp = pass * 16 + (lane >> 2), gq = lane & 3;
@@ -564,7 +599,7 @@ GcPlan gc_plan(int N, int C, int cg, int in_h, int in_w, int out_h, int out_w, i
   p.nwt = ceil_div(p.TR * p.TC, 32);
   p.ntiles = N * p.ntr * p.ntc;
   p.ncg = nchunks / p.nch;
-  pl.lds = (size_t)p.PR * p.PC * p.pitch + 4 * 32 * 80;
+  pl.lds = (size_t)p.PR * p.PC * p.pitch + 4 * 32 * 80 + 2 * 4 * 32 * 4;
   // two persistent workgroups per CU, each walking several tiles (measured: 1 -> 39, 2 -> 35, 4 -> 41, 8 -> 48 us for
   // fold + forward on 128 channels at 56 x 56: more workgroups start and finish in step and leave a longer tail)
   const int per_cu = (int)(160 * 1024 / pl.lds) < 2 ? 1 : 2;
@@ -960,13 +995,24 @@ int direct_splits(const Geom& g, int cg) {
 
 }  // namespace
 
+bool g_fprop_scaled_supported(const Geom& g, int groups, int dtype) {
+  GcParams gp;
+  return gc_fprop_plan(g, groups, dtype, &gp).ok;
+}
+
 hipError_t launch_g_fprop(const Geom& g, int groups, int dtype, const void* x, const void* w_krsc, const float* bias,
-                          void* z, hipStream_t st) {
+                          void* z, hipStream_t st, const BnEpilogue* bn) {
   const int cg = g.Cin / groups, og = g.Cout / groups;
+  if (g3_supported(g, groups, dtype)) {
+    BnEpilogue plain{};
+    plain.b = bias;
+    return launch_g3_fprop(g, groups, x, w_krsc, bn ? *bn : plain, z, st);
+  }
   GcParams gp;
   const GcPlan pl = gc_fprop_plan(g, groups, dtype, &gp);
   if (pl.ok) {
     gp.in = (const bf16_t*)x; gp.w = (const bf16_t*)w_krsc; gp.bias = bias; gp.out = (bf16_t*)z;
+    if (bn) gp.bn = *bn;
     return gc_launch(pl, gp, st);
   }
   if (gv_supported(g, groups, dtype)) return gv_launch(g, groups, false, x, w_krsc, bias, z, st);
@@ -984,6 +1030,7 @@ hipError_t launch_g_fprop(const Geom& g, int groups, int dtype, const void* x, c
 hipError_t launch_g_dgrad(const Geom& g, int groups, int dtype, const void* dz, const void* w_crsk, void* dx,
                           hipStream_t st) {
   const int cg = g.Cin / groups, og = g.Cout / groups;
+  if (g3_supported(g, groups, dtype)) return launch_g3_dgrad(g, groups, dz, w_crsk, dx, st);
   GcParams gp;
   const GcPlan pl = gc_dgrad_plan(g, groups, dtype, &gp);
   if (pl.ok) {
@@ -1008,6 +1055,7 @@ hipError_t launch_g_dgrad(const Geom& g, int groups, int dtype, const void* dz, 
 }
 
 int g_wgrad_slices(const Geom& g, int groups, int dtype) {
+  if (g3_supported(g, groups, dtype)) return g3_wgrad_slices(g);
   GwParams gp;
   if (gw_plan(g, groups, dtype, &gp).ok) return gp.nworkers;
   if (gv_supported(g, groups, dtype)) return gv_wgrad_slices(g, groups);
@@ -1015,6 +1063,7 @@ int g_wgrad_slices(const Geom& g, int groups, int dtype) {
 }
 
 bool g_wgrad_makes_rsum(const Geom& g, int groups, int dtype) {
+  if (g3_supported(g, groups, dtype)) return true;
   GwParams gp;
   return gw_plan(g, groups, dtype, &gp).ok;
 }
@@ -1022,6 +1071,7 @@ bool g_wgrad_makes_rsum(const Geom& g, int groups, int dtype) {
 hipError_t launch_g_wgrad(const Geom& g, int groups, int dtype, const void* x, const void* dz, float* part,
                           float* r_part, hipStream_t st) {
   const int cg = g.Cin / groups, og = g.Cout / groups;
+  if (g3_supported(g, groups, dtype)) return launch_g3_wgrad(g, groups, x, dz, part, r_part, st);
   GwParams gp;
   const GwPlan pl = gw_plan(g, groups, dtype, &gp);
   if (pl.ok) {

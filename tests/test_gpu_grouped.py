@@ -63,6 +63,23 @@ def test_refold_input_gradient_only_and_wide_scale():
     assert res["dW"] is None and res["dgamma"] is None
 
 
+# the row-sweep kernels: every group width, paddings 0-2, strides, segments and strips with a remainder, sides below one segment,
+# several strips per wave
+SWEEP = [(n, c, h, w, g, s, p) for n, c, h, w, g, s, p in [
+    (1, 32, 3, 3, 8, 1, 0), (2, 64, 5, 17, 16, 1, 1), (1, 128, 33, 35, 8, 1, 1), (2, 96, 8, 9, 3, 1, 2), (3, 256, 7, 50, 32, 1, 1),
+    (9, 1024, 7, 7, 32, 1, 1), (70, 32, 30, 29, 4, 1, 1), (1, 32, 3, 3, 8, 2, 0), (2, 64, 6, 35, 16, 2, 1), (1, 128, 33, 70, 8, 2, 1),
+    (2, 96, 8, 9, 3, 2, 2), (3, 256, 7, 49, 32, 2, 1), (9, 1024, 14, 13, 32, 2, 1), (60, 32, 30, 29, 4, 2, 0)]]
+
+
+@pytest.mark.parametrize("n,c,h,w,g,s,p", SWEEP)
+def test_row_sweep(n, c, h, w, g, s, p):
+    shape = BlockShape("g_sweep", n, c, h, w, c, 3, s, p, "bf16", 5 * c + h + w + p)
+    inp = synth.make_grouped_inputs(shape, g, bias=(h + w) % 2 == 0)
+    ref = oracle_grouped_block(inp)
+    compare(_run(inp), ref, "bf16", keys=KEYS, tag=str((n, c, h, w, g, s, p)))
+    compare(_run(inp, keep_folded=False), ref, "bf16", keys=KEYS[:-1], tag="refold")
+
+
 def test_one_group_matches_the_dense_block():
     from paper_2305_11624_amd.runner import BlockRun
     shape = BlockShape("g_dense", 2, 32, 10, 10, 48, 3, 1, 1, "bf16", 127)
