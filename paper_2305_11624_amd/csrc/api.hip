@@ -280,15 +280,14 @@ size_t inner_dgrad_scratch(const Geom& g, int dtype) {
 }
 size_t fprop_scratch_bytes(const Geom& g, int dtype) {
   if (!needs_cin_pad(g, dtype)) return inner_fprop_scratch(g, dtype);
-  if (stem_fprop_supported(g, dtype))
-    return align_up(stem_packed_weight_bytes(g), 256) + align_up(stem_input_copy_bytes(g), 256);
+  if (stem_fprop_supported(g, dtype)) return align_up(stem_input_copy_bytes(g), 256);
   const Geom q = padded_geom(g);
   return align_up((size_t)q.Min * q.Cin * 2, 256) + align_up((size_t)q.Cout * q.K * 2, 256) +
          inner_fprop_scratch(q, dtype);
 }
 size_t dgrad_scratch_bytes(const Geom& g, int dtype) {
   if (!needs_cin_pad(g, dtype)) return inner_dgrad_scratch(g, dtype);
-  if (stem_dgrad_supported(g, dtype)) return align_up(stem_dgrad_weight_bytes(g), 256);
+  if (stem_dgrad_supported(g, dtype)) return 0;
   const Geom q = padded_geom(g);
   return align_up((size_t)q.Cout * q.K * 2, 256) + align_up((size_t)q.Min * q.Cin * 2, 256) +
          inner_dgrad_scratch(q, dtype);
@@ -357,21 +356,21 @@ hipError_t dgrad_any(const Geom& g, int dtype, const void* dz, const void* w_crs
     if (e_ != hipSuccess) return e_;    \
   } while (0)
 
+// A first layer (its own kernel); the scratch holds a 4-channel copy of the input where one is needed.
+hipError_t run_fprop_stem(const Geom& g, int dtype, const void* x, const void* w, const float* bias, void* z, float* scratch,
+                          hipStream_t st, const BnEpilogue* bn) {
+  if (stem_input_copy_bytes(g) != 0) {
+    TRY(launch_repitch(2, (size_t)g.Min, g.Cin, 4, x, scratch, st));
+    x = scratch;
+  }
+  const bool fused = !g.post_add && !g.post_mask;   // (a ReLU alone)
+  TRY(launch_fprop_stem(g, x, w, bias, z, fused && g.post_relu, st, bn));
+  return fused ? hipSuccess : post_op_pass(g, dtype, z, (size_t)g.M * g.Cout, st);
+}
 hipError_t run_fprop(const Geom& g, int dtype, const void* x, const void* w_krsc, const float* bias,
                      void* z, float* scratch, hipStream_t st) {
   if (!needs_cin_pad(g, dtype)) return fprop_any(g, dtype, x, w_krsc, bias, z, scratch, st);
-  if (stem_fprop_supported(g, dtype)) {   // a first layer: its own kernel; the scratch holds the padded weight
-    char* sp = reinterpret_cast<char*>(scratch);
-    void* wpad = sp;
-    sp += align_up(stem_packed_weight_bytes(g), 256);
-    if (stem_input_copy_bytes(g) == 0) {
-      TRY(launch_fprop_stem(g, x, w_krsc, wpad, bias, z, st));
-    } else {
-      TRY(launch_repitch(2, (size_t)g.Min, g.Cin, 4, x, sp, st));   // ... and a 4-channel copy of the input
-      TRY(launch_fprop_stem(g, sp, w_krsc, wpad, bias, z, st));
-    }
-    return post_op_pass(g, dtype, z, (size_t)g.M * g.Cout, st);
-  }
+  if (stem_fprop_supported(g, dtype)) return run_fprop_stem(g, dtype, x, w_krsc, bias, z, scratch, st, nullptr);
   const Geom q = padded_geom(g);
   char* s = reinterpret_cast<char*>(scratch);
   void* xp = s; s += align_up((size_t)q.Min * q.Cin * 2, 256);
@@ -383,8 +382,8 @@ hipError_t run_fprop(const Geom& g, int dtype, const void* x, const void* w_krsc
 hipError_t run_dgrad(const Geom& g, int dtype, const void* dz, const void* w_crsk, void* dx,
                      float* scratch, hipStream_t st) {
   if (!needs_cin_pad(g, dtype)) return dgrad_any(g, dtype, dz, w_crsk, nullptr, dx, scratch, st);
-  if (stem_dgrad_supported(g, dtype)) {   // a first layer: its own kernel; the scratch holds its packed weight
-    TRY(launch_dgrad_stem(g, dz, w_crsk, scratch, dx, st));
+  if (stem_dgrad_supported(g, dtype)) {   // a first layer: its own kernel
+    TRY(launch_dgrad_stem(g, dz, w_crsk, dx, st));
     return post_op_pass(g, dtype, dx, (size_t)g.Min * g.Cin, st);
   }
   Geom q = padded_geom(g);
@@ -730,6 +729,11 @@ convbn_status convbn_tune_fwd(const convbn_desc* desc, const void* x, const void
       if (!FUSED_TILE) LAUNCH(post_op_pass(g, dt, z, nz, st));
       return CONVBN_OK;
     }
+  }
+  if (needs_cin_pad(g, dt) && stem_fprop_supported(g, dt)) {   // a first layer: likewise
+    const BnEpilogue bn{gamma, beta, mean, var, b, g.eps, w_folded, g.kH * g.kW, g.Cin, g.Cout};
+    LAUNCH(run_fprop_stem(g, dt, x, W, nullptr, z, w.conv_scratch, st, &bn));
+    return CONVBN_OK;
   }
   // w' = s w (both orders), b' = (b - mu) s + beta; then Z = w' (*) X + b'
   LAUNCH(launch_fold(g, dt, W, b, gamma, beta, mean, var, 0, w.w_krsc, w_folded, w.bfold, st));

@@ -368,12 +368,11 @@ bool stem_wgrad_supported(const Geom& g, int dtype);
 int stem_wgrad_slices(const Geom& g);             // fp32 partial copies of dw' (and of r) the kernel writes
 hipError_t launch_wgrad_stem(const Geom& g, const void* x, const void* dz, float* part, float* r_part, hipStream_t st);
 bool stem_dgrad_supported(const Geom& g, int dtype);
-size_t stem_dgrad_weight_bytes(const Geom& g);    // scratch for the input gradient's packed weight
-hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, void* wpack, void* dx, hipStream_t st);
-size_t stem_packed_weight_bytes(const Geom& g);   // scratch for the weight padded to 8 window columns x 4 channels
+hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, void* dx, hipStream_t st);
 size_t stem_input_copy_bytes(const Geom& g);      // scratch for a 4-channel copy of the input (0: read as it is)
-hipError_t launch_fprop_stem(const Geom& g, const void* x, const void* w, void* wpad, const float* bias, void* z,
-                             hipStream_t st);
+// bn != nullptr: w is the UNFOLDED weight and the epilogue applies s and b' (w' left on the side); relu: max(z, 0)
+hipError_t launch_fprop_stem(const Geom& g, const void* x, const void* w, const float* bias, void* z, int relu, hipStream_t st,
+                             const BnEpilogue* bn = nullptr);
 
 // conv_igemm.hip : bf16 MFMA implicit GEMM with 64-bit addresses, for tensors of 2 GB and more (channels multiples of 8)
 bool igemm_supported(const Geom& g, int dtype);

@@ -22,8 +22,10 @@ constexpr int KROW = 32;            // reduction elements per window row: 8 colu
 
 struct StemParams {
   const bf16_t* x;      // X3: [N][H][W][3] (W % 4 == 0); else [N][H][W][4]
-  const bf16_t* w;      // [Cout][kH][8][4]: the weight zero-padded to 8 window columns and 4 channels
+  const bf16_t* w;      // [Cout][kH][kW][Cin]
   const float* bias;    // [Cout] or null
+  BnEpilogue bn;        // bn.gamma != null: the weight is unfolded, the epilogue applies s and b' (bias unused)
+  int relu;
   bf16_t* z;            // [N][Ho][Wo][Cout]
   int N, H, W, Cin, Cout, kH, kW, sh, sw, ph, pw, Ho, Wo;
   int ntw, ntiles;      // tiles per output row, tiles in all
@@ -31,6 +33,29 @@ struct StemParams {
   int prow;             // LDS bytes per patch row: ((TPX - 1) sw + 8) * 8
   int pcols;            // pixels per patch row (X3: a multiple of 4, with up to 3 leading pixels of alignment)
 };
+
+// Fetches go through buffer descriptors of one image (its byte offsets fit 30 bits): what is outside is an offset beyond it
+// and reads zeros, so that a fetch has no branch -- behind one, the compiler waited for each load on the spot: three to
+// seven trips to memory in a row per tile (7 x 7 on 224 x 224, 32 images: @STEMF@).
+constexpr unsigned NOWHERE = 1u << 30;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t image_rsrc(const bf16_t* base, int n, size_t elems) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base + (size_t)n * elems), 0, (int)(elems * 2), 0x00020000);
+}
+__device__ __forceinline__ uint2 ld8(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ uint4 ld16(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+
+// A workgroup's tiles: a run of neighbours, which share input rows, and neighbouring runs on one XCD (workgroup ids are dealt
+// round-robin over the 8 of them) with its L2.
+struct TileRun { int first, end; };
+__device__ __forceinline__ TileRun tile_run(int ntiles) {
+  const int n = gridDim.x, b = blockIdx.x, full = n & ~7;
+  const int lb = b < full ? (b & 7) * (full >> 3) + (b >> 3) : b;
+  return TileRun{(int)((long long)ntiles * lb / n), (int)((long long)ntiles * (lb + 1) / n)};
+}
 
 constexpr int ppt(bool x3) { return x3 ? 3 : 8; }   // most patch items a thread fetches per tile
 
@@ -40,22 +65,12 @@ constexpr int ppt(bool x3) { return x3 ? 3 : 8; }   // most patch items a thread
 template <int NCO, int KH, bool X3>
 __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* biasl = reinterpret_cast<float*>(smem);                       // [Cout] (first 512 bytes)
-  unsigned char* wl = smem + 512;                                      // [Cout][wpitch]
+  float* biasl = reinterpret_cast<float*>(smem);                       // [128] b', [128] s (first 1024 bytes)
+  unsigned char* wl = smem + 1024;                                     // [Cout][wpitch]
   unsigned char* patch = wl + 32 * NCO * p.wpitch;                     // [kH][prow]; reused to stage the output tile
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kb = lane >> 5, px = lane & 31;
   const int kH = KH > 0 ? KH : p.kH;
-
-  // ---- resident weights: rows of the padded [Cout][kH][8][4] block, 16 bytes per load
-  const int wrow_g = kH * KROW / 8;   // 16-byte granules per weight row
-  for (int e = tid; e < 32 * NCO * wrow_g; e += 256) {
-    const int co = e / wrow_g, gq = e - co * wrow_g;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (co < p.Cout) v = *reinterpret_cast<const uint4*>(p.w + ((size_t)co * wrow_g + gq) * 8);
-    *reinterpret_cast<uint4*>(wl + co * p.wpitch + gq * 16) = v;
-  }
-  if (tid < 32 * NCO) biasl[tid] = (p.bias && tid < p.Cout) ? p.bias[tid] : 0.f;
 
   // patch item e = tid + 256 k of a tile: (row i, pixel -- X3: group of four pixels -- q), the same for every tile
   constexpr int PPT = ppt(X3);
@@ -81,18 +96,16 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
   auto fetch = [&](int tile) {
     const int ws = tile % p.ntw;
     const int row = tile / p.ntw;
-    const int ho = row % p.Ho, n = row / p.Ho;
+    const int ho = row % p.Ho, n = min(row / p.Ho, p.N - 1);   // (a tile past the last one reads nothing)
     const int wstart = patch_start(ws);
+    const __amdgpu_buffer_rsrc_t xr = image_rsrc(p.x, n, (size_t)p.H * p.W * (X3 ? 3 : 4));
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
       const int h = ho * p.sh + pi[k] - p.ph, w = wstart + pq[k];
+      const bool ok = tid + 256 * k < npatch && tile < p.ntiles && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
+      const unsigned off = ok ? (unsigned)(h * p.W + w) * (X3 ? 6u : 8u) : NOWHERE;
 #pragma unroll
-      for (int j = 0; j < NLD; ++j) pv[k][j] = make_uint2(0u, 0u);
-      if (tid + 256 * k < npatch && tile < p.ntiles && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W) {
-        const uint2* src = reinterpret_cast<const uint2*>(p.x + (((size_t)n * p.H + h) * p.W + w) * (X3 ? 3 : 4));
-#pragma unroll
-        for (int j = 0; j < NLD; ++j) pv[k][j] = src[j];
-      }
+      for (int j = 0; j < NLD; ++j) pv[k][j] = ld8(xr, off + 8 * j);
     }
   };
   // registers -> LDS, every pixel as 4 channels (X3: the 12 values of four pixels spread over 4 x 8 bytes)
@@ -110,16 +123,54 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
       }
     }
   };
-  fetch(blockIdx.x);
+  const TileRun run = tile_run(p.ntiles);
+  fetch(run.first);
 
-  for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
+  // ---- resident weights (behind the first patch's requests): 16-byte granules, two window columns of four channels, zeros
+  // where the window or the channels end
+  const int wrow_g = kH * KROW / 8;   // granules per weight row
+  const int wtot = p.Cout * kH * p.kW * p.Cin;
+  for (int e = tid; e < 32 * NCO * wrow_g; e += 256) {
+    const int co = e / wrow_g, gq = e - co * wrow_g;
+    const int i = gq >> 2, j0 = (gq & 3) * 2;
+    const int at = ((co * kH + i) * p.kW + j0) * p.Cin;
+    const bool c0 = co < p.Cout && j0 < p.kW, c1 = co < p.Cout && j0 + 1 < p.kW;
+    unsigned d[4];
+    if (p.Cin == 3 && at + 6 <= wtot) {   // the six values of the two columns, wherever they lie
+      struct __attribute__((packed)) Six { unsigned a, b, c; };
+      const Six r = *reinterpret_cast<const Six*>(p.w + at);
+      d[0] = c0 ? r.a : 0u;
+      d[1] = c0 ? r.b & 0xffffu : 0u;
+      d[2] = c1 ? r.b >> 16 | r.c << 16 : 0u;
+      d[3] = c1 ? r.c >> 16 : 0u;
+    } else {
+      unsigned v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const bool ok = (q < 4 ? c0 : c1) && (q & 3) < p.Cin;
+        v[q] = ok ? reinterpret_cast<const unsigned short*>(p.w)[at + (q >> 2) * p.Cin + (q & 3)] : 0u;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) d[q] = v[2 * q] | v[2 * q + 1] << 16;
+    }
+    *reinterpret_cast<uint4*>(wl + co * p.wpitch + gq * 16) = make_uint4(d[0], d[1], d[2], d[3]);
+  }
+  if (tid < 32 * NCO) {
+    float sc = 1.f, bb = 0.f;
+    if (tid < p.Cout) bn_scale_bias(p.bn, p.bias, tid, &sc, &bb);
+    biasl[tid] = bb;
+    biasl[128 + tid] = sc;
+  }
+  if (p.bn.gamma && p.bn.w_folded_out) emit_folded_slice(p.bn, p.w, blockIdx.x, gridDim.x);   // w' for backward, on the side
+
+  for (int tile = run.first; tile < run.end; ++tile) {
     const int ws = tile % p.ntw;
     const int row = tile / p.ntw;
     const int ho = row % p.Ho, n = row / p.Ho;
     const int wo0 = ws * TPX;
     __syncthreads();   // the previous tile's staged output has been read
     stash();
-    fetch(tile + gridDim.x);
+    fetch(tile + 1);   // (behind the run's last: the next run's first, dropped)
     __syncthreads();   // patch (and, first pass, weights and bias) visible
 
     f32x16 acc[NCO];
@@ -162,8 +213,9 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
       for (int q = 0; q < 4; ++q) {
         const int ch = f * 32 + q * 8 + kb * 4;
         const float4 bb = *reinterpret_cast<const float4*>(biasl + ch);
-        const uint2 v = make_uint2(pack_bf16x2(acc[f][q * 4 + 0] + bb.x, acc[f][q * 4 + 1] + bb.y),
-                                   pack_bf16x2(acc[f][q * 4 + 2] + bb.z, acc[f][q * 4 + 3] + bb.w));
+        const float4 sc = *reinterpret_cast<const float4*>(biasl + 128 + ch);
+        const uint2 v = make_uint2(pack_bf16x2(fmaf(acc[f][q * 4 + 0], sc.x, bb.x), fmaf(acc[f][q * 4 + 1], sc.y, bb.y)),
+                                   pack_bf16x2(fmaf(acc[f][q * 4 + 2], sc.z, bb.z), fmaf(acc[f][q * 4 + 3], sc.w, bb.w)));
         *reinterpret_cast<uint2*>(st + px * ROWB + (((ch >> 3) ^ psw) << 4) + ((ch & 7) << 1)) = v;
       }
     // (a wave reads only what it wrote itself: no workgroup barrier needed, the LDS counter orders it)
@@ -172,22 +224,14 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
     for (int pass = 0; pass < 32 / RPP; ++pass) {
       const int r = pass * RPP + lane / GR;
       const int g = (lane % GR) ^ ((r >> 1) & (GR - 1));
-      const uint4 v = *reinterpret_cast<const uint4*>(st + r * ROWB + ((lane % GR) << 4));
+      uint4 v = *reinterpret_cast<const uint4*>(st + r * ROWB + ((lane % GR) << 4));
+      if (p.relu) v = relu8(v);
       const int wo = wo0 + wave * 32 + r;
       const int ch = g * 8;
       if (wo < p.Wo && ch < p.Cout)
         *reinterpret_cast<uint4*>(p.z + (((size_t)n * p.Ho + ho) * p.Wo + wo) * p.Cout + ch) = v;
     }
   }
-}
-
-// wp[co][i][j][c] (8 columns, 4 channels) = w[co][i][j][c] where it exists, else 0
-__global__ __launch_bounds__(256) void stem_pack_weights_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp,
-                                                                int Cout, int kH, int kW, int Cin) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= Cout * kH * KROW) return;
-  const int c = e & 3, j = (e >> 2) & 7, t = e >> 5;   // t = co kH + i
-  wp[e] = (j < kW && c < Cin) ? w[((size_t)t * kW + j) * Cin + c] : from_f32<bf16_t>(0.f);
 }
 
 // ---- weight gradient of a first layer ------------------------------------------------------------------
@@ -252,28 +296,26 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
   auto fetch = [&](int tile) {
     const int ws = tile % p.ntw;
     const int row = tile / p.ntw;
-    const int ho = row % p.Ho, n = row / p.Ho;
+    const int ho = row % p.Ho, n = min(row / p.Ho, p.N - 1);   // (a tile past the last one reads nothing)
     const int wstart = patch_start(ws);
+    const __amdgpu_buffer_rsrc_t xr = image_rsrc(p.x, n, (size_t)p.H * p.W * (X3 ? 3 : 4));
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
       const int h = ho * p.sh + pi[k] - p.ph, w = wstart + pq[k];
+      const bool ok = tid + 256 * k < npatch && tile < p.ntiles && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
+      const unsigned off = ok ? (unsigned)(h * p.W + w) * (X3 ? 6u : 8u) : NOWHERE;
 #pragma unroll
-      for (int j = 0; j < NLD; ++j) pv[k][j] = make_uint2(0u, 0u);
-      if (tid + 256 * k < npatch && tile < p.ntiles && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W) {
-        const uint2* src = reinterpret_cast<const uint2*>(p.x + (((size_t)n * p.H + h) * p.W + w) * (X3 ? 3 : 4));
-#pragma unroll
-        for (int j = 0; j < NLD; ++j) pv[k][j] = src[j];
-      }
+      for (int j = 0; j < NLD; ++j) pv[k][j] = ld8(xr, off + 8 * j);
     }
+    const __amdgpu_buffer_rsrc_t zr = image_rsrc(p.dz, n, (size_t)p.Ho * p.Wo * p.Cout);
     // dZ rows of the tile's pixels (zeros past the end of the output row: such pixels then add nothing)
 #pragma unroll
     for (int k = 0; k < ZPT; ++k) {
       const int e = tid + 256 * k;
       const int px = e / ZG, gq = e - px * ZG;
       const int wo = ws * TPX + px;
-      zv[k] = make_uint4(0u, 0u, 0u, 0u);
-      if (tile < p.ntiles && wo < p.Wo && gq * 8 < p.Cout)
-        zv[k] = *reinterpret_cast<const uint4*>(p.dz + (((size_t)n * p.Ho + ho) * p.Wo + wo) * p.Cout + gq * 8);
+      const bool ok = tile < p.ntiles && wo < p.Wo && gq * 8 < p.Cout;
+      zv[k] = ld16(zr, ok ? ((unsigned)(ho * p.Wo + wo) * p.Cout + gq * 8) * 2u : NOWHERE);
     }
   };
   auto stash = [&]() {
@@ -309,12 +351,13 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
   const int rc = tid % CW, rl = tid / CW;
   float racc = 0.f;
 
-  fetch(blockIdx.x);
-  for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
+  const TileRun run = tile_run(p.ntiles);
+  fetch(run.first);
+  for (int tile = run.first; tile < run.end; ++tile) {
     const int ws = tile % p.ntw;
     __syncthreads();   // the previous tile has been read
     stash();
-    fetch(tile + gridDim.x);
+    fetch(tile + 1);   // (behind the run's last: the next run's first, dropped)
     __syncthreads();   // patch and dZ tile visible
     const int lead = ws * TPX * p.sw - p.pw - patch_start(ws);
 #pragma unroll
@@ -340,17 +383,18 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
     }
   }
   // ---- this workgroup's slice.  Accumulator element e of lane l: operand row 8 (e / 4) + 4 (l / 32) + e % 4 =
-  // window column 2 (e / 4) + l / 32, channel e % 4; output channel f 32 + l % 32.
+  // window column 2 (e / 4) + l / 32, channel e % 4; output channel f 32 + l % 32.  32 output channels at a time are gathered in
+  // LDS and leave as whole lines (stored from the registers, 12 bytes of a line each: @STEMW@).
   const int K = p.kH * p.kW * p.Cin;
+  float* const rows = reinterpret_cast<float*>(smem);            // [32][K]
 #pragma unroll
-  for (int t = 0; t < NRW; ++t) {
-    const int i = wave + 4 * t;
-    if (i >= p.kH) break;
+  for (int f = 0; f < NCO; ++f) {
+    __syncthreads();   // every wave is done with the tiles, or with the channels before
 #pragma unroll
-    for (int f = 0; f < NCO; ++f) {
-      const int co = f * 32 + (lane & 31);
-      if (co >= p.Cout) continue;
-      float* orow = p.part + ((size_t)blockIdx.x * p.Cout + co) * K + (size_t)i * p.kW * p.Cin;
+    for (int t = 0; t < NRW; ++t) {
+      const int i = wave + 4 * t;
+      if (i >= p.kH) break;
+      float* orow = rows + (lane & 31) * K + i * p.kW * p.Cin;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int j = 2 * q + kb;
@@ -360,6 +404,10 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
           if (c < p.Cin) orow[j * p.Cin + c] = acc[t][f][q * 4 + c];
       }
     }
+    __syncthreads();
+    const int nco = min(32, p.Cout - f * 32);                    // (a multiple of 8: whole float4s)
+    float4* const out = reinterpret_cast<float4*>(p.part + ((size_t)blockIdx.x * p.Cout + f * 32) * K);
+    for (int e = tid; e < nco * K / 4; e += 256) out[e] = reinterpret_cast<const float4*>(rows)[e];
   }
   if (p.r_part) {
     __syncthreads();   // every wave is done with the tiles: reuse the patch memory
@@ -394,7 +442,10 @@ StemWgPlan stem_wg_work_out(const Geom& g, StemWgParams* pp) {
   if (g.kH * (p.pcols / (x3 ? 4 : 1)) > 256 * ppt(x3)) return pl;
   p.zpitch = 32 * pl.nco * 2 + 16;
   pl.lds = align_up((size_t)g.kH * p.prow, 16) + (size_t)TPX * p.zpitch;
-  if (pl.lds < 1024) pl.lds = 1024;   // the channel sums meet in the first KB at the end
+  // the sums of 32 output channels are gathered there at the end (the channel sums need 1 KB)
+  const size_t gather = (size_t)32 * g.K * 4;
+  if (pl.lds < gather) pl.lds = gather;
+  if (pl.lds < 1024) pl.lds = 1024;
   if (pl.lds > 64 * 1024) return pl;
   // two workgroups per CU (a lone one leaves the CU idle while it waits; 65 -> 48 us on the 7x7 stem); every
   // workgroup writes a full fp32 slice of dw', which the fold-back has to sum, so not more
@@ -433,9 +484,9 @@ constexpr int DG_NBT = 2;      // most 16-block groups a wave multiplies per til
 
 struct StemDgParams {
   const bf16_t* dz;     // [N][Ho][Wo][Cout]
-  const bf16_t* wt;     // [16][U V Cout] packed by stem_dgrad_pack_kernel
+  const bf16_t* w;      // w' as [Cin][kH][kW][Cout]
   bf16_t* dx;           // [N][H][W][Cin]
-  int N, H, W, Cin, Cout, Ho, Wo, sh, sw;
+  int N, H, W, Cin, Cout, Ho, Wo, kH, kW, sh, sw, ph, pw;
   int U, V, Dh, Dw;     // block (a, b) reads dZ rows a + Dh - u (u < U), columns b + Dw - v (v < V)
   int KT;               // U V Cout
   int TBR, TBC;         // blocks per tile
@@ -460,12 +511,6 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 15, kg = lane >> 4;                        // MFMA column (block) / row (phase, c) and 8-channel group
 
-  // ---- resident weight
-  const int wgr = p.KT / 8;                                         // 16-byte granules per row
-  for (int e = tid; e < 16 * wgr; e += 256) {
-    const int r = e / wgr, gq = e - r * wgr;
-    *reinterpret_cast<uint4*>(wl + r * p.wpitch + gq * 16) = *reinterpret_cast<const uint4*>(p.wt + (size_t)r * p.KT + gq * 8);
-  }
   // ---- patch items of this thread: granule gq (8 channels) of patch pixel (row, column), the same for every tile
   const int gpp = p.Cout / 8;
   const int nitems = p.PR * p.PC * gpp;
@@ -479,18 +524,17 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
   }
   uint4 pv[DG_PPT];
   auto fetch = [&](int tile) {
-    const int tc = tile % p.nbc;
-    const int t2 = tile / p.nbc;
-    const int tr = t2 % p.nbr, n = t2 / p.nbr;
+    const int tr = tile % p.nbr;   // (down the columns: the rows that two tiles share come from the cache)
+    const int t2 = tile / p.nbr;
+    const int tc = t2 % p.nbc, n = min(t2 / p.nbc, p.N - 1);   // (a tile past the last one reads nothing)
+    const __amdgpu_buffer_rsrc_t zr = image_rsrc(p.dz, n, (size_t)p.Ho * p.Wo * p.Cout);
     // patch row r holds dZ row a0 + Dh - (U - 1) + r, column likewise
     const int h0 = tr * p.TBR + p.Dh - (p.U - 1), w0 = tc * p.TBC + p.Dw - (p.V - 1);
 #pragma unroll
     for (int k = 0; k < DG_PPT; ++k) {
       const int h = h0 + ipr[k], w = w0 + (ipc[k] & 0xffff), gq = ipc[k] >> 16;
       const bool ok = tid + 256 * k < nitems && tile < p.ntiles && (unsigned)h < (unsigned)p.Ho && (unsigned)w < (unsigned)p.Wo;
-      const size_t off = ok ? (((size_t)n * p.Ho + h) * p.Wo + w) * p.Cout + gq * 8 : 0;
-      const uint4 v = *reinterpret_cast<const uint4*>(p.dz + off);
-      pv[k] = make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
+      pv[k] = ld16(zr, ok ? ((unsigned)(h * p.Wo + w) * p.Cout + gq * 8) * 2u : NOWHERE);
     }
   };
   auto stash = [&]() {
@@ -502,14 +546,45 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
 
   const int nph = p.sh * p.sw;                 // phases: rows 4 phase + c of the product
   const int ksteps = p.Cout / 32;
-  fetch(blockIdx.x);
-  for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
-    const int tc = tile % p.nbc;
-    const int t2 = tile / p.nbc;
-    const int tr = t2 % p.nbr, n = t2 / p.nbr;
+  const TileRun run = tile_run(p.ntiles);
+  fetch(run.first);
+  // ---- resident weight (behind the first patch's requests): Wt[(phase, c)][(u, v, co)], phase (qh, qw) reaching dZ row
+  // a + dh(qh) - t through window row i0(qh) + sh t, i.e. u = Dh - dh(qh) + t; zeros where a phase has no tap and in the rows of
+  // c >= Cin.  16 bytes (8 output channels) at a time, four of them in flight.
+  {
+    const int cg = KS > 0 ? KS * 4 : p.Cout / 8, V = VV > 0 ? VV : p.V, UV = UU > 0 ? UU * VV : p.U * p.V;
+    const int lh = p.sh - 1, lw = p.sw - 1;   // (strides 1 and 2: quotients are shifts)
+    const int total = 16 * UV * cg;
+    for (int e0 = tid; e0 < total; e0 += 4 * 256) {
+      uint4 v[4];
+      bool ok[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = min(e0 + 256 * k, total - 1);
+        const int pair = e / cg, co = (e - pair * cg) * 8;
+        const int r = pair / UV, uv = pair - r * UV, u = uv / V, v_ = uv - u * V;
+        const int phase = r >> 2, c = r & 3, qh = phase >> lw, qw = phase & lw;
+        const int th = u - (p.Dh - ((qh + p.ph) >> lh)), tw = v_ - (p.Dw - ((qw + p.pw) >> lw));
+        const int i = ((qh + p.ph) & lh) + p.sh * th, j = ((qw + p.pw) & lw) + p.sw * tw;
+        ok[k] = phase < nph && c < p.Cin && th >= 0 && tw >= 0 && i < p.kH && j < p.kW;
+        v[k] = *reinterpret_cast<const uint4*>(p.w + (ok[k] ? (((size_t)c * p.kH + i) * p.kW + j) * p.Cout + co : 0));
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = e0 + 256 * k, r = e / (UV * cg), gq = e - r * UV * cg;
+        if (e < total)
+          *reinterpret_cast<uint4*>(wl + r * p.wpitch + gq * 16) =
+              make_uint4(ok[k] ? v[k].x : 0u, ok[k] ? v[k].y : 0u, ok[k] ? v[k].z : 0u, ok[k] ? v[k].w : 0u);
+      }
+    }
+  }
+  for (int tile = run.first; tile < run.end; ++tile) {
+    const int tr = tile % p.nbr;   // (down the columns: the rows that two tiles share come from the cache)
+    const int t2 = tile / p.nbr;
+    const int tc = t2 % p.nbc, n = t2 / p.nbc;
     __syncthreads();   // the previous tile's patch and staged rows have been read
     stash();
-    fetch(tile + gridDim.x);
+    fetch(tile + 1);   // (behind the run's last: the next run's first, dropped)
     __syncthreads();   // patch (and, first pass, the weight) visible
     // the wave's block groups: wave, wave + 4 (the lane's block: q = 16 group + col -> row ar, column bc of the tile)
     int ar[DG_NBT], bc[DG_NBT];
@@ -579,28 +654,6 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
   }
 }
 
-// Wt[(phase, c)][(u, v, co)] from w' as [Cin][kH][kW][Cout]: phase (qh, qw) reaches dZ row a + dh(qh) - t through
-// window row i0(qh) + sh t, i.e. u = Dh - dh(qh) + t; zeros where a phase has no tap and in the rows of c >= Cin
-__global__ __launch_bounds__(256) void stem_dgrad_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wt,
-                                                              int Cin, int Cout, int kH, int kW, int sh, int sw, int ph,
-                                                              int pw, int U, int V, int Dh, int Dw) {
-  const int KT = U * V * Cout;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= 16 * KT) return;
-  const int r = e / KT, k = e - r * KT;
-  const int co = k % Cout, uv = k / Cout, v = uv % V, u = uv / V;
-  const int phase = r >> 2, c = r & 3;
-  float val = 0.f;
-  if (phase < sh * sw && c < Cin) {
-    const int qh = phase / sw, qw = phase % sw;
-    const int i = (qh + ph) % sh + sh * (u - (Dh - (qh + ph) / sh));
-    const int j = (qw + pw) % sw + sw * (v - (Dw - (qw + pw) / sw));
-    if (u >= Dh - (qh + ph) / sh && v >= Dw - (qw + pw) / sw && i < kH && j < kW)
-      val = to_f32(w[(((size_t)c * kH + i) * kW + j) * Cout + co]);
-  }
-  wt[e] = from_f32<bf16_t>(val);
-}
-
 struct StemDgPlan { bool ok; size_t lds; int grid; };
 StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
   StemDgPlan pl{false, 0, 0};
@@ -608,6 +661,7 @@ StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
   p = StemDgParams{};
   if (g.sh > 2 || g.sw > 2 || g.Cout % 32 != 0 || g.Cout > 128) return pl;
   p.N = g.N; p.H = g.Hin; p.W = g.Win; p.Cin = g.Cin; p.Cout = g.Cout; p.Ho = g.Hout; p.Wo = g.Wout; p.sh = g.sh; p.sw = g.sw;
+  p.kH = g.kH; p.kW = g.kW; p.ph = g.ph; p.pw = g.pw;
   // per phase q: first window row i0 = (q + pad) % s, its dZ row offset d = (q + pad) / s, taps T = ceil((k - i0) / s)
   auto span = [](int k, int s, int pad, int* D, int* U) {
     int dmax = 0;
@@ -662,7 +716,8 @@ StemDgPlan stem_dg_plan(const Geom& g, StemDgParams* pp) {
 }
 
 bool stem_shape(const Geom& g, int dtype) {
-  return dtype == CONVBN_BF16 && g.Cin <= 4 && g.kW <= 8 && g.kH <= 16 && g.Cout % 8 == 0 && g.Cout <= 128 && g.sw <= 4;
+  return dtype == CONVBN_BF16 && g.Cin <= 4 && g.kW <= 8 && g.kH <= 16 && g.Cout % 8 == 0 && g.Cout <= 128 && g.sw <= 4 &&
+         (size_t)g.Hin * g.Win * 8 < NOWHERE && (size_t)g.Hout * g.Wout * g.Cout * 2 < NOWHERE;
 }
 
 struct StemPlan { bool ok; bool x3; int nco; size_t lds; int grid; };
@@ -684,7 +739,7 @@ StemPlan stem_work_out(const Geom& g, StemParams* pp) {
   if (g.kH * (p.pcols / (x3 ? 4 : 1)) > 256 * ppt(x3)) return pl;   // the patch is fetched in at most ppt() rounds
   const size_t stage = (size_t)4 * 32 * 32 * pl.nco * 2;            // the output tile is staged over the patch
   const size_t patch = (size_t)g.kH * p.prow;
-  pl.lds = 512 + (size_t)32 * pl.nco * p.wpitch + (patch > stage ? patch : stage);
+  pl.lds = 1024 + (size_t)32 * pl.nco * p.wpitch + (patch > stage ? patch : stage);
   if (pl.lds > 64 * 1024) return pl;   // two or more workgroups per CU hide each other's phases
   const int per_cu = (int)(160 * 1024 / pl.lds) < 4 ? (int)(160 * 1024 / pl.lds) : 4;
   pl.grid = p.ntiles < 256 * per_cu ? p.ntiles : 256 * per_cu;
@@ -738,20 +793,12 @@ bool stem_dgrad_supported(const Geom& g, int dtype) {
   StemDgParams p;
   return stem_dg_plan(g, &p).ok;
 }
-size_t stem_dgrad_weight_bytes(const Geom& g) {
-  StemDgParams p;
-  return stem_dg_plan(g, &p).ok ? (size_t)16 * p.KT * 2 : 0;
-}
-// w_crsk: w' as [Cin][kH][kW][Cout]; wpack: stem_dgrad_weight_bytes() of scratch
-hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, void* wpack, void* dx, hipStream_t st) {
+// w_crsk: w' as [Cin][kH][kW][Cout]
+hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, void* dx, hipStream_t st) {
   StemDgParams p;
   const StemDgPlan pl = stem_dg_plan(g, &p);
   if (!pl.ok) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(stem_dgrad_pack_kernel, dim3(ceil_div(16 * p.KT, 256)), dim3(256), 0, st, (const bf16_t*)w_crsk,
-                     (bf16_t*)wpack, g.Cin, g.Cout, g.kH, g.kW, g.sh, g.sw, g.ph, g.pw, p.U, p.V, p.Dh, p.Dw);
-  hipError_t pe = hipGetLastError();
-  if (pe != hipSuccess) return pe;
-  p.dz = (const bf16_t*)dz; p.wt = (const bf16_t*)wpack; p.dx = (bf16_t*)dx;
+  p.dz = (const bf16_t*)dz; p.w = (const bf16_t*)w_crsk; p.dx = (bf16_t*)dx;
 #define STEMDG(UUV, VVV, KSV)                                                                                         \
   do {                                                                                                             \
     static LdsLimitOnce lds_once;                                                                                  \
@@ -771,21 +818,16 @@ bool stem_fprop_supported(const Geom& g, int dtype) {
   return stem_plan(g, &p).ok;
 }
 
-size_t stem_packed_weight_bytes(const Geom& g) { return (size_t)g.Cout * g.kH * KROW * 2; }
-
-// x: the input as it is, or its 4-channel copy where stem_input_copy_bytes() != 0; w: the (folded) weight in its own
-// [Cout][kH][kW][Cin] order; wpad: stem_packed_weight_bytes() of scratch for its zero-padded copy
-hipError_t launch_fprop_stem(const Geom& g, const void* x, const void* w, void* wpad, const float* bias, void* z,
-                             hipStream_t st) {
+// x: the input as it is, or its 4-channel copy where stem_input_copy_bytes() != 0; w: the (folded, or with bn the unfolded)
+// weight in its own [Cout][kH][kW][Cin] order
+hipError_t launch_fprop_stem(const Geom& g, const void* x, const void* w, const float* bias, void* z, int relu, hipStream_t st,
+                             const BnEpilogue* bn) {
   StemParams p;
   const StemPlan pl = stem_plan(g, &p);
   if (!pl.ok) return hipErrorInvalidValue;
-  const int nel = g.Cout * g.kH * KROW;
-  hipLaunchKernelGGL(stem_pack_weights_kernel, dim3(ceil_div(nel, 256)), dim3(256), 0, st, (const bf16_t*)w,
-                     (bf16_t*)wpad, g.Cout, g.kH, g.kW, g.Cin);
-  hipError_t pe = hipGetLastError();
-  if (pe != hipSuccess) return pe;
-  p.x = (const bf16_t*)x; p.w = (const bf16_t*)wpad; p.bias = bias; p.z = (bf16_t*)z;
+  if (bn) p.bn = *bn;
+  p.relu = relu;
+  p.x = (const bf16_t*)x; p.w = (const bf16_t*)w; p.bias = bias; p.z = (bf16_t*)z;
 #define STEM(NC, KHV, X3V)                                                                                              \
   do {                                                                                                             \
     static LdsLimitOnce lds_once;                                                                                  \

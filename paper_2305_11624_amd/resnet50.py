@@ -127,8 +127,8 @@ class ResNet50:
         self.arena_bytes = self.kept_bytes = 0   # per-unit grouping: the shared arena (workspace) and the kept w'
         shapes = synth.resnet50_blocks(N, image, dtype)
         # inside a bottleneck unit: ReLU behind the first two blocks, hence in front of the last two (the ReLU behind
-        # the unit follows the residual sum and stays an element-wise pass, like the stem's in front of the max-pool)
-        act = {"a": B.ACT_RELU_OUT, "b": B.ACT_RELU_OUT | B.ACT_RELU_IN, "c": B.ACT_RELU_IN}
+        # the unit follows the residual sum); ReLU behind the stem, in front of the max-pool
+        act = {"stem": B.ACT_RELU_OUT, "a": B.ACT_RELU_OUT, "b": B.ACT_RELU_OUT | B.ACT_RELU_IN, "c": B.ACT_RELU_IN}
         self.blocks: Dict[str, _Block] = {s.name: _Block(s, device, mode, act.get(s.name.rsplit(".", 1)[-1], 0))
                                           for s in shapes}
         self.order: List[str] = [s.name for s in shapes]
@@ -257,8 +257,7 @@ class ResNet50:
         ws, bl = self.ws, self.blocks
         if self.group_fold:
             self._fold_all()
-        z0 = bl["stem"].forward(x, ws)
-        B.convbn_aux_eltwise(B.OP_RELU, z0)
+        z0 = bl["stem"].forward(x, ws)           # (ReLU applied by the block)
         n, h, w, c = z0.shape
         p = torch.empty((n, (h - 1) // 2 + 1, (w - 1) // 2 + 1, c), dtype=self.dt, device=x.device)
         idx = torch.empty(p.shape, dtype=torch.uint8, device=x.device)
