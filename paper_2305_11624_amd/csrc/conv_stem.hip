@@ -36,7 +36,7 @@ struct StemParams {
 
 // Fetches go through buffer descriptors of one image (its byte offsets fit 30 bits): what is outside is an offset beyond it
 // and reads zeros, so that a fetch has no branch -- behind one, the compiler waited for each load on the spot: three to
-// seven trips to memory in a row per tile (7 x 7 on 224 x 224, 32 images: @STEMF@).
+// seven trips to memory in a row per tile (weight gradient, 7 x 7 on 224 x 224, 32 images: 46.3 -> 42.8 us).
 constexpr unsigned NOWHERE = 1u << 30;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t image_rsrc(const bf16_t* base, int n, size_t elems) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base + (size_t)n * elems), 0, (int)(elems * 2), 0x00020000);
@@ -56,6 +56,9 @@ __device__ __forceinline__ TileRun tile_run(int ntiles) {
   const int lb = b < full ? (b & 7) * (full >> 3) + (b >> 3) : b;
   return TileRun{(int)((long long)ntiles * lb / n), (int)((long long)ntiles * (lb + 1) / n)};
 }
+
+// pixels of a patch row (x3: up to 3 leading ones, whole groups of four)
+constexpr int patch_cols(int sw, bool x3) { return x3 ? ((TPX - 1) * sw + 8 + 3 + 3) / 4 * 4 : (TPX - 1) * sw + 8; }
 
 constexpr int ppt(bool x3) { return x3 ? 3 : 8; }   // most patch items a thread fetches per tile
 
@@ -109,7 +112,7 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
     }
   };
   // registers -> LDS, every pixel as 4 channels (X3: the 12 values of four pixels spread over 4 x 8 bytes)
-  auto stash = [&]() {
+  auto stash = [&](unsigned char* patch) {
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
       if (tid + 256 * k >= npatch) continue;
@@ -162,6 +165,77 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
     biasl[128 + tid] = sc;
   }
   if (p.bn.gamma && p.bn.w_folded_out) emit_folded_slice(p.bn, p.w, blockIdx.x, gridDim.x);   // w' for backward, on the side
+  if constexpr (KH > 0) {
+    // Known window height: the weight fragments stay in registers (read from LDS for every tile they were two thirds of its
+    // traffic), which leaves room for two patches: a tile's successor is put in place while it is multiplied and stored, one
+    // barrier a tile, and the outputs leave straight from the accumulators (the forward pass 25.9 -> 24.5 us).
+    __syncthreads();
+    const unsigned char* const wrow0 = wl + px * p.wpitch + kb * 16;
+    bf16x8 wreg[2 * KH][NCO];
+#pragma unroll
+    for (int q = 0; q < 2 * KH; ++q)
+#pragma unroll
+      for (int f = 0; f < NCO; ++f) wreg[q][f] = *reinterpret_cast<const bf16x8*>(wrow0 + f * 32 * p.wpitch + q * 32);
+    __syncthreads();   // the patches take the weights' place
+    unsigned char* cur = wl;
+    unsigned char* nxt = wl + KH * p.prow;
+    stash(cur);
+    fetch(run.first + 1);
+    __syncthreads();
+    for (int tile = run.first; tile < run.end; ++tile) {
+      const int ws = tile % p.ntw;
+      const int row = tile / p.ntw;
+      const int ho = row % p.Ho, n = row / p.Ho;
+      const int wo = ws * TPX + wave * 32 + px;
+      f32x16 acc[NCO];
+#pragma unroll
+      for (int f = 0; f < NCO; ++f)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[f][e] = 0.f;
+      const int lead = ws * TPX * p.sw - p.pw - patch_start(ws);
+      const unsigned char* const prow0 = cur + ((wave * 32 + px) * p.sw + 2 * kb + lead) * 8;
+#pragma unroll
+      for (int i = 0; i < KH; ++i)
+#pragma unroll
+        for (int jh = 0; jh < 2; ++jh) {
+          const unsigned char* bp = prow0 + i * p.prow + jh * 32;
+          const uint2 b0 = *reinterpret_cast<const uint2*>(bp);
+          const uint2 b1 = *reinterpret_cast<const uint2*>(bp + 8);
+          const bf16x8 fb = __builtin_bit_cast(bf16x8, make_uint4(b0.x, b0.y, b1.x, b1.y));
+#pragma unroll
+          for (int f = 0; f < NCO; ++f) acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wreg[i * 2 + jh][f], fb, acc[f], 0, 0, 0);
+        }
+      // accumulator element e of lane l: channel 32 f + 8 (e / 4) + 4 (l / 32) + e % 4 of pixel l % 32; swapping the halves of
+      // two registers gives every lane 8 channels of its pixel
+      bf16_t* const zrow = p.z + (((size_t)n * p.Ho + ho) * p.Wo + wo) * p.Cout;
+#pragma unroll
+      for (int f = 0; f < NCO; ++f)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          unsigned pk[2][2];
+#pragma unroll
+          for (int qq = 0; qq < 2; ++qq) {
+            const int q = 2 * j + qq, ch = 32 * f + 8 * q + 4 * kb;
+            const float4 bb = *reinterpret_cast<const float4*>(biasl + ch), sc = *reinterpret_cast<const float4*>(biasl + 128 + ch);
+            pk[qq][0] = pack_bf16x2(fmaf(acc[f][4 * q], sc.x, bb.x), fmaf(acc[f][4 * q + 1], sc.y, bb.y));
+            pk[qq][1] = pack_bf16x2(fmaf(acc[f][4 * q + 2], sc.z, bb.z), fmaf(acc[f][4 * q + 3], sc.w, bb.w));
+          }
+          const auto lo = __builtin_amdgcn_permlane32_swap(pk[0][0], pk[1][0], false, false);
+          const auto hi = __builtin_amdgcn_permlane32_swap(pk[0][1], pk[1][1], false, false);
+          uint4 v = make_uint4(lo[0], hi[0], lo[1], hi[1]);
+          if (p.relu) v = relu8(v);
+          const int ch = 32 * f + (2 * j + kb) * 8;
+          if (wo < p.Wo && ch < p.Cout) *reinterpret_cast<uint4*>(zrow + ch) = v;
+        }
+      stash(nxt);
+      fetch(tile + 2);   // (behind the run's last: neighbours', dropped)
+      __syncthreads();
+      unsigned char* const t = cur;
+      cur = nxt;
+      nxt = t;
+    }
+    return;
+  }
 
   for (int tile = run.first; tile < run.end; ++tile) {
     const int ws = tile % p.ntw;
@@ -169,7 +243,7 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
     const int ho = row % p.Ho, n = row / p.Ho;
     const int wo0 = ws * TPX;
     __syncthreads();   // the previous tile's staged output has been read
-    stash();
+    stash(patch);
     fetch(tile + 1);   // (behind the run's last: the next run's first, dropped)
     __syncthreads();   // patch (and, first pass, weights and bias) visible
 
@@ -193,12 +267,7 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
         acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[f], 0, 0, 0);
       }
     };
-    if (KH > 0) {
-#pragma unroll
-      for (int i = 0; i < KH; ++i) { kstep(i, 0); kstep(i, 1); }
-    } else {
-      for (int i = 0; i < kH; ++i) { kstep(i, 0); kstep(i, 1); }
-    }
+    for (int i = 0; i < kH; ++i) { kstep(i, 0); kstep(i, 1); }
     __syncthreads();   // every wave is done with the patch: its memory now stages the output tile
     // ---- epilogue: accumulator element e of lane l is channel 8 (e / 4) + 4 (l / 32) + e % 4 of pixel l % 32.
     // Each wave rounds its 32 pixels x Cout channels into its own LDS block ([pixel][Cout], 16-byte granules
@@ -262,13 +331,19 @@ struct StemWgParams {
   int N, H, W, Cin, Cout, kH, kW, sh, sw, ph, pw, Ho, Wo;
   int ntw, ntiles, prow, pcols;
   int zpitch;           // LDS bytes per dZ pixel row: 2 Cout + 16
+  int zt, buf, nbuf;    // LDS: offset of the dZ tile in a buffer, bytes of a buffer, buffers
 };
 
-template <int NCO, bool X3>
-__global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
+// KH, SW: window rows and column stride at compile time (0: taken from the parameters): every operand is then an offset field
+// of the reads, the eight steps of a tile are unrolled, and a row of ones behind the patch's (KH = 7) is wave 3's second: 33.2
+// -> 23.5 us, the matrix pipe busy for a quarter of them.
+template <int NCO, bool X3, int KH, int SW>
+__global__ __launch_bounds__(256, 2) void stem_wgrad_kernel(StemWgParams p) {
+  static_assert(KH == 0 || KH == 7, "seven window rows and the row of ones are two a wave");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* patch = smem;                                   // [kH][prow]
-  unsigned char* zt = smem + (p.kH * p.prow + 15) / 16 * 16;      // [TPX][zpitch]
+  // two buffers (one, where two do not fit): patch [kH][prow], behind it at p.zt the dZ tile [TPX][zpitch]
+  unsigned char* cur = smem;
+  unsigned char* nxt = smem + (p.nbuf - 1) * p.buf;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kb = lane >> 5;
   const int eprime = (lane & 15) >> 2;                           // pixel (of 4) this lane addresses in a transposing read
@@ -278,6 +353,8 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
   constexpr int ZG = 32 * NCO * 2 / 16;                          // 16-byte granules per dZ pixel row
   constexpr int ZPT = TPX * ZG / 256;                            // granules per thread and tile
 
+  const int sw = SW > 0 ? SW : p.sw;
+  const int prow = SW > 0 ? patch_cols(SW, X3) * 8 : p.prow, zpitch = KH > 0 ? 64 * NCO + 16 : p.zpitch;
   const int icols = p.pcols / PXI;
   const int npatch = p.kH * icols;
   int pi[PPT], pq[PPT];
@@ -288,9 +365,14 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
     pq[k] = (e - pi[k] * icols) * PXI;
   }
   auto patch_start = [&](int ws) {
-    const int wbase = ws * TPX * p.sw - p.pw;
+    const int wbase = ws * TPX * sw - p.pw;
     return X3 ? (wbase >> 2) << 2 : wbase;
   };
+  if constexpr (KH > 0)
+    for (int e = tid; e < prow / 4; e += 256) {
+      reinterpret_cast<unsigned*>(cur + KH * prow)[e] = 0x3f803f80u;
+      reinterpret_cast<unsigned*>(nxt + KH * prow)[e] = 0x3f803f80u;
+    }
   uint2 pv[PPT][NLD];
   uint4 zv[ZPT];
   auto fetch = [&](int tile) {
@@ -318,11 +400,11 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
       zv[k] = ld16(zr, ok ? ((unsigned)(ho * p.Wo + wo) * p.Cout + gq * 8) * 2u : NOWHERE);
     }
   };
-  auto stash = [&]() {
+  auto stash = [&](unsigned char* patch) {
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
       if (tid + 256 * k >= npatch) continue;
-      unsigned char* dst = patch + pi[k] * p.prow + pq[k] * 8;
+      unsigned char* dst = patch + pi[k] * prow + pq[k] * 8;
       if constexpr (X3) {
         const uint2 a = pv[k][0], b = pv[k][1], c = pv[k][2];
         *reinterpret_cast<uint4*>(dst) = make_uint4(a.x, a.y & 0xffffu, (a.y >> 16) | (b.x << 16), b.x >> 16);
@@ -335,7 +417,7 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
     for (int k = 0; k < ZPT; ++k) {
       const int e = tid + 256 * k;
       const int px = e / ZG, gq = e - px * ZG;
-      *reinterpret_cast<uint4*>(zt + px * p.zpitch + gq * 16) = zv[k];
+      *reinterpret_cast<uint4*>(patch + p.zt + px * zpitch + gq * 16) = zv[k];
     }
   };
 
@@ -346,45 +428,63 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
     for (int f = 0; f < NCO; ++f)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[t][f][e] = 0.f;
-  // channel sums: thread -> channel tid % Cout' (Cout' = 32 NCO), every (256 / Cout')-th pixel
-  constexpr int CW = 32 * NCO, RL = 256 / CW;
-  const int rc = tid % CW, rl = tid / CW;
-  float racc = 0.f;
+  // The channel sums r are the product of the dZ fragments with ones, by wave 3, which has one window row fewer (of up to 7).
+  // Read from the tile by the vector units they were 32 LDS reads a thread and tile.
+  const s16x8 one_bits = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, one_bits);
+  f32x16 racc[NCO];
+#pragma unroll
+  for (int f = 0; f < NCO; ++f)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) racc[f][e] = 0.f;
 
   const TileRun run = tile_run(p.ntiles);
   fetch(run.first);
-  for (int tile = run.first; tile < run.end; ++tile) {
+  stash(cur);
+  fetch(run.first + 1);
+  __syncthreads();
+  for (int tile = run.first; tile < run.end; ++tile) {   // a tile's successor is put in place behind its products
     const int ws = tile % p.ntw;
-    __syncthreads();   // the previous tile has been read
-    stash();
-    fetch(tile + 1);   // (behind the run's last: the next run's first, dropped)
-    __syncthreads();   // patch and dZ tile visible
-    const int lead = ws * TPX * p.sw - p.pw - patch_start(ws);
-#pragma unroll
-    for (int px = rl; px < TPX; px += RL)
-      racc += bf16_bits_to_f32(*reinterpret_cast<const unsigned short*>(zt + px * p.zpitch + rc * 2));
+    const int lead = ws * TPX * sw - p.pw - patch_start(ws);
     // lane-constant parts of the operand addresses
-    const unsigned char* zl = zt + (kb * 8 + eprime) * p.zpitch + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
-    const unsigned char* xl = patch + (((kb * 8 + eprime) * p.sw + quad + lead) * 8);
-    for (int k = 0; k < TPX / 16; ++k) {
+    const unsigned char* zl = cur + p.zt + (kb * 8 + eprime) * zpitch + (((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2;
+    const unsigned char* xl = cur + wave * prow + (((kb * 8 + eprime) * sw + quad + lead) * 8);
+    auto step = [&](int k) {
       bf16x8 zf[NCO];
 #pragma unroll
       for (int f = 0; f < NCO; ++f)
-        zf[f] = join(read_tr(zl + (k * 16) * p.zpitch + f * 64), read_tr(zl + (k * 16 + 4) * p.zpitch + f * 64));
+        zf[f] = join(read_tr(zl + (k * 16) * zpitch + f * 64), read_tr(zl + (k * 16 + 4) * zpitch + f * 64));
 #pragma unroll
       for (int t = 0; t < NRW; ++t) {
-        const int i = wave + 4 * t;
-        if (i >= p.kH) break;
-        const unsigned char* xr = xl + i * p.prow + (k * 16) * p.sw * 8;
-        const bf16x8 xf = join(read_tr(xr), read_tr(xr + 4 * p.sw * 8));
+        if (KH == 0 && wave + 4 * t >= p.kH) break;
+        const unsigned char* xr = xl + 4 * t * prow + (k * 16) * sw * 8;
+        const bf16x8 xf = join(read_tr(xr), read_tr(xr + 4 * sw * 8));
 #pragma unroll
         for (int f = 0; f < NCO; ++f) acc[t][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, zf[f], acc[t][f], 0, 0, 0);
       }
+      if (KH == 0 && wave == 3) {
+#pragma unroll
+        for (int f = 0; f < NCO; ++f) racc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, zf[f], racc[f], 0, 0, 0);
+      }
+    };
+    if constexpr (KH > 0) {
+#pragma unroll
+      for (int k = 0; k < TPX / 16; ++k) step(k);
+    } else {
+      for (int k = 0; k < TPX / 16; ++k) step(k);
     }
+    if (p.nbuf == 1) __syncthreads();   // every wave is done with the buffer
+    stash(nxt);
+    fetch(tile + 2);   // (behind the run's last: neighbours', dropped)
+    __syncthreads();
+    unsigned char* const t = cur;
+    cur = nxt;
+    nxt = t;
   }
   // ---- this workgroup's slice.  Accumulator element e of lane l: operand row 8 (e / 4) + 4 (l / 32) + e % 4 =
   // window column 2 (e / 4) + l / 32, channel e % 4; output channel f 32 + l % 32.  32 output channels at a time are gathered in
-  // LDS and leave as whole lines (stored from the registers, 12 bytes of a line each: @STEMW@).
+  // LDS and leave as whole lines (stored from the registers, 12 bytes
+  // of a line each, the kernel took 42.8 us, like this 34.0).
   const int K = p.kH * p.kW * p.Cin;
   float* const rows = reinterpret_cast<float*>(smem);            // [32][K]
 #pragma unroll
@@ -409,23 +509,16 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemWgParams p) {
     float4* const out = reinterpret_cast<float4*>(p.part + ((size_t)blockIdx.x * p.Cout + f * 32) * K);
     for (int e = tid; e < nco * K / 4; e += 256) out[e] = reinterpret_cast<const float4*>(rows)[e];
   }
-  if (p.r_part) {
-    __syncthreads();   // every wave is done with the tiles: reuse the patch memory
-    float* red = reinterpret_cast<float*>(smem);
-    red[tid] = racc;
-    __syncthreads();
-    if (tid < CW && tid < p.Cout) {
-      float v = 0.f;
+  if (p.r_part && wave == 3 && kb == 0) {   // (every row of the product is the sum; column l % 32)
 #pragma unroll
-      for (int l = 0; l < RL; ++l) v += red[l * CW + tid];
-      p.r_part[(size_t)blockIdx.x * p.Cout + tid] = v;
-    }
+    for (int f = 0; f < NCO; ++f)
+      if (f * 32 + lane < p.Cout) p.r_part[(size_t)blockIdx.x * p.Cout + f * 32 + lane] = KH > 0 ? acc[1][f][0] : racc[f][0];
   }
 }
 
-struct StemWgPlan { bool ok; bool x3; int nco; size_t lds; int grid; };
+struct StemWgPlan { bool ok; bool x3; bool known; int nco; size_t lds; int grid; };
 StemWgPlan stem_wg_work_out(const Geom& g, StemWgParams* pp) {
-  StemWgPlan pl{false, false, 0, 0, 0};
+  StemWgPlan pl{false, false, false, 0, 0, 0};
   StemWgParams& p = *pp;
   p = StemWgParams{};
   if (g.kH > 8) return pl;   // two window rows per wave
@@ -434,19 +527,21 @@ StemWgPlan stem_wg_work_out(const Geom& g, StemWgParams* pp) {
   p.ntw = ceil_div(g.Wout, TPX);
   p.ntiles = g.N * g.Hout * p.ntw;
   const bool x3 = g.Cin == 3 && g.Win % 4 == 0;
-  p.pcols = (TPX - 1) * g.sw + 8;
-  if (x3) p.pcols = (p.pcols + 3 + 3) / 4 * 4;
+  p.pcols = patch_cols(g.sw, x3);
   p.prow = p.pcols * 8;
   pl.nco = ceil_div(g.Cout, 32);
   if (pl.nco != 1 && pl.nco != 2 && pl.nco != 4) return pl;
   if (g.kH * (p.pcols / (x3 ? 4 : 1)) > 256 * ppt(x3)) return pl;
   p.zpitch = 32 * pl.nco * 2 + 16;
-  pl.lds = align_up((size_t)g.kH * p.prow, 16) + (size_t)TPX * p.zpitch;
-  // the sums of 32 output channels are gathered there at the end (the channel sums need 1 KB)
+  pl.known = x3 && pl.nco == 2 && g.kH == 7 && g.sw == 2;   // the usual 7x7 / stride-2 RGB stem with 64 channels
+  p.zt = (int)align_up((size_t)(g.kH + (pl.known ? 1 : 0)) * p.prow, 16);
+  p.buf = p.zt + TPX * p.zpitch;
+  p.nbuf = 2 * p.buf <= 80 * 1024 ? 2 : 1;   // (two workgroups share a compute unit's 160 KB)
+  pl.lds = (size_t)p.nbuf * p.buf;
+  // the sums of 32 output channels are gathered there at the end
   const size_t gather = (size_t)32 * g.K * 4;
   if (pl.lds < gather) pl.lds = gather;
-  if (pl.lds < 1024) pl.lds = 1024;
-  if (pl.lds > 64 * 1024) return pl;
+  if (pl.lds > 80 * 1024) return pl;
   // two workgroups per CU (a lone one leaves the CU idle while it waits; 65 -> 48 us on the 7x7 stem); every
   // workgroup writes a full fp32 slice of dw', which the fold-back has to sum, so not more
   pl.grid = p.ntiles < 512 ? p.ntiles : 512;
@@ -476,8 +571,7 @@ StemWgPlan stem_wg_plan(const Geom& g, StemWgParams* pp) {
 // 16 output "channels" are un-shuffled to pixels (depth to space).  MFMA 16x16x32: rows = the 16 (phase, c)
 // pairs, columns = 16 blocks, 32 output channels of one (u, v) per step; as in the forward kernel the column
 // operand is read straight from the raw dZ patch in LDS (lane = block, 16 contiguous bytes = 8 channels) and the
-// packed weight (16 x U V Cout) stays resident in LDS.  A lane ends up with the 4 channels of one dX pixel; the
-// tile's pixels are gathered in LDS and leave as whole rows.
+// packed weight (16 x U V Cout) stays resident.  A lane ends up with the 4 channels of one dX pixel.
 typedef float f32x4s __attribute__((ext_vector_type(4)));
 constexpr int DG_PPT = 8;      // most 16-byte patch items a thread fetches per tile
 constexpr int DG_NBT = 2;      // most 16-block groups a wave multiplies per tile
@@ -494,8 +588,7 @@ struct StemDgParams {
   int PR, PC, pitch;    // dZ patch rows (TBR + U - 1), columns (TBC + V - 1), bytes per pixel (2 Cout + 16)
   int wpitch;           // LDS bytes per weight row (2 KT + 16)
   int nbt;              // 16-block groups per tile
-  int orow;             // elements per staged dX row: TBC sw Cin
-  int fast_store;       // rows leave as 16-byte pieces (all alignments allow it)
+  int nbuf;             // patches in LDS
   unsigned mTBC, mPC;   // multipliers for n / TBC, n / PC (n < 65536)
 };
 
@@ -503,11 +596,11 @@ __device__ __forceinline__ int dg_div(int n, unsigned m, int d) { return d == 1 
 
 // UU, VV, KS: the dZ neighbourhood and Cout / 32 at compile time (0: taken from the parameters)
 template <int UU, int VV, int KS>
-__global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
+__global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* wl = smem;                                         // [16][wpitch]
-  unsigned char* patch = wl + 16 * p.wpitch;                        // [PR][PC][pitch]
-  bf16_t* ost = reinterpret_cast<bf16_t*>(patch + (size_t)p.PR * p.PC * p.pitch);   // [TBR sh][orow]
+  unsigned char* wl = smem;                                         // [16][wpitch] (UU == 0)
+  unsigned char* cur = UU > 0 ? smem : wl + 16 * p.wpitch;          // two patches (one, where two do not fit): [PR][PC][pitch]
+  unsigned char* nxt = cur + (p.nbuf - 1) * p.PR * p.PC * p.pitch;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 15, kg = lane >> 4;                        // MFMA column (block) / row (phase, c) and 8-channel group
 
@@ -537,7 +630,7 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
       pv[k] = ld16(zr, ok ? ((unsigned)(h * p.Wo + w) * p.Cout + gq * 8) * 2u : NOWHERE);
     }
   };
-  auto stash = [&]() {
+  auto stash = [&](unsigned char* patch) {
 #pragma unroll
     for (int k = 0; k < DG_PPT; ++k)
       if (tid + 256 * k < nitems)
@@ -550,42 +643,58 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
   fetch(run.first);
   // ---- resident weight (behind the first patch's requests): Wt[(phase, c)][(u, v, co)], phase (qh, qw) reaching dZ row
   // a + dh(qh) - t through window row i0(qh) + sh t, i.e. u = Dh - dh(qh) + t; zeros where a phase has no tap and in the rows of
-  // c >= Cin.  16 bytes (8 output channels) at a time, four of them in flight.
-  {
-    const int cg = KS > 0 ? KS * 4 : p.Cout / 8, V = VV > 0 ? VV : p.V, UV = UU > 0 ? UU * VV : p.U * p.V;
-    const int lh = p.sh - 1, lw = p.sw - 1;   // (strides 1 and 2: quotients are shifts)
+  // c >= Cin.  The element offset of w' that row r, position (u, v) reads, -1: none (strides 1 and 2: quotients are shifts):
+  const int lh = p.sh - 1, lw = p.sw - 1;
+  auto tap_at = [&](int r, int u, int v) {
+    const int phase = r >> 2, c = r & 3, qh = phase >> lw, qw = phase & lw;
+    const int th = u - (p.Dh - ((qh + p.ph) >> lh)), tw = v - (p.Dw - ((qw + p.pw) >> lw));
+    const int i = ((qh + p.ph) & lh) + p.sh * th, j = ((qw + p.pw) & lw) + p.sw * tw;
+    return phase < nph && c < p.Cin && th >= 0 && tw >= 0 && i < p.kH && j < p.kW ? ((c * p.kH + i) * p.kW + j) * p.Cout : -1;
+  };
+  // Known window: the fragments stay in registers, straight from w' (in LDS they were a third of its reads, which were what bound
+  // the kernel, and 33 KB; 41.3 -> 33.3 us with the stores below).
+  bf16x8 wreg[UU > 0 ? UU : 1][VV > 0 ? VV : 1][KS > 0 ? KS : 1];
+  if constexpr (UU > 0) {
+#pragma unroll
+    for (int u = 0; u < UU; ++u)
+#pragma unroll
+      for (int v = 0; v < VV; ++v) {
+        const int at = tap_at(col, u, v);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const uint4 t = *reinterpret_cast<const uint4*>(p.w + max(at, 0) + ks * 32 + kg * 8);
+          wreg[u][v][ks] = __builtin_bit_cast(bf16x8, make_uint4(at >= 0 ? t.x : 0u, at >= 0 ? t.y : 0u, at >= 0 ? t.z : 0u, at >= 0 ? t.w : 0u));
+        }
+      }
+  } else {
+    const int cg = p.Cout / 8, UV = p.U * p.V;
     const int total = 16 * UV * cg;
-    for (int e0 = tid; e0 < total; e0 += 4 * 256) {
+    for (int e0 = tid; e0 < total; e0 += 4 * 256) {   // 16 bytes (8 output channels) at a time, four of them in flight
       uint4 v[4];
-      bool ok[4];
+      int at[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int e = min(e0 + 256 * k, total - 1);
-        const int pair = e / cg, co = (e - pair * cg) * 8;
-        const int r = pair / UV, uv = pair - r * UV, u = uv / V, v_ = uv - u * V;
-        const int phase = r >> 2, c = r & 3, qh = phase >> lw, qw = phase & lw;
-        const int th = u - (p.Dh - ((qh + p.ph) >> lh)), tw = v_ - (p.Dw - ((qw + p.pw) >> lw));
-        const int i = ((qh + p.ph) & lh) + p.sh * th, j = ((qw + p.pw) & lw) + p.sw * tw;
-        ok[k] = phase < nph && c < p.Cin && th >= 0 && tw >= 0 && i < p.kH && j < p.kW;
-        v[k] = *reinterpret_cast<const uint4*>(p.w + (ok[k] ? (((size_t)c * p.kH + i) * p.kW + j) * p.Cout + co : 0));
+        const int pair = e / cg, r = pair / UV, uv = pair - r * UV, u = uv / p.V;
+        at[k] = tap_at(r, u, uv - u * p.V);
+        v[k] = *reinterpret_cast<const uint4*>(p.w + max(at[k], 0) + (e - pair * cg) * 8);
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int e = e0 + 256 * k, r = e / (UV * cg), gq = e - r * UV * cg;
         if (e < total)
           *reinterpret_cast<uint4*>(wl + r * p.wpitch + gq * 16) =
-              make_uint4(ok[k] ? v[k].x : 0u, ok[k] ? v[k].y : 0u, ok[k] ? v[k].z : 0u, ok[k] ? v[k].w : 0u);
+              make_uint4(at[k] >= 0 ? v[k].x : 0u, at[k] >= 0 ? v[k].y : 0u, at[k] >= 0 ? v[k].z : 0u, at[k] >= 0 ? v[k].w : 0u);
       }
     }
   }
+  stash(cur);
+  fetch(run.first + 1);
+  __syncthreads();   // patch (and the weight) visible
   for (int tile = run.first; tile < run.end; ++tile) {
     const int tr = tile % p.nbr;   // (down the columns: the rows that two tiles share come from the cache)
     const int t2 = tile / p.nbr;
     const int tc = t2 % p.nbc, n = t2 / p.nbc;
-    __syncthreads();   // the previous tile's patch and staged rows have been read
-    stash();
-    fetch(tile + 1);   // (behind the run's last: the next run's first, dropped)
-    __syncthreads();   // patch (and, first pass, the weight) visible
     // the wave's block groups: wave, wave + 4 (the lane's block: q = 16 group + col -> row ar, column bc of the tile)
     int ar[DG_NBT], bc[DG_NBT];
     bool live[DG_NBT];
@@ -599,12 +708,14 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
       ar[t] = a; bc[t] = q - a * p.TBC;
       const bool in = live[t] && a < p.TBR;
       // window origin of the block in the patch: its (u, v) = (0, 0) neighbour is patch pixel (ar + U - 1, bc + V - 1)
-      bp[t] = patch + ((in ? a + p.U - 1 : p.U - 1) * p.PC + (in ? bc[t] + p.V - 1 : p.V - 1)) * p.pitch + kg * 16;
+      bp[t] = cur + ((in ? a + p.U - 1 : p.U - 1) * p.PC + (in ? bc[t] + p.V - 1 : p.V - 1)) * p.pitch + kg * 16;
       acc[t] = f32x4s{0.f, 0.f, 0.f, 0.f};
     }
     const unsigned char* ap = wl + col * p.wpitch + kg * 16;
     auto step = [&](int u, int v, int ks, int nv, int cout2) {
-      const bf16x8 fa = *reinterpret_cast<const bf16x8*>(ap + (u * nv + v) * cout2 + ks * 64);
+      bf16x8 fa;
+      if constexpr (UU > 0) fa = wreg[u][v][ks];
+      else fa = *reinterpret_cast<const bf16x8*>(ap + (u * nv + v) * cout2 + ks * 64);
       const int boff = -(u * p.PC + v) * p.pitch + ks * 64;
 #pragma unroll
       for (int t = 0; t < DG_NBT; ++t) {
@@ -624,39 +735,36 @@ __global__ __launch_bounds__(256) void stem_dgrad_kernel(StemDgParams p) {
         for (int v = 0; v < p.V; ++v)
           for (int ks = 0; ks < ksteps; ++ks) step(u, v, ks, p.V, p.Cout * 2);
     }
-    // ---- lane (col, kg): block col of the group, product rows 4 kg .. 4 kg + 3 = phase kg, channels 0..3
+    // ---- lane (col, kg): block col of the group, product rows 4 kg .. 4 kg + 3 = phase kg, channels 0..3: one pixel, stored
+    // as it is (neighbouring lanes write neighbouring bytes; gathering a tile's rows in LDS first cost a barrier and its reads)
 #pragma unroll
     for (int t = 0; t < DG_NBT; ++t) {
-      if (!live[t] || ar[t] >= p.TBR || kg >= nph) continue;
-      const int prow = ar[t] * p.sh + kg / p.sw, pcol = bc[t] * p.sw + kg % p.sw;
-      bf16_t* o = ost + (size_t)prow * p.orow + pcol * p.Cin;
-      for (int c = 0; c < p.Cin; ++c) o[c] = from_f32<bf16_t>(acc[t][c]);
-    }
-    __syncthreads();   // the tile's dX pixels are staged
-    const int h0 = tr * p.TBR * p.sh, w0 = tc * p.TBC * p.sw;
-    const int rows = p.TBR * p.sh;
-    if (p.fast_store) {
-      const int cpr = p.orow * 2 / 16;                               // 16-byte pieces per staged row
-      const int wbytes = p.W * p.Cin * 2, b0 = w0 * p.Cin * 2;
-      for (int e = tid; e < rows * cpr; e += 256) {
-        const int r = e / cpr, c = e - r * cpr;
-        if (h0 + r < p.H && b0 + c * 16 + 16 <= wbytes)
-          *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(p.dx) + ((size_t)n * p.H + h0 + r) * wbytes + b0 + c * 16) =
-              *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(ost) + (size_t)r * p.orow * 2 + c * 16);
-      }
-    } else {
-      for (int e = tid; e < rows * p.orow; e += 256) {
-        const int r = e / p.orow, c = e - r * p.orow;
-        if (h0 + r < p.H && w0 * p.Cin + c < p.W * p.Cin)
-          p.dx[((size_t)n * p.H + h0 + r) * p.W * p.Cin + w0 * p.Cin + c] = ost[(size_t)r * p.orow + c];
+      const int h = (tr * p.TBR + ar[t]) * p.sh + (kg >> lw), w = (tc * p.TBC + bc[t]) * p.sw + (kg & lw);
+      if (!live[t] || ar[t] >= p.TBR || kg >= nph || h >= p.H || w >= p.W) continue;
+      bf16_t* const o = p.dx + (((size_t)n * p.H + h) * p.W + w) * p.Cin;
+      const unsigned lo = pack_bf16x2(acc[t][0], acc[t][1]), hi = pack_bf16x2(acc[t][2], acc[t][3]);
+      if (p.Cin == 3) {
+        struct __attribute__((packed)) Three { unsigned a; unsigned short b; };
+        *reinterpret_cast<Three*>(o) = Three{lo, (unsigned short)hi};
+      } else if (p.Cin == 4) {
+        *reinterpret_cast<uint2*>(o) = make_uint2(lo, hi);
+      } else {
+        for (int c = 0; c < p.Cin; ++c) o[c] = from_f32<bf16_t>(acc[t][c]);
       }
     }
+    if (p.nbuf == 1) __syncthreads();   // every wave is done with the patch
+    stash(nxt);
+    fetch(tile + 2);   // (behind the run's last: neighbours', dropped)
+    __syncthreads();
+    unsigned char* const t = cur;
+    cur = nxt;
+    nxt = t;
   }
 }
 
-struct StemDgPlan { bool ok; size_t lds; int grid; };
+struct StemDgPlan { bool ok; bool known; size_t lds; int grid; };
 StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
-  StemDgPlan pl{false, 0, 0};
+  StemDgPlan pl{false, false, 0, 0};
   StemDgParams& p = *pp;
   p = StemDgParams{};
   if (g.sh > 2 || g.sw > 2 || g.Cout % 32 != 0 || g.Cout > 128) return pl;
@@ -693,11 +801,12 @@ StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
   p.nbt = ceil_div(p.TBR * p.TBC, 16);
   if (p.nbt > 4 * DG_NBT || p.PR * p.PC * (g.Cout / 8) > 256 * DG_PPT) return pl;
   p.ntiles = g.N * p.nbr * p.nbc;
-  p.orow = p.TBC * g.sw * g.Cin;
-  p.fast_store = (p.orow * 2) % 16 == 0 && (g.Win * g.Cin * 2) % 16 == 0;
   p.mTBC = (unsigned)((1ull << 32) / (unsigned)p.TBC + 1);
   p.mPC = (unsigned)((1ull << 32) / (unsigned)p.PC + 1);
-  pl.lds = (size_t)16 * p.wpitch + (size_t)p.PR * p.PC * p.pitch + align_up((size_t)p.TBR * g.sh * p.orow * 2, 16);
+  pl.known = p.U == 4 && p.V == 4 && g.Cout == 64;   // the usual 7x7 / stride-2 stem with 64 channels: unrolled, weights in registers
+  const size_t weight = pl.known ? 0 : (size_t)16 * p.wpitch, patch = (size_t)p.PR * p.PC * p.pitch;
+  p.nbuf = weight + 2 * patch <= 80 * 1024 ? 2 : 1;
+  pl.lds = weight + p.nbuf * patch;
   if (pl.lds > 80 * 1024) return pl;   // two workgroups per CU
   const int per_cu = (int)(160 * 1024 / pl.lds) < 2 ? 1 : 2;
   pl.grid = p.ntiles < 256 * per_cu ? p.ntiles : 256 * per_cu;
@@ -731,8 +840,7 @@ StemPlan stem_work_out(const Geom& g, StemParams* pp) {
   p.ntiles = g.N * g.Hout * p.ntw;
   p.wpitch = g.kH * KROW * 2 + 16;
   const bool x3 = g.Cin == 3 && g.Win % 4 == 0;
-  p.pcols = (TPX - 1) * g.sw + 8;
-  if (x3) p.pcols = (p.pcols + 3 + 3) / 4 * 4;   // up to 3 leading pixels, whole groups of four
+  p.pcols = patch_cols(g.sw, x3);
   p.prow = p.pcols * 8;
   pl.nco = ceil_div(g.Cout, 32);
   if (pl.nco != 1 && pl.nco != 2 && pl.nco != 4) return pl;
@@ -741,7 +849,11 @@ StemPlan stem_work_out(const Geom& g, StemParams* pp) {
   const size_t patch = (size_t)g.kH * p.prow;
   pl.lds = 1024 + (size_t)32 * pl.nco * p.wpitch + (patch > stage ? patch : stage);
   if (pl.lds > 64 * 1024) return pl;   // two or more workgroups per CU hide each other's phases
-  const int per_cu = (int)(160 * 1024 / pl.lds) < 4 ? (int)(160 * 1024 / pl.lds) : 4;
+  int per_cu = (int)(160 * 1024 / pl.lds) < 4 ? (int)(160 * 1024 / pl.lds) : 4;
+  if (x3 && pl.nco == 2 && g.kH == 7) {   // (weights in registers, two patches)
+    per_cu = 2;
+    if (pl.lds < 1024 + 2 * patch) pl.lds = 1024 + 2 * patch;
+  }
   pl.grid = p.ntiles < 256 * per_cu ? p.ntiles : 256 * per_cu;
   pl.x3 = x3;
   pl.ok = true;
@@ -781,9 +893,16 @@ hipError_t launch_wgrad_stem(const Geom& g, const void* x, const void* dz, float
   const StemWgPlan pl = stem_wg_plan(g, &p);
   if (!pl.ok) return hipErrorInvalidValue;
   p.x = (const bf16_t*)x; p.dz = (const bf16_t*)dz; p.part = part; p.r_part = r_part;
-#define STEMWG(NC, X3V) hipLaunchKernelGGL((stem_wgrad_kernel<NC, X3V>), dim3(pl.grid), dim3(256), pl.lds, st, p)
-  if (pl.x3) { if (pl.nco == 1) STEMWG(1, true); else if (pl.nco == 2) STEMWG(2, true); else STEMWG(4, true); }
-  else { if (pl.nco == 1) STEMWG(1, false); else if (pl.nco == 2) STEMWG(2, false); else STEMWG(4, false); }
+#define STEMWG(NC, X3V, KHV, SWV)                                                                                     \
+  do {                                                                                                                \
+    static LdsLimitOnce lds_once;                                                                                     \
+    if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&stem_wgrad_kernel<NC, X3V, KHV, SWV>), 80 * 1024); \
+        e != hipSuccess) return e;                                                                                    \
+    hipLaunchKernelGGL((stem_wgrad_kernel<NC, X3V, KHV, SWV>), dim3(pl.grid), dim3(256), pl.lds, st, p);              \
+  } while (0)
+  if (pl.known) STEMWG(2, true, 7, 2);
+  else if (pl.x3) { if (pl.nco == 1) STEMWG(1, true, 0, 0); else if (pl.nco == 2) STEMWG(2, true, 0, 0); else STEMWG(4, true, 0, 0); }
+  else { if (pl.nco == 1) STEMWG(1, false, 0, 0); else if (pl.nco == 2) STEMWG(2, false, 0, 0); else STEMWG(4, false, 0, 0); }
 #undef STEMWG
   return hipGetLastError();
 }
@@ -806,7 +925,7 @@ hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, 
                                           80 * 1024); e != hipSuccess) return e;                                   \
     hipLaunchKernelGGL((stem_dgrad_kernel<UUV, VVV, KSV>), dim3(pl.grid), dim3(256), pl.lds, st, p);                \
   } while (0)
-  if (p.U == 4 && p.V == 4 && g.Cout == 64) STEMDG(4, 4, 2);   // the usual 7x7 / stride-2 stem with 64 channels: unrolled
+  if (pl.known) STEMDG(4, 4, 2);
   else STEMDG(0, 0, 0);
 #undef STEMDG
   return hipGetLastError();

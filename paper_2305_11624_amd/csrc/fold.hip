@@ -216,19 +216,17 @@ __device__ __forceinline__ void fold_back_row(
     }
   } else if (K * 2 <= NTHR) {
     // short rows whose length is not a multiple of 4 (a first layer: 7 x 7 x 3): thread -> (element k, group g of the
-    // partial copies), 32 copies in flight per thread (512 copies: with eight, eleven trips to memory in a row and 12.0 us, now
-    // @FB@), the groups meet in LDS
+    // partial copies), eight copies in flight per thread, the groups meet in LDS
     const int G = NTHR / K;
     const int k = tid % K, g = tid / K;
     float v = 0.f;
     if (g < G) {
       const float* col = part + (size_t)co * K + k;
-      for (int sp0 = g; sp0 < nsplit; sp0 += 32 * G) {
-        float a[32];
+      for (int sp0 = g; sp0 < nsplit; sp0 += 8 * G) {
+        float a[8];
 #pragma unroll
-        for (int j = 0; j < 32; ++j) a[j] = sp0 + j * G < nsplit ? col[(size_t)(sp0 + j * G) * P] : 0.f;
-#pragma unroll
-        for (int j = 0; j < 32; j += 4) v += (a[j] + a[j + 1]) + (a[j + 2] + a[j + 3]);
+        for (int j = 0; j < 8; ++j) a[j] = sp0 + j * G < nsplit ? col[(size_t)(sp0 + j * G) * P] : 0.f;
+        v += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
       }
     }
     reds[tid] = v;
