@@ -671,6 +671,16 @@ __global__ __launch_bounds__(1024) void dw3_fold_back_kernel(const float* __rest
   __shared__ float sums[80];
   const int tid = threadIdx.x;
   const int v4 = tid % 20, l = tid / 20;
+  // (everything that is read is asked for at once) thread q * 8 + e: tap q of channel e, thread e: its vectors
+  const int ch = blockIdx.x * 8 + (tid & 7);
+  float w = 0.f, ga = 1.f, va = 1.f, mu = 0.f, bc = 0.f;
+  if (tid < 72) w = (float)W[(size_t)ch * 9 + (tid >> 3)];
+  if (tid < 72 && gamma) {
+    ga = gamma[ch];
+    va = var[ch];
+    mu = mean[ch];
+    if (b) bc = b[ch];
+  }
   const float4* src = reinterpret_cast<const float4*>(part + (size_t)blockIdx.x * slices * 80);
   if (l < LN) {
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -699,22 +709,22 @@ __global__ __launch_bounds__(1024) void dw3_fold_back_kernel(const float* __rest
     sums[tid] = v;
   }
   __syncthreads();
-  if (tid >= 8) return;
-  const int c = blockIdx.x * 8 + tid;
-  const float sd = gamma ? sqrtf(var[c] + eps) : 1.f;
-  const float s = gamma ? gamma[c] / sd : 1.f;
+  const float sd = gamma ? sqrtf(va + eps) : 1.f;
+  const float sc = gamma ? ga / sd : 1.f;
+  if (tid < 72) {
+    const float dw = sums[tid];
+    dW[(size_t)ch * 9 + (tid >> 3)] = (bf16_t)(sc * dw);
+    mid[0][tid] = dw * w;
+  }
+  __syncthreads();
+  if (tid >= 8 || !gamma) return;
   float dot = 0.f;
 #pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const float dw = sums[q * 8 + tid];
-    dW[(size_t)c * 9 + q] = (bf16_t)(s * dw);
-    dot += dw * (float)W[(size_t)c * 9 + q];
-  }
-  if (!gamma) return;
+  for (int q = 0; q < 9; ++q) dot += mid[0][q * 8 + tid];
   const float r = sums[72 + tid];
-  dgamma[c] = (dot + r * ((b ? b[c] : 0.f) - mean[c])) / sd;
-  dbeta[c] = r;
-  if (db) db[c] = s * r;
+  dgamma[ch] = (dot + r * (bc - mu)) / sd;
+  dbeta[ch] = r;
+  if (db) db[ch] = sc * r;
 }
 
 // ---- host side of these kernels

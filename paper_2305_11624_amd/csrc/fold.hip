@@ -142,17 +142,23 @@ __device__ __forceinline__ void fold_back_row(
   __shared__ float red[NSL];
   const int tid = threadIdx.x;
   const size_t P = (size_t)Cout * K;
-  float s = 1.f, sd = 1.f;
+  // Every trip to memory that does not depend on another starts here: with the weight, r and the channel's vectors read where
+  // they are used, four trips in a row, a launch took 4.6 us on 72 -> 136 channels at 27 x 33 and 5.6 on 64 -> 64 at 56 x 56;
+  // now 4.0 and 5.0.
+  float s = 1.f, sd = 1.f, mu = 0.f, bc = 0.f, r0 = 0.f;
   if (!identity) {
-    sd = sqrtf(var[co] + eps);
-    s = gamma[co] / sd;
+    const float ga = gamma[co], va = var[co];
+    mu = mean[co];
+    if (b) bc = b[co];
+    if (tid < nrpart) r0 = r_part[(size_t)tid * Cout + co];
+    sd = sqrtf(va + eps);
+    s = ga / sd;
   }
   float dot = 0.f;
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto finish = [&](int k4, const float4& v) {   // dW = s dw', <dw', w> of one float4 column
+  auto finish = [&](int k4, const float4& v, const float (&w4)[4]) {   // dW = s dw', <dw', w> of one float4 column
     const float g4[4] = {v.x, v.y, v.z, v.w};
-    float w4[4], o4[4];
-    load4(W + (size_t)co * K + 4 * k4, w4);
+    float o4[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       o4[e] = s * g4[e];
@@ -167,6 +173,8 @@ __device__ __forceinline__ void fold_back_row(
     const float* row = part + (size_t)co * K;
     for (int k4 = tid; k4 < K4; k4 += NTHR) {
       float4 v = zero4;
+      float w4[4];
+      load4(W + (size_t)co * K + 4 * k4, w4);
       int sp = 0;
       for (; sp + 3 < nsplit; sp += 4) {
         const float4 a0 = ld4(row + (size_t)sp * P + 4 * k4);
@@ -182,7 +190,7 @@ __device__ __forceinline__ void fold_back_row(
         const float4 a0 = ld4(row + (size_t)sp * P + 4 * k4);
         v.x += a0.x; v.y += a0.y; v.z += a0.z; v.w += a0.w;
       }
-      finish(k4, v);
+      finish(k4, v, w4);
     }
   } else if (VEC) {
     // short rows (fewer than 256 columns): thread -> (column c, group g of the partial copies)
@@ -190,6 +198,8 @@ __device__ __forceinline__ void fold_back_row(
     const int G = NTHR / K4;
     const int c = tid % K4, g = tid / K4;
     float4 v = zero4;
+    float w4[4] = {0.f, 0.f, 0.f, 0.f};
+    if (g == 0) load4(W + (size_t)co * K + 4 * c, w4);
     if (g < G) {
       const float* col = part + (size_t)co * K + 4 * c;
       for (int sp0 = g; sp0 < nsplit; sp0 += 16 * G) {
@@ -212,7 +222,7 @@ __device__ __forceinline__ void fold_back_row(
         const float4 o = red4[l * K4 + c];
         v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
       }
-      finish(c, v);
+      finish(c, v, w4);
     }
   } else if (K * 2 <= NTHR) {
     // short rows whose length is not a multiple of 4 (a first layer: 7 x 7 x 3): thread -> (element k, group g of the
@@ -220,6 +230,7 @@ __device__ __forceinline__ void fold_back_row(
     const int G = NTHR / K;
     const int k = tid % K, g = tid / K;
     float v = 0.f;
+    const float w = g == 0 ? to_f32(W[(size_t)co * K + k]) : 0.f;
     if (g < G) {
       const float* col = part + (size_t)co * K + k;
       for (int sp0 = g; sp0 < nsplit; sp0 += 8 * G) {
@@ -235,11 +246,12 @@ __device__ __forceinline__ void fold_back_row(
       for (int l = 1; l < G; ++l) v += reds[l * K + k];
       const size_t idx = (size_t)co * K + k;
       dW[idx] = from_f32<T>(s * v);
-      dot += v * to_f32(W[idx]);
+      dot += v * w;
     }
   } else {
     for (int k = tid; k < K; k += NTHR) {
       const size_t idx = (size_t)co * K + k;
+      const float w = to_f32(W[idx]);
       float v = 0.f;
       int sp = 0;
       for (; sp + 7 < nsplit; sp += 8) {   // eight copies in flight: each load is a round trip of its own
@@ -250,12 +262,12 @@ __device__ __forceinline__ void fold_back_row(
       }
       for (; sp < nsplit; ++sp) v += part[sp * P + idx];
       dW[idx] = from_f32<T>(s * v);
-      dot += v * to_f32(W[idx]);
+      dot += v * w;
     }
   }
   if (identity) return;
-  float r = 0.f;
-  for (int q = tid; q < nrpart; q += NTHR) r += r_part[(size_t)q * Cout + co];
+  float r = r0;
+  for (int q = tid + NTHR; q < nrpart; q += NTHR) r += r_part[(size_t)q * Cout + co];
   dot = wave_sum(dot);
   r = wave_sum(r);
   __shared__ float redr[NSL];
@@ -265,9 +277,8 @@ __device__ __forceinline__ void fold_back_row(
     dot = 0.f;
     r = 0.f;
     for (int l = 0; l < NSL; ++l) { dot += red[l]; r += redr[l]; }
-    const float bc = b ? b[co] : 0.f;
     dbeta[co] = r;
-    dgamma[co] = (dot + r * (bc - mean[co])) / sd;
+    dgamma[co] = (dot + r * (bc - mu)) / sd;
     if (db) db[co] = s * r;
   }
 }
