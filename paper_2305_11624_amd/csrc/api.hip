@@ -469,16 +469,15 @@ TconvFwdWs carve_tconv_fwd(const Geom& g, int dtype, void* ws) {
   r.bytes = c.off;
   return r;
 }
-struct TconvBwdWs { void* w_same; float* dwf_part; float* r_part; float* dot_part; float* conv_scratch; void* wgrad_scratch; int nsplit; int nrpart; size_t bytes; };
+struct TconvBwdWs { void* w_same; float* dwf_part; float* r_part; float* dot_part; float* conv_scratch; void* wgrad_scratch; int nsplit; size_t bytes; };
 TconvBwdWs carve_tconv_bwd(const Geom& g, int dtype, void* ws) {
   Carve c(ws);
   TconvBwdWs r;
   r.nsplit = nsplit_for(g, dtype);
-  r.nrpart = colsum_parts(tconv_out_rows(g));
   r.w_same = c.take((size_t)g.Cout * g.K * esize(dtype));
   r.dwf_part = (float*)c.take((size_t)r.nsplit * g.Cout * g.K * 4);
-  r.r_part = (float*)c.take((size_t)r.nrpart * g.Cin * 4);
-  r.dot_part = (float*)c.take((size_t)fold_back_t_chunks(g.Cout, g.kH * g.kW) * g.Cin * 4);
+  r.r_part = (float*)c.take((size_t)colsum_parts(tconv_out_rows(g)) * g.Cin * 4);
+  r.dot_part = (float*)c.take((size_t)fold_back_t_chunks(g.Cout, g.Cin, g.kH * g.kW, r.nsplit) * g.Cin * 4);
   r.conv_scratch = (float*)c.take(fprop_scratch_bytes(g, dtype));
   r.wgrad_scratch = c.take(wgrad_scratch_bytes(g, dtype));
   r.bytes = c.off;
@@ -960,9 +959,8 @@ convbn_status convbn_tconv_tune_bwd(const convbn_desc* desc, const void* x, cons
   if (!params) return CONVBN_OK;
   // dw'[ci][tap][co] = sum X[ci] dZ[co]: the associated convolution's weight gradient with dZ as its input
   LAUNCH(run_wgrad(g, dt, dz, x, w.dwf_part, nullptr, w.wgrad_scratch, st));
-  LAUNCH(launch_colsum(tconv_out_rows(g), dt, dz, w.r_part, st));       // r = sum dZ
-  LAUNCH(launch_fold_back_t(dt, g.Cout, g.Cin, taps, w.dwf_part, w.nsplit, w.r_part, w.nrpart, W, b, gamma, mean,
-                            var, g.eps, w.dot_part, dW, db, dgamma, dbeta, st));
+  LAUNCH(launch_fold_back_t(dt, g.Cout, g.Cin, taps, w.dwf_part, w.nsplit, tconv_out_rows(g), dz, w.r_part, W, b, gamma,
+                            mean, var, g.eps, w.dot_part, dW, db, dgamma, dbeta, st));
   return CONVBN_OK;
 }
 
@@ -1022,8 +1020,8 @@ convbn_status convbn_tconv_eval_bwd(const convbn_desc* desc, const void* x, cons
   if (dx) LAUNCH(run_fprop(g, dt, w.dy, W, nullptr, dx, w.conv_scratch, st));            // dX = w (*) dY
   if (!params) return CONVBN_OK;
   LAUNCH(run_wgrad(g, dt, w.dy, x, w.dwf_part, nullptr, w.wgrad_scratch, st));           // dW = sum X dY
-  LAUNCH(launch_fold_back_t(dt, g.Cout, g.Cin, g.kH * g.kW, w.dwf_part, w.nsplit, nullptr, 0, W, nullptr, nullptr,
-                            nullptr, nullptr, g.eps, nullptr, dW, nullptr, nullptr, nullptr, st));
+  LAUNCH(launch_fold_back_t(dt, g.Cout, g.Cin, g.kH * g.kW, w.dwf_part, w.nsplit, g, nullptr, nullptr, W, nullptr,
+                            nullptr, nullptr, nullptr, g.eps, nullptr, dW, nullptr, nullptr, nullptr, st));
   return CONVBN_OK;
 }
 

@@ -250,12 +250,13 @@ hipError_t launch_fold_back_group(const void* items_dev, int n, int grid_blocks,
 hipError_t launch_fold_t(int dtype, int Ci, int Co, int taps, const void* W, const float* b, const float* gamma,
                          const float* beta, const float* mean, const float* var, float eps, int tap_major,
                          void* w_same, void* w_swap, float* bfold, hipStream_t st);
-int fold_back_t_chunks(int Ci, int taps);   // rows of dot_part ([chunks][Co] fp32 scratch)
-// gamma == NULL (Eval path): dW = sum of the partial copies only; dot_part and the other outputs are not touched.
+int fold_back_t_chunks(int Ci, int Co, int taps, int nsplit);   // rows of dot_part ([chunks][Co] fp32 scratch)
+// dz [zrows.M][Co] gives r = sum dZ, through r_part ([colsum_parts(zrows)][Co] fp32 scratch).
+// gamma == NULL (Eval path): dW = sum of the partial copies only; dz, the scratch and the other outputs are not touched.
 hipError_t launch_fold_back_t(int dtype, int Ci, int Co, int taps, const float* dwf_part, int nsplit,
-                              const float* r_part, int nrpart, const void* W, const float* b, const float* gamma,
-                              const float* mean, const float* var, float eps, float* dot_part, void* dW, float* db,
-                              float* dgamma, float* dbeta, hipStream_t st);
+                              const Geom& zrows, const void* dz, float* r_part, const void* W, const float* b,
+                              const float* gamma, const float* mean, const float* var, float eps, float* dot_part, void* dW,
+                              float* db, float* dgamma, float* dbeta, hipStream_t st);
 int colsum_parts(const Geom& g);
 hipError_t launch_colsum(const Geom& g, int dtype, const void* dz, float* r_part, hipStream_t st);
 hipError_t launch_bn_affine_fwd(const Geom& g, int dtype, const void* y, const float* gamma,

@@ -346,31 +346,11 @@ __global__ __launch_bounds__(256) void colsum_kernel(const T* __restrict__ dz, i
   }
 }
 
-// bf16, Cout % 8 == 0: a thread reads 8 channels (16 bytes) of a row; (Cout/8) threads cover a row,
-// the remaining factor of the block strides over rows.  Requires Cout/8 <= 256.
 __global__ __launch_bounds__(256) void colsum_bf16x8_kernel(const uint4* __restrict__ dz, int M, int Cout,
                                                             int rows_per_block, float* __restrict__ part) {
   __shared__ float red[256][9];
-  const int c8 = Cout >> 3;
-  const int lanes = 256 / c8;
-  const int tc = threadIdx.x % c8, tr = threadIdx.x / c8;
   const int m0 = blockIdx.x * rows_per_block;
-  const int m1 = min(M, m0 + rows_per_block);
-  float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (tr < lanes)
-    for (int m = m0 + tr; m < m1; m += lanes) {
-      const uint4 v = dz[(size_t)m * c8 + tc];
-      a[0] += bf16_lo(v.x); a[1] += bf16_hi(v.x); a[2] += bf16_lo(v.y); a[3] += bf16_hi(v.y);
-      a[4] += bf16_lo(v.z); a[5] += bf16_hi(v.z); a[6] += bf16_lo(v.w); a[7] += bf16_hi(v.w);
-    }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) red[threadIdx.x][e] = a[e];
-  __syncthreads();
-  for (int c = threadIdx.x; c < Cout; c += 256) {
-    float acc = 0.f;
-    for (int l = 0; l < lanes; ++l) acc += red[l * c8 + (c >> 3)][c & 7];
-    part[(size_t)blockIdx.x * Cout + c] = acc;
-  }
+  colsum_slice_bf16x8(dz, m0, min(M, m0 + rows_per_block), Cout, threadIdx.x, red, part + (size_t)blockIdx.x * Cout);
 }
 
 template <typename T>

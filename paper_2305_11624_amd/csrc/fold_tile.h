@@ -1,5 +1,5 @@
-// The fold of a bf16 weight, one 64 x 64 tile at a time: shared by the fold kernels and by forward convolutions whose
-// launch folds on the side.
+// Pieces of the parameter-side kernels that run inside several launches: the fold of a bf16 weight, one 64 x 64 tile at a
+// time (the fold kernels, and forward convolutions whose launch folds on the side), and a slice of dZ's column sums.
 #pragma once
 #include "common.h"
 
@@ -92,6 +92,36 @@ __device__ __forceinline__ void fold_side(const BnEpilogue& bn, const bf16_t* wg
   const int t = wg * 2 + half;
   fold_tile_bf16x8(a, t % tk, t / tk, (int)threadIdx.x & 255,
                    reinterpret_cast<unsigned short (*)[72]>(smem + half * FOLD_TILE_BYTES));
+}
+
+// Column sums of rows [m0, m1) of a bf16 matrix [..][Cout], Cout % 8 == 0 and at most 2048, by 256 threads: a thread reads 8
+// channels (16 bytes) of a row, Cout / 8 threads cover one, the others stride over rows.  Eight rows of a thread are asked for
+// at once: one at a time, a block of 98 rows of 256 channels was 13 trips to memory in a row.
+__device__ __forceinline__ void colsum_slice_bf16x8(const uint4* __restrict__ dz, int m0, int m1, int Cout, int tid,
+                                                    float (*red)[9], float* __restrict__ out) {
+  const int c8 = Cout >> 3, lanes = 256 / c8;
+  const int tc = tid % c8, tr = tid / c8;
+  float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (tr < lanes)
+    for (int m = m0 + tr; m < m1; m += 8 * lanes) {
+      uint4 v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = dz[(size_t)min(m + j * lanes, m1 - 1) * c8 + tc];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if (m + j * lanes >= m1) v[j] = make_uint4(0u, 0u, 0u, 0u);
+        a[0] += bf16_lo(v[j].x); a[1] += bf16_hi(v[j].x); a[2] += bf16_lo(v[j].y); a[3] += bf16_hi(v[j].y);
+        a[4] += bf16_lo(v[j].z); a[5] += bf16_hi(v[j].z); a[6] += bf16_lo(v[j].w); a[7] += bf16_hi(v[j].w);
+      }
+    }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[tid][e] = a[e];
+  __syncthreads();
+  for (int c = tid; c < Cout; c += 256) {
+    float acc = 0.f;
+    for (int l = 0; l < lanes; ++l) acc += red[l * c8 + (c >> 3)][c & 7];
+    out[c] = acc;
+  }
 }
 
 }  // namespace convbn

@@ -67,6 +67,26 @@ def test_bf16_shapes(shape):
     compare(_run(inp, mode="eval"), ref, "bf16", keys=EVAL_KEYS, tag=shape.name + "/eval")
 
 
+# the ways the fold-back is split: many partial copies shared by 16 threads a column (Co / 4 above 16, and a divisor of no
+# power of two below), by 4 threads (a large weight), 32 rows a workgroup with a remainder, and fp32 copies
+FOLD_BACK = [
+    BlockShape("t_fb_16", 2, 64, 24, 24, 72, 4, 2, 1, "bf16", 121),
+    BlockShape("t_fb_16_narrow", 3, 64, 29, 31, 40, 4, 2, 1, "bf16", 122),
+    BlockShape("t_fb_16_tiny", 4, 16, 30, 30, 8, 2, 2, 0, "bf16", 123),
+    BlockShape("t_fb_64", 8, 128, 28, 28, 72, 4, 2, 1, "bf16", 124),
+    BlockShape("t_fb_rows32", 1, 920, 3, 3, 24, 3, 1, 1, "bf16", 125),
+    BlockShape("t_fb_f32", 2, 40, 17, 19, 20, 2, 2, 0, "f32", 126),
+]
+
+
+@pytest.mark.parametrize("shape", FOLD_BACK, ids=lambda s: s.name)
+def test_fold_back_splits(shape):
+    inp = synth.make_tconv_inputs(shape, bias=True)
+    ref = oracle_tconv_block(inp)
+    compare(_run(inp), ref, shape.dtype, keys=KEYS, tag=shape.name)
+    compare(_run(inp, mode="eval"), ref, shape.dtype, keys=EVAL_KEYS, tag=shape.name + "/eval")
+
+
 def test_refold_and_input_gradient_only():
     shape = BlockShape("t_refold", 2, 64, 10, 10, 32, 2, 2, 0, "bf16", 81)
     inp = synth.make_tconv_inputs(shape)
