@@ -1,4 +1,4 @@
-// Forward convolution of a network's first layer (Sec. 3.1's Y = w (*) X + b with at most four input
+// Convolutions of a network's first layer (Sec. 3.1's Y = w (*) X + b with at most four input
 // channels, e.g. the 7x7 / stride-2 stem of a ResNet on RGB images), bf16 MFMA with fp32 accumulation.
 //
 // With 3 input channels the reduction index (tap, channel) has no 16-byte runs for the generic kernels to
@@ -8,9 +8,10 @@
 // window columns x four channels -- are then 16 contiguous bytes of the input row, for every output pixel.
 // So no im2col is ever materialised: the operand fragments are read straight from the raw input patch in
 // LDS (output pixel wo, window columns j..j+1 -> patch bytes (wo sw + j) 8 ..), consecutive lanes 8 sw bytes
-// apart.  The weights (Cout x kH x 8 x 4, zero-padded) stay resident in LDS; a workgroup is persistent and
-// walks tiles of 128 consecutive pixels of one output row: patch in (kH rows x (127 sw + 8) pixels), kH x 2
-// MFMA k-steps, staged 16-byte stores out.
+// apart.  The weights (Cout x kH x 8 x 4, zero-padded, packed by each workgroup for itself) stay resident in LDS, for 7-row
+// windows on RGB images in registers; a workgroup is persistent and walks a run of tiles of 128 consecutive pixels of one output
+// row: patch in (kH rows x (127 sw + 8) pixels), kH x 2 MFMA k-steps, s, b' and a ReLU in the epilogue, 16-byte stores out (through
+// LDS; 7-row windows straight from the accumulators, with the next patch in a second buffer).
 #include "common.h"
 
 namespace convbn {
