@@ -525,17 +525,35 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
                                                               bf16_t* __restrict__ out) {
   const size_t nvec = MR >> 3;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < nvec; i += (size_t)gridDim.x * 256) {
-    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int sp = 0; sp < ksplit; ++sp) {
-      const float4 u = *reinterpret_cast<const float4*>(part + sp * MR + i * 8);
-      const float4 v = *reinterpret_cast<const float4*>(part + sp * MR + i * 8 + 4);
-      a[0] += u.x; a[1] += u.y; a[2] += u.z; a[3] += u.w;
-      a[4] += v.x; a[5] += v.y; a[6] += v.z; a[7] += v.w;
-    }
+    // the copies in order, four asked for at once: one at a time, each was a trip to memory (512 -> 512, 3x3 at 7 x 7, 3 images, two
+    // such launches a pass: 51.1 -> 49.1 us)
+    const float* src = part + i * 8;
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, bv[8];
     if (bias) {
       const int r = (int)((i * 8) % R);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] += bias[r + e];
+      for (int e = 0; e < 8; ++e) bv[e] = bias[r + e];
+    }
+    auto add = [&](const float4& u, const float4& v) {
+      a[0] += u.x; a[1] += u.y; a[2] += u.z; a[3] += u.w;
+      a[4] += v.x; a[5] += v.y; a[6] += v.z; a[7] += v.w;
+    };
+    int sp = 0;
+    for (; sp + 3 < ksplit; sp += 4) {
+      float4 u[4], v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        u[j] = *reinterpret_cast<const float4*>(src + (sp + j) * MR);
+        v[j] = *reinterpret_cast<const float4*>(src + (sp + j) * MR + 4);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) add(u[j], v[j]);
+    }
+    for (; sp < ksplit; ++sp)
+      add(*reinterpret_cast<const float4*>(src + sp * MR), *reinterpret_cast<const float4*>(src + sp * MR + 4));
+    if (bias) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] += bv[e];
     }
     *reinterpret_cast<uint4*>(out + i * 8) = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]),
                                                         pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
