@@ -56,6 +56,18 @@ def test_deep_layer_that_keeps_nothing(kw):
     compare(res, ref, "bf16", tag="deep_refold")
 
 
+@pytest.mark.parametrize("cin", [320, 384, 448, 512, 576])
+def test_split_product(cin):
+    """Few pixels and more than 40 chunks of 64 reduced channels: the product is split over them and its fp32 copies are added
+    four at a time, with every remainder (5 to 9 copies where each chunk is one)."""
+    from paper_2305_11624_amd.runner import BlockRun
+    shape = BlockShape("split_%d" % cin, 3, cin, 7, 5, cin, 3, 1, 1, "bf16", 70 + cin // 64)
+    inp = synth.make_inputs(shape, bias=True)
+    run = BlockRun(inp, mode="tune", poison=True)
+    run.step()
+    compare(run.results(), oracle_block(inp), "bf16", tag=shape.name)
+
+
 def test_deep_layer_replayed_from_a_graph():
     """A captured step replays with the same arguments, the launch tag of the workgroup exchange among them: each
     replay must find the slots of the previous one cleared.  Three replays over changing inputs, eager work and
