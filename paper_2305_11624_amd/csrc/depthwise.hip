@@ -174,7 +174,7 @@ __device__ __forceinline__ int dw_slice() {
   return gridDim.x == 1 && n % 8 == 0 ? (b & 7) * (n >> 3) + (b >> 3) : b;
 }
 
-// The filter of a thread's 4 channels (s already in it) and their b'; a forward launch leaves w' on the side.
+// The filter of a thread's 4 channels (s already in it) and their b' (forward, where also w' is left on the side).
 __device__ __forceinline__ void dw_filter(const Dw3Params& p, int c, float (&t)[9][4], float (&bb)[4]) {
   // (every load is issued before the first use; a vector that is not there is read from the filter, which is larger)
   const float* const any = reinterpret_cast<const float*>(p.W);
@@ -209,7 +209,8 @@ __device__ __forceinline__ void dw_filter(const Dw3Params& p, int c, float (&t)[
 #pragma unroll
       for (int q = 0; q < 9; ++q) {
         const int k = e * 9 + q;
-        w[q][e] = ((k & 1) ? bf16_hi(raw[k >> 1]) : bf16_lo(raw[k >> 1])) * s[e];
+        const float v = ((k & 1) ? bf16_hi(raw[k >> 1]) : bf16_lo(raw[k >> 1])) * s[e];
+        w[q][e] = p.bias ? v : (float)(bf16_t)v;   // backward folds the w' that forward would have kept, rounded as that is
       }
   }
 #pragma unroll

@@ -56,6 +56,18 @@ def test_refold_input_gradient_only_and_wide_scale():
     assert res["dW"] is None and res["dgamma"] is None
 
 
+@pytest.mark.parametrize("s,p", [(1, 1), (1, 0), (1, 2), (2, 1), (2, 0)])
+def test_refolding_reproduces_the_kept_filter(s, p):
+    """The filter that backward folds again is the one forward keeps (rounded to bf16 once): dX is the same bit for bit, with the
+    weight gradient beside it and on its own."""
+    shape = BlockShape("d_refold", 3, 40, 17, 14, 40, 3, s, p, "bf16", 11 + 3 * s + p)
+    inp = synth.make_dw_inputs(shape, wide_scale=True)
+    kept = _run(inp)["dX"]
+    assert torch.equal(kept, _run(inp, keep_folded=False)["dX"])
+    assert torch.equal(kept, _run(inp, keep_folded=False, params=False)["dX"])
+    assert torch.equal(kept, _run(inp, params=False)["dX"])
+
+
 # the sweep of the 3x3 kernels: every padding it takes, odd and even sides, strips with a remainder, one channel group and
 # several workgroups of channels, fewer positions than threads, strides
 SWEEP = [(n, c, h, w, s, p) for n, c, h, w, s, p in [

@@ -80,6 +80,16 @@ def test_row_sweep(n, c, h, w, g, s, p):
     compare(_run(inp, keep_folded=False), ref, "bf16", keys=KEYS[:-1], tag="refold")
 
 
+@pytest.mark.parametrize("s,p", [(1, 1), (2, 1), (1, 3)])
+def test_refolding_reproduces_the_kept_weight(s, p):
+    """The w' that backward folds again is the one forward keeps: dX is the same bit for bit."""
+    shape = BlockShape("g_refold", 2, 64, 13, 18, 64, 3, s, p, "bf16", 17 + 3 * s + p)
+    inp = synth.make_grouped_inputs(shape, 8, wide_scale=True)
+    kept = _run(inp)["dX"]
+    assert torch.equal(kept, _run(inp, keep_folded=False)["dX"])
+    assert torch.equal(kept, _run(inp, keep_folded=False, params=False)["dX"])
+
+
 def test_one_group_matches_the_dense_block():
     from paper_2305_11624_amd.runner import BlockRun
     shape = BlockShape("g_dense", 2, 32, 10, 10, 48, 3, 1, 1, "bf16", 127)
