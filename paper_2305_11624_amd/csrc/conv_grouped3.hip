@@ -375,6 +375,9 @@ struct G3Wg {
 
 // dw'[o][i][j][q] = sum over the pixels of dZ[pixel][o] X[pixel (i, j)][group(o) cg + q], r[o] = sum dZ.  A step brings a dZ row
 // and the S x rows that end its windows; NT: pairs of 16-channel tiles (2: groups within a tile; 4: groups of 32).
+// Zeros stand for what is outside, and an infinity times zero is no zero: products of rows that have no partner in the strip are
+// skipped, and x pixels beside the segment's last windows are cleared where they would meet the zeros behind its dZ.  An
+// infinite x then stays with the taps that touch it; an infinite dZ also reaches the taps whose column is in the padding.
 template <int S, int NT>
 __device__ __forceinline__ void g3_wgrad_body(const G3Params& p, const int block, unsigned char* smem) {
   using L = G3Wg<S>;
@@ -402,21 +405,28 @@ __device__ __forceinline__ void g3_wgrad_body(const G3Params& p, const int block
 
   for (int it = wg * 4 + wave; it < p.items; it += p.bpc * 4) {
     const G3Item im = g3_item(p, it);
-    const int rows = min(p.Ho - im.h0, p.R);
+    const int rows = min(p.Ho - im.h0, p.R), cols = min(p.Wo - im.c0, p.segw);
     unsigned xcol[L::XPX / 16], zcol[WPX / 16];
 #pragma unroll
     for (int k = 0; k < L::XPX / 16; ++k) {
       const int c = k * 16 + cpix, w = im.c0 * S + c - p.pb;
-      xcol[k] = c < (p.segw - 1) * S + 3 && (unsigned)w < (unsigned)p.Wa ? (unsigned)w * px + cgr : INV;
+      xcol[k] = c < (cols - 1) * S + 3 && (unsigned)w < (unsigned)p.Wa ? (unsigned)w * px + cgr : INV;
     }
 #pragma unroll
     for (int k = 0; k < WPX / 16; ++k) {
       const int c = k * 16 + cpix;
-      zcol[k] = c < p.segw && im.c0 + c < p.Wo ? (unsigned)(im.c0 + c) * px + cgr : INV;
+      zcol[k] = c < cols ? (unsigned)(im.c0 + c) * px + cgr : INV;
+    }
+    // the lane's pixels (two a register) that have a dZ: what window columns below 3 - S read behind them is real x
+    unsigned own[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const int left = cols - ((lane >> 4) * 8 + 2 * d);
+      own[d] = left >= 2 ? 0xffffffffu : left == 1 ? 0xffffu : 0u;
     }
     // step q: dZ row h0 + q and the x rows S (h0 + q) + i - pa, stride 1: i = 0; stride 2: i = -1 and 0
     const int nq = S == 1 ? rows + 2 : rows + 1;
-    int hx = im.h0 * S - p.pa - (S - 1), qf = 0;
+    int hx = im.h0 * S - p.pa - (S - 1), hq = hx, qf = 0;
     const int xend = min(p.Ha, hx + nq * S);
     unsigned xoff = ((unsigned)im.n * p.Ha + (unsigned)hx) * xrow, zoff = ((unsigned)im.n * p.Ho + (unsigned)im.h0) * zrow;
     unsigned fill = 0, read = 0;   // byte offsets of the stages that are filled and read next
@@ -461,7 +471,16 @@ __device__ __forceinline__ void g3_wgrad_body(const G3Params& p, const int block
       bf16x8 xf[S][3][2];
       g3_read_z(zread + read, zf[0]);
 #pragma unroll
-      for (int i = 0; i < S; ++i) g3_read_x<S>(xread + read + i * L::XROW, xf[i]);
+      for (int i = 0; i < S; ++i) {
+        g3_read_x<S>(xread + read + i * L::XROW, xf[i]);
+#pragma unroll
+        for (int j = 0; j < 3 - S; ++j)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const uint4 v = __builtin_bit_cast(uint4, xf[i][j][k]);
+            xf[i][j][k] = __builtin_bit_cast(bf16x8, make_uint4(v.x & own[0], v.y & own[1], v.z & own[2], v.w & own[3]));
+          }
+      }
       read = next(read);
       fetch();   // (into the stage that the step before read: its multiplies have its operands)
 #pragma unroll
@@ -475,14 +494,11 @@ __device__ __forceinline__ void g3_wgrad_body(const G3Params& p, const int block
           for (int k = 0; k < NT; ++k)
             acc[tap_row * 3 + j][k] = mfma(x[j][NT == 2 ? k : k >> 1], z[NT == 2 ? k : k & 1], acc[tap_row * 3 + j][k]);
       };
-      prods(0, xf[S - 1], zf[0]);
-      if constexpr (S == 1) {
-        prods(1, xf[0], zf[1]);
-        prods(2, xf[0], zf[2]);
-      } else {
-        prods(1, xf[0], zf[1]);
-        prods(2, xf[1], zf[1]);
-      }
+      const bool x0 = (unsigned)hq < (unsigned)p.Ha, x1 = (unsigned)(hq + S - 1) < (unsigned)p.Ha;   // the step's first, last x row
+      hq += S;
+      if (x1 && q < rows) prods(0, xf[S - 1], zf[0]);
+      if (x0 && q >= 1 && q <= rows) prods(1, xf[0], zf[1]);
+      if (x1 && (S == 1 ? q >= 2 : q >= 1)) prods(2, xf[S - 1], zf[S == 1 ? 2 : 1]);
     }
     g3_wait_vm<0>();   // the ring is refilled by the next strip
   }

@@ -90,6 +90,40 @@ def test_refolding_reproduces_the_kept_weight(s, p):
     assert torch.equal(kept, _run(inp, keep_folded=False, params=False)["dX"])
 
 
+@pytest.mark.parametrize("where", ["x", "dy"])
+@pytest.mark.parametrize("n,c,h,w,g,s,p", [(2, 128, 13, 35, 32, 1, 1), (2, 128, 13, 35, 32, 2, 1), (40, 64, 29, 30, 8, 1, 1),
+                                           (2, 128, 14, 70, 4, 2, 1), (40, 64, 30, 36, 8, 2, 0), (2, 96, 9, 40, 3, 1, 2)])
+def test_infinity_stays_with_the_taps_that_touch_it(n, c, h, w, g, s, p, where):
+    """One infinite value per group, at image, strip and segment edges: dW is infinite at the taps whose products contain it and
+    finite at the others.  (dZ not in the columns whose windows overhang the image: those products have a zero of the padding.)"""
+    shape = BlockShape("g_inf", n, c, h, w, c, 3, s, p, "bf16", 3 * c + h)
+    inp = synth.make_grouped_inputs(shape, g)
+    inp = dict(inp, x=torch.where(inp["x"] == 0, torch.ones_like(inp["x"]), inp["x"]),
+               dy=torch.where(inp["dy"] == 0, torch.ones_like(inp["dy"]), inp["dy"]))
+    t = inp[where].clone()
+    ho, wo = t.shape[2:]
+    inner = 0 if where == "x" else -(-p // s)
+    rows = sorted({0, 1, 2, ho // 2, ho // 2 + 1, ho - 3, ho - 2, ho - 1})
+    cols = [k for k in sorted({inner, 15, 16, 17, 18, 19, wo // 2, wo - 1 - inner}) if inner <= k < wo - inner]
+    cg = c // g
+    hit = torch.zeros(c, cg, 3, 3, dtype=torch.bool)
+    for k in range(g):
+        y, x = rows[(5 * k) % len(rows)], cols[(3 * k + k // len(cols)) % len(cols)]
+        ch = k * cg + k % cg
+        t[k % n, ch, y, x] = float("inf")
+        for i in range(3):
+            for j in range(3):
+                if where == "x":
+                    oh, ow = y + p - i, x + p - j
+                    if oh % s == 0 and ow % s == 0 and 0 <= oh // s < shape.Hout and 0 <= ow // s < shape.Wout:
+                        hit[k * cg:(k + 1) * cg, k % cg, i, j] = True
+                elif 0 <= y * s + i - p < h and 0 <= x * s + j - p < w:
+                    hit[ch, :, i, j] = True
+    for kw in (dict(), dict(need_dx=False)):
+        dW = _run(dict(inp, **{where: t}), **kw)["dW"]
+        assert torch.equal(torch.isinf(dW), hit) and torch.equal(torch.isfinite(dW), ~hit), kw
+
+
 def test_one_group_matches_the_dense_block():
     from paper_2305_11624_amd.runner import BlockRun
     shape = BlockShape("g_dense", 2, 32, 10, 10, 48, 3, 1, 1, "bf16", 127)
