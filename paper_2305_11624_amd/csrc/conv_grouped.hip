@@ -996,6 +996,7 @@ int direct_splits(const Geom& g, int cg) {
 }  // namespace
 
 bool g_fprop_scaled_supported(const Geom& g, int groups, int dtype) {
+  if (g3_supported(g, groups, dtype)) return true;
   GcParams gp;
   return gc_fprop_plan(g, groups, dtype, &gp).ok;
 }

@@ -90,6 +90,18 @@ def test_refolding_reproduces_the_kept_weight(s, p):
     assert torch.equal(kept, _run(inp, keep_folded=False, params=False)["dX"])
 
 
+def test_rounding_does_not_depend_on_the_width():
+    """Z of a wide image (704 output columns, for which the shared-tile kernel has no plan) and of its left part are the same
+    bit for bit where no window sees the cut."""
+    wide, narrow = (BlockShape("g_wide", 1, 32, 4, w, 32, 3, 2, 1, "bf16", 41) for w in (1408, 1200))
+    inp = synth.make_grouped_inputs(wide, 4)
+    cut = dict(inp, shape=narrow, x=inp["x"][..., :1200].contiguous(), dy=inp["dy"][..., :600].contiguous())
+    a, b = _run(inp), _run(cut)
+    assert torch.equal(a["Z"][..., :599], b["Z"][..., :599])
+    assert torch.equal(a["Wf"], b["Wf"])
+    compare(a, oracle_grouped_block(inp), "bf16", keys=KEYS, tag="wide")
+
+
 @pytest.mark.parametrize("where", ["x", "dy"])
 @pytest.mark.parametrize("n,c,h,w,g,s,p", [(2, 128, 13, 35, 32, 1, 1), (2, 128, 13, 35, 32, 2, 1), (40, 64, 29, 30, 8, 1, 1),
                                            (2, 128, 14, 70, 4, 2, 1), (40, 64, 30, 36, 8, 2, 0), (2, 96, 9, 40, 3, 1, 2)])
