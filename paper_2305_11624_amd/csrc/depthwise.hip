@@ -141,11 +141,11 @@ struct Dw3Params {
   const bf16_t* y;       // weight gradient: x
   bf16_t* out;           // z or dx
   const bf16_t* W;       // [C][9], or the folded filter [9][C] (tap_major)
-  const float *b, *gamma, *beta, *mean, *var;   // gamma == null: s = 1; b' is added where `bias`
+  const float *b, *gamma, *beta, *mean, *var;   // gamma == null: s = 1; b: forward
   bf16_t* wf_out;        // forward: where the folded filter [9][C] is left, or null
   float* part;           // weight gradient: [C / 8][slices_all][10][8], row 9 the channel sums of dZ
   float eps;
-  int tap_major, flip, bias;
+  int tap_major;
   int N, C, Ha, Wa, Ho, Wo;     // images; a's and out's (and y's) planes
   int pa, pb;                   // a's row for output row o and window row i: o S + i - pa
   int u0, v0;                   // stride 2 backward: the first dZ row and column a thread owns
@@ -174,15 +174,17 @@ __device__ __forceinline__ int dw_slice() {
   return gridDim.x == 1 && n % 8 == 0 ? (b & 7) * (n >> 3) + (b >> 3) : b;
 }
 
-// The filter of a thread's 4 channels (s already in it) and their b' (forward, where also w' is left on the side).
+// The filter of a thread's 4 channels (s already in it) and, in forward (FWD), their b'.  Backward folds the w' that forward
+// would have kept, rounded as that is.
+template <bool FWD, bool ROT>
 __device__ __forceinline__ void dw_filter(const Dw3Params& p, int c, float (&t)[9][4], float (&bb)[4]) {
   // (every load is issued before the first use; a vector that is not there is read from the filter, which is larger)
   const float* const any = reinterpret_cast<const float*>(p.W);
   const float4 ga = *reinterpret_cast<const float4*>((p.gamma ? p.gamma : any) + c);
   const float4 va = *reinterpret_cast<const float4*>((p.gamma ? p.var : any) + c);
-  const float4 me = *reinterpret_cast<const float4*>((p.bias && p.gamma ? p.mean : any) + c);
-  const float4 be = *reinterpret_cast<const float4*>((p.bias && p.gamma ? p.beta : any) + c);
-  const float4 bi = *reinterpret_cast<const float4*>((p.bias && p.b ? p.b : any) + c);
+  const float4 me = *reinterpret_cast<const float4*>((FWD && p.gamma ? p.mean : any) + c);
+  const float4 be = *reinterpret_cast<const float4*>((FWD && p.gamma ? p.beta : any) + c);
+  const float4 bi = *reinterpret_cast<const float4*>((FWD && p.b ? p.b : any) + c);
   const float gv[4] = {ga.x, ga.y, ga.z, ga.w}, vv[4] = {va.x, va.y, va.z, va.w}, mv[4] = {me.x, me.y, me.z, me.w};
   const float ev[4] = {be.x, be.y, be.z, be.w}, iv[4] = {bi.x, bi.y, bi.z, bi.w};
   float s[4];
@@ -190,10 +192,10 @@ __device__ __forceinline__ void dw_filter(const Dw3Params& p, int c, float (&t)[
   for (int e = 0; e < 4; ++e) {
     s[e] = p.gamma ? gv[e] / sqrtf(vv[e] + p.eps) : 1.f;
     const float b0 = p.b ? iv[e] : 0.f;
-    bb[e] = !p.bias ? 0.f : p.gamma ? (b0 - mv[e]) * s[e] + ev[e] : b0;
+    bb[e] = !FWD ? 0.f : p.gamma ? (b0 - mv[e]) * s[e] + ev[e] : b0;
   }
   float w[9][4];
-  if (p.tap_major) {
+  if (!FWD && p.tap_major) {
 #pragma unroll
     for (int q = 0; q < 9; ++q) unpack4(*reinterpret_cast<const u32x2*>(p.W + (size_t)q * p.C + c), w[q]);
   } else {
@@ -210,13 +212,13 @@ __device__ __forceinline__ void dw_filter(const Dw3Params& p, int c, float (&t)[
       for (int q = 0; q < 9; ++q) {
         const int k = e * 9 + q;
         const float v = ((k & 1) ? bf16_hi(raw[k >> 1]) : bf16_lo(raw[k >> 1])) * s[e];
-        w[q][e] = p.bias ? v : (float)(bf16_t)v;   // backward folds the w' that forward would have kept, rounded as that is
+        w[q][e] = FWD ? v : (float)(bf16_t)v;
       }
   }
 #pragma unroll
   for (int q = 0; q < 9; ++q)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) t[q][e] = p.flip ? w[8 - q][e] : w[q][e];
+    for (int e = 0; e < 4; ++e) t[q][e] = ROT ? w[8 - q][e] : w[q][e];
 }
 // w'[tap][c] = bf16(s w), a value per thread of the launch's first threads
 __device__ __forceinline__ void dw_emit_folded(const Dw3Params& p) {
@@ -254,15 +256,15 @@ __device__ __forceinline__ void dw_slice_sums(const Dw3Params& p, const float (&
   }
 }
 
-// Stride 1.  CONV: out[n][h][w] = b' + sum_{i,j} T[i][j] a[n][h + i - pa][w + j - pb], T the filter (flip: rotated).
-// WG (a = dZ, flip): dw'[8 - (i, j)] += y[n][h][w] a[n][h + i - pa][w + j - pb] over the owned (h, w), and the sums of a.
+// Stride 1.  CONV: out[n][h][w] = b' + sum_{i,j} T[i][j] a[n][h + i - pa][w + j - pb], T the filter (backward: rotated).
+// WG (a = dZ): dw'[8 - (i, j)] += y[n][h][w] a[n][h + i - pa][w + j - pb] over the owned (h, w), and the sums of a.
 // Products with a position outside an image are skipped, not multiplied by zero: an infinite x or dZ at the border does
 // not reach the taps that do not touch it.
 // PAD1: pa = pb = 1, the sizes of a and out are the same.
-template <bool CONV, bool WG, bool PAD1>
+template <bool FWD, bool CONV, bool WG, bool PAD1>
 __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p) {
   __shared__ float red[WG ? 20 * DW_BLK : 1];
-  if (CONV && !WG) dw_emit_folded(p);
+  if (FWD) dw_emit_folded(p);
   const int pad_h = PAD1 ? 1 : p.pa, pad_w = PAD1 ? 1 : p.pb;
   const int L = DW_BLK / p.cq;
   const int tx = threadIdx.x % p.cq, lane = threadIdx.x / p.cq;
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
       for (int e = 0; e < 4; ++e) wacc[q][e] = 0.f;
   }
   const int slice = dw_slice(), it1 = min(p.items, (slice + 1) * p.per_slice);
-  if (CONV && !WG && live) dw_filter(p, c, t, bb);
+  if (CONV && !WG && live) dw_filter<FWD, !FWD>(p, c, t, bb);
   bool first = true;
   if (live)
     for (int it = slice * p.per_slice + lane; it < it1; it += L) {
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
       };
       fetch(0, 0);
       fetch(1, 1);
-      if (CONV && WG && first) dw_filter(p, c, t, bb);   // (behind the first rows' requests)
+      if (CONV && WG && first) dw_filter<FWD, !FWD>(p, c, t, bb);   // (behind the first rows' requests)
       first = false;
       float acc[3][2][4], yv[3][2][4], ye[3][2][4];   // ye: zero where the neighbouring column of a is outside
 #pragma unroll
@@ -426,7 +428,7 @@ __global__ __launch_bounds__(DW_BLK, 4) void dw3_s2_fprop_kernel(Dw3Params p) {
   const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow);
   const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
   float t[9][4], bb[4];
-  dw_filter(p, c, t, bb);
+  dw_filter<true, false>(p, c, t, bb);
   const int slice = dw_slice(), it1 = min(p.items, (slice + 1) * p.per_slice);
   for (int it = slice * p.per_slice + lane; it < it1; it += L) {
     const int pair = it % p.npair;
@@ -506,7 +508,7 @@ __global__ __launch_bounds__(DW_BLK, 2) void dw3_s2_bwd_kernel(Dw3Params p) {
   const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow), ry = dw_rsrc(WG ? p.y : p.a, (size_t)p.N * p.Ho * orow);
   const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
   float t[9][4], bb[4], wacc[10][4];
-  if (CONV && live) dw_filter(p, c, t, bb);
+  if (CONV && live) dw_filter<false, false>(p, c, t, bb);
   if constexpr (WG) {
 #pragma unroll
     for (int q = 0; q < 10; ++q)
@@ -1032,11 +1034,10 @@ hipError_t launch_dw3_fprop(const Geom& g, const void* x, const void* W, const f
     p.a = (const bf16_t*)x + (size_t)n * g.Hin * g.Win * g.Cin;
     p.out = (bf16_t*)z + (size_t)n * g.Hout * g.Wout * g.Cin;
     p.W = (const bf16_t*)W; p.b = b; p.gamma = gamma; p.beta = beta; p.mean = mean; p.var = var;
-    p.bias = 1;
     p.wf_out = n == 0 ? (bf16_t*)w_folded : nullptr;
     p.Ha = g.Hin; p.Wa = g.Win; p.Ho = g.Hout; p.Wo = g.Wout; p.pa = g.ph; p.pb = g.pw;
     const dim3 grid(pl.nxb, pl.slices);
-    if (g.sh == 1) hipLaunchKernelGGL((dw3_s1_kernel<true, false, false>), grid, dim3(DW_BLK), 0, st, p);
+    if (g.sh == 1) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false, false>), grid, dim3(DW_BLK), 0, st, p);
     else hipLaunchKernelGGL(dw3_s2_fprop_kernel, grid, dim3(DW_BLK), 0, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1059,13 +1060,13 @@ hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const vo
     p.Ha = g.Hout; p.Wa = g.Wout; p.Ho = g.Hin; p.Wo = g.Win;
     const dim3 grid(pl.nxb, pl.slices);
     if (g.sh == 1) {
-      p.flip = 1; p.pa = 2 - g.ph; p.pb = 2 - g.pw;
+      p.pa = 2 - g.ph; p.pb = 2 - g.pw;
       const bool pad1 = g.ph == 1 && g.pw == 1;
-      if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<true, false, false>), grid, dim3(DW_BLK), 0, st, p);
-      else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<true, true, true>), grid, dim3(DW_BLK), 0, st, p);
-      else if (dx) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false>), grid, dim3(DW_BLK), 0, st, p);
-      else if (pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true>), grid, dim3(DW_BLK), 0, st, p);
-      else hipLaunchKernelGGL((dw3_s1_kernel<false, true, false>), grid, dim3(DW_BLK), 0, st, p);
+      if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<false, true, false, false>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, true>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, false>), grid, dim3(DW_BLK), 0, st, p);
+      else if (pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, true>), grid, dim3(DW_BLK), 0, st, p);
+      else hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, false>), grid, dim3(DW_BLK), 0, st, p);
     } else {
       p.pa = g.ph; p.pb = g.pw; p.v0 = dw3_first(g.ph); p.u0 = dw3_first(g.pw);
       if (dx && part) hipLaunchKernelGGL((dw3_s2_bwd_kernel<true, true>), grid, dim3(DW_BLK), 0, st, p);
