@@ -157,6 +157,22 @@ __device__ __forceinline__ void store_result(void* p, uint4 v) {
   __builtin_nontemporal_store(t, static_cast<u32x4*>(p));
 }
 
+// Whether a depthwise or grouped block's forward output of that many bytes is stored past the caches.  The next block reads it
+// at once, so what the line depends on is chains of blocks (pointwise, 3x3, pointwise; three or four in a row, forward):
+//   MB   the 3x3 layers                          stored in the caches   past them
+//   0.4  960 channels at 7 x 7, 4 images                         85.2        91.1 us
+//   12.8 512 channels at 14 x 14, 64 images                     169.5       183.1
+//   12.8 256 channels at 28 x 28, 32 images                     137.0       139.7
+//   25.7 256 channels at 28 x 28, 64 images                     239.2       237.2
+//   28.9 144 channels at 56 x 56, 32 images                     211.7       211.2
+//   57.8 144 channels at 56 x 56, 64 images                     362.6       347.9
+inline bool streams_output(size_t bytes) { return bytes >= ((size_t)24 << 20); }
+// Their input gradients leave past the caches at every size.  A single block gains (inputs from memory: 144 channels at 56 x 56,
+// 32 images, 52.8 -> 52.2 us a pass, 256 channels at 28 x 28 45.8 -> 44.5; inputs still in the last-level cache from the last
+// time: 50.2 -> 42.4, 41.7 -> 41.0).  A step over the chains above takes within 1 % of the same up to 13 MB (64 images of 384
+// channels at 14 x 14 311 -> 306, 32 of 1024 at 7 x 7 451.5 -> 455.3) and 0.5 - 2 % more above (57.8 MB: 931 -> 949).
+constexpr bool STREAM_GRAD = true;
+
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Raises a kernel's dynamic-LDS limit once per process -- also when several host threads launch it for the first

@@ -13,10 +13,9 @@
 // What bounds them: these layers move 13-26 MB, a few microseconds of traffic, so a launch lasts as long as its chain of
 // memory round trips.  The kernels that share a tile between the waves (fetch, barrier, LDS, multiply, store, in step, two
 // or three tiles in a row) took 18.6, 18.6 and 17.5 us for the three passes of 256 channels at 28 x 28, 32 images; here forward
-// takes 14, both gradients as one launch 21, and the fold is no launch: 60 -> 36 us a step with inputs from memory (groups of 4,
-// 128 channels at 56 x 56: 85 -> 47; 8 / stride 2 at 56 x 56: 86 -> 62; 32 at 7 x 7: 43 -> 34).  Stores are non-temporal: 37.6 ->
-// 36.3, 56.6 -> 47.0, 70.4 -> 62.2, 33.8 -> 33.8.  A third row ahead, and two chunks per workgroup so that it writes whole
-// lines, were no faster.
+// takes 12.5, both gradients as one launch 19, and the fold is no launch: 58.4 -> 36 us a step (groups of 4, 128 channels at
+// 56 x 56: 85 -> 47; 8 / stride 2 at 56 x 56: 86 -> 62; 32 at 7 x 7: 43 -> 34).  A third row ahead, and two chunks per workgroup so
+// that it writes whole lines, were no faster.  Stores: streams_output and STREAM_GRAD in common.h.
 #include "common.h"
 
 namespace convbn {
@@ -147,18 +146,18 @@ __device__ __forceinline__ void g3_emit_folded(const G3Params& p, int chunk, int
   }
 }
 
-template <bool EPI>
+template <bool EPI, bool STREAM>
 __device__ __forceinline__ void g3_store(__amdgpu_buffer_rsrc_t r, unsigned off, const f32x4 (&acc)[2], const float (&s)[8],
                                          const float (&b)[8]) {
   float v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = EPI ? fmaf(acc[e >> 2][e & 3], s[e], b[e]) : acc[e >> 2][e & 3];
   const u32x4 t = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-  __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)off, 0, 2);
+  __builtin_amdgcn_raw_buffer_store_b128(t, r, (int)off, 0, STREAM ? 2 : 0);
 }
 
 // Stride 1 (GRAD: the input gradient, a = dZ with the rotated window) and the strided forward pass (S = 2).
-template <int S, bool GRAD>
+template <int S, bool GRAD, bool STREAM>
 __device__ __forceinline__ void g3_conv_body(const G3Params& p, const int block) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lb = g3_logical(block, p.nblk);
@@ -231,7 +230,7 @@ __device__ __forceinline__ void g3_conv_body(const G3Params& p, const int block)
               for (int o = 0; o < 2; ++o) acc[(u + 3 - i) % 3][o] = mfma(wf[i * 3 + j][o], cur[0][j], acc[(u + 3 - i) % 3][o]);
           const unsigned r = (unsigned)(q - 2) < (unsigned)rows ? ooff : INV;
           ooff += orow;
-          g3_store<!GRAD>(ro, r + ocol, acc[(u + 1) % 3], s, b);
+          g3_store<!GRAD, STREAM>(ro, r + ocol, acc[(u + 1) % 3], s, b);
         } else {
           if (q == 0) {
 #pragma unroll
@@ -249,7 +248,7 @@ __device__ __forceinline__ void g3_conv_body(const G3Params& p, const int block)
             }
           const unsigned r = (unsigned)(q - 1) < (unsigned)rows ? ooff : INV;
           ooff += orow;
-          g3_store<!GRAD>(ro, r + ocol, acc[u % 2], s, b);
+          g3_store<!GRAD, STREAM>(ro, r + ocol, acc[u % 2], s, b);
         }
       }
     }
@@ -258,9 +257,9 @@ __device__ __forceinline__ void g3_conv_body(const G3Params& p, const int block)
     if (p.bn.w_folded_out && wave == 0) g3_emit_folded(p, chunk, wg, lane, wf);
   }
 }
-template <int S, bool GRAD>
+template <int S, bool GRAD, bool STREAM>
 __global__ __launch_bounds__(256, 2) void g3_conv_kernel(G3Params p) {
-  g3_conv_body<S, GRAD>(p, blockIdx.x);
+  g3_conv_body<S, GRAD, STREAM>(p, blockIdx.x);
 }
 
 // Stride 2, input gradient.  In coordinates that count the padding (hh = h + ph), dZ row v reaches hh = 2v, 2v + 1, 2v + 2: a
@@ -315,7 +314,7 @@ __global__ __launch_bounds__(256, 2) void g3_dgrad_s2_kernel(G3Params p) {
         const int h = 2 * v + 1 + i - p.pa;
         const unsigned r = (unsigned)h < (unsigned)p.Ho ? obase + (unsigned)h * orow : INV;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) g3_store<false>(ro, r + ocol[k], acc[i][k], none, none);
+        for (int k = 0; k < 2; ++k) g3_store<false, STREAM_GRAD>(ro, r + ocol[k], acc[i][k], none, none);
       }
 #pragma unroll
       for (int k = 0; k < 2; ++k) { f0[k] = f1[k]; f1[k] = nxt[k]; nxt[k] = far[k]; }
@@ -549,7 +548,7 @@ template <int NT>
 __global__ __launch_bounds__(256, 2) void g3_pair_kernel(G3Params wg, G3Params dg) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if ((int)blockIdx.x < wg.nblk) g3_wgrad_body<1, NT>(wg, blockIdx.x, smem);
-  else g3_conv_body<1, true>(dg, blockIdx.x - wg.nblk);
+  else g3_conv_body<1, true, STREAM_GRAD>(dg, blockIdx.x - wg.nblk);
 }
 
 // ---- host side
@@ -619,8 +618,11 @@ hipError_t launch_g3_fprop(const Geom& g, int groups, const void* x, const void*
   G3Params p = g3_params(g, groups, pl);
   p.a = (const bf16_t*)x; p.w = (const bf16_t*)W; p.out = (bf16_t*)z; p.bn = bn;
   p.Ha = g.Hin; p.Wa = g.Win; p.Ho = g.Hout; p.Wo = g.Wout; p.pa = g.ph; p.pb = g.pw;
-  if (g.sh == 1) hipLaunchKernelGGL((g3_conv_kernel<1, false>), dim3(p.nblk), dim3(256), 0, st, p);
-  else hipLaunchKernelGGL((g3_conv_kernel<2, false>), dim3(p.nblk), dim3(256), 0, st, p);
+  const bool stream = streams_output((size_t)g.M * g.Cout * 2);
+  if (g.sh == 1 && stream) hipLaunchKernelGGL((g3_conv_kernel<1, false, true>), dim3(p.nblk), dim3(256), 0, st, p);
+  else if (g.sh == 1) hipLaunchKernelGGL((g3_conv_kernel<1, false, false>), dim3(p.nblk), dim3(256), 0, st, p);
+  else if (stream) hipLaunchKernelGGL((g3_conv_kernel<2, false, true>), dim3(p.nblk), dim3(256), 0, st, p);
+  else hipLaunchKernelGGL((g3_conv_kernel<2, false, false>), dim3(p.nblk), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 namespace {
@@ -641,7 +643,7 @@ G3Params g3_wgrad_params(const Geom& g, int groups, const void* x, const void* d
 }  // namespace
 hipError_t launch_g3_dgrad(const Geom& g, int groups, const void* dz, const void* w_crsk, void* dx, hipStream_t st) {
   const G3Params p = g3_dgrad_params(g, groups, dz, w_crsk, dx);
-  if (g.sh == 1) hipLaunchKernelGGL((g3_conv_kernel<1, true>), dim3(p.nblk), dim3(256), 0, st, p);
+  if (g.sh == 1) hipLaunchKernelGGL((g3_conv_kernel<1, true, STREAM_GRAD>), dim3(p.nblk), dim3(256), 0, st, p);
   else hipLaunchKernelGGL(g3_dgrad_s2_kernel, dim3(p.nblk), dim3(256), 0, st, p);
   return hipGetLastError();
 }

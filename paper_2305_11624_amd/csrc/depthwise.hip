@@ -126,10 +126,9 @@ __global__ __launch_bounds__(256) void dw_dgrad_kernel(const T* __restrict__ dz,
 // and weight gradient are one sweep -- dx and dw' both need dZ, and the pixel that owns a dx element owns its x too, so
 // the halo is one tensor's --, and the filter is folded by the threads that use it: a forward pass is one launch, a
 // backward pass two.  Before (a thread per four outputs of one column, all loads of its patch up front, each pass and
-// the fold a launch of its own): 144 channels at 56 x 56, 32 images, 80.8 us a pass; now 41.5
-// (forward 18, backward 21, fold-back 5; 144 MB).  4 x 2 and two steps ahead: three rows ahead, 256 threads a workgroup and 16-byte accesses were no
-// faster.  Stores are non-temporal: lines written once leave the L2 while the kernel runs instead of at its end (47.8 -> 41.5
-// us; non-temporal loads cost the column overlap its L1 hits, 54.6).
+// the fold a launch of its own): 144 channels at 56 x 56, 32 images, 80.7 us a pass; now 38.7 (forward 14.4, backward 20.6,
+// fold-back 4.8; 144 MB).  4 x 2 and two steps ahead: three rows ahead, 256 threads a workgroup and 16-byte accesses were no
+// faster; non-temporal loads cost the column overlap its L1 hits (54.6).  Stores: streams_output and STREAM_GRAD in common.h.
 // Out-of-image loads and stores are offsets beyond the buffer, which read zeros and are dropped.
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 constexpr int DW_BLK = 512;              // threads of a workgroup
@@ -158,11 +157,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t dw_rsrc(const void* p, size_t 
 __device__ __forceinline__ u32x2 dw_load(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
 }
+template <bool STREAM>
 __device__ __forceinline__ void dw_store(__amdgpu_buffer_rsrc_t r, unsigned off, const float (&v)[4]) {
   u32x2 t;
   t.x = pack_bf16x2(v[0], v[1]);
   t.y = pack_bf16x2(v[2], v[3]);
-  __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)off, 0, 2);
+  __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)off, 0, STREAM ? 2 : 0);
 }
 __device__ __forceinline__ void unpack4(u32x2 t, float (&v)[4]) {
   v[0] = bf16_lo(t.x); v[1] = bf16_hi(t.x); v[2] = bf16_lo(t.y); v[3] = bf16_hi(t.y);
@@ -261,7 +261,7 @@ __device__ __forceinline__ void dw_slice_sums(const Dw3Params& p, const float (&
 // Products with a position outside an image are skipped, not multiplied by zero: an infinite x or dZ at the border does
 // not reach the taps that do not touch it.
 // PAD1: pa = pb = 1, the sizes of a and out are the same.
-template <bool FWD, bool CONV, bool WG, bool PAD1>
+template <bool FWD, bool CONV, bool WG, bool PAD1, bool STREAM>
 __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p) {
   __shared__ float red[WG ? 20 * DW_BLK : 1];
   if (FWD) dw_emit_folded(p);
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
             const unsigned r = (unsigned)(q - 2) < (unsigned)rows ? ooff : DW_INV;   // the row that is complete now
             ooff += orow;
 #pragma unroll
-            for (int x = 0; x < 2; ++x) dw_store(ro, r + ocol[x], acc[(u + 1) % 3][x]);
+            for (int x = 0; x < 2; ++x) dw_store<STREAM>(ro, r + ocol[x], acc[(u + 1) % 3][x]);
           }
           if constexpr (WG) {
             if ((unsigned)(h0 + q - pad_h) < (unsigned)p.Ha) {
@@ -418,6 +418,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
 
 // Stride 2, forward: two neighbouring output columns (5 input columns); a step brings the two input rows that complete
 // an output row, the second of which begins the next one.
+template <bool STREAM>
 __global__ __launch_bounds__(DW_BLK, 4) void dw3_s2_fprop_kernel(Dw3Params p) {
   dw_emit_folded(p);
   const int L = DW_BLK / p.cq;
@@ -478,7 +479,7 @@ __global__ __launch_bounds__(DW_BLK, 4) void dw3_s2_fprop_kernel(Dw3Params p) {
       const int o = h0 + q - 1;
       const unsigned r = q >= 1 && o < p.Ho ? obase + (unsigned)o * orow : DW_INV;
 #pragma unroll
-      for (int x = 0; x < 2; ++x) dw_store(ro, r + ocol[x], acc[x]);
+      for (int x = 0; x < 2; ++x) dw_store<STREAM>(ro, r + ocol[x], acc[x]);
 #pragma unroll
       for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -599,7 +600,7 @@ __global__ __launch_bounds__(DW_BLK, 2) void dw3_s2_bwd_kernel(Dw3Params p) {
           for (int i = 0; i < 2; ++i) {
             const unsigned r = o_row(2 * v + 1 + i - p.pa);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) dw_store(ro, r + ocol[k], acc[i][k]);
+            for (int k = 0; k < 4; ++k) dw_store<STREAM_GRAD>(ro, r + ocol[k], acc[i][k]);
           }
         }
         if constexpr (WG) {
@@ -1037,8 +1038,11 @@ hipError_t launch_dw3_fprop(const Geom& g, const void* x, const void* W, const f
     p.wf_out = n == 0 ? (bf16_t*)w_folded : nullptr;
     p.Ha = g.Hin; p.Wa = g.Win; p.Ho = g.Hout; p.Wo = g.Wout; p.pa = g.ph; p.pb = g.pw;
     const dim3 grid(pl.nxb, pl.slices);
-    if (g.sh == 1) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false, false>), grid, dim3(DW_BLK), 0, st, p);
-    else hipLaunchKernelGGL(dw3_s2_fprop_kernel, grid, dim3(DW_BLK), 0, st, p);
+    const bool stream = streams_output((size_t)g.M * g.Cout * 2);
+    if (g.sh == 1 && stream) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false, false, true>), grid, dim3(DW_BLK), 0, st, p);
+    else if (g.sh == 1) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false, false, false>), grid, dim3(DW_BLK), 0, st, p);
+    else if (stream) hipLaunchKernelGGL(dw3_s2_fprop_kernel<true>, grid, dim3(DW_BLK), 0, st, p);
+    else hipLaunchKernelGGL(dw3_s2_fprop_kernel<false>, grid, dim3(DW_BLK), 0, st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1062,11 +1066,11 @@ hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const vo
     if (g.sh == 1) {
       p.pa = 2 - g.ph; p.pb = 2 - g.pw;
       const bool pad1 = g.ph == 1 && g.pw == 1;
-      if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<false, true, false, false>), grid, dim3(DW_BLK), 0, st, p);
-      else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, true>), grid, dim3(DW_BLK), 0, st, p);
-      else if (dx) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, false>), grid, dim3(DW_BLK), 0, st, p);
-      else if (pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, true>), grid, dim3(DW_BLK), 0, st, p);
-      else hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, false>), grid, dim3(DW_BLK), 0, st, p);
+      if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<false, true, false, false, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, true, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);
+      else if (dx) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, false, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);
+      else if (pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, true, false>), grid, dim3(DW_BLK), 0, st, p);
+      else hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, false, false>), grid, dim3(DW_BLK), 0, st, p);
     } else {
       p.pa = g.ph; p.pb = g.pw; p.v0 = dw3_first(g.ph); p.u0 = dw3_first(g.pw);
       if (dx && part) hipLaunchKernelGGL((dw3_s2_bwd_kernel<true, true>), grid, dim3(DW_BLK), 0, st, p);

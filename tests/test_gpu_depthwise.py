@@ -106,6 +106,26 @@ def test_infinity_stays_with_the_taps_that_touch_it(where, s):
             assert bool(finite[5, 0, i, j]) == (i not in hit or j not in hit), (i, j)
 
 
+@pytest.mark.parametrize("s", [1, 2])
+def test_large_outputs(s):
+    """Outputs of 24 MB and more leave through other stores: 32 images at once give what two calls of 16 give, bit for bit."""
+    from paper_2305_11624_amd.runner import DepthwiseRun
+    c, h = 96, 64 * s
+    g = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    x, dy = normal(32, c, h, h), normal(32, c, 64, 64)
+    inp = dict(W=normal(c, 1, 3, 3), gamma=normal(c), beta=normal(c), rmean=normal(c), rvar=normal(c).abs() + 0.5, b=None, eps=1e-5)
+    z, dx = [], []
+    for a, b in ((0, 32), (0, 16), (16, 32)):
+        shape = BlockShape("large", b - a, c, h, h, c, 3, s, 1, "bf16")
+        r = DepthwiseRun(dict(inp, shape=shape, x=x[a:b], dy=dy[a:b]), poison=True)
+        r.step()
+        z.append(r.z)
+        dx.append(r.dx)
+    assert z[0].nbytes >= 24 << 20 > z[1].nbytes
+    assert torch.equal(z[0], torch.cat(z[1:])) and torch.equal(dx[0], torch.cat(dx[1:]))
+
+
 def test_full_size_layer():
     """A depthwise layer at network size: 144 channels, 56x56, N = 32 (an inverted-residual stage), sampled against
     the oracle run on the first two images (the block is independent across images except for the parameter gradients,

@@ -165,6 +165,27 @@ def test_groups_equal_to_channels_is_the_depthwise_block():
         assert torch.equal(res[k], dw[k]), k          # the same kernels: the grouped calls pass this limit on
 
 
+@pytest.mark.parametrize("s", [1, 2])
+def test_large_outputs(s):
+    """Outputs of 24 MB and more leave through other stores: 32 images at once give what two calls of 16 give, bit for bit."""
+    from paper_2305_11624_amd.runner import GroupedRun
+    c, h = 96, 64 * s
+    g = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    x, dy = normal(32, c, h, h), normal(32, c, 64, 64)
+    inp = dict(W=normal(c, 8, 3, 3), gamma=normal(c), beta=normal(c), rmean=normal(c), rvar=normal(c).abs() + 0.5, b=None, eps=1e-5,
+               groups=12)
+    z, dx = [], []
+    for a, b in ((0, 32), (0, 16), (16, 32)):
+        shape = BlockShape("large", b - a, c, h, h, c, 3, s, 1, "bf16")
+        r = GroupedRun(dict(inp, shape=shape, x=x[a:b], dy=dy[a:b]), poison=True)
+        r.step()
+        z.append(r.z)
+        dx.append(r.dx)
+    assert z[0].nbytes >= 24 << 20 > z[1].nbytes
+    assert torch.equal(z[0], torch.cat(z[1:])) and torch.equal(dx[0], torch.cat(dx[1:]))
+
+
 @pytest.mark.parametrize("name,C,H,stride", [("gx_56", 128, 56, 1), ("gx_56_s2", 256, 56, 2), ("gx_14", 512, 14, 1),
                                              ("gx_7", 1024, 7, 1), ("gx_7_w64", 2048, 7, 1)])
 def test_full_size_layers(name, C, H, stride):
