@@ -406,17 +406,23 @@ hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, cons
   p.nchunks = C / CB;
   p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
   if (bn) p.bn = *bn;
-  // An input gradient of 16 MB and more is stored past the last-level cache, which then keeps x and dz for the weight gradient
-  // that follows: config 1 (51 MB of dx) 55.0 -> 48.1 us a pass; a backbone step, where the previous block reads the dx again,
-  // takes the same time (2.960 and 2.963 ms), chains of three blocks with 6 MB of dx 1 % longer.  Forward outputs stay in
-  // the cache: the backbone's forward pass takes 861 us with them there, 919 without.
+  // An input gradient of 16 MB and more is stored past the caches.  The weight gradient behind it takes what it took (14.4 us), it is
+  // the next forward pass that finds more room (256 -> 64 at 56 x 56, 32 images: 21.2 -> 18.1).  A block on its own, inputs from
+  // memory: 256 -> 64 at 56 x 56, 32 images (51 MB of dx) 62.1 -> 58.2 us a pass, 16 images 42.6 -> 40.1, 64 images 98.3 -> 91.7;
+  // 512 -> 128 at 28 x 28, 32 images 47.1 -> 45.2; inputs still in the last-level cache from the pass before last 58.5 -> 52.2; the
+  // same tensors again at once 51.0 -> 51.3.  Where the previous block reads dx next, it pays some of it back: three blocks in a
+  // row, a step, 0.4 - 2 % longer from 17 to 103 MB (51 MB: 159.5 -> 162.5 us) and 5 % shorter at 206 MB (478 -> 454); the
+  // backbone's training step 16 and 32 images 0.3 % longer (2813 -> 2822), 64 and 128 images 0.5 and 1 % shorter (7643 -> 7565).
+  // Forward outputs stay in the caches: the backbone's forward pass, 32 images, takes 861 us with them there, 919 without.
   const bool stream = grad && (size_t)M * R * 2 >= ((size_t)16 << 20);
   p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
 #define GM_CASE(TM_, RES_, TN_, NS_) \
   if (pl.tm == TM_ && pl.res == RES_ && pl.tn == TN_ && pl.ns == NS_) \
     return stream ? launch_inst<TM_, RES_, TN_, NS_, true>(p, st) : launch_inst<TM_, RES_, TN_, NS_, false>(p, st);
-  GM_CASE(128, 0, 128, 2) GM_CASE(256, 0, 128, 3) GM_CASE(128, 0, 128, 3) GM_CASE(128, 1, 128, 3) GM_CASE(128, 2, 128, 3)
+  GM_CASE(128, 0, 128, 2) GM_CASE(256, 0, 128, 3) GM_CASE(128, 1, 128, 3) GM_CASE(128, 2, 128, 3)
   GM_CASE(128, 0, 64, 3) GM_CASE(128, 1, 64, 3) GM_CASE(128, 2, 64, 3)
+  if (pl.tm == 128 && pl.res == 0 && pl.tn == 128 && pl.ns == 3)   // (under 2 MIN_TILES tiles: never 16 MB)
+    return launch_inst<128, 0, 128, 3, false>(p, st);
 #undef GM_CASE
   return hipErrorInvalidValue;
 }

@@ -152,6 +152,43 @@ def test_residual_addends_against_oracle_and_unfused_calls(shape, mode, keep, re
         assert torch.equal(got[k], want[k]), k
 
 
+LARGE = [   # pointwise input gradients of 16 MB and more, which are stored another way: every plan of the tiled product that they get
+    ("one_chunk", 11, 56, 55, 256, 64), ("two_chunks", 6, 53, 54, 512, 128), ("one_chunk_64", 43, 56, 55, 64, 64),
+    ("two_chunks_64", 43, 56, 55, 64, 128), ("tiles_64", 15, 55, 56, 192, 192), ("two_stages", 11, 56, 55, 256, 256),
+    ("tiles_256", 11, 56, 55, 256, 512)]
+
+
+@pytest.mark.parametrize("name,n,h,w,cin,cout", LARGE, ids=[v[0] for v in LARGE])
+def test_large_input_gradients(name, n, h, w, cin, cout):
+    """dX plain against the definition in fp32; masked, with an addend and with both, bit for bit against the plain call
+    followed by the element-wise kernels."""
+    from paper_2305_11624_amd.runner import BlockRun
+    g = torch.Generator(device="cuda").manual_seed(cin + cout)
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    shape = BlockShape("large_" + name, n, cin, h, w, cout, 1, 1, 0, "bf16")
+    inp = dict(shape=shape, x=normal(n, cin, h, w).clamp_min(0), W=normal(cout, cin, 1, 1) * cin ** -0.5, gamma=normal(cout),
+               beta=normal(cout), rmean=normal(cout), rvar=normal(cout).abs() + 0.5, b=None, dy=normal(n, cout, h, w), eps=1e-5)
+    add = normal(n, h, w, cin).to(torch.bfloat16)
+
+    def dx(act, **kw):
+        r = BlockRun(inp, poison=True, act=act, **kw)
+        r.step()
+        assert r.dx.nbytes >= 16 << 20
+        return r
+
+    plain = dx(0)
+    ref = plain.dz.float().reshape(-1, cout) @ plain.w_folded.reshape(cin, cout).float().t().contiguous()
+    err = (plain.dx.reshape(-1, cin).float() - ref).abs().max() / ref.abs().max()
+    assert err <= 4e-3, err   # (dX is rounded to bf16 once: half of 2^-7 of a value that is at most the largest one)
+    masked, added, both = plain.dx.clone(), plain.dx.clone(), plain.dx.clone()
+    B.convbn_aux_eltwise(B.OP_RELU_BWD, masked, plain.x)
+    B.convbn_aux_eltwise(B.OP_ADD, added, add)
+    B.convbn_aux_add_relu_bwd(both, add, plain.x)
+    assert torch.equal(dx(B.ACT_RELU_IN).dx, masked)
+    assert torch.equal(dx(B.ACT_ADD_IN, add_in=add).dx, added)
+    assert torch.equal(dx(B.ACT_ADD_IN | B.ACT_RELU_IN, add_in=add).dx, both)
+
+
 def test_addend_bit_without_a_tensor_is_refused():
     from paper_2305_11624_amd.runner import BlockRun
     run = BlockRun(_inputs(SHAPES[0]), mode="tune")
