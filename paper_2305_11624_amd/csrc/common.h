@@ -315,7 +315,7 @@ hipError_t launch_dw_fold_back(const Geom& g, int dtype, const float* part, cons
                                float* sums, const void* W, const float* b, const float* gamma, const float* mean,
                                const float* var, void* dW, float* db, float* dgamma, float* dbeta, hipStream_t st);
 
-// ... 3x3 windows with stride 1 or 2 and paddings up to 2, bf16, channels multiples of 8: the filter is folded by the threads
+// ... 3x3 windows with stride 1 or 2, bf16, channels multiples of 8: the filter is folded by the threads
 // that use it (w is the unfolded [C][9] filter, gamma == null: s = 1), forward leaves w_folded [9][C] on the side (or
 // null), and backward's two gradients are one launch (w_folded: what forward kept, or null; dx or part may be null; part:
 // dw3_part_bytes()).

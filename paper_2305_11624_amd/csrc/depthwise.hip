@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void dw_dgrad_kernel(const T* __restrict__ dz,
   Vec<T, VEC>::store(dx + idx * VEC, acc);
 }
 
-// ---- 3x3 windows, stride 1 or 2, paddings 0..2, bf16, C % 8 == 0 ------------------------------------------------
+// ---- 3x3 windows, stride 1 or 2, any padding, bf16, C % 8 == 0 -------------------------------------------------
 // A pass has to move its tensors once and multiply 9 times per element (18 with the weight gradient), so two things
 // bound it: the bytes in flight, and the vector unit.  A thread owns 4 channels (8 bytes; consecutive threads =
 // consecutive channels, then columns) of two neighbouring columns and slides down R rows: an input row is requested
@@ -147,7 +147,7 @@ struct Dw3Params {
   int tap_major;
   int N, C, Ha, Wa, Ho, Wo;     // images; a's and out's (and y's) planes
   int pa, pb;                   // a's row for output row o and window row i: o S + i - pa
-  int u0, v0;                   // stride 2 backward: the first dZ row and column a thread owns
+  int u0, v0;                   // backward: the first column and row of the threads' domain (stride 1: of x, 2: of dZ)
   int R, nstrip, npair, cq, items, per_slice, slice0, slices_all;
 };
 
@@ -260,12 +260,14 @@ __device__ __forceinline__ void dw_slice_sums(const Dw3Params& p, const float (&
 // WG (a = dZ): dw'[8 - (i, j)] += y[n][h][w] a[n][h + i - pa][w + j - pb] over the owned (h, w), and the sums of a.
 // Products with a position outside an image are skipped, not multiplied by zero: an infinite x or dZ at the border does
 // not reach the taps that do not touch it.
-// PAD1: pa = pb = 1, the sizes of a and out are the same.
+// PAD1: pa = pb = 1, the sizes of a and out are the same.  Paddings above 2 put dZ rows and columns in front of (and behind) all
+// that x meets: they count in the sums of a alone, and the domain starts with them, before the first row of x.
 template <bool FWD, bool CONV, bool WG, bool PAD1, bool STREAM>
 __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p) {
   __shared__ float red[WG ? 20 * DW_BLK : 1];
   if (FWD) dw_emit_folded(p);
   const int pad_h = PAD1 ? 1 : p.pa, pad_w = PAD1 ? 1 : p.pb;
+  constexpr bool AHEAD = !FWD && !PAD1;   // the domain may start before the first row of out
   const int L = DW_BLK / p.cq;
   const int tx = threadIdx.x % p.cq, lane = threadIdx.x / p.cq;
   const int c = ((int)blockIdx.x * p.cq + tx) * 4;
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
       const int pair = it % p.npair;
       const int rest = it / p.npair;
       const int strip = rest % p.nstrip, n = rest / p.nstrip;
-      const int w0 = pair * 2, h0 = strip * p.R;
+      const int w0 = pair * 2 + (AHEAD ? p.u0 : 0), h0 = strip * p.R + (AHEAD ? p.v0 : 0);
       unsigned acol[4], ocol[2];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -296,11 +298,12 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
         acol[k] = (unsigned)w < (unsigned)p.Wa ? (unsigned)w * px : DW_INV;
       }
 #pragma unroll
-      for (int k = 0; k < 2; ++k) ocol[k] = w0 + k < p.Wo ? (unsigned)(w0 + k) * px : DW_INV;
+      for (int k = 0; k < 2; ++k) ocol[k] = (unsigned)(w0 + k) < (unsigned)p.Wo ? (unsigned)(w0 + k) * px : DW_INV;
       const bool has_l = acol[0] != DW_INV, has_r = acol[3] != DW_INV, two = ocol[1] != DW_INV;
       const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
       // running offsets: the next row of a (with its index), of y and of out
-      const int nq = p.R + 2, rows = max(min(p.Ho - h0, p.R), 0), hend = min(p.Ha, h0 - pad_h + nq);
+      const int nq = p.R + 2, rows = max(min(p.Ho - h0, p.R), 0), hend = max(min(p.Ha, h0 - pad_h + nq), 0);
+      const int row0 = AHEAD ? max(-h0, 0) : 0;   // the strip's first row that out has
       int ha = h0 - pad_h;
       unsigned aoff = abase + (unsigned)ha * arow, yoff = obase + (unsigned)h0 * orow, ooff = yoff - 2 * orow;
       u32x2 pa[2][4], py[2][2];
@@ -311,7 +314,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
 #pragma unroll
         for (int k = 0; k < 4; ++k) pa[slot][k] = dw_load(ra, r + acol[k]);
         if constexpr (WG) {
-          const unsigned s = q < rows ? yoff : DW_INV;
+          const unsigned s = q >= row0 && q < rows ? yoff : DW_INV;
           yoff += orow;
 #pragma unroll
           for (int k = 0; k < 2; ++k) py[slot][k] = dw_load(ry, s + ocol[k]);
@@ -361,18 +364,18 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
                 for (int x = 0; x < 2; ++x)
 #pragma unroll
                   for (int e = 0; e < 4; ++e) acc[(u + 3 - i) % 3][x][e] += t[i * 3 + j][e] * av[x + j][e];
-            const unsigned r = (unsigned)(q - 2) < (unsigned)rows ? ooff : DW_INV;   // the row that is complete now
+            const unsigned r = q - 2 >= row0 && q - 2 < rows ? ooff : DW_INV;   // the row that is complete now
             ooff += orow;
 #pragma unroll
             for (int x = 0; x < 2; ++x) dw_store<STREAM>(ro, r + ocol[x], acc[(u + 1) % 3][x]);
           }
           if constexpr (WG) {
             if ((unsigned)(h0 + q - pad_h) < (unsigned)p.Ha) {
-              if (q >= pad_h && q < pad_h + p.R) {   // a's owned pixels
+              if (q >= max(pad_h, 0) && q < max(pad_h, 0) + p.R) {   // a's owned pixels
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                   if constexpr (PAD1) wacc[9][e] += av[1][e] + av[2][e];
-                  else wacc[9][e] += pad_w == 0 ? av[0][e] + av[1][e] : pad_w == 1 ? av[1][e] + av[2][e] : av[2][e] + av[3][e];
+                  else wacc[9][e] += pad_w <= 0 ? av[0][e] + av[1][e] : pad_w == 1 ? av[1][e] + av[2][e] : av[2][e] + av[3][e];
                 }
               }
 #pragma unroll
@@ -381,7 +384,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
                 const float(&y)[2][4] = yv[(u + 3 - i) % 3];
                 const float(&z)[2][4] = ye[(u + 3 - i) % 3];
                 if (q >= i && q - i < p.R)   // (the others are the neighbouring strips' rows)
-                  if (q - i < rows) {
+                  if (q - i >= row0 && q - i < rows) {
                     if constexpr (PAD1) {
 #pragma unroll
                       for (int e = 0; e < 4; ++e) {
@@ -734,7 +737,7 @@ __global__ __launch_bounds__(1024) void dw3_fold_back_kernel(const float* __rest
 // ---- host side of these kernels
 bool dw3_shape(const Geom& g, int dtype) {   // the 32-bit offsets of a launch reach 1 GiB: several launches split the images
   return dtype == CONVBN_BF16 && g.Cin % 8 == 0 && g.kH == 3 && g.kW == 3 && g.sh == g.sw && (g.sh == 1 || g.sh == 2) &&
-         g.ph <= 2 && g.pw <= 2 && (size_t)g.Hin * g.Win * g.Cin * 2 < DW_INV && (size_t)g.Hout * g.Wout * g.Cin * 2 < DW_INV;
+         (size_t)g.Hin * g.Win * g.Cin * 2 < DW_INV && (size_t)g.Hout * g.Wout * g.Cin * 2 < DW_INV;
 }
 struct Dw3Plan {
   int cq, nxb;               // channel quads of a workgroup, workgroups across the channels
@@ -781,7 +784,7 @@ Dw3Plan dw3_fprop_plan(const Geom& g) {
 int dw3_first(int pad) { return pad == 0 ? -1 : 0; }   // stride 2: the first dZ row (column) that owns x rows
 Dw3Plan dw3_bwd_plan(const Geom& g) {
   return planned<Dw3Plan>(g, 1, [&] {
-    if (g.sh == 1)
+    if (g.sh == 1)   // (what starts ahead of x ends behind it: paddings above 2 make dZ the larger)
       return dw3_plan(g, g.Hin > g.Hout ? g.Hin : g.Hout, g.Win > g.Wout ? g.Win : g.Wout, 4, 2);
     // x row Hin - 1 belongs to the step v with 2 v + 2 >= Hin - 1 + ph; every dZ row is some step's own
     auto span = [](int in, int out, int pad) {
@@ -1065,6 +1068,7 @@ hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const vo
     const dim3 grid(pl.nxb, pl.slices);
     if (g.sh == 1) {
       p.pa = 2 - g.ph; p.pb = 2 - g.pw;
+      p.v0 = p.pa < 0 ? p.pa : 0; p.u0 = p.pb < 0 ? p.pb : 0;
       const bool pad1 = g.ph == 1 && g.pw == 1;
       if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<false, true, false, false, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);
       else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, true, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);

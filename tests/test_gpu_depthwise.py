@@ -74,7 +74,9 @@ SWEEP = [(n, c, h, w, s, p) for n, c, h, w, s, p in [
     (1, 8, 3, 3, 1, 0), (1, 8, 1, 1, 1, 1), (2, 16, 5, 4, 1, 2), (3, 264, 13, 11, 1, 1), (1, 520, 31, 7, 1, 0),
     (2, 32, 57, 63, 1, 1), (40, 96, 29, 30, 1, 1), (2, 24, 9, 10, 1, 2), (1, 8, 3, 3, 2, 0), (1, 8, 1, 2, 2, 1),
     (2, 16, 5, 4, 2, 2), (3, 264, 13, 10, 2, 1), (2, 40, 14, 15, 2, 0), (2, 32, 57, 64, 2, 1), (24, 96, 28, 29, 2, 1),
-    (2, 24, 8, 11, 2, 2)]]
+    (2, 24, 8, 11, 2, 2),
+    # paddings above the window: dZ's first and last rows and columns meet no x
+    (2, 24, 9, 7, 1, 3), (1, 8, 1, 1, 1, 4), (9, 72, 21, 30, 1, 5), (2, 24, 9, 8, 2, 3), (1, 8, 2, 1, 2, 4), (9, 72, 21, 30, 2, 5)]]
 
 
 @pytest.mark.parametrize("n,c,h,w,s,p", SWEEP)
@@ -86,6 +88,44 @@ def test_row_sweep(n, c, h, w, s, p):
     compare(_run(inp, keep_folded=False, need_dx=False), ref, "bf16", keys=("Z", "dW", "db", "dgamma", "dbeta"), tag="no dx")
     compare(_run(inp, keep_folded=False, params=False), ref, "bf16", keys=("dX",), tag="dx only")
     compare(_run(inp, mode="eval"), ref, "bf16", keys=EVAL_KEYS, tag="eval")
+
+
+@pytest.mark.parametrize("s", [1, 2])
+@pytest.mark.parametrize("ph,pw", [(1, 0), (0, 2), (2, 1), (1, 4), (5, 1), (3, 0)])
+def test_uneven_paddings(ph, pw, s):
+    """Rows and columns padded differently, all four gradients at once and dX or dW alone, against fp64 on the host."""
+    import torch.nn.functional as F
+    n, c, h, w = 3, 24, 11, 18
+    g = torch.Generator().manual_seed(17 * ph + pw)
+    r = lambda *size: torch.randn(*size, generator=g).to(torch.bfloat16).double()
+    x, wt, gamma, var = r(n, c, h, w).requires_grad_(), r(c, 1, 3, 3).requires_grad_(), r(c), r(c).abs() + 0.5
+    beta, mean = r(c), r(c)
+    scale = gamma / (var + 1e-5).sqrt()
+    y = F.conv2d(x, wt, None, s, (ph, pw), groups=c)
+    z = (y - mean[:, None, None]) * scale[:, None, None] + beta[:, None, None]
+    dz = r(*z.shape)
+    z.backward(dz)
+    ref = dict(Z=z.detach(), dX=x.grad, dW=wt.grad, dbeta=dz.sum((0, 2, 3)),
+               dgamma=(dz * ((y.detach() - mean[:, None, None]) / (var + 1e-5).sqrt()[:, None, None])).sum((0, 2, 3)))
+    ref = {k: v.numpy() for k, v in ref.items()}
+    d = B.make_desc(n, c, h, w, c, 3, 3, s, ph, pad_w=pw)
+    act, vec = (lambda t: B.act_to_device(t.detach().float(), torch.bfloat16, "cuda")), (lambda t: t.float().cuda())
+    xd, wd, dzd = act(x), wt.detach().reshape(c, 3, 3).to(torch.bfloat16).cuda(), act(dz)
+    nan = lambda like: torch.full_like(like, float("nan"))
+    ws = [torch.empty(max(16, B.convbn_dw_workspace_bytes(d, B.MODE_TUNE, p)), dtype=torch.uint8, device="cuda")
+          for p in (B.PASS_FWD, B.PASS_BWD)]
+    zd, wf = nan(dzd), torch.empty(3, 3, c, dtype=torch.bfloat16, device="cuda")
+    B.convbn_dw_tune_fwd(d, xd, wd, None, vec(gamma), vec(beta), vec(mean), vec(var), zd, wf, ws[0])
+    for need_dx, params in ((True, True), (True, False), (False, True)):
+        dx, dw, dga, dbe = (nan(t) for t in (xd, wd, vec(gamma), vec(beta)))
+        B.convbn_dw_tune_bwd(d, xd, wd, None, vec(gamma), vec(mean), vec(var), wf, dzd, dx if need_dx else None,
+                             dw if params else None, None, dga if params else None, dbe if params else None, ws[1])
+        got = dict(Z=B.act_from_device(zd))
+        if need_dx:
+            got["dX"] = B.act_from_device(dx)
+        if params:
+            got.update(dW=dw.double().cpu().reshape(c, 1, 3, 3), dgamma=dga.double().cpu(), dbeta=dbe.double().cpu())
+        compare(got, ref, "bf16", keys=list(got), tag=str((ph, pw, s)))
 
 
 @pytest.mark.parametrize("s", [1, 2])
