@@ -337,9 +337,10 @@ struct StemWgParams {
 
 // KH, SW: window rows and column stride at compile time (0: taken from the parameters): every operand is then an offset field
 // of the reads, the eight steps of a tile are unrolled, and a row of ones behind the patch's (KH = 7) is wave 3's second: 33.2
-// -> 23.5 us, the matrix pipe busy for a quarter of them.
+// -> 23.5 us, the matrix pipe busy for a quarter of them.  Two workgroups share a compute unit, but for 128 output channels, whose
+// 192 sums a lane would not all fit the registers then (32 images of 2 channels, 111 x 154, 4 x 4 / 2: a backward pass 152 us, so 110).
 template <int NCO, bool X3, int KH, int SW>
-__global__ __launch_bounds__(256, 2) void stem_wgrad_kernel(StemWgParams p) {
+__global__ __launch_bounds__(256, NCO == 4 ? 1 : 2) void stem_wgrad_kernel(StemWgParams p) {
   static_assert(KH == 0 || KH == 7, "seven window rows and the row of ones are two a wave");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // two buffers (one, where two do not fit): patch [kH][prow], behind it at p.zt the dZ tile [TPX][zpitch]

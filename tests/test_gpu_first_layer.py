@@ -17,7 +17,11 @@ SHAPES = [
     (3, 3, 64, 256, 64, 7, 2, 3),     # whole tiles
     (2, 3, 30, 44, 64, 7, 2, 0),      # no padding
     (2, 3, 21, 24, 32, 7, 2, 3),      # one fragment of output channels
-    (2, 3, 20, 28, 72, 7, 2, 3),      # a last fragment of 8 channels
+    (2, 3, 20, 28, 40, 7, 2, 3),      # a second fragment of 8 channels
+    (2, 3, 22, 24, 56, 7, 2, 3),      # ... of 24
+    (2, 3, 20, 28, 72, 7, 2, 3),      # three fragments: the input padded to 8 channels
+    (2, 3, 18, 36, 104, 7, 2, 3),     # four, the last of 8 channels
+    (3, 2, 21, 34, 128, 4, 2, 1),     # ... of a 4-channel copy of the input
     (2, 3, 19, 21, 64, 7, 2, 3),      # rows that are no whole groups of four pixels
     (2, 3, 24, 24, 64, 3, 2, 1),
     (2, 1, 23, 20, 64, 5, 1, 2), (2, 2, 17, 19, 40, 4, 2, 1), (2, 4, 18, 18, 64, 8, 2, 3), (1, 3, 16, 16, 128, 7, 1, 3)]
