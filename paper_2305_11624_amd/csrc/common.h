@@ -163,10 +163,12 @@ __device__ __forceinline__ void store_result(void* p, uint4 v) {
 //   0.4  960 channels at 7 x 7, 4 images                         85.2        91.1 us
 //   12.8 512 channels at 14 x 14, 64 images                     169.5       183.1
 //   12.8 256 channels at 28 x 28, 32 images                     137.0       139.7
+//   14.4 144 channels at 56 x 56, 16 images                    134.0       135.4
 //   25.7 256 channels at 28 x 28, 64 images                     239.2       237.2
 //   28.9 144 channels at 56 x 56, 32 images                     211.7       211.2
 //   57.8 144 channels at 56 x 56, 64 images                     362.6       347.9
-inline bool streams_output(size_t bytes) { return bytes >= ((size_t)24 << 20); }
+// 19.3 MB (96 channels at 112 x 112 / 2, 32 images): a chain of three takes 94 us either way, the block alone 21.6 and 18.4.
+inline bool streams_output(size_t bytes) { return bytes >= ((size_t)16 << 20); }
 // Their input gradients leave past the caches at every size.  A single block gains (inputs from memory: 144 channels at 56 x 56,
 // 32 images, 52.8 -> 52.2 us a pass, 256 channels at 28 x 28 45.8 -> 44.5; inputs still in the last-level cache from the last
 // time: 50.2 -> 42.4, 41.7 -> 41.0).  A step over the chains above takes within 1 % of the same up to 13 MB (64 images of 384

@@ -148,7 +148,7 @@ def test_infinity_stays_with_the_taps_that_touch_it(where, s):
 
 @pytest.mark.parametrize("s", [1, 2])
 def test_large_outputs(s):
-    """Outputs of 24 MB and more leave through other stores: 32 images at once give what two calls of 16 give, bit for bit."""
+    """Outputs of 16 MB and more leave through other stores: 32 images at once give what two calls of 16 give, bit for bit."""
     from paper_2305_11624_amd.runner import DepthwiseRun
     c, h = 96, 64 * s
     g = torch.Generator(device="cuda").manual_seed(7)
@@ -162,7 +162,7 @@ def test_large_outputs(s):
         r.step()
         z.append(r.z)
         dx.append(r.dx)
-    assert z[0].nbytes >= 24 << 20 > z[1].nbytes
+    assert z[0].nbytes >= 16 << 20 > z[1].nbytes
     assert torch.equal(z[0], torch.cat(z[1:])) and torch.equal(dx[0], torch.cat(dx[1:]))
 
 

@@ -167,7 +167,7 @@ def test_groups_equal_to_channels_is_the_depthwise_block():
 
 @pytest.mark.parametrize("s", [1, 2])
 def test_large_outputs(s):
-    """Outputs of 24 MB and more leave through other stores: 32 images at once give what two calls of 16 give, bit for bit."""
+    """Outputs of 16 MB and more leave through other stores: 32 images at once give what two calls of 16 give, bit for bit."""
     from paper_2305_11624_amd.runner import GroupedRun
     c, h = 96, 64 * s
     g = torch.Generator(device="cuda").manual_seed(7)
@@ -182,7 +182,7 @@ def test_large_outputs(s):
         r.step()
         z.append(r.z)
         dx.append(r.dx)
-    assert z[0].nbytes >= 24 << 20 > z[1].nbytes
+    assert z[0].nbytes >= 16 << 20 > z[1].nbytes
     assert torch.equal(z[0], torch.cat(z[1:])) and torch.equal(dx[0], torch.cat(dx[1:]))
 
 
