@@ -149,6 +149,10 @@ struct Dw3Params {
   int pa, pb;                   // a's row for output row o and window row i: o S + i - pa
   int u0, v0;                   // backward: the first column and row of the threads' domain (stride 1: of x, 2: of dZ)
   int R, nstrip, npair, cq, items, per_slice, slice0, slices_all;
+  // A launch's offsets are 32 bits from the first rows that it touches: images of 1 GiB and more go in bands of strips.
+  int strip0;                   // the launch's first strip
+  int a_row0, o_row0;           // the rows that a, and out and y, point to
+  unsigned a_bytes, o_bytes;    // how much of them a launch touches
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t dw_rsrc(const void* p, size_t bytes) {
@@ -273,8 +277,8 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
   const int c = ((int)blockIdx.x * p.cq + tx) * 4;
   const bool live = lane < L && c < p.C;
   const unsigned px = (unsigned)p.C * 2u, arow = px * p.Wa, orow = px * p.Wo;
-  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow), ry = dw_rsrc(WG ? p.y : p.a, (size_t)p.N * p.Ho * orow);
-  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
+  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, p.a_bytes), ry = dw_rsrc(WG ? p.y : p.a, p.o_bytes);
+  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, p.o_bytes);
   float t[9][4], bb[4], wacc[10][4];
   if constexpr (WG) {
 #pragma unroll
@@ -289,7 +293,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
     for (int it = slice * p.per_slice + lane; it < it1; it += L) {
       const int pair = it % p.npair;
       const int rest = it / p.npair;
-      const int strip = rest % p.nstrip, n = rest / p.nstrip;
+      const int strip = p.strip0 + rest % p.nstrip, n = rest / p.nstrip;
       const int w0 = pair * 2 + (AHEAD ? p.u0 : 0), h0 = strip * p.R + (AHEAD ? p.v0 : 0);
       unsigned acol[4], ocol[2];
 #pragma unroll
@@ -300,7 +304,7 @@ __global__ __launch_bounds__(DW_BLK, WG ? 2 : 4) void dw3_s1_kernel(Dw3Params p)
 #pragma unroll
       for (int k = 0; k < 2; ++k) ocol[k] = (unsigned)(w0 + k) < (unsigned)p.Wo ? (unsigned)(w0 + k) * px : DW_INV;
       const bool has_l = acol[0] != DW_INV, has_r = acol[3] != DW_INV, two = ocol[1] != DW_INV;
-      const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
+      const unsigned abase = (unsigned)(n * p.Ha - p.a_row0) * arow + c * 2u, obase = (unsigned)(n * p.Ho - p.o_row0) * orow + c * 2u;
       // running offsets: the next row of a (with its index), of y and of out
       const int nq = p.R + 2, rows = max(min(p.Ho - h0, p.R), 0), hend = max(min(p.Ha, h0 - pad_h + nq), 0);
       const int row0 = AHEAD ? max(-h0, 0) : 0;   // the strip's first row that out has
@@ -429,15 +433,14 @@ __global__ __launch_bounds__(DW_BLK, 4) void dw3_s2_fprop_kernel(Dw3Params p) {
   const int c = ((int)blockIdx.x * p.cq + tx) * 4;
   if (lane >= L || c >= p.C) return;
   const unsigned px = (unsigned)p.C * 2u, arow = px * p.Wa, orow = px * p.Wo;
-  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow);
-  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
+  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, p.a_bytes), ro = dw_rsrc(p.out, p.o_bytes);
   float t[9][4], bb[4];
   dw_filter<true, false>(p, c, t, bb);
   const int slice = dw_slice(), it1 = min(p.items, (slice + 1) * p.per_slice);
   for (int it = slice * p.per_slice + lane; it < it1; it += L) {
     const int pair = it % p.npair;
     const int rest = it / p.npair;
-    const int strip = rest % p.nstrip, n = rest / p.nstrip;
+    const int strip = p.strip0 + rest % p.nstrip, n = rest / p.nstrip;
     const int w0 = pair * 2, h0 = strip * p.R;
     unsigned acol[5], ocol[2];
 #pragma unroll
@@ -447,7 +450,7 @@ __global__ __launch_bounds__(DW_BLK, 4) void dw3_s2_fprop_kernel(Dw3Params p) {
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) ocol[k] = w0 + k < p.Wo ? (unsigned)(w0 + k) * px : DW_INV;
-    const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
+    const unsigned abase = (unsigned)(n * p.Ha - p.a_row0) * arow + c * 2u, obase = (unsigned)(n * p.Ho - p.o_row0) * orow + c * 2u;
     u32x2 pa[2][5];
     auto fetch = [&](int q) {   // window rows 1 and 2 of output row h0 + q - 1
 #pragma unroll
@@ -509,8 +512,8 @@ __global__ __launch_bounds__(DW_BLK, 2) void dw3_s2_bwd_kernel(Dw3Params p) {
   const int c = ((int)blockIdx.x * p.cq + tx) * 4;
   const bool live = lane < L && c < p.C;
   const unsigned px = (unsigned)p.C * 2u, arow = px * p.Wa, orow = px * p.Wo;
-  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, (size_t)p.N * p.Ha * arow), ry = dw_rsrc(WG ? p.y : p.a, (size_t)p.N * p.Ho * orow);
-  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, (size_t)p.N * p.Ho * orow);
+  const __amdgpu_buffer_rsrc_t ra = dw_rsrc(p.a, p.a_bytes), ry = dw_rsrc(WG ? p.y : p.a, p.o_bytes);
+  const __amdgpu_buffer_rsrc_t ro = dw_rsrc(p.out, p.o_bytes);
   float t[9][4], bb[4], wacc[10][4];
   if (CONV && live) dw_filter<false, false>(p, c, t, bb);
   if constexpr (WG) {
@@ -524,7 +527,7 @@ __global__ __launch_bounds__(DW_BLK, 2) void dw3_s2_bwd_kernel(Dw3Params p) {
     for (int it = slice * p.per_slice + lane; it < it1; it += L) {
       const int pair = it % p.npair;
       const int rest = it / p.npair;
-      const int strip = rest % p.nstrip, n = rest / p.nstrip;
+      const int strip = p.strip0 + rest % p.nstrip, n = rest / p.nstrip;
       const int u0 = p.u0 + pair * 2, v0 = p.v0 + strip * p.R;
       unsigned acol[3], ocol[4];
       bool inside = true;
@@ -542,7 +545,7 @@ __global__ __launch_bounds__(DW_BLK, 2) void dw3_s2_bwd_kernel(Dw3Params p) {
         inside &= ok;
       }
       const bool wave_inside = WG && __all(inside);
-      const unsigned abase = (unsigned)n * p.Ha * arow + c * 2u, obase = (unsigned)n * p.Ho * orow + c * 2u;
+      const unsigned abase = (unsigned)(n * p.Ha - p.a_row0) * arow + c * 2u, obase = (unsigned)(n * p.Ho - p.o_row0) * orow + c * 2u;
       auto a_row = [&](int v) { return (unsigned)v < (unsigned)p.Ha ? abase + (unsigned)v * arow : DW_INV; };
       auto o_row = [&](int h) { return (unsigned)h < (unsigned)p.Ho ? obase + (unsigned)h * orow : DW_INV; };
       u32x2 pa[3], py[2][4];
@@ -735,15 +738,16 @@ __global__ __launch_bounds__(1024) void dw3_fold_back_kernel(const float* __rest
 }
 
 // ---- host side of these kernels
-bool dw3_shape(const Geom& g, int dtype) {   // the 32-bit offsets of a launch reach 1 GiB: several launches split the images
+size_t dw3_row_bytes(const Geom& g) { return (size_t)(g.Win > g.Wout ? g.Win : g.Wout) * g.Cin * 2; }
+bool dw3_shape(const Geom& g, int dtype) {   // an image fits a launch, or bands of a strip or two of it (eight rows) do
+  const size_t rows = g.Hin > g.Hout ? g.Hin : g.Hout;
   return dtype == CONVBN_BF16 && g.Cin % 8 == 0 && g.kH == 3 && g.kW == 3 && g.sh == g.sw && (g.sh == 1 || g.sh == 2) &&
-         (size_t)g.Hin * g.Win * g.Cin * 2 < DW_INV && (size_t)g.Hout * g.Wout * g.Cin * 2 < DW_INV;
+         (rows < 8 ? rows : 8) * dw3_row_bytes(g) < DW_INV;
 }
 struct Dw3Plan {
   int cq, nxb;               // channel quads of a workgroup, workgroups across the channels
-  int imgs, launches;        // images of a launch
-  int rows, cols;            // rows and columns of two that the threads share out
-  int R, nstrip, npair, items, slices, per_slice;
+  int imgs, band, launches;  // images and strips of a launch (all, or a band of one image's), launches
+  int R, nstrip, npair, slices, per_slice;
 };
 // `waves`: per SIMD.  Rows per strip: as many as give every thread the same number of strips, a strip costing its rows
 // and the ones it shares with its neighbours (`extra`).
@@ -752,30 +756,35 @@ Dw3Plan dw3_plan(const Geom& g, int rows, int cols, int extra, int waves) {
   const int quads = g.Cin / 4;
   p.nxb = ceil_div(quads, DW_MAXQ);
   p.cq = ceil_div(quads, p.nxb);
-  const size_t img = (size_t)(g.Hin > g.Hout ? g.Hin : g.Hout) * (g.Win > g.Wout ? g.Win : g.Wout) * g.Cin * 2;
-  const size_t fit = (DW_INV - 1) / img;
-  p.imgs = fit < (size_t)g.N ? (fit > 1 ? (int)fit : 1) : g.N;
-  p.launches = ceil_div(g.N, p.imgs);
-  p.rows = rows; p.cols = cols;
+  const int fit_rows = (int)((DW_INV - 1) / dw3_row_bytes(g));   // of the larger tensor, in one launch
+  const int img_rows = g.Hin > g.Hout ? g.Hin : g.Hout;
+  p.imgs = fit_rows / img_rows < g.N ? fit_rows / img_rows : g.N;
+  const bool banded = p.imgs == 0;
+  if (banded) p.imgs = 1;
+  // a band of B strips touches at most sh B R + 4 rows of a tensor; bands are equally long but for the last
+  const int most = banded ? (fit_rows - 4) / g.sh : rows;
+  auto strips = [&](int ns, int R) { return banded ? ceil_div(ns, ceil_div(ns, most / R)) : ns; };   // of a launch
   p.npair = ceil_div(cols, 2);
   const int L = DW_BLK / p.cq;
   int want = 256 * waves / 2 / p.nxb;      // workgroups of eight waves that the chip holds
   if (want < 1) want = 1;
   long long best = -1;
-  p.R = rows;
+  p.R = 1;
   for (int ns = 1; ns <= rows; ++ns) {
     const int R = ceil_div(rows, ns);
-    if (ceil_div(rows, R) != ns) continue;
-    const long long items = (long long)p.imgs * ns * p.npair;
+    if (ceil_div(rows, R) != ns || R > most) continue;
+    const long long items = (long long)p.imgs * strips(ns, R) * p.npair;
     const long long rounds = (items + (long long)want * L - 1) / ((long long)want * L);
-    const long long cost = rounds * (R + extra);
+    const long long cost = ceil_div(ns, strips(ns, R)) * rounds * (R + extra);
     if (best < 0 || cost < best) { best = cost; p.R = R; }
   }
   p.nstrip = ceil_div(rows, p.R);
-  p.items = p.imgs * p.nstrip * p.npair;
-  const int rounds = ceil_div(p.items, want * L);
+  p.band = strips(p.nstrip, p.R);
+  p.launches = ceil_div(g.N, p.imgs) * ceil_div(p.nstrip, p.band);
+  const int items = p.imgs * p.band * p.npair;
+  const int rounds = ceil_div(items, want * L);
   p.per_slice = rounds * L;
-  p.slices = ceil_div(p.items, p.per_slice);
+  p.slices = ceil_div(items, p.per_slice);
   return p;
 }
 Dw3Plan dw3_fprop_plan(const Geom& g) {
@@ -795,17 +804,50 @@ Dw3Plan dw3_bwd_plan(const Geom& g) {
     return dw3_plan(g, span(g.Hin, g.Hout, g.ph), span(g.Win, g.Wout, g.pw), 2, 2);
   });
 }
-Dw3Params dw3_params(const Dw3Plan& pl, const Geom& g, int img0, int N) {
+// One launch of a plan's: its images and strips.  a_lo .. a_hi, o_lo .. o_hi: the rows of the two planes that strips s0 .. s1 - 1
+// touch, in terms of the domain's rows d0 = v0 + s0 R .. d1 = v0 + s1 R - 1 (clipped to the planes here).
+struct Dw3Launch { int img0, N, strip0, nstrip, index; };
+template <typename F>
+hipError_t dw3_each_launch(const Dw3Plan& pl, const Geom& g, F&& launch) {
+  int index = 0;
+  for (int n = 0; n < g.N; n += pl.imgs)
+    for (int s = 0; s < pl.nstrip; s += pl.band, ++index) {
+      const hipError_t e = launch(Dw3Launch{n, g.N - n < pl.imgs ? g.N - n : pl.imgs, s,
+                                            pl.nstrip - s < pl.band ? pl.nstrip - s : pl.band, index});
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+Dw3Params dw3_params(const Dw3Plan& pl, const Geom& g, const Dw3Launch& l) {
   Dw3Params p{};
   p.eps = g.eps;
-  p.N = N;
+  p.N = l.N;
   p.C = g.Cin;
-  p.R = pl.R; p.nstrip = pl.nstrip; p.npair = pl.npair; p.cq = pl.cq;
-  p.items = N * pl.nstrip * pl.npair;
+  p.R = pl.R; p.nstrip = l.nstrip; p.npair = pl.npair; p.cq = pl.cq;
+  p.strip0 = l.strip0;
+  p.items = l.N * l.nstrip * pl.npair;
   p.per_slice = pl.per_slice;
-  p.slice0 = img0 / pl.imgs * pl.slices;
+  p.slice0 = l.index * pl.slices;
   p.slices_all = pl.launches * pl.slices;
   return p;
+}
+// The planes' sizes are set: which rows the launch touches -- a: as x d + a_lo for the domain's first row d to as x d + a_hi for its
+// last, out and y likewise with os, o_lo, o_hi -- and the tensors from there on.
+void dw3_place(Dw3Params& p, const Dw3Plan& pl, const Dw3Launch& l, const void* a, const void* y, void* out, int as, int a_lo,
+               int a_hi, int os, int o_lo, int o_hi) {
+  const int d0 = p.v0 + l.strip0 * pl.R, d1 = p.v0 + (l.strip0 + l.nstrip) * pl.R - 1;
+  auto clip = [](int v, int hi) { return v < 0 ? 0 : v > hi ? hi : v; };
+  const bool whole = l.nstrip == pl.nstrip;
+  p.a_row0 = whole ? 0 : clip(as * d0 + a_lo, p.Ha);
+  p.o_row0 = whole ? 0 : clip(os * d0 + o_lo, p.Ho);
+  const int a_end = whole ? p.Ha : clip(as * d1 + a_hi + 1, p.Ha), o_end = whole ? p.Ho : clip(os * d1 + o_hi + 1, p.Ho);
+  const size_t arow = (size_t)p.Wa * p.C, orow = (size_t)p.Wo * p.C;   // elements
+  p.a_bytes = (unsigned)(((size_t)(l.N - 1) * p.Ha + a_end - p.a_row0) * arow * 2);
+  p.o_bytes = (unsigned)(((size_t)(l.N - 1) * p.Ho + o_end - p.o_row0) * orow * 2);
+  p.a = static_cast<const bf16_t*>(a) + ((size_t)l.img0 * p.Ha + p.a_row0) * arow;
+  const size_t o = ((size_t)l.img0 * p.Ho + p.o_row0) * orow;
+  p.y = y ? static_cast<const bf16_t*>(y) + o : nullptr;
+  p.out = out ? static_cast<bf16_t*>(out) + o : nullptr;
 }
 
 constexpr int WG_TAPS = 9;     // window positions a weight-gradient workgroup accumulates at once
@@ -1033,33 +1075,28 @@ hipError_t launch_dw3_fprop(const Geom& g, const void* x, const void* W, const f
                             const float* beta, const float* mean, const float* var, void* z, void* w_folded,
                             hipStream_t st) {
   const Dw3Plan pl = dw3_fprop_plan(g);
-  for (int n = 0; n < g.N; n += pl.imgs) {
-    Dw3Params p = dw3_params(pl, g, n, g.N - n < pl.imgs ? g.N - n : pl.imgs);
-    p.a = (const bf16_t*)x + (size_t)n * g.Hin * g.Win * g.Cin;
-    p.out = (bf16_t*)z + (size_t)n * g.Hout * g.Wout * g.Cin;
+  const bool stream = streams_output((size_t)g.M * g.Cout * 2);
+  return dw3_each_launch(pl, g, [&](const Dw3Launch& l) {
+    Dw3Params p = dw3_params(pl, g, l);
     p.W = (const bf16_t*)W; p.b = b; p.gamma = gamma; p.beta = beta; p.mean = mean; p.var = var;
-    p.wf_out = n == 0 ? (bf16_t*)w_folded : nullptr;
+    p.wf_out = l.index == 0 ? (bf16_t*)w_folded : nullptr;
     p.Ha = g.Hin; p.Wa = g.Win; p.Ho = g.Hout; p.Wo = g.Wout; p.pa = g.ph; p.pb = g.pw;
+    // (stride 2 asks for a row more in front, which belongs to no output of the strip)
+    dw3_place(p, pl, l, x, nullptr, z, g.sh, -p.pa - (g.sh - 1), 2 - p.pa, 1, 0, 0);
     const dim3 grid(pl.nxb, pl.slices);
-    const bool stream = streams_output((size_t)g.M * g.Cout * 2);
     if (g.sh == 1 && stream) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false, false, true>), grid, dim3(DW_BLK), 0, st, p);
     else if (g.sh == 1) hipLaunchKernelGGL((dw3_s1_kernel<true, true, false, false, false>), grid, dim3(DW_BLK), 0, st, p);
     else if (stream) hipLaunchKernelGGL(dw3_s2_fprop_kernel<true>, grid, dim3(DW_BLK), 0, st, p);
     else hipLaunchKernelGGL(dw3_s2_fprop_kernel<false>, grid, dim3(DW_BLK), 0, st, p);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const void* W, const void* w_folded,
                           const float* gamma, const float* var, void* dx, float* part, hipStream_t st) {
   const Dw3Plan pl = dw3_bwd_plan(g);
-  for (int n = 0; n < g.N; n += pl.imgs) {
-    Dw3Params p = dw3_params(pl, g, n, g.N - n < pl.imgs ? g.N - n : pl.imgs);
-    p.a = (const bf16_t*)dz + (size_t)n * g.Hout * g.Wout * g.Cin;
-    p.y = (const bf16_t*)x + (size_t)n * g.Hin * g.Win * g.Cin;
-    p.out = dx ? (bf16_t*)dx + (size_t)n * g.Hin * g.Win * g.Cin : nullptr;
+  return dw3_each_launch(pl, g, [&](const Dw3Launch& l) {
+    Dw3Params p = dw3_params(pl, g, l);
     p.part = part;
     p.W = (const bf16_t*)(w_folded ? w_folded : W);
     p.tap_major = w_folded != nullptr;
@@ -1069,6 +1106,7 @@ hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const vo
     if (g.sh == 1) {
       p.pa = 2 - g.ph; p.pb = 2 - g.pw;
       p.v0 = p.pa < 0 ? p.pa : 0; p.u0 = p.pb < 0 ? p.pb : 0;
+      dw3_place(p, pl, l, dz, x, dx, 1, -p.pa, 2 - p.pa, 1, 0, 0);
       const bool pad1 = g.ph == 1 && g.pw == 1;
       if (dx && !part) hipLaunchKernelGGL((dw3_s1_kernel<false, true, false, false, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);
       else if (dx && pad1) hipLaunchKernelGGL((dw3_s1_kernel<false, true, true, true, STREAM_GRAD>), grid, dim3(DW_BLK), 0, st, p);
@@ -1077,14 +1115,13 @@ hipError_t launch_dw3_bwd(const Geom& g, const void* x, const void* dz, const vo
       else hipLaunchKernelGGL((dw3_s1_kernel<false, false, true, false, false>), grid, dim3(DW_BLK), 0, st, p);
     } else {
       p.pa = g.ph; p.pb = g.pw; p.v0 = dw3_first(g.ph); p.u0 = dw3_first(g.pw);
+      dw3_place(p, pl, l, dz, x, dx, 1, 0, 1, 2, 1 - p.pa, 2 - p.pa);
       if (dx && part) hipLaunchKernelGGL((dw3_s2_bwd_kernel<true, true>), grid, dim3(DW_BLK), 0, st, p);
       else if (dx) hipLaunchKernelGGL((dw3_s2_bwd_kernel<true, false>), grid, dim3(DW_BLK), 0, st, p);
       else hipLaunchKernelGGL((dw3_s2_bwd_kernel<false, true>), grid, dim3(DW_BLK), 0, st, p);
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_dw3_fold_back(const Geom& g, const float* part, const void* W, const float* b, const float* gamma,

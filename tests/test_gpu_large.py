@@ -1,6 +1,7 @@
-"""GPU parity of tensors beyond 2 GiB, which the kernels with 32-bit byte offsets decline: bf16 runs the implicit GEMM
+"""GPU parity of large tensors.  Beyond 2 GiB, which the kernels with 32-bit byte offsets decline: bf16 runs the implicit GEMM
 (conv_igemm.hip), fp32 one thread per output (conv_direct.hip).  One 3x3 block, Tune mode; three images are compared,
-one of them across the 2 GiB line, against the definition in fp64, and the others' input gradient is zero."""
+one of them across the 2 GiB line, against the definition in fp64, and the others' input gradient is zero.  Depthwise
+blocks beyond 1 GiB, which take several launches, by images or by bands of an image's rows: everything against fp64."""
 import pytest
 import torch
 import torch.nn.functional as F
@@ -77,3 +78,57 @@ def test_block_beyond_2_gib(dtype, cin, cout):
     close(db, r * s, "db")
     for n in range(1, 31):
         assert not dx[n].any(), n
+
+
+@pytest.mark.parametrize("n,h,w,s,p", [(5, 3101, 3003, 1, 1), (5, 3101, 3003, 2, 1),   # three images and two
+                                       (1, 6100, 6003, 1, 1), (1, 6100, 6003, 2, 1), (1, 6100, 6003, 1, 3),
+                                       (2, 6101, 6003, 2, 0)])                         # bands of one image
+def test_depthwise_block_beyond_1_gib(n, h, w, s, p):
+    g = torch.Generator(device="cuda").manual_seed(h + s)
+    c, bf = 16, torch.bfloat16
+    d = B.make_desc(n, c, h, w, c, K, K, s, p)
+    ho, wo = (h + 2 * p - K) // s + 1, (w + 2 * p - K) // s + 1
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    x, dz = normal(n, h, w, c).to(bf), normal(n, ho, wo, c).to(bf)
+    assert x.nbytes > 1 << 30 and (n == 5 or x[0].nbytes > 1 << 30)
+    wt = normal(c, K, K).to(bf)
+    gamma, var = torch.rand(c, generator=g, device="cuda") + 0.5, torch.rand(c, generator=g, device="cuda") + 0.5
+    b, beta, mean = normal(c), normal(c), normal(c)
+    nan = lambda like: torch.full_like(like, float("nan"))
+    z, dx, dw, wf = nan(dz), nan(x), nan(wt), torch.empty((K, K, c), dtype=bf, device="cuda")
+    db, dgamma, dbeta = nan(b), nan(gamma), nan(beta)
+    ws = [torch.empty(max(16, B.convbn_dw_workspace_bytes(d, B.MODE_TUNE, q)), dtype=torch.uint8, device="cuda")
+          for q in (B.PASS_FWD, B.PASS_BWD)]
+    ws[1].fill_(255)   # (NaNs: every slice has to be written)
+    print("forward", flush=True)
+    B.convbn_dw_tune_fwd(d, x, wt, b, gamma, beta, mean, var, z, wf, ws[0])
+    torch.cuda.synchronize()
+    print("backward", flush=True)
+    B.convbn_dw_tune_bwd(d, x, wt, b, gamma, mean, var, wf, dz, dx, dw, db, dgamma, dbeta, ws[1])
+    torch.cuda.synchronize()
+
+    def close(got, ref, what):
+        err = (got.double() - ref).abs().max() / ref.abs().max()
+        assert err <= TOL["bf16"], (what, err.item())
+
+    isd = 1.0 / (var.double() + d.eps).sqrt()
+    scale, wd = gamma.double() * isd, wt.double()
+    rdw, rdgamma, r = torch.zeros_like(wd), torch.zeros_like(scale), torch.zeros_like(scale)
+    for i in range(n):
+        xp, zd = F.pad(x[i].double(), (0, 0, p, p, p, p)), dz[i].double()
+        dxp, y = torch.zeros_like(xp), torch.zeros_like(zd)
+        for u in range(K):
+            for v in range(K):
+                at = (slice(u, u + (ho - 1) * s + 1, s), slice(v, v + (wo - 1) * s + 1, s))
+                y += xp[at] * wd[:, u, v]
+                dxp[at] += zd * (wd[:, u, v] * scale)
+                rdw[:, u, v] += (zd * xp[at]).sum((0, 1)) * scale
+        y += b.double() - mean.double()
+        close(z[i], y * scale + beta.double(), ("Z", i))
+        close(dx[i], dxp[p:p + h, p:p + w], ("dX", i))
+        rdgamma += (zd * y).sum((0, 1)) * isd
+        r += zd.sum((0, 1))
+    close(dw, rdw, "dW")
+    close(dgamma, rdgamma, "dgamma")
+    close(dbeta, r, "dbeta")
+    close(db, r * scale, "db")
