@@ -35,12 +35,15 @@ struct StemParams {
   int pcols;            // pixels per patch row (X3: a multiple of 4, with up to 3 leading pixels of alignment)
 };
 
-// Fetches go through buffer descriptors of one image (its byte offsets fit 30 bits): what is outside is an offset beyond it
-// and reads zeros, so that a fetch has no branch -- behind one, the compiler waited for each load on the spot: three to
-// seven trips to memory in a row per tile (weight gradient, 7 x 7 on 224 x 224, 32 images: 46.3 -> 42.8 us).
+// Fetches go through buffer descriptors of the rows that a tile needs (their byte offsets fit 30 bits, however large the image):
+// what is outside is an offset beyond them and reads zeros, so that a fetch has no branch -- behind one, the compiler waited for
+// each load on the spot: three to seven trips to memory in a row per tile (weight gradient, 7 x 7 on 224 x 224, 32 images: 46.3 ->
+// 42.8 us).
 constexpr unsigned NOWHERE = 1u << 30;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t image_rsrc(const bf16_t* base, int n, size_t elems) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base + (size_t)n * elems), 0, (int)(elems * 2), 0x00020000);
+// `count` rows from row `row` of all images' on.  Rows that are not the image's, in front of the tensor even, are never read: their
+// offsets are NOWHERE.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const bf16_t* base, long long row, int count, int row_elems) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base) + row * row_elems, 0, count * row_elems * 2, 0x00020000);
 }
 __device__ __forceinline__ uint2 ld8(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
@@ -100,14 +103,15 @@ __global__ __launch_bounds__(256) void stem_fprop_kernel(StemParams p) {
   auto fetch = [&](int tile) {
     const int ws = tile % p.ntw;
     const int row = tile / p.ntw;
-    const int ho = row % p.Ho, n = min(row / p.Ho, p.N - 1);   // (a tile past the last one reads nothing)
+    const int ho = row % p.Ho, n = row / p.Ho;   // (a tile past the last one reads nothing)
     const int wstart = patch_start(ws);
-    const __amdgpu_buffer_rsrc_t xr = image_rsrc(p.x, n, (size_t)p.H * p.W * (X3 ? 3 : 4));
+    const int top = ho * p.sh - p.ph;
+    const __amdgpu_buffer_rsrc_t xr = rows_rsrc(p.x, (long long)n * p.H + top, kH, p.W * (X3 ? 3 : 4));
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-      const int h = ho * p.sh + pi[k] - p.ph, w = wstart + pq[k];
+      const int h = top + pi[k], w = wstart + pq[k];
       const bool ok = tid + 256 * k < npatch && tile < p.ntiles && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
-      const unsigned off = ok ? (unsigned)(h * p.W + w) * (X3 ? 6u : 8u) : NOWHERE;
+      const unsigned off = ok ? (unsigned)(pi[k] * p.W + w) * (X3 ? 6u : 8u) : NOWHERE;
 #pragma unroll
       for (int j = 0; j < NLD; ++j) pv[k][j] = ld8(xr, off + 8 * j);
     }
@@ -380,18 +384,19 @@ __global__ __launch_bounds__(256, NCO == 4 ? 1 : 2) void stem_wgrad_kernel(StemW
   auto fetch = [&](int tile) {
     const int ws = tile % p.ntw;
     const int row = tile / p.ntw;
-    const int ho = row % p.Ho, n = min(row / p.Ho, p.N - 1);   // (a tile past the last one reads nothing)
+    const int ho = row % p.Ho, n = row / p.Ho;   // (a tile past the last one reads nothing)
     const int wstart = patch_start(ws);
-    const __amdgpu_buffer_rsrc_t xr = image_rsrc(p.x, n, (size_t)p.H * p.W * (X3 ? 3 : 4));
+    const int top = ho * p.sh - p.ph;
+    const __amdgpu_buffer_rsrc_t xr = rows_rsrc(p.x, (long long)n * p.H + top, p.kH, p.W * (X3 ? 3 : 4));
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-      const int h = ho * p.sh + pi[k] - p.ph, w = wstart + pq[k];
+      const int h = top + pi[k], w = wstart + pq[k];
       const bool ok = tid + 256 * k < npatch && tile < p.ntiles && (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
-      const unsigned off = ok ? (unsigned)(h * p.W + w) * (X3 ? 6u : 8u) : NOWHERE;
+      const unsigned off = ok ? (unsigned)(pi[k] * p.W + w) * (X3 ? 6u : 8u) : NOWHERE;
 #pragma unroll
       for (int j = 0; j < NLD; ++j) pv[k][j] = ld8(xr, off + 8 * j);
     }
-    const __amdgpu_buffer_rsrc_t zr = image_rsrc(p.dz, n, (size_t)p.Ho * p.Wo * p.Cout);
+    const __amdgpu_buffer_rsrc_t zr = rows_rsrc(p.dz, row, 1, p.Wo * p.Cout);
     // dZ rows of the tile's pixels (zeros past the end of the output row: such pixels then add nothing)
 #pragma unroll
     for (int k = 0; k < ZPT; ++k) {
@@ -399,7 +404,7 @@ __global__ __launch_bounds__(256, NCO == 4 ? 1 : 2) void stem_wgrad_kernel(StemW
       const int px = e / ZG, gq = e - px * ZG;
       const int wo = ws * TPX + px;
       const bool ok = tile < p.ntiles && wo < p.Wo && gq * 8 < p.Cout;
-      zv[k] = ld16(zr, ok ? ((unsigned)(ho * p.Wo + wo) * p.Cout + gq * 8) * 2u : NOWHERE);
+      zv[k] = ld16(zr, ok ? ((unsigned)wo * p.Cout + gq * 8) * 2u : NOWHERE);
     }
   };
   auto stash = [&](unsigned char* patch) {
@@ -524,6 +529,7 @@ StemWgPlan stem_wg_work_out(const Geom& g, StemWgParams* pp) {
   StemWgParams& p = *pp;
   p = StemWgParams{};
   if (g.kH > 8) return pl;   // two window rows per wave
+  if ((size_t)g.Wout * g.Cout * 2 >= NOWHERE) return pl;
   p.N = g.N; p.H = g.Hin; p.W = g.Win; p.Cin = g.Cin; p.Cout = g.Cout; p.kH = g.kH; p.kW = g.kW;
   p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw; p.Ho = g.Hout; p.Wo = g.Wout;
   p.ntw = ceil_div(g.Wout, TPX);
@@ -621,15 +627,15 @@ __global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p) {
   auto fetch = [&](int tile) {
     const int tr = tile % p.nbr;   // (down the columns: the rows that two tiles share come from the cache)
     const int t2 = tile / p.nbr;
-    const int tc = t2 % p.nbc, n = min(t2 / p.nbc, p.N - 1);   // (a tile past the last one reads nothing)
-    const __amdgpu_buffer_rsrc_t zr = image_rsrc(p.dz, n, (size_t)p.Ho * p.Wo * p.Cout);
+    const int tc = t2 % p.nbc, n = t2 / p.nbc;   // (a tile past the last one reads nothing)
     // patch row r holds dZ row a0 + Dh - (U - 1) + r, column likewise
     const int h0 = tr * p.TBR + p.Dh - (p.U - 1), w0 = tc * p.TBC + p.Dw - (p.V - 1);
+    const __amdgpu_buffer_rsrc_t zr = rows_rsrc(p.dz, (long long)n * p.Ho + h0, p.PR, p.Wo * p.Cout);
 #pragma unroll
     for (int k = 0; k < DG_PPT; ++k) {
       const int h = h0 + ipr[k], w = w0 + (ipc[k] & 0xffff), gq = ipc[k] >> 16;
       const bool ok = tid + 256 * k < nitems && tile < p.ntiles && (unsigned)h < (unsigned)p.Ho && (unsigned)w < (unsigned)p.Wo;
-      pv[k] = ld16(zr, ok ? ((unsigned)(h * p.Wo + w) * p.Cout + gq * 8) * 2u : NOWHERE);
+      pv[k] = ld16(zr, ok ? ((unsigned)(ipr[k] * p.Wo + w) * p.Cout + gq * 8) * 2u : NOWHERE);
     }
   };
   auto stash = [&](unsigned char* patch) {
@@ -801,6 +807,7 @@ StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
   p.nbr = ceil_div(brows, p.TBR);
   p.PR = p.TBR + p.U - 1; p.PC = p.TBC + p.V - 1;
   p.nbt = ceil_div(p.TBR * p.TBC, 16);
+  if ((size_t)p.PR * g.Wout * g.Cout * 2 >= NOWHERE) return pl;
   if (p.nbt > 4 * DG_NBT || p.PR * p.PC * (g.Cout / 8) > 256 * DG_PPT) return pl;
   p.ntiles = g.N * p.nbr * p.nbc;
   p.mTBC = (unsigned)((1ull << 32) / (unsigned)p.TBC + 1);
@@ -828,7 +835,7 @@ StemDgPlan stem_dg_plan(const Geom& g, StemDgParams* pp) {
 
 bool stem_shape(const Geom& g, int dtype) {
   return dtype == CONVBN_BF16 && g.Cin <= 4 && g.kW <= 8 && g.kH <= 16 && g.Cout % 8 == 0 && g.Cout <= 128 && g.sw <= 4 &&
-         (size_t)g.Hin * g.Win * 8 < NOWHERE && (size_t)g.Hout * g.Wout * g.Cout * 2 < NOWHERE;
+         (size_t)g.kH * g.Win * 8 < NOWHERE;
 }
 
 struct StemPlan { bool ok; bool x3; int nco; size_t lds; int grid; };

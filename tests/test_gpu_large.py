@@ -1,7 +1,8 @@
 """GPU parity of large tensors.  Beyond 2 GiB, which the kernels with 32-bit byte offsets decline: bf16 runs the implicit GEMM
 (conv_igemm.hip), fp32 one thread per output (conv_direct.hip).  One 3x3 block, Tune mode; three images are compared,
 one of them across the 2 GiB line, against the definition in fp64, and the others' input gradient is zero.  Depthwise
-blocks beyond 1 GiB, which take several launches, by images or by bands of an image's rows: everything against fp64."""
+blocks beyond 1 GiB, which take several launches, by images or by bands of an image's rows, and first layers whose one image
+is beyond 1 GiB on one side or the other: everything against fp64."""
 import pytest
 import torch
 import torch.nn.functional as F
@@ -128,6 +129,58 @@ def test_depthwise_block_beyond_1_gib(n, h, w, s, p):
         close(dx[i], dxp[p:p + h, p:p + w], ("dX", i))
         rdgamma += (zd * y).sum((0, 1)) * isd
         r += zd.sum((0, 1))
+    close(dw, rdw, "dW")
+    close(dgamma, rdgamma, "dgamma")
+    close(dbeta, r, "dbeta")
+    close(db, r * scale, "db")
+
+
+@pytest.mark.parametrize("h,w,cin,cout,k", [(6000, 6004, 3, 64, 7), (6001, 5999, 3, 64, 7),   # dZ; read as it is, and widened
+                                            (11700, 11600, 3, 32, 3)])                        # x
+def test_first_layer_beyond_1_gib(h, w, cin, cout, k):
+    g = torch.Generator(device="cuda").manual_seed(h)
+    bf, s, p = torch.bfloat16, 2, k // 2
+    d = B.make_desc(1, cin, h, w, cout, k, k, s, p)
+    ho, wo = (h + 2 * p - k) // s + 1, (w + 2 * p - k) // s + 1
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    x, dz = normal(1, h, w, cin).to(bf), normal(1, ho, wo, cout).to(bf)
+    assert dz.nbytes > 1 << 30 or h * w * 8 > 1 << 30
+    wt = (normal(cout, k, k, cin) * 0.2).to(bf)
+    gamma, var = torch.rand(cout, generator=g, device="cuda") + 0.5, torch.rand(cout, generator=g, device="cuda") + 0.5
+    b, beta, mean = normal(cout), normal(cout), normal(cout)
+    nan = lambda like: torch.full_like(like, float("nan"))
+    z, dx, dw, wf = nan(dz), nan(x), nan(wt), torch.empty((cin, k, k, cout), dtype=bf, device="cuda")
+    db, dgamma, dbeta = nan(b), nan(gamma), nan(beta)
+    ws = [torch.empty(max(16, B.convbn_workspace_bytes(d, B.MODE_TUNE, q)), dtype=torch.uint8, device="cuda")
+          for q in (B.PASS_FWD, B.PASS_BWD)]
+    print("forward", flush=True)
+    B.convbn_tune_fwd(d, x, wt, b, gamma, beta, mean, var, z, wf, ws[0])
+    torch.cuda.synchronize()
+    print("backward", flush=True)
+    B.convbn_tune_bwd(d, x, wt, b, gamma, mean, var, wf, dz, dx, dw, db, dgamma, dbeta, ws[1])
+    torch.cuda.synchronize()
+
+    def close(got, ref, what):
+        err = (got.double() - ref).abs().max() / ref.abs().max()
+        assert err <= TOL["bf16"], (what, err.item())
+
+    isd = 1.0 / (var.double() + d.eps).sqrt()
+    scale, wd = gamma.double() * isd, wt.double()
+    xp, zd = F.pad(x[0].double(), (0, 0, p, p, p, p)), dz[0].double().reshape(-1, cout)
+    dxp, y, rdw = torch.zeros_like(xp), torch.zeros_like(zd), torch.zeros_like(wd)
+    for i in range(k):
+        for j in range(k):
+            at = (slice(i, i + (ho - 1) * s + 1, s), slice(j, j + (wo - 1) * s + 1, s))
+            xt = xp[at].reshape(-1, cin)
+            y += xt @ wd[:, i, j].t().contiguous()
+            dxp[at] += (zd @ (wd[:, i, j] * scale[:, None])).reshape(ho, wo, cin)
+            for c in range(cin):
+                rdw[:, i, j, c] = (zd * xt[:, c:c + 1]).sum(0) * scale
+    y += b.double() - mean.double()
+    r = zd.sum(0)
+    rdgamma = (zd * y).sum(0) * isd
+    close(z.reshape(-1, cout), y * scale + beta.double(), "Z")
+    close(dx[0], dxp[p:p + h, p:p + w], "dX")
     close(dw, rdw, "dW")
     close(dgamma, rdgamma, "dgamma")
     close(dbeta, r, "dbeta")
