@@ -618,7 +618,7 @@ hipError_t launch_g3_fprop(const Geom& g, int groups, const void* x, const void*
   G3Params p = g3_params(g, groups, pl);
   p.a = (const bf16_t*)x; p.w = (const bf16_t*)W; p.out = (bf16_t*)z; p.bn = bn;
   p.Ha = g.Hin; p.Wa = g.Win; p.Ho = g.Hout; p.Wo = g.Wout; p.pa = g.ph; p.pb = g.pw;
-  const bool stream = streams_output((size_t)g.M * g.Cout * 2);
+  const bool stream = bn.gamma && streams_output((size_t)g.M * g.Cout * 2);   // (Eval's Y is read in the same call)
   if (g.sh == 1 && stream) hipLaunchKernelGGL((g3_conv_kernel<1, false, true>), dim3(p.nblk), dim3(256), 0, st, p);
   else if (g.sh == 1) hipLaunchKernelGGL((g3_conv_kernel<1, false, false>), dim3(p.nblk), dim3(256), 0, st, p);
   else if (stream) hipLaunchKernelGGL((g3_conv_kernel<2, false, true>), dim3(p.nblk), dim3(256), 0, st, p);

@@ -1075,7 +1075,7 @@ hipError_t launch_dw3_fprop(const Geom& g, const void* x, const void* W, const f
                             const float* beta, const float* mean, const float* var, void* z, void* w_folded,
                             hipStream_t st) {
   const Dw3Plan pl = dw3_fprop_plan(g);
-  const bool stream = streams_output((size_t)g.M * g.Cout * 2);
+  const bool stream = gamma && streams_output((size_t)g.M * g.Cout * 2);   // (Eval's Y is read in the same call)
   return dw3_each_launch(pl, g, [&](const Dw3Launch& l) {
     Dw3Params p = dw3_params(pl, g, l);
     p.W = (const bf16_t*)W; p.b = b; p.gamma = gamma; p.beta = beta; p.mean = mean; p.var = var;
