@@ -1325,10 +1325,13 @@ convbn_status convbn_grouped_eval_bwd(const convbn_desc* desc, int groups, const
   if (params) LAUNCH(launch_bn_bwd_finalize(g, w.bn_part, w.nparts, gamma, var, dgamma, dbeta, db, st));
   if (dx) {
     LAUNCH(launch_fold(gf, dt, W, nullptr, nullptr, nullptr, nullptr, nullptr, 1, nullptr, w.w_crsk, nullptr, st));
-    LAUNCH(launch_g_dgrad(g, groups, dt, w.dy, w.w_crsk, dx, st));
+    if (!params || !g3_pair_supported(g, groups, dt)) LAUNCH(launch_g_dgrad(g, groups, dt, w.dy, w.w_crsk, dx, st));
   }
   if (!params) return CONVBN_OK;
-  LAUNCH(launch_g_wgrad(g, groups, dt, x, w.dy, w.part, nullptr, st));
+  if (dx && g3_pair_supported(g, groups, dt))   // dX and dW in one launch, as in Tune
+    LAUNCH(launch_g3_pair(g, groups, x, w.dy, w.w_crsk, dx, w.part, nullptr, st));
+  else
+    LAUNCH(launch_g_wgrad(g, groups, dt, x, w.dy, w.part, nullptr, st));
   LAUNCH(launch_fold_back(gf, dt, w.part, w.slices, nullptr, 0, W, nullptr, nullptr, nullptr, nullptr, 1, dW, nullptr,
                           nullptr, nullptr, st));
   return CONVBN_OK;
