@@ -71,13 +71,22 @@ SWEEP = [(n, c, h, w, g, s, p) for n, c, h, w, g, s, p in [
     (2, 96, 8, 9, 3, 2, 2), (3, 256, 7, 49, 32, 2, 1), (9, 1024, 14, 13, 32, 2, 1), (60, 32, 30, 29, 4, 2, 0)]]
 
 
-@pytest.mark.parametrize("n,c,h,w,g,s,p", SWEEP)
+# 3x3 layers that the row-sweep kernels leave to the shared-tile ones: paddings above 2 (strided: the residue classes of the
+# input gradient among them)
+SHARED = [(2, 64, 9, 13, 16, 1, 3), (3, 96, 21, 30, 12, 1, 4), (2, 64, 9, 13, 16, 2, 3), (3, 256, 22, 31, 32, 2, 3),
+          (2, 1024, 7, 7, 32, 2, 4), (2, 128, 12, 15, 4, 2, 3)]
+
+
+@pytest.mark.parametrize("n,c,h,w,g,s,p", SWEEP + SHARED)
 def test_row_sweep(n, c, h, w, g, s, p):
     shape = BlockShape("g_sweep", n, c, h, w, c, 3, s, p, "bf16", 5 * c + h + w + p)
     inp = synth.make_grouped_inputs(shape, g, bias=(h + w) % 2 == 0)
     ref = oracle_grouped_block(inp)
     compare(_run(inp), ref, "bf16", keys=KEYS, tag=str((n, c, h, w, g, s, p)))
     compare(_run(inp, keep_folded=False), ref, "bf16", keys=KEYS[:-1], tag="refold")
+    compare(_run(inp, mode="eval"), ref, "bf16", keys=EVAL_KEYS, tag="eval")
+    compare(_run(inp, mode="eval", need_dx=False), ref, "bf16", keys=("Z", "dW", "db", "dgamma", "dbeta"), tag="eval, no dx")
+    compare(_run(inp, mode="eval", params=False), ref, "bf16", keys=("Z", "dX"), tag="eval, dx only")
 
 
 @pytest.mark.parametrize("s,p", [(1, 1), (2, 1), (1, 3)])
@@ -88,6 +97,36 @@ def test_refolding_reproduces_the_kept_weight(s, p):
     kept = _run(inp)["dX"]
     assert torch.equal(kept, _run(inp, keep_folded=False)["dX"])
     assert torch.equal(kept, _run(inp, keep_folded=False, params=False)["dX"])
+
+
+@pytest.mark.parametrize("sh,sw,ph,pw", [(1, 2, 1, 1), (2, 1, 0, 2), (1, 1, 2, 0), (2, 2, 0, 1), (1, 1, 4, 1)])
+def test_uneven_strides_and_paddings(sh, sw, ph, pw):
+    """Rows and columns strided or padded differently, against fp64 on the host."""
+    import torch.nn.functional as F
+    n, c, groups, h, w = 3, 64, 8, 13, 18
+    g = torch.Generator().manual_seed(17 * ph + pw + sh)
+    r = lambda *size: torch.randn(*size, generator=g).to(torch.bfloat16).double()
+    x, wt, gamma, var = r(n, c, h, w).requires_grad_(), r(c, c // groups, 3, 3).requires_grad_(), r(c), r(c).abs() + 0.5
+    beta, mean = r(c), r(c)
+    isd = 1.0 / (var + 1e-5).sqrt()
+    y = F.conv2d(x, wt, None, (sh, sw), (ph, pw), groups=groups)
+    z = (y - mean[:, None, None]) * (gamma * isd)[:, None, None] + beta[:, None, None]
+    dz = r(*z.shape)
+    z.backward(dz)
+    ref = dict(Z=z.detach(), dX=x.grad, dW=wt.grad, dbeta=dz.sum((0, 2, 3)),
+               dgamma=(dz * (y.detach() - mean[:, None, None])).sum((0, 2, 3)) * isd)
+    d = B.make_desc(n, c, h, w, c, 3, 3, sh, ph, stride_w=sw, pad_w=pw)
+    act, vec = (lambda t: B.act_to_device(t.detach().float(), torch.bfloat16, "cuda")), (lambda t: t.float().cuda())
+    xd, wd, dzd = act(x), B.weight_to_device(wt.detach().float(), torch.bfloat16, "cuda"), act(dz)
+    nan = lambda like: torch.full_like(like, float("nan"))
+    ws = [torch.empty(max(16, B.convbn_grouped_workspace_bytes(d, groups, B.MODE_TUNE, p)), dtype=torch.uint8, device="cuda")
+          for p in (B.PASS_FWD, B.PASS_BWD)]
+    zd, dx, dw, dga, dbe = (nan(t) for t in (dzd, xd, wd, vec(gamma), vec(beta)))
+    B.convbn_grouped_tune_fwd(d, groups, xd, wd, None, vec(gamma), vec(beta), vec(mean), vec(var), zd, None, ws[0])
+    B.convbn_grouped_tune_bwd(d, groups, xd, wd, None, vec(gamma), vec(mean), vec(var), None, dzd, dx, dw, None, dga, dbe, ws[1])
+    got = dict(Z=B.act_from_device(zd), dX=B.act_from_device(dx), dW=B.weight_from_device(dw), dgamma=dga.double().cpu(),
+               dbeta=dbe.double().cpu())
+    compare(got, {k: v.numpy() for k, v in ref.items()}, "bf16", keys=list(got), tag=str((sh, sw, ph, pw)))
 
 
 def test_rounding_does_not_depend_on_the_width():

@@ -2,7 +2,7 @@
 (conv_igemm.hip), fp32 one thread per output (conv_direct.hip).  One 3x3 block, Tune mode; three images are compared,
 one of them across the 2 GiB line, against the definition in fp64, and the others' input gradient is zero.  Depthwise
 blocks beyond 1 GiB, which take several launches, by images or by bands of an image's rows, and first layers whose one image
-is beyond 1 GiB on one side or the other: everything against fp64."""
+is beyond 1 GiB on one side or the other, and a grouped block there: everything against fp64."""
 import pytest
 import torch
 import torch.nn.functional as F
@@ -181,6 +181,62 @@ def test_first_layer_beyond_1_gib(h, w, cin, cout, k):
     rdgamma = (zd * y).sum(0) * isd
     close(z.reshape(-1, cout), y * scale + beta.double(), "Z")
     close(dx[0], dxp[p:p + h, p:p + w], "dX")
+    close(dw, rdw, "dW")
+    close(dgamma, rdgamma, "dgamma")
+    close(dbeta, r, "dbeta")
+    close(db, r * scale, "db")
+
+
+@pytest.mark.parametrize("s", [1, 2])
+def test_grouped_block_beyond_1_gib(s):
+    g = torch.Generator(device="cuda").manual_seed(s)
+    n, h, w, c, groups, p, bf = 2, 3000, 2900, 32, 8, 1, torch.bfloat16
+    cg = c // groups
+    d = B.make_desc(n, c, h, w, c, K, K, s, p)
+    ho, wo = (h + 2 * p - K) // s + 1, (w + 2 * p - K) // s + 1
+    normal = lambda *size: torch.randn(*size, generator=g, device="cuda")
+    x, dz = normal(n, h, w, c).to(bf), normal(n, ho, wo, c).to(bf)
+    assert x.nbytes > 1 << 30
+    wt = (normal(c, K, K, cg) * 0.3).to(bf)
+    gamma, var = torch.rand(c, generator=g, device="cuda") + 0.5, torch.rand(c, generator=g, device="cuda") + 0.5
+    b, beta, mean = normal(c), normal(c), normal(c)
+    nan = lambda like: torch.full_like(like, float("nan"))
+    z, dx, dw, wf = nan(dz), nan(x), nan(wt), torch.empty((cg, K, K, c), dtype=bf, device="cuda")
+    db, dgamma, dbeta = nan(b), nan(gamma), nan(beta)
+    ws = [torch.empty(max(16, B.convbn_grouped_workspace_bytes(d, groups, B.MODE_TUNE, q)), dtype=torch.uint8, device="cuda")
+          for q in (B.PASS_FWD, B.PASS_BWD)]
+    print("forward", flush=True)
+    B.convbn_grouped_tune_fwd(d, groups, x, wt, b, gamma, beta, mean, var, z, wf, ws[0])
+    torch.cuda.synchronize()
+    print("backward", flush=True)
+    B.convbn_grouped_tune_bwd(d, groups, x, wt, b, gamma, mean, var, wf, dz, dx, dw, db, dgamma, dbeta, ws[1])
+    torch.cuda.synchronize()
+
+    def close(got, ref, what):
+        err = (got.double() - ref).abs().max() / ref.abs().max()
+        assert err <= TOL["bf16"], (what, err.item())
+
+    isd = 1.0 / (var.double() + d.eps).sqrt()
+    scale, wd = gamma.double() * isd, wt.double()
+    rdw, rdgamma, r = torch.zeros_like(wd), torch.zeros_like(scale), torch.zeros_like(scale)
+    for m in range(n):
+        xp, zd = F.pad(x[m].double(), (0, 0, p, p, p, p)), dz[m].double()
+        dxp, y = torch.zeros_like(xp), torch.zeros_like(zd)
+        for i in range(K):
+            for j in range(K):
+                rows, cols = slice(i, i + (ho - 1) * s + 1, s), slice(j, j + (wo - 1) * s + 1, s)
+                for k in range(groups):
+                    ch = slice(k * cg, (k + 1) * cg)
+                    xt = xp[rows, cols, ch]
+                    for o in range(k * cg, (k + 1) * cg):
+                        y[..., o] += (xt * wd[o, i, j]).sum(-1)
+                        dxp[rows, cols, ch] += zd[..., o:o + 1] * (wd[o, i, j] * scale[o])
+                        rdw[o, i, j] += (zd[..., o:o + 1] * xt).sum((0, 1)) * scale[o]
+        y += b.double() - mean.double()
+        close(z[m], y * scale + beta.double(), ("Z", m))
+        close(dx[m], dxp[p:p + h, p:p + w], ("dX", m))
+        rdgamma += (zd * y).sum((0, 1)) * isd
+        r += zd.sum((0, 1))
     close(dw, rdw, "dW")
     close(dgamma, rdgamma, "dgamma")
     close(dbeta, r, "dbeta")
