@@ -327,6 +327,8 @@ int gv_wgrad_slices(const Geom& g, int groups) {
 //   * The input gradient of a stride-1 block is the same kernel on dZ with the taps reversed and the weight read
 //     in its other order; that of a strided block runs the residue classes of input positions side by side
 //     (blockIdx.y), each with the taps that class has and a strided store.
+// conv_grouped3.hip takes the 3x3 windows of groups of 4 to 32; what is left of them here are paddings above 2, strides that
+// differ, and tensors of 1 GiB and more, with 1x1 windows and groups of 64.
 // n / d for 0 <= n < 65536 and 1 <= d < 65536 with m = 2^32 / d + 1 (exact: the error n (m d - 2^32) stays below 2^32)
 __device__ __forceinline__ int g_div(int n, unsigned m, int d) { return d == 1 ? n : (int)__umulhi((unsigned)n, m); }
 inline unsigned g_magic(int d) { return (unsigned)((1ull << 32) / (unsigned)d + 1); }

@@ -8,10 +8,11 @@
 // window columns x four channels -- are then 16 contiguous bytes of the input row, for every output pixel.
 // So no im2col is ever materialised: the operand fragments are read straight from the raw input patch in
 // LDS (output pixel wo, window columns j..j+1 -> patch bytes (wo sw + j) 8 ..), consecutive lanes 8 sw bytes
-// apart.  The weights (Cout x kH x 8 x 4, zero-padded, packed by each workgroup for itself) stay resident in LDS, for 7-row
-// windows on RGB images in registers; a workgroup is persistent and walks a run of tiles of 128 consecutive pixels of one output
-// row: patch in (kH rows x (127 sw + 8) pixels), kH x 2 MFMA k-steps, s, b' and a ReLU in the epilogue, 16-byte stores out (through
-// LDS; 7-row windows straight from the accumulators, with the next patch in a second buffer).
+// apart.  The weights (Cout x kH x 8 x 4, zero-padded, packed by each workgroup for itself) stay resident in LDS; a workgroup
+// is persistent and walks a run of tiles of 128 consecutive pixels of one output row: patch in (kH rows x (127 sw + 8) pixels),
+// kH x 2 MFMA k-steps, s, b' and a ReLU in the epilogue, 16-byte stores out through LDS.  7-row windows on RGB images with rows of
+// whole groups of four pixels and 33 to 64 output channels keep the weights in registers, store straight from the accumulators
+// and hold the next patch in a second buffer.
 #include "common.h"
 
 namespace convbn {
@@ -541,7 +542,7 @@ StemWgPlan stem_wg_work_out(const Geom& g, StemWgParams* pp) {
   if (pl.nco != 1 && pl.nco != 2 && pl.nco != 4) return pl;
   if (g.kH * (p.pcols / (x3 ? 4 : 1)) > 256 * ppt(x3)) return pl;
   p.zpitch = 32 * pl.nco * 2 + 16;
-  pl.known = x3 && pl.nco == 2 && g.kH == 7 && g.sw == 2;   // the usual 7x7 / stride-2 RGB stem with 64 channels
+  pl.known = x3 && pl.nco == 2 && g.kH == 7 && g.sw == 2;   // the usual 7x7 / stride-2 RGB stem, 33 to 64 channels
   p.zt = (int)align_up((size_t)(g.kH + (pl.known ? 1 : 0)) * p.prow, 16);
   p.buf = p.zt + TPX * p.zpitch;
   p.nbuf = 2 * p.buf <= 80 * 1024 ? 2 : 1;   // (two workgroups share a compute unit's 160 KB)
@@ -963,7 +964,7 @@ hipError_t launch_fprop_stem(const Geom& g, const void* x, const void* w, const 
                                           64 * 1024); e != hipSuccess) return e;                                   \
     hipLaunchKernelGGL((stem_fprop_kernel<NC, KHV, X3V>), dim3(pl.grid), dim3(256), pl.lds, st, p);                \
   } while (0)
-  if (pl.nco == 2 && g.kH == 7 && pl.x3) STEM(2, 7, true);   // the usual 7x7 RGB stem with 64 channels: rows unrolled
+  if (pl.nco == 2 && g.kH == 7 && pl.x3) STEM(2, 7, true);   // the usual 7x7 RGB stem, 33 to 64 channels: rows unrolled
   else if (pl.x3) { if (pl.nco == 1) STEM(1, 0, true); else if (pl.nco == 2) STEM(2, 0, true); else STEM(4, 0, true); }
   else if (pl.nco == 1) STEM(1, 0, false);
   else if (pl.nco == 2) STEM(2, 0, false);

@@ -126,8 +126,8 @@ __global__ __launch_bounds__(256) void dw_dgrad_kernel(const T* __restrict__ dz,
 // and weight gradient are one sweep -- dx and dw' both need dZ, and the pixel that owns a dx element owns its x too, so
 // the halo is one tensor's --, and the filter is folded by the threads that use it: a forward pass is one launch, a
 // backward pass two.  Before (a thread per four outputs of one column, all loads of its patch up front, each pass and
-// the fold a launch of its own): 144 channels at 56 x 56, 32 images, 80.7 us a pass; now 38.7 (forward 14.4, backward 20.6,
-// fold-back 4.8; 144 MB).  4 x 2 and two steps ahead: three rows ahead, 256 threads a workgroup and 16-byte accesses were no
+// the fold a launch of its own): 144 channels at 56 x 56, 32 images, 80.1 us a pass; now 38.2 (forward 14.4, backward 20.6,
+// fold-back 4.8 in a trace that adds launches' ends; 144 MB).  4 x 2 and two steps ahead: three rows ahead, 256 threads a workgroup and 16-byte accesses were no
 // faster; non-temporal loads cost the column overlap its L1 hits (54.6).  Stores: streams_output and STREAM_GRAD in common.h.
 // Out-of-image loads and stores are offsets beyond the buffer, which read zeros and are dropped.
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
