@@ -49,7 +49,7 @@ convbn_status make_geom(const convbn_desc* d, Geom* g) {
     return fail(CONVBN_ERR_UNSUPPORTED, "act %d: unknown activation bits", d->act);
   if (((d->act & CONVBN_ACT_ADD_OUT) && !d->add_out) || ((d->act & CONVBN_ACT_ADD_IN) && !d->add_in))
     return fail(CONVBN_ERR_NULL, "act %d asks for an addend that the descriptor does not give", d->act);
-  g->act = d->act; g->post_relu = 0; g->post_mask = nullptr; g->post_add = nullptr;
+  g->act = d->act; g->post_relu = 0; g->post_mask = nullptr; g->post_add = nullptr; g->fold_back = nullptr;
   g->add_out = (d->act & CONVBN_ACT_ADD_OUT) ? d->add_out : nullptr;
   g->add_in = (d->act & CONVBN_ACT_ADD_IN) ? d->add_in : nullptr;
   g->N = d->N; g->Cin = d->Cin; g->Hin = d->Hin; g->Win = d->Win;
@@ -209,6 +209,10 @@ EvalBwdWs carve_eval_bwd(const Geom& g, int dtype, void* ws) {
   return r;
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
 bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 #define REQUIRE_PTR(p)                                                            \
@@ -397,6 +401,15 @@ hipError_t run_dgrad(const Geom& g, int dtype, const void* dz, const void* w_crs
   TRY(dgrad_any(q, dtype, dz, wp, nullptr, dxp, reinterpret_cast<float*>(s), st));
   TRY(launch_repitch(2, (size_t)g.Min, q.Cin, g.Cin, dxp, dx, st));
   return post_op_pass(g, dtype, dx, (size_t)g.Min * g.Cin, st);
+}
+// Whether run_dgrad()'s launch takes a fold-back along (g.fold_back): the kernels that do.
+bool dgrad_folds_back_aside(const Geom& g, int dtype) {
+  if (dtype != CONVBN_BF16) return false;
+  if (needs_cin_pad(g, dtype))
+    return stem_dgrad_supported(g, dtype) && stem_wgrad_supported(g, dtype) && stem_dgrad_folds_back_aside(g);
+  if (g.K % 4) return false;
+  if (pw_dgrad_supported(g, dtype)) return gm_supported(g.M, g.Cout, g.Cin);
+  return !rw_dgrad_supported(g, dtype) && (st_dgrad_supported(g, dtype) || win_dgrad_taken(g, dtype));
 }
 // dw' partials and, when r_part != nullptr, the partial per-channel sums of dz.
 hipError_t wgrad_any(const Geom& g, int dtype, const void* x, const void* dz, float* part, float* r_part,
@@ -799,6 +812,21 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
       const int ns = win_pair_splits(g);
       LAUNCH(launch_win_pair(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       LAUNCH(launch_fold_back(g, dt, w.dwf_part, ns, w.r_part, ns, W, b, gamma, mean, var, 0, dW, db, dgamma, dbeta, st));
+      return CONVBN_OK;
+    }
+    // the weight gradient first: the fold-back then is no launch of its own (unless it writes where the input gradient reads)
+    auto reads = [&](const void* p, size_t bytes) {
+      const size_t e = esize(dt), ax = (size_t)g.Min * g.Cin * e;
+      return overlap(p, bytes, dz, (size_t)g.M * g.Cout * e) || overlap(p, bytes, wt, (size_t)g.Cout * g.K * e) ||
+             overlap(p, bytes, g.post_mask, ax) || overlap(p, bytes, g.post_add, ax);
+    };
+    const size_t vec = (size_t)g.Cout * 4;
+    if (params && dgrad_folds_back_aside(g, dt) && !reads(dW, (size_t)g.Cout * g.K * esize(dt)) && !reads(dgamma, vec) &&
+        !reads(dbeta, vec) && !reads(db, vec)) {
+      LAUNCH(run_wgrad(g, dt, x, dz, w.dwf_part, w.r_part, w.wgrad_scratch, st));
+      const FoldBackArgs fb{w.dwf_part, w.r_part, W, b, gamma, mean, var, dW, db, dgamma, dbeta, g.eps, w.nsplit, w.nrpart, 0, g.Cout, g.K, 0};
+      g.fold_back = &fb;
+      LAUNCH(run_dgrad(g, dt, dz, wt, dx, w.conv_scratch, st));
       return CONVBN_OK;
     }
     LAUNCH(run_dgrad(g, dt, dz, wt, dx, w.conv_scratch, st));   // dX = w'_rot (*) dZ

@@ -58,9 +58,22 @@ struct Geom {
   int post_relu;
   const void* post_mask;
   const void* post_add;
+  const struct FoldBackArgs* fold_back;   // an input gradient: the fold-back its launch takes along (fold_tile.h), or null
   const void* add_out;   // the descriptor's addends (CONVBN_ACT_ADD_OUT / _IN), null where the bit is not set
   const void* add_in;
 };
+
+// What the fold-back of a block reads and writes (fold_tile.h): dW, dgamma, dbeta, db from the nsplit partial copies of dw' and
+// the nrpart partial sums of dZ; identity: dW is the sum of the copies, nothing else is written.
+struct FoldBackArgs {
+  const float* part; const float* r_part; const void* W; const float* b; const float* gamma; const float* mean; const float* var;
+  void* dW; float* db; float* dgamma; float* dbeta;
+  float eps;
+  int nsplit, nrpart, identity, Cout, K;
+  int per;   // threads of a channel, where it rides in another launch
+  static constexpr bool BACK = true;
+};
+struct FoldSide { static constexpr bool BACK = false; };   // (a launch that may fold on the side, from its BnEpilogue)
 
 // The same on 8 packed bf16 values: max(., 0), and zero where the 8 packed bf16 values of m4 are <= 0.
 __device__ __forceinline__ uint4 relu8(uint4 v) {
@@ -387,6 +400,7 @@ bool stem_wgrad_supported(const Geom& g, int dtype);
 int stem_wgrad_slices(const Geom& g);             // fp32 partial copies of dw' (and of r) the kernel writes
 hipError_t launch_wgrad_stem(const Geom& g, const void* x, const void* dz, float* part, float* r_part, hipStream_t st);
 bool stem_dgrad_supported(const Geom& g, int dtype);
+bool stem_dgrad_folds_back_aside(const Geom& g);   // (where that and stem_wgrad_supported hold)
 hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, void* dx, hipStream_t st);
 size_t stem_input_copy_bytes(const Geom& g);      // scratch for a 4-channel copy of the input (0: read as it is)
 // bn != nullptr: w is the UNFOLDED weight and the epilogue applies s and b' (w' left on the side); relu: max(z, 0)
@@ -420,7 +434,8 @@ hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, co
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st);
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
                      void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd = nullptr,
-                     bool grad = false);   // grad: an input gradient
+                     bool grad = false,
+                     const FoldBackArgs* fb = nullptr);   // grad: an input gradient
 bool pw_fprop_supported(const Geom& g, int dtype);
 bool pw_fprop_scaled_supported(const Geom& g, int dtype);     // ... with a BnEpilogue
 bool pw_fprop_folds_aside(const Geom& g, int dtype);          // ... whose launch also leaves w_folded_out

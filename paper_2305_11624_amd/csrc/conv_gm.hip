@@ -48,7 +48,7 @@ struct GmParams {
   int ntr;               // channel tiles
   int nchunks;
   int order;             // of the tiles, see the kernel
-  int nconv;             // the product's workgroups, those behind it fold
+  int nconv;             // the product's workgroups, those behind it fold, or fold back
   // A pointwise layer with a stride (a downsampling shortcut) is the same product over the output pixels; gather: the
   // activation row of output pixel m = (n, ho, wo) is pixel (n, ho sh, wo sw) of an [N][Hs][Ws] tensor.
   int gather;
@@ -106,9 +106,10 @@ struct GmCfg {
   static_assert(NWAVES * 32 * CW * 2 <= STAGE, "the epilogue stages every wave's outputs (32 pixels at a time) in the first stage");
 };
 
-// STREAM: non-temporal stores, see launch_gm
-template <int TM, int RES, int TN, int NS, bool STREAM>
-__global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
+// STREAM: non-temporal stores, see launch_gm.  Side: what the workgroups behind the product's do, FoldBackArgs (an input gradient) or
+// FoldSide (the rest)
+template <int TM, int RES, int TN, int NS, bool STREAM, class Side>
+__global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p, Side side) {
   using Cfg = GmCfg<TM, RES, TN, NS>;
   constexpr bool ONE = Cfg::ONE;
   constexpr int CW = Cfg::CW;
@@ -119,7 +120,8 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* biasl = reinterpret_cast<float*>(smem + Cfg::OFF_BIAS);
   if ((int)blockIdx.x >= p.nconv) {
-    fold_side(p.bn, p.wgt, (int)blockIdx.x - p.nconv, smem);
+    if constexpr (Side::BACK) fold_back_side<64 * NWAVES>(side, (int)blockIdx.x - p.nconv, smem);
+    else fold_side(p.bn, p.wgt, (int)blockIdx.x - p.nconv, smem);
     return;
   }
 
@@ -367,19 +369,21 @@ GmPlan choose_plan(int M, int C, int R) {
   return none;
 }
 
-template <int TM, int RES, int TN, int NS, bool STREAM>
-hipError_t launch_inst(GmParams p, hipStream_t st) {
+template <int TM, int RES, int TN, int NS, bool STREAM, class Side>
+hipError_t launch_inst(GmParams p, Side side, hipStream_t st) {
   static LdsLimitOnce lds_once;
   constexpr int lds = GmCfg<TM, RES, TN, NS>::LDS_BYTES;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_gm_kernel<TM, RES, TN, NS, STREAM>), lds);
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_gm_kernel<TM, RES, TN, NS, STREAM, Side>), lds);
       e != hipSuccess) return e;
-  static_assert(2 * FOLD_TILE_BYTES <= lds, "two tiles of the fold on the side");
+  static_assert(2 * FOLD_TILE_BYTES <= lds && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= lds, "what folds on the side");
   const int npt = ceil_div(p.M, TM);
   const size_t out_bytes = (size_t)p.M * p.R * 2;
   p.order = out_bytes > LONG_OUTPUT || out_bytes + p.act_bytes > LONG_STREAM ? ORDER_TOGETHER
             : p.wgt_bytes > p.act_bytes ? ORDER_CHANNEL_RUNS : ORDER_PIXEL_RUNS;
   p.nconv = p.order == ORDER_TOGETHER ? ceil_div(npt, 8) * 8 * p.ntr : ceil_div(npt * p.ntr, 8) * 8;
-  hipLaunchKernelGGL((conv_gm_kernel<TM, RES, TN, NS, STREAM>), dim3(p.nconv + fold_side_blocks(p.bn)), dim3(64 * NWAVES), lds, st, p);
+  int nside;
+  if constexpr (Side::BACK) nside = fold_back_side_blocks(side, 64 * NWAVES); else nside = fold_side_blocks(p.bn);
+  hipLaunchKernelGGL((conv_gm_kernel<TM, RES, TN, NS, STREAM, Side>), dim3(p.nconv + nside), dim3(64 * NWAVES), lds, st, p, side);
   return hipGetLastError();
 }
 
@@ -388,7 +392,8 @@ hipError_t launch_inst(GmParams p, hipStream_t st) {
 bool gm_supported(int M, int C, int R) { return choose_plan(M, C, R).tm != 0; }
 
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
-                     void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd, bool grad) {
+                     void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd, bool grad,
+                     const FoldBackArgs* fb) {
   const GmPlan pl = choose_plan(M, C, R);
   if (pl.tm == 0) return hipErrorInvalidValue;
   GmParams p{};
@@ -416,13 +421,15 @@ hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, cons
   // Forward outputs stay in the caches: the backbone's forward pass, 32 images, takes 861 us with them there, 919 without.
   const bool stream = grad && (size_t)M * R * 2 >= ((size_t)16 << 20);
   p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
-#define GM_CASE(TM_, RES_, TN_, NS_) \
-  if (pl.tm == TM_ && pl.res == RES_ && pl.tn == TN_ && pl.ns == NS_) \
-    return stream ? launch_inst<TM_, RES_, TN_, NS_, true>(p, st) : launch_inst<TM_, RES_, TN_, NS_, false>(p, st);
+#define GM_CASE(TM_, RES_, TN_, NS_)                                                                                    \
+  if (pl.tm == TM_ && pl.res == RES_ && pl.tn == TN_ && pl.ns == NS_) {                                                 \
+    if (fb) return stream ? launch_inst<TM_, RES_, TN_, NS_, true>(p, *fb, st) : launch_inst<TM_, RES_, TN_, NS_, false>(p, *fb, st); \
+    return stream ? launch_inst<TM_, RES_, TN_, NS_, true>(p, FoldSide{}, st) : launch_inst<TM_, RES_, TN_, NS_, false>(p, FoldSide{}, st); \
+  }
   GM_CASE(128, 0, 128, 2) GM_CASE(256, 0, 128, 3) GM_CASE(128, 1, 128, 3) GM_CASE(128, 2, 128, 3)
   GM_CASE(128, 0, 64, 3) GM_CASE(128, 1, 64, 3) GM_CASE(128, 2, 64, 3)
   if (pl.tm == 128 && pl.res == 0 && pl.tn == 128 && pl.ns == 3)   // (under 2 MIN_TILES tiles: never 16 MB)
-    return launch_inst<128, 0, 128, 3, false>(p, st);
+    return fb ? launch_inst<128, 0, 128, 3, false>(p, *fb, st) : launch_inst<128, 0, 128, 3, false>(p, FoldSide{}, st);
 #undef GM_CASE
   return hipErrorInvalidValue;
 }

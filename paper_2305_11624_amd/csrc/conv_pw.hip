@@ -503,7 +503,8 @@ hipError_t launch_dgrad_pw(const Geom& g, const void* dz, const void* w_crsk, co
                            hipStream_t st) {
   if (gm_supported(g.M, g.Cout, g.Cin))
     return launch_gm(g.M, g.Cout, g.Cin, dz, w_crsk, bias, nullptr, dx, g.post_relu, g.post_mask, g.post_add, st, nullptr,
-                     bias == nullptr);   // (with a bias: a transposed convolution, forward)
+                     bias == nullptr,   // (with a bias: a transposed convolution, forward)
+                     g.fold_back);
   PwParams p = dgrad_params(g);
   const PwPlan pl = make_plan(p);
   if (!pl.ok) return hipErrorInvalidValue;

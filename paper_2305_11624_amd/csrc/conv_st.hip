@@ -31,6 +31,7 @@
 // window tile; operands of step s + 1 are read while step s multiplies.  Barriers open groups of G steps; the
 // constants and what they must satisfy are stated at the tile shapes below.
 #include "common.h"
+#include "fold_tile.h"
 
 #include <mutex>
 
@@ -105,6 +106,7 @@ struct StParams {
   const bf16_t* wgt;
   const float* bias;
   BnEpilogue bn;                  // bn.gamma != null: the weight is unfolded, the epilogue applies s and b' (bias unused)
+  int tiles;                      // the convolution's workgroups
   bf16_t* out;
   int relu;                       // the output leaves as max(., 0)
   const bf16_t* mask;             // not null: laid out like out, the output is zeroed where this is <= 0
@@ -162,8 +164,8 @@ __device__ unsigned long long st_trace[1024 * 128];
 #define STAMP(i) do {} while (0)
 #endif
 
-template <int KH, int KW, class S>
-__global__ __launch_bounds__(64 * NWAVES) void conv_st_kernel(StParams p) {
+template <int KH, int KW, class S, class Side>
+__global__ __launch_bounds__(64 * NWAVES) void conv_st_kernel(StParams p, Side side) {
   constexpr int TAPS = KH * KW;
   constexpr int TP = S::TP, TRC = S::TRC, NPS = S::NPS, NCS = S::NCS, WPW = S::WPW, HUW = S::HUW, HBUF = S::HBUF,
                 WSLAB = S::WSLAB, OFF_H = S::OFF_H, G = S::G, NBUF = S::NBUF, DIST = S::DIST;
@@ -175,6 +177,11 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_st_kernel(StParams p) {
   unsigned char* wbuf = smem + OFF_W;
   unsigned char* halo = smem + OFF_H;
 
+  if constexpr (Side::BACK)
+    if ((int)blockIdx.x >= p.tiles) {
+      fold_back_side<64 * NWAVES>(side, (int)blockIdx.x - p.tiles, smem);
+      return;
+    }
   const int tid = threadIdx.x, lane = tid & 63;
   STAMP(0);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -302,7 +309,7 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_st_kernel(StParams p) {
     for (int i = 0; i < NCS; ++i) fa[buf][i] = *reinterpret_cast<const bf16x8*>(wbuf + slot * WSLAB + aoff + i * 4096);
   };
 
-  if (p.bn.gamma && p.bn.w_folded_out) emit_folded_slice(p.bn, p.wgt, blockIdx.x, gridDim.x);   // while the first copies are in flight
+  if (p.bn.gamma && p.bn.w_folded_out) emit_folded_slice(p.bn, p.wgt, blockIdx.x, p.tiles);   // while the first copies are in flight
   STAMP(1);
   wait_vm_upto((DIST - G - 1) * WPW);   // as at every later group: the latest DIST - G - 1 slabs may still be on their way
   block_barrier();
@@ -520,22 +527,27 @@ bool dgrad_params(const Geom& g, StParams* p) {
   return k.ok;
 }
 
-template <class S>
-hipError_t launch_shape(const StParams& p, hipStream_t st) {
+template <class S, class Side>
+hipError_t launch_shape(StParams p, Side side, hipStream_t st) {
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_st_kernel<3, 3, S>),
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_st_kernel<3, 3, S, Side>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
   });
   if (attr_err != hipSuccess) return attr_err;
-  const int tiles = ceil_div(p.M, S::TP) * p.ntr;
-  hipLaunchKernelGGL((conv_st_kernel<3, 3, S>), dim3(tiles), dim3(64 * NWAVES), S::LDS_BYTES, st, p);
+  static_assert(FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= S::LDS_BYTES, "the fold-back on the side");
+  p.tiles = ceil_div(p.M, S::TP) * p.ntr;
+  int nside = 0;
+  if constexpr (Side::BACK) nside = fold_back_side_blocks(side, 64 * NWAVES);
+  hipLaunchKernelGGL((conv_st_kernel<3, 3, S, Side>), dim3(p.tiles + nside), dim3(64 * NWAVES), S::LDS_BYTES, st, p, side);
   return hipGetLastError();
 }
 
-hipError_t launch(const StParams& p, hipStream_t st) {
-  return p.wide == 1 ? launch_shape<Wide>(p, st) : (p.wide == 2 ? launch_shape<Tall>(p, st) : launch_shape<Narrow>(p, st));
+template <class Side>
+hipError_t launch(const StParams& p, const Side& side, hipStream_t st) {
+  return p.wide == 1 ? launch_shape<Wide>(p, side, st)
+                     : (p.wide == 2 ? launch_shape<Tall>(p, side, st) : launch_shape<Narrow>(p, side, st));
 }
 
 }  // namespace
@@ -555,7 +567,7 @@ hipError_t launch_fprop_st(const Geom& g, const void* x, const void* w_krsc, con
   if (bn) p.bn = *bn;
   p.act = (const bf16_t*)x; p.wgt = (const bf16_t*)w_krsc; p.bias = bias; p.out = (bf16_t*)z;
   p.relu = g.post_relu; p.mask = (const bf16_t*)g.post_mask; p.add = (const bf16_t*)g.post_add;
-  return launch(p, st);
+  return launch(p, FoldSide{}, st);
 }
 hipError_t launch_dgrad_st(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx,
                            hipStream_t st) {
@@ -563,7 +575,7 @@ hipError_t launch_dgrad_st(const Geom& g, const void* dz, const void* w_crsk, co
   if (!dgrad_params(g, &p)) return hipErrorInvalidValue;
   p.act = (const bf16_t*)dz; p.wgt = (const bf16_t*)w_crsk; p.bias = bias; p.out = (bf16_t*)dx;
   p.relu = g.post_relu; p.mask = (const bf16_t*)g.post_mask; p.add = (const bf16_t*)g.post_add;
-  return launch(p, st);
+  return g.fold_back ? launch(p, *g.fold_back, st) : launch(p, FoldSide{}, st);
 }
 
 }  // namespace convbn

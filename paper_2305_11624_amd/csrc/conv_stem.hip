@@ -14,6 +14,9 @@
 // whole groups of four pixels and 33 to 64 output channels keep the weights in registers, store straight from the accumulators
 // and hold the next patch in a second buffer.
 #include "common.h"
+#include "fold_tile.h"
+
+#include <algorithm>
 
 namespace convbn {
 
@@ -56,8 +59,8 @@ __device__ __forceinline__ uint4 ld16(__amdgpu_buffer_rsrc_t r, unsigned off) {
 // A workgroup's tiles: a run of neighbours, which share input rows, and neighbouring runs on one XCD (workgroup ids are dealt
 // round-robin over the 8 of them) with its L2.
 struct TileRun { int first, end; };
-__device__ __forceinline__ TileRun tile_run(int ntiles) {
-  const int n = gridDim.x, b = blockIdx.x, full = n & ~7;
+__device__ __forceinline__ TileRun tile_run(int ntiles, int n = gridDim.x) {   // n: the workgroups that share them
+  const int b = blockIdx.x, full = n & ~7;
   const int lb = b < full ? (b & 7) * (full >> 3) + (b >> 3) : b;
   return TileRun{(int)((long long)ntiles * lb / n), (int)((long long)ntiles * (lb + 1) / n)};
 }
@@ -599,14 +602,20 @@ struct StemDgParams {
   int nbt;              // 16-block groups per tile
   int nbuf;             // patches in LDS
   unsigned mTBC, mPC;   // multipliers for n / TBC, n / PC (n < 65536)
+  int nwg;              // the input gradient's workgroups, those behind them fold back
 };
 
 __device__ __forceinline__ int dg_div(int n, unsigned m, int d) { return d == 1 ? n : (int)__umulhi((unsigned)n, m); }
 
 // UU, VV, KS: the dZ neighbourhood and Cout / 32 at compile time (0: taken from the parameters)
-template <int UU, int VV, int KS>
-__global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p) {
+template <int UU, int VV, int KS, class Side>
+__global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p, Side side) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if constexpr (Side::BACK)
+    if ((int)blockIdx.x >= p.nwg) {
+      fold_back_side<256, ROW_ANY>(side, (int)blockIdx.x - p.nwg, smem);
+      return;
+    }
   unsigned char* wl = smem;                                         // [16][wpitch] (UU == 0)
   unsigned char* cur = UU > 0 ? smem : wl + 16 * p.wpitch;          // two patches (one, where two do not fit): [PR][PC][pitch]
   unsigned char* nxt = cur + (p.nbuf - 1) * p.PR * p.PC * p.pitch;
@@ -648,7 +657,7 @@ __global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p) {
 
   const int nph = p.sh * p.sw;                 // phases: rows 4 phase + c of the product
   const int ksteps = p.Cout / 32;
-  const TileRun run = tile_run(p.ntiles);
+  const TileRun run = tile_run(p.ntiles, p.nwg);
   fetch(run.first);
   // ---- resident weight (behind the first patch's requests): Wt[(phase, c)][(u, v, co)], phase (qh, qw) reaching dZ row
   // a + dh(qh) - t through window row i0(qh) + sh t, i.e. u = Dh - dh(qh) + t; zeros where a phase has no tap and in the rows of
@@ -771,9 +780,9 @@ __global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p) {
   }
 }
 
-struct StemDgPlan { bool ok; bool known; size_t lds; int grid; };
+struct StemDgPlan { bool ok; bool known; size_t lds; int grid, room; };   // room: workgroups that the chip holds at once
 StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
-  StemDgPlan pl{false, false, 0, 0};
+  StemDgPlan pl{false, false, 0, 0, 0};
   StemDgParams& p = *pp;
   p = StemDgParams{};
   if (g.sh > 2 || g.sw > 2 || g.Cout % 32 != 0 || g.Cout > 128) return pl;
@@ -819,6 +828,7 @@ StemDgPlan stem_dg_work_out(const Geom& g, StemDgParams* pp) {
   pl.lds = weight + p.nbuf * patch;
   if (pl.lds > 80 * 1024) return pl;   // two workgroups per CU
   const int per_cu = (int)(160 * 1024 / pl.lds) < 2 ? 1 : 2;
+  pl.room = 256 * (pl.known ? per_cu : std::min(4, (int)(160 * 1024 / pl.lds)));   // (250 or 120 registers a lane)
   pl.grid = p.ntiles < 256 * per_cu ? p.ntiles : 256 * per_cu;
   pl.ok = true;
   return pl;
@@ -922,23 +932,41 @@ bool stem_dgrad_supported(const Geom& g, int dtype) {
   StemDgParams p;
   return stem_dg_plan(g, &p).ok;
 }
+// Whether the launch takes the fold-back along: only where both fit the chip at once.  The input gradient's workgroups are
+// persistent, one behind a full round of them would start when they end (x[32,3,224,224], 7x7 / 2: 89.1 us a pass like that, 85.1
+// with a launch of its own).
+bool stem_dgrad_folds_back_aside(const Geom& g) {
+  StemDgParams p;
+  const StemDgPlan pl = stem_dg_plan(g, &p);
+  FoldBackArgs fb{};
+  fb.K = g.K; fb.Cout = g.Cout; fb.nsplit = stem_wgrad_slices(g); fb.part = reinterpret_cast<const float*>(16);
+  return pl.ok && g.K >= 4 && pl.grid + fold_back_side_blocks(fb, 256) <= pl.room;
+}
+namespace {
+template <int UU, int VV, int KS, class Side>
+hipError_t launch_dgrad_inst(const StemDgParams& p, const StemDgPlan& pl, Side side, hipStream_t st) {
+  static LdsLimitOnce lds_once;
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&stem_dgrad_kernel<UU, VV, KS, Side>), 80 * 1024);
+      e != hipSuccess) return e;
+  int nside = 0;
+  size_t lds = pl.lds;
+  if constexpr (Side::BACK) {
+    nside = fold_back_side_blocks(side, 256);
+    if (lds < (size_t)FOLD_BACK_SIDE_BYTES(256)) lds = FOLD_BACK_SIDE_BYTES(256);
+  }
+  hipLaunchKernelGGL((stem_dgrad_kernel<UU, VV, KS, Side>), dim3(pl.grid + nside), dim3(256), lds, st, p, side);
+  return hipGetLastError();
+}
+}  // namespace
 // w_crsk: w' as [Cin][kH][kW][Cout]
 hipError_t launch_dgrad_stem(const Geom& g, const void* dz, const void* w_crsk, void* dx, hipStream_t st) {
   StemDgParams p;
   const StemDgPlan pl = stem_dg_plan(g, &p);
   if (!pl.ok) return hipErrorInvalidValue;
   p.dz = (const bf16_t*)dz; p.w = (const bf16_t*)w_crsk; p.dx = (bf16_t*)dx;
-#define STEMDG(UUV, VVV, KSV)                                                                                         \
-  do {                                                                                                             \
-    static LdsLimitOnce lds_once;                                                                                  \
-    if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&stem_dgrad_kernel<UUV, VVV, KSV>), \
-                                          80 * 1024); e != hipSuccess) return e;                                   \
-    hipLaunchKernelGGL((stem_dgrad_kernel<UUV, VVV, KSV>), dim3(pl.grid), dim3(256), pl.lds, st, p);                \
-  } while (0)
-  if (pl.known) STEMDG(4, 4, 2);
-  else STEMDG(0, 0, 0);
-#undef STEMDG
-  return hipGetLastError();
+  p.nwg = pl.grid;
+  if (g.fold_back) return pl.known ? launch_dgrad_inst<4, 4, 2>(p, pl, *g.fold_back, st) : launch_dgrad_inst<0, 0, 0>(p, pl, *g.fold_back, st);
+  return pl.known ? launch_dgrad_inst<4, 4, 2>(p, pl, FoldSide{}, st) : launch_dgrad_inst<0, 0, 0>(p, pl, FoldSide{}, st);
 }
 
 bool stem_fprop_supported(const Geom& g, int dtype) {

@@ -24,20 +24,22 @@ WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv) {
   return {128, 64, tiles(128, 64) > 256 ? 3 : 6, flat};
 }
 
-template <int TM, int TN, int NST, bool FLAT>
-__global__ __launch_bounds__(64 * NWAVES) void conv_win_kernel(WnParams p) {
+template <int TM, int TN, int NST, bool FLAT, class Side>
+__global__ __launch_bounds__(64 * NWAVES) void conv_win_kernel(WnParams p, Side side) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  body<TM, TN, NST, FLAT>(p, blockIdx.x, smem);
+  body<TM, TN, NST, FLAT>(p, side, blockIdx.x, smem);
 }
 
-template <int TM, int TN, int NST, bool FLAT>
-hipError_t launch_inst(WnParams& p, hipStream_t st) {
+template <int TM, int TN, int NST, bool FLAT, class Side>
+hipError_t launch_inst(WnParams& p, Side side, hipStream_t st) {
   static LdsLimitOnce lds_once;
   constexpr int lds = WnCfg<TM, TN, NST>::LDS_BYTES;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_win_kernel<TM, TN, NST, FLAT>), lds);
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_win_kernel<TM, TN, NST, FLAT, Side>), lds);
       e != hipSuccess) return e;
   lay_out<TM, TN, FLAT>(p);
-  hipLaunchKernelGGL((conv_win_kernel<TM, TN, NST, FLAT>), dim3(p.nconv + fold_side_blocks(p.bn)), dim3(64 * NWAVES), lds, st, p);
+  int nside;
+  if constexpr (Side::BACK) nside = fold_back_side_blocks(side, 64 * NWAVES); else nside = fold_side_blocks(p.bn);
+  hipLaunchKernelGGL((conv_win_kernel<TM, TN, NST, FLAT, Side>), dim3(p.nconv + nside), dim3(64 * NWAVES), lds, st, p, side);
   return hipGetLastError();
 }
 
@@ -62,7 +64,7 @@ WnParams make_params(int C, int R, int n, const int* M, const Window* cv, size_t
 
 hipError_t launch_win(int C, int R, int n, const int* M, const Window* cv, const void* act, size_t act_bytes, const void* wgt,
                       size_t wgt_bytes, const float* bias, const BnEpilogue* bn, void* out, int relu, const void* mask,
-                      const void* add, hipStream_t st) {
+                      const void* add, hipStream_t st, const FoldBackArgs* fb = nullptr) {
   if (n < 1 || n > MAXC || C % 8 || R % 8 || act_bytes >= OOB || wgt_bytes >= OOB) return hipErrorInvalidValue;
   WnParams p = make_params(C, R, n, M, cv, act_bytes, wgt_bytes);
   p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
@@ -70,7 +72,8 @@ hipError_t launch_win(int C, int R, int n, const int* M, const Window* cv, const
   p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
   const WnPlan pl = win_plan(C, R, n, M, cv);
 #define WIN_CASE(TM_, TN_, NST_, F_) \
-  if (pl.tm == TM_ && pl.tn == TN_ && pl.nst == NST_ && pl.flat == F_) return launch_inst<TM_, TN_, NST_, F_>(p, st);
+  if (pl.tm == TM_ && pl.tn == TN_ && pl.nst == NST_ && pl.flat == F_) \
+    return fb ? launch_inst<TM_, TN_, NST_, F_>(p, *fb, st) : launch_inst<TM_, TN_, NST_, F_>(p, FoldSide{}, st);
   WIN_CASE(256, 128, 3, false) WIN_CASE(128, 128, 3, false) WIN_CASE(128, 64, 3, false) WIN_CASE(128, 64, 6, false)
   WIN_CASE(128, 128, 3, true) WIN_CASE(128, 64, 3, true) WIN_CASE(128, 64, 6, true)
 #undef WIN_CASE
@@ -138,11 +141,14 @@ hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, co
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st) {
   Window c[MAXC];
   int M[MAXC], n = 0;
+  const FoldBackArgs* fb = g.fold_back;
   auto flush = [&]() -> hipError_t {
     const int k = n;
+    const FoldBackArgs* const f = fb;   // (along with the first launch)
     n = 0;
+    fb = nullptr;
     return launch_win(g.Cout, g.Cin, k, M, c, dz, (size_t)g.M * g.Cout * 2, w_crsk, (size_t)g.Cout * g.K * 2, bias, nullptr, dx,
-                      g.post_relu, g.post_mask, g.post_add, st);
+                      g.post_relu, g.post_mask, g.post_add, st, f);
   };
   for (int a = 0; a < classes_h(g); ++a)
     for (int b = 0; b < classes_w(g); ++b) {

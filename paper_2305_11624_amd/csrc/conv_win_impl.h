@@ -74,7 +74,7 @@ struct WnParams {
   unsigned act_bytes, wgt_bytes;
   int C, R, ntr;         // ntr: channel tiles
   int by_channel;        // which operand an XCD keeps to itself, see the kernel
-  int ncls, nconv;       // nconv: the convolution's workgroups, those behind it fold
+  int ncls, nconv;       // nconv: the convolution's workgroups, those behind it fold, or fold back
   WnClass c[MAXC];
 };
 
@@ -111,13 +111,13 @@ struct WnCfg {
   static constexpr int OFF_BIAS = NST * STAGE;          // [TN] bias, [TN] scale
   static constexpr int LDS_BYTES = OFF_BIAS + 2 * TN * 4;
   static_assert(NWAVES * 32 * CW * 2 <= STAGE * NST, "the epilogue stages every wave's outputs in the ring");
-  static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES, "two tiles of the fold on the side");
+  static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES, "what folds on the side");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
-// Workgroup `wg` of the product (and, behind its workgroups, of the fold on the side); smem: WnCfg::LDS_BYTES
-template <int TM, int TN, int NST, bool FLAT>
-__device__ __forceinline__ void body(const WnParams& p, const int wg, unsigned char* smem) {
+// Workgroup `wg` of the product (and, behind its workgroups, of the fold or the fold-back on the side); smem: WnCfg::LDS_BYTES
+template <int TM, int TN, int NST, bool FLAT, class Side>
+__device__ __forceinline__ void body(const WnParams& p, const Side& side, const int wg, unsigned char* smem) {
   using Cfg = WnCfg<TM, TN, NST>;
   constexpr int CW = Cfg::CW;
   constexpr int GR = CW / 8;          // 16-byte granules of a wave's staged output row
@@ -125,7 +125,8 @@ __device__ __forceinline__ void body(const WnParams& p, const int wg, unsigned c
   constexpr int ITS = 32 / RPI;       // store instructions per 32-pixel subtile
   constexpr int NPS = Cfg::NPS, NCS = Cfg::NCS, AUW = Cfg::AUW, WUW = Cfg::WUW, CPW = Cfg::CPW, STAGE = Cfg::STAGE;
   if (wg >= p.nconv) {
-    fold_side(p.bn, p.wgt, wg - p.nconv, smem);
+    if constexpr (Side::BACK) fold_back_side<64 * NWAVES>(side, wg - p.nconv, smem);
+    else fold_side(p.bn, p.wgt, wg - p.nconv, smem);
     return;
   }
   float* biasl = reinterpret_cast<float*>(smem + Cfg::OFF_BIAS);

@@ -107,211 +107,30 @@ __global__ __launch_bounds__(256) void fold_group_kernel(const FoldGroupItem* __
   fold_tile_bf16x8(it.a, t % it.tiles_k, t / it.tiles_k, threadIdx.x, tile);
 }
 
-__device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ void load4(const float* p, float (&w)[4]) {
-  const float4 v = ld4(p);
-  w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
-}
-__device__ __forceinline__ void load4(const bf16_t* p, float (&w)[4]) {
-  const uint2 v = *reinterpret_cast<const uint2*>(p);
-  w[0] = bf16_lo(v.x); w[1] = bf16_hi(v.x); w[2] = bf16_lo(v.y); w[3] = bf16_hi(v.y);
-}
-__device__ __forceinline__ void store4(float* p, const float (&w)[4]) {
-  *reinterpret_cast<float4*>(p) = make_float4(w[0], w[1], w[2], w[3]);
-}
-__device__ __forceinline__ void store4(bf16_t* p, const float (&w)[4]) {
-  *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]));
-}
-
-// One block per output channel.  VEC (K % 4 == 0): a thread owns float4 columns of the row.  The
-// `nsplit` partial copies of a column lie far apart in memory, so every load is a latency round trip of
-// its own.  Short rows (fewer than 256 columns): a thread keeps sixteen copies of one column in
-// flight, the copies are divided over as many thread groups as fit the block, and the groups meet in
-// LDS.  Long rows: a column per thread, four copies in flight, columns in sequence.  Rows whose length is not a
-// multiple of 4: one element per thread; short ones divide the copies over thread groups in the same way.
-template <typename T, bool VEC, int NTHR>
-__device__ __forceinline__ void fold_back_row(
-    const int co, const float* __restrict__ part, int nsplit, const float* __restrict__ r_part, int nrpart,
-    const T* __restrict__ W, const float* __restrict__ b, const float* __restrict__ gamma,
-    const float* __restrict__ mean, const float* __restrict__ var, float eps, int identity, int Cout,
-    int K, T* __restrict__ dW, float* __restrict__ db, float* __restrict__ dgamma,
-    float* __restrict__ dbeta) {
-  constexpr int NSL = NTHR / 64;
-  __shared__ float4 red4[VEC ? NTHR : 1];
-  __shared__ float reds[VEC ? 1 : NTHR];
-  __shared__ float red[NSL];
-  const int tid = threadIdx.x;
-  const size_t P = (size_t)Cout * K;
-  // Every trip to memory that does not depend on another starts here: with the weight, r and the channel's vectors read where
-  // they are used, four trips in a row, a launch took 4.6 us on 72 -> 136 channels at 27 x 33 and 5.6 on 64 -> 64 at 56 x 56;
-  // now 4.0 and 5.0.
-  float s = 1.f, sd = 1.f, mu = 0.f, bc = 0.f, r0 = 0.f;
-  if (!identity) {
-    const float ga = gamma[co], va = var[co];
-    mu = mean[co];
-    if (b) bc = b[co];
-    if (tid < nrpart) r0 = r_part[(size_t)tid * Cout + co];
-    sd = sqrtf(va + eps);
-    s = ga / sd;
-  }
-  float dot = 0.f;
-  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto finish = [&](int k4, const float4& v, const float (&w4)[4]) {   // dW = s dw', <dw', w> of one float4 column
-    const float g4[4] = {v.x, v.y, v.z, v.w};
-    float o4[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o4[e] = s * g4[e];
-      dot += g4[e] * w4[e];
-    }
-    store4(dW + (size_t)co * K + 4 * k4, o4);
-  };
-  if (VEC && (K >> 2) >= 256) {
-    // long rows: one float4 column per thread at a time, all partial copies summed in registers, no
-    // barriers (many such blocks share a CU, which keeps enough loads in flight)
-    const int K4 = K >> 2;
-    const float* row = part + (size_t)co * K;
-    for (int k4 = tid; k4 < K4; k4 += NTHR) {
-      float4 v = zero4;
-      float w4[4];
-      load4(W + (size_t)co * K + 4 * k4, w4);
-      int sp = 0;
-      for (; sp + 3 < nsplit; sp += 4) {
-        const float4 a0 = ld4(row + (size_t)sp * P + 4 * k4);
-        const float4 a1 = ld4(row + (size_t)(sp + 1) * P + 4 * k4);
-        const float4 a2 = ld4(row + (size_t)(sp + 2) * P + 4 * k4);
-        const float4 a3 = ld4(row + (size_t)(sp + 3) * P + 4 * k4);
-        v.x += (a0.x + a1.x) + (a2.x + a3.x);
-        v.y += (a0.y + a1.y) + (a2.y + a3.y);
-        v.z += (a0.z + a1.z) + (a2.z + a3.z);
-        v.w += (a0.w + a1.w) + (a2.w + a3.w);
-      }
-      for (; sp < nsplit; ++sp) {
-        const float4 a0 = ld4(row + (size_t)sp * P + 4 * k4);
-        v.x += a0.x; v.y += a0.y; v.z += a0.z; v.w += a0.w;
-      }
-      finish(k4, v, w4);
-    }
-  } else if (VEC) {
-    // short rows (fewer than 256 columns): thread -> (column c, group g of the partial copies)
-    const int K4 = K >> 2;
-    const int G = NTHR / K4;
-    const int c = tid % K4, g = tid / K4;
-    float4 v = zero4;
-    float w4[4] = {0.f, 0.f, 0.f, 0.f};
-    if (g == 0) load4(W + (size_t)co * K + 4 * c, w4);
-    if (g < G) {
-      const float* col = part + (size_t)co * K + 4 * c;
-      for (int sp0 = g; sp0 < nsplit; sp0 += 16 * G) {
-        float4 a[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) a[j] = sp0 + j * G < nsplit ? ld4(col + (size_t)(sp0 + j * G) * P) : zero4;
-#pragma unroll
-        for (int j = 0; j < 16; j += 4) {
-          v.x += (a[j].x + a[j + 1].x) + (a[j + 2].x + a[j + 3].x);
-          v.y += (a[j].y + a[j + 1].y) + (a[j + 2].y + a[j + 3].y);
-          v.z += (a[j].z + a[j + 1].z) + (a[j + 2].z + a[j + 3].z);
-          v.w += (a[j].w + a[j + 1].w) + (a[j + 2].w + a[j + 3].w);
-        }
-      }
-    }
-    red4[tid] = v;
-    __syncthreads();
-    if (g == 0) {
-      for (int l = 1; l < G; ++l) {
-        const float4 o = red4[l * K4 + c];
-        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-      }
-      finish(c, v, w4);
-    }
-  } else if (K * 2 <= NTHR) {
-    // short rows whose length is not a multiple of 4 (a first layer: 7 x 7 x 3): thread -> (element k, group g of the
-    // partial copies), eight copies in flight per thread, the groups meet in LDS
-    const int G = NTHR / K;
-    const int k = tid % K, g = tid / K;
-    float v = 0.f;
-    const float w = g == 0 ? to_f32(W[(size_t)co * K + k]) : 0.f;
-    if (g < G) {
-      const float* col = part + (size_t)co * K + k;
-      for (int sp0 = g; sp0 < nsplit; sp0 += 8 * G) {
-        float a[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = sp0 + j * G < nsplit ? col[(size_t)(sp0 + j * G) * P] : 0.f;
-        v += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-      }
-    }
-    reds[tid] = v;
-    __syncthreads();
-    if (g == 0) {
-      for (int l = 1; l < G; ++l) v += reds[l * K + k];
-      const size_t idx = (size_t)co * K + k;
-      dW[idx] = from_f32<T>(s * v);
-      dot += v * w;
-    }
-  } else {
-    for (int k = tid; k < K; k += NTHR) {
-      const size_t idx = (size_t)co * K + k;
-      const float w = to_f32(W[idx]);
-      float v = 0.f;
-      int sp = 0;
-      for (; sp + 7 < nsplit; sp += 8) {   // eight copies in flight: each load is a round trip of its own
-        float a[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a[j] = part[(sp + j) * P + idx];
-        v += ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-      }
-      for (; sp < nsplit; ++sp) v += part[sp * P + idx];
-      dW[idx] = from_f32<T>(s * v);
-      dot += v * w;
-    }
-  }
-  if (identity) return;
-  float r = r0;
-  for (int q = tid + NTHR; q < nrpart; q += NTHR) r += r_part[(size_t)q * Cout + co];
-  dot = wave_sum(dot);
-  r = wave_sum(r);
-  __shared__ float redr[NSL];
-  if ((tid & 63) == 0) { red[tid >> 6] = dot; redr[tid >> 6] = r; }
-  __syncthreads();
-  if (tid == 0) {
-    dot = 0.f;
-    r = 0.f;
-    for (int l = 0; l < NSL; ++l) { dot += red[l]; r += redr[l]; }
-    dbeta[co] = r;
-    dgamma[co] = (dot + r * (bc - mu)) / sd;
-    if (db) db[co] = s * r;
-  }
-}
-
-template <typename T, bool VEC, int NTHR>
-__global__ __launch_bounds__(NTHR) void fold_back_kernel(
-    const float* __restrict__ part, int nsplit, const float* __restrict__ r_part, int nrpart,
-    const T* __restrict__ W, const float* __restrict__ b, const float* __restrict__ gamma,
-    const float* __restrict__ mean, const float* __restrict__ var, float eps, int identity, int Cout,
-    int K, T* __restrict__ dW, float* __restrict__ db, float* __restrict__ dgamma,
-    float* __restrict__ dbeta) {
-  fold_back_row<T, VEC, NTHR>(blockIdx.x, part, nsplit, r_part, nrpart, W, b, gamma, mean, var, eps, identity, Cout, K,
-                              dW, db, dgamma, dbeta);
+template <typename T, int NTHR, RowKind ROW>
+__global__ __launch_bounds__(NTHR) void fold_back_kernel(FoldBackArgs a) {
+  __shared__ float4 red4[NTHR];
+  __shared__ float red[2 * NTHR / 64];
+  fold_back_row<T, 16, ROW>(a, blockIdx.x, threadIdx.x, NTHR, red4, red);
 }
 
 // The fold-backs of several blocks in one launch (Table 2 "Tune", last four lines, for every block of a group):
 // workgroup w handles output channel w - first_block of the item it falls into.  Same arithmetic, in the same
 // order, as the 256-thread single-block kernel.
 struct FoldBackGroupItem {
-  const float* part; const float* r_part; const bf16_t* W; const float* b; const float* gamma; const float* mean;
-  const float* var; bf16_t* dW; float* db; float* dgamma; float* dbeta;
-  float eps; int nsplit, nrpart, Cout, K, first_block;
+  FoldBackArgs a;
+  int first_block;
 };
 __global__ __launch_bounds__(256) void fold_back_group_kernel(const FoldBackGroupItem* __restrict__ items, int n) {
+  __shared__ float4 red4[256];
+  __shared__ float red[8];
   int lo = 0, hi = n - 1;   // last item whose first_block <= blockIdx.x
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (items[mid].first_block <= (int)blockIdx.x) lo = mid; else hi = mid - 1;
   }
-  const FoldBackGroupItem it = items[lo];
-  fold_back_row<bf16_t, true, 256>(blockIdx.x - it.first_block, it.part, it.nsplit, it.r_part, it.nrpart, it.W, it.b,
-                                   it.gamma, it.mean, it.var, it.eps, 0, it.Cout, it.K, it.dW, it.db, it.dgamma,
-                                   it.dbeta);
+  const FoldBackArgs a = items[lo].a;
+  fold_back_row<bf16_t, 16, ROW_VEC>(a, blockIdx.x - items[lo].first_block, threadIdx.x, 256, red4, red);
 }
 
 // Column reductions over a [M][Cout] channels-last tensor.  `cw` threads walk the
@@ -601,8 +420,8 @@ bool fold_back_group_item(const Geom& g, int dtype, const float* dwf_part, int n
                           void* dW, float* db, float* dgamma, float* dbeta, int first_block, void* item_out,
                           int* blocks) {
   if (dtype != CONVBN_BF16 || g.K % 4 != 0) return false;
-  FoldBackGroupItem it{dwf_part, r_part, (const bf16_t*)W, b, gamma, mean, var, (bf16_t*)dW, db, dgamma, dbeta,
-                       g.eps, nsplit, nrpart, g.Cout, g.K, first_block};
+  const FoldBackGroupItem it{{dwf_part, r_part, W, b, gamma, mean, var, dW, db, dgamma, dbeta, g.eps, nsplit, nrpart, 0, g.Cout, g.K, 0},
+                             first_block};
   *blocks = g.Cout;
   memcpy(item_out, &it, sizeof(it));
   return true;
@@ -617,26 +436,18 @@ hipError_t launch_fold_back(const Geom& g, int dtype, const float* dwf_part, int
                             const float* r_part, int nrpart, const void* W, const float* b,
                             const float* gamma, const float* mean, const float* var, int identity,
                             void* dW, float* db, float* dgamma, float* dbeta, hipStream_t st) {
-#define FB_LAUNCH(T, VEC, NTHR)                                                                          \
-  hipLaunchKernelGGL((fold_back_kernel<T, VEC, NTHR>), dim3(g.Cout), dim3(NTHR), 0, st, dwf_part, nsplit, \
-                     r_part, nrpart, (const T*)W, b, gamma, mean, var, g.eps, identity, g.Cout,           \
-                     g.K, (T*)dW, db, dgamma, dbeta)
-  const bool vec = g.K % 4 == 0;
+  const FoldBackArgs a{dwf_part, r_part, W, b, gamma, mean, var, dW, db, dgamma, dbeta, g.eps, nsplit, nrpart, identity, g.Cout, g.K, 0};
+#define FB_LAUNCH(NTHR, ROW)                                                                                            \
+  do {                                                                                                                  \
+    if (dtype == CONVBN_BF16) hipLaunchKernelGGL((fold_back_kernel<bf16_t, NTHR, ROW>), dim3(g.Cout), dim3(NTHR), 0, st, a); \
+    else hipLaunchKernelGGL((fold_back_kernel<float, NTHR, ROW>), dim3(g.Cout), dim3(NTHR), 0, st, a);                   \
+  } while (0)
   // few output channels and many partial copies: a 1024-thread block per channel (16 waves share
   // the copies) keeps enough loads in flight on the few CUs such a grid occupies
-  const bool wide = vec && g.Cout <= 128 && nsplit >= 16 && (g.K >> 2) < 256;
-  const bool wide_scalar = !vec && g.Cout <= 128 && nsplit >= 16 && g.K * 2 <= 1024;   // (a first layer's 7 x 7 x 3 rows)
-  if (dtype == CONVBN_BF16) {
-    if (wide) FB_LAUNCH(bf16_t, true, 1024);
-    else if (vec) FB_LAUNCH(bf16_t, true, 256);
-    else if (wide_scalar) FB_LAUNCH(bf16_t, false, 1024);
-    else FB_LAUNCH(bf16_t, false, 256);
-  } else {
-    if (wide) FB_LAUNCH(float, true, 1024);
-    else if (vec) FB_LAUNCH(float, true, 256);
-    else if (wide_scalar) FB_LAUNCH(float, false, 1024);
-    else FB_LAUNCH(float, false, 256);
-  }
+  const bool wide = g.Cout <= 128 && nsplit >= 16 && ceil_div(g.K, 4) < 256;
+  if (g.K % 4 == 0) { if (wide) FB_LAUNCH(1024, ROW_VEC); else FB_LAUNCH(256, ROW_VEC); }
+  else if (wide && g.K >= 4) FB_LAUNCH(1024, ROW_ANY);
+  else FB_LAUNCH(256, ROW_ELEM);
 #undef FB_LAUNCH
   return hipGetLastError();
 }

@@ -124,4 +124,185 @@ __device__ __forceinline__ void colsum_slice_bf16x8(const uint4* __restrict__ dz
   }
 }
 
+// ---- fold-back: the partial copies of dw' of one output channel summed, dW = s dw', dgamma, dbeta, db (Table 2 "Tune")
+struct __attribute__((packed, aligned(4))) F4u { float x, y, z, w; };
+__device__ __forceinline__ float4 ld4u(const float* p) {   // 16 bytes from any element
+  const F4u v = *reinterpret_cast<const F4u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void fb_load4(const float* p, float (&w)[4]) {
+  const float4 v = *reinterpret_cast<const float4*>(p);
+  w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+}
+__device__ __forceinline__ void fb_load4(const bf16_t* p, float (&w)[4]) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  w[0] = bf16_lo(v.x); w[1] = bf16_hi(v.x); w[2] = bf16_lo(v.y); w[3] = bf16_hi(v.y);
+}
+__device__ __forceinline__ void fb_store4(float* p, const float (&w)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(w[0], w[1], w[2], w[3]);
+}
+__device__ __forceinline__ void fb_store4(bf16_t* p, const float (&w)[4]) {
+  *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]));
+}
+
+// Output channel co by `nthr` threads (a multiple of 64, tid counts them; all threads of the workgroup call this together,
+// there are barriers inside; co >= Cout does nothing but meet them).  A thread owns columns of four elements of the row (one,
+// where a row's length is no multiple of 4 and there are few copies); ROW_ANY: the last column then starts early and counts
+// only its own elements (7 x 7 x 3 rows, 512 copies, a launch: 11.5 us
+// with one element a thread, 8.5 with four).  The `nsplit` partial copies of a
+// column lie far apart in memory, so every load is a latency round trip of its own: short rows (fewer columns than threads)
+// keep FLIGHT copies of a column in flight per thread, the copies are divided over as many thread groups as there are
+// threads for, and the groups meet in LDS; long rows take the columns one after the other, four copies in flight.
+// red4: nthr entries, red: 2 per wave, of these threads' own.
+enum RowKind { ROW_VEC, ROW_ANY, ROW_ELEM };   // columns of four elements, K % 4 == 0; ... K >= 4; columns of one
+template <typename T, int FLIGHT, RowKind ROW>
+__device__ __forceinline__ void fold_back_row(const FoldBackArgs& a, int co, int tid, int nthr, float4* red4, float* red) {
+  const bool live = co < a.Cout;
+  co = min(co, a.Cout - 1);
+  const int K = a.K, nsplit = a.nsplit;
+  const T* const W = static_cast<const T*>(a.W) + (size_t)co * K;
+  T* const dW = static_cast<T*>(a.dW) + (size_t)co * K;
+  const size_t P = (size_t)a.Cout * K;
+  const float* const row = a.part + (size_t)co * K;
+  // Every trip to memory that does not depend on another starts here: with the weight, r and the channel's vectors read where
+  // they are used, four trips in a row, a launch took 4.6 us on 72 -> 136 channels at 27 x 33 and 5.6 on 64 -> 64 at 56 x 56;
+  // now 4.0 and 5.0.
+  constexpr bool VEC = ROW == ROW_VEC, ELEM = ROW == ROW_ELEM;
+  float s = 1.f, sd = 1.f, mu = 0.f, bc = 0.f, r = 0.f;
+  if (!a.identity) {
+    const float ga = a.gamma[co], va = a.var[co];
+    mu = a.mean[co];
+    if (a.b) bc = a.b[co];
+    if (tid < a.nrpart) r = a.r_part[(size_t)tid * a.Cout + co];
+    sd = sqrtf(va + a.eps);
+    s = ga / sd;
+  }
+  float dot = 0.f;
+  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int K4 = ELEM ? K : (K + 3) >> 2;
+  auto at = [&](int c) { return ELEM ? c : VEC ? 4 * c : min(4 * c, K - 4); };   // first element of column c
+  auto load_w = [&](int c, float (&w4)[4]) {
+    if constexpr (VEC) {
+      fb_load4(W + 4 * c, w4);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w4[e] = !ELEM || e == 0 ? to_f32(W[at(c) + e]) : 0.f;
+    }
+  };
+  auto load_part = [&](const float* p) {
+    if constexpr (ELEM) return make_float4(p[0], 0.f, 0.f, 0.f);
+    else if constexpr (VEC) return *reinterpret_cast<const float4*>(p);
+    else return ld4u(p);
+  };
+  auto finish = [&](int c, const float4& v, const float (&w4)[4]) {   // dW = s dw', <dw', w> of one column
+    const float g4[4] = {v.x, v.y, v.z, v.w};
+    float o4[4];
+    const int k = at(c), skip = VEC || ELEM ? 0 : 4 * c - k;   // (its first `skip` elements are the column before's)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o4[e] = s * g4[e];
+      if (e >= skip && (!ELEM || e == 0)) dot += g4[e] * w4[e];
+    }
+    if (!live) return;
+    if constexpr (VEC) {
+      fb_store4(dW + k, o4);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e >= skip && (!ELEM || e == 0)) dW[k + e] = from_f32<T>(o4[e]);
+    }
+  };
+  if (K4 >= nthr) {
+    for (int c = tid; c < K4; c += nthr) {
+      float4 v = zero4;
+      float w4[4];
+      load_w(c, w4);
+      const float* const col = row + at(c);
+      int sp = 0;
+      for (; sp + 3 < nsplit; sp += 4) {
+        const float4 a0 = load_part(col + (size_t)sp * P);
+        const float4 a1 = load_part(col + (size_t)(sp + 1) * P);
+        const float4 a2 = load_part(col + (size_t)(sp + 2) * P);
+        const float4 a3 = load_part(col + (size_t)(sp + 3) * P);
+        v.x += (a0.x + a1.x) + (a2.x + a3.x);
+        v.y += (a0.y + a1.y) + (a2.y + a3.y);
+        v.z += (a0.z + a1.z) + (a2.z + a3.z);
+        v.w += (a0.w + a1.w) + (a2.w + a3.w);
+      }
+      for (; sp < nsplit; ++sp) {
+        const float4 a0 = load_part(col + (size_t)sp * P);
+        v.x += a0.x; v.y += a0.y; v.z += a0.z; v.w += a0.w;
+      }
+      finish(c, v, w4);
+    }
+  } else {
+    // thread -> (column c, group g of the partial copies); a group more is a read from LDS in a row more, at the end
+    const int G = min(nthr / K4, (nsplit + FLIGHT - 1) / FLIGHT);
+    const int c = tid % K4, g = tid / K4;
+    float4 v = zero4;
+    float w4[4] = {0.f, 0.f, 0.f, 0.f};
+    if (g == 0) load_w(c, w4);
+    if (g < G) {
+      const float* const col = row + at(c);
+      for (int sp0 = g; sp0 < nsplit; sp0 += FLIGHT * G) {
+        float4 t[FLIGHT];
+#pragma unroll
+        for (int j = 0; j < FLIGHT; ++j) t[j] = sp0 + j * G < nsplit ? load_part(col + (size_t)(sp0 + j * G) * P) : zero4;
+#pragma unroll
+        for (int j = 0; j < FLIGHT; j += 4) {
+          v.x += (t[j].x + t[j + 1].x) + (t[j + 2].x + t[j + 3].x);
+          v.y += (t[j].y + t[j + 1].y) + (t[j + 2].y + t[j + 3].y);
+          v.z += (t[j].z + t[j + 1].z) + (t[j + 2].z + t[j + 3].z);
+          v.w += (t[j].w + t[j + 1].w) + (t[j + 2].w + t[j + 3].w);
+        }
+      }
+    }
+    red4[tid] = v;
+    __syncthreads();
+    if (g == 0) {
+      for (int l = 1; l < G; ++l) {
+        const float4 o = red4[l * K4 + c];
+        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+      }
+      finish(c, v, w4);
+    }
+  }
+  if (a.identity) return;
+#pragma unroll 4
+  for (int q = tid + nthr; q < a.nrpart; q += nthr) r += a.r_part[(size_t)q * a.Cout + co];
+  dot = wave_sum(dot);
+  r = wave_sum(r);
+  if ((tid & 63) == 0) { red[2 * (tid >> 6)] = dot; red[2 * (tid >> 6) + 1] = r; }
+  __syncthreads();
+  if (tid == 0 && live) {
+    dot = 0.f;
+    r = 0.f;
+    for (int l = 0; l < nthr >> 6; ++l) { dot += red[2 * l]; r += red[2 * l + 1]; }
+    a.dbeta[co] = r;
+    a.dgamma[co] = (dot + r * (bc - mu)) / sd;
+    if (a.db) a.db[co] = s * r;
+  }
+}
+
+// An input gradient launched behind the weight gradient takes the fold-back along, on workgroups of its own behind the product's:
+// they find the compute units that the product leaves idle, or that its first tiles have left, and the fold-back is no launch
+// (4 - 5 us; a pass: 256 -> 64 channels at 56 x 56, 32 images 46.8 -> 43.8 us, at 46 x 40, 13 images 23.5 -> 19.5; 3 -> 32, 3 x 3
+// / 2 at 172 x 172, 17 images 34.5 -> 29.4).  A workgroup of `threads` takes as many channels as leave a thread about sixteen loads.
+constexpr int FOLD_BACK_SIDE_BYTES(int threads) { return threads * 16 + threads / 64 * 8; }
+inline int fold_back_side_blocks(FoldBackArgs& a, int threads) {
+  if (!a.part) return 0;
+  const long long loads = (long long)ceil_div(a.K, 4) * a.nsplit;
+  a.per = 64;
+  while (a.per < threads && loads > 16LL * a.per) a.per *= 2;
+  return ceil_div(a.Cout, threads / a.per);
+}
+// smem: FOLD_BACK_SIDE_BYTES(THREADS)
+template <int THREADS, RowKind ROW = ROW_VEC>
+__device__ __forceinline__ void fold_back_side(const FoldBackArgs& a, int wg, unsigned char* smem) {
+  const int group = (int)threadIdx.x / a.per, tid = (int)threadIdx.x - group * a.per;
+  float4* const red4 = reinterpret_cast<float4*>(smem);
+  float* const red = reinterpret_cast<float*>(smem + THREADS * 16);
+  fold_back_row<bf16_t, 8, ROW>(a, wg * (THREADS / a.per) + group, tid, a.per, red4 + group * a.per, red + group * (a.per >> 5));
+}
+
 }  // namespace convbn

@@ -16,7 +16,7 @@ template <bool FLAT, int TA, int TB>
 __global__ __launch_bounds__(512) void win_pair_kernel(wgw::WwParams w, win::WnParams d, int nw) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   if ((int)blockIdx.x < nw) wgw::body<TA, TB>(w, blockIdx.x, smem);
-  else win::body<128, 64, 6, FLAT>(d, (int)blockIdx.x - nw, smem);
+  else win::body<128, 64, 6, FLAT>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
 }
 
 struct PairPlan { bool ok, flat; int ta, tb, nw; wgw::WwParams w; win::WnParams d; };

@@ -1,0 +1,46 @@
+"""GPU parity of the fold-back where it rides in the input gradient's launch (64 to 512 threads a channel, channels that do not fill a
+workgroup) and of rows that are no multiple of four elements, as columns of four and of one."""
+import pytest
+
+from paper_2305_11624_amd import synth
+from paper_2305_11624_amd.runner import BlockRun
+from paper_2305_11624_amd.synth import BlockShape
+
+from helpers import compare, oracle_block
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    #  N  Cin  H   W   Cout k  s  p
+    (20, 256, 30, 33, 64, 1, 1, 0, "bf16"),    # pointwise product: many copies of short rows
+    (24, 64, 41, 40, 192, 1, 1, 0, "bf16"),    # sixteen columns a row
+    (12, 512, 17, 19, 640, 1, 1, 0, "bf16"),   # few copies, 128 columns
+    (40, 128, 30, 30, 264, 3, 2, 1, "bf16"),   # residue classes; rows longer than a channel's threads, channels that fill no workgroup
+    (3, 128, 37, 41, 128, 3, 1, 1, "bf16"),    # the deep-layer kernel
+    (9, 3, 24, 24, 32, 3, 2, 1, "bf16"),       # first layers: 27 and 75 elements a row
+    (6, 3, 33, 52, 64, 5, 2, 2, "bf16"),
+    (1, 3, 8, 8, 32, 1, 1, 0, "bf16"),         # three elements a row
+    (4, 3, 40, 40, 16, 3, 1, 1, "f32"), (2, 5, 9, 11, 7, 1, 1, 0, "f32"), (1, 2, 6, 5, 3, 1, 1, 0, "f32"),
+]
+
+
+@pytest.mark.parametrize("n,cin,h,w,cout,k,s,p,dtype", SHAPES)
+def test_parameter_gradients(n, cin, h, w, cout, k, s, p, dtype):
+    inp = synth.make_inputs(BlockShape("fb", n, cin, h, w, cout, k, s, p, dtype, 3 * h + w), bias=True)
+    ref = oracle_block(inp)
+    for keep in (True, False):
+        r = BlockRun(inp, poison=True, keep_folded=keep)
+        r.step()
+        compare(r.results(), ref, dtype, tag="keep %s" % keep)
+
+
+@pytest.mark.parametrize("over", ["dz", "w_folded"])
+def test_gradient_over_an_operand(over):
+    """dW may take the place of what the input gradient reads: it is written behind it then."""
+    inp = synth.make_inputs(BlockShape("fb", 20, 256, 30, 33, 64, 1, 1, 0, "bf16", 7))
+    ref = oracle_block(inp)
+    r = BlockRun(inp, poison=True)
+    r.forward()
+    r.dW = getattr(r, over).flatten()[:r.dW.numel()].view(r.dW.shape)
+    r.backward()
+    compare(r.results(), ref, "bf16", keys=("dX", "dW", "dgamma", "dbeta"), tag=over)
