@@ -103,7 +103,7 @@ WgradWay wgrad_way(const Geom& g0, int dtype) {
   // (ResNet-50, grouped units, 4 images: step 1.81 ms with wgrad_sq, 1.76 without); no split: one launch with the fold-back.
   const bool sq = wgrad_sq_supported(g, dtype) &&
                   (wgrad_sq_splits(g) == 1 ||
-                   (!pair_taken(g, dtype) && g.sh == 1 && g.sw == 1 &&
+                   (!pair_taken(g, dtype) && !ks_dgrad_taken(g, dtype) && g.sh == 1 && g.sw == 1 &&
                     ((long long)g.Cin * g.Cout > 64 * 64 || (g.M > 32768 && wgrad_dgrad_pair_supported(g, dtype)))));
   if (sq) {
     const int s = wgrad_sq_splits(g);
@@ -244,10 +244,8 @@ convbn_status check_ws(size_t need, void* ws, size_t ws_bytes) {
 
 // Which problems the window product takes: strided windows, what the LDS-tile kernel has no plan for, and few tiles, where
 // that kernel would split its sums (fp32 partial outputs, a reduction launch, forward a fold launch), as long as one
-// workgroup's chain of 64-channel chunks is not what the launch then waits for -- and few tiles let the two gradient passes
-// share a launch (win_pair.hip).  Measured, whole steps: 1x1, 512 -> 128 at 28 x 28, 4 images (8 chunks) 38.2 -> 24 us;
-// 1024 -> 256 at 14 x 14, 1 image (16 forward) 37.2 -> 22.3; 512 -> 2048 at 8 x 8, 22 images (32 backward) 47 -> 31; 3x3 with
-// 256 channels at 14 x 14, 8 images (36) 50.7 -> 40.8; with 512 channels (72) 46.4 -> 66.
+// workgroup's chain of 64-channel chunks is not what the launch then waits for.  Few pixels go to its wave-split form
+// first (ks_*_taken).
 constexpr int WIN_CHUNKS = 40, WIN_SMALL_TILES = 128;
 bool win_small(int M, int R, int K) {   // M pixels, R produced channels, K reduced
   return K <= 64 * WIN_CHUNKS && (long long)ceil_div(M, 128) * ceil_div(R, 64) <= WIN_SMALL_TILES;
@@ -263,15 +261,12 @@ bool win_dgrad_taken(const Geom& g, int dtype) {
   return !tile_dgrad_supported(g, dtype) || win_small(g.Min, g.Cin, g.kH * g.kW * g.Cout);
 }
 
-// Whether the two gradient passes of a block share a launch (win_pair.hip): the input gradient then is the window product
-// also where the pointwise product would take it alone.
-bool pair_taken(const Geom& g, int dtype) {
-  return win_pair_supported(g, dtype) && !rw_dgrad_supported(g, dtype) && !st_dgrad_supported(g, dtype) &&
-         (pw_dgrad_supported(g, dtype) || win_dgrad_taken(g, dtype));
-}
+// Whether the two gradient passes of a block share a launch (win_pair.hip).
+bool pair_taken(const Geom& g, int dtype) { return win_pair_taken(g, dtype); }
 
 // Scratch the three convolutions of a problem need (0 for most): fp32 partial outputs when the
-// reduced channels are split over workgroups, and the zero-padded copies of needs_cin_pad().
+// reduced channels are split over workgroups, and the zero-padded copies of needs_cin_pad().  (The wave-split product needs
+// none; where it has taken over such a split, the size stays what callers were told before.)
 size_t inner_fprop_scratch(const Geom& g, int dtype) {
   if (pw_fprop_supported(g, dtype) || rw_fprop_supported(g, dtype) || st_fprop_supported(g, dtype) ||
       win_fprop_taken(g, dtype)) return 0;
@@ -327,7 +322,8 @@ hipError_t fprop_any(const Geom& g, int dtype, const void* x, const void* w_krsc
                      void* z, float* scratch, hipStream_t st) {
   hipError_t e;
   bool fused = false;
-  if (pw_fprop_supported(g, dtype)) { e = launch_fprop_pw(g, x, w_krsc, bias, z, st); fused = FUSED_PW; }
+  if (ks_fprop_taken(g, dtype)) { e = launch_fprop_win(g, x, w_krsc, bias, z, st); fused = true; }
+  else if (pw_fprop_supported(g, dtype)) { e = launch_fprop_pw(g, x, w_krsc, bias, z, st); fused = FUSED_PW; }
   else if (rw_fprop_supported(g, dtype)) { e = launch_fprop_rw(g, x, w_krsc, bias, z, st); fused = FUSED_RW; }
   else if (st_fprop_supported(g, dtype)) { e = launch_fprop_st(g, x, w_krsc, bias, z, st); fused = FUSED_ST; }
   else if (win_fprop_taken(g, dtype)) { e = launch_fprop_win(g, x, w_krsc, bias, z, st); fused = true; }
@@ -342,7 +338,8 @@ hipError_t dgrad_any(const Geom& g, int dtype, const void* dz, const void* w_crs
                      float* scratch, hipStream_t st) {
   hipError_t e;
   bool fused = false;
-  if (pw_dgrad_supported(g, dtype)) { e = launch_dgrad_pw(g, dz, w_crsk, bias, dx, st); fused = FUSED_PW; }
+  if (ks_dgrad_taken(g, dtype)) { e = launch_dgrad_win(g, dz, w_crsk, bias, dx, st); fused = true; }
+  else if (pw_dgrad_supported(g, dtype)) { e = launch_dgrad_pw(g, dz, w_crsk, bias, dx, st); fused = FUSED_PW; }
   else if (rw_dgrad_supported(g, dtype)) { e = launch_dgrad_rw(g, dz, w_crsk, bias, dx, st); fused = FUSED_RW; }
   else if (st_dgrad_supported(g, dtype)) { e = launch_dgrad_st(g, dz, w_crsk, bias, dx, st); fused = FUSED_ST; }
   else if (win_dgrad_taken(g, dtype)) { e = launch_dgrad_win(g, dz, w_crsk, bias, dx, st); fused = true; }
@@ -408,6 +405,7 @@ bool dgrad_folds_back_aside(const Geom& g, int dtype) {
   if (needs_cin_pad(g, dtype))
     return stem_dgrad_supported(g, dtype) && stem_wgrad_supported(g, dtype) && stem_dgrad_folds_back_aside(g);
   if (g.K % 4) return false;
+  if (ks_dgrad_taken(g, dtype)) return true;
   if (pw_dgrad_supported(g, dtype)) return gm_supported(g.M, g.Cout, g.Cin);
   return !rw_dgrad_supported(g, dtype) && (st_dgrad_supported(g, dtype) || win_dgrad_taken(g, dtype));
 }
@@ -709,6 +707,11 @@ convbn_status convbn_tune_fwd(const convbn_desc* desc, const void* x, const void
   if (wave_f32_supported(g, dt)) {   // one launch, as below
     const BnEpilogue bn{gamma, beta, mean, var, b, g.eps, w_folded, g.kH * g.kW, g.Cin, g.Cout};
     LAUNCH(launch_fprop_wave(g, x, W, nullptr, z, st, &bn));
+    return CONVBN_OK;
+  }
+  if (!needs_cin_pad(g, dt) && ks_fprop_taken(g, dt)) {   // few pixels: one launch, as below
+    const BnEpilogue bn{gamma, beta, mean, var, b, g.eps, w_folded, g.kH * g.kW, g.Cin, g.Cout};
+    LAUNCH(launch_fprop_win(g, x, W, nullptr, z, st, &bn));
     return CONVBN_OK;
   }
   if (!needs_cin_pad(g, dt) &&

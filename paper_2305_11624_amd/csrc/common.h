@@ -431,6 +431,9 @@ struct GmStride { int N, Ho, Wo, Hs, Ws, sh, sw; };
 bool win_supported(const Geom& g, int dtype);
 hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, const float* bias, void* z, hipStream_t st,
                             const BnEpilogue* bn = nullptr);
+// Few pixels: the launches above and below on small tiles whose reduction the waves of a workgroup split (conv_ks_impl.h)
+bool ks_fprop_taken(const Geom& g, int dtype);
+bool ks_dgrad_taken(const Geom& g, int dtype);
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st);
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
                      void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd = nullptr,
@@ -491,7 +494,7 @@ hipError_t launch_wgrad_win(const Geom& g, const void* x, const void* dz, float*
 
 // win_pair.hip : the two above as one launch, for problems whose workgroups fit the chip together; win_pair_splits() (at
 // most wgrad_win_splits()) fp32 copies of dw' and of r.
-bool win_pair_supported(const Geom& g, int dtype);
+bool win_pair_taken(const Geom& g, int dtype);
 int win_pair_splits(const Geom& g);
 hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const void* w_crsk, void* dx, float* dwf_part,
                            float* r_part, hipStream_t st);

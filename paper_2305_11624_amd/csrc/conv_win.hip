@@ -1,5 +1,7 @@
 // The window product as a launch of its own; its device code is in conv_win_impl.h.
-#include "conv_win_impl.h"
+#include "conv_ks_impl.h"
+
+#include <algorithm>
 
 namespace convbn {
 
@@ -7,8 +9,29 @@ using namespace win;
 
 namespace {
 
-struct WnPlan { int tm, tn, nst; bool flat; };
-WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv) {
+constexpr int KS_FEW = 6, KS_MANY = 48;
+// The tile of the wave-split product: the smallest whose workgroups are one round (3 x 3, 512 -> 512: 32 x 32 8.9 us, 64 x 32 11.3,
+// 64 x 64 14.3 where all three are; a second round takes as long as the first: 17.3).  None where 64 x 64 tiles are more
+// than that, or have fewer chunks than give six of the eight waves one (1 x 1, 88 -> 240 at 34 x 27 / 2, 13 images, forward: 5.0
+// on 128 x 64 tiles, 5.7), or where the deep-layer kernel has the layer and its chain is long (`deep`; 512 -> 512 at 6 x 6, 46
+// images, 72 chunks: 16.4 there, 17.7; 128 -> 128 at 28 x 28, 8 images, 18 chunks: 9.8 there, 8.3).
+struct KsTile { int tm, tn; };   // tm == 0: not taken
+KsTile ks_tile(int C, int R, int n, const int* M, const Window* cv, bool deep) {
+  constexpr int CUS = 256;
+  constexpr KsTile sizes[] = {{32, 32}, {64, 32}, {64, 64}};
+  int chunks = 0;
+  for (int i = 0; i < n; ++i) chunks = std::max(chunks, ceil_div(cv[i].kH * cv[i].kW * (C >> 3), CB / 8));
+  for (const KsTile& t : sizes) {
+    long long tiles = 0;
+    for (int i = 0; i < n; ++i)
+      if (cv[i].kH > 0) tiles += (long long)ceil_div(M[i], t.tm) * ceil_div(R, t.tn);
+    if (tiles > CUS) continue;
+    return t.tm * t.tn < 64 * 64 || (chunks >= KS_FEW && (chunks <= KS_MANY || !deep)) ? t : KsTile{0, 0};
+  }
+  return {0, 0};
+}
+struct WnPlan { int tm, tn, nst; bool flat; bool ks = false; };
+WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv, bool deep) {
   auto tiles = [&](int tm, int tn) {   // those with a product to compute
     long long t = 0;
     for (int i = 0; i < n; ++i)
@@ -16,6 +39,7 @@ WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv) {
     return t * ceil_div(R, tn);
   };
   const bool flat = C % CB != 0;
+  if (const KsTile t = ks_tile(C, R, n, M, cv, deep); t.tm) return {t.tm, t.tn, 0, true, true};
   // the largest tile that still gives most compute units one (as in conv_gm.hip); a tile of 128 channels only where the
   // last one is more than half full
   const bool wide = R % 128 == 0 || R % 128 > 64;
@@ -43,6 +67,25 @@ hipError_t launch_inst(WnParams& p, Side side, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int TM, int TN, class Side>
+__global__ __launch_bounds__(64 * NWAVES) void conv_ks_kernel(WnParams p, Side side) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  ks_body<TM, TN>(p, side, blockIdx.x, smem);
+}
+
+template <int TM, int TN, class Side>
+hipError_t launch_ks(WnParams& p, Side side, hipStream_t st) {
+  static LdsLimitOnce lds_once;
+  constexpr int lds = KsCfg<TM, TN>::LDS_BYTES;
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&conv_ks_kernel<TM, TN, Side>), lds); e != hipSuccess)
+    return e;
+  lay_out<TM, TN, true>(p);
+  int nside;
+  if constexpr (Side::BACK) nside = fold_back_side_blocks(side, 64 * NWAVES); else nside = fold_side_blocks(p.bn);
+  hipLaunchKernelGGL((conv_ks_kernel<TM, TN, Side>), dim3(p.nconv + nside), dim3(64 * NWAVES), lds, st, p, side);
+  return hipGetLastError();
+}
+
 // n problems that share the operands, in any order, as the parameters of a launch (no pointers)
 WnParams make_params(int C, int R, int n, const int* M, const Window* cv, size_t act_bytes, size_t wgt_bytes) {
   WnParams p{};
@@ -64,19 +107,23 @@ WnParams make_params(int C, int R, int n, const int* M, const Window* cv, size_t
 
 hipError_t launch_win(int C, int R, int n, const int* M, const Window* cv, const void* act, size_t act_bytes, const void* wgt,
                       size_t wgt_bytes, const float* bias, const BnEpilogue* bn, void* out, int relu, const void* mask,
-                      const void* add, hipStream_t st, const FoldBackArgs* fb = nullptr) {
+                      const void* add, hipStream_t st, bool deep, const FoldBackArgs* fb = nullptr) {
   if (n < 1 || n > MAXC || C % 8 || R % 8 || act_bytes >= OOB || wgt_bytes >= OOB) return hipErrorInvalidValue;
   WnParams p = make_params(C, R, n, M, cv, act_bytes, wgt_bytes);
   p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
   if (bn) p.bn = *bn;
   p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
-  const WnPlan pl = win_plan(C, R, n, M, cv);
+  const WnPlan pl = win_plan(C, R, n, M, cv, deep);
 #define WIN_CASE(TM_, TN_, NST_, F_) \
-  if (pl.tm == TM_ && pl.tn == TN_ && pl.nst == NST_ && pl.flat == F_) \
+  if (!pl.ks && pl.tm == TM_ && pl.tn == TN_ && pl.nst == NST_ && pl.flat == F_) \
     return fb ? launch_inst<TM_, TN_, NST_, F_>(p, *fb, st) : launch_inst<TM_, TN_, NST_, F_>(p, FoldSide{}, st);
   WIN_CASE(256, 128, 3, false) WIN_CASE(128, 128, 3, false) WIN_CASE(128, 64, 3, false) WIN_CASE(128, 64, 6, false)
   WIN_CASE(128, 128, 3, true) WIN_CASE(128, 64, 3, true) WIN_CASE(128, 64, 6, true)
 #undef WIN_CASE
+#define KS_CASE(TM_, TN_) \
+  if (pl.ks && pl.tm == TM_ && pl.tn == TN_) return fb ? launch_ks<TM_, TN_>(p, *fb, st) : launch_ks<TM_, TN_>(p, FoldSide{}, st);
+  KS_CASE(32, 32) KS_CASE(64, 32) KS_CASE(64, 64)
+#undef KS_CASE
   return hipErrorInvalidValue;
 }
 
@@ -110,6 +157,14 @@ void dgrad_class(const Geom& g, int a, int b, Window* cv, int* M) {
   *cv = c;
   *M = g.N * Hq * Wq;
 }
+Window fprop_window(const Geom& g) {
+  Window c{};
+  c.kH = g.kH; c.kW = g.kW; c.cph = g.ph; c.cpw = g.pw; c.csh = g.sh; c.csw = g.sw; c.aH = g.Hin; c.aW = g.Win;
+  c.a_n = g.Hin * g.Win * g.Cin; c.a_h = g.Win * g.Cin; c.a_w = g.Cin;
+  c.oHo = g.Hout; c.oWo = g.Wout;
+  c.wt_row = g.kW; c.wt_col = 1; c.wrow = g.K;
+  return c;
+}
 // residue classes that have positions, in rows and columns
 int classes_h(const Geom& g) { return g.sh < g.Hin ? g.sh : g.Hin; }
 int classes_w(const Geom& g) { return g.sw < g.Win ? g.sw : g.Win; }
@@ -127,16 +182,43 @@ bool win::dgrad_params(const Geom& g, WnParams* p) {
 }
 
 bool win_supported(const Geom& g, int dtype) { return sizes_fit(g, dtype); }
+bool ks_fprop_taken(const Geom& g, int dtype) {
+  if (!sizes_fit(g, dtype)) return false;
+  const Window c = fprop_window(g);
+  return ks_tile(g.Cin, g.Cout, 1, &g.M, &c, st_fprop_supported(g, dtype)).tm != 0;
+}
+namespace {
+struct KsGrad { bool taken; float us; };
+const KsGrad& ks_grad(const Geom& g) {
+  return planned<KsGrad>(g, CONVBN_BF16, [&] {
+    KsGrad r{};
+    WnParams p;
+    if (!dgrad_params(g, &p)) return r;
+    Window c[MAXC];
+    int M[MAXC];
+    for (int i = 0; i < p.ncls; ++i) { c[i] = p.c[i].cv; M[i] = p.c[i].M; }
+    const KsTile t = ks_tile(p.C, p.R, p.ncls, M, c, st_dgrad_supported(g, CONVBN_BF16));
+    if (t.tm == 0) {   // (another kernel's)
+      for (int i = 0; i < p.ncls; ++i) r.us = std::max(r.us, 5.5f + 0.2f * ceil_div(c[i].kH * c[i].kW * p.C, CB));
+      return r;
+    }
+    if (t.tm == 32) lay_out<32, 32, true>(p);
+    else if (t.tn == 32) lay_out<64, 32, true>(p);
+    else lay_out<64, 64, true>(p);
+    r.taken = true;
+    r.us = ks_us(t.tm, t.tn, p);
+    return r;
+  });
+}
+}  // namespace
+bool ks_dgrad_taken(const Geom& g, int dtype) { return sizes_fit(g, dtype) && ks_grad(g).taken; }
+float win::ks_dgrad_us(const Geom& g) { return ks_grad(g).us; }
 
 hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, const float* bias, void* z, hipStream_t st,
                             const BnEpilogue* bn) {
-  Window c{};
-  c.kH = g.kH; c.kW = g.kW; c.cph = g.ph; c.cpw = g.pw; c.csh = g.sh; c.csw = g.sw; c.aH = g.Hin; c.aW = g.Win;
-  c.a_n = g.Hin * g.Win * g.Cin; c.a_h = g.Win * g.Cin; c.a_w = g.Cin;
-  c.oHo = g.Hout; c.oWo = g.Wout;
-  c.wt_row = g.kW; c.wt_col = 1; c.wrow = g.K;
+  const Window c = fprop_window(g);
   return launch_win(g.Cin, g.Cout, 1, &g.M, &c, x, (size_t)g.Min * g.Cin * 2, w_krsc, (size_t)g.Cout * g.K * 2, bias, bn, z,
-                    g.post_relu, g.post_mask, g.post_add, st);
+                    g.post_relu, g.post_mask, g.post_add, st, st_fprop_supported(g, CONVBN_BF16));
 }
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st) {
   Window c[MAXC];
@@ -148,7 +230,7 @@ hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, c
     n = 0;
     fb = nullptr;
     return launch_win(g.Cout, g.Cin, k, M, c, dz, (size_t)g.M * g.Cout * 2, w_crsk, (size_t)g.Cout * g.K * 2, bias, nullptr, dx,
-                      g.post_relu, g.post_mask, g.post_add, st, f);
+                      g.post_relu, g.post_mask, g.post_add, st, st_dgrad_supported(g, CONVBN_BF16), f);
   };
   for (int a = 0; a < classes_h(g); ++a)
     for (int b = 0; b < classes_w(g); ++b) {

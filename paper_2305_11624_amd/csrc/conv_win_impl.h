@@ -115,6 +115,61 @@ struct WnCfg {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
+// ---- what a workgroup is for
+__device__ __forceinline__ int class_of(const WnParams& p, int wg) {
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < MAXC; ++i)
+    if (i < p.ncls && wg >= p.c[i].first) k = i;
+  return k;
+}
+// Positions that no tap reaches: block `block` of a class stores their rows, 16 bytes at a time.
+__device__ __forceinline__ void store_untapped(const WnParams& p, int k, int block) {
+  const Window cv = p.c[k].cv;
+  const int R8 = p.R >> 3;
+  const unsigned hw = (unsigned)(cv.oHo * cv.oWo), total = (unsigned)p.c[k].M * (unsigned)R8;
+  for (int e = 0; e < ZROWS; ++e) {
+    const unsigned i = ((unsigned)block * ZROWS + e) * (64 * NWAVES) + threadIdx.x;
+    if (i >= total) break;
+    const unsigned m = i / (unsigned)R8, ch = (i - m * R8) * 8;
+    const unsigned n = fdiv(m, p.c[k].dHW), rem = m - n * hw;
+    const unsigned ho = fdiv(rem, p.c[k].dW), wo = rem - ho * (unsigned)cv.oWo;
+    const size_t o = (size_t)cv.out_base + (size_t)n * cv.out_n + (size_t)ho * cv.out_h + (size_t)wo * cv.out_w + ch;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (p.bias) {
+      const float* b = p.bias + ch;
+      v = make_uint4(pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3]), pack_bf16x2(b[4], b[5]), pack_bf16x2(b[6], b[7]));
+    }
+    *reinterpret_cast<uint4*>(p.out + o) = post_op8(v, p.relu, p.mask, p.add, o);
+  }
+}
+// Workgroups are handed to the eight XCDs in turn (id % 8), and each XCD has its own L2, which what its workgroups share
+// should fit: the tiles are split into eight contiguous runs, along the channels where the weight is the larger operand
+// (an XCD then reads its channel tiles' rows and all activations), else along the pixels.  False: none left for this one.
+template <int TM, int TN>
+__device__ __forceinline__ bool tile_of(const WnParams& p, int k, int block, int& r0, int& m0) {
+  const int npt = (p.c[k].M + TM - 1) / TM, ntiles = npt * p.ntr;
+  const int tile = (block & 7) * ((ntiles + 7) >> 3) + (block >> 3);
+  if (tile >= min(ntiles, ((block & 7) + 1) * ((ntiles + 7) >> 3))) return false;
+  const int q = (int)fdiv((unsigned)tile, p.c[k].dTiles);
+  const int ptile = p.by_channel ? tile - q * npt : q, ctile = p.by_channel ? q : tile - q * p.ntr;
+  r0 = ctile * TN;
+  m0 = ptile * TM;
+  return true;
+}
+// bias and scale of channel r0 + c of a tile
+template <int TN>
+__device__ __forceinline__ void bias_and_scale(const WnParams& p, int r0, int c, float* biasl) {
+  const int ch = min(r0 + c, p.R - 1);
+  float bias_v = p.bias ? p.bias[ch] : 0.f, scale_v = 1.f;
+  if (p.bn.gamma) {   // Z = s (w (*) X) + b' (Sec. 3.3), s and b' worked out here
+    scale_v = p.bn.gamma[ch] / sqrtf(p.bn.var[ch] + p.bn.eps);
+    bias_v = ((p.bn.b ? p.bn.b[ch] : 0.f) - p.bn.mean[ch]) * scale_v + p.bn.beta[ch];
+  }
+  biasl[c] = bias_v;
+  biasl[TN + c] = scale_v;
+}
+
 // Workgroup `wg` of the product (and, behind its workgroups, of the fold or the fold-back on the side); smem: WnCfg::LDS_BYTES
 template <int TM, int TN, int NST, bool FLAT, class Side>
 __device__ __forceinline__ void body(const WnParams& p, const Side& side, const int wg, unsigned char* smem) {
@@ -131,10 +186,7 @@ __device__ __forceinline__ void body(const WnParams& p, const Side& side, const 
   }
   float* biasl = reinterpret_cast<float*>(smem + Cfg::OFF_BIAS);
 
-  int k = 0;
-#pragma unroll
-  for (int i = 1; i < MAXC; ++i)
-    if (i < p.ncls && wg >= p.c[i].first) k = i;
+  const int k = class_of(p, wg);
   const Window cv = p.c[k].cv;
   const FastDiv dHW = p.c[k].dHW, dW = p.c[k].dW;
   const int M = p.c[k].M, nchunks = p.c[k].nchunks;
@@ -143,48 +195,16 @@ __device__ __forceinline__ void body(const WnParams& p, const Side& side, const 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;      // pixel group, channel group
-  if (nchunks == 0) {   // a class that no tap reaches: its pixels' rows, 16 bytes at a time
-    const int R8 = p.R >> 3;
-    const unsigned hw = (unsigned)(cv.oHo * cv.oWo), total = (unsigned)M * (unsigned)R8;
-    for (int e = 0; e < ZROWS; ++e) {
-      const unsigned i = ((unsigned)block * ZROWS + e) * (64 * NWAVES) + threadIdx.x;
-      if (i >= total) break;
-      const unsigned m = i / (unsigned)R8, ch = (i - m * R8) * 8;
-      const unsigned n = fdiv(m, dHW), rem = m - n * hw;
-      const unsigned ho = fdiv(rem, dW), wo = rem - ho * (unsigned)cv.oWo;
-      const size_t o = (size_t)cv.out_base + (size_t)n * cv.out_n + (size_t)ho * cv.out_h + (size_t)wo * cv.out_w + ch;
-      uint4 v = make_uint4(0u, 0u, 0u, 0u);
-      if (p.bias) {
-        const float* b = p.bias + ch;
-        v = make_uint4(pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3]), pack_bf16x2(b[4], b[5]), pack_bf16x2(b[6], b[7]));
-      }
-      *reinterpret_cast<uint4*>(p.out + o) = post_op8(v, p.relu, p.mask, p.add, o);
-    }
+  if (nchunks == 0) {
+    store_untapped(p, k, block);
     return;
   }
-
-  // Workgroups are handed to the eight XCDs in turn (id % 8), and each XCD has its own L2, which what its workgroups share
-  // should fit: the tiles are split into eight contiguous runs, along the channels where the weight is the larger operand
-  // (an XCD then reads its channel tiles' rows and all activations), else along the pixels.
-  const int npt = (M + TM - 1) / TM, ntiles = npt * p.ntr;
-  const int tile = (block & 7) * ((ntiles + 7) >> 3) + (block >> 3);
-  if (tile >= min(ntiles, ((block & 7) + 1) * ((ntiles + 7) >> 3))) return;
-  const int q = (int)fdiv((unsigned)tile, p.c[k].dTiles);
-  const int ptile = p.by_channel ? tile - q * npt : q, ctile = p.by_channel ? q : tile - q * p.ntr;
-  const int r0 = ctile * TN, m0 = ptile * TM;
+  int r0, m0;
+  if (!tile_of<TM, TN>(p, k, block, r0, m0)) return;
   const __amdgpu_buffer_rsrc_t act_rsrc = make_rsrc(p.act, p.act_bytes);
   const __amdgpu_buffer_rsrc_t wgt_rsrc = make_rsrc(p.wgt, p.wgt_bytes);
 
-  if (tid < TN) {
-    const int ch = min(r0 + tid, p.R - 1);
-    float bias_v = p.bias ? p.bias[ch] : 0.f, scale_v = 1.f;
-    if (p.bn.gamma) {   // Z = s (w (*) X) + b' (Sec. 3.3), s and b' worked out here
-      scale_v = p.bn.gamma[ch] / sqrtf(p.bn.var[ch] + p.bn.eps);
-      bias_v = ((p.bn.b ? p.bn.b[ch] : 0.f) - p.bn.mean[ch]) * scale_v + p.bn.beta[ch];
-    }
-    biasl[tid] = bias_v;
-    biasl[TN + tid] = scale_v;
-  }
+  if (tid < TN) bias_and_scale<TN>(p, r0, tid, biasl);
 
   // ---- copies of this wave: unit u covers rows 8 u .. 8 u + 7 of its tile; lane l writes LDS granule l % 8 of row
   // 8 u + l / 8 and fetches the granule that belongs there, (l % 8) ^ key(row), key = (row / 2) % 8: u = wave + 8 j, so
@@ -430,6 +450,8 @@ inline void lay_out(WnParams& p) {
 
 // The parameters of an input gradient whose residue classes fit one launch (no pointers); false: they do not.
 bool dgrad_params(const Geom& g, WnParams* p);
+// An estimate of the input gradient as a launch of its own (0: its residue classes are more than one).
+float ks_dgrad_us(const Geom& g);
 
 }  // namespace win
 }  // namespace convbn

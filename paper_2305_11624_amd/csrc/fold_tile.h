@@ -297,12 +297,12 @@ inline int fold_back_side_blocks(FoldBackArgs& a, int threads) {
   return ceil_div(a.Cout, threads / a.per);
 }
 // smem: FOLD_BACK_SIDE_BYTES(THREADS)
-template <int THREADS, RowKind ROW = ROW_VEC>
+template <int THREADS, RowKind ROW = ROW_VEC, int FLIGHT = 16>
 __device__ __forceinline__ void fold_back_side(const FoldBackArgs& a, int wg, unsigned char* smem) {
   const int group = (int)threadIdx.x / a.per, tid = (int)threadIdx.x - group * a.per;
   float4* const red4 = reinterpret_cast<float4*>(smem);
   float* const red = reinterpret_cast<float*>(smem + THREADS * 16);
-  fold_back_row<bf16_t, 8, ROW>(a, wg * (THREADS / a.per) + group, tid, a.per, red4 + group * a.per, red + group * (a.per >> 5));
+  fold_back_row<bf16_t, FLIGHT, ROW>(a, wg * (THREADS / a.per) + group, tid, a.per, red4 + group * a.per, red + group * (a.per >> 5));
 }
 
 }  // namespace convbn

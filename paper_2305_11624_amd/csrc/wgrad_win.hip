@@ -7,6 +7,8 @@ using namespace wgw;
 
 namespace {
 
+constexpr int CUS = 256;   // a workgroup each (the ring fills the LDS)
+
 // Slices of the pixels, about `workgroups` in all.  Every slice is an fp32 copy of dw': written here, read by the fold-back, and
 // workspace that the caller holds.  So a slice has at least 128 pixels (two chunks) while the copies stay within 4 MB, else at
 // least 256 (weight gradient and fold-back with slices of 128 and of 256 pixels: 256 -> 128 channels at 56 x 56, 4 images, 98 or 49
@@ -28,21 +30,36 @@ void slice_up(WwParams& p, int workgroups) {
   p.slices = ceil_div(p.M, p.per);
 }
 
-WwPlan work_out_plan(const Geom& g) {
-  WwPlan pl{};
-  WwParams& p = pl.p;
+// The tile: small ones have longer slices, hence fewer copies of dw' to write and to sum; large ones read less per multiply.
+// The estimate: chunks of a workgroup's pixels, copies written at 4 TB/s (read, by the fold-back: 5 TB/s).  Weight gradient and
+// fold-back, us, 128 x 128 and 64 x 64 tiles: 1024 -> 256 at 15 x 15, 11 images 16.1, 12.1; 3 x 3, 128 -> 128 at 28 x 28, 8 images
+// 19.3, 15.5; 256 -> 1024 at 14 x 14, 32 images 21.0, 16.7; 3 x 3, 72 -> 136 at 27 x 33, 5 images 14.8, 12.0; a long range, transposed
+// 4 x 4 / 2, 256 -> 128 at 28 x 28, 20 images, the pass: 84.7, 92.1.
+WwPlan work_out_plan(const Geom& g, int workgroups) {
+  WwPlan best{};
+  WwParams q{};
   const size_t xb = (size_t)g.Min * g.Cin * 2, zb = (size_t)g.M * g.Cout * 2;
-  if (g.Cin % 8 || g.Cout % 8 || xb >= OOB || zb >= OOB) return pl;
-  p.x_bytes = (unsigned)xb; p.dz_bytes = (unsigned)zb;
-  p.Cin = g.Cin; p.Co = g.Cout; p.K = g.K; p.M = g.M; p.H = g.Hin; p.W = g.Win; p.Ho = g.Hout; p.Wo = g.Wout;
-  p.kH = g.kH; p.kW = g.kW; p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw;
-  pl.ta = g.Cout > 64 ? 128 : 64;
-  pl.tb = g.K > 64 ? 128 : 64;
-  p.nta = ceil_div(g.Cout, pl.ta);
-  p.ntb = ceil_div(g.K, pl.tb);
-  slice_up(p, 256);   // one workgroup per compute unit (the ring fills its LDS), one round
-  pl.ok = true;
-  return pl;
+  if (g.Cin % 8 || g.Cout % 8 || xb >= OOB || zb >= OOB) return best;
+  q.x_bytes = (unsigned)xb; q.dz_bytes = (unsigned)zb;
+  q.Cin = g.Cin; q.Co = g.Cout; q.K = g.K; q.M = g.M; q.H = g.Hin; q.W = g.Win; q.Ho = g.Hout; q.Wo = g.Wout;
+  q.kH = g.kH; q.kW = g.kW; q.sh = g.sh; q.sw = g.sw; q.ph = g.ph; q.pw = g.pw;
+  for (int ta = 64; ta <= (g.Cout > 64 ? 128 : 64); ta += 64)
+    for (int tb = 64; tb <= (g.K > 64 ? 128 : 64); tb += 64) {
+      WwPlan pl{};
+      pl.p = q;
+      pl.ta = ta; pl.tb = tb;
+      pl.p.nta = ceil_div(g.Cout, ta);
+      pl.p.ntb = ceil_div(g.K, tb);
+      slice_up(pl.p, workgroups);
+      const int total = pl.p.nta * pl.p.ntb * pl.p.slices;
+      const float copies = (float)pl.p.slices * g.Cout * g.K * 4.f * 1e-6f;   // MB
+      const float chunk = ta == tb ? (ta == 64 ? 0.65f : 0.85f) : 0.5f;
+      pl.us = 4.f + ceil_div(total, CUS) * ceil_div(pl.p.per, ta + tb == 128 ? 128 : 64) * chunk + copies * 0.25f;
+      pl.fold_us = 3.f + copies * 0.2f;
+      pl.ok = total <= workgroups || workgroups >= CUS;
+      if (pl.ok && (!best.ok || pl.us + pl.fold_us < best.us + best.fold_us)) best = pl;
+    }
+  return best;
 }
 template <int TA, int TB>
 __global__ __launch_bounds__(64 * NWAVES) void wgrad_win_kernel(WwParams p) {
@@ -63,12 +80,11 @@ hipError_t launch_inst(const WwParams& p, hipStream_t st) {
 }  // namespace
 
 const WwPlan& wgw::plan(const Geom& g) {
-  return planned<WwPlan>(g, CONVBN_BF16, [&] { return work_out_plan(g); });
+  return planned<WwPlan>(g, CONVBN_BF16, [&] { return work_out_plan(g, CUS); });
 }
-WwParams wgw::limited(const Geom& g, int workgroups) {
-  WwParams p = plan(g).p;
-  slice_up(p, workgroups);
-  return p;
+bool wgw::limited(const Geom& g, int workgroups, WwPlan* pl) {
+  *pl = work_out_plan(g, workgroups);
+  return pl->ok;
 }
 
 bool wgrad_win_supported(const Geom& g, int dtype) { return dtype == CONVBN_BF16 && plan(g).ok; }

@@ -281,10 +281,11 @@ __device__ __forceinline__ void body(const WwParams& p, const int wg, unsigned c
   }
 }
 
-struct WwPlan { bool ok; int ta, tb; WwParams p; };
+// us: an estimate of the launch, fold_us: of what summing its copies takes (see wgrad_win.hip)
+struct WwPlan { bool ok; int ta, tb; float us, fold_us; WwParams p; };
 const WwPlan& plan(const Geom& g);
-// the same plan with its workgroups limited to `workgroups` (fewer, longer slices of the pixels)
-WwParams limited(const Geom& g, int workgroups);
+// the plan for at most that many workgroups; false: there is none
+bool limited(const Geom& g, int workgroups, WwPlan* pl);
 
 }  // namespace wgw
 }  // namespace convbn

@@ -1,9 +1,9 @@
-// Both gradient passes of a small bf16 block in one launch: the window product's input gradient (conv_win_impl.h) and the
+// Both gradient passes of a small bf16 block in one launch: the wave-split input gradient (conv_ks_impl.h) and the
 // window weight gradient (wgrad_win_impl.h).  They are independent, and alone each leaves most compute units idle and lasts
-// as long as one workgroup's chain of copies (about 7 and 10 us for 256 -> 512 channels, 30 x 30 / 2, 6 images): together
-// they take as long as the longer one.  A workgroup of either has a compute unit to itself (its ring fills the LDS), so
-// this is for problems whose workgroups fit the chip together; the weight gradient's pixel slices are cut to that.
-#include "conv_win_impl.h"
+// as long as one workgroup's chain of copies: together they take as long as the longer one.  A workgroup of either has
+// a compute unit to itself (the LDS), so this is for problems whose workgroups fit the chip together; the weight
+// gradient's pixel slices are cut to that, and of the tiles of either those are taken whose longer chain is shortest.
+#include "conv_ks_impl.h"
 #include "wgrad_win_impl.h"
 
 namespace convbn {
@@ -12,46 +12,67 @@ namespace {
 
 constexpr int CUS = 256;
 
-template <bool FLAT, int TA, int TB>
+template <int TM, int TN, int TA, int TB>
 __global__ __launch_bounds__(512) void win_pair_kernel(wgw::WwParams w, win::WnParams d, int nw) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   if ((int)blockIdx.x < nw) wgw::body<TA, TB>(w, blockIdx.x, smem);
-  else win::body<128, 64, 6, FLAT>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
+  else win::ks_body<TM, TN>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
 }
 
-struct PairPlan { bool ok, flat; int ta, tb, nw; wgw::WwParams w; win::WnParams d; };
+struct PairPlan { bool ok; int tm, tn, ta, tb, nw; float us; wgw::WwParams w; win::WnParams d; };
+template <int TM, int TN>
+void consider(const Geom& g, PairPlan& best) {
+  PairPlan pl{};
+  if (!win::dgrad_params(g, &pl.d)) return;
+  win::lay_out<TM, TN, true>(pl.d);
+  int product = pl.d.nconv;   // (positions that no tap reaches: short workgroups, behind the others)
+  for (int i = 0; i < pl.d.ncls; ++i)
+    if (pl.d.c[i].nchunks == 0 && pl.d.c[i].first < product) product = pl.d.c[i].first;
+  if (product >= CUS) return;
+  wgw::WwPlan w{};
+  if (!wgw::limited(g, CUS - product, &w)) return;
+  const int total = w.p.nta * w.p.ntb * w.p.slices;
+  pl.nw = ceil_div(total, 8) * 8;
+  if (pl.nw + product > CUS) return;
+  const float du = win::ks_us(TM, TN, pl.d);
+  pl.ok = true;
+  pl.tm = TM; pl.tn = TN; pl.ta = w.ta; pl.tb = w.tb; pl.w = w.p;
+  pl.us = (du > w.us ? du : w.us) + w.fold_us;
+  if (!best.ok || pl.us < best.us) best = pl;
+}
 PairPlan work_out_plan(const Geom& g) {
   PairPlan pl{};
-  const wgw::WwPlan& w = wgw::plan(g);
-  if (!w.ok || !win::dgrad_params(g, &pl.d)) return pl;
-  pl.flat = pl.d.C % win::CB != 0;
-  if (pl.flat) win::lay_out<128, 64, true>(pl.d); else win::lay_out<128, 64, false>(pl.d);
-  if (pl.d.nconv > CUS / 2) return pl;
-  pl.ta = w.ta; pl.tb = w.tb;
-  pl.w = wgw::limited(g, CUS - pl.d.nconv);
-  const int total = pl.w.nta * pl.w.ntb * pl.w.slices;
-  if (total + pl.d.nconv > CUS) return pl;
-  pl.nw = ceil_div(total, 8) * 8;
-  pl.ok = true;
+  if (!wgw::plan(g).ok) return pl;
+  consider<32, 32>(g, pl);
+  consider<64, 32>(g, pl);
+  consider<64, 64>(g, pl);
   return pl;
 }
 const PairPlan& plan(const Geom& g) {
   return planned<PairPlan>(g, CONVBN_BF16, [&] { return work_out_plan(g); });
 }
 
-template <bool FLAT, int TA, int TB>
+template <int TM, int TN, int TA, int TB>
 hipError_t launch_inst(const wgw::WwParams& w, const win::WnParams& d, int nw, hipStream_t st) {
   static LdsLimitOnce lds_once;
-  constexpr int a = wgw::WwCfg<TA, TB>::LDS_BYTES, b = win::WnCfg<128, 64, 6>::LDS_BYTES, lds = a > b ? a : b;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&win_pair_kernel<FLAT, TA, TB>), lds);
+  constexpr int a = wgw::WwCfg<TA, TB>::LDS_BYTES, b = win::KsCfg<TM, TN>::LDS_BYTES, lds = a > b ? a : b;
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&win_pair_kernel<TM, TN, TA, TB>), lds);
       e != hipSuccess) return e;
-  hipLaunchKernelGGL((win_pair_kernel<FLAT, TA, TB>), dim3(nw + d.nconv), dim3(512), lds, st, w, d, nw);
+  hipLaunchKernelGGL((win_pair_kernel<TM, TN, TA, TB>), dim3(nw + d.nconv), dim3(512), lds, st, w, d, nw);
   return hipGetLastError();
 }
 
 }  // namespace
 
-bool win_pair_supported(const Geom& g, int dtype) { return dtype == CONVBN_BF16 && plan(g).ok; }
+// Against a launch each, the second of which takes the fold-back along.  The gradients, us, one launch and two: 3 x 3,
+// 256 -> 256 at 18 x 18, 1 image 14.7, 18.2; 88 -> 240 at 34 x 27 / 2, 13 images 10.4, 12.1; 2048 -> 512 at 9 x 9, 3 images 15.8, 22.4;
+// where the weight gradient is left too few compute units: 3 x 3, 128 -> 128 at 28 x 28, 8 images 22.6, 17.7
+bool win_pair_taken(const Geom& g, int dtype) {
+  if (dtype != CONVBN_BF16 || !plan(g).ok) return false;
+  const wgw::WwPlan& w = wgw::plan(g);
+  const float d = win::ks_dgrad_us(g);
+  return plan(g).us <= w.us + (d > w.fold_us ? d : w.fold_us) + 1.5f;
+}
 int win_pair_splits(const Geom& g) { return plan(g).w.slices; }
 hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const void* w_crsk, void* dx, float* part,
                            float* r_part, hipStream_t st) {
@@ -62,10 +83,13 @@ hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const v
   w.x = (const bf16_t*)x; w.dz = (const bf16_t*)dz; w.part = part; w.r_part = r_part;
   d.act = (const bf16_t*)dz; d.wgt = (const bf16_t*)w_crsk; d.out = (bf16_t*)dx;
   d.relu = g.post_relu; d.mask = (const bf16_t*)g.post_mask; d.add = (const bf16_t*)g.post_add;
-#define PAIR_CASE(F_, TA_, TB_) if (pl.flat == F_ && pl.ta == TA_ && pl.tb == TB_) return launch_inst<F_, TA_, TB_>(w, d, pl.nw, st);
-  PAIR_CASE(false, 128, 128) PAIR_CASE(false, 128, 64) PAIR_CASE(false, 64, 128) PAIR_CASE(false, 64, 64)
-  PAIR_CASE(true, 128, 128) PAIR_CASE(true, 128, 64) PAIR_CASE(true, 64, 128) PAIR_CASE(true, 64, 64)
+#define PAIR_TILE(TM_, TN_, TA_, TB_) \
+  if (pl.tm == TM_ && pl.tn == TN_ && pl.ta == TA_ && pl.tb == TB_) return launch_inst<TM_, TN_, TA_, TB_>(w, d, pl.nw, st);
+#define PAIR_CASE(TM_, TN_) \
+  PAIR_TILE(TM_, TN_, 64, 64) PAIR_TILE(TM_, TN_, 128, 64) PAIR_TILE(TM_, TN_, 64, 128) PAIR_TILE(TM_, TN_, 128, 128)
+  PAIR_CASE(32, 32) PAIR_CASE(64, 32) PAIR_CASE(64, 64)
 #undef PAIR_CASE
+#undef PAIR_TILE
   return hipErrorInvalidValue;
 }
 
