@@ -7,7 +7,7 @@
 // every wave copies its own operand stages (16 channels of 32 pixels and 32 output channels, 4 KB) into its own part of
 // the LDS.  Measured on the forward pass above: one thread per output element 452 us; operands loaded straight into
 // registers (a lane owns a row, the 64 lanes of a load touch 64 cache lines, and the address units set the pace) 13.7 us;
-// this way 11.2, of which 3 us are multiplies at full rate and about 4 what any launch takes.
+// this way 11, of which 3 us are multiplies at full rate and about 4 what any launch takes.
 // A workgroup's pixels all belong to one residue class of input positions in a strided input gradient, so no multiply
 // is spent on taps that do not reach them.
 #include "common.h"
@@ -19,8 +19,10 @@ namespace {
 constexpr unsigned OOB = 0x80000000u;   // beyond any buffer: the load returns zeros
 constexpr int KS = 8;                   // waves of a workgroup = slices of its reduction
 constexpr int STAGE = 4096;             // bytes of an operand stage: 64 rows (pixels, output channels) of 16 channels
-constexpr int WAVE_LDS = 2 * STAGE;     // two stages: the copies of one land while the other is multiplied (three or four
-                                        // leave one workgroup per compute unit: 35 -> 43 us for the step above)
+constexpr int WAVE_LDS = STAGE;         // one: the next step's copies are asked for as soon as this one's operands are in registers.
+                                        // With 33 KB of LDS and at most 80 registers three workgroups share a compute unit, and
+                                        // their waves cover one another (64 -> 64, 28 x 28, 8 images, a step: two stages and
+                                        // two workgroups 34.7 us, 31.5; 25 -> 87 at 23 x 17, 8 images 44.6, 33.4)
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -190,10 +192,10 @@ __device__ __forceinline__ void conv_body(const WvParams& p, const int block, co
     const unsigned read_row = lds_off(mine) + (unsigned)l32 * 64u;
     const unsigned sw = (unsigned)((l32 >> 2) & 3);
     const unsigned g0 = read_row + (((unsigned)half ^ sw) * 16u), g1 = read_row + (((2u + half) ^ sw) * 16u);
-    auto copy = [&](int buf) {
+    auto copy = [&] {
       const int g = cc * 4 + gran;
       const bool in = g * 4 < p.C;
-      unsigned char* const dst = mine + buf * STAGE;
+      unsigned char* const dst = mine;
 #pragma unroll
       for (int i = 0; i < 2; ++i) dma16(ra, in ? aoff[i] + g * 16u : OOB, dst + i * 1024);
 #pragma unroll
@@ -202,17 +204,12 @@ __device__ __forceinline__ void conv_body(const WvParams& p, const int block, co
     };
     const int last_full = (p.C & 15) == 0 || (p.C & 15) > 8;   // the last step of a tap has more than 8 channels
     int mc = cc;                                              // channels step that is multiplied
-    if (n_mine > 0) copy(0);
+    if (n_mine > 0) copy();
     for (int s = 0; s < n_mine; ++s) {
-      const unsigned buf = (unsigned)(s & 1) * STAGE;
-      if (s + 1 < n_mine) {
-        copy((s + 1) & 1);
-        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");   // all but the four copies of the next step
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       u32x4 x0, w0, x1, w1;
-      lds_read_stage(g0 + buf, g1 + buf, x0, w0, x1, w1);
+      lds_read_stage(g0, g1, x0, w0, x1, w1);
+      if (s + 1 < n_mine) copy();
       acc = mul(w0, x0, acc);
       if (mc + 1 < nch || last_full) acc = mul(w1, x1, acc);
       if (++mc == nch) mc = 0;
@@ -333,7 +330,7 @@ struct WgParams {
 
 template <int TG>
 __device__ __forceinline__ void wgrad_body(const WgParams& p, const int block, unsigned char* smem) {
-  constexpr int WD = 4;   // pixel pairs in flight
+  constexpr int WD = TG == 3 ? 3 : 4;   // pixel pairs in flight
   const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int t = block;
@@ -434,18 +431,18 @@ __device__ __forceinline__ void wgrad_body(const WgParams& p, const int block, u
 constexpr int SMEM = KS * WAVE_LDS + 256;
 
 template <bool WHOLE>
-__global__ __launch_bounds__(64 * KS) void wave_conv_kernel(WvParams p) {
+__global__ __launch_bounds__(64 * KS, 6) void wave_conv_kernel(WvParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   conv_body<WHOLE>(p, blockIdx.x, gridDim.x, smem);
 }
 template <int TG>
-__global__ __launch_bounds__(64 * KS) void wave_wgrad_kernel(WgParams p) {
+__global__ __launch_bounds__(64 * KS, 6) void wave_wgrad_kernel(WgParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   wgrad_body<TG>(p, blockIdx.x, smem);
 }
 // The two gradient passes are independent: one launch, the weight gradient's workgroups (the longer ones) first.
 template <bool WHOLE, int TG>
-__global__ __launch_bounds__(64 * KS) void wave_pair_kernel(WgParams g, WvParams d, int ng) {
+__global__ __launch_bounds__(64 * KS, 6) void wave_pair_kernel(WgParams g, WvParams d, int ng) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   if ((int)blockIdx.x < ng) wgrad_body<TG>(g, blockIdx.x, smem);
   else conv_body<WHOLE>(d, blockIdx.x - ng, gridDim.x - ng, smem);
@@ -489,11 +486,11 @@ constexpr long long MAX_BLOCKS = 0xffffffffLL / (64 * KS);   // a launch has few
 int tap_group(const Geom& g) { return g.kW == 3 ? 3 : 1; }
 struct WgSplit { int slices, per; };
 WgSplit wgrad_split(const Geom& g) {
-  // two workgroups per compute unit, no slice shorter than 64 pixels (four steps of a wave), and no more fp32 copies of
+  // one and a half workgroups per compute unit beside the input gradient's, no slice shorter than 64 pixels (four steps of a wave), and no more fp32 copies of
   // dw' than 16 MB: the fold-back reads them all
   const int units = ceil_div(g.Cin, 32) * ceil_div(g.Cout, 32) * ceil_div(g.kH * g.kW, tap_group(g));
   const size_t copy = (size_t)g.Cout * g.K * 4;
-  int want = ceil_div(512, units);
+  int want = ceil_div(384, units);
   const int most = (int)(((size_t)16 << 20) / copy);
   if (want > most) want = most;
   if (want > ceil_div(g.M, 64)) want = ceil_div(g.M, 64);
