@@ -59,6 +59,7 @@ struct Geom {
   const void* post_mask;
   const void* post_add;
   const struct FoldBackArgs* fold_back;   // an input gradient: the fold-back its launch takes along (fold_tile.h), or null
+  const struct FoldBackTArgs* fold_back_t;   // ... a transposed block's (fold_back_t_tile.h; the window product)
   const void* add_out;   // the descriptor's addends (CONVBN_ACT_ADD_OUT / _IN), null where the bit is not set
   const void* add_in;
 };
@@ -284,6 +285,13 @@ hipError_t launch_fold_t(int dtype, int Ci, int Co, int taps, const void* W, con
 int fold_back_t_chunks(int Ci, int Co, int taps, int nsplit);   // rows of dot_part ([chunks][Co] fp32 scratch)
 // dz [zrows.M][Co] gives r = sum dZ, through r_part ([colsum_parts(zrows)][Co] fp32 scratch).
 // gamma == NULL (Eval path): dW = sum of the partial copies only; dz, the scratch and the other outputs are not touched.
+// Its arguments where it rides in another launch (false: it cannot), and what then is left of it.
+bool fold_back_t_side(int dtype, int Ci, int Co, int taps, const float* dwf_part, int nsplit, const Geom& zrows, const void* dz,
+                      float* r_part, const void* W, const float* gamma, const float* var, float eps, float* dot_part, void* dW,
+                      struct FoldBackTArgs* a);
+hipError_t launch_fold_back_t_finish(int Ci, int Co, int taps, int nsplit, const Geom& zrows, const float* r_part, const float* b,
+                                     const float* gamma, const float* mean, const float* var, float eps, const float* dot_part,
+                                     float* db, float* dgamma, float* dbeta, hipStream_t st);
 hipError_t launch_fold_back_t(int dtype, int Ci, int Co, int taps, const float* dwf_part, int nsplit,
                               const Geom& zrows, const void* dz, float* r_part, const void* W, const float* b,
                               const float* gamma, const float* mean, const float* var, float eps, float* dot_part, void* dW,

@@ -33,7 +33,7 @@ struct KsCfg {
   static constexpr int LDS_BYTES = OFF_BIAS + 2 * TN * 4;
   static constexpr int GRANULES = TM * TN / 8;                       // 16-byte stores of a tile, one a thread
   static_assert(TM * TN * 4 <= STAGE && GRANULES <= 64 * NWAVES, "a wave's sums take the place of its chunks");
-  static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES, "what folds on the side");
+  static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES && 2 * FBT_SMEM <= LDS_BYTES, "what folds on the side");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 

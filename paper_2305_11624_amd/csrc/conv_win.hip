@@ -44,7 +44,8 @@ WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv, bool deep) 
   // last one is more than half full
   const bool wide = R % 128 == 0 || R % 128 > 64;
   if (wide && !flat && tiles(256, 128) >= 160) return {256, 128, 3, false};
-  if (wide && tiles(128, 128) >= 160) return {128, 128, 3, flat};
+  // (four stages: 512 <- 256 x 16 taps at 14 x 14, 32 images, 34.7 us with three, 33.7; granules over tap borders have no use for it)
+  if (wide && tiles(128, 128) >= 160) return {128, 128, flat ? 3 : 4, flat};
   return {128, 64, tiles(128, 64) > 256 ? 3 : 6, flat};
 }
 
@@ -107,7 +108,8 @@ WnParams make_params(int C, int R, int n, const int* M, const Window* cv, size_t
 
 hipError_t launch_win(int C, int R, int n, const int* M, const Window* cv, const void* act, size_t act_bytes, const void* wgt,
                       size_t wgt_bytes, const float* bias, const BnEpilogue* bn, void* out, int relu, const void* mask,
-                      const void* add, hipStream_t st, bool deep, const FoldBackArgs* fb = nullptr) {
+                      const void* add, hipStream_t st, bool deep, const FoldBackArgs* fb = nullptr,
+                      const FoldBackTArgs* fbt = nullptr) {
   if (n < 1 || n > MAXC || C % 8 || R % 8 || act_bytes >= OOB || wgt_bytes >= OOB) return hipErrorInvalidValue;
   WnParams p = make_params(C, R, n, M, cv, act_bytes, wgt_bytes);
   p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
@@ -116,12 +118,14 @@ hipError_t launch_win(int C, int R, int n, const int* M, const Window* cv, const
   const WnPlan pl = win_plan(C, R, n, M, cv, deep);
 #define WIN_CASE(TM_, TN_, NST_, F_) \
   if (!pl.ks && pl.tm == TM_ && pl.tn == TN_ && pl.nst == NST_ && pl.flat == F_) \
-    return fb ? launch_inst<TM_, TN_, NST_, F_>(p, *fb, st) : launch_inst<TM_, TN_, NST_, F_>(p, FoldSide{}, st);
-  WIN_CASE(256, 128, 3, false) WIN_CASE(128, 128, 3, false) WIN_CASE(128, 64, 3, false) WIN_CASE(128, 64, 6, false)
+    return fb ? launch_inst<TM_, TN_, NST_, F_>(p, *fb, st) : fbt ? launch_inst<TM_, TN_, NST_, F_>(p, *fbt, st)                \
+                                                                  : launch_inst<TM_, TN_, NST_, F_>(p, FoldSide{}, st);
+  WIN_CASE(256, 128, 3, false) WIN_CASE(128, 128, 4, false) WIN_CASE(128, 64, 3, false) WIN_CASE(128, 64, 6, false)
   WIN_CASE(128, 128, 3, true) WIN_CASE(128, 64, 3, true) WIN_CASE(128, 64, 6, true)
 #undef WIN_CASE
 #define KS_CASE(TM_, TN_) \
-  if (pl.ks && pl.tm == TM_ && pl.tn == TN_) return fb ? launch_ks<TM_, TN_>(p, *fb, st) : launch_ks<TM_, TN_>(p, FoldSide{}, st);
+  if (pl.ks && pl.tm == TM_ && pl.tn == TN_) \
+    return fb ? launch_ks<TM_, TN_>(p, *fb, st) : fbt ? launch_ks<TM_, TN_>(p, *fbt, st) : launch_ks<TM_, TN_>(p, FoldSide{}, st);
   KS_CASE(32, 32) KS_CASE(64, 32) KS_CASE(64, 64)
 #undef KS_CASE
   return hipErrorInvalidValue;
@@ -218,7 +222,7 @@ hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, co
                             const BnEpilogue* bn) {
   const Window c = fprop_window(g);
   return launch_win(g.Cin, g.Cout, 1, &g.M, &c, x, (size_t)g.Min * g.Cin * 2, w_krsc, (size_t)g.Cout * g.K * 2, bias, bn, z,
-                    g.post_relu, g.post_mask, g.post_add, st, st_fprop_supported(g, CONVBN_BF16));
+                    g.post_relu, g.post_mask, g.post_add, st, st_fprop_supported(g, CONVBN_BF16), nullptr, g.fold_back_t);
 }
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st) {
   Window c[MAXC];

@@ -19,7 +19,7 @@
 //  * A forward launch given the unfolded weight applies s and b' in the epilogue and folds on the side (fold_tile.h).
 #pragma once
 #include "common.h"
-#include "fold_tile.h"
+#include "fold_back_t_tile.h"
 
 namespace convbn {
 namespace win {
@@ -111,7 +111,7 @@ struct WnCfg {
   static constexpr int OFF_BIAS = NST * STAGE;          // [TN] bias, [TN] scale
   static constexpr int LDS_BYTES = OFF_BIAS + 2 * TN * 4;
   static_assert(NWAVES * 32 * CW * 2 <= STAGE * NST, "the epilogue stages every wave's outputs in the ring");
-  static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES, "what folds on the side");
+  static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES && 2 * FBT_SMEM <= LDS_BYTES, "what folds on the side");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 

@@ -9,7 +9,7 @@
 //   back   dW[ci][tap][co] = s[co] dw'[ci][tap][co],  dgamma[co] = (sum_{ci,tap} dw' W + r (b - mu)) / sqrt(var + eps),
 //          dbeta = r, db = s r
 // Both are memory-bound passes over the weight; threads run along co, so every access is contiguous.
-#include "fold_tile.h"
+#include "fold_back_t_tile.h"
 
 namespace convbn {
 
@@ -90,148 +90,12 @@ BackPlan back_plan(int rows, int Co, int nsplit) {
   return p;
 }
 
-__device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
-  const float4 t = *reinterpret_cast<const float4*>(p);
-  v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-}
-__device__ __forceinline__ void load4(const bf16_t* p, float (&v)[4]) {
-  const uint2 t = *reinterpret_cast<const uint2*>(p);
-  v[0] = bf16_lo(t.x); v[1] = bf16_hi(t.x); v[2] = bf16_lo(t.y); v[3] = bf16_hi(t.y);
-}
-__device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
-__device__ __forceinline__ void store4(bf16_t* p, const float (&v)[4]) {
-  *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-}
-
-// The first rs.blocks workgroups of a fold-back (bf16 with Co % 8 == 0, Co <= 2048; else none, and a launch before this one)
-// sum dZ's columns: that reads dZ while the others read the copies, and needs nothing of theirs.  512 -> 256 channels, 4 x 4,
-// 14 x 14, 32 images: 7.8 us, 38 MB (the sums in a launch of their own: 6.3 + 7.3).
-struct RSum { const uint4* dz; float* part; int M, rows, blocks; };
-__device__ __forceinline__ bool colsum_block(const RSum& rs, int Co, float (*red)[9]) {
+template <typename T>
+__global__ __launch_bounds__(256) void fold_back_t_kernel(FoldBackTArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[FBT_SMEM];
   const int block = blockIdx.x;
-  if (block >= rs.blocks) return false;
-  const int m0 = block * rs.rows;
-  colsum_slice_bf16x8(rs.dz, m0, min(rs.M, m0 + rs.rows), Co, threadIdx.x, red, rs.part + (size_t)block * Co);
-  return true;
-}
-
-// A wave owns RW rows of its workgroup's 4 RW, all asked for at once, and a lane four consecutive columns.
-template <typename T, int RW>
-__global__ __launch_bounds__(256) void fold_back_t_kernel(RSum rs, const float* __restrict__ part, int nsplit,
-                                                          const T* __restrict__ W, const float* __restrict__ gamma,
-                                                          const float* __restrict__ var, float eps, int rows, int Co, int ncol,
-                                                          T* __restrict__ dW, float* __restrict__ dot_part) {
-  __shared__ float red[256][9];
-  if (colsum_block(rs, Co, red)) return;
-  const int block = blockIdx.x - rs.blocks;
-  const int bx = block % ncol, by = block / ncol;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = bx * 256 + lane * 4;
-  const int r0 = by * 4 * RW + wave;   // and every fourth row behind it
-  const size_t P = (size_t)rows * Co;
-  float dot[4] = {0.f, 0.f, 0.f, 0.f};
-  if (col < Co && r0 < rows) {
-    size_t at[RW];
-    bool in[RW];
-    float w[RW][4], dw[RW][4] = {};
-    float s[4] = {1.f, 1.f, 1.f, 1.f}, v[4] = {1.f, 1.f, 1.f, 1.f};   // no gamma: plain sum
-    if (gamma) { load4(gamma + col, s); load4(var + col, v); }
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-      in[i] = r0 + 4 * i < rows;
-      at[i] = (size_t)(in[i] ? r0 + 4 * i : r0) * Co + col;
-      load4(W + at[i], w[i]);
-    }
-#pragma unroll 4
-    for (int sp = 0; sp < nsplit; ++sp)
-#pragma unroll
-      for (int i = 0; i < RW; ++i) {
-        const float4 t = *reinterpret_cast<const float4*>(part + sp * P + at[i]);
-        dw[i][0] += t.x; dw[i][1] += t.y; dw[i][2] += t.z; dw[i][3] += t.w;
-      }
-    if (gamma)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] /= sqrtf(v[e] + eps);
-#pragma unroll
-    for (int i = 0; i < RW; ++i) {
-      if (!in[i]) continue;
-      float o[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { o[e] = s[e] * dw[i][e]; dot[e] += dw[i][e] * w[i][e]; }
-      store4(dW + at[i], o);
-    }
-  }
-  if (!dot_part) return;
-  float* const sum = &red[0][0];   // [wave][256]
-#pragma unroll
-  for (int e = 0; e < 4; ++e) sum[wave * 256 + lane * 4 + e] = dot[e];
-  __syncthreads();
-  const int c = threadIdx.x, co = bx * 256 + c;
-  if (co < Co) dot_part[(size_t)by * Co + co] = sum[c] + sum[256 + c] + sum[512 + c] + sum[768 + c];
-}
-
-// Thread -> column group el (of EL / cw rows, cw columns of four each) and every (256 / EL)-th partial copy.
-template <typename T, int EL>
-__global__ __launch_bounds__(256) void fold_back_t_split_kernel(RSum rs, const float* __restrict__ part, int nsplit,
-                                                                const T* __restrict__ W, const float* __restrict__ gamma,
-                                                                const float* __restrict__ var, float eps, int rows, int Co,
-                                                                int ncol, int cw, T* __restrict__ dW,
-                                                                float* __restrict__ dot_part) {
-  constexpr int SL = 256 / EL;
-  __shared__ union { float r[256][9]; struct { float copy[SL][EL * 4], dot[EL * 4]; } s; } red;
-  if (colsum_block(rs, Co, red.r)) return;
-  const int block = blockIdx.x - rs.blocks, bx = block % ncol, by = block / ncol;
-  const int nr = EL / cw;
-  const size_t P = (size_t)rows * Co;
-  // element `el` of the workgroup: its offset in a copy (one inside where there is none) and whether there is one
-  auto element = [&](int el, size_t& at) {
-    const int rr = el / cw, row = by * nr + rr, c = (bx * cw + el - rr * cw) * 4;
-    const bool in = rr < nr && row < rows && c < Co;
-    at = in ? (size_t)row * Co + c : 0;
-    return in;
-  };
-  const int tid = threadIdx.x;
-  // the element this thread finishes: column e of group fe
-  const int fe = tid >> 2, fc = (bx * cw + fe % cw) * 4 + (tid & 3);
-  size_t fat = 0;
-  const bool fin = tid < EL * 4 && element(fe, fat);
-  fat += tid & 3;
-  const float fw = fin ? to_f32(W[fat]) : 0.f;
-  const float fg = fin && gamma ? gamma[fc] : 1.f, fv = fin && gamma ? var[fc] : 1.f;
-  {
-    const int el = tid % EL, sl = tid / EL;
-    size_t at;
-    const bool in = element(el, at);
-    float dw[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int sp = sl; sp < nsplit; sp += 4 * SL) {
-      float4 t[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) t[j] = *reinterpret_cast<const float4*>(part + (size_t)min(sp + j * SL, nsplit - 1) * P + at);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (sp + j * SL >= nsplit) t[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        dw[0] += t[j].x; dw[1] += t[j].y; dw[2] += t[j].z; dw[3] += t[j].w;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red.s.copy[sl][el * 4 + e] = in ? dw[e] : 0.f;
-  }
-  __syncthreads();
-  if (tid < EL * 4) {
-    float dw = 0.f;
-#pragma unroll
-    for (int l = 0; l < SL; ++l) dw += red.s.copy[l][tid];
-    if (fin) dW[fat] = from_f32<T>(gamma ? fg / sqrtf(fv + eps) * dw : dw);
-    red.s.dot[tid] = fin ? dw * fw : 0.f;
-  }
-  if (!dot_part) return;
-  __syncthreads();
-  if (!fin || fe >= cw) return;
-  float dot = 0.f;
-  for (int rr = 0; rr < nr; ++rr) dot += red.s.dot[rr * cw * 4 + tid];
-  dot_part[(size_t)by * Co + fc] = dot;
+  if (block < a.rs.blocks) fbt_colsum(a.rs, a.Co, block, threadIdx.x, smem);
+  else fbt_block<T>(a, block - a.rs.blocks, threadIdx.x, smem);
 }
 
 // Any Co.  grid (ceil(Co/64), ceil(rows/8)).  Thread -> column tid%64, row lane tid/64.
@@ -327,49 +191,61 @@ hipError_t launch_fold_t(int dtype, int Ci, int Co, int taps, const void* W, con
 
 int fold_back_t_chunks(int Ci, int Co, int taps, int nsplit) { return back_plan(Ci * taps, Co, nsplit).chunks; }
 
+namespace {
+bool sums_aside(int dtype, int Co) { return dtype == CONVBN_BF16 && Co % 8 == 0 && Co <= 2048; }
+FoldBackTArgs back_args(int dtype, int Ci, int Co, int taps, const float* dwf_part, int nsplit, const Geom& zrows, const void* dz,
+                        float* r_part, const void* W, const float* gamma, const float* var, float eps, float* dot_part, void* dW) {
+  const int rows = Ci * taps;
+  const BackPlan bp = back_plan(rows, Co, nsplit);
+  const int nrpart = colsum_parts(zrows);
+  FoldBackTArgs a{};
+  if (gamma && sums_aside(dtype, Co)) a.rs = {static_cast<const uint4*>(dz), r_part, zrows.M, ceil_div(zrows.M, nrpart), nrpart};
+  a.part = dwf_part; a.W = W; a.gamma = gamma; a.var = var; a.dW = dW; a.dot_part = dot_part; a.eps = eps;
+  a.nsplit = nsplit; a.rows = rows; a.Co = Co; a.ncol = bp.ncol; a.cw = bp.cols / 4;
+  a.kind = bp.el == 64 ? FBT_SPLIT_64 : bp.el == 16 ? FBT_SPLIT_16 : bp.rows == 32 ? FBT_ROWS_8 : FBT_ROWS_2;
+  a.blocks = bp.ncol * bp.chunks;
+  return a;
+}
+}  // namespace
+
+bool fold_back_t_side(int dtype, int Ci, int Co, int taps, const float* dwf_part, int nsplit, const Geom& zrows, const void* dz,
+                      float* r_part, const void* W, const float* gamma, const float* var, float eps, float* dot_part, void* dW,
+                      FoldBackTArgs* a) {
+  if (!sums_aside(dtype, Co)) return false;
+  *a = back_args(dtype, Ci, Co, taps, dwf_part, nsplit, zrows, dz, r_part, W, gamma, var, eps, dot_part, dW);
+  return true;
+}
+hipError_t launch_fold_back_t_finish(int Ci, int Co, int taps, int nsplit, const Geom& zrows, const float* r_part, const float* b,
+                                     const float* gamma, const float* mean, const float* var, float eps, const float* dot_part,
+                                     float* db, float* dgamma, float* dbeta, hipStream_t st) {
+  const int chunks = fold_back_t_chunks(Ci, Co, taps, nsplit), nrpart = colsum_parts(zrows);
+#define FINISH(V)                                                                                                      \
+  hipLaunchKernelGGL(fold_back_t_finish_kernel<V>, dim3(Co / V), dim3(256), 0, st, dot_part, chunks, r_part, nrpart, b, \
+                     gamma, mean, var, eps, Co, db, dgamma, dbeta)
+  if (Co % 4 == 0) FINISH(4); else FINISH(1);
+#undef FINISH
+  return hipGetLastError();
+}
+
 hipError_t launch_fold_back_t(int dtype, int Ci, int Co, int taps, const float* dwf_part, int nsplit,
                               const Geom& zrows, const void* dz, float* r_part, const void* W, const float* b,
                               const float* gamma, const float* mean, const float* var, float eps, float* dot_part, void* dW,
                               float* db, float* dgamma, float* dbeta, hipStream_t st) {
-  const int rows = Ci * taps;
-  const BackPlan bp = back_plan(rows, Co, nsplit);
-  const int chunks = bp.chunks, ncol = bp.ncol;
-  const int nrpart = gamma ? colsum_parts(zrows) : 0;
-  RSum rs{};
-  if (gamma && dtype == CONVBN_BF16 && Co % 8 == 0 && Co <= 2048)
-    rs = {static_cast<const uint4*>(dz), r_part, zrows.M, ceil_div(zrows.M, nrpart), nrpart};
-  else if (gamma)
+  const FoldBackTArgs a = back_args(dtype, Ci, Co, taps, dwf_part, nsplit, zrows, dz, r_part, W, gamma, var, eps, dot_part, dW);
+  if (gamma && a.rs.blocks == 0)
     if (hipError_t e = launch_colsum(zrows, dtype, dz, r_part, st); e != hipSuccess) return e;
-  const bool vec = Co % 4 == 0;
-  const dim3 grid(rs.blocks + (unsigned)ncol * chunks);
-#define FBT_ROWS(T, RW)                                                                                                  \
-  hipLaunchKernelGGL((fold_back_t_kernel<T, RW>), grid, dim3(256), 0, st, rs, dwf_part, nsplit, (const T*)W, gamma, var, \
-                     eps, rows, Co, ncol, (T*)dW, dot_part)
-#define FBT_SPLIT(T, EL)                                                                                               \
-  hipLaunchKernelGGL((fold_back_t_split_kernel<T, EL>), grid, dim3(256), 0, st, rs, dwf_part, nsplit, (const T*)W, gamma, \
-                     var, eps, rows, Co, ncol, bp.cols / 4, (T*)dW, dot_part)
-#define FBT(T)                                                                                                         \
-  do {                                                                                                                 \
-    if (!vec) hipLaunchKernelGGL(fold_back_t_scalar_kernel<T>, dim3(ncol, chunks), dim3(256), 0, st, dwf_part, nsplit, \
-                                 (const T*)W, gamma, var, eps, rows, Co, (T*)dW, dot_part);                           \
-    else if (bp.el == 64) FBT_SPLIT(T, 64);                                                                            \
-    else if (bp.el == 16) FBT_SPLIT(T, 16);                                                                            \
-    else if (bp.rows == 32) FBT_ROWS(T, 8);                                                                            \
-    else FBT_ROWS(T, 2);                                                                                               \
-  } while (0)
-  if (dtype == CONVBN_BF16) FBT(bf16_t);
-  else FBT(float);
-#undef FBT
-#undef FBT_SPLIT
-#undef FBT_ROWS
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !gamma) return e;   // no gamma: dW = sum of the partial copies, nothing else
-#define FINISH(V)                                                                                                      \
-  hipLaunchKernelGGL(fold_back_t_finish_kernel<V>, dim3(Co / V), dim3(256), 0, st, dot_part, chunks, r_part, nrpart, b, \
-                     gamma, mean, var, eps, Co, db, dgamma, dbeta)
-  if (vec) FINISH(4); else FINISH(1);
-#undef FINISH
-  return hipGetLastError();
+  const dim3 grid(a.rs.blocks + a.blocks), scalar(a.ncol, a.blocks / a.ncol);
+  if (dtype == CONVBN_BF16) {
+    if (Co % 4 == 0) hipLaunchKernelGGL(fold_back_t_kernel<bf16_t>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(fold_back_t_scalar_kernel<bf16_t>, scalar, dim3(256), 0, st, dwf_part, nsplit, (const bf16_t*)W, gamma,
+                            var, eps, a.rows, Co, (bf16_t*)dW, dot_part);
+  } else {
+    if (Co % 4 == 0) hipLaunchKernelGGL(fold_back_t_kernel<float>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(fold_back_t_scalar_kernel<float>, scalar, dim3(256), 0, st, dwf_part, nsplit, (const float*)W, gamma,
+                            var, eps, a.rows, Co, (float*)dW, dot_part);
+  }
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || !gamma) return e;   // no gamma: dW = sum of the partial copies, nothing else
+  return launch_fold_back_t_finish(Ci, Co, taps, nsplit, zrows, r_part, b, gamma, mean, var, eps, dot_part, db, dgamma, dbeta, st);
 }
 
 }  // namespace convbn

@@ -1,12 +1,12 @@
 """GPU parity of the fold-back where it rides in the input gradient's launch (64 to 512 threads a channel, channels that do not fill a
-workgroup) and of rows that are no multiple of four elements, as columns of four and of one."""
+workgroup; transposed blocks: rows and shared copies, odd numbers of workgroups) and of rows that are no multiple of four elements, as columns of four and of one."""
 import pytest
 
 from paper_2305_11624_amd import synth
-from paper_2305_11624_amd.runner import BlockRun
+from paper_2305_11624_amd.runner import BlockRun, TconvRun
 from paper_2305_11624_amd.synth import BlockShape
 
-from helpers import compare, oracle_block
+from helpers import compare, oracle_block, oracle_tconv_block
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +40,38 @@ def test_gradient_over_an_operand(over):
     inp = synth.make_inputs(BlockShape("fb", 20, 256, 30, 33, 64, 1, 1, 0, "bf16", 7))
     ref = oracle_block(inp)
     r = BlockRun(inp, poison=True)
+    r.forward()
+    r.dW = getattr(r, over).flatten()[:r.dW.numel()].view(r.dW.shape)
+    r.backward()
+    compare(r.results(), ref, "bf16", keys=("dX", "dW", "dgamma", "dbeta"), tag=over)
+
+
+TCONV = [
+    #  N  Cin  H   W   Cout k  s  p
+    (1, 64, 5, 7, 32, 4, 2, 1),       # eight rows a workgroup
+    (3, 512, 14, 14, 256, 4, 2, 1),   # thirty-two
+    (2, 72, 30, 23, 40, 4, 2, 1),     # the copies shared by the threads of sixteen column groups
+    (2, 128, 40, 41, 64, 4, 2, 1),    # ... of sixty-four
+    (1, 24, 9, 5, 8, 3, 2, 1),
+    (2, 16, 6, 6, 12, 4, 2, 1),       # not a multiple of eight: launches of their own
+]
+
+
+@pytest.mark.parametrize("n,cin,h,w,cout,k,s,p", TCONV)
+def test_transposed(n, cin, h, w, cout, k, s, p):
+    inp = synth.make_tconv_inputs(BlockShape("fbt", n, cin, h, w, cout, k, s, p, "bf16", h + w), bias=True)
+    ref = oracle_tconv_block(inp)
+    for keep in (True, False):
+        r = TconvRun(inp, poison=True, keep_folded=keep)
+        r.step()
+        compare(r.results(), ref, "bf16", tag="keep %s" % keep)
+
+
+@pytest.mark.parametrize("over", ["dz", "w_folded"])
+def test_transposed_gradient_over_an_operand(over):
+    inp = synth.make_tconv_inputs(BlockShape("fbt", 9, 64, 14, 13, 32, 4, 2, 1, "bf16", 5))
+    ref = oracle_tconv_block(inp)
+    r = TconvRun(inp, poison=True)
     r.forward()
     r.dW = getattr(r, over).flatten()[:r.dW.numel()].view(r.dW.shape)
     r.backward()
