@@ -120,7 +120,7 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p, Side s
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* biasl = reinterpret_cast<float*>(smem + Cfg::OFF_BIAS);
   if ((int)blockIdx.x >= p.nconv) {
-    if constexpr (Side::BACK) fold_back_side<64 * NWAVES, ROW_VEC, 8>(side, (int)blockIdx.x - p.nconv, smem);
+    if constexpr (Side::BACK) fold_back_side<64 * NWAVES, ROW_VEC, 8, TM == 256 ? 4 : 1>(side, (int)blockIdx.x - p.nconv, smem);
     else fold_side(p.bn, p.wgt, (int)blockIdx.x - p.nconv, smem);
     return;
   }

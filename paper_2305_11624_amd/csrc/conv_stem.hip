@@ -613,7 +613,7 @@ __global__ __launch_bounds__(256, 2) void stem_dgrad_kernel(StemDgParams p, Side
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if constexpr (Side::BACK)
     if ((int)blockIdx.x >= p.nwg) {
-      fold_back_side<256, ROW_ANY>(side, (int)blockIdx.x - p.nwg, smem);
+      fold_back_side<256, ROW_ANY, 16, 1>(side, (int)blockIdx.x - p.nwg, smem);
       return;
     }
   unsigned char* wl = smem;                                         // [16][wpitch] (UU == 0)

@@ -11,12 +11,13 @@ namespace {
 
 constexpr int KS_FEW = 6, KS_MANY = 48;
 // The tile of the wave-split product: the smallest whose workgroups are one round (3 x 3, 512 -> 512: 32 x 32 8.9 us, 64 x 32 11.3,
-// 64 x 64 14.3 where all three are; a second round takes as long as the first: 17.3).  None where 64 x 64 tiles are more
+// 64 x 64 14.3 where all three are; a second round takes as long as the first: 17.3), `aside` counted in: 256 tiles and eight
+// workgroups that fold took 8.1 us (128 -> 512 at 31 x 31, 1 image), 128 x 64 tiles 5.4.  None where 64 x 64 tiles are more
 // than that, or have fewer chunks than give six of the eight waves one (1 x 1, 88 -> 240 at 34 x 27 / 2, 13 images, forward: 5.0
 // on 128 x 64 tiles, 5.7), or where the deep-layer kernel has the layer and its chain is long (`deep`; 512 -> 512 at 6 x 6, 46
 // images, 72 chunks: 16.4 there, 17.7; 128 -> 128 at 28 x 28, 8 images, 18 chunks: 9.8 there, 8.3).
 struct KsTile { int tm, tn; };   // tm == 0: not taken
-KsTile ks_tile(int C, int R, int n, const int* M, const Window* cv, bool deep) {
+KsTile ks_tile(int C, int R, int n, const int* M, const Window* cv, bool deep, int aside) {
   constexpr int CUS = 256;
   constexpr KsTile sizes[] = {{32, 32}, {64, 32}, {64, 64}};
   int chunks = 0;
@@ -25,13 +26,13 @@ KsTile ks_tile(int C, int R, int n, const int* M, const Window* cv, bool deep) {
     long long tiles = 0;
     for (int i = 0; i < n; ++i)
       if (cv[i].kH > 0) tiles += (long long)ceil_div(M[i], t.tm) * ceil_div(R, t.tn);
-    if (tiles > CUS) continue;
+    if (tiles > CUS || (t.tm * t.tn > 32 * 32 && tiles + aside > CUS)) continue;   // (32 x 32: two workgroups a compute unit)
     return t.tm * t.tn < 64 * 64 || (chunks >= KS_FEW && (chunks <= KS_MANY || !deep)) ? t : KsTile{0, 0};
   }
   return {0, 0};
 }
 struct WnPlan { int tm, tn, nst; bool flat; bool ks = false; };
-WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv, bool deep) {
+WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv, bool deep, int aside) {
   auto tiles = [&](int tm, int tn) {   // those with a product to compute
     long long t = 0;
     for (int i = 0; i < n; ++i)
@@ -39,7 +40,7 @@ WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv, bool deep) 
     return t * ceil_div(R, tn);
   };
   const bool flat = C % CB != 0;
-  if (const KsTile t = ks_tile(C, R, n, M, cv, deep); t.tm) return {t.tm, t.tn, 0, true, true};
+  if (const KsTile t = ks_tile(C, R, n, M, cv, deep, aside); t.tm) return {t.tm, t.tn, 0, true, true};
   // the largest tile that still gives most compute units one (as in conv_gm.hip); a tile of 128 channels only where the
   // last one is more than half full
   const bool wide = R % 128 == 0 || R % 128 > 64;
@@ -108,14 +109,14 @@ WnParams make_params(int C, int R, int n, const int* M, const Window* cv, size_t
 
 hipError_t launch_win(int C, int R, int n, const int* M, const Window* cv, const void* act, size_t act_bytes, const void* wgt,
                       size_t wgt_bytes, const float* bias, const BnEpilogue* bn, void* out, int relu, const void* mask,
-                      const void* add, hipStream_t st, bool deep, const FoldBackArgs* fb = nullptr,
+                      const void* add, hipStream_t st, bool deep, int aside, const FoldBackArgs* fb = nullptr,
                       const FoldBackTArgs* fbt = nullptr) {
   if (n < 1 || n > MAXC || C % 8 || R % 8 || act_bytes >= OOB || wgt_bytes >= OOB) return hipErrorInvalidValue;
   WnParams p = make_params(C, R, n, M, cv, act_bytes, wgt_bytes);
   p.act = (const bf16_t*)act; p.wgt = (const bf16_t*)wgt; p.bias = bias; p.out = (bf16_t*)out;
   if (bn) p.bn = *bn;
   p.relu = relu; p.mask = (const bf16_t*)mask; p.add = (const bf16_t*)add;
-  const WnPlan pl = win_plan(C, R, n, M, cv, deep);
+  const WnPlan pl = win_plan(C, R, n, M, cv, deep, aside);
 #define WIN_CASE(TM_, TN_, NST_, F_) \
   if (!pl.ks && pl.tm == TM_ && pl.tn == TN_ && pl.nst == NST_ && pl.flat == F_) \
     return fb ? launch_inst<TM_, TN_, NST_, F_>(p, *fb, st) : fbt ? launch_inst<TM_, TN_, NST_, F_>(p, *fbt, st)                \
@@ -169,6 +170,8 @@ Window fprop_window(const Geom& g) {
   c.wt_row = g.kW; c.wt_col = 1; c.wrow = g.K;
   return c;
 }
+// Workgroups that fold behind a forward product: where w' is small enough to be kept (the call may decide otherwise)
+int folds_aside(const Geom& g) { return g.K <= g.M ? ceil_div(ceil_div(g.K, 64) * ceil_div(g.Cout, 64), 2) : 0; }
 // residue classes that have positions, in rows and columns
 int classes_h(const Geom& g) { return g.sh < g.Hin ? g.sh : g.Hin; }
 int classes_w(const Geom& g) { return g.sw < g.Win ? g.sw : g.Win; }
@@ -189,7 +192,7 @@ bool win_supported(const Geom& g, int dtype) { return sizes_fit(g, dtype); }
 bool ks_fprop_taken(const Geom& g, int dtype) {
   if (!sizes_fit(g, dtype)) return false;
   const Window c = fprop_window(g);
-  return ks_tile(g.Cin, g.Cout, 1, &g.M, &c, st_fprop_supported(g, dtype)).tm != 0;
+  return ks_tile(g.Cin, g.Cout, 1, &g.M, &c, st_fprop_supported(g, dtype), folds_aside(g)).tm != 0;
 }
 namespace {
 struct KsGrad { bool taken; float us; };
@@ -201,7 +204,7 @@ const KsGrad& ks_grad(const Geom& g) {
     Window c[MAXC];
     int M[MAXC];
     for (int i = 0; i < p.ncls; ++i) { c[i] = p.c[i].cv; M[i] = p.c[i].M; }
-    const KsTile t = ks_tile(p.C, p.R, p.ncls, M, c, st_dgrad_supported(g, CONVBN_BF16));
+    const KsTile t = ks_tile(p.C, p.R, p.ncls, M, c, st_dgrad_supported(g, CONVBN_BF16), 0);
     if (t.tm == 0) {   // (another kernel's)
       for (int i = 0; i < p.ncls; ++i) r.us = std::max(r.us, 5.5f + 0.2f * ceil_div(c[i].kH * c[i].kW * p.C, CB));
       return r;
@@ -222,7 +225,7 @@ hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, co
                             const BnEpilogue* bn) {
   const Window c = fprop_window(g);
   return launch_win(g.Cin, g.Cout, 1, &g.M, &c, x, (size_t)g.Min * g.Cin * 2, w_krsc, (size_t)g.Cout * g.K * 2, bias, bn, z,
-                    g.post_relu, g.post_mask, g.post_add, st, st_fprop_supported(g, CONVBN_BF16), nullptr, g.fold_back_t);
+                    g.post_relu, g.post_mask, g.post_add, st, st_fprop_supported(g, CONVBN_BF16), folds_aside(g), nullptr, g.fold_back_t);
 }
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st) {
   Window c[MAXC];
@@ -234,7 +237,7 @@ hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, c
     n = 0;
     fb = nullptr;
     return launch_win(g.Cout, g.Cin, k, M, c, dz, (size_t)g.M * g.Cout * 2, w_crsk, (size_t)g.Cout * g.K * 2, bias, nullptr, dx,
-                      g.post_relu, g.post_mask, g.post_add, st, st_dgrad_supported(g, CONVBN_BF16), f);
+                      g.post_relu, g.post_mask, g.post_add, st, st_dgrad_supported(g, CONVBN_BF16), 0, f);
   };
   for (int a = 0; a < classes_h(g); ++a)
     for (int b = 0; b < classes_w(g); ++b) {

@@ -111,7 +111,7 @@ template <typename T, int NTHR, RowKind ROW>
 __global__ __launch_bounds__(NTHR) void fold_back_kernel(FoldBackArgs a) {
   __shared__ float4 red4[NTHR];
   __shared__ float red[2 * NTHR / 64];
-  fold_back_row<T, 16, ROW>(a, blockIdx.x, threadIdx.x, NTHR, red4, red);
+  fold_back_row<T, 16, 1, ROW>(a, blockIdx.x, threadIdx.x, NTHR, red4, red);
 }
 
 // The fold-backs of several blocks in one launch (Table 2 "Tune", last four lines, for every block of a group):
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void fold_back_group_kernel(const FoldBackGrou
     if (items[mid].first_block <= (int)blockIdx.x) lo = mid; else hi = mid - 1;
   }
   const FoldBackArgs a = items[lo].a;
-  fold_back_row<bf16_t, 16, ROW_VEC>(a, blockIdx.x - items[lo].first_block, threadIdx.x, 256, red4, red);
+  fold_back_row<bf16_t, 16, 1, ROW_VEC>(a, blockIdx.x - items[lo].first_block, threadIdx.x, 256, red4, red);
 }
 
 // Column reductions over a [M][Cout] channels-last tensor.  `cw` threads walk the
