@@ -6,16 +6,21 @@
 #include "conv_ks_impl.h"
 #include "wgrad_win_impl.h"
 
+#include <algorithm>
+
 namespace convbn {
 
 namespace {
 
 constexpr int CUS = 256;
 
+// TM 128: the window product's 128 x 64 tiles (conv_win_impl.h), fewer workgroups where the wave-split ones would leave the weight
+// gradient too few (256 -> 1024 at 14 x 14, 16 images, a pass: 21.6 us with them, 25.5 on two launches)
 template <int TM, int TN, int TA, int TB>
 __global__ __launch_bounds__(512) void win_pair_kernel(wgw::WwParams w, win::WnParams d, int nw) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   if ((int)blockIdx.x < nw) wgw::body<TA, TB>(w, blockIdx.x, smem);
+  else if constexpr (TM == 128) win::body<128, 64, 6, true>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
   else win::ks_body<TM, TN>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
 }
 
@@ -34,7 +39,11 @@ void consider(const Geom& g, PairPlan& best) {
   const int total = w.p.nta * w.p.ntb * w.p.slices;
   pl.nw = ceil_div(total, 8) * 8;
   if (pl.nw + product > CUS) return;
-  const float du = win::ks_us(TM, TN, pl.d);
+  float du = win::ks_us(TM, TN, pl.d);
+  if (TM == 128) {
+    du = 0.f;
+    for (int i = 0; i < pl.d.ncls; ++i) du = std::max(du, 4.5f + 0.3f * pl.d.c[i].nchunks);
+  }
   pl.ok = true;
   pl.product = product;
   pl.tm = TM; pl.tn = TN; pl.ta = w.ta; pl.tb = w.tb; pl.w = w.p;
@@ -47,16 +56,29 @@ PairPlan work_out_plan(const Geom& g) {
   consider<32, 32>(g, pl);
   consider<64, 32>(g, pl);
   consider<64, 64>(g, pl);
+  win::WnParams d;   // (64 x 64 tiles on more than 144 compute units; on 140 and 98 of them they are the better: 72 -> 136 at 27 x 33
+                     // 21.3 a pass, 24.0)
+  if (win::dgrad_params(g, &d)) {
+    int tiles = 0;
+    for (int i = 0; i < d.ncls; ++i)
+      if (d.c[i].cv.kH > 0) tiles += ceil_div(d.c[i].M, 64) * ceil_div(d.R, 64);
+    if (tiles > 144) consider<128, 64>(g, pl);
+  }
   return pl;
 }
 const PairPlan& plan(const Geom& g) {
   return planned<PairPlan>(g, CONVBN_BF16, [&] { return work_out_plan(g); });
 }
 
+template <int TM, int TN>
+constexpr int dgrad_lds() {
+  if constexpr (TM == 128) return win::WnCfg<128, 64, 6>::LDS_BYTES;
+  else return win::KsCfg<TM, TN>::LDS_BYTES;
+}
 template <int TM, int TN, int TA, int TB>
 hipError_t launch_inst(const wgw::WwParams& w, const win::WnParams& d, int nw, hipStream_t st) {
   static LdsLimitOnce lds_once;
-  constexpr int a = wgw::WwCfg<TA, TB>::LDS_BYTES, b = win::KsCfg<TM, TN>::LDS_BYTES, lds = a > b ? a : b;
+  constexpr int a = wgw::WwCfg<TA, TB>::LDS_BYTES, b = dgrad_lds<TM, TN>(), lds = a > b ? a : b;
   if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&win_pair_kernel<TM, TN, TA, TB>), lds);
       e != hipSuccess) return e;
   hipLaunchKernelGGL((win_pair_kernel<TM, TN, TA, TB>), dim3(nw + d.nconv), dim3(512), lds, st, w, d, nw);
@@ -90,7 +112,7 @@ hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const v
   if (pl.tm == TM_ && pl.tn == TN_ && pl.ta == TA_ && pl.tb == TB_) return launch_inst<TM_, TN_, TA_, TB_>(w, d, pl.nw, st);
 #define PAIR_CASE(TM_, TN_) \
   PAIR_TILE(TM_, TN_, 64, 64) PAIR_TILE(TM_, TN_, 128, 64) PAIR_TILE(TM_, TN_, 64, 128) PAIR_TILE(TM_, TN_, 128, 128)
-  PAIR_CASE(32, 32) PAIR_CASE(64, 32) PAIR_CASE(64, 64)
+  PAIR_CASE(32, 32) PAIR_CASE(64, 32) PAIR_CASE(64, 64) PAIR_CASE(128, 64)
 #undef PAIR_CASE
 #undef PAIR_TILE
   return hipErrorInvalidValue;
