@@ -35,6 +35,7 @@ struct KsCfg {
   static_assert(TM * TN * 4 <= STAGE && GRANULES <= 64 * NWAVES, "a wave's sums take the place of its chunks");
   static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES && 2 * FBT_SMEM <= LDS_BYTES, "what folds on the side");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+  static constexpr int SHARED = shared_cu(LDS_BYTES), WAVES_SIMD = SHARED ? NWAVES / 2 : NWAVES / 4;
 };
 
 template <int TM, int TN, class Side>
@@ -42,7 +43,7 @@ __device__ __forceinline__ void ks_body(const WnParams& p, const Side& side, con
   using Cfg = KsCfg<TM, TN>;
   constexpr int AU = Cfg::AU, WU = Cfg::WU, NPS = Cfg::NPS, NCS = Cfg::NCS, STAGE = Cfg::STAGE;
   if (wg >= p.nconv) {
-    if constexpr (Side::BACK) fold_back_side<64 * NWAVES>(side, wg - p.nconv, smem);
+    if constexpr (Side::BACK) fold_back_aside<Cfg::SHARED>(side, wg - p.nconv, smem);
     else fold_side(p.bn, p.wgt, wg - p.nconv, smem);
     return;
   }

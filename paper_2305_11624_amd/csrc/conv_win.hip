@@ -51,7 +51,7 @@ WnPlan win_plan(int C, int R, int n, const int* M, const Window* cv, bool deep, 
 }
 
 template <int TM, int TN, int NST, bool FLAT, class Side>
-__global__ __launch_bounds__(64 * NWAVES) void conv_win_kernel(WnParams p, Side side) {
+__global__ __launch_bounds__(64 * NWAVES, (WnCfg<TM, TN, NST>::WAVES_SIMD)) void conv_win_kernel(WnParams p, Side side) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   body<TM, TN, NST, FLAT>(p, side, blockIdx.x, smem);
 }
@@ -70,7 +70,7 @@ hipError_t launch_inst(WnParams& p, Side side, hipStream_t st) {
 }
 
 template <int TM, int TN, class Side>
-__global__ __launch_bounds__(64 * NWAVES) void conv_ks_kernel(WnParams p, Side side) {
+__global__ __launch_bounds__(64 * NWAVES, (KsCfg<TM, TN>::WAVES_SIMD)) void conv_ks_kernel(WnParams p, Side side) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   ks_body<TM, TN>(p, side, blockIdx.x, smem);
 }

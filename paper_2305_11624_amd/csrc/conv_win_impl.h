@@ -99,6 +99,16 @@ template <int N> __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Tiles whose LDS leaves room for a second workgroup on the compute unit leave it the registers too, at most 128 a lane: what folds
+// back on the side then has fewer loads in flight.  (With the 16 and 4 of the larger tiles such kernels had 162 to 168 registers and
+// a compute unit to each workgroup, in an input gradient of thousands of them: 3 x 3 / 2, 64 -> 64 at 112 x 112, 64 images 152.5 us
+// a pass, 129.7 like this; at 56 x 56, 128 images 86.2, 73.8; transposed 4 x 4 / 2, 64 -> 32 at 56 x 56, 32 images 81.6, 71.2.)
+constexpr bool shared_cu(int lds) { return 2 * lds <= 160 * 1024; }
+template <bool SHARED, class Side>
+__device__ __forceinline__ void fold_back_aside(const Side& side, int wg, unsigned char* smem) {
+  fold_back_side<64 * NWAVES, ROW_VEC, SHARED ? 8 : 16, SHARED ? 2 : 4>(side, wg, smem);
+}
+
 template <int TM, int TN, int NST>
 struct WnCfg {
   static constexpr int CW = TN / 2;                     // channels per wave
@@ -113,6 +123,7 @@ struct WnCfg {
   static_assert(NWAVES * 32 * CW * 2 <= STAGE * NST, "the epilogue stages every wave's outputs in the ring");
   static_assert(2 * FOLD_TILE_BYTES <= LDS_BYTES && FOLD_BACK_SIDE_BYTES(64 * NWAVES) <= LDS_BYTES && 2 * FBT_SMEM <= LDS_BYTES, "what folds on the side");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+  static constexpr int SHARED = shared_cu(LDS_BYTES), WAVES_SIMD = SHARED ? NWAVES / 2 : NWAVES / 4;
 };
 
 // ---- what a workgroup is for
@@ -180,7 +191,7 @@ __device__ __forceinline__ void body(const WnParams& p, const Side& side, const 
   constexpr int ITS = 32 / RPI;       // store instructions per 32-pixel subtile
   constexpr int NPS = Cfg::NPS, NCS = Cfg::NCS, AUW = Cfg::AUW, WUW = Cfg::WUW, CPW = Cfg::CPW, STAGE = Cfg::STAGE;
   if (wg >= p.nconv) {
-    if constexpr (Side::BACK) fold_back_side<64 * NWAVES>(side, wg - p.nconv, smem);
+    if constexpr (Side::BACK) fold_back_aside<Cfg::SHARED>(side, wg - p.nconv, smem);
     else fold_side(p.bn, p.wgt, wg - p.nconv, smem);
     return;
   }

@@ -27,8 +27,8 @@ __device__ __forceinline__ void fbt_colsum(const RSum& rs, int Co, int block, in
   colsum_slice_bf16x8(rs.dz, m0, min(rs.M, m0 + rs.rows), Co, tid, reinterpret_cast<float (*)[9]>(smem), rs.part + (size_t)block * Co);
 }
 
-// A wave owns RW rows of its workgroup's 4 RW, all asked for at once, and a lane four consecutive columns.
-template <typename T, int RW>
+// A wave owns RW rows of its workgroup's 4 RW, UN copies of them all asked for at once, and a lane four consecutive columns.
+template <typename T, int RW, int UN>
 __device__ __forceinline__ void fbt_rows(const FoldBackTArgs& a, int block, int tid, unsigned char* smem) {
   const float* const part = a.part; const T* const W = static_cast<const T*>(a.W); T* const dW = static_cast<T*>(a.dW);
   const float* const gamma = a.gamma;
@@ -51,7 +51,7 @@ __device__ __forceinline__ void fbt_rows(const FoldBackTArgs& a, int block, int 
       at[i] = (size_t)(in[i] ? r0 + 4 * i : r0) * Co + col;
       fb_load4(W + at[i], w[i]);
     }
-#pragma unroll 4
+#pragma unroll UN
     for (int sp = 0; sp < nsplit; ++sp)
 #pragma unroll
       for (int i = 0; i < RW; ++i) {
@@ -141,26 +141,26 @@ __device__ __forceinline__ void fbt_split(const FoldBackTArgs& a, int block, int
 }
 
 
-// block of the fold-back proper, by 256 threads
-template <typename T>
+// block of the fold-back proper, by 256 threads; UN copies of eight rows in flight a thread
+template <typename T, int UN>
 __device__ __forceinline__ void fbt_block(const FoldBackTArgs& a, int block, int tid, unsigned char* smem) {
-  if (a.kind == FBT_ROWS_2) fbt_rows<T, 2>(a, block, tid, smem);
-  else if (a.kind == FBT_ROWS_8) fbt_rows<T, 8>(a, block, tid, smem);
+  if (a.kind == FBT_ROWS_2) fbt_rows<T, 2, 4>(a, block, tid, smem);
+  else if (a.kind == FBT_ROWS_8) fbt_rows<T, 8, UN>(a, block, tid, smem);
   else if (a.kind == FBT_SPLIT_16) fbt_split<T, 16>(a, block, tid, smem);
   else fbt_split<T, 64>(a, block, tid, smem);
 }
 
 // Along with the block's input gradient (a convolution of dZ), as fold_back_side in fold_tile.h: workgroup `wg` of 512 threads
 // takes two blocks, both of the column sums or both of the fold-back (the halves meet at the same barriers); where
-// there is an odd one its neighbour is done twice, with the same values.  bf16.  smem: 2 FBT_SMEM.
+// there is an odd one its neighbour is done twice, with the same values.  bf16.  FLIGHT as there.  smem: 2 FBT_SMEM.
 inline int fold_back_side_blocks(const FoldBackTArgs& a, int) { return ceil_div(a.rs.blocks, 2) + ceil_div(a.blocks, 2); }
-template <int THREADS>
+template <int THREADS, RowKind, int FLIGHT, int>
 __device__ __forceinline__ void fold_back_side(const FoldBackTArgs& a, int wg, unsigned char* smem) {
   static_assert(THREADS == 512, "two halves");
   const int half = (int)threadIdx.x >> 8, tid = (int)threadIdx.x & 255, sums = (a.rs.blocks + 1) >> 1;
   unsigned char* const mine = smem + half * FBT_SMEM;
   if (wg < sums) fbt_colsum(a.rs, a.Co, min(2 * wg + half, a.rs.blocks - 1), tid, mine);
-  else fbt_block<bf16_t>(a, min(2 * (wg - sums) + half, a.blocks - 1), tid, mine);
+  else fbt_block<bf16_t, FLIGHT < 16 ? 1 : 4>(a, min(2 * (wg - sums) + half, a.blocks - 1), tid, mine);
 }
 
 }  // namespace convbn
