@@ -347,6 +347,12 @@ convbn_status convbn_fold_group(int n, const void *table_dev, int grid_blocks, v
  * convbn_tune_bwd. */
 int32_t convbn_tune_bwd_is_fused(const convbn_desc *desc);
 
+/* Which kernels convbn_tune_fwd / convbn_tune_bwd (with dx and dW wanted) launch for this block, in short words: what a
+ * test or a measurement that is meant for one of them checks first.  Launches are separated by commas.  The words and
+ * the choices are no part of the interface.  Thread-local storage, valid until the next call; "" for an invalid
+ * descriptor. */
+const char *convbn_tune_route(const convbn_desc *desc, int pass);
+
 /* The fold-backs of several blocks in ONE launch (Table 2 "Tune", last four lines: dW = s dw',
  * db = s r, dgamma = (<dw', w> + r (b - mu))/sqrt(var+eps), dbeta = r, for every block of the
  * group).  A fold-back moves little data, so one launch per block is bound by the launches.

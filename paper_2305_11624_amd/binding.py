@@ -34,7 +34,7 @@ EXPORTS = ["convbn_hout", "convbn_wout", "convbn_workspace_bytes", "convbn_saved
            "convbn_tune_fwd_scale_epilogue", "convbn_grouped_workspace_bytes", "convbn_grouped_saved_bytes",
            "convbn_grouped_tune_fwd", "convbn_grouped_tune_bwd", "convbn_grouped_eval_fwd", "convbn_grouped_eval_bwd",
            "convbn_tune_fwd_static", "convbn_static_workspace_limit", "convbn_fold_back_group_table_bytes",
-           "convbn_fold_back_group_plan", "convbn_fold_back_group", "convbn_tune_bwd_is_fused"]
+           "convbn_fold_back_group_plan", "convbn_fold_back_group", "convbn_tune_bwd_is_fused", "convbn_tune_route"]
 
 
 class Desc(C.Structure):
@@ -183,6 +183,8 @@ def lib():
         L.convbn_tune_fwd_scale_epilogue.argtypes = [dp, vp, vp, fp, fp, fp, fp, fp, vp, vp]
         L.convbn_tune_bwd_is_fused.restype = C.c_int32
         L.convbn_tune_bwd_is_fused.argtypes = [dp]
+        L.convbn_tune_route.restype = C.c_char_p
+        L.convbn_tune_route.argtypes = [dp, C.c_int]
         L.convbn_fold_back_group_table_bytes.restype = C.c_size_t
         L.convbn_fold_back_group_table_bytes.argtypes = [C.c_int]
         L.convbn_fold_back_group_plan.restype = C.c_int
@@ -356,6 +358,10 @@ def convbn_fold_group(n, table, grid_blocks, stream=None, check=True):
 
 def convbn_tune_bwd_is_fused(desc) -> bool:
     return bool(lib().convbn_tune_bwd_is_fused(C.byref(desc)))
+
+
+def convbn_tune_route(desc, pass_) -> str:
+    return lib().convbn_tune_route(C.byref(desc), pass_).decode()
 
 
 def convbn_fold_back_group_plan(blocks, device="cuda", check=True):

@@ -318,35 +318,53 @@ bool has_post_op(const Geom& g) { return g.post_relu || g.post_mask || g.post_ad
 // FUSED_*: the kernel applies g's post-operation itself.
 constexpr bool FUSED_PW = true, FUSED_RW = true, FUSED_ST = true, FUSED_TILE = true;
 
+// The kernel of each convolution (KS: the window product's wave-split tiles)
+enum class Conv { KS, PW, RW, ST, WIN, TILE, WAVE, IGEMM, DIRECT };
+Conv fprop_kernel(const Geom& g, int dtype) {
+  return ks_fprop_taken(g, dtype) ? Conv::KS : pw_fprop_supported(g, dtype) ? Conv::PW : rw_fprop_supported(g, dtype) ? Conv::RW
+         : st_fprop_supported(g, dtype) ? Conv::ST : win_fprop_taken(g, dtype) ? Conv::WIN
+         : tile_fprop_supported(g, dtype) ? Conv::TILE : wave_f32_supported(g, dtype) ? Conv::WAVE
+         : igemm_supported(g, dtype) ? Conv::IGEMM : Conv::DIRECT;
+}
+Conv dgrad_kernel(const Geom& g, int dtype) {
+  return ks_dgrad_taken(g, dtype) ? Conv::KS : pw_dgrad_supported(g, dtype) ? Conv::PW : rw_dgrad_supported(g, dtype) ? Conv::RW
+         : st_dgrad_supported(g, dtype) ? Conv::ST : win_dgrad_taken(g, dtype) ? Conv::WIN
+         : tile_dgrad_supported(g, dtype) ? Conv::TILE : wave_f32_supported(g, dtype) ? Conv::WAVE
+         : igemm_supported(g, dtype) ? Conv::IGEMM : Conv::DIRECT;
+}
 hipError_t fprop_any(const Geom& g, int dtype, const void* x, const void* w_krsc, const float* bias,
                      void* z, float* scratch, hipStream_t st) {
-  hipError_t e;
+  hipError_t e = hipErrorInvalidValue;
   bool fused = false;
-  if (ks_fprop_taken(g, dtype)) { e = launch_fprop_win(g, x, w_krsc, bias, z, st); fused = true; }
-  else if (pw_fprop_supported(g, dtype)) { e = launch_fprop_pw(g, x, w_krsc, bias, z, st); fused = FUSED_PW; }
-  else if (rw_fprop_supported(g, dtype)) { e = launch_fprop_rw(g, x, w_krsc, bias, z, st); fused = FUSED_RW; }
-  else if (st_fprop_supported(g, dtype)) { e = launch_fprop_st(g, x, w_krsc, bias, z, st); fused = FUSED_ST; }
-  else if (win_fprop_taken(g, dtype)) { e = launch_fprop_win(g, x, w_krsc, bias, z, st); fused = true; }
-  else if (tile_fprop_supported(g, dtype)) { e = launch_fprop_tile(g, x, w_krsc, bias, z, scratch, st); fused = FUSED_TILE; }
-  else if (wave_f32_supported(g, dtype)) { e = launch_fprop_wave(g, x, w_krsc, bias, z, st); fused = true; }
-  else e = igemm_supported(g, dtype) ? launch_fprop_igemm(g, x, w_krsc, bias, z, st)
-                                     : launch_fprop_direct(g, dtype, x, w_krsc, bias, z, st);
+  switch (fprop_kernel(g, dtype)) {
+    case Conv::KS:
+    case Conv::WIN: e = launch_fprop_win(g, x, w_krsc, bias, z, st); fused = true; break;
+    case Conv::PW: e = launch_fprop_pw(g, x, w_krsc, bias, z, st); fused = FUSED_PW; break;
+    case Conv::RW: e = launch_fprop_rw(g, x, w_krsc, bias, z, st); fused = FUSED_RW; break;
+    case Conv::ST: e = launch_fprop_st(g, x, w_krsc, bias, z, st); fused = FUSED_ST; break;
+    case Conv::TILE: e = launch_fprop_tile(g, x, w_krsc, bias, z, scratch, st); fused = FUSED_TILE; break;
+    case Conv::WAVE: e = launch_fprop_wave(g, x, w_krsc, bias, z, st); fused = true; break;
+    case Conv::IGEMM: e = launch_fprop_igemm(g, x, w_krsc, bias, z, st); break;
+    case Conv::DIRECT: e = launch_fprop_direct(g, dtype, x, w_krsc, bias, z, st); break;
+  }
   if (e != hipSuccess || fused || !has_post_op(g)) return e;
   return post_op_pass(g, dtype, z, (size_t)g.M * g.Cout, st);
 }
 hipError_t dgrad_any(const Geom& g, int dtype, const void* dz, const void* w_crsk, const float* bias, void* dx,
                      float* scratch, hipStream_t st) {
-  hipError_t e;
+  hipError_t e = hipErrorInvalidValue;
   bool fused = false;
-  if (ks_dgrad_taken(g, dtype)) { e = launch_dgrad_win(g, dz, w_crsk, bias, dx, st); fused = true; }
-  else if (pw_dgrad_supported(g, dtype)) { e = launch_dgrad_pw(g, dz, w_crsk, bias, dx, st); fused = FUSED_PW; }
-  else if (rw_dgrad_supported(g, dtype)) { e = launch_dgrad_rw(g, dz, w_crsk, bias, dx, st); fused = FUSED_RW; }
-  else if (st_dgrad_supported(g, dtype)) { e = launch_dgrad_st(g, dz, w_crsk, bias, dx, st); fused = FUSED_ST; }
-  else if (win_dgrad_taken(g, dtype)) { e = launch_dgrad_win(g, dz, w_crsk, bias, dx, st); fused = true; }
-  else if (tile_dgrad_supported(g, dtype)) { e = launch_dgrad_tile(g, dz, w_crsk, bias, dx, scratch, st); fused = FUSED_TILE; }
-  else if (wave_f32_supported(g, dtype)) { e = launch_dgrad_wave(g, dz, w_crsk, bias, dx, st); fused = true; }
-  else e = igemm_supported(g, dtype) ? launch_dgrad_igemm(g, dz, w_crsk, bias, dx, st)
-                                     : launch_dgrad_direct(g, dtype, dz, w_crsk, bias, dx, st);
+  switch (dgrad_kernel(g, dtype)) {
+    case Conv::KS:
+    case Conv::WIN: e = launch_dgrad_win(g, dz, w_crsk, bias, dx, st); fused = true; break;
+    case Conv::PW: e = launch_dgrad_pw(g, dz, w_crsk, bias, dx, st); fused = FUSED_PW; break;
+    case Conv::RW: e = launch_dgrad_rw(g, dz, w_crsk, bias, dx, st); fused = FUSED_RW; break;
+    case Conv::ST: e = launch_dgrad_st(g, dz, w_crsk, bias, dx, st); fused = FUSED_ST; break;
+    case Conv::TILE: e = launch_dgrad_tile(g, dz, w_crsk, bias, dx, scratch, st); fused = FUSED_TILE; break;
+    case Conv::WAVE: e = launch_dgrad_wave(g, dz, w_crsk, bias, dx, st); fused = true; break;
+    case Conv::IGEMM: e = launch_dgrad_igemm(g, dz, w_crsk, bias, dx, st); break;
+    case Conv::DIRECT: e = launch_dgrad_direct(g, dtype, dz, w_crsk, bias, dx, st); break;
+  }
   if (e != hipSuccess || fused || !has_post_op(g)) return e;
   return post_op_pass(g, dtype, dx, (size_t)g.Min * g.Cin, st);
 }
@@ -405,15 +423,30 @@ bool dgrad_folds_back_aside(const Geom& g, int dtype) {
   if (needs_cin_pad(g, dtype))
     return stem_dgrad_supported(g, dtype) && stem_wgrad_supported(g, dtype) && stem_dgrad_folds_back_aside(g);
   if (g.K % 4) return false;
-  if (ks_dgrad_taken(g, dtype)) return true;
-  if (pw_dgrad_supported(g, dtype)) return gm_supported(g.M, g.Cout, g.Cin);
-  return !rw_dgrad_supported(g, dtype) && (st_dgrad_supported(g, dtype) || win_dgrad_taken(g, dtype));
+  const Conv k = dgrad_kernel(g, dtype);
+  return k == Conv::PW ? gm_supported(g.M, g.Cout, g.Cin) : k == Conv::KS || k == Conv::ST || k == Conv::WIN;
 }
 // ... run_fprop()'s, a transposed block's fold-back (g.fold_back_t)
 bool fprop_folds_back_aside(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16 || needs_cin_pad(g, dtype)) return false;
-  if (ks_fprop_taken(g, dtype)) return true;
-  return !pw_fprop_supported(g, dtype) && !rw_fprop_supported(g, dtype) && !st_fprop_supported(g, dtype) && win_fprop_taken(g, dtype);
+  const Conv k = fprop_kernel(g, dtype);
+  return k == Conv::KS || k == Conv::WIN;
+}
+// How a Tune block's backward call runs.  FUSED: weight gradient and fold-back in one launch, the input gradient in another;
+// *_PAIR: both gradients in one, then the fold-back; ASIDE: the weight gradient, then the input gradient and the fold-back in
+// one; APART: a launch each.
+enum class Bwd { FUSED, RW_PAIR, WAVE_PAIR, WIN_PAIR, ASIDE, APART };
+bool wgrad_fused_taken(const Geom& g, int dtype) {
+  return !needs_cin_pad(g, dtype) && wgrad_sq_fused_supported(g, dtype) &&
+         wgrad_sq_fused_scratch_bytes(g) <= (size_t)wgrad_way(g, dtype).nsplit * g.Cout * g.K * 4;
+}
+Bwd bwd_way(const Geom& g, int dtype, bool params, bool dx) {
+  const bool both = params && dx, pair = both && !needs_cin_pad(g, dtype) && pair_taken(g, dtype);
+  if (params && !pair && wgrad_fused_taken(g, dtype)) return Bwd::FUSED;
+  if (!both) return Bwd::APART;
+  if (!needs_cin_pad(g, dtype) && wgrad_way(g, dtype).sq && wgrad_dgrad_pair_supported(g, dtype)) return Bwd::RW_PAIR;
+  if (wave_f32_supported(g, dtype)) return Bwd::WAVE_PAIR;
+  return pair ? Bwd::WIN_PAIR : dgrad_folds_back_aside(g, dtype) ? Bwd::ASIDE : Bwd::APART;
 }
 // dw' partials and, when r_part != nullptr, the partial per-channel sums of dz.
 hipError_t wgrad_any(const Geom& g, int dtype, const void* x, const void* dz, float* part, float* r_part,
@@ -787,8 +820,8 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.act & CONVBN_ACT_RELU_IN) g.post_mask = x;   // dx comes out masked with x > 0
   g.post_add = g.add_in;                             // ... after the addend
-  const bool pair = params && dx && !needs_cin_pad(g, dt) && pair_taken(g, dt);
-  if (params && !pair && convbn_tune_bwd_is_fused(desc)) {
+  const Bwd way = bwd_way(g, dt, params, dx != nullptr);
+  if (way == Bwd::FUSED) {
     // deep layers: dw', r and the fold-back in one launch (the fp32 dw' never reaches memory); the space of the
     // fp32 copy holds the few partial sums the workgroups exchange.  Where nothing was kept, the same launch leaves
     // w' for the input gradient, which then runs second: no fold launch.
@@ -803,7 +836,7 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
       LAUNCH(launch_fold(g, dt, W, b, gamma, nullptr, mean, var, 0, nullptr, w.w_crsk, nullptr, st));
       wt = w.w_crsk;
     }
-    if (params && !needs_cin_pad(g, dt) && wgrad_way(g, dt).sq && wgrad_dgrad_pair_supported(g, dt)) {
+    if (way == Bwd::RW_PAIR) {
       // shallow layers: the two gradient passes are independent and share one launch (see wgrad_sq.hip)
       LAUNCH(launch_wgrad_dgrad_pair(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       if (!FUSED_RW) LAUNCH(post_op_pass(g, dt, dx, (size_t)g.Min * g.Cin, st));
@@ -811,13 +844,13 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
                               dW, db, dgamma, dbeta, st));
       return CONVBN_OK;
     }
-    if (params && wave_f32_supported(g, dt)) {   // both gradient passes in one launch
+    if (way == Bwd::WAVE_PAIR) {   // both gradient passes in one launch
       LAUNCH(launch_pair_wave(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       LAUNCH(launch_fold_back(g, dt, w.dwf_part, w.nsplit, w.r_part, w.nrpart, W, b, gamma, mean, var, 0,
                               dW, db, dgamma, dbeta, st));
       return CONVBN_OK;
     }
-    if (pair) {   // ... few pixels: likewise
+    if (way == Bwd::WIN_PAIR) {   // ... few pixels: likewise
       const int ns = win_pair_splits(g);
       LAUNCH(launch_win_pair(g, x, dz, wt, dx, w.dwf_part, w.r_part, st));
       LAUNCH(launch_fold_back(g, dt, w.dwf_part, ns, w.r_part, ns, W, b, gamma, mean, var, 0, dW, db, dgamma, dbeta, st));
@@ -830,7 +863,7 @@ convbn_status convbn_tune_bwd(const convbn_desc* desc, const void* x, const void
              overlap(p, bytes, g.post_mask, ax) || overlap(p, bytes, g.post_add, ax);
     };
     const size_t vec = (size_t)g.Cout * 4;
-    if (params && dgrad_folds_back_aside(g, dt) && !reads(dW, (size_t)g.Cout * g.K * esize(dt)) && !reads(dgamma, vec) &&
+    if (way == Bwd::ASIDE && !reads(dW, (size_t)g.Cout * g.K * esize(dt)) && !reads(dgamma, vec) &&
         !reads(dbeta, vec) && !reads(db, vec)) {
       LAUNCH(run_wgrad(g, dt, x, dz, w.dwf_part, w.r_part, w.wgrad_scratch, st));
       const FoldBackArgs fb{w.dwf_part, w.r_part, W, b, gamma, mean, var, dW, db, dgamma, dbeta, g.eps, w.nsplit, w.nrpart, 0, g.Cout, g.K, 0};
@@ -1470,10 +1503,43 @@ convbn_status convbn_fold_group(int n, const void* table_dev, int grid_blocks, v
 
 int32_t convbn_tune_bwd_is_fused(const convbn_desc* desc) {
   Geom g;
-  if (make_geom(desc, &g) != CONVBN_OK) return 0;
+  return make_geom(desc, &g) == CONVBN_OK && wgrad_fused_taken(g, desc->dtype);
+}
+
+const char* convbn_tune_route(const convbn_desc* desc, int pass) {
+  static thread_local char text[128];
+  Geom g;
+  if (make_geom(desc, &g) != CONVBN_OK) return "";
   const int dt = desc->dtype;
-  return !needs_cin_pad(g, dt) && wgrad_sq_fused_supported(g, dt) &&
-         wgrad_sq_fused_scratch_bytes(g) <= (size_t)wgrad_way(g, dt).nsplit * g.Cout * g.K * 4;
+  const bool fwd = pass == CONVBN_PASS_FWD, first = needs_cin_pad(g, dt);
+  const Geom q = first ? padded_geom(g) : g;
+  char conv[64];
+  if (first && (fwd ? stem_fprop_supported(g, dt) : stem_dgrad_supported(g, dt))) {
+    snprintf(conv, sizeof(conv), "stem");
+  } else {
+    static const char* const names[] = {"", "pw", "rw", "st", "", "tile", "wave", "igemm", "direct"};
+    const Conv k = fwd ? fprop_kernel(q, dt) : dgrad_kernel(q, dt);
+    if (k == Conv::KS || k == Conv::WIN) win_describe(q, fwd, conv, sizeof(conv));
+    else if (k == Conv::PW && gm_supported(q.M, fwd ? q.Cin : q.Cout, fwd ? q.Cout : q.Cin)) snprintf(conv, sizeof(conv), "gm");
+    else if (k == Conv::TILE && (fwd ? tile_fprop_partial_bytes(q) : tile_dgrad_partial_bytes(q)) > 0) snprintf(conv, sizeof(conv), "tile split");
+    else snprintf(conv, sizeof(conv), "%s", names[(int)k]);
+  }
+  if (fwd) {
+    snprintf(text, sizeof(text), "%s", conv);
+    return text;
+  }
+  const WgradWay w = wgrad_way(g, dt);
+  const char* const wgrad = first && stem_wgrad_supported(g, dt) ? "stem" : w.sq ? "sq" : w.win ? "win" : w.wave ? "wave"
+                            : igemm_supported(q, dt) ? "igemm" : "direct";
+  switch (bwd_way(g, dt, true, true)) {
+    case Bwd::FUSED: snprintf(text, sizeof(text), "fused, %s", conv); break;
+    case Bwd::RW_PAIR: snprintf(text, sizeof(text), "pair sq rw, fold-back"); break;
+    case Bwd::WAVE_PAIR: snprintf(text, sizeof(text), "pair wave, fold-back"); break;
+    case Bwd::WIN_PAIR: win_pair_describe(g, conv, sizeof(conv)); snprintf(text, sizeof(text), "pair %s, fold-back", conv); break;
+    case Bwd::ASIDE: snprintf(text, sizeof(text), "%s, %s + fold-back", wgrad, conv); break;
+    case Bwd::APART: snprintf(text, sizeof(text), "%s, %s, fold-back", conv, wgrad); break;
+  }
+  return text;
 }
 
 size_t convbn_fold_back_group_table_bytes(int n) { return n > 0 ? (size_t)n * fold_back_group_item_bytes() : 0; }

@@ -443,6 +443,7 @@ hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, co
 bool ks_fprop_taken(const Geom& g, int dtype);
 bool ks_dgrad_taken(const Geom& g, int dtype);
 hipError_t launch_dgrad_win(const Geom& g, const void* dz, const void* w_crsk, const float* bias, void* dx, hipStream_t st);
+void win_describe(const Geom& g, bool fwd, char* text, size_t bytes);   // "win 128x64", "ks 32x32"
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
                      void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd = nullptr,
                      bool grad = false,
@@ -504,6 +505,7 @@ hipError_t launch_wgrad_win(const Geom& g, const void* x, const void* dz, float*
 // most wgrad_win_splits()) fp32 copies of dw' and of r.
 bool win_pair_taken(const Geom& g, int dtype);
 int win_pair_splits(const Geom& g);
+void win_pair_describe(const Geom& g, char* text, size_t bytes);   // "ks 64x32 win 64x64": the tiles of either gradient
 hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const void* w_crsk, void* dx, float* dwf_part,
                            float* r_part, hipStream_t st);
 

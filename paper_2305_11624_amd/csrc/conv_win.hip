@@ -1,6 +1,8 @@
 // The window product as a launch of its own; its device code is in conv_win_impl.h.
 #include "conv_ks_impl.h"
 
+#include <stdio.h>
+
 #include <algorithm>
 
 namespace convbn {
@@ -220,6 +222,21 @@ const KsGrad& ks_grad(const Geom& g) {
 }  // namespace
 bool ks_dgrad_taken(const Geom& g, int dtype) { return sizes_fit(g, dtype) && ks_grad(g).taken; }
 float win::ks_dgrad_us(const Geom& g) { return ks_grad(g).us; }
+
+void win_describe(const Geom& g, bool fwd, char* text, size_t bytes) {
+  Window c[MAXC];
+  int M[MAXC], n = 1;
+  if (fwd) {
+    c[0] = fprop_window(g);
+    M[0] = g.M;
+  } else {   // (of more classes than a launch takes, those of the first)
+    n = std::min(MAXC, classes_h(g) * classes_w(g));
+    for (int i = 0; i < n; ++i) dgrad_class(g, i / classes_w(g), i % classes_w(g), &c[i], &M[i]);
+  }
+  const WnPlan pl = fwd ? win_plan(g.Cin, g.Cout, n, M, c, st_fprop_supported(g, CONVBN_BF16), folds_aside(g))
+                        : win_plan(g.Cout, g.Cin, n, M, c, st_dgrad_supported(g, CONVBN_BF16), 0);
+  snprintf(text, bytes, "%s %dx%d", pl.ks ? "ks" : "win", pl.tm, pl.tn);
+}
 
 hipError_t launch_fprop_win(const Geom& g, const void* x, const void* w_krsc, const float* bias, void* z, hipStream_t st,
                             const BnEpilogue* bn) {

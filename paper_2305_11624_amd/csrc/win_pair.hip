@@ -6,6 +6,8 @@
 #include "conv_ks_impl.h"
 #include "wgrad_win_impl.h"
 
+#include <stdio.h>
+
 #include <algorithm>
 
 namespace convbn {
@@ -99,6 +101,10 @@ bool win_pair_taken(const Geom& g, int dtype) {
   return plan(g).us <= w.us + (d > w.fold_us ? d : w.fold_us) + slack;
 }
 int win_pair_splits(const Geom& g) { return plan(g).w.slices; }
+void win_pair_describe(const Geom& g, char* text, size_t bytes) {
+  const PairPlan& pl = plan(g);
+  snprintf(text, bytes, "%s %dx%d win %dx%d", pl.tm == 128 ? "win" : "ks", pl.tm, pl.tn, pl.ta, pl.tb);
+}
 hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const void* w_crsk, void* dx, float* part,
                            float* r_part, hipStream_t st) {
   const PairPlan& pl = plan(g);

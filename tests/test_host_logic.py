@@ -330,3 +330,20 @@ def test_copies_of_the_weight_gradient_are_long_slices_or_small(n):
         d = B.desc_from_shape(s)
         copy, m = 4 * s.Cout * s.K, s.N * s.Hout * s.Wout
         assert B.convbn_wgrad_parts(d) * copy <= max(4 << 20, -(-m // 256) * copy), s.name
+
+
+@pytest.mark.parametrize("dims,dtype,fwd,bwd", [
+    ((37, 512, 7, 7, 512, 3, 1, 1), "bf16", "st", "fused, st"),
+    ((40, 64, 56, 56, 64, 3, 1, 1), "bf16", "rw", "pair sq rw, fold-back"),
+    ((1, 256, 18, 18, 256, 3, 1, 1), "bf16", "ks 32x32", "pair ks 32x32 win 64x64, fold-back"),
+    ((40, 128, 30, 30, 264, 3, 2, 1), "bf16", "win 128x64", "win, win 128x128 + fold-back"),
+    ((20, 256, 30, 33, 64, 1, 1, 0), "bf16", "gm", "win, gm + fold-back"),
+    ((9, 3, 24, 24, 32, 3, 2, 1), "bf16", "stem", "stem, stem + fold-back"),
+    ((2, 16, 12, 10, 24, 3, 1, 1), "f32", "wave", "pair wave, fold-back"),
+])
+def test_route_names_what_a_call_launches(dims, dtype, fwd, bwd):
+    from paper_2305_11624_amd.synth import BlockShape
+    d = B.desc_from_shape(BlockShape("route", *dims, dtype, 1))
+    assert (B.convbn_tune_route(d, B.PASS_FWD), B.convbn_tune_route(d, B.PASS_BWD)) == (fwd, bwd)
+    d.stride_h = 0
+    assert B.convbn_tune_route(d, B.PASS_FWD) == ""
