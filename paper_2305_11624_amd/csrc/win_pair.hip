@@ -16,22 +16,23 @@ namespace {
 
 constexpr int CUS = 256;
 
-// TM 128: the window product's 128 x 64 tiles (conv_win_impl.h), fewer workgroups where the wave-split ones would leave the weight
+// TM 128: the window product's 128 x 64 tiles (conv_win_impl.h; FLAT: as there), fewer workgroups where the wave-split ones would leave the weight
 // gradient too few (256 -> 1024 at 14 x 14, 16 images, a pass: 21.6 us with them, 25.5 on two launches)
-template <int TM, int TN, int TA, int TB>
+template <int TM, int TN, bool FLAT, int TA, int TB>
 __global__ __launch_bounds__(512) void win_pair_kernel(wgw::WwParams w, win::WnParams d, int nw) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   if ((int)blockIdx.x < nw) wgw::body<TA, TB>(w, blockIdx.x, smem);
-  else if constexpr (TM == 128) win::body<128, 64, 6, true>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
+  else if constexpr (TM == 128) win::body<128, 64, 6, FLAT>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
   else win::ks_body<TM, TN>(d, FoldSide{}, (int)blockIdx.x - nw, smem);
 }
 
-struct PairPlan { bool ok; int tm, tn, ta, tb, nw, product; float us; wgw::WwParams w; win::WnParams d; };
+struct PairPlan { bool ok, flat; int tm, tn, ta, tb, nw, product; float us; wgw::WwParams w; win::WnParams d; };
 template <int TM, int TN>
 void consider(const Geom& g, PairPlan& best) {
   PairPlan pl{};
   if (!win::dgrad_params(g, &pl.d)) return;
-  win::lay_out<TM, TN, true>(pl.d);
+  pl.flat = TM != 128 || pl.d.C % win::CB != 0;
+  if (pl.flat) win::lay_out<TM, TN, true>(pl.d); else win::lay_out<TM, TN, false>(pl.d);
   int product = pl.d.nconv;   // (positions that no tap reaches: short workgroups, behind the others)
   for (int i = 0; i < pl.d.ncls; ++i)
     if (pl.d.c[i].nchunks == 0 && pl.d.c[i].first < product) product = pl.d.c[i].first;
@@ -77,13 +78,13 @@ constexpr int dgrad_lds() {
   if constexpr (TM == 128) return win::WnCfg<128, 64, 6>::LDS_BYTES;
   else return win::KsCfg<TM, TN>::LDS_BYTES;
 }
-template <int TM, int TN, int TA, int TB>
+template <int TM, int TN, bool FLAT, int TA, int TB>
 hipError_t launch_inst(const wgw::WwParams& w, const win::WnParams& d, int nw, hipStream_t st) {
   static LdsLimitOnce lds_once;
   constexpr int a = wgw::WwCfg<TA, TB>::LDS_BYTES, b = dgrad_lds<TM, TN>(), lds = a > b ? a : b;
-  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&win_pair_kernel<TM, TN, TA, TB>), lds);
+  if (hipError_t e = set_lds_limit_once(lds_once, reinterpret_cast<const void*>(&win_pair_kernel<TM, TN, FLAT, TA, TB>), lds);
       e != hipSuccess) return e;
-  hipLaunchKernelGGL((win_pair_kernel<TM, TN, TA, TB>), dim3(nw + d.nconv), dim3(512), lds, st, w, d, nw);
+  hipLaunchKernelGGL((win_pair_kernel<TM, TN, FLAT, TA, TB>), dim3(nw + d.nconv), dim3(512), lds, st, w, d, nw);
   return hipGetLastError();
 }
 
@@ -114,11 +115,11 @@ hipError_t launch_win_pair(const Geom& g, const void* x, const void* dz, const v
   w.x = (const bf16_t*)x; w.dz = (const bf16_t*)dz; w.part = part; w.r_part = r_part;
   d.act = (const bf16_t*)dz; d.wgt = (const bf16_t*)w_crsk; d.out = (bf16_t*)dx;
   d.relu = g.post_relu; d.mask = (const bf16_t*)g.post_mask; d.add = (const bf16_t*)g.post_add;
-#define PAIR_TILE(TM_, TN_, TA_, TB_) \
-  if (pl.tm == TM_ && pl.tn == TN_ && pl.ta == TA_ && pl.tb == TB_) return launch_inst<TM_, TN_, TA_, TB_>(w, d, pl.nw, st);
-#define PAIR_CASE(TM_, TN_) \
-  PAIR_TILE(TM_, TN_, 64, 64) PAIR_TILE(TM_, TN_, 128, 64) PAIR_TILE(TM_, TN_, 64, 128) PAIR_TILE(TM_, TN_, 128, 128)
-  PAIR_CASE(32, 32) PAIR_CASE(64, 32) PAIR_CASE(64, 64) PAIR_CASE(128, 64)
+#define PAIR_TILE(TM_, TN_, F_, TA_, TB_) \
+  if (pl.tm == TM_ && pl.tn == TN_ && pl.flat == F_ && pl.ta == TA_ && pl.tb == TB_) return launch_inst<TM_, TN_, F_, TA_, TB_>(w, d, pl.nw, st);
+#define PAIR_CASE(TM_, TN_, F_) \
+  PAIR_TILE(TM_, TN_, F_, 64, 64) PAIR_TILE(TM_, TN_, F_, 128, 64) PAIR_TILE(TM_, TN_, F_, 64, 128) PAIR_TILE(TM_, TN_, F_, 128, 128)
+  PAIR_CASE(32, 32, true) PAIR_CASE(64, 32, true) PAIR_CASE(64, 64, true) PAIR_CASE(128, 64, true) PAIR_CASE(128, 64, false)
 #undef PAIR_CASE
 #undef PAIR_TILE
   return hipErrorInvalidValue;
