@@ -525,6 +525,7 @@ hipError_t launch_wgrad_dgrad_pair(const Geom& g, const void* x, const void* dz,
 // w_folded_out (optional): the launch also leaves w' = s w there as [Cin][taps][Cout], for an input gradient that
 // runs after it.
 bool wgrad_sq_fused_supported(const Geom& g, int dtype);
+float wgrad_sq_fused_us(const Geom& g);   // an estimate of that launch
 size_t wgrad_sq_fused_scratch_bytes(const Geom& g);
 hipError_t launch_wgrad_sq_fused(const Geom& g, const void* x, const void* dz, const void* W, const float* b,
                                  const float* gamma, const float* mean, const float* var, void* dW, float* db,

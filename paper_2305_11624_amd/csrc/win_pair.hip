@@ -97,6 +97,10 @@ bool win_pair_taken(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16 || !plan(g).ok) return false;
   const wgw::WwPlan& w = wgw::plan(g);
   const float d = win::ks_dgrad_us(g);
+  // A deep layer's weight gradient comes with its fold-back in one launch; a pair needs a fold-back, and a fold where nothing was kept,
+  // and a workgroup's chain of 128 x 64 tiles is long.  A pass, us, the pair and that launch: 3 x 3, 512 -> 512 at 7 x 7, 16 images
+  // 40.8, 42.6, with 128 x 64 tiles 24 images 54.1, 50.4, 36 images 54.4, 51.5; 640 -> 512 at 8 x 9, 4 images 40.9, 46.6.
+  if (wgrad_sq_fused_supported(g, dtype)) return plan(g).tm < 128 && plan(g).us + 4.f <= wgrad_sq_fused_us(g) + d;
   // (positions that no tap reaches take compute units off the weight gradient: 1 x 1 / 2, 512 -> 1024 at 18 x 17, 15 images 23.9 a pass, 22.5)
   const float slack = plan(g).d.nconv > CUS / 2 && plan(g).product < plan(g).d.nconv ? -2.f : 1.5f;
   return plan(g).us <= w.us + (d > w.fold_us ? d : w.fold_us) + slack;

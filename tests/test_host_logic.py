@@ -347,3 +347,17 @@ def test_route_names_what_a_call_launches(dims, dtype, fwd, bwd):
     assert (B.convbn_tune_route(d, B.PASS_FWD), B.convbn_tune_route(d, B.PASS_BWD)) == (fwd, bwd)
     d.stride_h = 0
     assert B.convbn_tune_route(d, B.PASS_FWD) == ""
+
+
+@pytest.mark.parametrize("dims,bwd", [
+    # a deep layer's weight gradient and fold-back in one launch, and the input gradient: against a launch of both gradients on 128 x 64
+    # tiles 50.4 us a pass, 60.3 (24 images), 51.5, 59.7 (36)
+    ((24, 512, 7, 7, 512, 3, 1, 1), "fused, ks 64x64"),
+    ((36, 512, 7, 7, 512, 3, 1, 1), "fused, st"),
+    ((28, 384, 8, 8, 640, 3, 1, 1), "fused, ks 64x64"),
+    # ... where small tiles do, one launch: 40.8 us a pass, 42.6
+    ((16, 512, 7, 7, 512, 3, 1, 1), "pair ks 64x64 win 128x128, fold-back"),
+])
+def test_one_launch_of_both_gradients_or_two(dims, bwd):
+    from paper_2305_11624_amd.synth import BlockShape
+    assert B.convbn_tune_route(B.desc_from_shape(BlockShape("route", *dims, "bf16", 1)), B.PASS_BWD) == bwd
