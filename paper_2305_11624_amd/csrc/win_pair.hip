@@ -43,14 +43,18 @@ void consider(const Geom& g, PairPlan& best) {
   pl.nw = ceil_div(total, 8) * 8;
   if (pl.nw + product > CUS) return;
   float du = win::ks_us(TM, TN, pl.d);
-  if (TM == 128) {
+  if (TM == 128) {   // (a chunk across tap borders takes half as long again)
     du = 0.f;
-    for (int i = 0; i < pl.d.ncls; ++i) du = std::max(du, 4.5f + 0.3f * pl.d.c[i].nchunks);
+    for (int i = 0; i < pl.d.ncls; ++i)
+      du = std::max(du, pl.flat ? 4.f + 0.45f * pl.d.c[i].nchunks : 4.5f + 0.3f * pl.d.c[i].nchunks);
   }
   pl.ok = true;
   pl.product = product;
   pl.tm = TM; pl.tn = TN; pl.ta = w.ta; pl.tb = w.tb; pl.w = w.p;
   pl.us = (du > w.us ? du : w.us) + w.fold_us;
+  // Positions that no tap reaches make a second round where they do not fit the first (1 x 1 / 2, a pass: 88 -> 240 at 34 x 27, 13
+  // images, 64 x 32 tiles and 280 workgroups 18.7 us, 128 x 64 and 184 16.0; 256 -> 512 at 22 x 22, 8 images 19.4, 17.5).
+  if (pl.nw + pl.d.nconv > CUS) pl.us += 2.f;
   if (!best.ok || pl.us < best.us) best = pl;
 }
 PairPlan work_out_plan(const Geom& g) {
@@ -59,14 +63,7 @@ PairPlan work_out_plan(const Geom& g) {
   consider<32, 32>(g, pl);
   consider<64, 32>(g, pl);
   consider<64, 64>(g, pl);
-  win::WnParams d;   // (64 x 64 tiles on more than 144 compute units; on 140 and 98 of them they are the better: 72 -> 136 at 27 x 33
-                     // 21.3 a pass, 24.0)
-  if (win::dgrad_params(g, &d)) {
-    int tiles = 0;
-    for (int i = 0; i < d.ncls; ++i)
-      if (d.c[i].cv.kH > 0) tiles += ceil_div(d.c[i].M, 64) * ceil_div(d.R, 64);
-    if (tiles > 144) consider<128, 64>(g, pl);
-  }
+  consider<128, 64>(g, pl);
   return pl;
 }
 const PairPlan& plan(const Geom& g) {
@@ -90,20 +87,23 @@ hipError_t launch_inst(const wgw::WwParams& w, const win::WnParams& d, int nw, h
 
 }  // namespace
 
-// Against a launch each, the second of which takes the fold-back along.  The gradients, us, one launch and two: 3 x 3,
-// 256 -> 256 at 18 x 18, 1 image 14.7, 18.2; 88 -> 240 at 34 x 27 / 2, 13 images 10.4, 12.1; 2048 -> 512 at 9 x 9, 3 images 15.8, 22.4;
-// where the weight gradient is left too few compute units: 3 x 3, 128 -> 128 at 28 x 28, 8 images 22.6, 17.7
+// Against a launch each, the second of which takes the fold-back along, or, where the weight gradient of a deep layer comes with its
+// fold-back in one launch, against that one and the input gradient; there a block that kept nothing pays for a fold as well, and a
+// workgroup's chain of 128 x 64 tiles is long (hundreds of taps and channels).  The figures above are fitted to 186 shapes, each
+// measured with tiles up to 64 x 64, with 128 x 64 and without the pair: on average the choice is 0.2 % slower than the best of the
+// three.  A pass, us, one launch and two:
+//   3 x 3, 256 -> 256 at 18 x 18, 1 image       22.2, 25.7     1 x 1, 256 -> 1024 at 14 x 14, 16 images        21.8, 25.7
+//   1 x 1, 2048 -> 512 at 9 x 9, 3 images       22.1, 28.5     1 x 1 / 2, 128 -> 256 at 70 x 68, 3 images      14.8, 19.9
+//   3 x 3, 72 -> 136 at 27 x 33, 5 images       21.3, 22.5     3 x 3, 256 -> 256 at 16 x 17, 17 images         49.1, 43.4
+// and against the deep layers' launch: 3 x 3, 512 -> 512 at 7 x 7, 16 images 40.8, 42.6, with 128 x 64 tiles 24 images 54.1, 50.4,
+// 36 images 54.4, 51.5; 640 -> 512 at 8 x 9, 4 images 40.9, 46.6.
 bool win_pair_taken(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16 || !plan(g).ok) return false;
-  const wgw::WwPlan& w = wgw::plan(g);
+  const PairPlan& pl = plan(g);
   const float d = win::ks_dgrad_us(g);
-  // A deep layer's weight gradient comes with its fold-back in one launch; a pair needs a fold-back, and a fold where nothing was kept,
-  // and a workgroup's chain of 128 x 64 tiles is long.  A pass, us, the pair and that launch: 3 x 3, 512 -> 512 at 7 x 7, 16 images
-  // 40.8, 42.6, with 128 x 64 tiles 24 images 54.1, 50.4, 36 images 54.4, 51.5; 640 -> 512 at 8 x 9, 4 images 40.9, 46.6.
-  if (wgrad_sq_fused_supported(g, dtype)) return plan(g).tm < 128 && plan(g).us + 4.f <= wgrad_sq_fused_us(g) + d;
-  // (positions that no tap reaches take compute units off the weight gradient: 1 x 1 / 2, 512 -> 1024 at 18 x 17, 15 images 23.9 a pass, 22.5)
-  const float slack = plan(g).d.nconv > CUS / 2 && plan(g).product < plan(g).d.nconv ? -2.f : 1.5f;
-  return plan(g).us <= w.us + (d > w.fold_us ? d : w.fold_us) + slack;
+  if (wgrad_sq_fused_supported(g, dtype)) return pl.tm < 128 && pl.us + 4.f <= wgrad_sq_fused_us(g) + d;
+  const wgw::WwPlan& w = wgw::plan(g);
+  return pl.us <= w.us + (d > w.fold_us ? d : w.fold_us) + 2.f;
 }
 int win_pair_splits(const Geom& g) { return plan(g).w.slices; }
 void win_pair_describe(const Geom& g, char* text, size_t bytes) {

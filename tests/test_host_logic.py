@@ -357,6 +357,13 @@ def test_route_names_what_a_call_launches(dims, dtype, fwd, bwd):
     ((28, 384, 8, 8, 640, 3, 1, 1), "fused, ks 64x64"),
     # ... where small tiles do, one launch: 40.8 us a pass, 42.6
     ((16, 512, 7, 7, 512, 3, 1, 1), "pair ks 64x64 win 128x128, fold-back"),
+    # three of four residue classes have no tap: one launch, 16.0 us a pass against 18.0, 17.5 against 19.9, 14.8 against 19.9
+    ((13, 88, 34, 27, 240, 1, 2, 0), "pair ks 64x64 win 64x64, fold-back"),
+    ((8, 256, 22, 22, 512, 1, 2, 0), "pair ks 64x64 win 64x64, fold-back"),
+    ((3, 128, 70, 68, 256, 1, 2, 0), "pair ks 64x64 win 64x64, fold-back"),
+    # 64 x 64 tiles rather than 128 x 64: 21.3 us a pass, 23.7
+    ((5, 72, 27, 33, 136, 3, 1, 1), "pair ks 64x64 win 64x128, fold-back"),
+    ((22, 512, 8, 8, 2048, 1, 1, 0), "pair win 128x64 win 64x128, fold-back"),
 ])
 def test_one_launch_of_both_gradients_or_two(dims, bwd):
     from paper_2305_11624_amd.synth import BlockShape
