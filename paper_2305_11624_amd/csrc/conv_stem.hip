@@ -938,9 +938,7 @@ bool stem_dgrad_supported(const Geom& g, int dtype) {
 bool stem_dgrad_folds_back_aside(const Geom& g) {
   StemDgParams p;
   const StemDgPlan pl = stem_dg_plan(g, &p);
-  FoldBackArgs fb{};
-  fb.K = g.K; fb.Cout = g.Cout; fb.nsplit = stem_wgrad_slices(g); fb.part = reinterpret_cast<const float*>(16);
-  return pl.ok && g.K >= 4 && pl.grid + fold_back_side_blocks(fb, 256) <= pl.room;
+  return pl.ok && g.K >= 4 && pl.grid + fold_back_side_blocks(g.K, stem_wgrad_slices(g), g.Cout, 256) <= pl.room;
 }
 namespace {
 template <int UU, int VV, int KS, class Side>

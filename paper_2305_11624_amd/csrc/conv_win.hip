@@ -11,7 +11,7 @@ using namespace win;
 
 namespace {
 
-constexpr int KS_FEW = 6, KS_MANY = 48;
+constexpr int CUS = 256, KS_FEW = 6, KS_MANY = 48;
 // The tile of the wave-split product: the smallest whose workgroups are one round (3 x 3, 512 -> 512: 32 x 32 8.9 us, 64 x 32 11.3,
 // 64 x 64 14.3 where all three are; a second round takes as long as the first: 17.3), `aside` counted in: 256 tiles and eight
 // workgroups that fold took 8.1 us (128 -> 512 at 31 x 31, 1 image), 128 x 64 tiles 5.4.  None where 64 x 64 tiles are more
@@ -20,7 +20,6 @@ constexpr int KS_FEW = 6, KS_MANY = 48;
 // images, 72 chunks: 16.4 there, 17.7; 128 -> 128 at 28 x 28, 8 images, 18 chunks: 9.8 there, 8.3).
 struct KsTile { int tm, tn; };   // tm == 0: not taken
 KsTile ks_tile(int C, int R, int n, const int* M, const Window* cv, bool deep, int aside) {
-  constexpr int CUS = 256;
   constexpr KsTile sizes[] = {{32, 32}, {64, 32}, {64, 64}};
   int chunks = 0;
   for (int i = 0; i < n; ++i) chunks = std::max(chunks, ceil_div(cv[i].kH * cv[i].kW * (C >> 3), CB / 8));
@@ -174,6 +173,10 @@ Window fprop_window(const Geom& g) {
 }
 // Workgroups that fold behind a forward product: where w' is small enough to be kept (the call may decide otherwise)
 int folds_aside(const Geom& g) { return g.K <= g.M ? ceil_div(ceil_div(g.K, 64) * ceil_div(g.Cout, 64), 2) : 0; }
+// ... that fold back behind an input gradient (of the copies that a window weight gradient leaves; another kernel may have left others)
+int folds_back_aside(const Geom& g) {
+  return wgrad_win_supported(g, CONVBN_BF16) ? fold_back_side_blocks(g.K, wgrad_win_splits(g), g.Cout, 64 * NWAVES) : 0;
+}
 // residue classes that have positions, in rows and columns
 int classes_h(const Geom& g) { return g.sh < g.Hin ? g.sh : g.Hin; }
 int classes_w(const Geom& g) { return g.sw < g.Win ? g.sw : g.Win; }
@@ -197,7 +200,7 @@ bool ks_fprop_taken(const Geom& g, int dtype) {
   return ks_tile(g.Cin, g.Cout, 1, &g.M, &c, st_fprop_supported(g, dtype), folds_aside(g)).tm != 0;
 }
 namespace {
-struct KsGrad { bool taken; float us; };
+struct KsGrad { bool taken; float us, back_us; };
 const KsGrad& ks_grad(const Geom& g) {
   return planned<KsGrad>(g, CONVBN_BF16, [&] {
     KsGrad r{};
@@ -209,6 +212,7 @@ const KsGrad& ks_grad(const Geom& g) {
     const KsTile t = ks_tile(p.C, p.R, p.ncls, M, c, st_dgrad_supported(g, CONVBN_BF16), 0);
     if (t.tm == 0) {   // (another kernel's)
       for (int i = 0; i < p.ncls; ++i) r.us = std::max(r.us, 5.5f + 0.2f * ceil_div(c[i].kH * c[i].kW * p.C, CB));
+      r.back_us = r.us;
       return r;
     }
     if (t.tm == 32) lay_out<32, 32, true>(p);
@@ -216,12 +220,15 @@ const KsGrad& ks_grad(const Geom& g) {
     else lay_out<64, 64, true>(p);
     r.taken = true;
     r.us = ks_us(t.tm, t.tn, p);
+    // (where the compute units are full they start when its first workgroups are done: 3 x 3, 184 -> 208 at 22 x 48, 5 images, 249 tiles
+    // and 52 that fold back 16.0 us; 32 x 32: two share a compute unit)
+    r.back_us = t.tm > 32 && p.nconv + folds_back_aside(g) > CUS ? r.us + 4.f : r.us;
     return r;
   });
 }
 }  // namespace
 bool ks_dgrad_taken(const Geom& g, int dtype) { return sizes_fit(g, dtype) && ks_grad(g).taken; }
-float win::ks_dgrad_us(const Geom& g) { return ks_grad(g).us; }
+float win::ks_dgrad_us(const Geom& g, bool back) { return back ? ks_grad(g).back_us : ks_grad(g).us; }
 
 void win_describe(const Geom& g, bool fwd, char* text, size_t bytes) {
   Window c[MAXC];

@@ -461,8 +461,9 @@ inline void lay_out(WnParams& p) {
 
 // The parameters of an input gradient whose residue classes fit one launch (no pointers); false: they do not.
 bool dgrad_params(const Geom& g, WnParams* p);
-// An estimate of the input gradient as a launch of its own (0: its residue classes are more than one).
-float ks_dgrad_us(const Geom& g);
+// An estimate of the input gradient as a launch of its own, with a fold-back behind its workgroups where `back` (0: it has more
+// residue classes than a launch takes).
+float ks_dgrad_us(const Geom& g, bool back);
 
 }  // namespace win
 }  // namespace convbn

@@ -297,11 +297,17 @@ __device__ __forceinline__ void fold_back_row(const FoldBackArgs& a, int co, int
 // (4 - 5 us; a pass: 256 -> 64 channels at 56 x 56, 32 images 46.8 -> 43.8 us, at 46 x 40, 13 images 23.5 -> 19.5; 3 -> 32, 3 x 3
 // / 2 at 172 x 172, 17 images 34.5 -> 29.4).  A workgroup of `threads` takes as many channels as leave a thread about sixteen loads.
 constexpr int FOLD_BACK_SIDE_BYTES(int threads) { return threads * 16 + threads / 64 * 8; }
+inline int fold_back_side_threads(int K, int nsplit, int threads) {   // of a channel
+  const long long loads = (long long)ceil_div(K, 4) * nsplit;
+  int per = 64;
+  while (per < threads && loads > 16LL * per) per *= 2;
+  return per;
+}
+inline int fold_back_side_blocks(int K, int nsplit, int Cout, int threads) {
+  return ceil_div(Cout, threads / fold_back_side_threads(K, nsplit, threads));
+}
 inline int fold_back_side_blocks(FoldBackArgs& a, int threads) {
-  if (!a.part) return 0;
-  const long long loads = (long long)ceil_div(a.K, 4) * a.nsplit;
-  a.per = 64;
-  while (a.per < threads && loads > 16LL * a.per) a.per *= 2;
+  a.per = fold_back_side_threads(a.K, a.nsplit, threads);
   return ceil_div(a.Cout, threads / a.per);
 }
 // smem: FOLD_BACK_SIDE_BYTES(THREADS)

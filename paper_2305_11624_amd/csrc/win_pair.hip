@@ -100,9 +100,9 @@ hipError_t launch_inst(const wgw::WwParams& w, const win::WnParams& d, int nw, h
 bool win_pair_taken(const Geom& g, int dtype) {
   if (dtype != CONVBN_BF16 || !plan(g).ok) return false;
   const PairPlan& pl = plan(g);
-  const float d = win::ks_dgrad_us(g);
-  if (wgrad_sq_fused_supported(g, dtype)) return pl.tm < 128 && pl.us + 4.f <= wgrad_sq_fused_us(g) + d;
+  if (wgrad_sq_fused_supported(g, dtype)) return pl.tm < 128 && pl.us + 4.f <= wgrad_sq_fused_us(g) + win::ks_dgrad_us(g, false);
   const wgw::WwPlan& w = wgw::plan(g);
+  const float d = win::ks_dgrad_us(g, true);
   return pl.us <= w.us + (d > w.fold_us ? d : w.fold_us) + 2.f;
 }
 int win_pair_splits(const Geom& g) { return plan(g).w.slices; }

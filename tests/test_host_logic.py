@@ -364,6 +364,11 @@ def test_route_names_what_a_call_launches(dims, dtype, fwd, bwd):
     # 64 x 64 tiles rather than 128 x 64: 21.3 us a pass, 23.7
     ((5, 72, 27, 33, 136, 3, 1, 1), "pair ks 64x64 win 64x128, fold-back"),
     ((22, 512, 8, 8, 2048, 1, 1, 0), "pair win 128x64 win 64x128, fold-back"),
+    # the input gradient fills the compute units, so that workgroups that fold back would start a second round: 38.7 us a pass, 44.2;
+    # 40.6, 46.6; 25.9, 30.0
+    ((5, 184, 22, 48, 208, 3, 1, 1), "pair win 128x64 win 128x128, fold-back"),
+    ((31, 256, 12, 11, 256, 3, 1, 1), "pair win 128x64 win 128x128, fold-back"),
+    ((6, 72, 22, 39, 216, 3, 1, 1), "pair ks 64x64 win 128x128, fold-back"),
 ])
 def test_one_launch_of_both_gradients_or_two(dims, bwd):
     from paper_2305_11624_amd.synth import BlockShape
