@@ -29,7 +29,7 @@ __device__ __forceinline__ void fbt_colsum(const RSum& rs, int Co, int block, in
 
 // A wave owns RW rows of its workgroup's 4 RW, UN copies of them all asked for at once, and a lane four consecutive columns.
 template <typename T, int RW, int UN>
-__device__ __forceinline__ void fbt_rows(const FoldBackTArgs& a, int block, int tid, unsigned char* smem) {
+__device__ __forceinline__ void fbt_rows(const FoldBackTArgs& a, int block, int tid, bool live, unsigned char* smem) {
   const float* const part = a.part; const T* const W = static_cast<const T*>(a.W); T* const dW = static_cast<T*>(a.dW);
   const float* const gamma = a.gamma;
   const int nsplit = a.nsplit, rows = a.rows, Co = a.Co;
@@ -63,7 +63,7 @@ __device__ __forceinline__ void fbt_rows(const FoldBackTArgs& a, int block, int 
       for (int e = 0; e < 4; ++e) s[e] /= sqrtf(v[e] + a.eps);
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
-      if (!in[i]) continue;
+      if (!in[i] || !live) continue;
       float o[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) { o[e] = s[e] * dw[i][e]; dot[e] += dw[i][e] * w[i][e]; }
@@ -76,12 +76,12 @@ __device__ __forceinline__ void fbt_rows(const FoldBackTArgs& a, int block, int 
   for (int e = 0; e < 4; ++e) sum[wave * 256 + lane * 4 + e] = dot[e];
   __syncthreads();
   const int c = tid, co = bx * 256 + c;
-  if (co < Co) a.dot_part[(size_t)by * Co + co] = sum[c] + sum[256 + c] + sum[512 + c] + sum[768 + c];
+  if (live && co < Co) a.dot_part[(size_t)by * Co + co] = sum[c] + sum[256 + c] + sum[512 + c] + sum[768 + c];
 }
 
 // Thread -> column group el (of EL / cw rows, cw columns of four each) and every (256 / EL)-th partial copy.
 template <typename T, int EL>
-__device__ __forceinline__ void fbt_split(const FoldBackTArgs& a, int block, int tid, unsigned char* smem) {
+__device__ __forceinline__ void fbt_split(const FoldBackTArgs& a, int block, int tid, bool live, unsigned char* smem) {
   constexpr int SL = 256 / EL;
   struct Red { float copy[SL][EL * 4], dot[EL * 4]; };
   static_assert(sizeof(Red) <= FBT_SMEM, "LDS of 256 threads");
@@ -102,7 +102,7 @@ __device__ __forceinline__ void fbt_split(const FoldBackTArgs& a, int block, int
     // the element this thread finishes: column e of group fe
   const int fe = tid >> 2, fc = (bx * cw + fe % cw) * 4 + (tid & 3);
   size_t fat = 0;
-  const bool fin = tid < EL * 4 && element(fe, fat);
+  const bool fin = live && tid < EL * 4 && element(fe, fat);
   fat += tid & 3;
   const float fw = fin ? to_f32(W[fat]) : 0.f;
   const float fg = fin && gamma ? gamma[fc] : 1.f, fv = fin && gamma ? a.var[fc] : 1.f;
@@ -141,26 +141,31 @@ __device__ __forceinline__ void fbt_split(const FoldBackTArgs& a, int block, int
 }
 
 
-// block of the fold-back proper, by 256 threads; UN copies of eight rows in flight a thread
+// block of the fold-back proper, by 256 threads; UN copies of eight rows in flight a thread; !live: nothing is stored
 template <typename T, int UN>
-__device__ __forceinline__ void fbt_block(const FoldBackTArgs& a, int block, int tid, unsigned char* smem) {
-  if (a.kind == FBT_ROWS_2) fbt_rows<T, 2, 4>(a, block, tid, smem);
-  else if (a.kind == FBT_ROWS_8) fbt_rows<T, 8, UN>(a, block, tid, smem);
-  else if (a.kind == FBT_SPLIT_16) fbt_split<T, 16>(a, block, tid, smem);
-  else fbt_split<T, 64>(a, block, tid, smem);
+__device__ __forceinline__ void fbt_block(const FoldBackTArgs& a, int block, int tid, bool live, unsigned char* smem) {
+  if (a.kind == FBT_ROWS_2) fbt_rows<T, 2, 4>(a, block, tid, live, smem);
+  else if (a.kind == FBT_ROWS_8) fbt_rows<T, 8, UN>(a, block, tid, live, smem);
+  else if (a.kind == FBT_SPLIT_16) fbt_split<T, 16>(a, block, tid, live, smem);
+  else fbt_split<T, 64>(a, block, tid, live, smem);
 }
 
 // Along with the block's input gradient (a convolution of dZ), as fold_back_side in fold_tile.h: workgroup `wg` of 512 threads
 // takes two blocks, both of the column sums or both of the fold-back (the halves meet at the same barriers); where
-// there is an odd one its neighbour is done twice, with the same values.  bf16.  FLIGHT as there.  smem: 2 FBT_SMEM.
+// there is an odd one the second half only meets the barriers and stores nothing (dW may take the place of W, which the first half
+// still reads then).  bf16.  FLIGHT as there.  smem: 2 FBT_SMEM.
 inline int fold_back_side_blocks(const FoldBackTArgs& a, int) { return ceil_div(a.rs.blocks, 2) + ceil_div(a.blocks, 2); }
 template <int THREADS, RowKind, int FLIGHT, int>
 __device__ __forceinline__ void fold_back_side(const FoldBackTArgs& a, int wg, unsigned char* smem) {
   static_assert(THREADS == 512, "two halves");
   const int half = (int)threadIdx.x >> 8, tid = (int)threadIdx.x & 255, sums = (a.rs.blocks + 1) >> 1;
   unsigned char* const mine = smem + half * FBT_SMEM;
-  if (wg < sums) fbt_colsum(a.rs, a.Co, min(2 * wg + half, a.rs.blocks - 1), tid, mine);
-  else fbt_block<bf16_t, FLIGHT < 16 ? 1 : 4>(a, min(2 * (wg - sums) + half, a.blocks - 1), tid, mine);
+  if (wg < sums) {
+    fbt_colsum(a.rs, a.Co, min(2 * wg + half, a.rs.blocks - 1), tid, mine);
+  } else {
+    const int block = 2 * (wg - sums) + half;
+    fbt_block<bf16_t, FLIGHT < 16 ? 1 : 4>(a, min(block, a.blocks - 1), tid, block < a.blocks, mine);
+  }
 }
 
 }  // namespace convbn

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void fold_back_t_kernel(FoldBackTArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[FBT_SMEM];
   const int block = blockIdx.x;
   if (block < a.rs.blocks) fbt_colsum(a.rs, a.Co, block, threadIdx.x, smem);
-  else fbt_block<T, 4>(a, block - a.rs.blocks, threadIdx.x, smem);
+  else fbt_block<T, 4>(a, block - a.rs.blocks, threadIdx.x, true, smem);
 }
 
 // Any Co.  grid (ceil(Co/64), ceil(rows/8)).  Thread -> column tid%64, row lane tid/64.

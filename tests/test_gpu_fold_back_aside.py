@@ -76,3 +76,20 @@ def test_transposed_gradient_over_an_operand(over):
     r.dW = getattr(r, over).flatten()[:r.dW.numel()].view(r.dW.shape)
     r.backward()
     compare(r.results(), ref, "bf16", keys=("dX", "dW", "dgamma", "dbeta"), tag=over)
+
+
+@pytest.mark.parametrize("n,cin,h,w,cout,k,s,p", [
+    (1, 24, 9, 5, 8, 3, 2, 1),        # rows, 27 workgroups of 256 threads: the last has nothing beside it
+    (1, 40, 6, 5, 16, 3, 2, 1),       # ... 45
+    (2, 72, 30, 23, 40, 4, 2, 1),     # copies shared
+])
+def test_transposed_gradient_in_place_of_the_weight(n, cin, h, w, cout, k, s, p):
+    """dW may take the place of W: every row is read by the threads that write it, and by no others."""
+    inp = synth.make_tconv_inputs(BlockShape("fbt", n, cin, h, w, cout, k, s, p, "bf16", 11))
+    ref = oracle_tconv_block(inp)
+    for keep in (True, False):
+        r = TconvRun(inp, poison=True, keep_folded=keep)
+        r.forward()
+        r.dW = r.W
+        r.backward()
+        compare(r.results(), ref, "bf16", keys=("dX", "dW", "dgamma", "dbeta"), tag="keep %s" % keep)
