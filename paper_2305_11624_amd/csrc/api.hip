@@ -121,6 +121,13 @@ WgradWay wgrad_way(const Geom& g0, int dtype) {
 }
 int nsplit_for(const Geom& g, int dtype) { return wgrad_way(g, dtype).nsplit; }
 
+// Partial copies that a Tune block's backward call may leave: of a launch for both gradients (which may be more), or of the weight
+// gradient on its own.
+int bwd_copies(const Geom& g, int dtype, int alone) {
+  const int pair = !needs_cin_pad(g, dtype) && pair_taken(g, dtype) ? win_pair_splits(g) : 0;
+  return pair > alone ? pair : alone;
+}
+
 size_t inner_fprop_scratch(const Geom& g, int dtype);
 size_t inner_dgrad_scratch(const Geom& g, int dtype);
 // Elements of the largest fp32 buffer of partial sums a problem's kernels would write: the split copies of dw' and
@@ -132,7 +139,7 @@ long long widest_partial_elems(const Geom& g0, int dtype) {
   const long long act = (long long)(g0.M > g0.Min ? g0.M : g0.Min) * (g0.Cout > g0.Cin ? g0.Cout : g0.Cin);
   if (pp <= lim / 1024 && act <= lim / 64) return 0;
   const Geom g = needs_cin_pad(g0, dtype) ? padded_geom(g0) : g0;
-  long long widest = (long long)wgrad_way(g0, dtype).nsplit * g.Cout * g.K;
+  const long long widest = (long long)bwd_copies(g0, dtype, wgrad_way(g0, dtype).nsplit) * g.Cout * g.K;
   const long long conv = (long long)((inner_fprop_scratch(g, dtype) > inner_dgrad_scratch(g, dtype)
                                           ? inner_fprop_scratch(g, dtype) : inner_dgrad_scratch(g, dtype)) / 4);
   return widest > conv ? widest : conv;
@@ -182,11 +189,9 @@ TuneBwdWs carve_tune_bwd(const Geom& g, int dtype, void* ws) {
   const WgradWay way = wgrad_way(g, dtype);
   r.nsplit = way.nsplit;
   r.nrpart = way.nrpart;
-  // (room for either of the two ways that backward may take: both gradients in one launch, or this one on its own)
-  const int npair = !needs_cin_pad(g, dtype) && pair_taken(g, dtype) ? win_pair_splits(g) : 0;
   r.w_crsk = c.take((size_t)g.Cout * g.K * esize(dtype));
-  r.dwf_part = (float*)c.take((size_t)(npair > r.nsplit ? npair : r.nsplit) * g.Cout * g.K * 4);
-  r.r_part = (float*)c.take((size_t)(npair > r.nrpart ? npair : r.nrpart) * g.Cout * 4);
+  r.dwf_part = (float*)c.take((size_t)bwd_copies(g, dtype, r.nsplit) * g.Cout * g.K * 4);
+  r.r_part = (float*)c.take((size_t)bwd_copies(g, dtype, r.nrpart) * g.Cout * 4);
   r.conv_scratch = (float*)c.take(dgrad_scratch_bytes(g, dtype));
   r.wgrad_scratch = c.take(wgrad_scratch_bytes(g, dtype));
   r.bytes = c.off;

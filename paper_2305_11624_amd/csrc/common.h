@@ -501,8 +501,8 @@ bool wgrad_win_supported(const Geom& g, int dtype);
 int wgrad_win_splits(const Geom& g);
 hipError_t launch_wgrad_win(const Geom& g, const void* x, const void* dz, float* dwf_part, float* r_part, hipStream_t st);
 
-// win_pair.hip : the two above as one launch, for problems whose workgroups fit the chip together; win_pair_splits() (at
-// most wgrad_win_splits()) fp32 copies of dw' and of r.
+// win_pair.hip : the two above as one launch, for problems whose workgroups fit the chip together; win_pair_splits()
+// (its tiles are its own: also more than wgrad_win_splits()) fp32 copies of dw' and of r.
 bool win_pair_taken(const Geom& g, int dtype);
 int win_pair_splits(const Geom& g);
 void win_pair_describe(const Geom& g, char* text, size_t bytes);   // "ks 64x32 win 64x64": the tiles of either gradient
