@@ -269,18 +269,28 @@ bool win_dgrad_taken(const Geom& g, int dtype) {
 // Whether the two gradient passes of a block share a launch (win_pair.hip).
 bool pair_taken(const Geom& g, int dtype) { return win_pair_taken(g, dtype); }
 
+// The kernel of each convolution (KS: the window product's wave-split tiles)
+enum class Conv { KS, PW, RW, ST, WIN, TILE, WAVE, IGEMM, DIRECT };
+Conv fprop_kernel(const Geom& g, int dtype) {
+  return ks_fprop_taken(g, dtype) ? Conv::KS : pw_fprop_supported(g, dtype) ? Conv::PW : rw_fprop_supported(g, dtype) ? Conv::RW
+         : st_fprop_supported(g, dtype) ? Conv::ST : win_fprop_taken(g, dtype) ? Conv::WIN
+         : tile_fprop_supported(g, dtype) ? Conv::TILE : wave_f32_supported(g, dtype) ? Conv::WAVE
+         : igemm_supported(g, dtype) ? Conv::IGEMM : Conv::DIRECT;
+}
+Conv dgrad_kernel(const Geom& g, int dtype) {
+  return ks_dgrad_taken(g, dtype) ? Conv::KS : pw_dgrad_supported(g, dtype) ? Conv::PW : rw_dgrad_supported(g, dtype) ? Conv::RW
+         : st_dgrad_supported(g, dtype) ? Conv::ST : win_dgrad_taken(g, dtype) ? Conv::WIN
+         : tile_dgrad_supported(g, dtype) ? Conv::TILE : wave_f32_supported(g, dtype) ? Conv::WAVE
+         : igemm_supported(g, dtype) ? Conv::IGEMM : Conv::DIRECT;
+}
+
 // Scratch the three convolutions of a problem need (0 for most): fp32 partial outputs when the
-// reduced channels are split over workgroups, and the zero-padded copies of needs_cin_pad().  (The wave-split product needs
-// none; where it has taken over such a split, the size stays what callers were told before.)
+// reduced channels are split over workgroups, and the zero-padded copies of needs_cin_pad().
 size_t inner_fprop_scratch(const Geom& g, int dtype) {
-  if (pw_fprop_supported(g, dtype) || rw_fprop_supported(g, dtype) || st_fprop_supported(g, dtype) ||
-      win_fprop_taken(g, dtype)) return 0;
-  return tile_fprop_supported(g, dtype) ? align_up(tile_fprop_partial_bytes(g), 256) : 0;
+  return fprop_kernel(g, dtype) == Conv::TILE ? align_up(tile_fprop_partial_bytes(g), 256) : 0;
 }
 size_t inner_dgrad_scratch(const Geom& g, int dtype) {
-  if (pw_dgrad_supported(g, dtype) || rw_dgrad_supported(g, dtype) || st_dgrad_supported(g, dtype) ||
-      win_dgrad_taken(g, dtype)) return 0;
-  return tile_dgrad_supported(g, dtype) ? align_up(tile_dgrad_partial_bytes(g), 256) : 0;
+  return dgrad_kernel(g, dtype) == Conv::TILE ? align_up(tile_dgrad_partial_bytes(g), 256) : 0;
 }
 size_t fprop_scratch_bytes(const Geom& g, int dtype) {
   if (!needs_cin_pad(g, dtype)) return inner_fprop_scratch(g, dtype);
@@ -323,20 +333,6 @@ bool has_post_op(const Geom& g) { return g.post_relu || g.post_mask || g.post_ad
 // FUSED_*: the kernel applies g's post-operation itself.
 constexpr bool FUSED_PW = true, FUSED_RW = true, FUSED_ST = true, FUSED_TILE = true;
 
-// The kernel of each convolution (KS: the window product's wave-split tiles)
-enum class Conv { KS, PW, RW, ST, WIN, TILE, WAVE, IGEMM, DIRECT };
-Conv fprop_kernel(const Geom& g, int dtype) {
-  return ks_fprop_taken(g, dtype) ? Conv::KS : pw_fprop_supported(g, dtype) ? Conv::PW : rw_fprop_supported(g, dtype) ? Conv::RW
-         : st_fprop_supported(g, dtype) ? Conv::ST : win_fprop_taken(g, dtype) ? Conv::WIN
-         : tile_fprop_supported(g, dtype) ? Conv::TILE : wave_f32_supported(g, dtype) ? Conv::WAVE
-         : igemm_supported(g, dtype) ? Conv::IGEMM : Conv::DIRECT;
-}
-Conv dgrad_kernel(const Geom& g, int dtype) {
-  return ks_dgrad_taken(g, dtype) ? Conv::KS : pw_dgrad_supported(g, dtype) ? Conv::PW : rw_dgrad_supported(g, dtype) ? Conv::RW
-         : st_dgrad_supported(g, dtype) ? Conv::ST : win_dgrad_taken(g, dtype) ? Conv::WIN
-         : tile_dgrad_supported(g, dtype) ? Conv::TILE : wave_f32_supported(g, dtype) ? Conv::WAVE
-         : igemm_supported(g, dtype) ? Conv::IGEMM : Conv::DIRECT;
-}
 hipError_t fprop_any(const Geom& g, int dtype, const void* x, const void* w_krsc, const float* bias,
                      void* z, float* scratch, hipStream_t st) {
   hipError_t e = hipErrorInvalidValue;

@@ -373,3 +373,26 @@ def test_route_names_what_a_call_launches(dims, dtype, fwd, bwd):
 def test_one_launch_of_both_gradients_or_two(dims, bwd):
     from paper_2305_11624_amd.synth import BlockShape
     assert B.convbn_tune_route(B.desc_from_shape(BlockShape("route", *dims, "bf16", 1)), B.PASS_BWD) == bwd
+
+
+@pytest.mark.parametrize("dims,scratch", [
+    # few pixels, wave-split tiles: no fp32 copies
+    ((3, 512, 7, 5, 512, 3, 1, 1), 0), ((19, 512, 7, 7, 512, 3, 1, 1), 0), ((10, 512, 7, 7, 512, 3, 1, 1), 0),
+    # sums split over workgroups: their copies
+    ((6, 128, 34, 41, 96, 2, 1, 1), 2 * 6 * 35 * 42 * 96 * 4), ((21, 128, 52, 4, 216, 1, 1, 0), 2 * 21 * 52 * 4 * 216 * 4),
+])
+def test_forward_scratch_is_what_its_kernel_writes(dims, scratch):
+    from paper_2305_11624_amd.synth import BlockShape
+    s = BlockShape("scratch", *dims, "bf16", 1)
+    d = B.desc_from_shape(s)
+    up = lambda n: -(-n // 256) * 256
+    assert B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_FWD) == up(s.Cout * s.K * 2) + up(s.Cout * 4) + up(scratch)
+    assert (B.convbn_tune_route(d, B.PASS_FWD) == "tile split") == (scratch > 0)
+
+
+def test_forward_without_scratch_fits_the_built_in_workspace():
+    """The weight and little else: 28 MB, whatever the sums of another kernel would take."""
+    from paper_2305_11624_amd.synth import BlockShape
+    d = B.desc_from_shape(BlockShape("static", 8, 1536, 7, 7, 1024, 3, 1, 1, "bf16", 1))
+    assert B.convbn_tune_route(d, B.PASS_FWD).startswith("ks ")
+    assert B.convbn_workspace_bytes(d, B.MODE_TUNE, B.PASS_FWD) <= B.convbn_static_workspace_limit()

@@ -12,7 +12,8 @@ from helpers import TOL, oracle_block, rel_err
 pytestmark = pytest.mark.gpu
 
 FIRST = BlockShape("na_big", 8, 256, 14, 14, 256, 3, 1, 1, "bf16", 71)
-SPLIT = BlockShape("na_split", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 73)      # split sums: part of the workspace is fp32 partials
+SPLIT = BlockShape("na_split", 6, 128, 34, 41, 96, 2, 1, 1, "bf16", 73)      # split sums: part of the workspace is fp32 partials
+DEEP = BlockShape("na_deep", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 74)        # wave-split tiles
 SECOND = BlockShape("na_small", 2, 64, 9, 11, 72, 3, 1, 1, "bf16", 72)
 
 
@@ -50,8 +51,10 @@ def _run(shape, B):
 
 def test_static_workspace_forward_two_calls_in_a_row():
     from paper_2305_11624_amd import binding as B
+    assert B.convbn_tune_route(B.desc_from_shape(SPLIT), B.PASS_FWD) == "tile split"
     assert B.convbn_conv_workspace_bytes(B.desc_from_shape(SPLIT), B.PASS_FWD) > 0
     _run(SPLIT, B)
+    _run(DEEP, B)
     _run(FIRST, B)
     _run(SECOND, B)     # a smaller block right after: the array still holds the first call's bytes
 
