@@ -12,6 +12,13 @@ def dims_of(s):
     return Dims(s.N, s.Cin, s.Hin, s.Win, s.Cout, s.k, s.k, s.stride, s.stride, s.pad, s.pad)
 
 
+def routes(s):
+    """What a forward and a backward Tune call of the block launch."""
+    from paper_2305_11624_amd import binding as B
+    d = B.desc_from_shape(s)
+    return B.convbn_tune_route(d, B.PASS_FWD), B.convbn_tune_route(d, B.PASS_BWD)
+
+
 def _np(t):
     return None if t is None else t.double().numpy()
 

@@ -9,7 +9,7 @@ import torch
 from paper_2305_11624_amd import synth
 from paper_2305_11624_amd.synth import BlockShape
 
-from helpers import compare, oracle_block
+from helpers import compare, oracle_block, routes
 
 pytestmark = pytest.mark.gpu
 
@@ -46,7 +46,7 @@ def test_deep_layer_that_keeps_nothing(kw):
     again.  Same definition, same tolerances."""
     from paper_2305_11624_amd.runner import BlockRun
     shape = BlockShape("deep_refold", 35, 512, 7, 7, 512, 3, 1, 1, "bf16", 67)
-    assert shape.P > shape.A_z
+    assert shape.P > shape.A_z and routes(shape) == ("st", "fused, st")
     inp = synth.make_inputs(shape, **kw)
     ref = oracle_block(inp)
     run = BlockRun(inp, mode="tune", keep_folded=False, poison=True)
@@ -57,26 +57,61 @@ def test_deep_layer_that_keeps_nothing(kw):
 
 
 @pytest.mark.parametrize("cin", [320, 384, 448, 512, 576])
-def test_split_product(cin):
-    """Few pixels and more than 40 chunks of 64 reduced channels: the product is split over them and its fp32 copies are added
-    four at a time, with every remainder (5 to 9 copies where each chunk is one)."""
+def test_few_pixels_many_channels(cin):
+    """45 to 81 chunks of 64 reduced channels for 105 pixels: the waves of a workgroup share them, both gradients in one launch."""
     from paper_2305_11624_amd.runner import BlockRun
-    shape = BlockShape("split_%d" % cin, 3, cin, 7, 5, cin, 3, 1, 1, "bf16", 70 + cin // 64)
+    shape = BlockShape("few_%d" % cin, 3, cin, 7, 5, cin, 3, 1, 1, "bf16", 70 + cin // 64)
+    fwd, bwd = routes(shape)
+    assert fwd.startswith("ks ") and bwd.startswith("pair ks ")
     inp = synth.make_inputs(shape, bias=True)
     run = BlockRun(inp, mode="tune", poison=True)
     run.step()
     compare(run.results(), oracle_block(inp), "bf16", tag=shape.name)
 
 
+SPLIT = [
+    #  N  Cin  H   W   Cout k  s  p   copies forward (None: those of the input gradient are tested)
+    (21, 128, 52, 4, 216, 1, 1, 0, 2), (27, 192, 35, 9, 80, 1, 1, 0, 3), (14, 352, 15, 50, 88, 2, 1, 0, 4),
+    (29, 320, 9, 29, 88, 2, 1, 1, 5), (39, 384, 29, 7, 72, 2, 1, 1, 6), (11, 448, 11, 62, 120, 2, 1, 1, 7),
+    (37, 512, 28, 9, 80, 3, 1, 0, 8), (4, 640, 60, 37, 96, 3, 1, 1, 5),
+    (31, 8, 9, 62, 352, 3, 1, 0, None), (9, 32, 44, 50, 160, 3, 1, 0, None), (40, 88, 30, 8, 256, 7, 1, 3, None),
+    (29, 896, 3, 15, 352, 3, 1, 0, None),   # ... with the weight gradient's launch that folds back
+]
+
+
+@pytest.mark.parametrize("n,cin,h,w,cout,k,s,p,copies", SPLIT)
+def test_split_product(n, cin, h, w, cout, k, s, p, copies):
+    """Tiles that leave most compute units idle: the reduced channels are split over workgroups and the fp32 copies added four at a
+    time, with every remainder."""
+    from paper_2305_11624_amd import binding as B
+    from paper_2305_11624_amd.runner import BlockRun
+    shape = BlockShape("split", n, cin, h, w, cout, k, s, p, "bf16", 3 * h + w)
+    fwd, bwd = routes(shape)
+    if copies is None:
+        assert "tile split" in bwd
+    else:
+        assert fwd == "tile split"
+        scratch = B.convbn_conv_workspace_bytes(B.desc_from_shape(shape), B.PASS_FWD)
+        assert scratch // (shape.N * shape.Hout * shape.Wout * cout * 4) == copies
+    inp = synth.make_inputs(shape, bias=True)
+    ref = oracle_block(inp)
+    run = BlockRun(inp, mode="tune", poison=True)
+    run.step()
+    first = {k: (None if v is None else v.clone()) for k, v in run.results().items()}
+    compare(first, ref, "bf16", tag="first")
+    run.step()
+    for k in ("Z", "dX", "dW", "dgamma", "dbeta"):
+        assert torch.equal(first[k], run.results()[k]), k
+
+
 def test_deep_layer_replayed_from_a_graph():
     """A captured step replays with the same arguments, the launch tag of the workgroup exchange among them: each
     replay must find the slots of the previous one cleared.  Three replays over changing inputs, eager work and
     synchronisations in between, each compared bit for bit with an eager step on the same inputs."""
-    from paper_2305_11624_amd import binding as B
     from paper_2305_11624_amd.runner import BlockRun
     shapes = [BlockShape("deep_graph", 33, 512, 7, 7, 512, 3, 1, 1, "bf16", 70 + i) for i in range(2)]
     inps = [synth.make_inputs(s, bias=True) for s in shapes]
-    assert B.convbn_tune_bwd_is_fused(B.desc_from_shape(shapes[0], eps=inps[0]["eps"]))
+    assert routes(shapes[0])[1] == "fused, st"
     eager = []
     for inp in inps:
         run = BlockRun(inp, mode="tune", keep_folded=False)
