@@ -6,27 +6,40 @@ from paper_2305_11624_amd import synth
 from paper_2305_11624_amd.runner import BlockRun, TconvRun
 from paper_2305_11624_amd.synth import BlockShape
 
-from helpers import compare, oracle_block, oracle_tconv_block
+from helpers import compare, oracle_block, oracle_tconv_block, routes
 
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
     #  N  Cin  H   W   Cout k  s  p
-    (20, 256, 30, 33, 64, 1, 1, 0, "bf16"),    # pointwise product: many copies of short rows
-    (24, 64, 41, 40, 192, 1, 1, 0, "bf16"),    # sixteen columns a row
-    (12, 512, 17, 19, 640, 1, 1, 0, "bf16"),   # few copies, 128 columns
-    (40, 128, 30, 30, 264, 3, 2, 1, "bf16"),   # residue classes; rows longer than a channel's threads, channels that fill no workgroup
-    (3, 128, 37, 41, 128, 3, 1, 1, "bf16"),    # the deep-layer kernel
-    (9, 3, 24, 24, 32, 3, 2, 1, "bf16"),       # first layers: 27 and 75 elements a row
-    (6, 3, 33, 52, 64, 5, 2, 2, "bf16"),
-    (1, 3, 8, 8, 32, 1, 1, 0, "bf16"),         # three elements a row
-    (4, 3, 40, 40, 16, 3, 1, 1, "f32"), (2, 5, 9, 11, 7, 1, 1, 0, "f32"), (1, 2, 6, 5, 3, 1, 1, 0, "f32"),
+    (20, 256, 30, 33, 64, 1, 1, 0, "bf16", "win, gm + fold-back"),     # pointwise product: many copies of short rows
+    (24, 64, 41, 40, 192, 1, 1, 0, "bf16", "win, gm + fold-back"),     # sixteen columns a row
+    (12, 512, 17, 19, 640, 1, 1, 0, "bf16", "win, gm + fold-back"),    # few copies, 128 columns
+    # residue classes; rows longer than a channel's threads, channels that fill no workgroup
+    (40, 128, 30, 30, 264, 3, 2, 1, "bf16", "win, win 128x128 + fold-back"),
+    (40, 96, 31, 40, 40, 3, 1, 1, "bf16", "win, win 128x128 + fold-back"),
+    (30, 128, 28, 17, 136, 3, 2, 1, "bf16", "win, win 128x64 + fold-back"),
+    (42, 600, 30, 6, 64, 2, 2, 0, "bf16", "win, win 256x128 + fold-back"),
+    (21, 128, 28, 28, 128, 3, 1, 1, "bf16", "sq, st + fold-back"),     # the deep-layer kernel
+    (2, 1032, 7, 6, 16, 5, 2, 0, "bf16", "win, ks 32x32 + fold-back"),   # wave-split tiles
+    (4, 992, 6, 16, 8, 5, 2, 0, "bf16", "win, ks 64x32 + fold-back"),
+    (40, 736, 6, 5, 16, 5, 1, 0, "bf16", "win, ks 64x64 + fold-back"),
+    (3, 128, 37, 41, 128, 3, 1, 1, "bf16", "pair win 128x64 win 64x128, fold-back"),   # launches of their own, behind both gradients
+    (38, 1024, 9, 9, 2048, 1, 2, 0, "bf16", "pair win 128x64 win 128x128, fold-back"),
+    (24, 256, 13, 13, 256, 3, 1, 1, "bf16", "pair win 128x64 win 128x128, fold-back"),
+    (9, 3, 24, 24, 32, 3, 2, 1, "bf16", "stem, stem + fold-back"),     # first layers: 27 and 75 elements a row
+    (6, 3, 33, 52, 64, 5, 2, 2, "bf16", "stem, stem + fold-back"),
+    (1, 3, 8, 8, 32, 1, 1, 0, "bf16", "stem, stem, fold-back"),        # three elements a row
+    (4, 3, 40, 40, 16, 3, 1, 1, "f32", "pair wave, fold-back"), (2, 5, 9, 11, 7, 1, 1, 0, "f32", "pair wave, fold-back"),
+    (1, 2, 6, 5, 3, 1, 1, 0, "f32", "pair wave, fold-back"),
 ]
 
 
-@pytest.mark.parametrize("n,cin,h,w,cout,k,s,p,dtype", SHAPES)
-def test_parameter_gradients(n, cin, h, w, cout, k, s, p, dtype):
-    inp = synth.make_inputs(BlockShape("fb", n, cin, h, w, cout, k, s, p, dtype, 3 * h + w), bias=True)
+@pytest.mark.parametrize("n,cin,h,w,cout,k,s,p,dtype,route", SHAPES)
+def test_parameter_gradients(n, cin, h, w, cout, k, s, p, dtype, route):
+    shape = BlockShape("fb", n, cin, h, w, cout, k, s, p, dtype, 3 * h + w)
+    assert routes(shape)[1] == route
+    inp = synth.make_inputs(shape, bias=True)
     ref = oracle_block(inp)
     for keep in (True, False):
         r = BlockRun(inp, poison=True, keep_folded=keep)

@@ -10,7 +10,7 @@ from paper_2305_11624_amd import synth
 from paper_2305_11624_amd.runner import BlockRun
 from paper_2305_11624_amd.synth import BlockShape
 
-from helpers import compare, oracle_block
+from helpers import compare, oracle_block, routes
 
 pytestmark = pytest.mark.gpu
 
@@ -26,7 +26,11 @@ SHAPES = [
     (2, 16, 13, 9, 200, 5, 1, 2),      # four taps a chunk
     (5, 512, 7, 7, 512, 3, 1, 1),      # 32 x 32 tiles, 72 chunks
     (20, 512, 7, 7, 512, 3, 1, 1),     # 64 x 32
-    (6, 256, 19, 17, 256, 3, 1, 1),    # 64 x 64, the last ragged
+    (6, 256, 19, 17, 256, 3, 1, 1),    # ... ragged; both gradients on 128 x 64 tiles
+    (5, 72, 27, 33, 136, 3, 1, 1),     # 64 x 64 tiles, ragged both ways; both gradients too
+    (12, 256, 14, 16, 256, 3, 1, 1),   # ... the last tile's pixels ragged
+    (45, 376, 5, 37, 40, 1, 1, 0),     # ... six chunks, the last not full
+    (40, 736, 6, 5, 16, 5, 1, 0),      # ... in the input gradient, with a fold-back on the side
     (7, 1024, 15, 15, 256, 1, 1, 0),
     (3, 512, 9, 7, 512, 3, 2, 1),      # four residue classes
     (2, 64, 11, 14, 96, 1, 2, 0),      # three of them without a tap
@@ -52,6 +56,18 @@ def test_block(n, cin, h, w, cout, k, s, p, keep):
         B.convbn_fold(r.desc, r.W, r.b, r.gamma, r.beta, r.mean, r.var, None, wf, None)
         torch.cuda.synchronize()
         assert torch.equal(wf, r.w_folded)
+
+
+@pytest.mark.parametrize("dims,fwd,bwd", [
+    ((1, 64, 5, 7, 40, 1, 1, 0), "ks 32x32", "pair ks 32x32"), ((20, 512, 7, 7, 512, 3, 1, 1), "ks 64x32", "fused, ks 64x32"),
+    ((5, 512, 7, 7, 512, 3, 1, 1), "ks 32x32", "pair ks 64x32"), ((5, 72, 27, 33, 136, 3, 1, 1), "ks 64x64", "pair ks 64x64"),
+    ((12, 256, 14, 16, 256, 3, 1, 1), "ks 64x64", "pair win 128x64"), ((45, 376, 5, 37, 40, 1, 1, 0), "ks 64x64", "win, win 128x128"),
+    ((40, 736, 6, 5, 16, 5, 1, 0), "ks 32x32", "win, ks 64x64 + fold-back"), ((2, 32, 16, 17, 48, 2, 3, 0), "ks 32x32", "win, ks 32x32 + fold-back"),
+])
+def test_shapes_reach_what_they_are_for(dims, fwd, bwd):
+    assert dims in SHAPES
+    f, b = routes(BlockShape("ks", *dims, "bf16", 1))
+    assert f == fwd and b.startswith(bwd)
 
 
 @pytest.mark.parametrize("n,cin,h,w,cout,k,s,p", [(3, 136, 11, 13, 56, 3, 1, 1), (2, 64, 11, 14, 96, 1, 2, 0)])
