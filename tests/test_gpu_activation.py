@@ -11,21 +11,21 @@ from paper_2305_11624_amd import binding as B
 from paper_2305_11624_amd import synth
 from paper_2305_11624_amd.synth import BlockShape
 
-from helpers import compare, oracle_block
+from helpers import compare, oracle_block, routes
 
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
-    BlockShape("act_pw_1x1", 6, 256, 20, 20, 64, 1, 1, 0, "bf16", 301),          # pointwise kernel
+    BlockShape("act_pw_1x1", 6, 256, 20, 20, 64, 1, 1, 0, "bf16", 301),          # pointwise, few pixels
     BlockShape("act_pw_1x1_wide", 5, 64, 28, 28, 256, 1, 1, 0, "bf16", 302),
     BlockShape("act_pw_strided", 4, 256, 28, 28, 512, 1, 2, 0, "bf16", 303),      # a downsampling shortcut
     BlockShape("act_shallow_3x3", 9, 64, 47, 53, 64, 3, 1, 1, "bf16", 304),       # weight and window resident in LDS
-    BlockShape("act_deep_3x3", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 305),         # split sums + their reduction, fused weight gradient
-    BlockShape("act_mid_3x3", 6, 128, 28, 28, 128, 3, 1, 1, "bf16", 306),         # LDS-tile kernel
+    BlockShape("act_deep_3x3", 10, 512, 7, 7, 512, 3, 1, 1, "bf16", 305),         # wave-split tiles, few pixels and 72 chunks
+    BlockShape("act_mid_3x3", 6, 128, 28, 28, 128, 3, 1, 1, "bf16", 306),         # wave-split tiles of 64 x 64; both gradients in one launch
     BlockShape("act_mid_3x3_s2", 6, 128, 28, 28, 128, 3, 2, 1, "bf16", 307),      # strided: residue classes in the input gradient
-    BlockShape("act_split_sums", 2, 256, 14, 14, 256, 3, 1, 1, "bf16", 308),    # few pixels, a 36-chunk reduction: window product
+    BlockShape("act_split_sums", 2, 256, 14, 14, 256, 3, 1, 1, "bf16", 308),    # few pixels, a 36-chunk reduction: wave-split tiles
     BlockShape("act_stem", 2, 3, 64, 64, 64, 7, 2, 3, "bf16", 309),               # first layer: padded channels
-    BlockShape("act_odd_bf16", 2, 24, 9, 11, 40, 3, 1, 1, "bf16", 310),           # no channel count fits a tile: window product
+    BlockShape("act_odd_bf16", 2, 24, 9, 11, 40, 3, 1, 1, "bf16", 310),           # no channel count fits the LDS-tile kernel
     BlockShape("act_gm_fwd_256", 5, 128, 31, 33, 1024, 1, 1, 0, "bf16", 313),    # tiled matrix product, 256-pixel tiles, ragged tail
     BlockShape("act_gm_fwd_128", 5, 192, 31, 33, 512, 1, 1, 0, "bf16", 314),     # ... 128-pixel tiles, three chunks
     BlockShape("act_gm_bwd", 5, 1024, 31, 33, 128, 1, 1, 0, "bf16", 315),        # ... in the input gradient
@@ -38,9 +38,28 @@ SHAPES = [
     BlockShape("act_gm_strided", 30, 256, 27, 29, 512, 1, 2, 0, "bf16", 322),    # ... a downsampling shortcut: gathered / scattered rows
     BlockShape("act_f32", 2, 16, 12, 10, 24, 3, 1, 1, "f32", 311),
     BlockShape("act_f32_ragged", 1, 5, 7, 9, 7, 3, 2, 1, "f32", 312),             # element counts that are not multiples of 8
-    BlockShape("act_split_sums_ragged", 3, 384, 13, 11, 320, 3, 1, 1, "bf16", 323),   # split sums + their reduction, both passes
+    BlockShape("act_split_sums_ragged", 3, 384, 13, 11, 320, 3, 1, 1, "bf16", 323),   # wave-split tiles, both passes
+    BlockShape("act_tile", 40, 96, 31, 40, 40, 3, 1, 1, "bf16", 324),             # LDS-tile kernel
+    BlockShape("act_tile_bwd", 44, 200, 5, 36, 32, 1, 1, 0, "bf16", 325),         # ... in the input gradient
+    BlockShape("act_tile_split", 6, 128, 34, 41, 96, 2, 1, 1, "bf16", 326),       # ... split sums + their reduction
+    BlockShape("act_tile_split_bwd", 31, 8, 9, 62, 352, 3, 1, 0, "bf16", 327),    # ... in the input gradient
+    BlockShape("act_deep_fwd", 35, 64, 6, 4, 960, 3, 1, 1, "bf16", 328),          # deep-layer kernel
+    BlockShape("act_deep_fused", 36, 832, 5, 6, 384, 3, 1, 0, "bf16", 329),       # ... in the input gradient, behind the fused weight gradient
+    BlockShape("act_pw_fwd", 38, 32, 21, 22, 8, 1, 1, 0, "bf16", 330),            # pointwise kernel
+    BlockShape("act_pw_bwd", 43, 8, 13, 52, 32, 1, 1, 0, "bf16", 331),
 ]
 BOTH = B.ACT_RELU_OUT | B.ACT_RELU_IN
+
+
+@pytest.mark.parametrize("name,fwd,bwd", [
+    ("act_gm_fwd_256", "gm", "pair"), ("act_gm_one_bwd", "gm", "win, gm + fold-back"), ("act_shallow_3x3", "rw", "rw, win"), ("act_stem", "stem", "stem, stem"),
+    ("act_deep_3x3", "ks 32x32", "pair ks 64x64"), ("act_mid_3x3", "ks 64x64", "pair win 128x64"), ("act_tile", "tile", "win, win"),
+    ("act_tile_bwd", "ks 32x32", "tile, win"), ("act_tile_split", "tile split", "pair win"), ("act_tile_split_bwd", "win 128x128", "tile split"),
+    ("act_deep_fwd", "st", "pair ks"), ("act_deep_fused", "ks 32x32", "fused, st"), ("act_pw_fwd", "pw", "pair"), ("act_pw_bwd", "win", "pw"),
+])
+def test_shapes_reach_what_they_are_for(name, fwd, bwd):
+    f, b = routes([s for s in SHAPES if s.name == name][0])
+    assert f.startswith(fwd) and b.startswith(bwd)
 
 
 def _inputs(shape):
