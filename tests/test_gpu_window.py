@@ -10,16 +10,16 @@ from paper_2305_11624_amd import binding as B
 from paper_2305_11624_amd import synth
 from paper_2305_11624_amd.synth import BlockShape
 
-from helpers import compare, oracle_block
+from helpers import compare, oracle_block, routes
 
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
     BlockShape("win_8_channels", 2, 8, 5, 7, 8, 3, 1, 1, "bf16", 921),                # eight taps in a chunk
-    BlockShape("win_one_chunk", 3, 24, 9, 5, 72, 1, 1, 0, "bf16", 922),               # one chunk, ring of six
+    BlockShape("win_one_chunk", 3, 24, 9, 5, 72, 1, 1, 0, "bf16", 922),               # one chunk
     BlockShape("win_72_136", 2, 72, 17, 19, 136, 3, 1, 1, "bf16", 923),
     BlockShape("win_200_56_5x5", 1, 200, 11, 13, 56, 5, 1, 2, "bf16", 924),
-    BlockShape("win_many_tiles_ragged", 24, 40, 33, 31, 232, 3, 1, 1, "bf16", 925),   # ring of three, 128 x 128 tiles
+    BlockShape("win_many_tiles_ragged", 24, 40, 33, 31, 232, 3, 1, 1, "bf16", 925),   # 128 x 128 tiles
     BlockShape("win_stride2_64", 5, 64, 23, 18, 64, 3, 2, 1, "bf16", 926),
     BlockShape("win_stride2_512", 9, 512, 14, 13, 512, 3, 2, 1, "bf16", 927),         # weight larger than the activations
     BlockShape("win_stride2_1x1", 4, 192, 13, 15, 320, 1, 2, 0, "bf16", 928),         # three classes without a tap
@@ -38,9 +38,41 @@ SHAPES = [
     BlockShape("ww_alone", 30, 136, 29, 31, 264, 1, 1, 0, "bf16", 938),               # too many workgroups for one launch of both
     BlockShape("ww_alone_5x5", 12, 96, 27, 26, 72, 5, 2, 2, "bf16", 939),
     BlockShape("pair_3x3_256", 3, 256, 13, 14, 256, 3, 1, 1, "bf16", 940),
+    # the product's own tiles (the shapes above that have few pixels are wave-split): whole chunks of a tap and chunks across taps, rings of
+    # three, four and six, one chunk and less, ragged pixels and channels
+    BlockShape("win_ring6_flat_one_chunk", 33, 8, 20, 26, 8, 1, 1, 0, "bf16", 945),
+    BlockShape("win_ring6_flat", 24, 8, 41, 30, 8, 2, 1, 0, "bf16", 946),             # ... input gradient too
+    BlockShape("win_ring6_one_chunk", 13, 64, 31, 54, 80, 1, 2, 0, "bf16", 947),
+    BlockShape("win_ring6", 43, 192, 58, 27, 8, 1, 2, 0, "bf16", 948),
+    BlockShape("win_ring3_flat_one_chunk", 39, 8, 15, 57, 8, 1, 1, 0, "bf16", 949),
+    BlockShape("win_ring3_flat", 40, 8, 22, 54, 8, 2, 1, 0, "bf16", 950),
+    BlockShape("win_ring3_one_chunk", 45, 64, 28, 27, 232, 1, 2, 0, "bf16", 951),
+    BlockShape("win_ring3", 58, 128, 27, 38, 136, 1, 2, 0, "bf16", 952),              # ... input gradient: three classes without a tap
+    BlockShape("win_128_flat", 17, 72, 32, 39, 8, 2, 1, 0, "bf16", 953),              # 128 x 128 tiles: input gradient
+    BlockShape("win_128_flat_fwd", 26, 8, 41, 20, 72, 1, 1, 0, "bf16", 954),
+    BlockShape("win_128", 45, 72, 19, 38, 64, 2, 2, 1, "bf16", 955),
+    BlockShape("win_128_one_chunk_fwd", 45, 64, 30, 43, 208, 1, 2, 0, "bf16", 956),
+    BlockShape("win_256", 47, 88, 21, 57, 64, 2, 2, 1, "bf16", 957),
+    BlockShape("win_no_tap", 33, 144, 22, 52, 8, 1, 2, 0, "bf16", 958),
     BlockShape("win_stride_beyond_image", 2, 64, 5, 4, 64, 3, 65536, 1, "bf16", 943),   # twenty classes of one position, most without a tap
 ]
 BOTH = B.ACT_RELU_OUT | B.ACT_RELU_IN
+
+
+@pytest.mark.parametrize("name,fwd,bwd", [
+    ("win_many_tiles_ragged", "win 128x128", "win, win 128x64 + fold-back"), ("win_stride2_wide", "win 128x64", "win, win 128x128 + fold-back"),
+    ("win_stride2_256", "win 256x128", "win, win 256x128 + fold-back"), ("win_ring6_flat_one_chunk", "win 128x64", "pair"),
+    ("win_ring6_flat", "win 128x64", "win, win 128x64 + fold-back"), ("win_ring6_one_chunk", "win 128x64", "pair"),
+    ("win_ring6", "win 128x64", "win, win 128x64 + fold-back"), ("win_ring3_flat_one_chunk", "win 128x64", "win, win 128x64 + fold-back"),
+    ("win_ring3_flat", "win 128x64", "win, win 128x64 + fold-back"), ("win_ring3_one_chunk", "win 128x64", "pair"),
+    ("win_ring3", "win 128x64", "win, win 128x64 + fold-back"), ("win_128_flat", "win 128x64", "win, win 128x128 + fold-back"),
+    ("win_128_flat_fwd", "win 128x128", "pair"), ("win_128", "win 128x64", "win, win 128x128 + fold-back"),
+    ("win_128_one_chunk_fwd", "win 128x128", "pair"), ("win_256", "ks 64x64", "win, win 256x128 + fold-back"),
+    ("win_no_tap", "ks 64x32", "win, win 128x64 + fold-back"),
+])
+def test_shapes_reach_what_they_are_for(name, fwd, bwd):
+    f, b = routes(next(s for s in SHAPES if s.name == name))
+    assert f == fwd and b.startswith(bwd)
 
 
 @pytest.mark.parametrize("keep", [True, False], ids=["keeps_w", "keeps_nothing"])
@@ -63,9 +95,10 @@ def test_block(shape, keep):
         assert torch.equal(w, run.w_folded)
 
 
-def test_addend_reaches_positions_no_tap_does():
+@pytest.mark.parametrize("name", ["win_stride2_1x1", "win_no_tap"])
+def test_addend_reaches_positions_no_tap_does(name):
     from paper_2305_11624_amd.runner import BlockRun
-    shape = next(s for s in SHAPES if s.name == "win_stride2_1x1")
+    shape = next(s for s in SHAPES if s.name == name)
     inp = synth.make_inputs(shape)
     add = torch.randn((shape.N, shape.Hin, shape.Win, shape.Cin), generator=torch.Generator().manual_seed(5)).bfloat16().cuda()
     run = BlockRun(inp, mode="tune", poison=True, act=B.ACT_ADD_IN, add_in=add)
