@@ -250,7 +250,11 @@ convbn_status check_ws(size_t need, void* ws, size_t ws_bytes) {
 // Which problems the window product takes: strided windows, what the LDS-tile kernel has no plan for, and few tiles, where
 // that kernel would split its sums (fp32 partial outputs, a reduction launch, forward a fold launch), as long as one
 // workgroup's chain of 64-channel chunks is not what the launch then waits for.  Few pixels go to its wave-split form
-// first (ks_*_taken).
+// first (ks_*_taken); what is left for the last rule are few channels over more pixels, where those tiles and the workgroups that
+// fold are more than a round.  Forward, us, window product and split sums: 3 x 3, 320 -> 112 at 40 x 58, 3 images (45 chunks) 18.4,
+// 24.7; 2 x 2, 768 -> 16 at 13 x 53, 24 images (48) 18.7, 24.4; 3 x 3, 448 -> 8 at 39 x 21, 19 images (63) 23.5, 20.2; 576 -> 72 at
+// 11 x 17, 49 images (81) 28.6, 25.4; 5 x 5, 256 -> 48 at 28 x 39, 16 images (100) 35.6, 29.3.  The line stays below all that lose;
+// few layers lie between 40 and 60 chunks.
 constexpr int WIN_CHUNKS = 40, WIN_SMALL_TILES = 128;
 bool win_small(int M, int R, int K) {   // M pixels, R produced channels, K reduced
   return K <= 64 * WIN_CHUNKS && (long long)ceil_div(M, 128) * ceil_div(R, 64) <= WIN_SMALL_TILES;
