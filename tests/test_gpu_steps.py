@@ -240,3 +240,31 @@ def test_scale_in_the_epilogue_forward_refuses_other_shapes():
     x = torch.zeros(1 << 16, device="cuda", dtype=torch.bfloat16)
     v = torch.zeros(64, device="cuda")
     assert B.convbn_tune_fwd_scale_epilogue(d, x, x, None, v, v, v, v, x, check=False) == B.ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("n,cin,h,cout,copies", [(1, 128, 14, 256, 4), (3, 160, 9, 40, 4), (6, 256, 7, 64, 5), (4, 256, 9, 64, 6), (1, 128, 20, 32, 7),
+                                                  (6, 256, 9, 64, 8)])
+def test_fold_back_adds_copies_of_long_rows_in_pairs(n, cin, h, cout, copies):
+    """Rows of 1024 elements and more: every four copies are added in pairs, the rest one by one (in sequence throughout, the sums would
+    be further off), in fp32 and with a scale of one bit for bit."""
+    from paper_2305_11624_amd import binding as B
+    d = B.desc_from_shape(BlockShape("fb_pairs", n, cin, h, h, cout, 3, 1, 1, "f32", 1), eps=1e-5)
+    assert B.convbn_wgrad_parts(d) == copies
+    g = torch.Generator(device="cuda")
+    g.manual_seed(copies)
+    part = torch.randn((copies, cout * cin * 9), generator=g, device="cuda")
+    r_part = torch.randn((B.convbn_rsum_parts(d), cout), generator=g, device="cuda")
+    W = torch.randn(cout * cin * 9, generator=g, device="cuda")
+    one = torch.ones(cout, device="cuda")
+    var = one - 1e-5
+    assert torch.equal(var + 1e-5, one)
+    dW, dgamma, dbeta = torch.empty_like(W), torch.empty_like(one), torch.empty_like(one)
+    B.convbn_fold_back(d, part, r_part, W, None, one, one, var, dW, None, dgamma, dbeta)
+    want, i = torch.zeros_like(W), 0
+    while i < copies:
+        if i + 3 < copies:
+            want, i = want + ((part[i] + part[i + 1]) + (part[i + 2] + part[i + 3])), i + 4
+        else:
+            want, i = want + part[i], i + 1
+    torch.cuda.synchronize()
+    assert torch.equal(dW, want)
