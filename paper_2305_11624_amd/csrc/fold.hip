@@ -107,11 +107,11 @@ __global__ __launch_bounds__(256) void fold_group_kernel(const FoldGroupItem* __
   fold_tile_bf16x8(it.a, t % it.tiles_k, t / it.tiles_k, threadIdx.x, tile);
 }
 
-template <typename T, int NTHR, RowKind ROW>
+template <typename T, int NTHR, RowKind ROW, RowLen LEN>
 __global__ __launch_bounds__(NTHR) void fold_back_kernel(FoldBackArgs a) {
   __shared__ float4 red4[NTHR];
   __shared__ float red[2 * NTHR / 64];
-  fold_back_row<T, 16, 1, ROW>(a, blockIdx.x, threadIdx.x, NTHR, red4, red);
+  fold_back_row<T, 16, 1, ROW, LEN>(a, blockIdx.x, threadIdx.x, NTHR, red4, red);
 }
 
 // The fold-backs of several blocks in one launch (Table 2 "Tune", last four lines, for every block of a group):
@@ -437,17 +437,21 @@ hipError_t launch_fold_back(const Geom& g, int dtype, const float* dwf_part, int
                             const float* gamma, const float* mean, const float* var, int identity,
                             void* dW, float* db, float* dgamma, float* dbeta, hipStream_t st) {
   const FoldBackArgs a{dwf_part, r_part, W, b, gamma, mean, var, dW, db, dgamma, dbeta, g.eps, nsplit, nrpart, identity, g.Cout, g.K, 0};
-#define FB_LAUNCH(NTHR, ROW)                                                                                            \
+#define FB_LAUNCH(NTHR, ROW, LEN)                                                                                       \
   do {                                                                                                                  \
-    if (dtype == CONVBN_BF16) hipLaunchKernelGGL((fold_back_kernel<bf16_t, NTHR, ROW>), dim3(g.Cout), dim3(NTHR), 0, st, a); \
-    else hipLaunchKernelGGL((fold_back_kernel<float, NTHR, ROW>), dim3(g.Cout), dim3(NTHR), 0, st, a);                   \
+    if (dtype == CONVBN_BF16) hipLaunchKernelGGL((fold_back_kernel<bf16_t, NTHR, ROW, LEN>), dim3(g.Cout), dim3(NTHR), 0, st, a); \
+    else hipLaunchKernelGGL((fold_back_kernel<float, NTHR, ROW, LEN>), dim3(g.Cout), dim3(NTHR), 0, st, a);              \
   } while (0)
   // few output channels and many partial copies: a 1024-thread block per channel (16 waves share
   // the copies) keeps enough loads in flight on the few CUs such a grid occupies
   const bool wide = g.Cout <= 128 && nsplit >= 16 && ceil_div(g.K, 4) < 256;
-  if (g.K % 4 == 0) { if (wide) FB_LAUNCH(1024, ROW_VEC); else FB_LAUNCH(256, ROW_VEC); }
-  else if (wide && g.K >= 4) FB_LAUNCH(1024, ROW_ANY);
-  else FB_LAUNCH(256, ROW_ELEM);
+  if (g.K % 4 == 0) {
+    if (wide) FB_LAUNCH(1024, ROW_VEC, LEN_SHORT);
+    else if (g.K / 4 < 256) FB_LAUNCH(256, ROW_VEC, LEN_SHORT);
+    else FB_LAUNCH(256, ROW_VEC, LEN_LONG);
+  } else if (wide && g.K >= 4) FB_LAUNCH(1024, ROW_ANY, LEN_SHORT);
+  else if (g.K < 256) FB_LAUNCH(256, ROW_ELEM, LEN_SHORT);
+  else FB_LAUNCH(256, ROW_ELEM, LEN_LONG);
 #undef FB_LAUNCH
   return hipGetLastError();
 }

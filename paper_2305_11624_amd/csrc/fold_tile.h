@@ -156,7 +156,10 @@ __device__ __forceinline__ void fb_store4(bf16_t* p, const float (&w)[4]) {
 // threads and two copies beside an input gradient of 208 workgroups: that launch 21.7 us, 16.9).  Four copies are added in pairs.
 // red4: nthr entries, red: 2 per wave, of these threads' own.
 enum RowKind { ROW_VEC, ROW_ANY, ROW_ELEM };   // columns of four elements, K % 4 == 0; ... K >= 4; columns of one
-template <typename T, int FLIGHT, int COLS, RowKind ROW>
+// LEN: how many columns a row has, where the launch knows: each form alone takes fewer registers and less code (1024 -> 2048, 1 x 1,
+// one copy, a launch: 6.5 us with both in the kernel, 5.3).
+enum RowLen { LEN_ANY, LEN_SHORT, LEN_LONG };   // ...; fewer than threads; at least as many
+template <typename T, int FLIGHT, int COLS, RowKind ROW, RowLen LEN = LEN_ANY>
 __device__ __forceinline__ void fold_back_row(const FoldBackArgs& a, int co, int tid, int nthr, float4* red4, float* red) {
   const bool live = co < a.Cout;
   co = min(co, a.Cout - 1);
@@ -216,7 +219,7 @@ __device__ __forceinline__ void fold_back_row(const FoldBackArgs& a, int co, int
         if (e >= skip && (!ELEM || e == 0)) dW[k + e] = from_f32<T>(o4[e]);
     }
   };
-  if (K4 >= nthr) {
+  if (LEN == LEN_LONG || (LEN == LEN_ANY && K4 >= nthr)) {
     for (int c0 = tid; c0 < K4; c0 += COLS * nthr) {
       float4 v[COLS];
       float w4[COLS][4];
@@ -225,37 +228,49 @@ __device__ __forceinline__ void fold_back_row(const FoldBackArgs& a, int co, int
         v[i] = zero4;
         if (i == 0 || c0 + i * nthr < K4) load_w(c0 + i * nthr, w4[i]);
       }
-      auto load_col = [&](int sp, int i) {
-        return i == 0 || c0 + i * nthr < K4 ? load_part(row + (size_t)sp * P + at(c0 + i * nthr)) : zero4;
-      };
       auto add = [&](float4& u, const float4& o) { u.x += o.x; u.y += o.y; u.z += o.z; u.w += o.w; };
-      int sp = 0;
-      for (; sp + 3 < nsplit; sp += 4) {
-        float4 t[4][COLS];
+      auto pairs = [&](float4& u, float4* t) {   // u + ((t0 + t1) + (t2 + t3))
+        add(t[0], t[1]);
+        add(t[2], t[3]);
+        add(t[0], t[2]);
+        add(u, t[0]);
+      };
+      if constexpr (LEN == LEN_LONG) {
+        static_assert(COLS == 1);
+        int sp = 0;
+        for (; sp + 3 < nsplit; sp += 4) {
+          float4 t[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int i = 0; i < COLS; ++i) t[j][i] = load_col(sp + j, i);
-#pragma unroll
-        for (int i = 0; i < COLS; ++i) {
-          add(t[0][i], t[1][i]);
-          add(t[2][i], t[3][i]);
-          add(t[0][i], t[2][i]);
-          add(v[i], t[0][i]);
+          for (int j = 0; j < 4; ++j) t[j] = load_part(row + (size_t)(sp + j) * P + at(c0));
+          pairs(v[0], t);
         }
-      }
-      if (sp < nsplit) {
-        float4 t[3][COLS];
+        float4 t[3];
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-          if (sp + j < nsplit)
-#pragma unroll
-            for (int i = 0; i < COLS; ++i) t[j][i] = load_col(sp + j, i);
+          if (sp + j < nsplit) t[j] = load_part(row + (size_t)(sp + j) * P + at(c0));
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-          if (sp + j < nsplit)
+          if (sp + j < nsplit) add(v[0], t[j]);
+      } else {   // (in the form above an input gradient with a fold-back beside it takes 1 - 4 us more, in this one a launch of its own 1 us)
+        for (int sp = 0; sp < nsplit; sp += 4) {
+          float4 t[COLS][4];
 #pragma unroll
-            for (int i = 0; i < COLS; ++i) add(v[i], t[j][i]);
+          for (int j = 0; j < 4; ++j)
+            if (sp + j < nsplit)
+#pragma unroll
+              for (int i = 0; i < COLS; ++i)
+                if (i == 0 || c0 + i * nthr < K4) t[i][j] = load_part(row + (size_t)(sp + j) * P + at(c0 + i * nthr));
+          if (sp + 3 < nsplit) {
+#pragma unroll
+            for (int i = 0; i < COLS; ++i) pairs(v[i], t[i]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+              if (sp + j < nsplit)
+#pragma unroll
+                for (int i = 0; i < COLS; ++i) add(v[i], t[i][j]);
+          }
+        }
       }
 #pragma unroll
       for (int i = 0; i < COLS; ++i)
