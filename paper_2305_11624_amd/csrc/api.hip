@@ -429,7 +429,13 @@ bool dgrad_folds_back_aside(const Geom& g, int dtype) {
     return stem_dgrad_supported(g, dtype) && stem_wgrad_supported(g, dtype) && stem_dgrad_folds_back_aside(g);
   if (g.K % 4) return false;
   const Conv k = dgrad_kernel(g, dtype);
-  return k == Conv::PW ? gm_supported(g.M, g.Cout, g.Cin) : k == Conv::KS || k == Conv::ST || k == Conv::WIN;
+  if (k != Conv::PW) return k == Conv::KS || k == Conv::ST || k == Conv::WIN;
+  if (!gm_supported(g.M, g.Cout, g.Cin)) return false;
+  // Long rows that would start when a full round of tiles ends: a launch of its own has more workgroups for them (pointwise, a pass,
+  // beside and apart: 2048 -> 512 at 7 x 9, 62 images 50.3 us, 49.0, at 9 x 9, 20 images 38.3, 37.0; 1024 -> 256 at 19 x 19, 10 images
+  // 27.1, 26.4; short rows the other way: 256 -> 1024 at 16 x 16, 42 images 37.4, 42.0, and where there is room: 2048 -> 512 at
+  // 6 x 6, 41 images 32.7, 36.5)
+  return g.K < 1024 || !gm_round_full(g.M, g.Cout, g.Cin, fold_back_side_blocks(g.K, nsplit_for(g, dtype), g.Cout, 512));
 }
 // ... run_fprop()'s, a transposed block's fold-back (g.fold_back_t)
 bool fprop_folds_back_aside(const Geom& g, int dtype) {

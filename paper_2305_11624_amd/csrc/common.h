@@ -431,6 +431,8 @@ hipError_t launch_wgrad_igemm(const Geom& g, const void* x, const void* dz, floa
 // the tiled matrix product that takes the pointwise layers of the middle stages (conv_gm.hip); reached through the
 // pw_* calls below
 bool gm_supported(int M, int C, int R);
+// Whether the product is one round, a workgroup per compute unit, that leaves too few of them for `aside` more.
+bool gm_round_full(int M, int C, int R, int aside);
 // sd != null: a strided pointwise layer -- the activation row of output pixel (n, ho, wo) is pixel (n, ho sh, wo sw) of an
 // [N][Hs][Ws] tensor.
 struct GmStride { int N, Ho, Wo, Hs, Ws, sh, sw; };

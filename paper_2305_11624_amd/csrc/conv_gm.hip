@@ -103,6 +103,7 @@ struct GmCfg {
   static constexpr int STAGE = (TM + TN) * 128;
   static constexpr int OFF_BIAS = (RES ? RES : NS) * STAGE;   // [TN] bias, [TN] scale
   static constexpr int LDS_BYTES = OFF_BIAS + 2 * TN * 4;
+  static constexpr bool SHARED = 2 * LDS_BYTES <= 160 * 1024;   // two workgroups, and more, share a compute unit
   static_assert(NWAVES * 32 * CW * 2 <= STAGE, "the epilogue stages every wave's outputs (32 pixels at a time) in the first stage");
 };
 
@@ -120,7 +121,10 @@ __global__ __launch_bounds__(64 * NWAVES) void conv_gm_kernel(GmParams p, Side s
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* biasl = reinterpret_cast<float*>(smem + Cfg::OFF_BIAS);
   if ((int)blockIdx.x >= p.nconv) {
-    if constexpr (Side::BACK) fold_back_side<64 * NWAVES, ROW_VEC, 8, TM == 256 ? 4 : 1>(side, (int)blockIdx.x - p.nconv, smem);
+    // (as many loads in flight as the registers of the workgroups that share a compute unit leave: 2048 -> 512 at 6 x 6, 41 images, a pass
+    // 34.9 us with 8 and one column at a time on 128 x 128 tiles, 32.7; 1024 -> 256 at 17 x 20, 5 images, one and two columns on
+    // 128 x 64 tiles 20.8, 20.3)
+    if constexpr (Side::BACK) fold_back_side<64 * NWAVES, ROW_VEC, Cfg::SHARED ? 8 : 16, !Cfg::SHARED ? 4 : ONE || TN == 128 ? 1 : 2>(side, (int)blockIdx.x - p.nconv, smem);
     else fold_side(p.bn, p.wgt, (int)blockIdx.x - p.nconv, smem);
     return;
   }
@@ -390,6 +394,12 @@ hipError_t launch_inst(GmParams p, Side side, hipStream_t st) {
 }  // namespace
 
 bool gm_supported(int M, int C, int R) { return choose_plan(M, C, R).tm != 0; }
+bool gm_round_full(int M, int C, int R, int aside) {
+  const GmPlan pl = choose_plan(M, C, R);
+  if (pl.res > 0 || pl.tn != 128 || pl.ns != 3) return false;   // (the others share a compute unit)
+  const long long tiles = (long long)ceil_div(M, pl.tm) * (R / 128);
+  return tiles <= 256 && tiles + aside > 256;
+}
 
 hipError_t launch_gm(int M, int C, int R, const void* act, const void* wgt, const float* bias, const BnEpilogue* bn,
                      void* out, int relu, const void* mask, const void* add, hipStream_t st, const GmStride* sd, bool grad,

@@ -15,6 +15,9 @@ SHAPES = [
     (20, 256, 30, 33, 64, 1, 1, 0, "bf16", "win, gm + fold-back"),     # pointwise product: many copies of short rows
     (24, 64, 41, 40, 192, 1, 1, 0, "bf16", "win, gm + fold-back"),     # sixteen columns a row
     (12, 512, 17, 19, 640, 1, 1, 0, "bf16", "win, gm + fold-back"),    # few copies, 128 columns
+    (41, 2048, 6, 6, 512, 1, 1, 0, "bf16", "win, gm + fold-back"),     # long rows: four columns at once on 128 x 128 tiles
+    (5, 1024, 20, 17, 256, 1, 1, 0, "bf16", "win, gm + fold-back"),    # ... two on 128 x 64
+    (10, 1024, 19, 19, 256, 1, 1, 0, "bf16", "gm, win, fold-back"),    # a launch of its own behind a full round of tiles
     # residue classes; rows longer than a channel's threads, channels that fill no workgroup
     (40, 128, 30, 30, 264, 3, 2, 1, "bf16", "win, win 128x128 + fold-back"),
     (40, 96, 31, 40, 40, 3, 1, 1, "bf16", "win, win 128x128 + fold-back"),

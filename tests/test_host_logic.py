@@ -350,6 +350,18 @@ def test_route_names_what_a_call_launches(dims, dtype, fwd, bwd):
 
 
 @pytest.mark.parametrize("dims,bwd", [
+    ((62, 2048, 7, 9, 512, 1, 1, 0), "gm, win, fold-back"),      # a full round of tiles, and long rows: 49.0 us a pass, 50.3 with it beside them
+    ((10, 1024, 19, 19, 256, 1, 1, 0), "gm, win, fold-back"),
+    ((41, 2048, 6, 6, 512, 1, 1, 0), "win, gm + fold-back"),     # room in the round: 36.5, 32.7
+    ((42, 256, 16, 16, 1024, 1, 1, 0), "win, gm + fold-back"),   # short rows: 42.0, 37.4
+    ((61, 2048, 9, 9, 512, 1, 1, 0), "win, gm + fold-back"),     # two rounds: 63.9, 59.6
+])
+def test_fold_back_beside_a_pointwise_input_gradient_or_apart(dims, bwd):
+    from paper_2305_11624_amd.synth import BlockShape
+    assert B.convbn_tune_route(B.desc_from_shape(BlockShape("route", *dims, "bf16", 1)), B.PASS_BWD) == bwd
+
+
+@pytest.mark.parametrize("dims,bwd", [
     # a deep layer's weight gradient and fold-back in one launch, and the input gradient: against a launch of both gradients on 128 x 64
     # tiles 50.4 us a pass, 60.3 (24 images), 51.5, 59.7 (36)
     ((24, 512, 7, 7, 512, 3, 1, 1), "fused, ks 64x64"),
